@@ -269,36 +269,84 @@ __global__ __launch_bounds__(256) void quantize_e4m3_kernel(const T* __restrict_
   }
 }
 
-// ---- merge of per-chunk softmax statistics -------------------------------------------
+// ---- merge of per-tile softmax statistics ----------------------------------------------
 
-__global__ __launch_bounds__(256) void finalize_kernel(const float* __restrict__ part,
-                                                       const float* __restrict__ zy, int nchunks,
-                                                       int64_t Ncap, const int32_t* __restrict__ len,
-                                                       const int32_t* __restrict__ cu, int R, int T,
-                                                       float* __restrict__ logp, float* __restrict__ lse,
-                                                       float* __restrict__ ent) {
+// One workgroup per 64 slots (one per lane); its sixteen wavefronts each merge every sixteenth vocabulary tile,
+// kFinBatch tiles at a time, and the sixteen results are merged in a fixed order.  The kernel reads
+// 8 bytes (12 with entropy) per token and vocabulary tile once and is bound by those reads; what it has to avoid is a
+// chain of dependent round trips: with one thread per slot and a serial loop over the tiles (two loops, in fact:
+// maximum, then sums) it took 438 us for 120 tokens and 676 us for 41 k tokens at V = 151936 (0.3 TB/s), now 11 us
+// and 58 us.  Sixteen wavefronts with 2 x 8 loads in flight each keep 64 KB per workgroup outstanding, enough
+// for one workgroup per compute unit to run at memory speed when there are few tokens.
+constexpr int kFinWaves = 16, kFinBatch = 8;
+
+__global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* __restrict__ part,
+                                                                  const float* __restrict__ zy, int ntiles,
+                                                                  int64_t Ncap, const int32_t* __restrict__ len,
+                                                                  const int32_t* __restrict__ cu, int R, int T,
+                                                                  float* __restrict__ logp, float* __restrict__ lse,
+                                                                  float* __restrict__ ent) {
+  __shared__ float red[kFinWaves][3][64];
   const int64_t N = (int64_t)R * T;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= N) return;
-  const int r = (int)(i / T);
-  const int t = (int)(i - (int64_t)r * T);
-  const int n = min(max(len[r], 0), T);
-  float o_lp = 0.f, o_lse = 0.f, o_ent = 0.f;
-  if (t < n) {
-    const int64_t k = cu[r] + t;
-    const size_t plane = (size_t)nchunks * Ncap;
-    float m = -__builtin_huge_valf();
-    for (int c = 0; c < nchunks; ++c) m = fmaxf(m, part[(size_t)c * Ncap + k]);
-    float s = 0.f, tt = 0.f;
-    for (int c = 0; c < nchunks; ++c) {
-      const size_t idx = (size_t)c * Ncap + k;
-      const float mc = part[idx];
-      if (mc == -__builtin_huge_valf()) continue;
-      const float w = __builtin_amdgcn_exp2f((mc - m) * kLog2e);
-      s = fmaf(part[plane + idx], w, s);
-      if (ent) tt = fmaf(part[2 * plane + idx], w, tt);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  int64_t k = -1;   // compact row of this slot, -1 on padding
+  if (i < N) {
+    const int r = (int)(i / T);
+    const int t = (int)(i - (int64_t)r * T);
+    if (t < min(max(len[r], 0), T)) k = cu[r] + t;
+  }
+  // statistics (m, s, t) of a union of tiles, each scaled to the running maximum; exp2(-inf) = 0 drops empty ones
+  float m = -__builtin_huge_valf(), s = 0.f, tt = 0.f;
+  if (k >= 0) {
+    const size_t plane = (size_t)ntiles * Ncap;
+    const float* const p = part + k;
+    for (int c0 = w; c0 < ntiles; c0 += kFinWaves * kFinBatch) {
+      float mc[kFinBatch], sc[kFinBatch], tc[kFinBatch];
+#pragma unroll
+      for (int u = 0; u < kFinBatch; ++u) {
+        const int c = c0 + u * kFinWaves;
+        const bool in = c < ntiles;
+        mc[u] = in ? p[(size_t)c * Ncap] : -__builtin_huge_valf();
+        sc[u] = in ? p[plane + (size_t)c * Ncap] : 0.f;
+        tc[u] = in && ent ? p[2 * plane + (size_t)c * Ncap] : 0.f;
+      }
+      float mn = m;
+#pragma unroll
+      for (int u = 0; u < kFinBatch; ++u) mn = fmaxf(mn, mc[u]);
+      const float ms = mn == -__builtin_huge_valf() ? 0.f : mn;
+      const float old = __builtin_amdgcn_exp2f((m - ms) * kLog2e);
+      s *= old;
+      tt *= old;
+#pragma unroll
+      for (int u = 0; u < kFinBatch; ++u) {
+        const float f = __builtin_amdgcn_exp2f((mc[u] - ms) * kLog2e);
+        s = fmaf(sc[u], f, s);
+        tt = fmaf(tc[u], f, tt);
+      }
+      m = mn;
     }
-    o_lse = m + __builtin_amdgcn_logf(s) * kLn2;
+  }
+  red[w][0][lane] = m;
+  red[w][1][lane] = s;
+  red[w][2][lane] = tt;
+  __syncthreads();
+  if (w != 0 || i >= N) return;
+  float o_lp = 0.f, o_lse = 0.f, o_ent = 0.f;
+  if (k >= 0) {
+    float mx = -__builtin_huge_valf();
+#pragma unroll
+    for (int q = 0; q < kFinWaves; ++q) mx = fmaxf(mx, red[q][0][lane]);
+    const float ms = mx == -__builtin_huge_valf() ? 0.f : mx;
+    s = 0.f;
+    tt = 0.f;
+#pragma unroll
+    for (int q = 0; q < kFinWaves; ++q) {
+      const float f = __builtin_amdgcn_exp2f((red[q][0][lane] - ms) * kLog2e);
+      s = fmaf(red[q][1][lane], f, s);
+      tt = fmaf(red[q][2][lane], f, tt);
+    }
+    o_lse = mx + __builtin_amdgcn_logf(s) * kLn2;
     o_lp = zy[k] - o_lse;
     o_ent = o_lse - tt / s;
   }
@@ -453,12 +501,12 @@ int device_compute_units() {
   return n;
 }
 
-hipError_t launch_finalize(const float* part, const float* zy, int nchunks, int64_t Ncap,
+hipError_t launch_finalize(const float* part, const float* zy, int ntiles, int64_t Ncap,
                            const int32_t* len, const int32_t* cu_len, int R, int T, float* logp,
                            float* lse, float* entropy, hipStream_t s) {
   const int64_t N = (int64_t)R * T;
-  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, part, zy,
-                     nchunks, Ncap, len, cu_len, R, T, logp, lse, entropy);
+  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 63) / 64)), dim3(64 * kFinWaves), 0, s, part, zy,
+                     ntiles, Ncap, len, cu_len, R, T, logp, lse, entropy);
   return hipGetLastError();
 }
 
