@@ -2,6 +2,8 @@
 // by the unit test of the mapping).
 #pragma once
 
+#include <stdint.h>
+
 #ifdef LMHEAD_TILE_MAP_HOST
 #define LMHEAD_HD
 #else
@@ -14,24 +16,35 @@ namespace lmhead {
 // Workgroup -> tile mapping that keeps L2 traffic local to an XCD.
 //
 // The chip dispatches workgroup i of a 1-D grid to XCD i % 8, and each XCD has a private L2.
-// A work grid of X x Y items (x selects the A-side operand slab, y the B-side slab) is cut
-// into eight contiguous y-ranges, one per XCD; inside its range an XCD walks blocks of
-// bx x by items (x fastest), so the 32 workgroups it runs at a time cover a compact block and
-// share bx + by operand slabs instead of fetching 64.  Returns false for workgroups beyond the
-// work (the grid is sized for the largest possible Y).
+// A work grid of X x Y items (x selects the A-side operand slab, y the B-side slab) is shared out so
+// that every XCD gets the same number of items, give or take one:
+//  - the first 8 floor(Y / 8) values of y in eight contiguous ranges, one per XCD.  Inside its range an XCD
+//    walks blocks of bx x by items (x fastest), so the 32 workgroups it runs at a time cover a compact block and
+//    share bx + by operand slabs instead of fetching 64;
+//  - the items of the remaining r = Y % 8 values of y in eight contiguous pieces of the order "y fastest, then x":
+//    neighbours share the x slab, and all of them the r slabs of y.
+// (Cutting Y into eight ranges of ceil(Y / 8) leaves XCDs idle when Y is small: at 41 token blocks one of the
+// eight has nothing to do, at one token block seven.  Forward of 120 tokens x 151936: 838 -> 182 us; the 8x8x256
+// step, 41 blocks: 19.2 -> 18.4 ms; 160 blocks or more: no change.)
+// Returns false for workgroups beyond the work (the grid is sized for the largest possible Y).
 constexpr int kNumXcd = 8;
 LMHEAD_HD inline bool xcd_tile_coords(int wg, int X, int Y, int bx, int by, int& x, int& y) {
   const int xcd = wg % kNumXcd;
   const int j = wg / kNumXcd;
-  const int y_per = (Y + kNumXcd - 1) / kNumXcd;
-  const int y_base = xcd * y_per;
-  const int y_cnt = min(y_per, Y - y_base);
-  if (y_cnt <= 0) return false;
+  const int y_per = Y / kNumXcd;
+  if (j >= y_per * X) {
+    const int rest = Y - y_per * kNumXcd;
+    const int64_t items = (int64_t)rest * X;
+    const int i = (int)(items * xcd / kNumXcd) + (j - y_per * X);
+    if (i >= (int)(items * (xcd + 1) / kNumXcd)) return false;
+    x = i / rest;
+    y = y_per * kNumXcd + (i - x * rest);
+    return true;
+  }
   const int per_yblk = X * by;
   const int yb = j / per_yblk;
   int r = j - yb * per_yblk;
-  const int h = min(by, y_cnt - yb * by);
-  if (h <= 0 || r >= X * h) return false;
+  const int h = min(by, y_per - yb * by);
   const int nfull = X / bx;
   const int full_items = nfull * bx * h;
   int yin;
@@ -46,14 +59,14 @@ LMHEAD_HD inline bool xcd_tile_coords(int wg, int X, int Y, int bx, int by, int&
     yin = r / tw;
     x = nfull * bx + (r - yin * tw);
   }
-  y = y_base + yb * by + yin;
+  y = xcd * y_per + yb * by + yin;
   return true;
 }
-// Grid size that covers every item for any Y <= Y_cap under the mapping above.
-inline unsigned xcd_grid_size(int X, long long Y_cap, int by) {
-  const long long y_per = (Y_cap + kNumXcd - 1) / kNumXcd;
-  const long long yblks = (y_per + by - 1) / by;
-  return (unsigned)(kNumXcd * yblks * by * X);
+// Grid size that covers every item for any Y <= Y_cap under the mapping above (an XCD's share grows with Y and
+// does not depend on the block shape).
+inline unsigned xcd_grid_size(int X, long long Y_cap, int /*by*/) {
+  const long long rest = Y_cap % kNumXcd;
+  return (unsigned)(kNumXcd * (Y_cap / kNumXcd * X + (rest * X + kNumXcd - 1) / kNumXcd));
 }
 
 }  // namespace lmhead

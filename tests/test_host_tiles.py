@@ -1,0 +1,17 @@
+"""CPU-only checks of the rules that share work out over the chip."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _run_host_check(tmp_path, name):
+    exe = tmp_path / name
+    subprocess.run(["g++", "-O2", "-std=c++17", "-o", str(exe), os.path.join(ROOT, "tests", "host", name + ".cpp")],
+                   check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and "bad=0" in r.stdout, r.stdout + r.stderr
+
+
+def test_tile_walk_is_balanced_over_the_xcds(tmp_path):
+    _run_host_check(tmp_path, "tile_balance_check")
