@@ -24,45 +24,46 @@ namespace {
 
 constexpr int kKvMapBx = 4, kKvMapBy = 4;
 
-// Compute units of the current device (256 on MI355X); asked once.
-int compute_units() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v >= kNumXcd)
-      cus = v;
-    else
-      cus = 256;
-  }
-  return cus;
+// Tile edge of the KV kernels: 64, 128 or 256, four wavefronts each.  The smaller the edge, the more operand bytes per
+// flop (edge 256 is the only one that the vector L1 can feed at full matrix rate), but the more workgroups there are
+// to fill the chip with, and the shorter a tile's serial K loop and epilogue are.  Spectral projection, d = 1024, us:
+//     n            256   1024   2048   4096   8192  12000  16384  65536
+//     edge 64     11.5   12.7   14.0   20.2   36.8   50.6   59.9    252
+//     edge 128    14.3   15.3   15.7   17.2   25.3   35.9   44.5    179
+//     edge 256    29.4   30.5   30.8   31.9   34.5   37.0   42.2    143
+// (fp32, n = 1024: 26.8 / 66.8 / 239; n = 4096: 80 / 78 / 241.)  So: the smallest edge whose tiles run in one round, two to
+// a compute unit.  The reconstruction's tiles differ in length, which leaves its rounds more ragged, and more
+// and smaller tiles even them out: edge 128 up to four rounds (n = 16411, 32768, 65536: 32.8 / 51.6 / 95.5 against
+// 39.0 / 54.6 / 91.8 with edge 256).
+int tile_edge(int mode, int M, int64_t Nn) {
+  const int64_t room = 2 * (int64_t)device_compute_units();
+  auto tiles = [&](int edge) { return (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge); };
+  if (tiles(64) <= room) return 64;
+  return tiles(128) <= (mode == 2 ? 4 : 1) * room ? 128 : 256;
 }
-
-// Tile edge of the KV kernels.  256: one workgroup per compute unit (all of LDS).  128 (build with
-// -DKV_TILE=128): half the LDS and a quarter of the accumulators per workgroup, so two workgroups
-// share a compute unit and one can run its main loop while the other is in its prologue or
-// epilogue, at twice the operand traffic per flop.  Measured on the 262144 x 1024 stream, 128 is
-// 25-40 % slower (714 / 818 / 623 us against 562 / 570 / 500 us for the three kernels), so 256 it is.
-#ifndef KV_TILE
-#define KV_TILE 256
-#endif
-constexpr int kKvTileEdge = KV_TILE;
-constexpr int kKvWgPerCu = kKvTileEdge == 256 ? 1 : 2;
+// Workgroups of one tile edge that share a compute unit (bound by LDS: five slots of edge x 128 bytes each).
+constexpr int wg_per_cu(int edge) { return 256 / edge; }
 
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
-template <typename E, bool kMask>
-using KvTile = GemmTile<E, kKvTileEdge, kKvTileEdge, 2, 2, /*kLeadB=*/true, kMask>;
+template <typename E, int Edge, bool kMask>
+using KvTile = GemmTile<E, Edge, Edge, 2, 2, /*kLeadB=*/true, kMask>;
 
 // One output tile; `wg` is the tile's position in the XCD-aware walk.
-template <typename E, int Mode>
+template <typename E, int Edge, int Mode>
 __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
-  using G = KvTile<E, Mode == 2>;
+  using G = KvTile<E, Edge, Mode == 2>;
   constexpr int ESZ = Elem<E>::size;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
   const int ntiles = (int)((a.Nn + G::BN - 1) / G::BN);
   int mt, nt;
   if (!xcd_tile_coords(wg, mtiles, ntiles, kKvMapBx, kKvMapBy, mt, nt)) return;
+  if constexpr (Mode == 2) {
+    // Token tiles come in order of falling step count: they are dealt out to the XCDs in turn.  (In contiguous ranges
+    // the first XCD had the longest eighth of the tokens: 262144 tokens, retain rate 0.44: 491 us, now 392.)
+    const int per = ntiles / kNumXcd;
+    if (nt < per * kNumXcd) nt = nt % per * kNumXcd + nt / per;
+  }
   const int64_t n0 = (int64_t)nt * G::BN;
   const int m0 = mt * G::BM;
   const int64_t pitchA = a.ldA * ESZ;
@@ -189,9 +190,10 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
 #pragma unroll
       for (int u = 0; u < RB; ++u) {
         int64_t row = __builtin_amdgcn_readlane(my_row, jg * RPW + (i0 + u) * RPI);
-        if constexpr (RPI == 2) {
-          const int r1 = __builtin_amdgcn_readlane(my_row, jg * RPW + (i0 + u) * RPI + 1);
-          row = h ? r1 : row;
+#pragma unroll
+        for (int hh = 1; hh < RPI; ++hh) {
+          const int rh = __builtin_amdgcn_readlane(my_row, jg * RPW + (i0 + u) * RPI + hh);
+          row = h == hh ? rh : row;
         }
         orow[u] = m < a.M ? row : -1;
       }
@@ -223,28 +225,37 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
 }
 
 // Tiles here are short (d_kv / 64 K-steps or fewer), so the workgroups are persistent: as many as
-// are resident at a time, each taking every gridDim.x-th tile of the walk, which saves a workgroup
+// are resident at a time (wg_per_cu of them on each compute unit), each taking every gridDim.x-th tile of the walk, which saves a workgroup
 // launch per tile.  gridDim.x is a multiple of 8, so a tile stays on the XCD that the walk meant it for.
-template <typename E, int Mode>
-__global__ __launch_bounds__(256) void kv_gemm_kernel(KvGemmArgs a) {
+template <typename E, int Edge, int Mode>
+__global__ __launch_bounds__(256, wg_per_cu(Edge)) void kv_gemm_kernel(KvGemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Mode>(a, wg, smem);
+  for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Edge, Mode>(a, wg, smem);
 }
 
-template <typename E, int Mode>
-hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
-  using G = KvTile<E, Mode == 2>;
+template <typename E, int Edge, int Mode>
+hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
+  using G = KvTile<E, Edge, Mode == 2>;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
   const int64_t ntiles = (a.Nn + G::BN - 1) / G::BN;
   if (a.accumulate && (Mode == 2 || a.out_f || !a.out_e)) return hipErrorInvalidValue;
   KvGemmArgs b = a;
   b.walk_len = (int)xcd_grid_size(mtiles, ntiles, kKvMapBy);
-  const unsigned resident = (unsigned)compute_units() / kNumXcd * kNumXcd * kKvWgPerCu;   // LDS-bound
+  const unsigned resident = (unsigned)device_compute_units() / kNumXcd * kNumXcd * wg_per_cu(Edge);   // LDS-bound
   const dim3 grid(b.walk_len < (int)resident ? (unsigned)b.walk_len : resident);
-  hipError_t e = allow_lds<kv_gemm_kernel<E, Mode>>(G::LDS_BYTES);
+  hipError_t e = allow_lds<kv_gemm_kernel<E, Edge, Mode>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((kv_gemm_kernel<E, Mode>), grid, dim3(G::NT), G::LDS_BYTES, s, b);
+  hipLaunchKernelGGL((kv_gemm_kernel<E, Edge, Mode>), grid, dim3(G::NT), G::LDS_BYTES, s, b);
   return hipGetLastError();
+}
+
+template <typename E, int Mode>
+hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
+  switch (tile_edge(Mode, a.M, a.Nn)) {
+    case 64: return launch_tiles<E, 64, Mode>(a, s);
+    case 128: return launch_tiles<E, 128, Mode>(a, s);
+    default: return launch_tiles<E, 256, Mode>(a, s);
+  }
 }
 
 template <typename E>

@@ -498,7 +498,9 @@ struct GemmTile {
       static_assert(NSUB == 2 && FC == 1 && TM == TN && TM % 2 == 0, "two regions per sub-step");
       constexpr int RMMAS = TM * TN / 2;     // MFMAs per region
       constexpr int RREADS = TM;             // fragment reads per region
-      static_assert(RREADS + LD_REGION <= RMMAS, "region pattern");
+      // loads start behind the reads where a region is long enough, else they share its last MFMAs
+      constexpr int LOAD0 = RREADS + LD_REGION <= RMMAS ? RREADS : RMMAS - LD_REGION;
+      static_assert(LOAD0 >= 0 && RREADS <= RMMAS, "region pattern");
       auto read_a1 = [&](const char* sa, int sub, int buf, int i) {
         const int r = rA0 + i * NB;
         fa[buf][i][0] = *reinterpret_cast<const u32x4_t*>(sa + row_off(r) + (((LG * sub + grp) ^ swz(r)) << 4));
@@ -522,7 +524,7 @@ struct GemmTile {
       // the loads [q0, q0 + LD_REGION) of operand `lx` for K-step `lks` into ring slot `lslot`.
       auto region = [&](int buf, int i0, bool rd, bool rx, const char* src, int sub, int rbuf, bool ld, bool lx, int lks,
                         int lslot, int q0) {
-        constexpr int kGap = (RMMAS - RREADS) / LD_REGION;
+        constexpr int kGap = (RMMAS - LOAD0) / LD_REGION;
 #pragma unroll
         for (int idx = 0; idx < RMMAS; ++idx) {
           const int i = i0 + idx / TN, j = idx % TN;
@@ -530,8 +532,8 @@ struct GemmTile {
           if (rd && idx < RREADS) {
             if (rx == !kLeadB) read_a1(src, sub, rbuf, idx); else read_b1(src, sub, rbuf, idx);
           }
-          if (ld && idx >= RREADS && (idx - RREADS) % kGap == 0 && (idx - RREADS) / kGap < LD_REGION) {
-            const int q = q0 + (idx - RREADS) / kGap;
+          if (ld && idx >= LOAD0 && (idx - LOAD0) % kGap == 0 && (idx - LOAD0) / kGap < LD_REGION) {
+            const int q = q0 + (idx - LOAD0) / kGap;
             if (lx == !kLeadB) issue_a1(lks, lslot, q); else issue_b1(lks, lslot, q);
           }
           __builtin_amdgcn_sched_barrier(0);

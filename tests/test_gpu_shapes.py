@@ -25,3 +25,45 @@ def test_softmax_merge_over_vocabulary_tiles(tiles, T):
     o_lp, o_lse, o_ent = O.lmhead_logprob_fwd(wl.as_f64(inp["H"]), wl.as_f64(inp["W"]), inp["tok"], inp["lens"], cfg.T)
     for got, want in ((logp, o_lp), (lse, o_lse), (ent, o_ent)):
         assert np.abs(np64(got) - want).max() <= 1e-4
+
+
+def _kv_edge(mode, d, n, cus):
+    """Tile edge that the KV products take (the rule of dynakv_gemm.hip)."""
+    tiles = lambda e: -(-d // e) * -(-n // e)  # noqa: E731
+    return 64 if tiles(64) <= 2 * cus else 128 if tiles(128) <= (8 if mode == 2 else 2) * cus else 256
+
+
+# token counts at the edges of the rule that picks a tile edge, of the tiles themselves, and of the XCD deal-out
+@pytest.mark.parametrize("dtype,d,n", [
+    ("bf16", 64, 1), ("bf16", 64, 63), ("bf16", 192, 65), ("bf16", 320, 6553), ("bf16", 320, 6593),
+    ("bf16", 448, 16384), ("bf16", 448, 16400), ("bf16", 448, 65537), ("f32", 64, 64), ("f32", 192, 129),
+    ("f32", 320, 6600), ("f32", 448, 16390)])
+def test_kv_products_over_tile_edges(dtype, d, n):
+    import torch
+    import workloads.dynakv as kv
+    from oracle import dynakv_oracle as K
+    from tests.harness import KvProblem
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d, dtype=dtype)
+    inp = kv.kv_inputs(cfg)
+    kp = KvProblem(cfg, inp)
+    xt, k, m, _ = kp.gate(cfg.tau)
+    off, packed = kp.store(xt, k)
+    xbar = kp.reconstruct(packed, int(off[-1].item()), off, k)
+    assert kp.check() == 0
+    # every tile's first, last and middle rows, and the rows next to a tile boundary
+    e0, e2 = _kv_edge(0, d, n, cus), _kv_edge(2, d, n, cus)
+    rows = np.unique(np.clip([v for e in (e0, e2) for c in (0, 1, n // e // 2, n // e) for v in
+                              (c * e - 1, c * e, c * e + e // 2, n - 1)], 0, n - 1))
+    f = wl.as_f64
+    o = K.gate(f(inp["x"][rows]), f(inp["U"]), f(inp["W"]), inp["b"], cfg.tau, store_dtype=dtype)
+    # one bf16 rounding of x~ may fall the other way; the mask moves by the logit that such a step moves (see
+    # test_gpu_dynakv.py, whose bounds these are); fp32: sums of d products, d * 2^-24 relative
+    ulp, tol_m = (2.0 ** -7, 5e-3) if dtype == "bf16" else (2.0 ** -22, 1e-4)
+    got = np64(xt)[rows]
+    assert np.all(np.abs(got - o["xt"]) <= ulp * np.abs(o["xt"]) + 1e-6 * np.abs(o["xt"]).max())
+    assert np.abs(np64(m)[rows] - o["m"]).max() <= tol_m
+    # the reconstruction of what the device stored
+    kk = k.cpu().numpy()[rows]
+    kept = np.where(np.arange(d)[None, :] < kk[:, None], got, 0.0)
+    assert rel_fro(np64(xbar)[rows], kept @ f(inp["U_inv"])) <= (4e-3 if dtype == "bf16" else 1e-5)
