@@ -239,6 +239,7 @@ struct GemmTArgs {
   int64_t part_ld;     // rows of part_ld floats without the row map, and launch_splitk_reduce forms out
   int64_t part_slice;  // from the slices.  part_slice = floats per slice.  Required when ksplit > 1.
   bool part_accumulate;
+  int edge;            // workgroup tile edge: 64, 128 or 256 (n_tiles_cap stays in units of kTile)
 };
 
 // out[row(n)][m] (+)= sum_s part[s][n][m] for n < n_valid, m < M, slices summed in order.  With a row map:

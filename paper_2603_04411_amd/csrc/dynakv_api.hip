@@ -259,7 +259,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   }
 
   // Parameter gradients: contractions over the tokens, out[row][col] = sum_t B[row][t] A[col][t] with
-  // token-contiguous copies of both operands, cut into ksplit slices of the token range.
+  // token-contiguous copies of both operands, cut into ksplit slices of the token range (one: stored directly).
   auto param_grad = [&](const void* rows_src, int64_t ld_rows, const void* cols_src, int kind, float* out) -> int {
     {
       TimedLaunch tl(13, s);
@@ -277,14 +277,22 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
     ta.n_tiles_cap = L.dp / kTile;
     ta.hdr = hdr;
     ta.ksplit = L.ksplit;
-    ta.part = static_cast<float*>(at(L.part));
-    ta.part_ld = d;
-    ta.part_slice = (int64_t)d * d;
+    ta.edge = L.edge;
+    if (L.ksplit > 1) {
+      ta.part = static_cast<float*>(at(L.part));
+      ta.part_ld = d;
+      ta.part_slice = (int64_t)d * d;
+    } else {
+      ta.out = out;
+      ta.ldo = d;
+      ta.accumulate = accum;
+    }
     {
       TimedLaunch tl(kind, s);
       LM_TRY(launch_gemm_t(dt, ta, s, 2));
     }
-    LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, out, accum, s));
+    if (L.ksplit > 1)
+      LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, out, accum, s));
     return LMHEAD_OK;
   };
   // dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]

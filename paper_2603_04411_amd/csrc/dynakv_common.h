@@ -60,7 +60,7 @@ struct KvBwdLayout {
   int esz;
   int64_t n, d, ncap, dp, ldT;
   int64_t ldK;       // pitch (elements) of the token-contiguous copies: ncap + one 128-byte line
-  int ksplit;        // slices of the contraction over tokens per output tile of dW / dU
+  int edge, ksplit;  // tile edge of dW / dU and slices of their contraction over the tokens
   int nblk;          // workgroups of the mask backward kernel = rows of the db partial sums
   size_t hdr, Wp, Up, WT, logits, gl, gxt, T1, T2, part, dbpart, total;
 };
@@ -78,15 +78,28 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.dp = (int64_t)round_up((size_t)L.d, kTile);
   L.ldT = L.d + 128 / L.esz;
   L.ldK = L.ncap + 128 / L.esz;
+  // Tile edge and slices of the contraction over the tokens: as many slices as give one workgroup per compute unit,
+  // on the largest edge whose slices then keep 16 K-steps (of 128 bytes), else edge 64 with at least 2 each.
+  // dW alone / whole backward call, us, bf16 unless said, with the choice in brackets:
+  //     n x d           edge 256         edge 128          edge 64          (slices giving 256 workgroups, or the best)
+  //     32768 x 1024    [72.6 / 611]     99.6 / 638        208 / 867
+  //     8192 x 2048     [63.4 / 528]     79.2 / 555        113 / 626
+  //     4096 x 1024     23.4 / 177       [18.3 / 156]      30.6 / 181
+  //     512 x 1024      17.4 / 117       11.3 / 100        [9.8 / 93]
+  //     8192 x 256      18.0 / 115       11.5 / 102        [9.6 / 92]
+  //     300 x 128 fp32  20.6 / 83        9.9 / 63          [7.6 / 59]
   {
-    // (d / 256)^2 output tiles; the contraction over the tokens is cut so that about one workgroup
-    // per compute unit runs, each slice keeping at least 8 K-steps
-    const int64_t tiles = (L.dp / kTile) * (L.dp / kTile);
     const int64_t ksteps = L.ncap * L.esz / 128;
-    int64_t ks = (256 + tiles - 1) / tiles;
-    if (ks > ksteps / 8) ks = ksteps / 8;
-    if (ks < 1) ks = 1;
-    L.ksplit = (int)ks;
+    for (int edge : {256, 128, 64}) {
+      const int64_t side = (L.d + edge - 1) / edge;
+      int64_t ks = (256 + side * side - 1) / (side * side);
+      const bool last = edge == 64;
+      if (last && ks > ksteps / 2) ks = ksteps / 2;
+      if (ks < 1) ks = 1;
+      L.edge = edge;
+      L.ksplit = (int)ks;
+      if (last || ksteps / ks >= 16) break;
+    }
   }
   {
     const int64_t blocks = (L.n + 3) / 4;

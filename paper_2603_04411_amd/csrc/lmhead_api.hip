@@ -278,6 +278,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     ha.accumulate = c > 0;
     ha.n_tiles_cap = L.Ncap / kTile;
     ha.hdr = hdr;
+    ha.edge = kTile;
     ha.ksplit = L.ksplit;
     ha.part = (L.ksplit > 1 || dh16) ? w.at<float>(L.dHpart) : nullptr;
     ha.part_ld = L.dp;
@@ -312,6 +313,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     wa.ldo = desc->d;
     wa.accumulate = (desc->flags & LMHEAD_FLAG_ACCUM_DW) != 0;
     wa.hdr = hdr;
+    wa.edge = kTile;
     // Every output tile is one workgroup and the compute units take them a round at a time.  The vocabulary
     // tiles of this chunk that would start a mostly empty last round (with d / 256 tiles along d, 16 of them
     // fill the 256 compute units at d = 4096; a chunk of 18 leaves 2) are launched apart, their contraction

@@ -32,9 +32,9 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // leading (within 0.5 % either way).
 constexpr bool kLeadFwd = true, kLeadDz = true, kLeadDh = true, kLeadDw = true;
 
-// 256 x 256 workgroup tile, four wavefronts (2 x 2) of 128 x 128.
-template <typename E, bool kLeadB = false>
-using Tile = GemmTile<E, 256, 256, 2, 2, kLeadB>;
+// Workgroup tile, four wavefronts (2 x 2).
+template <typename E, bool kLeadB = false, int Edge = 256>
+using Tile = GemmTile<E, Edge, Edge, 2, 2, kLeadB>;
 
 // Block shape of the XCD-local tile walk (see xcd_tile_coords): 4 x 4 work items.
 constexpr int kMapBx = 4, kMapBy = 4;
@@ -573,9 +573,9 @@ __global__ __launch_bounds__(Tile<E>::NT) void dz_kernel(DzArgs a) {
 // Role: 0 = dH (contracts over a vocabulary chunk), 1 = dW (contracts over the valid tokens), 2 = a
 // parameter gradient of the KV gate (contracts over the tokens of a stream).  The code is the same; the
 // parameter only gives the uses distinct kernel names in profiles (and picks the lead operand).
-template <typename E, int Role>
-__global__ __launch_bounds__(Tile<E>::NT) void gemm_t_kernel(GemmTArgs a) {
-  using G = Tile<E, (Role == 0 ? kLeadDh : kLeadDw)>;
+template <typename E, int Role, int Edge>
+__global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTArgs a) {
+  using G = Tile<E, (Role == 0 ? kLeadDh : kLeadDw), Edge>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nv = a.hdr->nv;
   const int64_t n_lim = a.n_from_nv ? (int64_t)nv : a.n_limit;
@@ -607,21 +607,24 @@ __global__ __launch_bounds__(Tile<E>::NT) void gemm_t_kernel(GemmTArgs a) {
     offB[q] = (uint32_t)(row * pitchB) + G::ld_byte(row);
   }
 
-  // The wave streams out tile columns (output rows) wave, wave + 4, ... of each phase of the epilogue.
-  // Lane 32 p + i fetches the output row of iteration i of phase p now; the epilogue reads it with
-  // readlane instead of one dependent global load per row.
-  constexpr int JG = 64 / G::NB;                  // column blocks per wave per phase (64 columns)
+  // The fp32 tile leaves through LDS as [n][m] rows, as many tile columns per phase as fit: CH lanes of 16 bytes per
+  // row, RPI rows per wavefront instruction, RPW rows per wave and phase (rows wave, wave + 4, ... in units of RPI).
+  // The output row that lane RPW p + RPI i + h needs in instruction i of phase p is fetched now; the epilogue reads
+  // it with readlane instead of one dependent global load per row.
+  constexpr int JG = 64 / G::NB < G::TN ? 64 / G::NB : G::TN;   // column blocks per wave per phase
+  constexpr int NPH = G::TN / JG;
   constexpr int NCOL = G::WGN * JG * G::NB;       // tile columns (n) staged per phase
-  constexpr int ROWS_PER_WAVE = NCOL / G::NWAVES; // per phase
-  static_assert(ROWS_PER_WAVE * (G::TN / JG) == 64, "one output row index per lane");
-  int my_row;
+  constexpr int CH = G::BM * 4 / 16;              // lanes per staged row
+  constexpr int RPI = 64 / CH;                    // staged rows per wavefront instruction
+  constexpr int RPW = NCOL / G::NWAVES;           // staged rows per wave and phase
+  constexpr int IPW = RPW / RPI;                  // instructions per wave and phase
+  static_assert(G::TN % JG == 0 && 64 % CH == 0 && RPW % RPI == 0 && RPW * NPH <= 64, "one output row index per lane");
+  int my_row = -1;
   {
-    const int p = G::lane() / ROWS_PER_WAVE, i = G::lane() % ROWS_PER_WAVE;
-    const int r = G::wave() + G::NWAVES * i;
+    const int p = G::lane() / RPW, i = G::lane() % RPW;
+    const int r = (G::wave() + G::NWAVES * (i / RPI)) * RPI + i % RPI;
     const int64_t n = n0 + (r / (JG * G::NB)) * G::WN + p * (JG * G::NB) + r % (JG * G::NB);
-    int64_t row = -1;
-    if (n < n_lim) row = a.part ? n : (a.rowmap ? (int64_t)a.rowmap[n] : a.row_base + n);
-    my_row = (int)row;
+    if (p < NPH && n < n_lim) my_row = (int)(a.part ? n : (a.rowmap ? (int64_t)a.rowmap[n] : a.row_base + n));
   }
   float* const outp = a.part ? a.part + (size_t)slice * a.part_slice : a.out;
   const int64_t ldo = a.part ? a.part_ld : a.ldo;
@@ -632,18 +635,16 @@ __global__ __launch_bounds__(Tile<E>::NT) void gemm_t_kernel(GemmTArgs a) {
   G::run(acc, static_cast<const char*>(a.A) + (int64_t)m0 * pitchA + (int64_t)k_first * G::KB, offA,
          static_cast<const char*>(a.B) + n0 * pitchB + (int64_t)k_first * G::KB, offB, ksteps, smem, Role == 0 ? 3 : (Role == 1 ? 4 : 0));
 
-  // The fp32 tile leaves through LDS as [n][m] rows, so that each output row segment (BM floats
-  // = 1 KB) is read-modify-written by one wavefront instruction with 16 bytes per lane.  Rows go in
-  // batches: the LDS reads and the loads of the old values of a whole batch are issued before its
-  // first store, so the wave (alone on its SIMD) does not sit out one memory round trip per row.
+  // Rows go in batches: the LDS reads and the loads of the old values of a whole batch are issued before its
+  // first store, so a wave that is alone on its SIMD does not sit out one memory round trip per row.
   constexpr int P = G::BM * 4 + 16;               // staging row pitch in bytes
-  static_assert(NCOL * P <= G::LDS_BYTES && G::TN % JG == 0, "staging fits in LDS");
-  static_assert(G::BM * 4 / 16 == 64, "one staged row is one wavefront store");
-  const int c = G::lane();                        // 16-byte chunk of the row = 4 output columns
+  static_assert(NCOL * P <= G::LDS_BYTES, "staging fits in LDS");
+  const int h = G::lane() / CH;                   // which of the instruction's rows this lane works on
+  const int c = G::lane() % CH;                   // its 16-byte chunk of the row = 4 output columns
   const int m = m0 + c * 4;
   const bool m_ok = m < a.M;
 #pragma unroll
-  for (int jg = 0; jg < G::TN / JG; ++jg) {
+  for (int jg = 0; jg < NPH; ++jg) {
 #pragma unroll
     for (int jj = 0; jj < JG; ++jj) {
       const int j = jg * JG + jj;
@@ -657,16 +658,21 @@ __global__ __launch_bounds__(Tile<E>::NT) void gemm_t_kernel(GemmTArgs a) {
         }
     }
     lds_barrier();
-    constexpr int RB = 8;
+    constexpr int RB = IPW < 8 ? IPW : 8;
 #pragma unroll
-    for (int i0 = 0; i0 < ROWS_PER_WAVE; i0 += RB) {
+    for (int i0 = 0; i0 < IPW; i0 += RB) {
       f32x4_t v[RB], old[RB];
       f32x4_t* dst[RB];
 #pragma unroll
       for (int u = 0; u < RB; ++u) {
-        const int64_t row = __builtin_amdgcn_readlane(my_row, jg * ROWS_PER_WAVE + i0 + u);
+        int64_t row = __builtin_amdgcn_readlane(my_row, jg * RPW + (i0 + u) * RPI);
+#pragma unroll
+        for (int hh = 1; hh < RPI; ++hh) {
+          const int rh = __builtin_amdgcn_readlane(my_row, jg * RPW + (i0 + u) * RPI + hh);
+          row = h == hh ? rh : row;
+        }
         dst[u] = (row >= 0 && m_ok) ? reinterpret_cast<f32x4_t*>(outp + row * ldo + m) : nullptr;
-        v[u] = *reinterpret_cast<const f32x4_t*>(smem + (G::wave() + G::NWAVES * (i0 + u)) * P + c * 16);
+        v[u] = *reinterpret_cast<const f32x4_t*>(smem + ((G::wave() + G::NWAVES * (i0 + u)) * RPI + h) * P + c * 16);
       }
       if (accumulate) {
 #pragma unroll
@@ -678,7 +684,7 @@ __global__ __launch_bounds__(Tile<E>::NT) void gemm_t_kernel(GemmTArgs a) {
       for (int u = 0; u < RB; ++u)
         if (dst[u]) *dst[u] = v[u];
     }
-    if (jg + 1 < G::TN / JG) lds_barrier();
+    if (jg + 1 < NPH) lds_barrier();
   }
 }
 
@@ -715,23 +721,34 @@ hipError_t launch_dz(int op_dtype, int out_dtype, const DzArgs& a, hipStream_t s
   return op_dtype == LMHEAD_BF16 ? launch_dz_e<bf16_tag, bf16_tag>(a, s) : launch_dz_e<f32_tag, f32_tag>(a, s);
 }
 
-template <typename E, int Role>
-static hipError_t launch_gemm_t_impl(const GemmTArgs& a, hipStream_t s) {
-  using G = Tile<E>;
-  const dim3 grid(xcd_grid_size((a.M + kTile - 1) / kTile, a.n_tiles_cap * a.ksplit, kMapBy));
-  hipError_t e = allow_lds<gemm_t_kernel<E, Role>>(G::LDS_BYTES);
+template <typename E, int Role, int Edge>
+static hipError_t launch_gemm_t_edge(const GemmTArgs& a, hipStream_t s) {
+  using G = Tile<E, false, Edge>;
+  const dim3 grid(xcd_grid_size((a.M + Edge - 1) / Edge, a.n_tiles_cap * (kTile / Edge) * a.ksplit, kMapBy));
+  hipError_t e = allow_lds<gemm_t_kernel<E, Role, Edge>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gemm_t_kernel<E, Role>), grid, dim3(G::NT), G::LDS_BYTES, s, a);
+  hipLaunchKernelGGL((gemm_t_kernel<E, Role, Edge>), grid, dim3(G::NT), G::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
+template <typename E, int Role>
+static hipError_t launch_gemm_t_impl(const GemmTArgs& a, hipStream_t s) {
+  switch (a.edge) {
+    case 64: return launch_gemm_t_edge<E, Role, 64>(a, s);
+    case 128: return launch_gemm_t_edge<E, Role, 128>(a, s);
+    default: return launch_gemm_t_edge<E, Role, 256>(a, s);
+  }
+}
+
 hipError_t launch_gemm_t(int dtype, const GemmTArgs& a, hipStream_t s, int role) {
-  const bool dw = a.k_from_nv;
-  if (role == 2)
-    return dtype == LMHEAD_BF16 ? launch_gemm_t_impl<bf16_tag, 2>(a, s) : launch_gemm_t_impl<f32_tag, 2>(a, s);
+  if (role < 0) role = a.k_from_nv ? 1 : 0;
   if (dtype == LMHEAD_BF16)
-    return dw ? launch_gemm_t_impl<bf16_tag, 1>(a, s) : launch_gemm_t_impl<bf16_tag, 0>(a, s);
-  return dw ? launch_gemm_t_impl<f32_tag, 1>(a, s) : launch_gemm_t_impl<f32_tag, 0>(a, s);
+    return role == 0   ? launch_gemm_t_impl<bf16_tag, 0>(a, s)
+           : role == 1 ? launch_gemm_t_impl<bf16_tag, 1>(a, s)
+                       : launch_gemm_t_impl<bf16_tag, 2>(a, s);
+  return role == 0   ? launch_gemm_t_impl<f32_tag, 0>(a, s)
+         : role == 1 ? launch_gemm_t_impl<f32_tag, 1>(a, s)
+                     : launch_gemm_t_impl<f32_tag, 2>(a, s);
 }
 
 }  // namespace lmhead

@@ -67,3 +67,40 @@ def test_kv_products_over_tile_edges(dtype, d, n):
     kk = k.cpu().numpy()[rows]
     kept = np.where(np.arange(d)[None, :] < kk[:, None], got, 0.0)
     assert rel_fro(np64(xbar)[rows], kept @ f(inp["U_inv"])) <= (4e-3 if dtype == "bf16" else 1e-5)
+
+
+# each tile edge of dW / dU with one and several slices, odd token counts and widths that are no multiple of the edge
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 64, 1), ("bf16", 192, 515), ("bf16", 1088, 700), ("bf16", 832, 5000),
+                                       ("bf16", 1024, 16500), ("f32", 64, 3), ("f32", 320, 129), ("f32", 576, 2500)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_kv_parameter_gradients_over_splits(dtype, d, n, accumulate):
+    import torch
+    import workloads.dynakv as kv
+    from tests.harness import KvProblem
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d, dtype=dtype)
+    inp = kv.kv_inputs(cfg)
+    kp = KvProblem(cfg, inp)
+    xt, _, m, _ = kp.gate(cfg.tau)
+    g_xhat, _ = kv.upstream(cfg)
+    init = None
+    if accumulate:
+        init = [torch.full(s, 0.25, dtype=torch.float32, device="cuda") for s in ((d, d), (d, d), (d,))]
+    dx, dU, dW, db = kp.gate_bwd(xt, to_device(g_xhat), accumulate_into=init)
+    assert kp.check() == 0
+    # the chain rule in 64 bits from the device's own spectral state and mask
+    x, U, W = (torch.from_numpy(wl.as_f64(inp[k])).cuda() for k in ("x", "U", "W"))
+    t, gx = xt.double(), torch.from_numpy(wl.as_f64(g_xhat)).cuda()
+    p = torch.softmax(t @ W + torch.from_numpy(inp["b"]).cuda().double(), 1)
+    mask = p.flip(1).cumsum(1).flip(1)
+    r = (gx * t).cumsum(1)
+    gl = p * (r - (p * r).sum(1, keepdim=True))
+    gxt = gx * mask + gl @ W.t()
+    base = 0.25 if accumulate else 0.0
+    # bf16: one rounding (2^-9) of the gradients that enter each product; fp32: sums of n or d products
+    tol = 1e-2 if dtype == "bf16" else 2e-5
+    for got, want in ((dx, gxt @ U.t()), (dU, x.t() @ gxt), (dW, t.t() @ gl), (db, gl.sum(0))):
+        off = 0.0 if got is dx else base
+        err = (got.double() - off - want).norm() / want.norm()
+        # adding to 0.25 in fp32 costs 2^-25 * 0.25 per element
+        slack = 2.0 ** -27 * want.numel() ** 0.5 / want.norm() if off else 0.0
+        assert err <= tol + slack, (float(err), got.shape)
