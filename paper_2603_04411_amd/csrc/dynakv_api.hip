@@ -175,8 +175,7 @@ int dynakv_retain(const dynakv_desc* desc, const int32_t* k, const float* m, flo
   if ((m && !aligned16(m)) || (g_m && !aligned16(g_m))) return LMHEAD_E_ALIGN;
   const KvLayout& L = w.L;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  LM_TRY(launch_kv_clear_header(w.at<WsHeader>(L.hdr), s));
-  LM_TRY(launch_kv_retain(k, m, L.n, desc->d, alpha, out, g_m, w.at<double>(L.red), s));
+  LM_TRY(launch_kv_retain(k, m, L.n, desc->d, alpha, out, g_m, w.at<double>(L.red), w.at<WsHeader>(L.hdr), s));
   return LMHEAD_OK;
 }
 

@@ -26,6 +26,12 @@ __device__ inline int wave_sum_i(int v) {
   return v;
 }
 
+// First write of every call to the error word (and the token count, which this path does not use).
+__device__ inline void clear_header(WsHeader* hdr) {
+  hdr->err = 0;
+  hdr->nv = 0;
+}
+
 template <typename T>
 struct Store4;
 template <>
@@ -428,27 +434,61 @@ void kv_mask_bwd_kernel(const float* __restrict__ logits, const float* __restric
   }
 }
 
-// out[j] (+)= sum over the rows of part.  A workgroup owns 64 columns; its four wavefronts each sum
-// every fourth row (four independent running sums each), and the partial sums are combined in a fixed
-// order, so the result does not depend on the launch.
-__global__ __launch_bounds__(256) void kv_sum_rows_kernel(const float* __restrict__ part, int rows, int64_t row_pitch,
-                                                          int64_t len, float* __restrict__ out, int accumulate) {
-  __shared__ float sm[4][64];
+// out[j] (+)= sum over the rows of part, in a fixed order.  Bound by reading part once; what differs is where the
+// parallelism is.
+//  - Few rows (slices of a parameter gradient): one thread per four columns walks the rows.
+//  - Many rows, few columns (the column sums of the mask backward): a workgroup owns 64 columns, its sixteen
+//    wavefronts each sum every sixteenth row, eight loads at a time.  (With four wavefronts and a chain of four loads each,
+//    1024 rows of 1024 columns took 22 us, now 5.4.)
+__global__ __launch_bounds__(256) void kv_sum_slices_kernel(const float* __restrict__ part, int rows, int64_t row_pitch,
+                                                            int64_t len4, float* __restrict__ out, int accumulate) {
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j >= len4) return;
+  float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int r = 0; r < rows; ++r) {
+    const float4 v = reinterpret_cast<const float4*>(part + (int64_t)r * row_pitch)[j];
+    t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+  }
+  float4* const dst = reinterpret_cast<float4*>(out) + j;
+  if (accumulate) {
+    const float4 o = *dst;
+    t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+  }
+  *dst = t;
+}
+
+constexpr int kSumWaves = 16, kSumBatch = 8;
+
+__global__ __launch_bounds__(64 * kSumWaves) void kv_sum_rows_kernel(const float* __restrict__ part, int rows,
+                                                                     int64_t row_pitch, int64_t len,
+                                                                     float* __restrict__ out, int accumulate) {
+  __shared__ float sm[kSumWaves][64];
   const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
   const int64_t j = (int64_t)blockIdx.x * 64 + cl;
-  float t[4] = {0.f, 0.f, 0.f, 0.f};
+  float t[kSumBatch] = {};
   if (j < len) {
+    const float* const p = part + j;
     int r = rl;
-    for (; r + 12 < rows; r += 16) {
+    for (; r + (kSumBatch - 1) * kSumWaves < rows; r += kSumWaves * kSumBatch) {
+      float v[kSumBatch];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) t[u] += part[(int64_t)(r + 4 * u) * row_pitch + j];
+      for (int u = 0; u < kSumBatch; ++u) v[u] = p[(int64_t)(r + u * kSumWaves) * row_pitch];
+#pragma unroll
+      for (int u = 0; u < kSumBatch; ++u) t[u] += v[u];
     }
-    for (; r < rows; r += 4) t[0] += part[(int64_t)r * row_pitch + j];
+    for (; r < rows; r += kSumWaves) t[0] += p[(int64_t)r * row_pitch];
   }
-  sm[rl][cl] = (t[0] + t[1]) + (t[2] + t[3]);
+#pragma unroll
+  for (int o = kSumBatch / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int u = 0; u < o; ++u) t[u] += t[u + o];
+  sm[rl][cl] = t[0];
   __syncthreads();
   if (rl == 0 && j < len) {
-    const float v = (sm[0][cl] + sm[1][cl]) + (sm[2][cl] + sm[3][cl]);
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSumWaves; ++w) v += sm[w][cl];
     out[j] = accumulate ? out[j] + v : v;
   }
 }
@@ -659,29 +699,37 @@ __global__ __launch_bounds__(256) void kv_scatter_kernel(const int32_t* __restri
 
 // ---- retain rate ----------------------------------------------------------------------------
 
-// red[2*b] = sum of k over the block's 256 tokens, red[2*b+1] = sum of m over their rows.
+// red[2*b] = sum of k over the block's tokens, red[2*b+1] = sum of m over their rows.  The tokens are cut evenly over
+// the blocks.  Bound by the one read of m: as many blocks as the chip holds at once (kKvRetainBlocks), each thread with
+// four loads in flight.  (One block per 256 tokens gave 16 blocks for 4096 tokens and 66 us, now 5.5.)
 __global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* __restrict__ k,
                                                                 const float* __restrict__ m, int64_t n, int d,
-                                                                double* __restrict__ red) {
+                                                                double* __restrict__ red, WsHeader* hdr) {
   __shared__ double sk[4], sm[4];
-  const int64_t t0 = (int64_t)blockIdx.x * 256;
-  const int64_t tn = min((int64_t)256, n - t0);
-  int ks = 0;
-  if (k && threadIdx.x < tn) ks = min(max(k[t0 + threadIdx.x], 0), d);
-  float ms = 0.f;
+  if (blockIdx.x == 0 && threadIdx.x == 0) clear_header(hdr);
+  const int64_t t0 = n * blockIdx.x / gridDim.x;
+  const int64_t tn = n * (blockIdx.x + 1) / gridDim.x - t0;
+  double ks = 0.0;
+  if (k)
+    for (int64_t i = threadIdx.x; i < tn; i += 256) ks += min(max(k[t0 + i], 0), d);
+  float ms[4] = {};
   if (m) {
     const int64_t cnt4 = tn * d / 4;
     const float4* p = reinterpret_cast<const float4*>(m + t0 * d);
-    for (int64_t i = threadIdx.x; i < cnt4; i += 256) {
-      const float4 v = p[i];
-      ms += (v.x + v.y) + (v.z + v.w);
+    for (int64_t i = threadIdx.x; i < cnt4; i += 1024) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = i + 256 * u < cnt4 ? p[i + 256 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ms[u] += (v[u].x + v[u].y) + (v[u].z + v[u].w);
     }
   }
-  ks = wave_sum_i(ks);
-  ms = wave_sum(ms);
+  const float msum = wave_sum((ms[0] + ms[1]) + (ms[2] + ms[3]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ks += __shfl_xor(ks, o);
   if ((threadIdx.x & 63) == 0) {
     sk[threadIdx.x >> 6] = ks;
-    sm[threadIdx.x >> 6] = ms;
+    sm[threadIdx.x >> 6] = msum;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -690,29 +738,34 @@ __global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* _
   }
 }
 
+// One block.  Eight pairs in flight per thread, then a tree over the threads.
 __global__ __launch_bounds__(256) void kv_retain_final_kernel(const double* __restrict__ red, int nblocks,
                                                               int64_t n, int d, float alpha, int have_k,
                                                               int have_m, float* __restrict__ out) {
-  __shared__ double sk[256], sm[256];
+  __shared__ double sk[4], sm[4];
   double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += 256) {
-    a += red[2 * i];
-    b += red[2 * i + 1];
-  }
-  sk[threadIdx.x] = a;
-  sm[threadIdx.x] = b;
-  __syncthreads();
-  for (unsigned o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) {
-      sk[threadIdx.x] += sk[threadIdx.x + o];
-      sm[threadIdx.x] += sm[threadIdx.x + o];
+#pragma unroll
+  for (int u = 0; u < kKvRetainBlocks / 256; ++u) {
+    const int i = threadIdx.x + 256 * u;
+    if (i < nblocks) {
+      a += red[2 * i];
+      b += red[2 * i + 1];
     }
-    __syncthreads();
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o);
+    b += __shfl_xor(b, o);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sk[threadIdx.x >> 6] = a;
+    sm[threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     const double nd = (double)n * d;
-    const double rh = have_k ? sk[0] / nd : 0.0;
-    const double rs = have_m ? sm[0] / nd : 0.0;
+    const double rh = have_k ? ((sk[0] + sk[1]) + (sk[2] + sk[3])) / nd : 0.0;
+    const double rs = have_m ? ((sm[0] + sm[1]) + (sm[2] + sm[3])) / nd : 0.0;
     out[0] = (float)rh;
     out[1] = (float)rs;
     out[2] = (float)(alpha * rs * rs);
@@ -728,10 +781,7 @@ __global__ __launch_bounds__(256) void kv_retain_grad_kernel(const float* __rest
 }
 
 __global__ void kv_clear_header_kernel(WsHeader* hdr) {
-  if (threadIdx.x == 0) {
-    hdr->err = 0;
-    hdr->nv = 0;
-  }
+  if (threadIdx.x == 0) clear_header(hdr);
 }
 
 }  // namespace
@@ -813,8 +863,13 @@ hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, co
 
 hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, int64_t len, float* out,
                               bool accumulate, hipStream_t s) {
-  hipLaunchKernelGGL(kv_sum_rows_kernel, dim3((unsigned)((len + 63) / 64)), dim3(256), 0, s, part, rows, row_pitch,
-                     len, out, accumulate ? 1 : 0);
+  // 256 rows: above the most slices of a parameter gradient, which has d x d columns
+  if (rows <= 256 && len % 4 == 0 && row_pitch % 4 == 0 && len >= 16384)
+    hipLaunchKernelGGL(kv_sum_slices_kernel, dim3((unsigned)((len / 4 + 255) / 256)), dim3(256), 0, s, part, rows,
+                       row_pitch, len / 4, out, accumulate ? 1 : 0);
+  else
+    hipLaunchKernelGGL(kv_sum_rows_kernel, dim3((unsigned)((len + 63) / 64)), dim3(64 * kSumWaves), 0, s, part, rows,
+                       row_pitch, len, out, accumulate ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -873,9 +928,9 @@ hipError_t launch_kv_order(int dtype, const int32_t* k, const int64_t* off, int6
 }
 
 hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, float alpha, float* out,
-                            float* g_m, double* red, hipStream_t s) {
-  const int nblocks = (int)((n + 255) / 256);
-  hipLaunchKernelGGL(kv_retain_partial_kernel, dim3(nblocks), dim3(256), 0, s, k, m, n, d, red);
+                            float* g_m, double* red, WsHeader* hdr, hipStream_t s) {
+  const int nblocks = (int)(n < kKvRetainBlocks ? n : kKvRetainBlocks);
+  hipLaunchKernelGGL(kv_retain_partial_kernel, dim3(nblocks), dim3(256), 0, s, k, m, n, d, red, hdr);
   hipLaunchKernelGGL(kv_retain_final_kernel, dim3(1), dim3(256), 0, s, red, nblocks, n, d, alpha, k ? 1 : 0,
                      m ? 1 : 0, out);
   if (g_m) {

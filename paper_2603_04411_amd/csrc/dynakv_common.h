@@ -7,6 +7,7 @@
 namespace lmhead {
 
 constexpr int kKvMaxD = 8192;
+constexpr int kKvRetainBlocks = 2048;   // blocks of the retain-rate sums: 256 threads each, one resident round
 constexpr int kKvScanBlock = 1024;   // tokens per block of the offset scan
 
 // Sticky error bits of this path (same header word as the LM-head path).
@@ -48,7 +49,7 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
   L.pos_len = take((size_t)L.ncap * 4);
   L.hist = take((size_t)L.nbuckets * 3 * 4);          // counts, start positions, cursors
   L.blocksum = take((size_t)(L.ncap / kKvScanBlock + 2) * 8);
-  L.red = take((size_t)(L.ncap / 256 + 2) * 2 * 8);   // per-block partial sums of the retain rate
+  L.red = take((size_t)kKvRetainBlocks * 2 * 8);      // per-block partial sums of the retain rate
   L.total = off;
   return L;
 }
@@ -174,8 +175,9 @@ hipError_t launch_kv_order(int dtype, const int32_t* k, const int64_t* off, int6
                            int d, int nbuckets, int32_t* hist, int32_t* order, uint32_t* pos_off, int32_t* pos_len,
                            WsHeader* hdr, hipStream_t s);
 
+// Retain rates; clears the header.
 hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, float alpha, float* out,
-                            float* g_m, double* red, hipStream_t s);
+                            float* g_m, double* red, WsHeader* hdr, hipStream_t s);
 
 // Backward of softmax + cumulative mask + soft gating for every token (one wavefront per token):
 //   q = g_xhat * xt + g_m + g_m_const;  r = inclusive prefix sums of q;  g_l = p * (r - sum p r);

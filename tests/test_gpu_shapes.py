@@ -104,3 +104,22 @@ def test_kv_parameter_gradients_over_splits(dtype, d, n, accumulate):
         # adding to 0.25 in fp32 costs 2^-25 * 0.25 per element
         slack = 2.0 ** -27 * want.numel() ** 0.5 / want.norm() if off else 0.0
         assert err <= tol + slack, (float(err), got.shape)
+
+
+# one token per block, one more than the blocks there are, shares that differ by one
+@pytest.mark.parametrize("n,d", [(1, 64), (2, 128), (2047, 64), (2049, 64), (5000, 192)])
+def test_kv_retain_rate_over_block_shares(n, d):
+    import torch
+    import paper_2603_04411_amd as L
+    g = torch.Generator().manual_seed(n)
+    m = torch.rand(n, d, generator=g)
+    k = torch.randint(0, d + 1, (n,), generator=g, dtype=torch.int32)
+    desc = L.make_kv_desc(n, d, "bf16")
+    ws = torch.empty(L.dynakv_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    out, gm = torch.empty(3, device="cuda"), torch.empty(n, d, device="cuda")
+    L.dynakv_retain(desc, k.cuda(), m.cuda(), 0.5, out, gm, ws)
+    assert L.dynakv_check(ws) == 0
+    hard, soft = k.double().mean().item() / d, m.double().mean().item()
+    # k is summed exactly; of m at most a few hundred values enter one fp32 sum: well under 256 * 2^-24
+    np.testing.assert_allclose(out.cpu().numpy(), [hard, soft, 0.5 * soft ** 2], rtol=1.5e-5)
+    np.testing.assert_allclose(gm.cpu().numpy(), soft / (n * d), rtol=1.5e-5)
