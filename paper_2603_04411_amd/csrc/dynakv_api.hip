@@ -29,6 +29,11 @@ struct Ws {
   T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
 };
 
+// K-contiguous (transposed) or row-padded copy of a dense d x d parameter matrix, zero up to dp rows of the copy
+KvCopy param_copy(const void* in, int d, void* out, int64_t ld_out, int64_t dp, bool transposed) {
+  return {in, d, d, transposed ? d : dp, d, (int)(transposed ? dp : d), out, ld_out, transposed, 0};
+}
+
 // common prologue of the compute entry points
 int open_ws(const dynakv_desc* desc, void* ws, size_t ws_bytes, Ws& w) {
   const int rc = validate(desc);
@@ -67,10 +72,13 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
   const int dt = desc->dtype;
   const int d = desc->d;
 
-  LM_TRY(launch_kv_clear_header(hdr, s));
   // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
-  LM_TRY(launch_transpose(dt, U, d, d, d, false, hdr, w.at<void>(L.UT), L.ldT, d, L.dp, s));
-  LM_TRY(launch_transpose(dt, W, d, d, d, false, hdr, w.at<void>(L.WT), L.ldT, d, L.dp, s));
+  KvPrepareArgs pa{};
+  pa.hdr = hdr;
+  pa.job[0] = param_copy(U, d, w.at<void>(L.UT), L.ldT, L.dp, true);
+  pa.job[1] = param_copy(W, d, w.at<void>(L.WT), L.ldT, L.dp, true);
+  pa.njobs = 2;
+  LM_TRY(launch_kv_prepare(dt, pa, s));
 
   KvGemmArgs ga{};
   ga.mode = 0;
@@ -117,7 +125,6 @@ int dynakv_store(const dynakv_desc* desc, const void* xt, const int32_t* k, int6
   const KvLayout& L = w.L;
   hipStream_t s = static_cast<hipStream_t>(stream);
   WsHeader* hdr = w.at<WsHeader>(L.hdr);
-  LM_TRY(launch_kv_clear_header(hdr, s));
   LM_TRY(launch_kv_store(desc->dtype, xt, k, L.n, desc->d, off_base, off, packed, capacity,
                          w.at<int64_t>(L.blocksum), hdr, s));
   return LMHEAD_OK;
@@ -138,11 +145,15 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
   const int dt = desc->dtype;
   const int d = desc->d;
 
-  LM_TRY(launch_kv_clear_header(hdr, s));
   // A[j][kk] = U_inv[kk][j]: row j of the copy is output column j, contiguous over the retained index
-  LM_TRY(launch_transpose(dt, U_inv, d, d, d, false, hdr, w.at<void>(L.UiT), L.ldT, d, L.dp, s));
-  LM_TRY(launch_kv_order(dt, k, off, packed_elems * L.esz, L.n, L.ncap, d, L.nbuckets, w.at<int32_t>(L.hist),
-                         w.at<int32_t>(L.order), w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), hdr, s));
+  KvPrepareArgs pa{};
+  pa.hdr = hdr;
+  pa.job[0] = param_copy(U_inv, d, w.at<void>(L.UiT), L.ldT, L.dp, true);
+  pa.njobs = 1;
+  pa.count = make_kv_count(k, L.n, d, L.nbuckets, w.at<int32_t>(L.hist));
+  LM_TRY(launch_kv_prepare(dt, pa, s));
+  LM_TRY(launch_kv_order(dt, pa.count, off, packed_elems * L.esz, L.ncap, w.at<int32_t>(L.order),
+                         w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), hdr, s));
 
   KvGemmArgs ga{};
   ga.mode = 2;
@@ -205,12 +216,15 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0;
   const bool accum = (desc->flags & DYNAKV_FLAG_ACCUM_GRAD) != 0;
 
-  LM_TRY(launch_kv_clear_header(hdr, s));
   // parameter operands of the three token-major products: W^T (K-contiguous copy) for the logits, and
   // row-padded copies of W and U, which are K-contiguous as they are for g_l W^T and g_x~ U^T
-  LM_TRY(launch_transpose(dt, W, d, d, d, false, hdr, at(L.WT), L.ldT, d, L.dp, s));
-  LM_TRY(launch_kv_pad_copy(dt, W, d, d, d, at(L.Wp), L.ldT, (int)L.dp, s));
-  LM_TRY(launch_kv_pad_copy(dt, U, d, d, d, at(L.Up), L.ldT, (int)L.dp, s));
+  KvPrepareArgs pa{};
+  pa.hdr = hdr;
+  pa.job[0] = param_copy(W, d, at(L.WT), L.ldT, L.dp, true);
+  pa.job[1] = param_copy(W, d, at(L.Wp), L.ldT, L.dp, false);
+  pa.job[2] = param_copy(U, d, at(L.Up), L.ldT, L.dp, false);
+  pa.njobs = 3;
+  LM_TRY(launch_kv_prepare(dt, pa, s));
 
   KvGemmArgs ga{};
   ga.mode = 1;
@@ -262,8 +276,11 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   auto param_grad = [&](const void* rows_src, int64_t ld_rows, const void* cols_src, int kind, float* out) -> int {
     {
       TimedLaunch tl(13, s);
-      LM_TRY(launch_kv_transpose(dt, rows_src, ld_rows, L.n, d, at(L.T1), L.ldK, L.ncap, (int)L.dp, s));
-      LM_TRY(launch_kv_transpose(dt, cols_src, d, L.n, d, at(L.T2), L.ldK, L.ncap, (int)L.dp, s));
+      KvPrepareArgs ta{};
+      ta.job[0] = {rows_src, ld_rows, L.n, L.ncap, d, (int)L.dp, at(L.T1), L.ldK, true, 0};
+      ta.job[1] = {cols_src, d, L.n, L.ncap, d, (int)L.dp, at(L.T2), L.ldK, true, 0};
+      ta.njobs = 2;
+      LM_TRY(launch_kv_prepare(dt, ta, s));
     }
     GemmTArgs ta{};
     ta.A = at(L.T2);

@@ -493,18 +493,73 @@ __global__ __launch_bounds__(64 * kSumWaves) void kv_sum_rows_kernel(const float
   }
 }
 
-// Row-padded copy of a parameter matrix: 16 bytes per thread, zero beyond the source's extent.
-__global__ __launch_bounds__(256) void kv_pad_copy_kernel(const char* __restrict__ in, int64_t in_pitch, int rows,
-                                                          int row_bytes, char* __restrict__ out, int64_t out_pitch,
-                                                          int rows_p) {
-  const int chunks = (int)(out_pitch / 16);
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t r = id / chunks;
-  const int c = (int)(id % chunks) * 16;
-  if (r >= rows_p) return;
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (r < rows && c < row_bytes) v = *reinterpret_cast<const uint4*>(in + r * in_pitch + c);
-  *reinterpret_cast<uint4*>(out + r * out_pitch + c) = v;
+// ---- operand copies, with what else a call has to prepare ------------------------------------
+
+__device__ inline int bucket_of(int k, int d, int esz) {
+  k = min(max(k, 0), d);
+  return (k * esz + 127) / 128;
+}
+
+// One launch prepares a call: it clears the header, makes up to kKvMaxCopies operand copies (64 x 64 tiles, 16-byte
+// accesses on both sides, the transposed ones through LDS as in transpose16_kernel) and counts the tokens of each
+// length for the reconstruction's grouping.  Every one of these was a launch of its own, 3-5 us each and mostly dispatch
+// (the copies of d = 1024 are 2 MB).
+template <typename T>
+__global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a) {
+  constexpr int VEC = 16 / sizeof(T);         // elements per 16-byte chunk
+  constexpr int CPR = 64 / VEC;               // chunks per tile row
+  constexpr int PITCH = 64 + 4 / sizeof(T);   // elements; keeps rows 4-byte aligned and the gather conflict-free
+  __shared__ __attribute__((aligned(16))) T tile[64 * PITCH];
+  if (a.hdr && blockIdx.x == 0 && threadIdx.x == 0) clear_header(a.hdr);
+  int b = blockIdx.x;
+  if (b < a.count.blocks) {
+    // counts per K-step bucket of this block's tokens; no global atomics, so nothing has to be cleared first
+    int32_t* const h = reinterpret_cast<int32_t*>(tile);   // nbuckets <= 257
+    for (int i = threadIdx.x; i < a.count.nbuckets; i += 256) h[i] = 0;
+    __syncthreads();
+    const int64_t t1 = min(a.count.n, (int64_t)(b + 1) * a.count.per_block);
+    for (int64_t i = (int64_t)b * a.count.per_block + threadIdx.x; i < t1; i += 256)
+      atomicAdd(&h[bucket_of(a.count.k[i], a.count.d, sizeof(T))], 1);
+    __syncthreads();
+    for (int i = threadIdx.x; i < a.count.nbuckets; i += 256) a.count.hist[(int64_t)b * a.count.nbuckets + i] = h[i];
+    return;
+  }
+  b -= a.count.blocks;
+  int jb = 0;
+  while (jb + 1 < a.njobs && b >= a.job[jb].tiles) b -= a.job[jb++].tiles;
+  if (jb >= a.njobs || b >= a.job[jb].tiles) return;
+  const KvCopy& c = a.job[jb];
+  const T* const in = static_cast<const T*>(c.in);
+  T* const out = static_cast<T*>(c.out);
+  const int row_tiles = (int)(c.rows_p / 64);
+  const int64_t r0 = (int64_t)(b % row_tiles) * 64;
+  const int c0 = b / row_tiles * 64;
+#pragma unroll
+  for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
+    const int id = pass * 256 + threadIdx.x;
+    const int rr = id / CPR, cc = id % CPR;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (r0 + rr < c.rows && c0 < c.cols) v = *reinterpret_cast<const uint4*>(in + (r0 + rr) * c.ld_in + c0 + cc * VEC);
+    if (!c.transposed) {
+      *reinterpret_cast<uint4*>(out + (r0 + rr) * c.ld_out + c0 + cc * VEC) = v;
+    } else {
+      uint32_t* const dst = reinterpret_cast<uint32_t*>(tile + rr * PITCH + cc * VEC);
+      dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+    }
+  }
+  if (!c.transposed) return;
+  __syncthreads();
+#pragma unroll
+  for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
+    const int id = pass * 256 + threadIdx.x;
+    const int col = id / CPR, rc = id % CPR;
+    T e[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) e[i] = tile[(rc * VEC + i) * PITCH + col];
+    uint4 v;
+    __builtin_memcpy(&v, e, 16);
+    *reinterpret_cast<uint4*>(out + (int64_t)(c0 + col) * c.ld_out + r0 + rc * VEC) = v;
+  }
 }
 
 // ---- ragged store ---------------------------------------------------------------------------
@@ -517,22 +572,26 @@ __device__ inline int seg_len(int k, int d, int& bad) {
   return (k + DYNAKV_GRANULE - 1) / DYNAKV_GRANULE * DYNAKV_GRANULE;
 }
 
-// Block totals of the segment lengths (kKvScanBlock tokens per block).
-__global__ __launch_bounds__(256) void kv_scan_totals_kernel(const int32_t* __restrict__ k, int64_t n, int d,
-                                                             int64_t* __restrict__ blocksum, WsHeader* hdr) {
-  __shared__ int wsum[4];
-  const int64_t base = (int64_t)blockIdx.x * kKvScanBlock;
-  int bad = 0, tot = 0;
-  for (int i = threadIdx.x; i < kKvScanBlock; i += 256)
-    if (base + i < n) tot += seg_len(k[base + i], d, bad);
-  tot = wave_sum_i(tot);
+// Block totals of the segment lengths (kKvScanBlock tokens per block).  Clears the header: the counts are checked, and
+// errors raised, by the kernel that packs.
+__global__ __launch_bounds__(kKvScanBlock) void kv_scan_totals_kernel(const int32_t* __restrict__ k, int64_t n, int d,
+                                                                      int64_t* __restrict__ blocksum, WsHeader* hdr) {
+  __shared__ int wsum[kKvScanBlock / 64];
+  const int64_t i = (int64_t)blockIdx.x * kKvScanBlock + threadIdx.x;
+  if (i == 0) clear_header(hdr);
+  int bad = 0;
+  const int tot = wave_sum_i(i < n ? seg_len(k[i], d, bad) : 0);
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = tot;
-  if (bad) atomicOr(&hdr->err, kErrKvCount);
   __syncthreads();
-  if (threadIdx.x == 0) blocksum[blockIdx.x] = (int64_t)wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (threadIdx.x == 0) {
+    int64_t t = 0;
+#pragma unroll
+    for (int w = 0; w < kKvScanBlock / 64; ++w) t += wsum[w];
+    blocksum[blockIdx.x] = t;
+  }
 }
 
-// One workgroup: blocksum <- its exclusive prefix sum; blocksum[nblocks] = grand total.
+// One workgroup: blocksum <- its exclusive prefix sum.
 __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restrict__ blocksum, int nblocks) {
   __shared__ int64_t buf[1024];
   __shared__ int64_t carry_s;
@@ -555,146 +614,165 @@ __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restric
     if (threadIdx.x == 1023) carry_s = carry + buf[1023];
     __syncthreads();
   }
-  if (threadIdx.x == 0) blocksum[nblocks] = carry_s;
 }
 
-// off[i] = prefix of the block + exclusive prefix inside the block; off[n] = grand total.
-__global__ __launch_bounds__(1024) void kv_scan_offsets_kernel(const int32_t* __restrict__ k, int64_t n, int d,
-                                                               const int64_t* __restrict__ blocksum,
-                                                               int nblocks, int64_t off_base,
-                                                               int64_t* __restrict__ off) {
-  __shared__ int buf[1024];
-  const int64_t i = (int64_t)blockIdx.x * kKvScanBlock + threadIdx.x;
-  int bad = 0;
-  const int x = i < n ? seg_len(k[i], d, bad) : 0;
-  buf[threadIdx.x] = x;
-  __syncthreads();
-  for (unsigned o = 1; o < 1024; o <<= 1) {
-    const int y = threadIdx.x >= o ? buf[threadIdx.x - o] : 0;
-    __syncthreads();
-    buf[threadIdx.x] += y;
-    __syncthreads();
-  }
-  if (i < n) off[i] = off_base + blocksum[blockIdx.x] + buf[threadIdx.x] - x;
-  if (i == n - 1) off[n] = off_base + blocksum[nblocks];
-}
-static_assert(kKvScanBlock == 1024, "the offset kernel scans one token per thread");
-
-// One wavefront per token: copy the segment, zero the tail of its last granule.
+// Offsets and copy of the segments, kKvPackTokens tokens per workgroup, a wavefront per token.  A workgroup adds up
+// what lies before its tokens itself: the totals of the blocks before (or their prefix sum, when there are so many that
+// `scanned` says that has been formed) and the tokens before it in its own block.  That replaces a scan launch and an offset
+// launch: five launches (25 us at 16 tokens, 32 us at 16411) became two, one up to kKvScanBlock tokens.
+// Then (no totals launch: blocksum is null) the first workgroup sees every token: it clears the header and sets
+// the error word for all of them with one store.
+constexpr int kKvPackTokens = 16;
 template <typename T>
 __global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, const int32_t* __restrict__ k,
-                                                      const int64_t* __restrict__ off, int64_t n, int d,
+                                                      const int64_t* __restrict__ blocksum, int scanned, int64_t n,
+                                                      int d, int64_t off_base, int64_t* __restrict__ off,
                                                       T* __restrict__ packed, int64_t capacity, WsHeader* hdr) {
   constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
-  const int lane = threadIdx.x & 63;
-  const int64_t tok = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tok >= n) return;
+  __shared__ int64_t part[4];
+  __shared__ int seg_s[kKvPackTokens];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t0 = (int64_t)blockIdx.x * kKvPackTokens;
+  const int64_t blk = t0 / kKvScanBlock;
   int bad = 0;
-  const int kk = min(max(k[tok], 0), d);
-  const int seg = seg_len(kk, d, bad);
-  const int64_t o = off[tok];
-  if (o + seg > capacity) {
-    if (lane == 0) atomicOr(&hdr->err, kErrKvCapacity);
-    return;
+  int64_t before = 0;
+  if (scanned) {
+    if (threadIdx.x == 0) before = blocksum[blk];
+  } else {
+    for (int64_t i = threadIdx.x; i < blk; i += 256) before += blocksum[i];
   }
-  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-  for (int c = lane; c * EPC < seg; c += 64) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(xt + tok * d + c * EPC);
-    if ((c + 1) * EPC > kk) {
-      T e[EPC];
-      __builtin_memcpy(e, &v, 16);
+  const int64_t own = blk * kKvScanBlock + threadIdx.x;   // one token of the own block per thread
+  const int own_seg = own < n ? seg_len(k[own], d, bad) : 0;
+  if (own < t0) before += own_seg;
+  if (own >= t0 && own < t0 + kKvPackTokens) seg_s[own - t0] = own_seg;
 #pragma unroll
-      for (int j = 0; j < EPC; ++j)
-        if (c * EPC + j >= kk) e[j] = (T)0.0f;
-      __builtin_memcpy(&v, e, 16);
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+  if (lane == 0) part[wave] = before;
+  __syncthreads();
+  const int64_t base = off_base + ((part[0] + part[1]) + (part[2] + part[3]));
+  if (!blocksum && blockIdx.x == 0) {
+    // one block of tokens: this workgroup holds all the segments; a token is out of room if the running total is
+    __shared__ int wtot[4], werr[4];
+    int incl = own_seg;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o);
+      if (lane >= o) incl += y;
     }
-    *reinterpret_cast<u32x4*>(packed + o + c * EPC) = v;
+    if (lane == 63) wtot[wave] = incl;
+    __syncthreads();
+    int64_t end = off_base + incl;
+    for (int w = 0; w < wave; ++w) end += wtot[w];
+    int err = (bad ? kErrKvCount : 0) | (own < n && end > capacity ? kErrKvCapacity : 0);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o);
+    if (lane == 0) werr[wave] = err;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      hdr->err = (werr[0] | werr[1]) | (werr[2] | werr[3]);
+      hdr->nv = 0;
+    }
+  }
+  if (blocksum && bad && own >= t0 && own < t0 + kKvPackTokens) atomicOr(&hdr->err, kErrKvCount);
+#pragma unroll
+  for (int u = 0; u < kKvPackTokens / 4; ++u) {
+    const int ti = u * 4 + wave;
+    const int64_t tok = t0 + ti;
+    if (tok >= n) break;
+    int64_t o = base;
+    for (int q = 0; q < ti; ++q) o += seg_s[q];
+    const int seg = seg_s[ti];
+    if (lane == 0) {
+      off[tok] = o;
+      if (tok == n - 1) off[n] = o + seg;
+    }
+    if (o + seg > capacity) {
+      if (blocksum && lane == 0) atomicOr(&hdr->err, kErrKvCapacity);
+      continue;
+    }
+    const int kk = min(max(k[tok], 0), d);
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    for (int c = lane; c * EPC < seg; c += 64) {
+      u32x4 v = *reinterpret_cast<const u32x4*>(xt + tok * d + c * EPC);
+      if ((c + 1) * EPC > kk) {
+        T e[EPC];
+        __builtin_memcpy(e, &v, 16);
+#pragma unroll
+        for (int j = 0; j < EPC; ++j)
+          if (c * EPC + j >= kk) e[j] = (T)0.0f;
+        __builtin_memcpy(&v, e, 16);
+      }
+      *reinterpret_cast<u32x4*>(packed + o + c * EPC) = v;
+    }
   }
 }
+static_assert(kKvScanBlock == 256 && kKvScanBlock % kKvPackTokens == 0, "one thread per token of a block");
 
 // ---- grouping by contraction length --------------------------------------------------------
 
-__global__ __launch_bounds__(256) void kv_fill_i32_kernel(int32_t* __restrict__ p, int64_t count, int32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < count) p[i] = v;
-}
-
-__device__ inline int bucket_of(int k, int d, int esz) {
-  k = min(max(k, 0), d);
-  return (k * esz + 127) / 128;
-}
-
-__global__ __launch_bounds__(256) void kv_hist_kernel(const int32_t* __restrict__ k, int64_t n, int d, int esz,
-                                                      int nbuckets, int32_t* __restrict__ hist) {
-  extern __shared__ int32_t h[];
-  for (int i = threadIdx.x; i < nbuckets; i += 256) h[i] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * 4096;
-  for (int i = threadIdx.x; i < 4096; i += 256)
-    if (base + i < n) atomicAdd(&h[bucket_of(k[base + i], d, esz)], 1);
-  __syncthreads();
-  for (int i = threadIdx.x; i < nbuckets; i += 256)
-    if (h[i]) atomicAdd(&hist[i], h[i]);
-}
-
-// start[b] = number of tokens in longer buckets (descending order of step count)
-__global__ void kv_bucket_start_kernel(int32_t* __restrict__ hist, int nbuckets) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int32_t run = 0;
-  for (int b = nbuckets - 1; b >= 0; --b) {
-    hist[nbuckets + b] = run;
-    run += hist[b];
-  }
-}
-
-// The position inside a bucket comes from integer atomics (a rank inside the workgroup's 4096 tokens
-// from LDS, one global reservation per workgroup and bucket), so `order` may differ from run to run
-// within a bucket; the reconstruction's results do not depend on it (a token's output only involves
-// its own row, and extra K-steps of a tile add exact zeros).
-// Besides the token, each sorted position gets the byte offset and byte length of the token's
-// segment in the store (validated here against the readable extent), so that the reconstruction
-// reads three contiguous arrays instead of chasing order -> off, k.
+// Position of every token in descending order of K-step count.  Block b owns the tokens that block b of
+// kv_prepare_kernel counted and derives where its tokens of each bucket start from the counts of all the blocks: the
+// longer buckets, then its own bucket in the blocks before it.  The position inside that range comes from an LDS
+// counter, so `order` may differ from run to run within a block's share of a bucket; the reconstruction's results do
+// not depend on it (a token's output only involves its own row, and extra K-steps of a tile add exact zeros).
+// With the counts made by kv_prepare_kernel this replaces seven launches (four fills, counts, starts, scatter; 27 us of
+// kernels at 16411 tokens) by one.
+// Besides the token, each sorted position gets the byte offset and byte length of the token's segment in the store
+// (validated here against the readable extent), so that the reconstruction reads three contiguous arrays instead of chasing
+// order -> off, k.  The positions from n to the tile multiple are padded with (-1, out of range, 0).
 __global__ __launch_bounds__(256) void kv_scatter_kernel(const int32_t* __restrict__ k,
-                                                         const int64_t* __restrict__ off, int64_t n, int d, int esz,
-                                                         int64_t bytes, int nbuckets, int32_t* __restrict__ hist,
+                                                         const int64_t* __restrict__ off, int64_t n, int64_t ncap,
+                                                         int d, int esz, int64_t bytes, int nbuckets,
+                                                         const int32_t* __restrict__ hist, int nblocks, int per_block,
                                                          int32_t* __restrict__ order, uint32_t* __restrict__ pos_off,
                                                          int32_t* __restrict__ pos_len, WsHeader* hdr) {
-  extern __shared__ int32_t h[];   // [nbuckets] counts, then [nbuckets] bases
-  constexpr int PER = 16;          // tokens per thread
-  for (int i = threadIdx.x; i < nbuckets; i += 256) h[i] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * (256 * PER);
-  int bk[PER], rank[PER];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int64_t i = base + j * 256 + threadIdx.x;
-    bk[j] = -1;
-    if (i < n) {
-      bk[j] = bucket_of(k[i], d, esz);
-      rank[j] = atomicAdd(&h[bk[j]], 1);
+  extern __shared__ int32_t h[];   // [nbuckets] totals, [nbuckets] next free position of this block
+  int32_t* const next = h + nbuckets;
+  const int blk = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int b = wave; b < nbuckets; b += 4) {
+    int tot = 0, mine = 0;
+    for (int i = lane; i < nblocks; i += 64) {
+      const int c = hist[(int64_t)i * nbuckets + b];
+      tot += c;
+      mine += i < blk ? c : 0;
+    }
+    tot = wave_sum_i(tot);
+    mine = wave_sum_i(mine);
+    if (lane == 0) {
+      h[b] = tot;
+      next[b] = mine;
     }
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < nbuckets; b += 256)
-    h[nbuckets + b] = hist[nbuckets + b] + (h[b] ? atomicAdd(&hist[2 * nbuckets + b], h[b]) : 0);
+  for (int b = threadIdx.x; b < nbuckets; b += 256) {
+    int longer = 0;
+    for (int q = b + 1; q < nbuckets; ++q) longer += h[q];
+    next[b] += longer;
+  }
   __syncthreads();
   int bad = 0;
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    if (bk[j] < 0) continue;
-    const int64_t i = base + j * 256 + threadIdx.x;
-    const int pos = h[nbuckets + bk[j]] + rank[j];
+  const int64_t t1 = min(n, (int64_t)(blk + 1) * per_block);
+  for (int64_t i = (int64_t)blk * per_block + threadIdx.x; i < t1; i += 256) {
+    const int kk = k[i];
     const int64_t o = off[i];
-    int dummy = 0;
-    const int seg = seg_len(k[i], d, dummy);
+    const int pos = atomicAdd(&next[bucket_of(kk, d, esz)], 1);
+    int clamped = 0;
+    const int seg = seg_len(kk, d, clamped);
+    const bool outside = o < 0 || (o & (DYNAKV_GRANULE - 1)) || (o + seg) * esz > bytes;
+    if (outside) bad = 1;
     order[pos] = (int32_t)i;
     pos_len[pos] = seg * esz;
-    if (o < 0 || (o & (DYNAKV_GRANULE - 1)) || (o + seg) * esz > bytes)
-      bad = 1;                     // pos_off keeps its fill value: every load of the row is out of range -> zeros
-    else
-      pos_off[pos] = (uint32_t)(o * esz);
+    pos_off[pos] = outside ? 0x80000000u : (uint32_t)(o * esz);   // out of range: every load of the row gives zeros
   }
   if (bad) atomicOr(&hdr->err, kErrKvCapacity);
+  if (blk == 0) {
+    for (int64_t p = n + threadIdx.x; p < ncap; p += 256) {
+      order[p] = -1;
+      pos_len[p] = 0;
+      pos_off[p] = 0x80000000u;
+    }
+  }
 }
 
 // ---- retain rate ----------------------------------------------------------------------------
@@ -780,16 +858,7 @@ __global__ __launch_bounds__(256) void kv_retain_grad_kernel(const float* __rest
   reinterpret_cast<float4*>(g)[i] = make_float4(v, v, v, v);
 }
 
-__global__ void kv_clear_header_kernel(WsHeader* hdr) {
-  if (threadIdx.x == 0) clear_header(hdr);
-}
-
 }  // namespace
-
-hipError_t launch_kv_clear_header(WsHeader* hdr, hipStream_t s) {
-  hipLaunchKernelGGL(kv_clear_header_kernel, dim3(1), dim3(64), 0, s, hdr);
-  return hipGetLastError();
-}
 
 template <typename T>
 static void launch_mask_t(const float* logits, const float* b, const void* xt, int64_t n, int d, float tau,
@@ -873,57 +942,49 @@ hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, in
   return hipGetLastError();
 }
 
-hipError_t launch_kv_pad_copy(int dtype, const void* in, int64_t ld_in, int rows, int cols, void* out,
-                              int64_t ld_out, int rows_p, hipStream_t s) {
-  const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
-  const int64_t threads = (int64_t)rows_p * (ld_out * esz / 16);
-  hipLaunchKernelGGL(kv_pad_copy_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                     static_cast<const char*>(in), ld_in * esz, rows, cols * esz, static_cast<char*>(out),
-                     ld_out * esz, rows_p);
+hipError_t launch_kv_prepare(int dtype, const KvPrepareArgs& a, hipStream_t s) {
+  KvPrepareArgs b = a;
+  int64_t blocks = b.count.blocks;
+  for (int j = 0; j < b.njobs; ++j) {
+    b.job[j].tiles = (int)(b.job[j].rows_p / 64 * (b.job[j].cols_p / 64));
+    blocks += b.job[j].tiles;
+  }
+  const dim3 grid((unsigned)(blocks > 0 ? blocks : 1));
+  if (dtype == LMHEAD_BF16)
+    hipLaunchKernelGGL(kv_prepare_kernel<uint16_t>, grid, dim3(256), 0, s, b);
+  else
+    hipLaunchKernelGGL(kv_prepare_kernel<uint32_t>, grid, dim3(256), 0, s, b);
   return hipGetLastError();
-}
-
-hipError_t launch_kv_transpose(int dtype, const void* in, int64_t ld_in, int64_t rows, int cols, void* out,
-                               int64_t ld_out, int64_t rows_p, int cols_p, hipStream_t s) {
-  // rows 16-byte aligned and extents multiples of 64 here: takes the 16-byte-access kernel
-  return launch_transpose(dtype, in, ld_in, rows, cols, false, nullptr, out, ld_out, rows_p, cols_p, s);
 }
 
 hipError_t launch_kv_store(int dtype, const void* xt, const int32_t* k, int64_t n, int d, int64_t off_base,
                            int64_t* off, void* packed, int64_t capacity, int64_t* blocksum, WsHeader* hdr,
                            hipStream_t s) {
-  const int nblocks = (int)((n + kKvScanBlock - 1) / kKvScanBlock);
-  hipLaunchKernelGGL(kv_scan_totals_kernel, dim3(nblocks), dim3(256), 0, s, k, n, d, blocksum, hdr);
-  hipLaunchKernelGGL(kv_scan_blocks_kernel, dim3(1), dim3(1024), 0, s, blocksum, nblocks);
-  hipLaunchKernelGGL(kv_scan_offsets_kernel, dim3(nblocks), dim3(1024), 0, s, k, n, d, blocksum, nblocks, off_base,
-                     off);
-  const dim3 grid((unsigned)((n + 3) / 4));
+  const int64_t nblocks = (n + kKvScanBlock - 1) / kKvScanBlock;
+  // Up to kScanFrom blocks every packing workgroup adds up the totals before it by itself (8 loads per thread at
+  // the most); beyond, that would grow with the square of n and one workgroup forms the prefix sums first.
+  constexpr int64_t kScanFrom = 2048;
+  const int scanned = nblocks > kScanFrom ? 1 : 0;
+  if (nblocks > 1)
+    hipLaunchKernelGGL(kv_scan_totals_kernel, dim3((unsigned)nblocks), dim3(kKvScanBlock), 0, s, k, n, d, blocksum, hdr);
+  if (scanned) hipLaunchKernelGGL(kv_scan_blocks_kernel, dim3(1), dim3(1024), 0, s, blocksum, (int)nblocks);
+  const int64_t* const totals = nblocks > 1 ? blocksum : nullptr;
+  const dim3 grid((unsigned)((n + kKvPackTokens - 1) / kKvPackTokens));
   if (dtype == LMHEAD_BF16)
-    hipLaunchKernelGGL(kv_pack_kernel<__bf16>, grid, dim3(256), 0, s, static_cast<const __bf16*>(xt), k, off, n, d,
-                       static_cast<__bf16*>(packed), capacity, hdr);
+    hipLaunchKernelGGL(kv_pack_kernel<__bf16>, grid, dim3(256), 0, s, static_cast<const __bf16*>(xt), k, totals, scanned,
+                       n, d, off_base, off, static_cast<__bf16*>(packed), capacity, hdr);
   else
-    hipLaunchKernelGGL(kv_pack_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(xt), k, off, n, d,
-                       static_cast<float*>(packed), capacity, hdr);
+    hipLaunchKernelGGL(kv_pack_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(xt), k, totals, scanned, n,
+                       d, off_base, off, static_cast<float*>(packed), capacity, hdr);
   return hipGetLastError();
 }
 
-hipError_t launch_kv_order(int dtype, const int32_t* k, const int64_t* off, int64_t bytes, int64_t n, int64_t ncap,
-                           int d, int nbuckets, int32_t* hist, int32_t* order, uint32_t* pos_off, int32_t* pos_len,
-                           WsHeader* hdr, hipStream_t s) {
+hipError_t launch_kv_order(int dtype, const KvCount& c, const int64_t* off, int64_t bytes, int64_t ncap, int32_t* order,
+                           uint32_t* pos_off, int32_t* pos_len, WsHeader* hdr, hipStream_t s) {
   const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
-  const unsigned fill_blocks = (unsigned)((ncap + 255) / 256);
-  hipLaunchKernelGGL(kv_fill_i32_kernel, dim3((unsigned)((3 * nbuckets + 255) / 256)), dim3(256), 0, s, hist,
-                     (int64_t)3 * nbuckets, 0);
-  hipLaunchKernelGGL(kv_fill_i32_kernel, dim3(fill_blocks), dim3(256), 0, s, order, ncap, -1);
-  hipLaunchKernelGGL(kv_fill_i32_kernel, dim3(fill_blocks), dim3(256), 0, s, reinterpret_cast<int32_t*>(pos_off),
-                     ncap, (int32_t)0x80000000u);
-  hipLaunchKernelGGL(kv_fill_i32_kernel, dim3(fill_blocks), dim3(256), 0, s, pos_len, ncap, 0);
-  hipLaunchKernelGGL(kv_hist_kernel, dim3((unsigned)((n + 4095) / 4096)), dim3(256), nbuckets * sizeof(int32_t), s,
-                     k, n, d, esz, nbuckets, hist);
-  hipLaunchKernelGGL(kv_bucket_start_kernel, dim3(1), dim3(64), 0, s, hist, nbuckets);
-  hipLaunchKernelGGL(kv_scatter_kernel, dim3((unsigned)((n + 4095) / 4096)), dim3(256),
-                     2 * nbuckets * sizeof(int32_t), s, k, off, n, d, esz, bytes, nbuckets, hist, order, pos_off,
-                     pos_len, hdr);
+  hipLaunchKernelGGL(kv_scatter_kernel, dim3((unsigned)c.blocks), dim3(256), 2 * c.nbuckets * sizeof(int32_t), s, c.k,
+                     off, c.n, ncap, c.d, esz, bytes, c.nbuckets, c.hist, c.blocks, c.per_block, order, pos_off, pos_len,
+                     hdr);
   return hipGetLastError();
 }
 

@@ -8,7 +8,8 @@ namespace lmhead {
 
 constexpr int kKvMaxD = 8192;
 constexpr int kKvRetainBlocks = 2048;   // blocks of the retain-rate sums: 256 threads each, one resident round
-constexpr int kKvScanBlock = 1024;   // tokens per block of the offset scan
+constexpr int kKvScanBlock = 256;    // tokens per block of the offset scan
+constexpr int kKvCountBlocks = 256;    // most blocks of the counts per contraction length
 
 // Sticky error bits of this path (same header word as the LM-head path).
 constexpr int kErrKvCount = 4;       // a k outside [0, d]
@@ -47,7 +48,7 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
   L.order = take((size_t)L.ncap * 4);
   L.pos_off = take((size_t)L.ncap * 4);
   L.pos_len = take((size_t)L.ncap * 4);
-  L.hist = take((size_t)L.nbuckets * 3 * 4);          // counts, start positions, cursors
+  L.hist = take((size_t)kKvCountBlocks * L.nbuckets * 4);   // tokens per block and bucket
   L.blocksum = take((size_t)(L.ncap / kKvScanBlock + 2) * 8);
   L.red = take((size_t)kKvRetainBlocks * 2 * 8);      // per-block partial sums of the retain rate
   L.total = off;
@@ -161,19 +162,50 @@ hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
 hipError_t launch_kv_mask(int dtype, const float* logits, const float* b, const void* xt, int64_t n, int d,
                           float tau, bool literal, int32_t* k, float* m, void* xhat, hipStream_t s);
 
-// off = off_base + exclusive prefix sum of roundup(k, 8); then the segments are copied.
+// off = off_base + exclusive prefix sum of roundup(k, 8), and the segments are copied; clears the header.
 hipError_t launch_kv_store(int dtype, const void* xt, const int32_t* k, int64_t n, int d, int64_t off_base,
                            int64_t* off, void* packed, int64_t capacity, int64_t* blocksum, WsHeader* hdr,
                            hipStream_t s);
 
-// order = tokens sorted by descending number of K-steps (ceil(k * esz / 128)), padded with -1 up to
-// ncap; pos_off / pos_len = byte offset and byte length (k rounded up to the granule) of each sorted
-// position's segment in a store of `bytes` readable bytes (0x80000000 / 0 for padding and for
-// segments that do not lie inside it, which also set the error word).  hist holds 3 * nbuckets ints
-// of scratch.
-hipError_t launch_kv_order(int dtype, const int32_t* k, const int64_t* off, int64_t bytes, int64_t n, int64_t ncap,
-                           int d, int nbuckets, int32_t* hist, int32_t* order, uint32_t* pos_off, int32_t* pos_len,
-                           WsHeader* hdr, hipStream_t s);
+// Tokens per K-step bucket (ceil(k * esz / 128)), counted in `blocks` blocks of per_block tokens:
+// hist[block][bucket].  Blocks of 1024 tokens, larger ones beyond kKvCountBlocks of them.
+struct KvCount {
+  const int32_t* k;
+  int64_t n;
+  int d, nbuckets, blocks, per_block;
+  int32_t* hist;
+};
+static inline KvCount make_kv_count(const int32_t* k, int64_t n, int d, int nbuckets, int32_t* hist) {
+  const int64_t per = (n + (int64_t)kKvCountBlocks * 1024 - 1) / ((int64_t)kKvCountBlocks * 1024) * 1024;
+  return {k, n, d, nbuckets, (int)((n + per - 1) / per), (int)per, hist};
+}
+
+// One operand copy: out[r][c] = in[r][c], or out[c][r] when transposed, for r < rows, c < cols; zero up to rows_p x
+// cols_p (of the source's orientation).  Rows of both sides 16-byte aligned; cols, cols_p, rows_p multiples of 64.
+struct KvCopy {
+  const void* in;
+  int64_t ld_in, rows, rows_p;
+  int cols, cols_p;
+  void* out;
+  int64_t ld_out;
+  bool transposed;
+  int tiles;           // set by the launcher
+};
+constexpr int kKvMaxCopies = 4;
+struct KvPrepareArgs {
+  WsHeader* hdr;       // cleared unless null
+  KvCopy job[kKvMaxCopies];
+  int njobs;
+  KvCount count;       // blocks = 0: nothing to count
+};
+hipError_t launch_kv_prepare(int dtype, const KvPrepareArgs& a, hipStream_t s);
+
+// order = tokens sorted by descending number of K-steps, padded with -1 up to ncap; pos_off / pos_len = byte offset and
+// byte length (k rounded up to the granule) of each sorted position's segment in a store of `bytes` readable bytes
+// (0x80000000 / 0 for padding; 0x80000000 for segments that do not lie inside it, which also set the error word).
+// The counts have been made by launch_kv_prepare.
+hipError_t launch_kv_order(int dtype, const KvCount& c, const int64_t* off, int64_t bytes, int64_t ncap, int32_t* order,
+                           uint32_t* pos_off, int32_t* pos_len, WsHeader* hdr, hipStream_t s);
 
 // Retain rates; clears the header.
 hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, float alpha, float* out,
@@ -191,16 +223,5 @@ hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, co
 // out[j] (+)= sum_r part[r][j] for j < len (rows of pitch row_pitch floats), in a fixed order.
 hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, int64_t len, float* out,
                               bool accumulate, hipStream_t s);
-
-// out[r][c] = in[r][c] for r < rows, c < cols; zero up to [rows_p x ld_out].
-hipError_t launch_kv_pad_copy(int dtype, const void* in, int64_t ld_in, int rows, int cols, void* out,
-                              int64_t ld_out, int rows_p, hipStream_t s);
-
-// out[c][r] = in[r][c] for r < rows, c < cols; zero up to [cols_p x rows_p] (pitch ld_out).  Rows of both
-// sides 16-byte aligned; cols, cols_p, rows_p multiples of 64.
-hipError_t launch_kv_transpose(int dtype, const void* in, int64_t ld_in, int64_t rows, int cols, void* out,
-                               int64_t ld_out, int64_t rows_p, int cols_p, hipStream_t s);
-
-hipError_t launch_kv_clear_header(WsHeader* hdr, hipStream_t s);
 
 }  // namespace lmhead

@@ -123,3 +123,50 @@ def test_kv_retain_rate_over_block_shares(n, d):
     # k is summed exactly; of m at most a few hundred values enter one fp32 sum: well under 256 * 2^-24
     np.testing.assert_allclose(out.cpu().numpy(), [hard, soft, 0.5 * soft ** 2], rtol=1.5e-5)
     np.testing.assert_allclose(gm.cpu().numpy(), soft / (n * d), rtol=1.5e-5)
+
+
+# packing groups of 16 tokens, scan blocks of 256, the step to a separate prefix sum (2048 blocks), counting blocks of 1024
+@pytest.mark.parametrize("dtype,d,n", [("bf16", 64, 1), ("bf16", 128, 15), ("bf16", 64, 16), ("f32", 64, 17),
+                                       ("bf16", 64, 255), ("bf16", 64, 256), ("bf16", 64, 257), ("f32", 128, 1025),
+                                       ("bf16", 64, 2049), ("bf16", 64, 524288), ("bf16", 64, 524300)])
+@pytest.mark.parametrize("off_base", [0, 1000 * 8])
+def test_kv_store_and_grouping_over_token_blocks(dtype, d, n, off_base):
+    import torch
+    import paper_2603_04411_amd as L
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    xt = torch.randn(n, d, generator=g, device="cuda").to(tdt)
+    k = torch.randint(0, d + 1, (n,), generator=g, dtype=torch.int32, device="cuda")
+    desc = L.make_kv_desc(n, d, dtype)
+    ws = torch.full((L.dynakv_workspace_bytes(desc),), 0xA5, dtype=torch.uint8, device="cuda")
+    cap = off_base + n * d
+    off = torch.full((n + 1,), -1, dtype=torch.int64, device="cuda")
+    packed = torch.full((cap,), 5.0, dtype=tdt, device="cuda")
+    L.dynakv_store(desc, xt, k, off_base, off, packed, cap, ws)
+    assert L.dynakv_check(ws) == 0
+    seg = (k.long() + 7) // 8 * 8
+    want_off = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), seg.cumsum(0)]) + off_base
+    assert torch.equal(off, want_off)
+    j = torch.arange(d, device="cuda")[None, :]
+    want = torch.full_like(packed, 5.0)
+    at = (want_off[:-1, None] + j)
+    want[at[j < seg[:, None]]] = torch.where(j < k[:, None], xt, torch.zeros((), dtype=tdt, device="cuda"))[j < seg[:, None]]
+    assert torch.equal(packed, want)
+    # the identity as U^-1: the reconstruction returns the kept components exactly, every token in its own row
+    eye = torch.eye(d, device="cuda").to(tdt)
+    xbar = torch.full((n, d), 3.0, dtype=tdt, device="cuda")
+    L.dynakv_reconstruct(desc, packed, cap, off, k, eye, xbar, ws)
+    assert L.dynakv_check(ws) == 0
+    assert torch.equal(xbar, torch.where(j < k[:, None], xt, torch.zeros((), dtype=tdt, device="cuda")))
+    # one element too little room: the last non-empty segment is refused and reported, nothing else changes
+    if int(seg.sum()) > 0:
+        last = int((seg > 0).nonzero()[-1])
+        packed.fill_(5.0)
+        L.dynakv_store(desc, xt, k, off_base, off, packed, int(want_off[-1]) - 1, ws)
+        assert L.dynakv_check(ws) == -6
+        want[int(want_off[last]):] = 5.0
+        assert torch.equal(packed, want)
+        bad = k.clone()
+        bad[n // 2] = d + 1
+        L.dynakv_store(desc, xt, bad, off_base, off, packed, cap, ws)
+        assert L.dynakv_check(ws) == -6
