@@ -9,6 +9,7 @@
 #include <atomic>
 
 #include "../../include/lmhead.h"
+#include "tile_map.h"
 
 namespace lmhead {
 
@@ -26,11 +27,58 @@ constexpr int kErrTok = 2;  // a token id outside [0, V) on a valid slot
 struct WsHeader {
   int32_t err;  // sticky error bits
   int32_t nv;   // number of valid slots N_v (written by the index kernel)
-  int32_t pad[62];
+  int32_t ksplit;   // slices of dH's contraction (written by the index kernel of the backward)
+  int32_t pad[61];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte line");
 
 static inline size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
+
+// Tile edges of the LM-head kernels (four wavefronts per tile whatever the edge; 256 / edge workgroups share a compute
+// unit).  256 needs the fewest operand bytes per flop, the only edge the vector L1 feeds at full bf16 rate.  The smaller
+// ones give more and shorter tiles when 256 x 256 would leave most of the chip idle, waste less on padding when
+// there are few tokens, and two or four workgroups on a compute unit overlap one's stores with another's loads.
+// Times in us (n = slots, about 60 % of them valid; forward / dW; dH below):
+//                                            edge 256        edge 128        edge 64
+//   n 256   d 1024 V 8000   bf16            32.1 / 37.0     15.7 / 14.4     13.1 / 15.9
+//   n 1024  d 1024 V 20000  bf16            36.9 / 66.6     40.1 / 49.3     62.1 / 49.7
+//   n 192   d 2048 V 151936 bf16             239 / 310       215 / 295       218 / 296
+//   n 64    d 2048 V 151936 bf16             243 / 271       213 / 256       188 / 287
+//   n 384   d 2048 V 151936 bf16, all valid  296 / 432       288 / 497
+//   n 256   d 256  V 4096   fp32            72.9 / 32.0     23.5 / 19.9     11.4 / 10.4
+//   n 1024  d 512  V 20000  fp32             135 / 162       130 / 125       114 / 112
+//   n 4096  d 1024 V 16000  fp32             721 / 558       609 / 567       591 / 595
+// fp32 products are matrix-core bound on any edge, so there the edge only has to keep the chip evenly filled.
+static inline int64_t tiles_of(int64_t m, int64_t n, int edge) { return ((m + edge - 1) / edge) * ((n + edge - 1) / edge); }
+// the smallest edge whose tiles run in one round, two to a compute unit
+static inline int one_round_edge(int64_t m, int64_t n) {
+  return tiles_of(m, n, 64) <= 2 * kComputeUnits ? 64 : tiles_of(m, n, 128) <= 2 * kComputeUnits ? 128 : kTile;
+}
+// Logits (forward and dZ): m = vocabulary rows of all policies, n = token slots.
+static inline int logits_edge(bool f32, int64_t m, int64_t n) {
+  if (f32 && tiles_of(m, n, kTile) <= 4 * kComputeUnits) return 64;
+  const int e = n <= 64 ? 64 : n <= 192 ? 128 : kTile;   // few tokens: one tile of them, with little padding
+  const int r = one_round_edge(m, n);
+  return r < e ? r : e;
+}
+// dW: m = d, rows = vocabulary rows of a chunk, n = token slots (the contraction).
+static inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
+  const int64_t t = tiles_of(m, rows, kTile);
+  if (f32) return t <= kComputeUnits * 7 / 8 ? 64 : kTile;
+  const int r = one_round_edge(m, rows);
+  return r < kTile ? r : (n <= 192 || t <= 2 * kComputeUnits) ? 128 : kTile;
+}
+// dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
+// slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not
+// exceed the tokens by much.  (n 1024 d 1024 V 20000: 68.9 / 48.8 / 59.9 us on edge 256 / 128 / 64; n 256 V 8000:
+// 40.5 / 25.6 / 23.1; n 256 d 256 V 4096 fp32: 133 / 28 / 17.7; n 4096 d 1024 V 16000 fp32: 736 / 702 / 623.)
+static inline int dh_edge(bool f32, int64_t m, int64_t n, int64_t ksteps) {
+  if (f32) return tiles_of(m, n, kTile) <= 4 * kComputeUnits ? 64 : kTile;
+  const int64_t slices = ksteps / 32 > 0 ? ksteps / 32 : 1;
+  if (n > 128 && tiles_of(m, n, kTile) * slices >= kComputeUnits) return kTile;
+  if (n > 64 && tiles_of(m, n, 128) * slices >= kComputeUnits) return 128;
+  return 64;
+}
 
 // Byte offsets of every workspace region for one descriptor.  All regions are
 // 256-byte aligned.  "cap" sizes are worst cases (every slot valid) because
@@ -43,14 +91,15 @@ struct WsLayout {
   int64_t dp;       // d rounded up to the tile
   int64_t Vc;       // vocabulary chunk of the backward (multiple of the tile)
   int64_t nchunks;  // number of vocabulary chunks
-  int64_t ntiles;   // vocabulary tiles = planes of per-tile softmax statistics per row
+  int edge;         // tile edge of the logits kernels
+  int edge_w;       // tile edge of dW
+  int64_t ntiles;   // vocabulary tiles of `edge` = planes of per-tile softmax statistics per row
   // Row pitches (elements) of the workspace matrices.  Each is its logical width plus one
   // 128-byte line: a power-of-two pitch would put every row of a tile on the same L2
   // channel and set (the token-major operands have a pitch of Ncap elements, often 2^k).
   int64_t ldHc, ldHcT, ldWT, ldZ, ldZT;
   int64_t ld8;      // pitch (bytes) of the e4m3 operand copies: d + one 128-byte line
-  int ksplit;       // dH: slices of the contraction per output tile (> 1 only when the tile grid
-                    // alone would leave most of the chip idle); partial tiles go to dHpart
+  DhSplit dh;           // dH: tiles and how their contraction may be cut; partial tiles go to dHpart
   size_t dHpart;
   size_t dWpart;        // partial tiles of the dW launches that split a remainder of vocabulary tiles
   size_t dWpart_bytes;
@@ -90,7 +139,10 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   if (vc > L.Vp) vc = L.Vp;
   L.Vc = vc;
   L.nchunks = (L.Vp + vc - 1) / vc;
-  L.ntiles = L.Vp / kTile;
+  const bool f32 = d->dtype == LMHEAD_F32;
+  L.edge = (d->flags & LMHEAD_FLAG_FP8_LOGITS) ? kTile : logits_edge(f32, npol * (int64_t)d->V, L.N);
+  L.edge_w = dw_edge(f32, d->d, vc, L.N);
+  L.ntiles = (d->V + L.edge - 1) / L.edge;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
@@ -117,17 +169,13 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.WT = take((size_t)L.dp * L.ldWT * L.esz);
   L.dZ = take((size_t)L.Ncap * L.ldZ * L.esz);
   L.dZT = take((size_t)L.Vc * L.ldZT * L.esz);
-  // dH has (d / 256) x (tokens / 256) output tiles.  Below about four per compute unit the last
-  // round of workgroups is mostly empty, so the contraction of each tile is cut into ksplit slices
-  // that run as separate workgroups and are summed afterwards in a fixed order.
   {
-    const int64_t tiles = (L.dp / kTile) * (L.Ncap / kTile);
-    int64_t ks = tiles >= 1024 ? 1 : (1536 + tiles - 1) / tiles;
-    if (ks > 8) ks = 8;
-    L.ksplit = (int)ks;
-    // a bf16 dH is accumulated in these fp32 buffers too and rounded once at the end
-    const bool need = ks > 1 || (d->flags & LMHEAD_FLAG_DH_BF16) != 0;
-    L.dHpart = take(need ? (size_t)ks * L.Ncap * L.dp * 4 : 0);
+    L.dh.ksteps = (int)(L.Vc * L.esz / 128);
+    L.dh.edge = dh_edge(f32, d->d, L.N, L.dh.ksteps);
+    L.dh.m_tiles = (d->d + L.dh.edge - 1) / L.dh.edge;
+    // slice tiles for any N_v; a bf16 dH is accumulated in these fp32 buffers too and rounded once at the end
+    const int64_t tiles = dh_split_tiles(L.dh, (L.N + L.dh.edge - 1) / L.dh.edge, (d->flags & LMHEAD_FLAG_DH_BF16) != 0);
+    L.dHpart = take((size_t)tiles * L.dh.edge * L.dh.edge * 4);
   }
   // dW: the vocabulary tiles of a chunk that would start a mostly empty round of workgroups are contracted
   // in slices instead (see lmhead_logprob_bwd); slices x rows x d of them never exceed compute units x 64 Ki floats
@@ -144,9 +192,11 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
 
 // ---- launchers (each enqueues on `s` and returns hipGetLastError()) --------------------
 
-// lens -> cu_len, header.nv, mask, row_slot (padded with -1 up to the next tile multiple).
+// lens -> cu_len, header.nv, mask, row_slot (padded with -1 up to the next tile multiple); with `split` also
+// header.ksplit, the cheapest allowed number of slices for N_v.
 hipError_t launch_index(const int32_t* len, int R, int T, WsHeader* hdr, int32_t* cu_ws,
-                        int32_t* row_slot, uint8_t* mask_out, int32_t* cu_out, hipStream_t s);
+                        int32_t* row_slot, uint8_t* mask_out, int32_t* cu_out, hipStream_t s,
+                        const DhSplit* split = nullptr);
 
 // Gathers the valid rows of H into the dense, zero-padded Hc[Ncap x d]; also compacts tok
 // (range-checked), and optionally g_logp and lse.  The npol vectors zy[p * Ncap + .] are cleared and
@@ -170,7 +220,8 @@ struct FwdArgs {
   int64_t ldW;
   int d, V;
   int64_t Ncap;
-  int ntiles;          // vocabulary tiles (one per workgroup and policy)
+  int edge;            // tile edge: 64, 128 or 256 (256 for e4m3)
+  int ntiles;          // vocabulary tiles of that edge (one per workgroup and policy)
   const int32_t* tok_c;
   const WsHeader* hdr;
   float* part;         // [npol][3][ntiles][Ncap]: per-tile (max, sum exp, sum exp*z) of each row
@@ -196,7 +247,8 @@ struct DzArgs {
   int64_t ldZ;    // pitch of dZ (elements)
   int64_t ldZT;   // pitch of dZT (elements)
   int c0;         // first vocabulary id of the chunk
-  int ntiles;     // vocabulary tiles in this chunk
+  int edge;       // tile edge: 64, 128 or 256 (256 for e4m3)
+  int ntiles;     // vocabulary tiles of kTile columns in this chunk
   const int32_t* tok_c;
   const float* g_c;
   const float* lse_c;
@@ -234,20 +286,23 @@ struct GemmTArgs {
   bool accumulate;
   int64_t n_tiles_cap; // grid extent over n
   const WsHeader* hdr;
-  int ksplit;          // slices of the contraction per output tile (>= 1)
-  float* part;         // non-null: slice s writes (part_accumulate: adds) its tile to part[s][n][m], dense
-  int64_t part_ld;     // rows of part_ld floats without the row map, and launch_splitk_reduce forms out
-  int64_t part_slice;  // from the slices.  part_slice = floats per slice.  Required when ksplit > 1.
-  bool part_accumulate;
+  int ksplit;          // slices of the contraction per output tile; 0: header.ksplit of them
+  float* part;         // slice s writes (part_accumulate: adds) its tile to part[s][n][m], dense rows of part_ld
+  int64_t part_ld;     // floats without the row map, and launch_splitk_reduce forms out from the slices.  Required
+  int64_t part_slice;  // when there can be several; with header.ksplit = 1 of them the tile goes to out instead
+  bool part_accumulate;   // unless part_single.  part_slice = floats per slice (header.ksplit: n tiles x edge x part_ld).
+  bool part_single;
   int edge;            // workgroup tile edge: 64, 128 or 256 (n_tiles_cap stays in units of kTile)
 };
 
 // out[row(n)][m] (+)= sum_s part[s][n][m] for n < n_valid, m < M, slices summed in order.  With a row map:
-// row(n) = rowmap[n] and n_valid = header.nv; without: row(n) = row_base + n and n_valid = n_cap.
+// row(n) = rowmap[n] and n_valid = header.nv; without: row(n) = row_base + n and n_valid = n_cap.  ksplit = 0:
+// header.ksplit slices of the n tiles of `edge` rows, and nothing to do when that is one and single_too is not set.
 // out is float, or bf16 when out_bf16 (then accumulate must be false).
 hipError_t launch_splitk_reduce(const float* part, int ksplit, int64_t part_slice, int64_t part_ld, int M,
                                 const int32_t* rowmap, const WsHeader* hdr, int64_t n_cap, void* out, int64_t ldo,
-                                bool accumulate, bool out_bf16, hipStream_t s, int64_t row_base = 0);
+                                bool accumulate, bool out_bf16, hipStream_t s, int64_t row_base = 0, int edge = 0,
+                                bool single_too = false);
 // Compute units of the current device (asked of the runtime once per device; 256 if it cannot be asked).
 int device_compute_units();
 // role: -1 = by use (dW when k_from_nv, else dH); 2 = parameter gradient of the KV gate (distinct kernel name).

@@ -144,6 +144,7 @@ static int forward(const lmhead_desc* desc, const void* H, const void* const* W,
   fa.d = desc->d;
   fa.V = desc->V;
   fa.Ncap = L.Ncap;
+  fa.edge = L.edge;
   fa.ntiles = (int)L.ntiles;
   fa.tok_c = w.at<int32_t>(L.tok_c);
   fa.hdr = hdr;
@@ -212,7 +213,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
   const int dt = desc->dtype;
 
   LM_TRY(launch_index(len, (int)L.R, desc->T, hdr, w.at<int32_t>(L.cu_len), w.at<int32_t>(L.row_slot),
-                      nullptr, nullptr, s));
+                      nullptr, nullptr, s, &L.dh));
   LM_TRY(launch_compact(dt, H, desc->ldH, desc->d, desc->V, tok, g_logp, lse, L.N, hdr,
                         w.at<int32_t>(L.row_slot), w.at<void>(L.Hc), L.ldHc, w.at<int32_t>(L.tok_c),
                         w.at<float>(L.g_c), w.at<float>(L.lse_c), w.at<float>(L.zy), w.at<int32_t>(L.gid), 1, L.Ncap, s));
@@ -250,6 +251,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     za.ldZ = L.ldZ;
     za.ldZT = L.ldZT;
     za.c0 = c0;
+    za.edge = L.edge;
     za.ntiles = ntiles;
     za.tok_c = w.at<int32_t>(L.tok_c);
     za.g_c = w.at<float>(L.g_c);
@@ -278,23 +280,18 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     ha.accumulate = c > 0;
     ha.n_tiles_cap = L.Ncap / kTile;
     ha.hdr = hdr;
-    ha.edge = kTile;
-    ha.ksplit = L.ksplit;
-    ha.part = (L.ksplit > 1 || dh16) ? w.at<float>(L.dHpart) : nullptr;
-    ha.part_ld = L.dp;
-    ha.part_slice = L.Ncap * L.dp;
+    ha.edge = L.dh.edge;
+    ha.ksplit = 0;
+    ha.part = w.at<float>(L.dHpart);
+    ha.part_ld = (int64_t)L.dh.m_tiles * L.dh.edge;
     ha.part_accumulate = dh16 && c > 0;   // a bf16 dH is summed over the chunks in the scratch slices
+    ha.part_single = dh16;
     {
       TimedLaunch tl(2, s);
       LM_TRY(launch_gemm_t(dt, ha, s));
-      if (dh16) {
-        if (c + 1 == (int)L.nchunks)
-          LM_TRY(launch_splitk_reduce(ha.part, L.ksplit, ha.part_slice, ha.part_ld, desc->d, ha.rowmap, hdr,
-                                      L.Ncap, dH, desc->d, false, true, s));
-      } else if (L.ksplit > 1) {
-        LM_TRY(launch_splitk_reduce(ha.part, L.ksplit, ha.part_slice, ha.part_ld, desc->d, ha.rowmap, hdr, L.Ncap,
-                                    dH, desc->d, c > 0, false, s));
-      }
+      if (!dh16 || c + 1 == (int)L.nchunks)
+        LM_TRY(launch_splitk_reduce(ha.part, 0, 0, ha.part_ld, desc->d, ha.rowmap, hdr, L.Ncap, dH, desc->d,
+                                    !dh16 && c > 0, dh16, s, 0, L.dh.edge, dh16));
     }
 
     // dW[c0 + n][m] = sum_i Hc^T[m][i] dZ^T[n][i]
@@ -313,14 +310,14 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     wa.ldo = desc->d;
     wa.accumulate = (desc->flags & LMHEAD_FLAG_ACCUM_DW) != 0;
     wa.hdr = hdr;
-    wa.edge = kTile;
+    wa.edge = L.edge_w;
     // Every output tile is one workgroup and the compute units take them a round at a time.  The vocabulary
     // tiles of this chunk that would start a mostly empty last round (with d / 256 tiles along d, 16 of them
     // fill the 256 compute units at d = 4096; a chunk of 18 leaves 2) are launched apart, their contraction
     // over the tokens cut into as many slices as make that round full; the slices are summed in a fixed order.
     const int m_tiles = (int)(L.dp / kTile), cus = device_compute_units();
     int t_rem = 0, ks = 1;
-    if (m_tiles <= cus && cus % m_tiles == 0) {
+    if (wa.edge == kTile && m_tiles <= cus && cus % m_tiles == 0) {
       t_rem = ntiles % (cus / m_tiles);
       ks = t_rem > 0 ? cus / (t_rem * m_tiles) : 1;
       if (ks > 8) ks = 8;

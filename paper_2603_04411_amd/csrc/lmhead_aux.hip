@@ -19,9 +19,11 @@ constexpr float kLn2 = 0.6931471805599453f;
 // ---- indexing --------------------------------------------------------------------------
 
 // One workgroup: exclusive prefix sum of the (clamped) lengths.
+// `want_split`: the wavefront's lanes also price one number of slices of dH's contraction each; the cheapest (fewest
+// slices on a tie) goes to the header.
 __global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restrict__ len, int R, int T,
                                                         WsHeader* hdr, int32_t* __restrict__ cu_ws,
-                                                        int32_t* __restrict__ cu_out) {
+                                                        int32_t* __restrict__ cu_out, int want_split, DhSplit split) {
   __shared__ int32_t wsum[16];
   __shared__ int32_t carry_s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -62,6 +64,17 @@ __global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restric
     __syncthreads();
   }
   if (bad) atomicOr(&hdr->err, kErrLen);
+  if (want_split && wave == 0) {
+    const int n_tiles = (carry_s + split.edge - 1) / split.edge;
+    const int ks = lane + 1;
+    static_assert(kMaxSplit == 64, "one number of slices per lane");
+    const float cost = dh_split_allowed(split, n_tiles, ks) ? dh_split_cost(split, n_tiles, ks) : __builtin_huge_valf();
+    float best = cost;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o));
+    const uint64_t ties = __ballot(cost == best);
+    if (lane == 0) hdr->ksplit = __ffsll((unsigned long long)ties);
+  }
   if (tid == 0) {
     const int total = carry_s;
     cu_ws[R] = total;
@@ -364,29 +377,44 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
                                                             const int32_t* __restrict__ rowmap,
                                                             const WsHeader* __restrict__ hdr, int64_t n_cap,
                                                             int64_t row_base, TO* __restrict__ out, int64_t ldo,
-                                                            int accumulate) {
-  const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= (rowmap ? (int64_t)hdr->nv : n_cap)) return;
-  const int64_t row = rowmap ? (int64_t)rowmap[n] : row_base + n;
-  if (row < 0) return;
+                                                            int accumulate, int edge, int single_too) {
+  const int64_t n_valid = rowmap ? (int64_t)hdr->nv : n_cap;
+  if (ksplit == 0) {
+    ksplit = hdr->ksplit;
+    if (ksplit == 1 && !single_too) return;
+    part_slice = (n_valid + edge - 1) / edge * edge * part_ld;
+  }
   const int lane = threadIdx.x & 63;
-  for (int m = lane * 4; m < M; m += 256) {
-    float4 v = *reinterpret_cast<const float4*>(part + n * part_ld + m);
-    for (int s = 1; s < ksplit; ++s) {
-      const float4 p = *reinterpret_cast<const float4*>(part + (size_t)s * part_slice + n * part_ld + m);
-      v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-    }
-    if constexpr (sizeof(TO) == 4) {
-      float4* dst = reinterpret_cast<float4*>(out + row * ldo + m);
-      if (accumulate) {
-        const float4 o = *dst;
-        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+  for (int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); n < n_valid; n += (int64_t)gridDim.x * 4) {
+    const int64_t row = rowmap ? (int64_t)rowmap[n] : row_base + n;
+    if (row < 0) continue;
+    for (int m = lane * 4; m < M; m += 256) {
+      const float* const p = part + n * part_ld + m;
+      float4 v = *reinterpret_cast<const float4*>(p);
+      int s = 1;
+      for (; s + 3 < ksplit; s += 4) {
+        float4 q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const float4*>(p + (size_t)(s + u) * part_slice);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { v.x += q[u].x; v.y += q[u].y; v.z += q[u].z; v.w += q[u].w; }
       }
-      *dst = v;
-    } else {
-      typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-      const bf16x4_t h = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
-      *reinterpret_cast<bf16x4_t*>(out + row * ldo + m) = h;
+      for (; s < ksplit; ++s) {
+        const float4 q = *reinterpret_cast<const float4*>(p + (size_t)s * part_slice);
+        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+      }
+      if constexpr (sizeof(TO) == 4) {
+        float4* dst = reinterpret_cast<float4*>(out + row * ldo + m);
+        if (accumulate) {
+          const float4 o = *dst;
+          v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+        }
+        *dst = v;
+      } else {
+        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+        const bf16x4_t h = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
+        *reinterpret_cast<bf16x4_t*>(out + row * ldo + m) = h;
+      }
     }
   }
 }
@@ -412,8 +440,9 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(TO* __restrict__ dH, int
 }  // namespace
 
 hipError_t launch_index(const int32_t* len, int R, int T, WsHeader* hdr, int32_t* cu_ws,
-                        int32_t* row_slot, uint8_t* mask_out, int32_t* cu_out, hipStream_t s) {
-  hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, len, R, T, hdr, cu_ws, cu_out);
+                        int32_t* row_slot, uint8_t* mask_out, int32_t* cu_out, hipStream_t s, const DhSplit* split) {
+  hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, len, R, T, hdr, cu_ws, cu_out, split ? 1 : 0,
+                     split ? *split : DhSplit{});
   const int64_t N = (int64_t)R * T;
   const unsigned blocks = (unsigned)((N + kTile + 255) / 256);
   hipLaunchKernelGGL(fill_index_kernel, dim3(blocks), dim3(256), 0, s, len, R, T, cu_ws, row_slot, mask_out);
@@ -477,14 +506,20 @@ hipError_t launch_quantize_e4m3(int dtype, const void* in, int64_t ld_in, int64_
 
 hipError_t launch_splitk_reduce(const float* part, int ksplit, int64_t part_slice, int64_t part_ld, int M,
                                 const int32_t* rowmap, const WsHeader* hdr, int64_t n_cap, void* out, int64_t ldo,
-                                bool accumulate, bool out_bf16, hipStream_t s, int64_t row_base) {
-  const dim3 grid((unsigned)((n_cap + 3) / 4));
+                                bool accumulate, bool out_bf16, hipStream_t s, int64_t row_base, int edge,
+                                bool single_too) {
+  // rows are taken in turn by at most one resident round of workgroups: most of n_cap may turn out to be padding,
+  // or the whole call idle
+  constexpr int64_t kMost = 2048;
+  const int64_t need = (n_cap + 3) / 4;
+  const dim3 grid((unsigned)(need < kMost ? need : kMost));
   if (out_bf16)
     hipLaunchKernelGGL(splitk_reduce_kernel<__bf16>, grid, dim3(256), 0, s, part, ksplit, part_slice, part_ld, M,
-                       rowmap, hdr, n_cap, row_base, static_cast<__bf16*>(out), ldo, 0);
+                       rowmap, hdr, n_cap, row_base, static_cast<__bf16*>(out), ldo, 0, edge, single_too ? 1 : 0);
   else
-    hipLaunchKernelGGL(splitk_reduce_kernel<float>, grid, dim3(256), 0, s, part, ksplit, part_slice, part_ld, M,
-                       rowmap, hdr, n_cap, row_base, static_cast<float*>(out), ldo, accumulate ? 1 : 0);
+    hipLaunchKernelGGL(splitk_reduce_kernel<float>, grid, dim3(256), 0, s, part, ksplit, part_slice, part_ld, M, rowmap,
+                       hdr, n_cap, row_base, static_cast<float*>(out), ldo, accumulate ? 1 : 0, edge,
+                       single_too ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -52,9 +52,9 @@ __device__ inline void merge_stats(float& m, float& s, float& t, float m2, float
   m = mn;
 }
 
-template <typename E>
-__global__ __launch_bounds__(Tile<E>::NT) void fwd_kernel(FwdArgs a) {
-  using G = Tile<E, kLeadFwd>;
+template <typename E, int Edge>
+__global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void fwd_kernel(FwdArgs a) {
+  using G = Tile<E, kLeadFwd, Edge>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nv = a.hdr->nv;
   const int nblk = (nv + G::BN - 1) / G::BN;
@@ -151,13 +151,14 @@ __global__ __launch_bounds__(Tile<E>::NT) void fwd_kernel(FwdArgs a) {
     // is folded into the constants of the group instead of being applied per element
     const float zscale = a.zscale;
     const float kz = kLog2e * zscale;
-    constexpr int BPC = 16 / G::VB;            // blocks per group of 16 values
-    static_assert(G::TM % BPC == 0, "groups of 16 values");
+    constexpr int BPC = 16 / G::VB < G::TM ? 16 / G::VB : G::TM;   // blocks per group
+    constexpr int GV = BPC * G::VB;            // values per group: 16 (8 in the 64 wide bf16 tile)
+    static_assert(G::TM % BPC == 0 && GV % 2 == 0, "whole groups");
     auto group_stats = [&](auto full_tag, auto ent_tag, int ic, int j, float& m_run, float& s_run, float& t_run) {
       constexpr bool kFull = decltype(full_tag)::value;
       constexpr bool kEnt = decltype(ent_tag)::value;   // the third accumulator (sum exp * z) feeds the entropy only
-      float z[16];
-      bool ok[16];
+      float z[GV];
+      bool ok[GV];
 #pragma unroll
       for (int b = 0; b < BPC; ++b)
 #pragma unroll
@@ -167,14 +168,14 @@ __global__ __launch_bounds__(Tile<E>::NT) void fwd_kernel(FwdArgs a) {
         }
       float tmax = fmaxf(z[0], z[1]);
 #pragma unroll
-      for (int v = 2; v < 16; v += 2) tmax = fmaxf(tmax, fmaxf(z[v], z[v + 1]));
+      for (int v = 2; v < GV; v += 2) tmax = fmaxf(tmax, fmaxf(z[v], z[v + 1]));
       const float mn = fmaxf(m_run, tmax * zscale);
       const float ms = (mn == kNegInf) ? 0.f : mn;
       const float sc = fast_exp2((m_run - ms) * kLog2e);
       const float bias = -ms * kLog2e;
       float ss = 0.f, ts = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < GV; ++v) {
         const float e = fast_exp2(fmaf(z[v], kz, bias));   // exp2(-inf) = 0 on padding rows
         ss += e;
         if constexpr (kEnt) ts = fmaf(e, ok[v] ? z[v] : 0.f, ts);
@@ -266,14 +267,14 @@ struct Store4<f32_tag> {
   __device__ static inline void one(void* p, float a) { *reinterpret_cast<float*>(p) = a; }
 };
 
-// Row order of the W tile in LDS for the 16x16-block dZ kernel.  LDS row R = 128 w + 16 i + r feeds
-// row r of MFMA block i of wave row w, and accumulator element v of lane group q belongs to block row
-// r = 4 q + v.  Loading vocabulary row 128 w + 32 (i / 2) + 8 q + 4 (i % 2) + v there makes the eight
-// values that a lane holds in blocks 2a and 2a + 1 the vocabulary rows 128 w + 32 a + 8 q + [0, 8) of its
+// Row order of the W tile in LDS for the 16x16-block dZ kernel.  LDS row R = WM w + 16 i + r feeds
+// row r of MFMA block i of wave row w (WM rows per wave row, a multiple of 32), and accumulator element v of lane
+// group q belongs to block row r = 4 q + v.  Loading vocabulary row WM w + 32 (i / 2) + 8 q + 4 (i % 2) + v there makes
+// the eight values that a lane holds in blocks 2a and 2a + 1 the vocabulary rows WM w + 32 a + 8 q + [0, 8) of its
 // token: 16 bytes of a dZ row, stored straight from registers.
 struct DzRows {
   __device__ static constexpr int tile_row_of_lds_row(int R) {
-    return (R & ~127) + 32 * ((R >> 5) & 3) + 8 * ((R >> 2) & 3) + 4 * ((R >> 4) & 1) + (R & 3);
+    return (R & ~31) + 8 * ((R >> 2) & 3) + 4 * ((R >> 4) & 1) + (R & 3);
   }
   // compile-time part of the tile row of element v of block i (the rest depends on the lane only)
   __device__ static constexpr int offset(int i, int v) { return 32 * (i >> 1) + 4 * (i & 1) + v; }
@@ -390,31 +391,31 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
   // [vocabulary row][token] rows -> dZT
   constexpr int CPR = G::BN * 2 / 16;            // 16-byte chunks per staged row
   constexpr int RPP = G::NT / CPR;               // rows per pass
-  static_assert(RPP == 8, "the rows of a pass share their bank permutation");
   const int c = threadIdx.x % CPR;
   const int rin = threadIdx.x / CPR;
 #pragma unroll 8
   for (int r0 = 0; r0 < G::BM; r0 += RPP) {
     const int m = r0 + rin;
-    const int f = (r0 >> 3) & 3;
+    const int f = (m >> 3) & 3;
     const u32x4_t v = *reinterpret_cast<const u32x4_t*>(smem + m * P2 + ((((c >> 1) ^ f) << 5) | ((c & 1) << 4)));
     *reinterpret_cast<u32x4_t*>(dZT + ((size_t)(mrel0 + m) * a.ldZT + n0 + c * 8) * 2) = v;
   }
 }
 
 // E: type of the operands Hc and W (possibly e4m3 copies); EO: type of dZ / dZT.
-template <typename E, typename EO>
-__global__ __launch_bounds__(Tile<E>::NT) void dz_kernel(DzArgs a) {
-  using G = Tile<E, kLeadDz>;
+template <typename E, typename EO, int Edge>
+__global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
+  using G = Tile<E, kLeadDz, Edge>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nv = a.hdr->nv;
   const int nblk = (nv + G::BN - 1) / G::BN;
   int mt, nb;
-  if (!xcd_tile_coords(blockIdx.x, a.ntiles, nblk, kMapBx, kMapBy, mt, nb)) return;
+  if (!xcd_tile_coords(blockIdx.x, a.ntiles * (kTile / Edge), nblk, kMapBx, kMapBy, mt, nb)) return;
   trace_stamp(0, 2);
   const int64_t n0 = (int64_t)nb * G::BN;
   const int mrel0 = mt * G::BM;  // within the chunk
   const int m0 = a.c0 + mrel0;
+  const int mw = min(m0, a.V - 1);   // chunks end on multiples of 256: a narrower tile can lie beyond V (its dZ is 0)
   const int ksteps = a.d * Elem<E>::size / G::KB;
   const int64_t pitchH = a.ldHc * Elem<E>::size;
   const int64_t pitchW = a.ldW * Elem<E>::size;
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(Tile<E>::NT) void dz_kernel(DzArgs a) {
   for (int q = 0; q < G::A_LD; ++q) {
     const int row = G::ldA_row(q);
     const int vrow = kDirect ? DzRows::tile_row_of_lds_row(row) : row;
-    offA[q] = (uint32_t)((min(m0 + vrow, a.V - 1) - m0) * pitchW) + G::ld_byte(row);
+    offA[q] = (uint32_t)((min(m0 + vrow, a.V - 1) - mw) * pitchW) + G::ld_byte(row);
   }
 #pragma unroll
   for (int q = 0; q < G::B_LD; ++q) {
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(Tile<E>::NT) void dz_kernel(DzArgs a) {
   typename G::Acc acc;
   G::zero(acc);
   trace_stamp(1, 2);
-  G::run(acc, static_cast<const char*>(a.W) + (int64_t)m0 * pitchW, offA,
+  G::run(acc, static_cast<const char*>(a.W) + (int64_t)mw * pitchW, offA,
          static_cast<const char*>(a.Hc) + n0 * pitchH, offB, ksteps, smem, 2);
   trace_stamp(2, 2); trace_cycles(2, 2);
   if constexpr (kDirect) {
@@ -478,7 +479,8 @@ __global__ __launch_bounds__(Tile<E>::NT) void dz_kernel(DzArgs a) {
   // is neither orientation's row.  JG of the wave's TN token blocks are staged per phase (as many
   // as fit next to each other in LDS in both orientations).
   constexpr int ESZ = Elem<EO>::size;
-  constexpr int JG = (ESZ == 2 ? 64 : 32) / G::NB;   // token blocks per wave per phase
+  constexpr int JG0 = (ESZ == 2 ? 64 : 32) / G::NB;
+  constexpr int JG = JG0 < G::TN ? JG0 : G::TN;      // token blocks per wave per phase
   constexpr int NTOK = G::WGN * JG * G::NB;       // tokens staged per phase
   constexpr int P1 = G::BM * ESZ + 16;            // pitch of the [token][vocab] staging rows
   constexpr int P2 = NTOK * ESZ + 16;             // pitch of the [vocab][token] staging rows
@@ -581,15 +583,18 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   const int64_t n_lim = a.n_from_nv ? (int64_t)nv : a.n_limit;
   // the walk's y axis runs over (slice of the contraction, n tile): neighbours share the slice's K range
   const int ntiles = (int)((n_lim + G::BN - 1) / G::BN);
+  const int ksplit = a.ksplit > 0 ? a.ksplit : a.hdr->ksplit;
   int mt, ny;
-  if (!xcd_tile_coords(blockIdx.x, (a.M + G::BM - 1) / G::BM, ntiles * a.ksplit, kMapBx, kMapBy, mt, ny)) return;
+  if (!xcd_tile_coords(blockIdx.x, (a.M + G::BM - 1) / G::BM, ntiles * ksplit, kMapBx, kMapBy, mt, ny)) return;
+  // where the tile goes: a slice of the partial sums, or out
+  const bool to_part = a.part && (a.ksplit > 0 || ksplit > 1 || a.part_single);
   const int slice = ny / ntiles;
   const int nt = ny - slice * ntiles;
   const int64_t n0 = (int64_t)nt * G::BN;
   const int m0 = mt * G::BM;
   const int64_t kel = a.k_from_nv ? (int64_t)nv : a.K;
   const int ksteps_all = (int)((kel * Elem<E>::size + G::KB - 1) / G::KB);
-  const int per_slice = (ksteps_all + a.ksplit - 1) / a.ksplit;
+  const int per_slice = (ksteps_all + ksplit - 1) / ksplit;
   const int k_first = slice * per_slice;
   const int ksteps = max(0, min(per_slice, ksteps_all - k_first));
   const int64_t pitchA = a.ldA * Elem<E>::size;
@@ -624,11 +629,12 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
     const int p = G::lane() / RPW, i = G::lane() % RPW;
     const int r = (G::wave() + G::NWAVES * (i / RPI)) * RPI + i % RPI;
     const int64_t n = n0 + (r / (JG * G::NB)) * G::WN + p * (JG * G::NB) + r % (JG * G::NB);
-    if (p < NPH && n < n_lim) my_row = (int)(a.part ? n : (a.rowmap ? (int64_t)a.rowmap[n] : a.row_base + n));
+    if (p < NPH && n < n_lim) my_row = (int)(to_part ? n : (a.rowmap ? (int64_t)a.rowmap[n] : a.row_base + n));
   }
-  float* const outp = a.part ? a.part + (size_t)slice * a.part_slice : a.out;
-  const int64_t ldo = a.part ? a.part_ld : a.ldo;
-  const bool accumulate = a.part ? a.part_accumulate : a.accumulate;
+  const int64_t part_slice = a.ksplit > 0 ? a.part_slice : (int64_t)ntiles * G::BN * a.part_ld;
+  float* const outp = to_part ? a.part + (size_t)slice * part_slice : a.out;
+  const int64_t ldo = to_part ? a.part_ld : a.ldo;
+  const bool accumulate = to_part ? a.part_accumulate : a.accumulate;
 
   typename G::Acc acc;
   G::zero(acc);
@@ -690,41 +696,62 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
 
 }  // namespace
 
-template <typename E>
+template <typename E, int Edge>
 static hipError_t launch_fwd_e(const FwdArgs& a, hipStream_t s) {
-  using G = Tile<E>;
-  const dim3 grid(xcd_grid_size(a.ntiles * a.npol, a.Ncap / kTile, kFwdMapBy));
-  hipError_t e = allow_lds<fwd_kernel<E>>(G::LDS_BYTES);
+  using G = Tile<E, false, Edge>;
+  const dim3 grid(xcd_grid_size(a.ntiles * a.npol, a.Ncap / Edge, kFwdMapBy));
+  hipError_t e = allow_lds<fwd_kernel<E, Edge>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fwd_kernel<E>, grid, dim3(G::NT), G::LDS_BYTES, s, a);
+  hipLaunchKernelGGL((fwd_kernel<E, Edge>), grid, dim3(G::NT), G::LDS_BYTES, s, a);
   return hipGetLastError();
+}
+
+template <typename E>
+static hipError_t launch_fwd_edge(const FwdArgs& a, hipStream_t s) {
+  switch (a.edge) {
+    case 64: return launch_fwd_e<E, 64>(a, s);
+    case 128: return launch_fwd_e<E, 128>(a, s);
+    default: return launch_fwd_e<E, 256>(a, s);
+  }
 }
 
 hipError_t launch_fwd(int dtype, const FwdArgs& a, hipStream_t s) {
-  if (dtype == kDtypeFp8) return launch_fwd_e<fp8_tag>(a, s);
-  return dtype == LMHEAD_BF16 ? launch_fwd_e<bf16_tag>(a, s) : launch_fwd_e<f32_tag>(a, s);
+  if (dtype == kDtypeFp8) return launch_fwd_e<fp8_tag, 256>(a, s);   // its main loop is written for edge 256
+  return dtype == LMHEAD_BF16 ? launch_fwd_edge<bf16_tag>(a, s) : launch_fwd_edge<f32_tag>(a, s);
 }
 
-template <typename E, typename EO>
+template <typename E, typename EO, int Edge>
 static hipError_t launch_dz_e(const DzArgs& a, hipStream_t s) {
-  using G = Tile<E>;
-  const dim3 grid(xcd_grid_size(a.ntiles, a.Ncap / kTile, kMapBy));
-  hipError_t e = allow_lds<dz_kernel<E, EO>>(G::LDS_BYTES);
+  using G = Tile<E, false, Edge>;
+  const dim3 grid(xcd_grid_size(a.ntiles * (kTile / Edge), a.Ncap / Edge, kMapBy));
+  hipError_t e = allow_lds<dz_kernel<E, EO, Edge>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dz_kernel<E, EO>), grid, dim3(G::NT), G::LDS_BYTES, s, a);
+  hipLaunchKernelGGL((dz_kernel<E, EO, Edge>), grid, dim3(G::NT), G::LDS_BYTES, s, a);
   return hipGetLastError();
+}
+
+template <typename E>
+static hipError_t launch_dz_edge(const DzArgs& a, hipStream_t s) {
+  switch (a.edge) {
+    case 64: return launch_dz_e<E, E, 64>(a, s);
+    case 128: return launch_dz_e<E, E, 128>(a, s);
+    default: return launch_dz_e<E, E, 256>(a, s);
+  }
 }
 
 hipError_t launch_dz(int op_dtype, int out_dtype, const DzArgs& a, hipStream_t s) {
   if (op_dtype == kDtypeFp8)
-    return out_dtype == LMHEAD_BF16 ? launch_dz_e<fp8_tag, bf16_tag>(a, s) : launch_dz_e<fp8_tag, f32_tag>(a, s);
-  return op_dtype == LMHEAD_BF16 ? launch_dz_e<bf16_tag, bf16_tag>(a, s) : launch_dz_e<f32_tag, f32_tag>(a, s);
+    return out_dtype == LMHEAD_BF16 ? launch_dz_e<fp8_tag, bf16_tag, 256>(a, s) : launch_dz_e<fp8_tag, f32_tag, 256>(a, s);
+  return op_dtype == LMHEAD_BF16 ? launch_dz_edge<bf16_tag>(a, s) : launch_dz_edge<f32_tag>(a, s);
 }
 
 template <typename E, int Role, int Edge>
 static hipError_t launch_gemm_t_edge(const GemmTArgs& a, hipStream_t s) {
   using G = Tile<E, false, Edge>;
-  const dim3 grid(xcd_grid_size((a.M + Edge - 1) / Edge, a.n_tiles_cap * (kTile / Edge) * a.ksplit, kMapBy));
+  const int64_t m_tiles = (a.M + Edge - 1) / Edge, n_cap = a.n_tiles_cap * (kTile / Edge);
+  // slices chosen on the device: at most kSplitTiles slice tiles when there are several per tile
+  const int64_t y_cap = a.ksplit > 0 ? n_cap * a.ksplit : (n_cap > kSplitTiles / m_tiles ? n_cap : kSplitTiles / m_tiles);
+  const dim3 grid(xcd_grid_size((int)m_tiles, y_cap, kMapBy));
   hipError_t e = allow_lds<gemm_t_kernel<E, Role, Edge>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((gemm_t_kernel<E, Role, Edge>), grid, dim3(G::NT), G::LDS_BYTES, s, a);

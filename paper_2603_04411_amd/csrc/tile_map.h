@@ -69,4 +69,38 @@ inline unsigned xcd_grid_size(int X, long long Y_cap, int /*by*/) {
   return (unsigned)(kNumXcd * (Y_cap / kNumXcd * X + (rest * X + kNumXcd - 1) / kNumXcd));
 }
 
+// Compute units that the launch rules count on (a GPU need not be present where workspaces are sized).
+constexpr int kComputeUnits = 256;
+
+// Slices of dH's contraction over the vocabulary: a tile grid that fills the chip's rounds badly (few tokens, or
+// 1.4 rounds of tiles) is cut into `ks` slices per tile, summed in order afterwards.  The number of tiles follows from
+// N_v, which only the device knows, so the index kernel picks ks there (WsHeader::ksplit): the cheapest allowed one,
+// the fewest slices on a tie.  (Picked on the host from the capacity, 20 token blocks x 16 tiles along d of a step with
+// room for 32 blocks took three slices and 5.43 ms; now four and 4.89.)
+constexpr int kSplitTiles = 2048, kMaxSplit = 64;
+struct DhSplit {
+  int m_tiles;   // tiles along d
+  int edge;
+  int ksteps;    // K-steps of a vocabulary chunk
+};
+// Time of a split in K-steps of a 256 wide tile: rounds of workgroups, each a slice's K-steps plus about ten for its
+// pipeline fill and epilogue; then the sum, 512 KB per 256 x 256 slice tile at memory speed (0.085) and a launch.
+LMHEAD_HD inline float dh_split_cost(const DhSplit& p, int n_tiles, int ks) {
+  const int tiles = p.m_tiles * n_tiles;
+  const int rounds = (tiles * ks + kComputeUnits - 1) / kComputeUnits;
+  const int steps = (p.ksteps + ks - 1) / ks;
+  const float area = (float)p.edge / 256.f;
+  return (float)rounds * (float)(steps + 10) + (ks > 1 ? 8.f + 0.085f * area * (float)(tiles * ks) : 0.f);
+}
+// At most kSplitTiles slice tiles exist when there are several per tile, which bounds the scratch.
+LMHEAD_HD inline bool dh_split_allowed(const DhSplit& p, int n_tiles, int ks) {
+  return ks == 1 || ((int64_t)p.m_tiles * n_tiles * ks <= kSplitTiles && ks <= p.ksteps);
+}
+// Slice tiles that scratch is needed for at any number of tokens up to n_tiles tiles of them (single: also when ks = 1).
+inline int64_t dh_split_tiles(const DhSplit& p, int64_t n_tiles, bool single) {
+  const int64_t tiles = p.m_tiles * n_tiles;
+  const int64_t split = tiles * kMaxSplit < kSplitTiles ? tiles * kMaxSplit : kSplitTiles;
+  return single && split < tiles ? tiles : split;
+}
+
 }  // namespace lmhead

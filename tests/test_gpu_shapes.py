@@ -170,3 +170,29 @@ def test_kv_store_and_grouping_over_token_blocks(dtype, d, n, off_base):
         bad[n // 2] = d + 1
         L.dynakv_store(desc, xt, bad, off_base, off, packed, cap, ws)
         assert L.dynakv_check(ws) == -6
+
+
+# every tile edge of the logits, dH and dW kernels (token counts and vocabulary sizes that are no multiples of them, tiles that
+# lie wholly beyond the vocabulary), one and several slices of dH, one and several vocabulary chunks
+@pytest.mark.parametrize("dtype,P,G,T,d,V,chunk", [
+    ("bf16", 1, 1, 5, 64, 70, 0), ("bf16", 1, 3, 21, 64, 1025, 256), ("bf16", 1, 3, 64, 128, 4113, 0),
+    ("bf16", 1, 7, 27, 576, 17000, 0), ("bf16", 1, 8, 130, 320, 9000, 4096), ("bf16", 2, 8, 64, 256, 33000, 0),
+    ("f32", 1, 1, 3, 32, 65, 0), ("f32", 2, 4, 32, 96, 1300, 512), ("f32", 2, 8, 64, 288, 9000, 0)])
+@pytest.mark.parametrize("dh16", [False, True])
+def test_lm_step_over_tile_edges(dtype, P, G, T, d, V, chunk, dh16):
+    cfg = wl.CONFIGS[1].scaled(P=P, G=G, T=T, d=d, V=V, dtype=dtype, len_lo=1, len_hi=T)
+    inp = small_inputs(cfg)
+    gp = GpuProblem(cfg, inp["H"], inp["W"], inp["tok"], inp["lens"], vocab_chunk=chunk, flags=8 if dh16 else 0)
+    gp.ws.fill_(0xFF)                      # scratch that is read before it is written shows up as NaN
+    logp, lse, ent, _, _ = gp.fwd()
+    g = wl.synthetic_upstream_grad(cfg, inp["lens"])
+    dH, dW = gp.bwd(lse, to_device(g))
+    assert gp.check() == 0
+    H, W = wl.as_f64(inp["H"]), wl.as_f64(inp["W"])
+    o_lp, o_lse, o_ent = O.lmhead_logprob_fwd(H, W, inp["tok"], inp["lens"], T)
+    for got, want in ((logp, o_lp), (lse, o_lse), (ent, o_ent)):
+        assert np.abs(np64(got) - want).max() <= 1e-4
+    o_dH, o_dW = O.lmhead_logprob_bwd(H, W, inp["tok"], inp["lens"], T, g.astype(np.float64))
+    tol = 1e-2 if dtype == "bf16" else 1e-5
+    assert rel_fro(np64(dW), o_dW) <= tol
+    assert rel_fro(np64(dH), o_dH) <= (max(tol, 4e-3) if dh16 else tol)   # 2^-9 for the rounding of dH itself

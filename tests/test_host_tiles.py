@@ -15,3 +15,7 @@ def _run_host_check(tmp_path, name):
 
 def test_tile_walk_is_balanced_over_the_xcds(tmp_path):
     _run_host_check(tmp_path, "tile_balance_check")
+
+
+def test_split_of_dh_is_allowed_cheapest_and_within_its_scratch(tmp_path):
+    _run_host_check(tmp_path, "dh_split_check")
