@@ -192,25 +192,70 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
 
 // ---- launchers (each enqueues on `s` and returns hipGetLastError()) --------------------
 
-// lens -> cu_len, header.nv, mask, row_slot (padded with -1 up to the next tile multiple); with `split` also
-// header.ksplit, the cheapest allowed number of slices for N_v.
-hipError_t launch_index(const int32_t* len, int R, int T, WsHeader* hdr, int32_t* cu_ws,
-                        int32_t* row_slot, uint8_t* mask_out, int32_t* cu_out, hipStream_t s,
-                        const DhSplit* split = nullptr);
+// The index of a batch and the gather of its valid rows:
+//   len -> cu_len (workspace, and cu_out unless null), header.nv, header.err (lengths only), mask (unless null),
+//   row_slot (padded with -1 up to the next tile multiple); with want_split also header.ksplit, the cheapest allowed
+//   number of slices for N_v;
+//   valid rows of H -> the dense, zero-padded Hc[Ncap x d]; tok -> tok_c (-1 for an id outside [0, V) and on the
+//   padding), g -> g_c and lse -> lse_c (unless null); the npol vectors zy[p * Ncap + .] are cleared and the npol vectors
+//   gid[p * Ncap + .] set to -1.
+struct IndexArgs {
+  const int32_t* len;
+  int R, T;
+  const char* H;
+  int64_t pitchH;      // bytes
+  int row_bytes;
+  int V;
+  const int32_t* tok;
+  const float* g;
+  const float* lse;
+  WsHeader* hdr;
+  int32_t* cu_ws;
+  int32_t* cu_out;
+  uint8_t* mask;
+  int32_t* row_slot;
+  char* Hc;
+  int64_t pitchHc;     // bytes
+  int32_t* tok_c;
+  float* g_c;
+  float* lse_c;
+  float* zy;
+  int32_t* gid;
+  int npol;
+  int64_t Ncap;
+  int want_split;
+  DhSplit split;
+};
+hipError_t launch_index(const IndexArgs& a, hipStream_t s);
 
-// Gathers the valid rows of H into the dense, zero-padded Hc[Ncap x d]; also compacts tok
-// (range-checked), and optionally g_logp and lse.  The npol vectors zy[p * Ncap + .] are cleared and
-// the npol vectors gid[p * Ncap + .] set to -1.
-hipError_t launch_compact(int dtype, const void* H, int64_t ldH, int d, int V, const int32_t* tok,
-                          const float* g, const float* lse, int64_t N, WsHeader* hdr,
-                          const int32_t* row_slot, void* Hc, int64_t ldHc, int32_t* tok_c, float* g_c,
-                          float* lse_c, float* zy, int32_t* gid, int npol, int64_t Ncap, hipStream_t s);
-
-// out[c][r] = in[r][c] for r < rows (rows read from the header when rows_from_nv), zero padding
-// up to out's extent [cols_p x rows_p] (pitch ld_out >= rows_p).
-hipError_t launch_transpose(int dtype, const void* in, int64_t ld_in, int64_t rows_cap, int cols,
-                            bool rows_from_nv, const WsHeader* hdr, void* out, int64_t ld_out,
-                            int64_t rows_p, int64_t cols_p, hipStream_t s);
+// out[c][r] = in[r][c] for r < rows (header.nv when rows_from_nv), c < cols, zero padding up to out's extent
+// [cols_p x rows_p] (pitch ld_out >= rows_p).  e4m3 (unless null): also e4m3(in[r][c] * scale) as it lies, zero up to rows_p.
+struct Transpose {
+  const void* in;
+  int64_t ld_in, rows, rows_p;
+  int cols, cols_p;
+  bool rows_from_nv;
+  void* out;
+  int64_t ld_out;
+  uint8_t* e4m3;
+  int64_t ld_e4m3;
+  float scale;
+  int tiles;           // set by the launcher
+};
+// The backward's K-contiguous operand copies; rows of dH of padded slots are set to 0; a token id outside [0, V) on a
+// valid slot sets header.err.
+struct OperandArgs {
+  WsHeader* hdr;
+  const int32_t* len;
+  const int32_t* tok;
+  int64_t N;
+  int T, V;
+  char* dH;
+  int64_t dh_bytes;    // bytes per row
+  Transpose job[2];
+  int zero_blocks;     // set by the launcher
+};
+hipError_t launch_operands(int dtype, const OperandArgs& a, hipStream_t s);
 
 struct FwdArgs {
   const void* Hc;      // [Ncap x d], pitch ldHc
@@ -233,8 +278,9 @@ struct FwdArgs {
 hipError_t launch_fwd(int dtype, const FwdArgs& a, hipStream_t s);
 
 // Merges the per-tile partials and scatters logp / lse / entropy to slot order (0 on padding).
-hipError_t launch_finalize(const float* part, const float* zy, int ntiles, int64_t Ncap,
-                           const int32_t* len, const int32_t* cu_len, int R, int T, float* logp,
+// A valid slot whose tok_c is -1 sets header.err.
+hipError_t launch_finalize(const float* part, const float* zy, const int32_t* tok_c, WsHeader* hdr, int ntiles,
+                           int64_t Ncap, const int32_t* len, const int32_t* cu_len, int R, int T, float* logp,
                            float* lse, float* entropy, hipStream_t s);
 
 struct DzArgs {
@@ -307,10 +353,6 @@ hipError_t launch_splitk_reduce(const float* part, int ksplit, int64_t part_slic
 int device_compute_units();
 // role: -1 = by use (dW when k_from_nv, else dH); 2 = parameter gradient of the KV gate (distinct kernel name).
 hipError_t launch_gemm_t(int dtype, const GemmTArgs& a, hipStream_t s, int role = -1);
-
-// Rows of dH that belong to padded slots are set to 0.
-hipError_t launch_zero_padded_rows(void* dH, bool bf16, int d, const int32_t* len, int R, int T,
-                                   hipStream_t s);
 
 hipError_t launch_group_advantage(const float* reward, int P, int G, float eps, int ddof,
                                   float* adv, hipStream_t s);

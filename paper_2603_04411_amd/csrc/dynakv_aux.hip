@@ -501,7 +501,7 @@ __device__ inline int bucket_of(int k, int d, int esz) {
 }
 
 // One launch prepares a call: it clears the header, makes up to kKvMaxCopies operand copies (64 x 64 tiles, 16-byte
-// accesses on both sides, the transposed ones through LDS as in transpose16_kernel) and counts the tokens of each
+// accesses on both sides, the transposed ones through LDS) and counts the tokens of each
 // length for the reconstruction's grouping.  Every one of these was a launch of its own, 3-5 us each and mostly dispatch
 // (the copies of d = 1024 are 2 MB).
 template <typename T>

@@ -55,6 +55,33 @@ struct Ws {
   T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
 };
 
+// What the index kernel is given by the forward and the backward alike.
+IndexArgs index_args(const lmhead_desc* d, const Ws& w, const void* H, const int32_t* tok, const int32_t* len, int npol) {
+  const WsLayout& L = w.L;
+  IndexArgs a{};
+  a.len = len;
+  a.R = (int)L.R;
+  a.T = d->T;
+  a.H = static_cast<const char*>(H);
+  a.pitchH = d->ldH * L.esz;
+  a.row_bytes = d->d * L.esz;
+  a.V = d->V;
+  a.tok = tok;
+  a.hdr = w.at<WsHeader>(L.hdr);
+  a.cu_ws = w.at<int32_t>(L.cu_len);
+  a.row_slot = w.at<int32_t>(L.row_slot);
+  a.Hc = w.at<char>(L.Hc);
+  a.pitchHc = L.ldHc * L.esz;
+  a.tok_c = w.at<int32_t>(L.tok_c);
+  a.g_c = w.at<float>(L.g_c);
+  a.lse_c = w.at<float>(L.lse_c);
+  a.zy = w.at<float>(L.zy);
+  a.gid = w.at<int32_t>(L.gid);
+  a.npol = npol;
+  a.Ncap = L.Ncap;
+  return a;
+}
+
 size_t loss_ws_bytes(int64_t P, int64_t G, int64_t T) {
   const int64_t R = P * G;
   const int64_t nb = (T + kLossSlotsPerBlock - 1) / kLossSlotsPerBlock;
@@ -111,11 +138,10 @@ static int forward(const lmhead_desc* desc, const void* H, const void* const* W,
   const WsLayout& L = w.L;
   WsHeader* hdr = w.at<WsHeader>(L.hdr);
 
-  LM_TRY(launch_index(len, (int)L.R, desc->T, hdr, w.at<int32_t>(L.cu_len), w.at<int32_t>(L.row_slot),
-                      mask, cu_len, s));
-  LM_TRY(launch_compact(desc->dtype, H, desc->ldH, desc->d, desc->V, tok, nullptr, nullptr, L.N, hdr,
-                        w.at<int32_t>(L.row_slot), w.at<void>(L.Hc), L.ldHc, w.at<int32_t>(L.tok_c), nullptr,
-                        nullptr, w.at<float>(L.zy), w.at<int32_t>(L.gid), npol, L.Ncap, s));
+  IndexArgs ia = index_args(desc, w, H, tok, len, npol);
+  ia.mask = mask;
+  ia.cu_out = cu_len;
+  LM_TRY(launch_index(ia, s));
   const bool fp8 = (desc->flags & LMHEAD_FLAG_FP8_LOGITS) != 0;
   FwdArgs fa{};
   fa.zscale = 1.0f;
@@ -158,7 +184,7 @@ static int forward(const lmhead_desc* desc, const void* H, const void* const* W,
   }
   for (int p = 0; p < npol; ++p)
     LM_TRY(launch_finalize(w.at<float>(L.part) + (size_t)p * 3 * L.ntiles * L.Ncap,
-                           w.at<float>(L.zy) + (size_t)p * L.Ncap, (int)L.ntiles, L.Ncap, len,
+                           w.at<float>(L.zy) + (size_t)p * L.Ncap, w.at<int32_t>(L.tok_c), hdr, (int)L.ntiles, L.Ncap, len,
                            w.at<int32_t>(L.cu_len), (int)L.R, desc->T, logp[p], p == 0 ? lse : nullptr,
                            p == 0 ? entropy : nullptr, s));
   return LMHEAD_OK;
@@ -212,26 +238,37 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
   WsHeader* hdr = w.at<WsHeader>(L.hdr);
   const int dt = desc->dtype;
 
-  LM_TRY(launch_index(len, (int)L.R, desc->T, hdr, w.at<int32_t>(L.cu_len), w.at<int32_t>(L.row_slot),
-                      nullptr, nullptr, s, &L.dh));
-  LM_TRY(launch_compact(dt, H, desc->ldH, desc->d, desc->V, tok, g_logp, lse, L.N, hdr,
-                        w.at<int32_t>(L.row_slot), w.at<void>(L.Hc), L.ldHc, w.at<int32_t>(L.tok_c),
-                        w.at<float>(L.g_c), w.at<float>(L.lse_c), w.at<float>(L.zy), w.at<int32_t>(L.gid), 1, L.Ncap, s));
-  // K-contiguous copies of the two operands that the backward contracts along their rows
-  LM_TRY(launch_transpose(dt, w.at<void>(L.Hc), L.ldHc, L.Ncap, desc->d, true, hdr, w.at<void>(L.HcT),
-                          L.ldHcT, L.Ncap, L.dp, s));
-  LM_TRY(launch_transpose(dt, W, desc->ldW, desc->V, desc->d, false, hdr, w.at<void>(L.WT), L.ldWT, L.Vp,
-                          L.dp, s));
   const bool dh16 = (desc->flags & LMHEAD_FLAG_DH_BF16) != 0;
-  LM_TRY(launch_zero_padded_rows(dH, dh16, desc->d, len, (int)L.R, desc->T, s));
   const bool fp8 = (desc->flags & LMHEAD_FLAG_FP8_LOGITS) != 0;
+
+  IndexArgs ia = index_args(desc, w, H, tok, len, 1);
+  ia.g = g_logp;
+  ia.lse = lse;
+  ia.want_split = 1;
+  ia.split = L.dh;
+  LM_TRY(launch_index(ia, s));
+  // K-contiguous copies of the two operands that the backward contracts along their rows.  With 8-bit logits the
+  // recompute must see the logits the forward saw: the same 8-bit copies, W's from the same pass over it.
+  OperandArgs oa{};
+  oa.hdr = hdr;
+  oa.len = len;
+  oa.tok = tok;
+  oa.N = L.N;
+  oa.T = desc->T;
+  oa.V = desc->V;
+  oa.dH = static_cast<char*>(dH);
+  oa.dh_bytes = (int64_t)desc->d * (dh16 ? 2 : 4);
+  oa.job[0] = {w.at<void>(L.Hc), L.ldHc, L.Ncap, L.Ncap, desc->d, (int)L.dp, true, w.at<void>(L.HcT), L.ldHcT};
+  oa.job[1] = {W, desc->ldW, desc->V, L.Vp, desc->d, (int)L.dp, false, w.at<void>(L.WT), L.ldWT};
   if (fp8) {
-    // the recompute must see the logits the forward saw: same 8-bit copies
+    oa.job[1].e4m3 = w.at<uint8_t>(L.W8);
+    oa.job[1].ld_e4m3 = L.ld8;
+    oa.job[1].scale = ldexpf(1.0f, desc->fp8_exp_w);
+  }
+  LM_TRY(launch_operands(dt, oa, s));
+  if (fp8)
     LM_TRY(launch_quantize_e4m3(dt, w.at<void>(L.Hc), L.ldHc, 0, true, hdr, desc->d, desc->fp8_exp_h,
                                 w.at<void>(L.Hc8), L.ld8, L.Ncap, s));
-    LM_TRY(launch_quantize_e4m3(dt, W, desc->ldW, desc->V, false, hdr, desc->d, desc->fp8_exp_w, w.at<void>(L.W8),
-                                L.ld8, L.Vp, s));
-  }
 
   const int total_tiles = (int)(L.Vp / kTile);
   const int tiles_per_chunk = (int)(L.Vc / kTile);

@@ -16,24 +16,36 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// ---- indexing --------------------------------------------------------------------------
+// ---- indexing and gather of the valid rows ---------------------------------------------
 
-// One workgroup: exclusive prefix sum of the (clamped) lengths.
-// `want_split`: the wavefront's lanes also price one number of slices of dH's contraction each; the cheapest (fewest
-// slices on a tie) goes to the header.
-__global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restrict__ len, int R, int T,
-                                                        WsHeader* hdr, int32_t* __restrict__ cu_ws,
-                                                        int32_t* __restrict__ cu_out, int want_split, DhSplit split) {
-  __shared__ int32_t wsum[16];
-  __shared__ int32_t carry_s;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) {
-    carry_s = 0;
-    hdr->err = 0;  // this kernel is the first of every call: reset the sticky word here
+// Header of a call: N_v, the error word (bad_len: a length outside [0, T]) and, with want_split, the cheapest allowed
+// number of slices of dH's contraction (fewest on a tie): one wavefront, each lane prices one number.
+__device__ inline void write_header(WsHeader* hdr, int nv, int bad_len, int want_split, const DhSplit& split, int lane) {
+  if (want_split) {
+    const int n_tiles = (nv + split.edge - 1) / split.edge;
+    const int ks = lane + 1;
+    static_assert(kMaxSplit == 64, "one number of slices per lane");
+    const float cost = dh_split_allowed(split, n_tiles, ks) ? dh_split_cost(split, n_tiles, ks) : __builtin_huge_valf();
+    float best = cost;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o));
+    const uint64_t ties = __ballot(cost == best);
+    if (lane == 0) hdr->ksplit = __ffsll((unsigned long long)ties);
   }
-  int bad = 0;
-  __syncthreads();
-  for (int base = 0; base < R; base += 1024) {
+  if (lane == 0) {
+    hdr->nv = nv;
+    hdr->err = bad_len ? kErrLen : 0;
+  }
+}
+
+// Exclusive prefix sum of the clamped lengths by one workgroup of NT threads: out[0 .. R], out[R] = N_v; a
+// length outside [0, T] sets `bad` in the thread that read it.  Ends with a barrier.
+template <int NT>
+__device__ inline void scan_lengths(const int32_t* __restrict__ len, int R, int T, int32_t* out, int& bad) {
+  __shared__ int32_t wsum[NT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int carry = 0;
+  for (int base = 0; base < R; base += NT) {
     const int r = base + tid;
     int x = 0;
     if (r < R) {
@@ -51,114 +63,111 @@ __global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restric
     }
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    int woff = 0;
-    for (int w = 0; w < wave; ++w) woff += wsum[w];
-    const int carry = carry_s;
-    const int excl = carry + woff + incl - x;
-    if (r < R) {
-      cu_ws[r] = excl;
-      if (cu_out) cu_out[r] = excl;
-    }
-    __syncthreads();
-    if (tid == 1023) carry_s = excl + x;
-    __syncthreads();
-  }
-  if (bad) atomicOr(&hdr->err, kErrLen);
-  if (want_split && wave == 0) {
-    const int n_tiles = (carry_s + split.edge - 1) / split.edge;
-    const int ks = lane + 1;
-    static_assert(kMaxSplit == 64, "one number of slices per lane");
-    const float cost = dh_split_allowed(split, n_tiles, ks) ? dh_split_cost(split, n_tiles, ks) : __builtin_huge_valf();
-    float best = cost;
+    int before = carry;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o));
-    const uint64_t ties = __ballot(cost == best);
-    if (lane == 0) hdr->ksplit = __ffsll((unsigned long long)ties);
+    for (int w = 0; w < NT / 64; ++w) {
+      before += w < wave ? wsum[w] : 0;
+      carry += wsum[w];
+    }
+    if (r < R) out[r] = before + incl - x;
+    __syncthreads();
   }
-  if (tid == 0) {
-    const int total = carry_s;
-    cu_ws[R] = total;
-    if (cu_out) cu_out[R] = total;
-    hdr->nv = total;
-  }
+  if (tid == 0) out[R] = carry;
+  __syncthreads();
 }
 
-// One thread per slot (plus one tile of tail threads that pad row_slot with -1).
-__global__ __launch_bounds__(256) void fill_index_kernel(const int32_t* __restrict__ len, int R, int T,
-                                                         const int32_t* __restrict__ cu,
-                                                         int32_t* __restrict__ row_slot,
-                                                         uint8_t* __restrict__ mask) {
-  const int64_t N = (int64_t)R * T;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < N) {
-    const int r = (int)(i / T);
-    const int t = (int)(i - (int64_t)r * T);
-    const int n = min(max(len[r], 0), T);
-    const bool valid = t < n;
-    if (mask) mask[i] = valid ? 1 : 0;
-    if (valid) row_slot[cu[r] + t] = (int32_t)i;
-  } else {
-    const int64_t nv = cu[R];
-    const int64_t k = nv + (i - N);
-    const int64_t cap = (N + kTile - 1) / kTile * kTile;
-    if (i - N < kTile && k < cap) row_slot[k] = -1;
-  }
+// Many responses: one workgroup scans the lengths and writes the header before the index kernel runs.
+__global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restrict__ len, int R, int T,
+                                                        WsHeader* hdr, int32_t* __restrict__ cu_ws,
+                                                        int32_t* __restrict__ cu_out, int want_split, DhSplit split) {
+  int bad = 0;
+  scan_lengths<1024>(len, R, T, cu_ws, bad);
+  bad = __syncthreads_or(bad);
+  if (cu_out)
+    for (int r = threadIdx.x; r <= R; r += 1024) cu_out[r] = cu_ws[r];
+  if (threadIdx.x < 64) write_header(hdr, cu_ws[R], bad, want_split, split, threadIdx.x);
 }
 
-// ---- gather of valid rows ------------------------------------------------------------
-
-// One wavefront per compact row k: copies H[row_slot[k], :] (16 bytes per lane per step) or
-// zero-fills the rows between N_v and the next tile multiple.
-__global__ __launch_bounds__(256) void compact_kernel(const char* __restrict__ H, int64_t pitchH,
-                                                      int row_bytes, int64_t pitchHc, int V,
-                                                      const int32_t* __restrict__ tok,
-                                                      const float* __restrict__ g,
-                                                      const float* __restrict__ lse, WsHeader* hdr,
-                                                      const int32_t* __restrict__ row_slot,
-                                                      char* __restrict__ Hc, int32_t* __restrict__ tok_c,
-                                                      float* __restrict__ g_c, float* __restrict__ lse_c,
-                                                      float* __restrict__ zy, int32_t* __restrict__ gid,
-                                                      int npol, int64_t Ncap) {
-  const int nv = hdr->nv;
+// Everything that the valid slots' positions decide, in one launch: mask, compaction map, and the gather of the
+// valid rows of H (16 bytes per lane and step; zeros from N_v to the next tile multiple) with their token ids,
+// gradients and statistics.  Bound by the copy of H.  kScan: each workgroup scans the lengths itself (up to
+// kIndexMaxR of them, a microsecond), which saves the launch that would have to come first: three
+// launches of 5 us each became one.  The range of the token ids is reported by the kernels that follow
+// (an id outside [0, V) is -1 here): the header is only cleared in this launch.
+// A wavefront takes kIndexRows consecutive rows at a time; its lanes look up their slots together.
+constexpr int kIndexMaxR = 4096, kIndexRows = 4;
+template <bool kScan>
+__global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
+  __shared__ int32_t cu_s[kScan ? kIndexMaxR + 1 : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int32_t* cu = a.cu_ws;
+  if constexpr (kScan) {
+    int bad = 0;
+    scan_lengths<256>(a.len, a.R, a.T, cu_s, bad);
+    cu = cu_s;
+    if (blockIdx.x == 0) {
+      bad = __syncthreads_or(bad);
+      for (int r = threadIdx.x; r <= a.R; r += 256) {
+        a.cu_ws[r] = cu_s[r];
+        if (a.cu_out) a.cu_out[r] = cu_s[r];
+      }
+      if (wave == 0) write_header(a.hdr, cu_s[a.R], bad, a.want_split, a.split, lane);
+    }
+  }
+  const int64_t N = (int64_t)a.R * a.T;
+  if (a.mask) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 256) {
+      const int r = (int)(i / a.T);
+      a.mask[i] = (int)(i - (int64_t)r * a.T) < cu[r + 1] - cu[r] ? 1 : 0;
+    }
+  }
+  const int nv = cu[a.R];
   const int64_t nvp = ((int64_t)nv + kTile - 1) / kTile * kTile;
-  const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (k >= nvp) return;
-  const int lane = threadIdx.x & 63;
   typedef __attribute__((ext_vector_type(4))) uint32_t u4;
-  u4* dst = reinterpret_cast<u4*>(Hc + k * pitchHc);
-  const int nvec = row_bytes / 16;
-  if (k < nv) {
-    const int64_t slot = row_slot[k];
-    const u4* src = reinterpret_cast<const u4*>(H + slot * pitchH);
-    for (int c = lane; c < nvec; c += 64) dst[c] = src[c];
-    if (lane == 0) {
-      int tk = tok[slot];
-      if (tk < 0 || tk >= V) {
-        atomicOr(&hdr->err, kErrTok);
-        tk = -1;
+  const int nvec = a.row_bytes / 16;
+  for (int64_t k0 = ((int64_t)blockIdx.x * 4 + wave) * kIndexRows; k0 < nvp; k0 += (int64_t)gridDim.x * 4 * kIndexRows) {
+    // slot of row k0 + lane: the last response that starts at or before it (empty ones share their start with the next)
+    const int64_t k = k0 + lane;
+    int slot = -1;
+    if (lane < kIndexRows && k < nv) {
+      int lo = 0, hi = a.R;
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (cu[mid] <= k) lo = mid; else hi = mid;
       }
-      tok_c[k] = tk;
-      if (g_c) g_c[k] = g[slot];
-      if (lse_c) lse_c[k] = lse[slot];
-      for (int p = 0; p < npol; ++p) {
-        zy[p * Ncap + k] = 0.f;
-        gid[p * Ncap + k] = -1;
+      slot = lo * a.T + (int)(k - cu[lo]);
+    }
+    if (lane < kIndexRows) {
+      a.row_slot[k] = slot;
+      int tk = -1;
+      if (slot >= 0) {
+        tk = a.tok[slot];
+        if (tk < 0 || tk >= a.V) tk = -1;
+      }
+      a.tok_c[k] = tk;
+      if (a.g) a.g_c[k] = slot >= 0 ? a.g[slot] : 0.f;
+      if (a.lse) a.lse_c[k] = slot >= 0 ? a.lse[slot] : 0.f;
+      for (int p = 0; p < a.npol; ++p) {
+        a.zy[p * a.Ncap + k] = 0.f;
+        a.gid[p * a.Ncap + k] = -1;
       }
     }
-  } else {
-    const u4 z = {0, 0, 0, 0};
-    for (int c = lane; c < nvec; c += 64) dst[c] = z;
-    if (lane == 0) {
-      tok_c[k] = -1;
-      if (g_c) g_c[k] = 0.f;
-      if (lse_c) lse_c[k] = 0.f;
-      for (int p = 0; p < npol; ++p) {
-        zy[p * Ncap + k] = 0.f;
-        gid[p * Ncap + k] = -1;
-      }
+    const u4* src[kIndexRows];
+#pragma unroll
+    for (int u = 0; u < kIndexRows; ++u) {
+      const int sl = __builtin_amdgcn_readlane(slot, u);
+      src[u] = sl >= 0 ? reinterpret_cast<const u4*>(a.H + (int64_t)sl * a.pitchH) : nullptr;
+    }
+    for (int c = lane; c < nvec; c += 64) {
+      u4 v[kIndexRows];
+#pragma unroll
+      for (int u = 0; u < kIndexRows; ++u) v[u] = src[u] ? src[u][c] : u4{0, 0, 0, 0};
+#pragma unroll
+      for (int u = 0; u < kIndexRows; ++u) reinterpret_cast<u4*>(a.Hc + (k0 + u) * a.pitchHc)[c] = v[u];
     }
   }
 }
+static_assert(kTile % kIndexRows == 0, "a wavefront's rows stay inside the padded extent");
 
 // ---- transpose -------------------------------------------------------------------------
 
@@ -191,31 +200,96 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
   }
 }
 
-// The same transposition for the common case of 16-byte aligned rows on both sides and extents that are
-// multiples of 64: 64 x 64 tiles with 16-byte global accesses on both sides (the element-wise kernel above
-// moves 2 or 4 bytes per lane and runs at about half the rate).  Rows of the source go to LDS as they are
-// (padded pitch); each thread then gathers the 16 bytes of one output chunk (consecutive r of one column).
-template <typename T>
-__global__ __launch_bounds__(256) void transpose16_kernel(const T* __restrict__ in, int64_t ld_in, int64_t rows_fixed,
-                                                          int cols, int rows_from_nv, const WsHeader* __restrict__ hdr,
-                                                          T* __restrict__ out, int64_t ld_out) {
+// Eight (bf16) or four (fp32) values as e4m3: x * scale, rounded to nearest even.  The hardware conversion turns
+// magnitudes beyond the format's range into NaN, so values are clamped to +-448 (the largest e4m3 number) first.
+template <int N>
+__device__ inline void to_e4m3(const float (&x)[N], float scale, uint32_t (&out)[N / 4]) {
+  float v[N];
+#pragma unroll
+  for (int e = 0; e < N; ++e) v[e] = fminf(fmaxf(x[e] * scale, -448.f), 448.f);
+#pragma unroll
+  for (int w = 0; w < N / 4; ++w) {
+    int p = 0;
+    p = __builtin_amdgcn_cvt_pk_fp8_f32(v[4 * w], v[4 * w + 1], p, false);
+    p = __builtin_amdgcn_cvt_pk_fp8_f32(v[4 * w + 2], v[4 * w + 3], p, true);
+    out[w] = (uint32_t)p;
+  }
+}
+
+// The backward's operands in one launch, 64 x 64 tiles with 16-byte global accesses on both sides (the element-wise kernel
+// above moves 2 or 4 bytes per lane and runs at about half the rate): HcT, WT and, with 8-bit logits, the
+// e4m3 copy of W, which the same read of W serves (151936 x 4096: 765 us for everything, 846 us in launches of their own); the rows of dH that
+// belong to padding are zeroed and the token ids of valid slots checked.  Rows of the source go to LDS as they
+// are (padded pitch); each thread then gathers the 16 bytes of one output chunk (consecutive r of one column).
+// At memory speed: 4.7 to 5.2 TB/s of reads and writes (tiles of 128 rows: no faster).
+constexpr int kZeroSlots = 64;   // slots per workgroup of the zeroing
+template <typename T, bool kE4m3>
+__global__ __launch_bounds__(256) void operands_kernel(OperandArgs a) {
   constexpr int VEC = 16 / sizeof(T);         // elements per 16-byte chunk
   constexpr int CPR = 64 / VEC;               // chunks per tile row
   constexpr int PITCH = 64 + 4 / sizeof(T);   // elements; keeps rows 4-byte aligned and the gather conflict-free
   __shared__ __attribute__((aligned(16))) T tile[64 * PITCH];
-  const int64_t rows = rows_from_nv ? (int64_t)hdr->nv : rows_fixed;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  const int c0 = blockIdx.y * 64;
+  int b = blockIdx.x;
+  if (b < a.zero_blocks) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int PER = kZeroSlots / 4;       // slots per wavefront
+    const int64_t i0 = (int64_t)b * kZeroSlots + wave * PER;
+    const int64_t i = i0 + lane;
+    bool pad = false;
+    if (lane < PER && i < a.N) {
+      const int r = (int)(i / a.T);
+      pad = (int)(i - (int64_t)r * a.T) >= min(max(a.len[r], 0), a.T);
+      if (!pad) {
+        const int tk = a.tok[i];
+        if (tk < 0 || tk >= a.V) atomicOr(&a.hdr->err, kErrTok);
+      }
+    }
+    typedef __attribute__((ext_vector_type(4))) float f4;    // 16 bytes of zeros, whatever the element type
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    for (uint64_t left = __ballot(pad); left; left &= left - 1) {
+      f4* const row = reinterpret_cast<f4*>(a.dH + (i0 + __ffsll((unsigned long long)left) - 1) * a.dh_bytes);
+      for (int64_t c = lane; c < a.dh_bytes / 16; c += 64) row[c] = z;
+    }
+    return;
+  }
+  b -= a.zero_blocks;
+  const bool second = b >= a.job[0].tiles;
+  if (second) b -= a.job[0].tiles;
+  const Transpose& t = a.job[second ? 1 : 0];
+  const int64_t rows = t.rows_from_nv ? (int64_t)a.hdr->nv : t.rows;
+  const int row_tiles = (int)(t.rows_p / 64);
+  const int64_t r0 = (int64_t)(b % row_tiles) * 64;
+  const int c0 = b / row_tiles * 64;
   // nothing beyond the tile-padded valid extent is ever read by the contractions
-  if (rows_from_nv && r0 >= (rows + kTile - 1) / kTile * kTile) return;
+  if (t.rows_from_nv && r0 >= (rows + kTile - 1) / kTile * kTile) return;
+  const T* const in = static_cast<const T*>(t.in);
+  T* const out = static_cast<T*>(t.out);
 #pragma unroll
   for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
     const int id = pass * 256 + threadIdx.x;
     const int rr = id / CPR, cc = id % CPR;
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r0 + rr < rows && c0 < cols) v = *reinterpret_cast<const uint4*>(in + (r0 + rr) * ld_in + c0 + cc * VEC);
+    if (r0 + rr < rows && c0 < t.cols) v = *reinterpret_cast<const uint4*>(in + (r0 + rr) * t.ld_in + c0 + cc * VEC);
     uint32_t* dst = reinterpret_cast<uint32_t*>(tile + rr * PITCH + cc * VEC);
     dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+    if (kE4m3 && second && c0 < t.cols) {
+      float x[VEC];
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        if constexpr (sizeof(T) == 2)
+          x[e] = __builtin_bit_cast(float, (e & 1) ? w[e / 2] & 0xffff0000u : w[e / 2] << 16);
+        else
+          x[e] = __builtin_bit_cast(float, w[e]);
+      }
+      uint32_t q[VEC / 4];
+      to_e4m3(x, t.scale, q);
+      uint32_t* const o8 = reinterpret_cast<uint32_t*>(t.e4m3 + (r0 + rr) * t.ld_e4m3 + c0 + cc * VEC);
+      if constexpr (VEC == 8)
+        *reinterpret_cast<uint2*>(o8) = make_uint2(q[0], q[1]);
+      else
+        *o8 = q[0];
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -226,23 +300,14 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const T* __restrict__ 
 #pragma unroll
     for (int i = 0; i < VEC; ++i) e[i] = tile[(rc * VEC + i) * PITCH + c];
     uint4 v;
-    if constexpr (sizeof(T) == 2) {
-      v.x = (uint32_t)e[0] | ((uint32_t)e[1] << 16);
-      v.y = (uint32_t)e[2] | ((uint32_t)e[3] << 16);
-      v.z = (uint32_t)e[4] | ((uint32_t)e[5] << 16);
-      v.w = (uint32_t)e[6] | ((uint32_t)e[7] << 16);
-    } else {
-      v = make_uint4(e[0], e[1], e[2], e[3]);
-    }
-    *reinterpret_cast<uint4*>(out + (int64_t)(c0 + c) * ld_out + r0 + rc * VEC) = v;
+    __builtin_memcpy(&v, e, 16);
+    *reinterpret_cast<uint4*>(out + (int64_t)(c0 + c) * t.ld_out + r0 + rc * VEC) = v;
   }
 }
 
 // ---- 8-bit operand copies ---------------------------------------------------------------
 
-// One wavefront per row: out = e4m3(in * scale), eight values per lane and pass.  The hardware
-// conversion rounds to nearest even but turns magnitudes beyond the format's range into NaN, so
-// values are clamped to +-448 (the largest e4m3 number) first.
+// One wavefront per row: out = e4m3(in * scale), eight values per lane and pass.
 template <typename T>
 __global__ __launch_bounds__(256) void quantize_e4m3_kernel(const T* __restrict__ in, int64_t ld_in,
                                                             int64_t rows_fixed, int rows_from_nv,
@@ -269,14 +334,9 @@ __global__ __launch_bounds__(256) void quantize_e4m3_kernel(const T* __restrict_
         v[0] = t0.x; v[1] = t0.y; v[2] = t0.z; v[3] = t0.w;
         v[4] = t1.x; v[5] = t1.y; v[6] = t1.z; v[7] = t1.w;
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = fminf(fmaxf(v[e] * scale, -448.f), 448.f);
-      int lo = 0, hi = 0;
-      lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], lo, false);
-      lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], lo, true);
-      hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[4], v[5], hi, false);
-      hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[6], v[7], hi, true);
-      packed = make_uint2((unsigned)lo, (unsigned)hi);
+      uint32_t q[2];
+      to_e4m3(v, scale, q);
+      packed = make_uint2(q[0], q[1]);
     }
     *reinterpret_cast<uint2*>(out + r * ld_out + c) = packed;
   }
@@ -291,34 +351,50 @@ __global__ __launch_bounds__(256) void quantize_e4m3_kernel(const T* __restrict_
 // maximum, then sums) it took 438 us for 120 tokens and 676 us for 41 k tokens at V = 151936 (0.3 TB/s), now 11 us
 // and 58 us.  Sixteen wavefronts with 2 x 8 loads in flight each keep 64 KB per workgroup outstanding, enough
 // for one workgroup per compute unit to run at memory speed when there are few tokens.
-constexpr int kFinWaves = 16, kFinBatch = 8;
+// Slots per workgroup: 64, one per lane.  Few slots, 16: the four quarters of a wavefront then merge tiles of their own
+// with 64-byte reads (192 slots x 1187 tiles: 20.6 -> 13.2 us; 8192 slots x 594: 14.1 us with 64, 23.7 with 16).
+// Also reports token ids that the index kernel found outside the vocabulary.
+constexpr int kFinWaves = 16, kFinBatch = 8, kFinFewSlots = 2048;
 
+// Statistics (m, s, t) of two disjoint sets of logits, scaled to the common maximum; exp2(-inf) = 0 drops empty ones.
+__device__ inline void merge_stats(float& m, float& s, float& t, float m2, float s2, float t2) {
+  const float mn = fmaxf(m, m2);
+  const float ms = mn == -__builtin_huge_valf() ? 0.f : mn;
+  const float f = __builtin_amdgcn_exp2f((m - ms) * kLog2e), f2 = __builtin_amdgcn_exp2f((m2 - ms) * kLog2e);
+  s = s * f + s2 * f2;
+  t = t * f + t2 * f2;
+  m = mn;
+}
+
+template <int Slots>
 __global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* __restrict__ part,
-                                                                  const float* __restrict__ zy, int ntiles,
+                                                                  const float* __restrict__ zy,
+                                                                  const int32_t* __restrict__ tok_c,
+                                                                  WsHeader* __restrict__ hdr, int ntiles,
                                                                   int64_t Ncap, const int32_t* __restrict__ len,
                                                                   const int32_t* __restrict__ cu, int R, int T,
                                                                   float* __restrict__ logp, float* __restrict__ lse,
                                                                   float* __restrict__ ent) {
-  __shared__ float red[kFinWaves][3][64];
+  constexpr int kStreams = kFinWaves * 64 / Slots;   // the tiles are dealt out to this many groups of Slots lanes
+  __shared__ float red[kFinWaves][3][Slots];
   const int64_t N = (int64_t)R * T;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const int lane = threadIdx.x % Slots, w = threadIdx.x / Slots;   // slot, stream
+  const int64_t i = (int64_t)blockIdx.x * Slots + lane;
   int64_t k = -1;   // compact row of this slot, -1 on padding
   if (i < N) {
     const int r = (int)(i / T);
     const int t = (int)(i - (int64_t)r * T);
     if (t < min(max(len[r], 0), T)) k = cu[r] + t;
   }
-  // statistics (m, s, t) of a union of tiles, each scaled to the running maximum; exp2(-inf) = 0 drops empty ones
   float m = -__builtin_huge_valf(), s = 0.f, tt = 0.f;
   if (k >= 0) {
     const size_t plane = (size_t)ntiles * Ncap;
     const float* const p = part + k;
-    for (int c0 = w; c0 < ntiles; c0 += kFinWaves * kFinBatch) {
+    for (int c0 = w; c0 < ntiles; c0 += kStreams * kFinBatch) {
       float mc[kFinBatch], sc[kFinBatch], tc[kFinBatch];
 #pragma unroll
       for (int u = 0; u < kFinBatch; ++u) {
-        const int c = c0 + u * kFinWaves;
+        const int c = c0 + u * kStreams;
         const bool in = c < ntiles;
         mc[u] = in ? p[(size_t)c * Ncap] : -__builtin_huge_valf();
         sc[u] = in ? p[plane + (size_t)c * Ncap] : 0.f;
@@ -340,9 +416,17 @@ __global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* _
       m = mn;
     }
   }
-  red[w][0][lane] = m;
-  red[w][1][lane] = s;
-  red[w][2][lane] = tt;
+  // the streams of a wavefront, then the wavefronts
+#pragma unroll
+  for (int o = Slots; o < 64; o <<= 1) {
+    const float m2 = __shfl_xor(m, o), s2 = __shfl_xor(s, o), t2 = __shfl_xor(tt, o);
+    merge_stats(m, s, tt, m2, s2, t2);
+  }
+  if (threadIdx.x % 64 < Slots) {
+    red[threadIdx.x / 64][0][lane] = m;
+    red[threadIdx.x / 64][1][lane] = s;
+    red[threadIdx.x / 64][2][lane] = tt;
+  }
   __syncthreads();
   if (w != 0 || i >= N) return;
   float o_lp = 0.f, o_lse = 0.f, o_ent = 0.f;
@@ -362,6 +446,7 @@ __global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* _
     o_lse = mx + __builtin_amdgcn_logf(s) * kLn2;
     o_lp = zy[k] - o_lse;
     o_ent = o_lse - tt / s;
+    if (tok_c[k] < 0) atomicOr(&hdr->err, kErrTok);
   }
   logp[i] = o_lp;
   if (lse) lse[i] = o_lse;
@@ -419,73 +504,67 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   }
 }
 
-// ---- padded rows of dH -------------------------------------------------------------------
-
-// One wavefront per slot; only padded slots write.
-template <typename TO>
-__global__ __launch_bounds__(256) void zero_rows_kernel(TO* __restrict__ dH, int d,
-                                                        const int32_t* __restrict__ len, int R, int T) {
-  const int64_t N = (int64_t)R * T;
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= N) return;
-  const int r = (int)(i / T);
-  const int t = (int)(i - (int64_t)r * T);
-  if (t < min(max(len[r], 0), T)) return;
-  typedef __attribute__((ext_vector_type(4))) float f4;    // 16 bytes of zeros, whatever the element type
-  f4* row = reinterpret_cast<f4*>(dH + i * (int64_t)d);
-  const f4 z = {0.f, 0.f, 0.f, 0.f};
-  for (int c = threadIdx.x & 63; c < d * (int)sizeof(TO) / 16; c += 64) row[c] = z;
-}
-
 }  // namespace
 
-hipError_t launch_index(const int32_t* len, int R, int T, WsHeader* hdr, int32_t* cu_ws,
-                        int32_t* row_slot, uint8_t* mask_out, int32_t* cu_out, hipStream_t s, const DhSplit* split) {
-  hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, len, R, T, hdr, cu_ws, cu_out, split ? 1 : 0,
-                     split ? *split : DhSplit{});
-  const int64_t N = (int64_t)R * T;
-  const unsigned blocks = (unsigned)((N + kTile + 255) / 256);
-  hipLaunchKernelGGL(fill_index_kernel, dim3(blocks), dim3(256), 0, s, len, R, T, cu_ws, row_slot, mask_out);
-  return hipGetLastError();
-}
-
-hipError_t launch_compact(int dtype, const void* H, int64_t ldH, int d, int V, const int32_t* tok,
-                          const float* g, const float* lse, int64_t N, WsHeader* hdr,
-                          const int32_t* row_slot, void* Hc, int64_t ldHc, int32_t* tok_c, float* g_c,
-                          float* lse_c, float* zy, int32_t* gid, int npol, int64_t Ncap, hipStream_t s) {
-  const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
-  const int64_t cap = (N + kTile - 1) / kTile * kTile;
-  hipLaunchKernelGGL(compact_kernel, dim3((unsigned)(cap / 4)), dim3(256), 0, s,
-                     static_cast<const char*>(H), ldH * esz, d * esz, ldHc * esz, V, tok, g, lse, hdr, row_slot,
-                     static_cast<char*>(Hc), tok_c, g ? g_c : nullptr, lse ? lse_c : nullptr, zy, gid, npol, Ncap);
-  return hipGetLastError();
-}
-
-hipError_t launch_transpose(int dtype, const void* in, int64_t ld_in, int64_t rows_cap, int cols,
-                            bool rows_from_nv, const WsHeader* hdr, void* out, int64_t ld_out,
-                            int64_t rows_p, int64_t cols_p, hipStream_t s) {
-  const dim3 grid((unsigned)((rows_p + 63) / 64), (unsigned)((cols_p + 63) / 64));
-  const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
-  const bool wide = cols % 64 == 0 && cols_p % 64 == 0 && rows_p % 64 == 0 && (ld_in * esz) % 16 == 0 &&
-                    (ld_out * esz) % 16 == 0 && (reinterpret_cast<uintptr_t>(in) & 15u) == 0 &&
-                    (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
-  if (wide) {
-    if (dtype == LMHEAD_BF16)
-      hipLaunchKernelGGL(transpose16_kernel<uint16_t>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(in), ld_in,
-                         rows_cap, cols, rows_from_nv ? 1 : 0, hdr, static_cast<uint16_t*>(out), ld_out);
-    else
-      hipLaunchKernelGGL(transpose16_kernel<uint32_t>, grid, dim3(256), 0, s, static_cast<const uint32_t*>(in), ld_in,
-                         rows_cap, cols, rows_from_nv ? 1 : 0, hdr, static_cast<uint32_t*>(out), ld_out);
-    return hipGetLastError();
-  }
-  if (dtype == LMHEAD_BF16) {
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, s,
-                       static_cast<const uint16_t*>(in), ld_in, rows_cap, cols, rows_from_nv ? 1 : 0,
-                       hdr, static_cast<uint16_t*>(out), ld_out, rows_p, cols_p);
+hipError_t launch_index(const IndexArgs& a, hipStream_t s) {
+  // one resident round of workgroups, or as many as there are rows and mask bytes for
+  constexpr int64_t kMost = 2048;
+  const int64_t cap = ((int64_t)a.R * a.T + kTile - 1) / kTile * kTile;
+  const int64_t need = cap / (4 * kIndexRows);
+  const dim3 grid((unsigned)(need < kMost ? need : kMost));
+  if (a.R <= kIndexMaxR) {
+    hipLaunchKernelGGL(index_kernel<true>, grid, dim3(256), 0, s, a);
   } else {
-    hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, dim3(256), 0, s,
-                       static_cast<const uint32_t*>(in), ld_in, rows_cap, cols, rows_from_nv ? 1 : 0,
-                       hdr, static_cast<uint32_t*>(out), ld_out, rows_p, cols_p);
+    hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, a.len, a.R, a.T, a.hdr, a.cu_ws, a.cu_out,
+                       a.want_split, a.split);
+    hipLaunchKernelGGL(index_kernel<false>, grid, dim3(256), 0, s, a);
+  }
+  return hipGetLastError();
+}
+
+// rows that are no multiple of 64 elements (fp32 only), or not 16-byte aligned
+static hipError_t launch_transpose(int dtype, const Transpose& t, const WsHeader* hdr, hipStream_t s) {
+  const dim3 grid((unsigned)((t.rows_p + 63) / 64), (unsigned)((t.cols_p + 63) / 64));
+  if (dtype == LMHEAD_BF16)
+    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(t.in), t.ld_in,
+                       t.rows, t.cols, t.rows_from_nv ? 1 : 0, hdr, static_cast<uint16_t*>(t.out), t.ld_out, t.rows_p,
+                       t.cols_p);
+  else
+    hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, dim3(256), 0, s, static_cast<const uint32_t*>(t.in), t.ld_in,
+                       t.rows, t.cols, t.rows_from_nv ? 1 : 0, hdr, static_cast<uint32_t*>(t.out), t.ld_out, t.rows_p,
+                       t.cols_p);
+  return hipGetLastError();
+}
+
+hipError_t launch_operands(int dtype, const OperandArgs& a, hipStream_t s) {
+  OperandArgs b = a;
+  const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
+  b.zero_blocks = (int)((b.N + kZeroSlots - 1) / kZeroSlots);
+  int64_t blocks = b.zero_blocks;
+  for (Transpose& t : b.job) {
+    const bool wide = t.cols % 64 == 0 && t.cols_p % 64 == 0 && t.rows_p % 64 == 0 && (t.ld_in * esz) % 16 == 0 &&
+                      (t.ld_out * esz) % 16 == 0 && (reinterpret_cast<uintptr_t>(t.in) & 15u) == 0 &&
+                      (reinterpret_cast<uintptr_t>(t.out) & 15u) == 0;
+    t.tiles = wide ? (int)(t.rows_p / 64 * (t.cols_p / 64)) : 0;
+    if (!wide) {
+      // (d is a multiple of 128 wherever an e4m3 copy is wanted: the wide kernel makes it)
+      const hipError_t e = launch_transpose(dtype, t, b.hdr, s);
+      if (e != hipSuccess) return e;
+    }
+    blocks += t.tiles;
+  }
+  const dim3 grid((unsigned)blocks);
+  const bool e4m3 = b.job[1].e4m3 != nullptr;
+  if (dtype == LMHEAD_BF16) {
+    if (e4m3)
+      hipLaunchKernelGGL((operands_kernel<uint16_t, true>), grid, dim3(256), 0, s, b);
+    else
+      hipLaunchKernelGGL((operands_kernel<uint16_t, false>), grid, dim3(256), 0, s, b);
+  } else {
+    if (e4m3)
+      hipLaunchKernelGGL((operands_kernel<uint32_t, true>), grid, dim3(256), 0, s, b);
+    else
+      hipLaunchKernelGGL((operands_kernel<uint32_t, false>), grid, dim3(256), 0, s, b);
   }
   return hipGetLastError();
 }
@@ -536,22 +615,16 @@ int device_compute_units() {
   return n;
 }
 
-hipError_t launch_finalize(const float* part, const float* zy, int ntiles, int64_t Ncap,
-                           const int32_t* len, const int32_t* cu_len, int R, int T, float* logp,
+hipError_t launch_finalize(const float* part, const float* zy, const int32_t* tok_c, WsHeader* hdr, int ntiles,
+                           int64_t Ncap, const int32_t* len, const int32_t* cu_len, int R, int T, float* logp,
                            float* lse, float* entropy, hipStream_t s) {
   const int64_t N = (int64_t)R * T;
-  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((N + 63) / 64)), dim3(64 * kFinWaves), 0, s, part, zy,
-                     ntiles, Ncap, len, cu_len, R, T, logp, lse, entropy);
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_padded_rows(void* dH, bool bf16, int d, const int32_t* len, int R, int T, hipStream_t s) {
-  const int64_t N = (int64_t)R * T;
-  const dim3 grid((unsigned)((N + 3) / 4));
-  if (bf16)
-    hipLaunchKernelGGL(zero_rows_kernel<__bf16>, grid, dim3(256), 0, s, static_cast<__bf16*>(dH), d, len, R, T);
+  if (N <= kFinFewSlots)
+    hipLaunchKernelGGL(finalize_kernel<16>, dim3((unsigned)((N + 15) / 16)), dim3(64 * kFinWaves), 0, s, part, zy, tok_c,
+                       hdr, ntiles, Ncap, len, cu_len, R, T, logp, lse, entropy);
   else
-    hipLaunchKernelGGL(zero_rows_kernel<float>, grid, dim3(256), 0, s, static_cast<float*>(dH), d, len, R, T);
+    hipLaunchKernelGGL(finalize_kernel<64>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kFinWaves), 0, s, part, zy, tok_c,
+                       hdr, ntiles, Ncap, len, cu_len, R, T, logp, lse, entropy);
   return hipGetLastError();
 }
 

@@ -196,3 +196,46 @@ def test_lm_step_over_tile_edges(dtype, P, G, T, d, V, chunk, dh16):
     tol = 1e-2 if dtype == "bf16" else 1e-5
     assert rel_fro(np64(dW), o_dW) <= tol
     assert rel_fro(np64(dH), o_dH) <= (max(tol, 4e-3) if dh16 else tol)   # 2^-9 for the rounding of dH itself
+
+
+# responses scanned by every workgroup (up to 4096) or by one launch ahead, empty responses, out-of-range ids and lengths
+@pytest.mark.parametrize("R,T", [(1, 1), (3, 5), (255, 2), (257, 3), (4096, 2), (4097, 2), (5000, 1)])
+def test_index_over_response_counts(R, T):
+    import torch
+    import paper_2603_04411_amd as L
+    d, V = 64, 100
+    rng = np.random.default_rng(R)
+    lens = rng.integers(0, T + 1, size=R).astype(np.int32)
+    lens[0] = T
+    tok = rng.integers(0, V, size=R * T).astype(np.int32)
+    H = rng.standard_normal((R * T, d)).astype(np.float32)
+    W = (rng.standard_normal((V, d)) * 0.1).astype(np.float32)
+    cfg = wl.CONFIGS[0].scaled(P=R, G=1, T=T, d=d, V=V, len_lo=0, len_hi=T)
+    gp = GpuProblem(cfg, H, W, tok, lens)
+    logp, lse, ent, mask, cu = gp.fwd()
+    assert gp.check() == 0
+    valid = np.arange(T)[None, :] < lens[:, None]
+    assert np.array_equal(mask.cpu().numpy(), valid.reshape(-1).astype(np.uint8))
+    assert np.array_equal(cu.cpu().numpy(), np.concatenate([[0], np.cumsum(lens)]))
+    from tests.harness import assert_index_parity
+    assert_index_parity(gp, np.nonzero(valid.reshape(-1))[0], tok)
+    z = H.astype(np.float64) @ W.astype(np.float64).T
+    o = z[np.arange(R * T), tok] - np.log(np.exp(z).sum(1))
+    assert np.abs(np64(logp) - np.where(valid.reshape(-1), o, 0.0)).max() <= 1e-4
+    # an id outside the vocabulary on a valid slot is reported by both directions, on a padded one by neither
+    g = torch.full((R * T,), 0.5, device="cuda")
+    for slot, code in ((0, -6), (int(np.nonzero(~valid.reshape(-1))[0][0]) if (~valid).any() else None, 0)):
+        if slot is None:
+            continue
+        t2 = tok.copy()
+        t2[slot] = V
+        g2 = GpuProblem(cfg, H, W, t2, lens)
+        _, lse2, _, _, _ = g2.fwd()
+        assert g2.check() == code
+        g2.bwd(lse2, g)
+        assert g2.check() == code
+    bad = lens.copy()
+    bad[R // 2] = T + 1
+    g3 = GpuProblem(cfg, H, W, tok, bad)
+    g3.fwd()
+    assert g3.check() == -6
