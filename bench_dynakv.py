@@ -28,6 +28,7 @@ PEAK_F32_MFMA_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 KINDS = {4: "kv_gemm_kernel<spectral projection>", 5: "kv_gemm_kernel<gate logits>",
          6: "kv_mask_kernel (softmax + cumulative mask + threshold)", 7: "kv_gemm_kernel<reconstruction>"}
+FUSED_GATE = "kv_gate_kernel (x U, gate logits, softmax, cumulative mask, threshold)"   # recorded as kind 4
 # --backward: one step = dynakv_gate (training outputs off) + dynakv_gate_bwd
 BWD_KINDS = {4: "kv_gemm_kernel<spectral projection>", 5: "kv_gemm_kernel<gate logits> (forward + recompute)",
              6: "kv_mask_kernel", 8: "kv_mask_bwd_kernel", 9: "kv_gemm_kernel<g_x~ = g_l W^T + g_xhat m>",
@@ -135,8 +136,13 @@ def backward_main(args, cfg, inp, L, desc, params, ws, xt, k) -> int:
     # algorithmic bytes per launch: mask backward reads logits (4), x~ and g_xhat (esz each) and writes
     # g_l and g_xhat*m (esz each); a transpose pair reads and writes two [n x d] operands
     byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz), 13: 4.0 * n * d * esz}
+    fused = kern[6][1] == 0          # large streams: the forward's gate is one kernel, gate logits only the recompute
     kinds = []
     for kind, name in BWD_KINDS.items():
+        if fused and kind == 6:
+            continue
+        if fused and kind == 4:
+            name = FUSED_GATE
         ms, cnt = kern[kind]
         avg = ms / cnt if cnt else 0.0
         if kind in byts:
@@ -144,7 +150,7 @@ def backward_main(args, cfg, inp, L, desc, params, ws, xt, k) -> int:
             kinds.append({"kernel": name, "kind": kind, "launches": int(cnt), "avg_ms": avg, "bound": "hbm",
                           "gbs": rate, "frac": rate / PEAK_HBM_GBS})
         else:
-            rate = dense / (avg * 1e-3) / 1e12 if avg else 0.0
+            rate = dense * (2 if fused and kind == 4 else 1) / (avg * 1e-3) / 1e12 if avg else 0.0
             kinds.append({"kernel": name, "kind": kind, "launches": int(cnt), "avg_ms": avg, "bound": "mfma",
                           "tflops": rate, "frac": rate / peak})
     per_step = {e["kernel"]: e["avg_ms"] * e["launches"] / args.steps for e in kinds}
@@ -264,9 +270,17 @@ def main(argv=None) -> int:
     # is 2 d sum_i k_i; the mask kernel reads the fp32 logits and the bias once and writes k
     peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_F32_MFMA_TFLOPS
     work = {4: 2.0 * n * d * d, 5: 2.0 * n * d * d, 7: 2.0 * d * float(k_host.sum())}
+    step_flops = work[4] + work[5] + work[7]
     mask_bytes = n * d * 4.0 + n * 4.0 + d * 4.0
+    fused = kern[6][1] == 0          # large streams: one kernel for the whole gate
+    if fused:
+        work[4] += work[5]
     kinds = []
     for kind, name in KINDS.items():
+        if fused and kind in (5, 6):
+            continue
+        if fused and kind == 4:
+            name = FUSED_GATE
         ms, cnt = kern[kind]
         avg = ms / cnt if cnt else 0.0
         if kind == 6:
@@ -297,7 +311,6 @@ def main(argv=None) -> int:
         got = xbar[:m].double().cpu().numpy()
         cpu["gpu_vs_oracle_rel_fro_xbar_on_sample"] = float(np.linalg.norm(got - o_xbar) / np.linalg.norm(o_xbar))
 
-    step_flops = work[4] + work[5] + work[7]
     out = {
         "metric": "tokens/s KV gate + ragged store + low-rank reconstruction (1 GPU)",
         "value": n / (ms_per_step * 1e-3), "unit": "tokens/s",

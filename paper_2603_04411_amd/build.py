@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblmhead.so")
 TRACE_LIB = os.path.join(HERE, "liblmhead_trace.so")
 SOURCES = ["lmhead_api.hip", "lmhead_aux.hip", "lmhead_loss.hip", "lmhead_gemm.hip", "lmhead_probe.hip",
-           "dynakv_api.hip", "dynakv_aux.hip", "dynakv_gemm.hip"]
+           "dynakv_api.hip", "dynakv_aux.hip", "dynakv_gemm.hip", "dynakv_gate.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     # packed fp32 VALU forms are kept off for every device translation unit

@@ -383,7 +383,7 @@ hipError_t static_scratch(float** out);
 // stream.  The pool is fixed-size; launches beyond it are simply not timed.
 // Kinds: 0 logits fwd, 1 dZ recompute, 2 dH, 3 dW, 4 spectral projection, 5 gate logits,
 // 6 truncation mask, 7 low-rank reconstruction; gate backward: 8 mask backward, 9 g_x~ product, 10 dx
-// product, 11 dW, 12 dU, 13 operand transposes.
+// product, 11 dW, 12 dU, 13 operand transposes.  The gate in one kernel is recorded as 4.
 constexpr int kTimingKinds = 14;
 constexpr int kTimingPool = 8192;
 struct TimingState {

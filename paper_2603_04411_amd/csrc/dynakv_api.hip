@@ -31,7 +31,8 @@ struct Ws {
 
 // K-contiguous (transposed) or row-padded copy of a dense d x d parameter matrix, zero up to dp rows of the copy
 KvCopy param_copy(const void* in, int d, void* out, int64_t ld_out, int64_t dp, bool transposed) {
-  return {in, d, d, transposed ? d : dp, d, (int)(transposed ? dp : d), out, ld_out, transposed, 0};
+  return {in, d, d, transposed ? d : dp, d, (int)(transposed ? dp : d), out, ld_out,
+          transposed ? KvCopy::kTransposed : KvCopy::kPlain, 0};
 }
 
 // common prologue of the compute entry points
@@ -72,9 +73,20 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
   const int dt = desc->dtype;
   const int d = desc->d;
 
-  // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
   KvPrepareArgs pa{};
   pa.hdr = hdr;
+  if (!m && !xhat && kv_gate_fits(dt, L.n, d, desc->ldx)) {
+    // nothing but x~ and k is wanted: one kernel, with the parameter matrices in its fragment order
+    const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0;
+    pa.job[0] = {U, d, d, d, d, d, w.at<void>(L.UT), 0, KvCopy::kFragments, 0};
+    pa.job[1] = {W, d, d, d, d, d, w.at<void>(L.WT), 0, literal ? KvCopy::kFragmentsFlipped : KvCopy::kFragments, 0};
+    pa.njobs = 2;
+    LM_TRY(launch_kv_prepare(dt, pa, s));
+    TimedLaunch tl(4, s);
+    LM_TRY(launch_kv_gate({x, desc->ldx, w.at<void>(L.UT), w.at<void>(L.WT), b, L.n, tau, literal ? 1 : 0, xt, k}, d, s));
+    return LMHEAD_OK;
+  }
+  // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
   pa.job[0] = param_copy(U, d, w.at<void>(L.UT), L.ldT, L.dp, true);
   pa.job[1] = param_copy(W, d, w.at<void>(L.WT), L.ldT, L.dp, true);
   pa.njobs = 2;
@@ -277,8 +289,8 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
     {
       TimedLaunch tl(13, s);
       KvPrepareArgs ta{};
-      ta.job[0] = {rows_src, ld_rows, L.n, L.ncap, d, (int)L.dp, at(L.T1), L.ldK, true, 0};
-      ta.job[1] = {cols_src, d, L.n, L.ncap, d, (int)L.dp, at(L.T2), L.ldK, true, 0};
+      ta.job[0] = {rows_src, ld_rows, L.n, L.ncap, d, (int)L.dp, at(L.T1), L.ldK, KvCopy::kTransposed, 0};
+      ta.job[1] = {cols_src, d, L.n, L.ncap, d, (int)L.dp, at(L.T2), L.ldK, KvCopy::kTransposed, 0};
       ta.njobs = 2;
       LM_TRY(launch_kv_prepare(dt, ta, s));
     }

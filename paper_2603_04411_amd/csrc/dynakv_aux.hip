@@ -540,14 +540,14 @@ __global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a) {
     const int rr = id / CPR, cc = id % CPR;
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
     if (r0 + rr < c.rows && c0 < c.cols) v = *reinterpret_cast<const uint4*>(in + (r0 + rr) * c.ld_in + c0 + cc * VEC);
-    if (!c.transposed) {
+    if (c.form == KvCopy::kPlain) {
       *reinterpret_cast<uint4*>(out + (r0 + rr) * c.ld_out + c0 + cc * VEC) = v;
     } else {
       uint32_t* const dst = reinterpret_cast<uint32_t*>(tile + rr * PITCH + cc * VEC);
       dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
     }
   }
-  if (!c.transposed) return;
+  if (c.form == KvCopy::kPlain) return;
   __syncthreads();
 #pragma unroll
   for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
@@ -558,7 +558,15 @@ __global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a) {
     for (int i = 0; i < VEC; ++i) e[i] = tile[(rc * VEC + i) * PITCH + col];
     uint4 v;
     __builtin_memcpy(&v, e, 16);
-    *reinterpret_cast<uint4*>(out + (int64_t)(c0 + col) * c.ld_out + r0 + rc * VEC) = v;
+    if (c.form == KvCopy::kTransposed) {
+      *reinterpret_cast<uint4*>(out + (int64_t)(c0 + col) * c.ld_out + r0 + rc * VEC) = v;
+    } else {
+      const int d = c.cols, k = (int)r0 + rc * VEC;
+      const int pos = c.form == KvCopy::kFragmentsFlipped ? d - 1 - (c0 + col) : c0 + col;
+      const int w = pos / (d / 4), q = pos % (d / 4) / (d / 16), i = pos % (d / 16) / 4;
+      const int lane = k / 8 % 4 * 16 + 4 * q + pos % 4;
+      *reinterpret_cast<uint4*>(out + (((int64_t)w * (d / 32) + k / 32) * (d / 64) + i) * 512 + lane * 8) = v;
+    }
   }
 }
 

@@ -157,6 +157,28 @@ struct KvGemmArgs {
 };
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
 
+// The whole gate of many tokens in one kernel (dynakv_gate.hip), for callers that want x~ and k only.  Ufrag, Wfrag: the
+// parameter matrices in fragment order (KvCopy::kFragments, W's with the same `literal`).
+struct KvGateArgs {
+  const void* x;
+  int64_t ldx;
+  const void* Ufrag;
+  const void* Wfrag;
+  const float* bias;
+  int64_t n;
+  float tau;
+  int literal;
+  void* xt;
+  int32_t* k;
+};
+// From this many tokens on.  Its workgroups take 64 tokens (128 at d = 512) through everything, 60 us a round, so below
+// a round the separate kernels with their smaller tiles win.  Whole call, us, separate kernels / this one:
+//   d 1024: n 8192 60.9 / 65.5   12000 90.6 / 70.0   16384 99.9 / 83.6   65536 392 / 287   262144 1334 / 1049
+//   d 512:  n 8192 34.5 / 38.3   16384 50.0 / 42.1   32768 77.7 / 49.0   65536 154 / 90    262144 560 / 342
+constexpr int kKvGateFrom = 10240;
+bool kv_gate_fits(int dtype, int64_t n, int d, int64_t ldx);
+hipError_t launch_kv_gate(const KvGateArgs& a, int d, hipStream_t s);
+
 // Softmax over the gate logits (+ bias), the cumulative mask, the threshold count and the
 // optional training outputs.
 hipError_t launch_kv_mask(int dtype, const float* logits, const float* b, const void* xt, int64_t n, int d,
@@ -180,15 +202,20 @@ static inline KvCount make_kv_count(const int32_t* k, int64_t n, int d, int nbuc
   return {k, n, d, nbuckets, (int)((n + per - 1) / per), (int)per, hist};
 }
 
-// One operand copy: out[r][c] = in[r][c], or out[c][r] when transposed, for r < rows, c < cols; zero up to rows_p x
-// cols_p (of the source's orientation).  Rows of both sides 16-byte aligned; cols, cols_p, rows_p multiples of 64.
+// One operand copy.  kPlain: out[r][c] = in[r][c]; kTransposed: out[c][r] = in[r][c], for r < rows, c < cols; zero up to
+// rows_p x cols_p (of the source's orientation).  Rows of both sides 16-byte aligned; cols, cols_p, rows_p multiples
+// of 64.  kFragments (bf16, d x d, d a multiple of 64): the MFMA fragments in the order in which kv_gate_kernel's
+// wavefronts consume them, ((w * d/32 + s) * d/64 + i) KB + 16 lane bytes holding in[k][c] for the 8 values
+// k = 32 s + 8 (lane / 16) + [0, 8) and column c = position d/4 w + d/16 ((lane % 16) / 4) + 4 i + lane % 4
+// (kFragmentsFlipped: c = d - 1 - position).
 struct KvCopy {
+  enum Form { kPlain, kTransposed, kFragments, kFragmentsFlipped };
   const void* in;
   int64_t ld_in, rows, rows_p;
   int cols, cols_p;
   void* out;
   int64_t ld_out;
-  bool transposed;
+  Form form;
   int tiles;           // set by the launcher
 };
 constexpr int kKvMaxCopies = 4;

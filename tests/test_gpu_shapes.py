@@ -239,3 +239,37 @@ def test_index_over_response_counts(R, T):
     g3 = GpuProblem(cfg, H, W, tok, bad)
     g3.fwd()
     assert g3.check() == -6
+
+
+# the one-kernel gate (large streams, no soft outputs): its smallest size, last tiles of one token and of all but one, strided
+# rows, both readings of Eq. 6, thresholds that keep everything and nothing
+@pytest.mark.parametrize("d,n,ldx", [(1024, 10240, None), (1024, 10241, None), (512, 10367, None), (1024, 16447, 1088),
+                                     (512, 33000, 520)])
+@pytest.mark.parametrize("literal", [False, True])
+def test_kv_gate_in_one_kernel(d, n, ldx, literal):
+    import torch
+    import workloads.dynakv as kv
+    import paper_2603_04411_amd as L
+    from tests.harness import KvProblem
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d)
+    kp = KvProblem(cfg, kv.kv_inputs(cfg), flags=L.FLAG_LITERAL_FLIP if literal else 0, ldx=ldx)
+    kp.ws.fill_(0xFF)
+    xt, k, _, _ = kp.gate(cfg.tau, soft=False)
+    xt2, k2, m, _ = kp.gate(cfg.tau)          # the separate kernels, which the oracle tests cover
+    assert kp.check() == 0
+    # the same bf16 products in the same order of K: the same spectral state
+    assert torch.equal(xt, xt2)
+    # the mask is the same sum of the same exponentials in another order (<= d * 2^-24 relative): a count may differ only
+    # where the other path's mask is within that of the threshold
+    rows = torch.arange(n, device="cuda")
+    for kk in (k, k2):
+        assert int(kk.min()) >= 0 and int(kk.max()) <= d
+    lo, hi = torch.minimum(k, k2).long(), torch.maximum(k, k2).long()
+    differ = (lo != hi).nonzero().flatten()
+    eps = 2 * d * 2.0 ** -24
+    for r in differ.tolist():
+        assert (m[r, lo[r]:hi[r]] - cfg.tau).abs().max() <= eps
+    assert differ.numel() <= 1 + n // 1000
+    for tau, want in ((-1.0, d), (1.5, 0)):
+        _, kt, _, _ = kp.gate(tau, soft=False)
+        assert torch.equal(kt, torch.full_like(kt, want))
