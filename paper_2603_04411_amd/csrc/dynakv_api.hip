@@ -86,6 +86,22 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     LM_TRY(launch_kv_gate({x, desc->ldx, w.at<void>(L.UT), w.at<void>(L.WT), b, L.n, tau, literal ? 1 : 0, xt, k}, d, s));
     return LMHEAD_OK;
   }
+  if (kv_few_fits(L.n, d)) {
+    KvFewArgs fa{x, desc->ldx, U, (int)L.n, d, xt, nullptr, hdr, false, false};
+    {
+      TimedLaunch tl(4, s);
+      LM_TRY(launch_kv_few(dt, fa, s));
+    }
+    fa = {xt, d, W, (int)L.n, d, nullptr, w.at<float>(L.logits), nullptr, false, false};
+    {
+      TimedLaunch tl(5, s);
+      LM_TRY(launch_kv_few(dt, fa, s));
+    }
+    TimedLaunch tl(6, s);
+    LM_TRY(launch_kv_mask(dt, w.at<float>(L.logits), b, xt, L.n, d, tau, (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0,
+                          k, m, xhat, s));
+    return LMHEAD_OK;
+  }
   // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
   pa.job[0] = param_copy(U, d, w.at<void>(L.UT), L.ldT, L.dp, true);
   pa.job[1] = param_copy(W, d, w.at<void>(L.WT), L.ldT, L.dp, true);
@@ -228,6 +244,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0;
   const bool accum = (desc->flags & DYNAKV_FLAG_ACCUM_GRAD) != 0;
 
+  const bool few = kv_few_fits(L.n, d);   // the parameters as the caller has them, no copies
   // parameter operands of the three token-major products: W^T (K-contiguous copy) for the logits, and
   // row-padded copies of W and U, which are K-contiguous as they are for g_l W^T and g_x~ U^T
   KvPrepareArgs pa{};
@@ -236,7 +253,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   pa.job[1] = param_copy(W, d, at(L.Wp), L.ldT, L.dp, false);
   pa.job[2] = param_copy(U, d, at(L.Up), L.ldT, L.dp, false);
   pa.njobs = 3;
-  LM_TRY(launch_kv_prepare(dt, pa, s));
+  if (!few) LM_TRY(launch_kv_prepare(dt, pa, s));
 
   KvGemmArgs ga{};
   ga.mode = 1;
@@ -252,7 +269,10 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ga.hdr = hdr;
   {
     TimedLaunch tl(5, s);
-    LM_TRY(launch_kv_gemm(dt, ga, s));
+    if (few)
+      LM_TRY(launch_kv_few(dt, {xt, d, W, (int)L.n, d, nullptr, ga.out_f, hdr, false, false}, s));
+    else
+      LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   {
     // g_l, and the direct part g_xhat * m of dL/dx~ (into the buffer that the next product adds to)
@@ -271,7 +291,10 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ga.accumulate = true;
   {
     TimedLaunch tl(9, s);
-    LM_TRY(launch_kv_gemm(dt, ga, s));
+    if (few)
+      LM_TRY(launch_kv_few(dt, {at(L.gl), d, W, (int)L.n, d, at(L.gxt), nullptr, nullptr, true, true}, s));
+    else
+      LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   // dx = g_x~ U^T
   ga.A = at(L.Up);
@@ -280,7 +303,10 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ga.accumulate = false;
   {
     TimedLaunch tl(10, s);
-    LM_TRY(launch_kv_gemm(dt, ga, s));
+    if (few)
+      LM_TRY(launch_kv_few(dt, {at(L.gxt), d, U, (int)L.n, d, dx, nullptr, nullptr, true, false}, s));
+    else
+      LM_TRY(launch_kv_gemm(dt, ga, s));
   }
 
   // Parameter gradients: contractions over the tokens, out[row][col] = sum_t B[row][t] A[col][t] with

@@ -157,6 +157,22 @@ struct KvGemmArgs {
 };
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
 
+// out[n][j] = sum_k x[n][k] M[k][j], or with `rows` sum_k x[n][k] M[j][k], for few tokens: M [d x d] as the caller has
+// it (no copy), 16 tokens x 64 columns per workgroup.  out_e (storage type) or out_f (fp32), dense rows of d, whichever is
+// non-null; accumulate: out_e is added to.  Clears the header unless null.
+struct KvFewArgs {
+  const void* x;
+  int64_t ldx;
+  const void* M;
+  int n, d;
+  void* out_e;
+  float* out_f;
+  WsHeader* hdr;
+  bool rows, accumulate;
+};
+bool kv_few_fits(int64_t n, int d);
+hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s);
+
 // The whole gate of many tokens in one kernel (dynakv_gate.hip), for callers that want x~ and k only.  Ufrag, Wfrag: the
 // parameter matrices in fragment order (KvCopy::kFragments, W's with the same `literal`).
 struct KvGateArgs {

@@ -249,6 +249,102 @@ hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// ---- few tokens -----------------------------------------------------------------------------
+//
+// A decoding step's products (16 tokens x 1024 x 1024: 2 MB of parameters, 34 Mflop) are latency and nothing else.  One
+// workgroup makes 16 tokens x 64 columns with sixteen wavefronts that share out the contraction, every load of a
+// wavefront in flight at once, and the sixteen partial tiles are added up in LDS in a fixed order.  The
+// parameter matrix is read as the caller has it, row k in memory = index k of the contraction: a lane takes 4
+// consecutive columns of the rows it needs, so MFMA t of four covers the columns 4 r + t (r = MFMA row), and the
+// bf16 fragments (8 values of k per lane and column) are put together with byte permutes.  kRows: out = x M^T, whose
+// fragments lie in memory as they are; MFMA t covers the columns 16 t + r.  No transposed or padded copies, so the launch
+// that made them goes too.
+constexpr int kFewWaves = 16, kFewCols = 64, kFewTok = 16;
+
+template <typename E, bool kRows>
+__global__ __launch_bounds__(64 * kFewWaves) void kv_few_kernel(KvFewArgs a) {
+  constexpr int PITCH = kFewCols + 4;   // floats
+  __shared__ __attribute__((aligned(16))) float part[kFewWaves][kFewTok * PITCH];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int q = lane >> 4, tl = lane & 15;
+  if (a.hdr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    a.hdr->err = 0;
+    a.hdr->nv = 0;
+  }
+  const int c0 = blockIdx.x * kFewCols, t0 = blockIdx.y * kFewTok;
+  const int tok = min(t0 + tl, a.n - 1);   // tokens past the end re-read the last one
+  f32x4_t acc[4] = {};
+  const int nsub = a.d / 32;               // sub-steps of 32 values of k, dealt out to the wavefronts
+  for (int s = w; s < nsub; s += kFewWaves) {
+    if constexpr (Elem<E>::size == 2) {
+      const char* const xp = static_cast<const char*>(a.x) + ((int64_t)tok * a.ldx + s * 32 + q * 8) * 2;
+      const bf16x8_t fx = *reinterpret_cast<const bf16x8_t*>(xp);
+      if constexpr (kRows) {
+        const char* const mp = static_cast<const char*>(a.M) + ((int64_t)(c0 + tl) * a.d + s * 32 + q * 8) * 2;
+        bf16x8_t f[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) f[t] = *reinterpret_cast<const bf16x8_t*>(mp + (int64_t)t * 16 * a.d * 2);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[t], fx, acc[t], 0, 0, 0);
+      } else {
+        const char* const mp = static_cast<const char*>(a.M) + ((int64_t)(s * 32 + q * 8) * a.d + c0 + tl * 4) * 2;
+        uint2 row[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) row[e] = *reinterpret_cast<const uint2*>(mp + (int64_t)e * a.d * 2);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          u32x4_t f;
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const uint32_t lo = t < 2 ? row[2 * p].x : row[2 * p].y, hi = t < 2 ? row[2 * p + 1].x : row[2 * p + 1].y;
+            f[p] = __builtin_amdgcn_perm(hi, lo, t & 1 ? 0x07060302u : 0x05040100u);
+          }
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f), fx, acc[t], 0, 0, 0);
+        }
+      }
+    } else {
+      // one value of k per lane and MFMA: group q takes k = 32 s + 16 h + 4 q + e in MFMA e
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k0 = s * 32 + h * 16 + q * 4;
+        const f32x4_t fx = *reinterpret_cast<const f32x4_t*>(static_cast<const float*>(a.x) + (int64_t)tok * a.ldx + k0);
+        // rows[u]: four columns of row k0 + u, or (kRows) k0 .. k0 + 3 of column 16 u + tl
+        const float* const mp = static_cast<const float*>(a.M) +
+                                (kRows ? (int64_t)(c0 + tl) * a.d + k0 : (int64_t)k0 * a.d + c0 + tl * 4);
+        f32x4_t rows[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rows[u] = *reinterpret_cast<const f32x4_t*>(mp + (int64_t)(kRows ? 16 : 1) * u * a.d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kRows ? rows[t][e] : rows[e][t], fx[e], acc[t], 0, 0, 0);
+      }
+    }
+  }
+  // accumulator v of MFMA t in lane group q is column 16 q + 4 v + t of the lane's token, or (kRows) 16 t + 4 q + v
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const f32x4_t o = kRows ? acc[u] : f32x4_t{acc[0][u], acc[1][u], acc[2][u], acc[3][u]};
+    *reinterpret_cast<f32x4_t*>(&part[w][tl * PITCH + (kRows ? 16 * u + 4 * q : 16 * q + 4 * u)]) = o;
+  }
+  __syncthreads();
+  const int ot = threadIdx.x / kFewCols, oc = threadIdx.x % kFewCols;
+  if (t0 + ot >= a.n) return;
+  float sum = 0.f;
+#pragma unroll
+  for (int u = 0; u < kFewWaves; ++u) sum += part[u][ot * PITCH + oc];
+  const int64_t at = (int64_t)(t0 + ot) * a.d + c0 + oc;
+  if (a.out_f) {
+    a.out_f[at] = sum;
+  } else {
+    using T = typename std::conditional<Elem<E>::size == 2, __bf16, float>::type;
+    T* const out = static_cast<T*>(a.out_e) + at;
+    *out = (T)(a.accumulate ? sum + (float)*out : sum);
+  }
+}
+static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
+
 template <typename E, int Mode>
 hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
   switch (tile_edge(Mode, a.M, a.Nn)) {
@@ -268,6 +364,31 @@ hipError_t launch_e(const KvGemmArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+// Up to two workgroups per compute unit: every 16 tokens read all of the parameters again.  Gate of n tokens, copies and
+// tiled products / these (us):
+//   d 1024 bf16: n 16 27.4 / 15.7   n 256 28.3 / 17.1   n 512 32.0 / 24.1   n 1024 32.5 / 36.0
+//   d 2048 bf16: n 16 48.0 / 20.8   n 256 47.6 / 37.6;   d 1024 fp32: n 16 54.3 / 23.6   n 512 58.3 / 39.4
+bool kv_few_fits(int64_t n, int d) {
+  return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= 2 * (int64_t)kComputeUnits;
+}
+
+hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)(a.d / kFewCols), (unsigned)((a.n + kFewTok - 1) / kFewTok));
+  const dim3 block(64 * kFewWaves);
+  if (dtype == LMHEAD_BF16) {
+    if (a.rows)
+      hipLaunchKernelGGL((kv_few_kernel<bf16_tag, true>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((kv_few_kernel<bf16_tag, false>), grid, block, 0, s, a);
+  } else {
+    if (a.rows)
+      hipLaunchKernelGGL((kv_few_kernel<f32_tag, true>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((kv_few_kernel<f32_tag, false>), grid, block, 0, s, a);
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s) {
   return dtype == LMHEAD_BF16 ? launch_e<bf16_tag>(a, s) : launch_e<f32_tag>(a, s);

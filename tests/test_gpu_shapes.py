@@ -273,3 +273,29 @@ def test_kv_gate_in_one_kernel(d, n, ldx, literal):
     for tau, want in ((-1.0, d), (1.5, 0)):
         _, kt, _, _ = kp.gate(tau, soft=False)
         assert torch.equal(kt, torch.full_like(kt, want))
+
+
+# the few-token products: one token to a group of 16 and its neighbours, the contraction shared by two to sixteen wavefronts and
+# taken in several turns, strided rows
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,d,ldx", [(1, 64, None), (1, 1024, None), (15, 128, 136), (16, 1024, 1032), (17, 576, None),
+                                     (33, 1088, None), (240, 1024, None), (8, 2048, None)])
+def test_kv_gate_of_few_tokens(dtype, n, d, ldx):
+    import workloads.dynakv as kv
+    from oracle import dynakv_oracle as K
+    from tests.harness import KvProblem
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d, dtype=dtype)
+    inp = kv.kv_inputs(cfg)
+    kp = KvProblem(cfg, inp, ldx=ldx)
+    kp.ws.fill_(0xFF)
+    xt, k, m, xhat = kp.gate(cfg.tau)
+    assert kp.check() == 0
+    f = wl.as_f64
+    o = K.gate(f(inp["x"]), f(inp["U"]), f(inp["W"]), inp["b"], cfg.tau, store_dtype=dtype)
+    # bounds as in test_kv_products_over_tile_edges
+    ulp, tol_m = (2.0 ** -7, 5e-3) if dtype == "bf16" else (2.0 ** -22, 1e-4)
+    assert np.all(np.abs(np64(xt) - o["xt"]) <= ulp * np.abs(o["xt"]) + 1e-6 * np.abs(o["xt"]).max())
+    assert np.abs(np64(m) - o["m"]).max() <= tol_m
+    assert np.abs(np64(xhat) - np64(xt) * np64(m)).max() <= 2.0 ** -8 * np.abs(np64(xt)).max()
+    xt2, k2, _, _ = kp.gate(cfg.tau, soft=False)
+    assert np.array_equal(np64(xt2), np64(xt)) and np.array_equal(k2.cpu().numpy(), k.cpu().numpy())
