@@ -339,6 +339,9 @@ struct GemmTArgs {
   bool part_accumulate;   // unless part_single.  part_slice = floats per slice (header.ksplit: n tiles x edge x part_ld).
   bool part_single;
   int edge;            // workgroup tile edge: 64, 128 or 256 (n_tiles_cap stays in units of kTile)
+  const void* A2;      // non-null: a second product of the same shape in the same launch, with its own operands and
+  const void* B2;      // out, its slices behind the first one's
+  float* out2;
 };
 
 // out[row(n)][m] (+)= sum_s part[s][n][m] for n < n_valid, m < M, slices summed in order.  With a row map:

@@ -311,50 +311,59 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
 
   // Parameter gradients: contractions over the tokens, out[row][col] = sum_t B[row][t] A[col][t] with
   // token-contiguous copies of both operands, cut into ksplit slices of the token range (one: stored directly).
-  auto param_grad = [&](const void* rows_src, int64_t ld_rows, const void* cols_src, int kind, float* out) -> int {
+  //   dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
+  auto token_copy = [&](const void* src, int64_t ld, size_t to) {
+    return KvCopy{src, ld, L.n, L.ncap, d, (int)L.dp, at(to), L.ldK, KvCopy::kTransposed, 0};
+  };
+  GemmTArgs ta{};
+  ta.A = at(L.T2);
+  ta.ldA = L.ldK;
+  ta.B = at(L.T1);
+  ta.ldB = L.ldK;
+  ta.M = d;
+  ta.n_limit = d;
+  ta.K = L.ncap;
+  ta.n_tiles_cap = L.dp / kTile;
+  ta.hdr = hdr;
+  ta.ksplit = L.ksplit;
+  ta.edge = L.edge;
+  ta.part = L.ksplit > 1 ? static_cast<float*>(at(L.part)) : nullptr;
+  ta.part_ld = d;
+  ta.part_slice = (int64_t)d * d;
+  ta.ldo = d;
+  ta.accumulate = accum;
+  // one gradient, or both: the second one's operands are in T3, T4
+  auto param_grad = [&](const KvPrepareArgs& copies, int kind, float* out, float* out2) -> int {
     {
       TimedLaunch tl(13, s);
-      KvPrepareArgs ta{};
-      ta.job[0] = {rows_src, ld_rows, L.n, L.ncap, d, (int)L.dp, at(L.T1), L.ldK, KvCopy::kTransposed, 0};
-      ta.job[1] = {cols_src, d, L.n, L.ncap, d, (int)L.dp, at(L.T2), L.ldK, KvCopy::kTransposed, 0};
-      ta.njobs = 2;
-      LM_TRY(launch_kv_prepare(dt, ta, s));
+      LM_TRY(launch_kv_prepare(dt, copies, s));
     }
-    GemmTArgs ta{};
-    ta.A = at(L.T2);
-    ta.ldA = L.ldK;
-    ta.B = at(L.T1);
-    ta.ldB = L.ldK;
-    ta.M = d;
-    ta.n_limit = d;
-    ta.K = L.ncap;
-    ta.n_tiles_cap = L.dp / kTile;
-    ta.hdr = hdr;
-    ta.ksplit = L.ksplit;
-    ta.edge = L.edge;
-    if (L.ksplit > 1) {
-      ta.part = static_cast<float*>(at(L.part));
-      ta.part_ld = d;
-      ta.part_slice = (int64_t)d * d;
-    } else {
-      ta.out = out;
-      ta.ldo = d;
-      ta.accumulate = accum;
-    }
+    ta.out = out;
+    ta.out2 = out2;
+    ta.A2 = out2 ? at(L.T4) : nullptr;
+    ta.B2 = out2 ? at(L.T3) : nullptr;
     {
       TimedLaunch tl(kind, s);
       LM_TRY(launch_gemm_t(dt, ta, s, 2));
     }
-    if (L.ksplit > 1)
-      LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, out, accum, s));
+    if (L.ksplit > 1) LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, out, accum, s, out2));
     return LMHEAD_OK;
   };
-  // dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
-  int prc = param_grad(xt, d, at(L.gl), 11, dW);
+  KvPrepareArgs copies{};
+  copies.job[0] = token_copy(xt, d, L.T1);
+  copies.job[1] = token_copy(at(L.gl), d, L.T2);
+  copies.njobs = 2;
+  if (L.pair) {
+    copies.job[2] = token_copy(x, desc->ldx, L.T3);
+    copies.job[3] = token_copy(at(L.gxt), d, L.T4);
+    copies.njobs = 4;
+    return param_grad(copies, 11, dW, dU);
+  }
+  const int prc = param_grad(copies, 11, dW, nullptr);
   if (prc != LMHEAD_OK) return prc;
-  prc = param_grad(x, desc->ldx, at(L.gxt), 12, dU);
-  if (prc != LMHEAD_OK) return prc;
-  return LMHEAD_OK;
+  copies.job[0] = token_copy(x, desc->ldx, L.T1);
+  copies.job[1] = token_copy(at(L.gxt), d, L.T2);
+  return param_grad(copies, 12, dU, nullptr);
 }
 
 int dynakv_check(void* ws, void* stream) { return lmhead_check(ws, stream); }

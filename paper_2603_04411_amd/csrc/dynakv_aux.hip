@@ -441,9 +441,14 @@ void kv_mask_bwd_kernel(const float* __restrict__ logits, const float* __restric
 //    wavefronts each sum every sixteenth row, eight loads at a time.  (With four wavefronts and a chain of four loads each,
 //    1024 rows of 1024 columns took 22 us, now 5.4.)
 __global__ __launch_bounds__(256) void kv_sum_slices_kernel(const float* __restrict__ part, int rows, int64_t row_pitch,
-                                                            int64_t len4, float* __restrict__ out, int accumulate) {
+                                                            int64_t len4, float* __restrict__ out,
+                                                            float* __restrict__ out2, int accumulate) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j >= len4) return;
+  if (blockIdx.y) {
+    part += (int64_t)rows * row_pitch;
+    out = out2;
+  }
   float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
   for (int r = 0; r < rows; ++r) {
@@ -462,8 +467,13 @@ constexpr int kSumWaves = 16, kSumBatch = 8;
 
 __global__ __launch_bounds__(64 * kSumWaves) void kv_sum_rows_kernel(const float* __restrict__ part, int rows,
                                                                      int64_t row_pitch, int64_t len,
-                                                                     float* __restrict__ out, int accumulate) {
+                                                                     float* __restrict__ out, float* __restrict__ out2,
+                                                                     int accumulate) {
   __shared__ float sm[kSumWaves][64];
+  if (blockIdx.y) {
+    part += (int64_t)rows * row_pitch;
+    out = out2;
+  }
   const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
   const int64_t j = (int64_t)blockIdx.x * 64 + cl;
   float t[kSumBatch] = {};
@@ -939,14 +949,15 @@ hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, co
 }
 
 hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, int64_t len, float* out,
-                              bool accumulate, hipStream_t s) {
+                              bool accumulate, hipStream_t s, float* out2) {
+  const unsigned outs = out2 ? 2 : 1;
   // 256 rows: above the most slices of a parameter gradient, which has d x d columns
   if (rows <= 256 && len % 4 == 0 && row_pitch % 4 == 0 && len >= 16384)
-    hipLaunchKernelGGL(kv_sum_slices_kernel, dim3((unsigned)((len / 4 + 255) / 256)), dim3(256), 0, s, part, rows,
-                       row_pitch, len / 4, out, accumulate ? 1 : 0);
+    hipLaunchKernelGGL(kv_sum_slices_kernel, dim3((unsigned)((len / 4 + 255) / 256), outs), dim3(256), 0, s, part, rows,
+                       row_pitch, len / 4, out, out2, accumulate ? 1 : 0);
   else
-    hipLaunchKernelGGL(kv_sum_rows_kernel, dim3((unsigned)((len + 63) / 64)), dim3(64 * kSumWaves), 0, s, part, rows,
-                       row_pitch, len, out, accumulate ? 1 : 0);
+    hipLaunchKernelGGL(kv_sum_rows_kernel, dim3((unsigned)((len + 63) / 64), outs), dim3(64 * kSumWaves), 0, s, part,
+                       rows, row_pitch, len, out, out2, accumulate ? 1 : 0);
   return hipGetLastError();
 }
 

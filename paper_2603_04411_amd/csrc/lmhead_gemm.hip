@@ -632,14 +632,15 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
     if (p < NPH && n < n_lim) my_row = (int)(to_part ? n : (a.rowmap ? (int64_t)a.rowmap[n] : a.row_base + n));
   }
   const int64_t part_slice = a.ksplit > 0 ? a.part_slice : (int64_t)ntiles * G::BN * a.part_ld;
-  float* const outp = to_part ? a.part + (size_t)slice * part_slice : a.out;
+  const bool second = blockIdx.y != 0;
+  float* const outp = to_part ? a.part + (size_t)(slice + (second ? ksplit : 0)) * part_slice : second ? a.out2 : a.out;
   const int64_t ldo = to_part ? a.part_ld : a.ldo;
   const bool accumulate = to_part ? a.part_accumulate : a.accumulate;
 
   typename G::Acc acc;
   G::zero(acc);
-  G::run(acc, static_cast<const char*>(a.A) + (int64_t)m0 * pitchA + (int64_t)k_first * G::KB, offA,
-         static_cast<const char*>(a.B) + n0 * pitchB + (int64_t)k_first * G::KB, offB, ksteps, smem, Role == 0 ? 3 : (Role == 1 ? 4 : 0));
+  G::run(acc, static_cast<const char*>(second ? a.A2 : a.A) + (int64_t)m0 * pitchA + (int64_t)k_first * G::KB, offA,
+         static_cast<const char*>(second ? a.B2 : a.B) + n0 * pitchB + (int64_t)k_first * G::KB, offB, ksteps, smem, Role == 0 ? 3 : (Role == 1 ? 4 : 0));
 
   // Rows go in batches: the LDS reads and the loads of the old values of a whole batch are issued before its
   // first store, so a wave that is alone on its SIMD does not sit out one memory round trip per row.
@@ -751,7 +752,7 @@ static hipError_t launch_gemm_t_edge(const GemmTArgs& a, hipStream_t s) {
   const int64_t m_tiles = (a.M + Edge - 1) / Edge, n_cap = a.n_tiles_cap * (kTile / Edge);
   // slices chosen on the device: at most kSplitTiles slice tiles when there are several per tile
   const int64_t y_cap = a.ksplit > 0 ? n_cap * a.ksplit : (n_cap > kSplitTiles / m_tiles ? n_cap : kSplitTiles / m_tiles);
-  const dim3 grid(xcd_grid_size((int)m_tiles, y_cap, kMapBy));
+  const dim3 grid(xcd_grid_size((int)m_tiles, y_cap, kMapBy), a.A2 ? 2 : 1);
   hipError_t e = allow_lds<gemm_t_kernel<E, Role, Edge>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((gemm_t_kernel<E, Role, Edge>), grid, dim3(G::NT), G::LDS_BYTES, s, a);
