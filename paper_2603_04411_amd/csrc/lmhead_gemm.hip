@@ -650,6 +650,10 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   const int c = G::lane() % CH;                   // its 16-byte chunk of the row = 4 output columns
   const int m = m0 + c * 4;
   const bool m_ok = m < a.M;
+  // dW is written once, gigabytes of it, and not read again by this library: past the caches, so that W, which the next
+  // forward reads, can stay there in part (192 x 2048 x 151936: that forward 211 -> 185 us, the step 1177 -> 1152).  The
+  // slices of a split contraction are read back at once and stay in (streamed too, dH took 199 us instead of 187).
+  const bool stream = Role == 1 && !to_part && !accumulate;
 #pragma unroll
   for (int jg = 0; jg < NPH; ++jg) {
 #pragma unroll
@@ -687,9 +691,15 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
 #pragma unroll
         for (int u = 0; u < RB; ++u) v[u] += old[u];
       }
+      if (stream) {
 #pragma unroll
-      for (int u = 0; u < RB; ++u)
-        if (dst[u]) *dst[u] = v[u];
+        for (int u = 0; u < RB; ++u)
+          if (dst[u]) __builtin_nontemporal_store(v[u], dst[u]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < RB; ++u)
+          if (dst[u]) *dst[u] = v[u];
+      }
     }
     if (jg + 1 < NPH) lds_barrier();
   }
