@@ -652,8 +652,10 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   const bool m_ok = m < a.M;
   // dW is written once, gigabytes of it, and not read again by this library: past the caches, so that W, which the next
   // forward reads, can stay there in part (192 x 2048 x 151936: that forward 211 -> 185 us, the step 1177 -> 1152).  The
-  // slices of a split contraction are read back at once and stay in (streamed too, dH took 199 us instead of 187).
-  const bool stream = Role == 1 && !to_part && !accumulate;
+  // slices of a split contraction are read back at once and stay in (streamed too, dH took 199 us instead of 187), and
+  // so does dW where the matrix cores bound it: over 5000 tokens or more streaming cost 0.1 to 0.4 % of the step.
+  constexpr int64_t kStreamTokens = 2048;
+  const bool stream = Role == 1 && !to_part && !accumulate && kel <= kStreamTokens;
 #pragma unroll
   for (int jg = 0; jg < NPH; ++jg) {
 #pragma unroll
