@@ -35,11 +35,18 @@ constexpr int kKvMapBx = 4, kKvMapBy = 4;
 // a compute unit.  The reconstruction's tiles differ in length, which leaves its rounds more ragged, and more
 // and smaller tiles even them out: edge 128 up to four rounds (n = 16411, 32768, 65536: 32.8 / 51.6 / 95.5 against
 // 39.0 / 54.6 / 91.8 with edge 256).
-int tile_edge(int mode, int M, int64_t Nn) {
+// Beyond that the padding of the d columns counts too: 320 columns are 512 in 256 wide tiles and 384 in 128 wide ones,
+// 128 columns 256 and 128 (gate of 37065 x 320 94 -> 63 us, fp32 40000 x 320 354 -> 195, 262144 x 128 201 -> 147).
+int tile_edge(bool f32, int mode, int M, int64_t Nn) {
   const int64_t room = 2 * (int64_t)device_compute_units();
   auto tiles = [&](int edge) { return (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge); };
   if (tiles(64) <= room) return 64;
-  return tiles(128) <= (mode == 2 ? 4 : 1) * room ? 128 : 256;
+  if (tiles(128) <= (mode == 2 ? 4 : 1) * room) return 128;
+  int best = 256;
+  auto cost = [&](int edge) { return (float)((M + edge - 1) / edge * edge) / tile_rate(edge, f32); };
+  for (int edge : {128, 64})
+    if (cost(edge) < cost(best)) best = edge;
+  return best;
 }
 // Workgroups of one tile edge that share a compute unit (bound by LDS: five slots of edge x 128 bytes each).
 constexpr int wg_per_cu(int edge) { return 256 / edge; }
@@ -347,7 +354,7 @@ static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
 
 template <typename E, int Mode>
 hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
-  switch (tile_edge(Mode, a.M, a.Nn)) {
+  switch (tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn)) {
     case 64: return launch_tiles<E, 64, Mode>(a, s);
     case 128: return launch_tiles<E, 128, Mode>(a, s);
     default: return launch_tiles<E, 256, Mode>(a, s);

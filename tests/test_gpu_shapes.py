@@ -27,23 +27,21 @@ def test_softmax_merge_over_vocabulary_tiles(tiles, T):
         assert np.abs(np64(got) - want).max() <= 1e-4
 
 
-def _kv_edge(mode, d, n, cus):
-    """Tile edge that the KV products take (the rule of dynakv_gemm.hip)."""
-    tiles = lambda e: -(-d // e) * -(-n // e)  # noqa: E731
-    return 64 if tiles(64) <= 2 * cus else 128 if tiles(128) <= (8 if mode == 2 else 2) * cus else 256
+def _kv_edges(d, n):
+    """Tile edges that the KV products may take."""
+    return [e for e in (64, 128, 256) if e == 64 or d > 64]
 
 
 # token counts at the edges of the rule that picks a tile edge, of the tiles themselves, and of the XCD deal-out
 @pytest.mark.parametrize("dtype,d,n", [
     ("bf16", 64, 1), ("bf16", 64, 63), ("bf16", 192, 65), ("bf16", 320, 6553), ("bf16", 320, 6593),
     ("bf16", 448, 16384), ("bf16", 448, 16400), ("bf16", 448, 65537), ("f32", 64, 64), ("f32", 192, 129),
-    ("f32", 320, 6600), ("f32", 448, 16390)])
+    ("f32", 320, 6600), ("f32", 448, 16390),
+    ("bf16", 128, 70001), ("bf16", 320, 40003), ("f32", 128, 70001)])
 def test_kv_products_over_tile_edges(dtype, d, n):
-    import torch
     import workloads.dynakv as kv
     from oracle import dynakv_oracle as K
     from tests.harness import KvProblem
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
     cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d, dtype=dtype)
     inp = kv.kv_inputs(cfg)
     kp = KvProblem(cfg, inp)
@@ -52,8 +50,7 @@ def test_kv_products_over_tile_edges(dtype, d, n):
     xbar = kp.reconstruct(packed, int(off[-1].item()), off, k)
     assert kp.check() == 0
     # every tile's first, last and middle rows, and the rows next to a tile boundary
-    e0, e2 = _kv_edge(0, d, n, cus), _kv_edge(2, d, n, cus)
-    rows = np.unique(np.clip([v for e in (e0, e2) for c in (0, 1, n // e // 2, n // e) for v in
+    rows = np.unique(np.clip([v for e in _kv_edges(d, n) for c in (0, 1, n // e // 2, n // e) for v in
                               (c * e - 1, c * e, c * e + e // 2, n - 1)], 0, n - 1))
     f = wl.as_f64
     o = K.gate(f(inp["x"][rows]), f(inp["U"]), f(inp["W"]), inp["b"], cfg.tau, store_dtype=dtype)
@@ -71,7 +68,7 @@ def test_kv_products_over_tile_edges(dtype, d, n):
 
 # each tile edge of dW / dU with one and several slices, odd token counts and widths that are no multiple of the edge
 @pytest.mark.parametrize("dtype,d,n", [("bf16", 64, 1), ("bf16", 192, 515), ("bf16", 1088, 700), ("bf16", 832, 5000),
-                                       ("bf16", 1024, 16500), ("f32", 64, 3), ("f32", 320, 129), ("f32", 576, 2500)])
+                                       ("bf16", 1024, 16500), ("bf16", 128, 20001), ("bf16", 320, 9001), ("f32", 64, 3), ("f32", 320, 129), ("f32", 576, 2500)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_kv_parameter_gradients_over_splits(dtype, d, n, accumulate):
     import torch
