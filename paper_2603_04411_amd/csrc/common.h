@@ -13,9 +13,6 @@
 
 namespace lmhead {
 
-// Macro-tile of every contraction: 256 x 256 outputs.
-constexpr int kTile = 256;
-
 // Internal operand-type code of the logits kernels when LMHEAD_FLAG_FP8_LOGITS is set (the public
 // dtype codes are LMHEAD_F32 = 0 and LMHEAD_BF16 = 1).
 constexpr int kDtypeFp8 = 2;
@@ -33,52 +30,6 @@ struct WsHeader {
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte line");
 
 static inline size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
-
-// Tile edges of the LM-head kernels (four wavefronts per tile whatever the edge; 256 / edge workgroups share a compute
-// unit).  256 needs the fewest operand bytes per flop, the only edge the vector L1 feeds at full bf16 rate.  The smaller
-// ones give more and shorter tiles when 256 x 256 would leave most of the chip idle, waste less on padding when
-// there are few tokens, and two or four workgroups on a compute unit overlap one's stores with another's loads.
-// Times in us (n = slots, about 60 % of them valid; forward / dW; dH below):
-//                                            edge 256        edge 128        edge 64
-//   n 256   d 1024 V 8000   bf16            32.1 / 37.0     15.7 / 14.4     13.1 / 15.9
-//   n 1024  d 1024 V 20000  bf16            36.9 / 66.6     40.1 / 49.3     62.1 / 49.7
-//   n 192   d 2048 V 151936 bf16             239 / 310       215 / 295       218 / 296
-//   n 64    d 2048 V 151936 bf16             243 / 271       213 / 256       188 / 287
-//   n 384   d 2048 V 151936 bf16, all valid  296 / 432       288 / 497
-//   n 256   d 256  V 4096   fp32            72.9 / 32.0     23.5 / 19.9     11.4 / 10.4
-//   n 1024  d 512  V 20000  fp32             135 / 162       130 / 125       114 / 112
-//   n 4096  d 1024 V 16000  fp32             721 / 558       609 / 567       591 / 595
-// fp32 products are matrix-core bound on any edge, so there the edge only has to keep the chip evenly filled.
-static inline int64_t tiles_of(int64_t m, int64_t n, int edge) { return ((m + edge - 1) / edge) * ((n + edge - 1) / edge); }
-// the smallest edge whose tiles run in one round, two to a compute unit
-static inline int one_round_edge(int64_t m, int64_t n) {
-  return tiles_of(m, n, 64) <= 2 * kComputeUnits ? 64 : tiles_of(m, n, 128) <= 2 * kComputeUnits ? 128 : kTile;
-}
-// Logits (forward and dZ): m = vocabulary rows of all policies, n = token slots.
-static inline int logits_edge(bool f32, int64_t m, int64_t n) {
-  if (f32 && tiles_of(m, n, kTile) <= 4 * kComputeUnits) return 64;
-  const int e = n <= 64 ? 64 : n <= 192 ? 128 : kTile;   // few tokens: one tile of them, with little padding
-  const int r = one_round_edge(m, n);
-  return r < e ? r : e;
-}
-// dW: m = d, rows = vocabulary rows of a chunk, n = token slots (the contraction).
-static inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
-  const int64_t t = tiles_of(m, rows, kTile);
-  if (f32) return t <= kComputeUnits * 7 / 8 ? 64 : kTile;
-  const int r = one_round_edge(m, rows);
-  return r < kTile ? r : (n <= 192 || t <= 2 * kComputeUnits) ? 128 : kTile;
-}
-// dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
-// slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not
-// exceed the tokens by much.  (n 1024 d 1024 V 20000: 68.9 / 48.8 / 59.9 us on edge 256 / 128 / 64; n 256 V 8000:
-// 40.5 / 25.6 / 23.1; n 256 d 256 V 4096 fp32: 133 / 28 / 17.7; n 4096 d 1024 V 16000 fp32: 736 / 702 / 623.)
-static inline int dh_edge(bool f32, int64_t m, int64_t n, int64_t ksteps) {
-  if (f32) return tiles_of(m, n, kTile) <= 4 * kComputeUnits ? 64 : kTile;
-  const int64_t slices = ksteps / 32 > 0 ? ksteps / 32 : 1;
-  if (n > 128 && tiles_of(m, n, kTile) * slices >= kComputeUnits) return kTile;
-  if (n > 64 && tiles_of(m, n, 128) * slices >= kComputeUnits) return 128;
-  return 64;
-}
 
 // Byte offsets of every workspace region for one descriptor.  All regions are
 // 256-byte aligned.  "cap" sizes are worst cases (every slot valid) because
@@ -140,7 +91,7 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.Vc = vc;
   L.nchunks = (L.Vp + vc - 1) / vc;
   const bool f32 = d->dtype == LMHEAD_F32;
-  L.edge = (d->flags & LMHEAD_FLAG_FP8_LOGITS) ? kTile : logits_edge(f32, npol * (int64_t)d->V, L.N);
+  L.edge = (d->flags & LMHEAD_FLAG_FP8_LOGITS) ? kTile : logits_edge(f32, d->V, L.N);
   L.edge_w = dw_edge(f32, d->d, vc, L.N);
   L.ntiles = (d->V + L.edge - 1) / L.edge;
   size_t off = 0;

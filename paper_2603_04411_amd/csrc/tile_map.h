@@ -13,6 +13,9 @@
 
 namespace lmhead {
 
+// Macro-tile of the contractions: the widest tile edge, and the unit that operands are padded to.
+constexpr int kTile = 256;
+
 // Workgroup -> tile mapping that keeps L2 traffic local to an XCD.
 //
 // The chip dispatches workgroup i of a 1-D grid to XCD i % 8, and each XCD has a private L2.
@@ -77,6 +80,53 @@ inline float tile_rate(int edge, bool f32) {
 
 // Compute units that the launch rules count on (a GPU need not be present where workspaces are sized).
 constexpr int kComputeUnits = 256;
+
+// Tile edges of the LM-head kernels (four wavefronts per tile whatever the edge; 256 / edge workgroups share a compute
+// unit).  256 needs the fewest operand bytes per flop, the only edge the vector L1 feeds at full bf16 rate.  The smaller
+// ones give more and shorter tiles when 256 x 256 would leave most of the chip idle, waste less on padding when
+// there are few tokens, and two or four workgroups on a compute unit overlap one's stores with another's loads.
+// Times in us (n = slots, about 60 % of them valid; forward / dW; dH below):
+//                                            edge 256        edge 128        edge 64
+//   n 256   d 1024 V 8000   bf16            32.1 / 37.0     15.7 / 14.4     13.1 / 15.9
+//   n 1024  d 1024 V 20000  bf16            36.9 / 66.6     40.1 / 49.3     62.1 / 49.7
+//   n 192   d 2048 V 151936 bf16             239 / 310       215 / 295       218 / 296
+//   n 64    d 2048 V 151936 bf16             243 / 271       213 / 256       188 / 287
+//   n 384   d 2048 V 151936 bf16, all valid  296 / 432       288 / 497
+//   n 256   d 256  V 4096   fp32            72.9 / 32.0     23.5 / 19.9     11.4 / 10.4
+//   n 1024  d 512  V 20000  fp32             135 / 162       130 / 125       114 / 112
+//   n 4096  d 1024 V 16000  fp32             721 / 558       609 / 567       591 / 595
+// fp32 products are matrix-core bound on any edge, so there the edge only has to keep the chip evenly filled.
+inline int64_t tiles_of(int64_t m, int64_t n, int edge) { return ((m + edge - 1) / edge) * ((n + edge - 1) / edge); }
+// the smallest edge whose tiles run in one round, two to a compute unit
+inline int one_round_edge(int64_t m, int64_t n) {
+  return tiles_of(m, n, 64) <= 2 * kComputeUnits ? 64 : tiles_of(m, n, 128) <= 2 * kComputeUnits ? 128 : kTile;
+}
+// Logits (forward and dZ): m = vocabulary rows, n = token slots.  A pass over several weight matrices takes the edge of a
+// single one: the edge groups the terms of the softmax, and the two calls promise the same bits.
+inline int logits_edge(bool f32, int64_t m, int64_t n) {
+  if (f32 && tiles_of(m, n, kTile) <= 4 * kComputeUnits) return 64;
+  const int e = n <= 64 ? 64 : n <= 192 ? 128 : kTile;   // few tokens: one tile of them, with little padding
+  const int r = one_round_edge(m, n);
+  return r < e ? r : e;
+}
+// dW: m = d, rows = vocabulary rows of a chunk, n = token slots (the contraction).
+inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
+  const int64_t t = tiles_of(m, rows, kTile);
+  if (f32) return t <= kComputeUnits * 7 / 8 ? 64 : kTile;
+  const int r = one_round_edge(m, rows);
+  return r < kTile ? r : (n <= 192 || t <= 2 * kComputeUnits) ? 128 : kTile;
+}
+// dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
+// slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not
+// exceed the tokens by much.  (n 1024 d 1024 V 20000: 68.9 / 48.8 / 59.9 us on edge 256 / 128 / 64; n 256 V 8000:
+// 40.5 / 25.6 / 23.1; n 256 d 256 V 4096 fp32: 133 / 28 / 17.7; n 4096 d 1024 V 16000 fp32: 736 / 702 / 623.)
+inline int dh_edge(bool f32, int64_t m, int64_t n, int64_t ksteps) {
+  if (f32) return tiles_of(m, n, kTile) <= 4 * kComputeUnits ? 64 : kTile;
+  const int64_t slices = ksteps / 32 > 0 ? ksteps / 32 : 1;
+  if (n > 128 && tiles_of(m, n, kTile) * slices >= kComputeUnits) return kTile;
+  if (n > 64 && tiles_of(m, n, 128) * slices >= kComputeUnits) return 128;
+  return 64;
+}
 
 // Slices of dH's contraction over the vocabulary: a tile grid that fills the chip's rounds badly (few tokens, or
 // 1.4 rounds of tiles) is cut into `ks` slices per tile, summed in order afterwards.  The number of tiles follows from

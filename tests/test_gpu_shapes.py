@@ -296,3 +296,32 @@ def test_kv_gate_of_few_tokens(dtype, n, d, ldx):
     assert np.abs(np64(xhat) - np64(xt) * np64(m)).max() <= 2.0 ** -8 * np.abs(np64(xt)).max()
     xt2, k2, _, _ = kp.gate(cfg.tau, soft=False)
     assert np.array_equal(np64(xt2), np64(xt)) and np.array_equal(k2.cpu().numpy(), k.cpu().numpy())
+
+
+# one pass over several weight matrices against separate calls, bit for bit, at sizes where a rule that counted the vocabulary
+# rows of all the matrices would take another tile edge than the single call
+@pytest.mark.parametrize("dtype,N,V,d", [("bf16", 208, 32000, 64), ("bf16", 520, 8192, 64), ("bf16", 264, 4096, 128),
+                                         ("bf16", 60, 16500, 64), ("f32", 8200, 4096, 32), ("f32", 200, 151936, 32)])
+def test_multi_policy_pass_is_bit_identical_to_separate_calls(dtype, N, V, d):
+    import torch
+    import paper_2603_04411_amd as L
+    g = torch.Generator(device="cuda").manual_seed(N + V)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    H = torch.randn(N, d, generator=g, device="cuda").to(tdt)
+    Ws = [(torch.randn(V, d, generator=g, device="cuda") * 0.1).to(tdt) for _ in range(3)]
+    tok = torch.randint(0, V, (N,), generator=g, device="cuda", dtype=torch.int32)
+    lens = torch.tensor([N // 2, N // 2 - 3], dtype=torch.int32, device="cuda")
+    desc = L.make_desc(1, 2, N // 2, d, V, dtype)
+    out = lambda: torch.full((N,), 7.0, device="cuda")  # noqa: E731
+    singles = []
+    ws = torch.empty(L.workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    for W in Ws:
+        o = [out() for _ in range(3)]
+        L.lmhead_logprob_fwd(desc, H, W, tok, lens, *o, None, None, ws)
+        singles.append(o)
+    for npol in (1, 2, 3):
+        logps, lse, ent = [out() for _ in range(npol)], out(), out()
+        ws = torch.empty(L.multi_workspace_bytes(desc, npol), dtype=torch.uint8, device="cuda")
+        L.lmhead_logprob_fwd_multi(desc, H, Ws[:npol], tok, lens, logps, lse, ent, None, None, ws)
+        assert all(torch.equal(logps[p], singles[p][0]) for p in range(npol)), npol
+        assert torch.equal(lse, singles[0][1]) and torch.equal(ent, singles[0][2]), npol
