@@ -400,6 +400,13 @@ __global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* _
         sc[u] = in ? p[plane + (size_t)c * Ncap] : 0.f;
         tc[u] = in && ent ? p[2 * plane + (size_t)c * Ncap] : 0.f;
       }
+      // a tile whose logits are all -inf holds nothing: its sum of exp * z is 0 * -inf
+#pragma unroll
+      for (int u = 0; u < kFinBatch; ++u) {
+        const bool none = mc[u] == -__builtin_huge_valf();
+        sc[u] = none ? 0.f : sc[u];
+        tc[u] = none ? 0.f : tc[u];
+      }
       float mn = m;
 #pragma unroll
       for (int u = 0; u < kFinBatch; ++u) mn = fmaxf(mn, mc[u]);

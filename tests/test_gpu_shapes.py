@@ -325,3 +325,23 @@ def test_multi_policy_pass_is_bit_identical_to_separate_calls(dtype, N, V, d):
         L.lmhead_logprob_fwd_multi(desc, H, Ws[:npol], tok, lens, logps, lse, ent, None, None, ws)
         assert all(torch.equal(logps[p], singles[p][0]) for p in range(npol)), npol
         assert torch.equal(lse, singles[0][1]) and torch.equal(ent, singles[0][2]), npol
+
+
+# vocabulary rows masked with -inf: a run of 256 of them is one tile, or several, that holds nothing; few and many slots
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [40, 1100])
+def test_vocabulary_tiles_of_minus_infinity(dtype, T):
+    cfg = wl.CONFIGS[1].scaled(P=1, G=2, T=T, d=64, V=1024, dtype=dtype, len_lo=1, len_hi=T)
+    inp = small_inputs(cfg)
+    H, W = inp["H"].copy(), inp["W"].copy()
+    one, ninf = (0x3F80, 0xFF80) if dtype == "bf16" else (1.0, -np.inf)
+    H[:, 0] = one
+    W[256:512, 0] = ninf
+    tok = inp["tok"] % 256
+    gp = GpuProblem(cfg, H, W, tok, inp["lens"])
+    logp, lse, ent, _, _ = gp.fwd()
+    assert gp.check() == 0
+    rows = np.r_[0:256, 512:1024]          # what is left of the vocabulary; the ids lie in its first 256
+    o = O.lmhead_logprob_fwd(wl.as_f64(H), wl.as_f64(W[rows]), tok, inp["lens"], cfg.T)
+    for got, want in zip((logp, lse, ent), o):
+        assert np.abs(np64(got) - want).max() <= 1e-4
