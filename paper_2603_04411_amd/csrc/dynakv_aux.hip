@@ -808,7 +808,7 @@ __global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* _
   double ks = 0.0;
   if (k)
     for (int64_t i = threadIdx.x; i < tn; i += 256) ks += min(max(k[t0 + i], 0), d);
-  float ms[4] = {};
+  double ms = 0.0;
   if (m) {
     const int64_t cnt4 = tn * d / 4;
     const float4* p = reinterpret_cast<const float4*>(m + t0 * d);
@@ -816,16 +816,20 @@ __global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* _
       float4 v[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] = i + 256 * u < cnt4 ? p[i + 256 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+      float t[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) ms[u] += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+      for (int u = 0; u < 4; ++u) t[u] = (v[u].x + v[u].y) + (v[u].z + v[u].w);
+      ms += (double)((t[0] + t[1]) + (t[2] + t[3]));
     }
   }
-  const float msum = wave_sum((ms[0] + ms[1]) + (ms[2] + ms[3]));
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ks += __shfl_xor(ks, o);
+  for (int o = 32; o > 0; o >>= 1) {
+    ks += __shfl_xor(ks, o);
+    ms += __shfl_xor(ms, o);
+  }
   if ((threadIdx.x & 63) == 0) {
     sk[threadIdx.x >> 6] = ks;
-    sm[threadIdx.x >> 6] = msum;
+    sm[threadIdx.x >> 6] = ms;
   }
   __syncthreads();
   if (threadIdx.x == 0) {

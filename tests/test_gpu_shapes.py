@@ -345,3 +345,19 @@ def test_vocabulary_tiles_of_minus_infinity(dtype, T):
     o = O.lmhead_logprob_fwd(wl.as_f64(H), wl.as_f64(W[rows]), tok, inp["lens"], cfg.T)
     for got, want in zip((logp, lse, ent), o):
         assert np.abs(np64(got) - want).max() <= 1e-4
+
+
+# many tokens per block of the sum: its error is that of one rounding to fp32, not of a long fp32 chain
+@pytest.mark.parametrize("n,d", [(4096, 1024), (16000000, 64)])
+def test_kv_retain_rate_of_a_constant_mask(n, d):
+    import torch
+    import paper_2603_04411_amd as L
+    desc = L.make_kv_desc(n, d, "bf16")
+    m = torch.full((n, d), 0.1, device="cuda")
+    out = torch.empty(3, device="cuda")
+    ws = torch.empty(L.dynakv_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    L.dynakv_retain(desc, None, m, 0.5, out, None, ws)
+    assert L.dynakv_check(ws) == 0
+    want = float(np.float32(0.1))
+    # 16 values are added up in fp32 before fp64 takes over (four roundings, 2^-24 each), then one rounding of the result
+    assert abs(float(out[1]) - want) <= 5 * 2.0 ** -24 * want
