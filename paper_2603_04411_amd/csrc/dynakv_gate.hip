@@ -24,6 +24,8 @@
 #include "dynakv_common.h"
 #include "gemm_core.h"
 
+#include <type_traits>
+
 namespace lmhead {
 
 namespace {
@@ -43,7 +45,7 @@ struct Gate {
   static constexpr int LDS_BYTES = RED_OFF + 3 * 4 * TOK * 4;
   static constexpr int STEP = NI * 1024;        // bytes of one wavefront's fragments per sub-step
   static constexpr int PIECES = TOK / 4 * (ROW / 1024);   // 1 KB pieces of token rows per wavefront
-  static_assert((ROW == 1024 || ROW == 2048) && PIECES % S == 0 && S % 2 == 0 && LDS_BYTES <= 160 * 1024, "tile shape");
+  static_assert((ROW == 1024 || ROW == 2048) && PIECES % S == 0 && S % 2 == 0 && S >= 6 && LDS_BYTES <= 160 * 1024, "tile shape");
 };
 
 template <typename G>
@@ -100,25 +102,20 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
   f32x4_t acc[NI][TJ];
   Frags wb[2];
   u32x4_t fb[2][TJ];
-  // accumulators forced into their registers ahead of the asm MFMAs, and the wait states that those need (see
-  // GemmTile::settle)
-  auto settle = [&]() {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) asm volatile("" : "+a"(acc[i][j]));
-    asm volatile("s_nop 7");
-  };
-  // One sub-step: NI x TJ MFMAs; the token fragments of the next sub-step are read behind the first of them, and
+  // One sub-step: NI x TJ MFMAs (the first of a product starts from 0: no pass that clears the accumulators, and
+  // none of the wait states that a just-written addend needs, see GemmTile::settle); the token fragments of the next sub-step are read behind the first of them, and
   // each parameter fragment is replaced, one MFMA after its last use, by that of sub-step `ns` of stream `nr`.
-  auto substep = [&](const char* xrow, int s, int buf, bool more, bool refill, const __amdgpu_buffer_rsrc_t& nr, int ns) {
+  auto substep = [&](auto first_tag, const char* xrow, int s, int buf, bool more, bool refill, const __amdgpu_buffer_rsrc_t& nr, int ns) {
     const char* const xn = xrow + (s + 1) * 64;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
-        Elem<bf16_tag>::mma(acc[i][j], reinterpret_cast<const u32x4_t(&)[1]>(wb[buf][i]),
-                            reinterpret_cast<const u32x4_t(&)[1]>(fb[buf][j]));
+        if constexpr (decltype(first_tag)::value)
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[i][j]) : "v"(wb[buf][i]), "v"(fb[buf][j]));
+        else
+          Elem<bf16_tag>::mma(acc[i][j], reinterpret_cast<const u32x4_t(&)[1]>(wb[buf][i]),
+                              reinterpret_cast<const u32x4_t(&)[1]>(fb[buf][j]));
         if (more && i < 2 && (TJ <= 4 || j % 2 == i)) {
           // TJ reads over the first two rows of blocks
           if (TJ > 4 || (i == 0)) fb[buf ^ 1][j] = *reinterpret_cast<const u32x4_t*>(xn + j * 16 * G::PITCH);
@@ -130,23 +127,26 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     if (refill) wb[buf][NI - 1] = load_frag(nr, ns, NI - 1);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // acc += X W for one stream; with `chain`, the first two sub-steps of the next stream are on their way at the end
+  // acc = X W for one stream; with `chain`, the first two sub-steps of the next stream are on their way at the end
   auto product = [&](const __amdgpu_buffer_rsrc_t& r, bool chain, const __amdgpu_buffer_rsrc_t& next, auto&& per_substep) {
     const int l = lane_id();
     const char* const xrow = smem + (l & 15) * G::PITCH + (l >> 4) * 16;
 #pragma unroll
     for (int j = 0; j < TJ; ++j) fb[0][j] = *reinterpret_cast<const u32x4_t*>(xrow + j * 16 * G::PITCH);
-    settle();
     __builtin_amdgcn_sched_barrier(0);
-    for (int s = 0; s < S - 2; s += 2) {
-      substep(xrow, s, 0, true, true, r, s + 2);
+    substep(std::true_type{}, xrow, 0, 0, true, true, r, 2);
+    per_substep(0);
+    substep(std::false_type{}, xrow, 1, 1, true, true, r, 3);
+    per_substep(1);
+    for (int s = 2; s < S - 2; s += 2) {
+      substep(std::false_type{}, xrow, s, 0, true, true, r, s + 2);
       per_substep(s);
-      substep(xrow, s + 1, 1, true, true, r, s + 3);
+      substep(std::false_type{}, xrow, s + 1, 1, true, true, r, s + 3);
       per_substep(s + 1);
     }
-    substep(xrow, S - 2, 0, true, chain, next, 0);
+    substep(std::false_type{}, xrow, S - 2, 0, true, chain, next, 0);
     per_substep(S - 2);
-    substep(xrow, S - 1, 1, false, chain, next, 1);
+    substep(std::false_type{}, xrow, S - 1, 1, false, chain, next, 1);
     per_substep(S - 1);
     asm volatile("s_nop 15\n\ts_nop 15");   // results are read by ordinary instructions next
   };
@@ -167,10 +167,6 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     __syncthreads();
 
     // ---- x~ = x U
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     product(rU, true, rW, [](int) {});
     lds_barrier();   // every wavefront has read its last token fragments
     // rounded to bf16 into the place of x; blocks i, i + 1 are 8 consecutive columns
@@ -190,17 +186,8 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     }
     lds_barrier();
 
-    // ---- logits = x~ W + b, with x~ streamed out to memory meanwhile
+    // ---- x~ W, with x~ streamed out to memory meanwhile
     const int l2 = lane_id();
-    {
-      const float* const bp = bias_s + w * (G::D / 4) + (l2 >> 4) * (G::D / 16);
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const f32x4_t b = *reinterpret_cast<const f32x4_t*>(bp + 4 * i);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = b;
-      }
-    }
     const uint32_t xt0 = (uint32_t)t0 * G::ROW + l2 * 16;
     product(rW, false, rU, [&](int s) {
 #pragma unroll
@@ -223,21 +210,33 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     };
     const int x16 = l3 ^ 16, x32 = l3 ^ 32;
     float mx[TJ];
+    {
+      // The bias goes onto the finished sums, as in the separate kernels: started from it, the accumulators would round
+      // every step of the contraction at the bias's magnitude.  (262144 tokens: 1019 -> 1026 us at d = 1024, 317 -> 313
+      // at d = 512, the passes that cleared the accumulators having gone; as fp32 MFMAs of bias * 1 under the maxima of
+      // the neighbouring block 1084 and 336.)  Four running maxima per token: a single chain would wait for itself.
+      const float* const bp = bias_s + w * (G::D / 4) + q * (G::D / 16);
+      f32x4_t m4[TJ];
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      // four running maxima: a single chain would wait for itself
-      f32x4_t m4 = acc[0][j];
+      for (int i = 0; i < NI; ++i) {
+        const f32x4_t b = *reinterpret_cast<const f32x4_t*>(bp + 4 * i);
 #pragma unroll
-      for (int i = 1; i < NI; ++i) {
-        const f32x4_t z = acc[i][j];
+        for (int j = 0; j < TJ; ++j) {
+          const f32x4_t z = acc[i][j] + b;
+          acc[i][j] = z;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) m4[v] = fmaxf(m4[v], z[v]);
+          for (int v = 0; v < 4; ++v) m4[j][v] = i == 0 ? z[v] : fmaxf(m4[j][v], z[v]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      float m = fmaxf(fmaxf(m4.x, m4.y), fmaxf(m4.z, m4.w));
-      m = fmaxf(m, of_lane(x16, m));
-      m = fmaxf(m, of_lane(x32, m));
-      if (q == 0) rt[w * G::TOK + 16 * j] = m;
-      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        float m = fmaxf(fmaxf(m4[j].x, m4[j].y), fmaxf(m4[j].z, m4[j].w));
+        m = fmaxf(m, of_lane(x16, m));
+        m = fmaxf(m, of_lane(x32, m));
+        if (q == 0) rt[w * G::TOK + 16 * j] = m;
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     lds_barrier();
     float own[TJ], above[TJ];   // sums of this lane's run and of the wavefront's runs behind it

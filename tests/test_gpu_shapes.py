@@ -361,3 +361,23 @@ def test_kv_retain_rate_of_a_constant_mask(n, d):
     want = float(np.float32(0.1))
     # 16 values are added up in fp32 before fp64 takes over (four roundings, 2^-24 each), then one rounding of the result
     assert abs(float(out[1]) - want) <= 5 * 2.0 ** -24 * want
+
+
+# a bias far above the logits (softmax does not see a common offset): the product is complete before the bias is added, as in
+# the separate kernels, so that the logits have one rounding at the bias's magnitude and not one per step of the contraction
+@pytest.mark.parametrize("d", [512, 1024])
+def test_kv_gate_in_one_kernel_under_a_large_bias(d):
+    import torch
+    import workloads.dynakv as kv
+    from tests.harness import KvProblem
+    n = 10300
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d)
+    kp = KvProblem(cfg, kv.kv_inputs(cfg))
+    kp.b = kp.b + 1.0e5
+    _, k, _, _ = kp.gate(cfg.tau, soft=False)
+    _, k2, m, _ = kp.gate(cfg.tau)
+    assert kp.check() == 0
+    lo, hi = torch.minimum(k, k2).long(), torch.maximum(k, k2).long()
+    for r in (lo != hi).nonzero().flatten().tolist():
+        # equal logits: the two masks are sums of the same exponentials in two orders
+        assert (m[r, lo[r]:hi[r]] - cfg.tau).abs().max() <= 2 * d * 2.0 ** -24
