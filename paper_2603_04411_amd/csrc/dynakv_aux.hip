@@ -609,16 +609,21 @@ __global__ __launch_bounds__(kKvScanBlock) void kv_scan_totals_kernel(const int3
   }
 }
 
-// One workgroup: blocksum <- its exclusive prefix sum.
+// One workgroup: blocksum <- its exclusive prefix sum, four totals per thread and turn.
 __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restrict__ blocksum, int nblocks) {
+  constexpr int PER = 4;
   __shared__ int64_t buf[1024];
   __shared__ int64_t carry_s;
   if (threadIdx.x == 0) carry_s = 0;
   __syncthreads();
-  for (int base = 0; base < nblocks; base += 1024) {
-    const int i = base + threadIdx.x;
-    const int64_t x = i < nblocks ? blocksum[i] : 0;
-    buf[threadIdx.x] = x;
+  for (int base = 0; base < nblocks; base += 1024 * PER) {
+    const int i = base + threadIdx.x * PER;
+    int64_t x[PER], own = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) x[u] = i + u < nblocks ? blocksum[i + u] : 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) own += x[u];
+    buf[threadIdx.x] = own;
     __syncthreads();
     for (unsigned o = 1; o < 1024; o <<= 1) {
       const int64_t y = threadIdx.x >= o ? buf[threadIdx.x - o] : 0;
@@ -627,7 +632,12 @@ __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restric
       __syncthreads();
     }
     const int64_t carry = carry_s;
-    if (i < nblocks) blocksum[i] = carry + buf[threadIdx.x] - x;
+    int64_t before = carry + buf[threadIdx.x] - own;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (i + u < nblocks) blocksum[i + u] = before;
+      before += x[u];
+    }
     __syncthreads();
     if (threadIdx.x == 1023) carry_s = carry + buf[1023];
     __syncthreads();
@@ -638,6 +648,8 @@ __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restric
 // what lies before its tokens itself: the totals of the blocks before (or their prefix sum, when there are so many that
 // `scanned` says that has been formed) and the tokens before it in its own block.  That replaces a scan launch and an offset
 // launch: five launches (25 us at 16 tokens, 32 us at 16411) became two, one up to kKvScanBlock tokens.
+// A wavefront's four tokens are under way together: one 16-byte chunk per lane of each is requested before the first is
+// stored (one token after the other 262144 x 64 took 61.7 us, now 43.6).
 // Then (no totals launch: blocksum is null) the first workgroup sees every token: it clears the header and sets
 // the error word for all of them with one store.
 constexpr int kKvPackTokens = 16;
@@ -648,7 +660,7 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, 
                                                       T* __restrict__ packed, int64_t capacity, WsHeader* hdr) {
   constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
   __shared__ int64_t part[4];
-  __shared__ int seg_s[kKvPackTokens];
+  __shared__ int seg_s[kKvPackTokens], k_s[kKvPackTokens];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t t0 = (int64_t)blockIdx.x * kKvPackTokens;
   const int64_t blk = t0 / kKvScanBlock;
@@ -660,9 +672,13 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, 
     for (int64_t i = threadIdx.x; i < blk; i += 256) before += blocksum[i];
   }
   const int64_t own = blk * kKvScanBlock + threadIdx.x;   // one token of the own block per thread
-  const int own_seg = own < n ? seg_len(k[own], d, bad) : 0;
+  const int own_k = own < n ? k[own] : 0;
+  const int own_seg = seg_len(own_k, d, bad);
   if (own < t0) before += own_seg;
-  if (own >= t0 && own < t0 + kKvPackTokens) seg_s[own - t0] = own_seg;
+  if (own >= t0 && own < t0 + kKvPackTokens) {
+    seg_s[own - t0] = own_seg;
+    k_s[own - t0] = min(max(own_k, 0), d);
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
   if (lane == 0) part[wave] = before;
@@ -692,26 +708,41 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, 
     }
   }
   if (blocksum && bad && own >= t0 && own < t0 + kKvPackTokens) atomicOr(&hdr->err, kErrKvCount);
+  // every wavefront: the sixteen segments' lengths and their exclusive prefix sums, one per lane
+  const int l16 = lane & (kKvPackTokens - 1);
+  const int seg16 = seg_s[l16], k16 = k_s[l16];
+  int excl16 = seg16;
 #pragma unroll
-  for (int u = 0; u < kKvPackTokens / 4; ++u) {
+  for (int o = 1; o < kKvPackTokens; o <<= 1) {
+    const int y = __shfl_up(excl16, o, kKvPackTokens);
+    if (l16 >= o) excl16 += y;
+  }
+  excl16 -= seg16;
+  if (wave == 0 && lane < kKvPackTokens && t0 + lane < n) {
+    const int64_t o = base + excl16;
+    off[t0 + lane] = o;
+    if (t0 + lane == n - 1) off[n] = o + seg16;
+    if (blocksum && o + seg16 > capacity) atomicOr(&hdr->err, kErrKvCapacity);
+  }
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  constexpr int PER = kKvPackTokens / 4;   // tokens of a wavefront
+  u32x4 first[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int ti = u * 4 + wave;
+    const int seg = __builtin_amdgcn_readlane(seg16, ti);
+    // lanes past the segment, and tokens past the last, read what is there and drop it
+    first[u] = *reinterpret_cast<const u32x4*>(xt + min(t0 + ti, n - 1) * d + max(min(lane * EPC, seg - EPC), 0));
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
     const int ti = u * 4 + wave;
     const int64_t tok = t0 + ti;
-    if (tok >= n) break;
-    int64_t o = base;
-    for (int q = 0; q < ti; ++q) o += seg_s[q];
-    const int seg = seg_s[ti];
-    if (lane == 0) {
-      off[tok] = o;
-      if (tok == n - 1) off[n] = o + seg;
-    }
-    if (o + seg > capacity) {
-      if (blocksum && lane == 0) atomicOr(&hdr->err, kErrKvCapacity);
-      continue;
-    }
-    const int kk = min(max(k[tok], 0), d);
-    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    const int seg = __builtin_amdgcn_readlane(seg16, ti), kk = __builtin_amdgcn_readlane(k16, ti);
+    const int64_t o = base + __builtin_amdgcn_readlane(excl16, ti);
+    if (tok >= n || o + seg > capacity) continue;
     for (int c = lane; c * EPC < seg; c += 64) {
-      u32x4 v = *reinterpret_cast<const u32x4*>(xt + tok * d + c * EPC);
+      u32x4 v = c == lane ? first[u] : *reinterpret_cast<const u32x4*>(xt + tok * d + c * EPC);
       if ((c + 1) * EPC > kk) {
         T e[EPC];
         __builtin_memcpy(e, &v, 16);
@@ -724,7 +755,7 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, 
     }
   }
 }
-static_assert(kKvScanBlock == 256 && kKvScanBlock % kKvPackTokens == 0, "one thread per token of a block");
+static_assert(kKvScanBlock == 256 && kKvScanBlock % kKvPackTokens == 0 && kKvPackTokens == 16, "one thread per token of a block");
 
 // ---- grouping by contraction length --------------------------------------------------------
 
@@ -984,9 +1015,10 @@ hipError_t launch_kv_store(int dtype, const void* xt, const int32_t* k, int64_t 
                            int64_t* off, void* packed, int64_t capacity, int64_t* blocksum, WsHeader* hdr,
                            hipStream_t s) {
   const int64_t nblocks = (n + kKvScanBlock - 1) / kKvScanBlock;
-  // Up to kScanFrom blocks every packing workgroup adds up the totals before it by itself (8 loads per thread at
-  // the most); beyond, that would grow with the square of n and one workgroup forms the prefix sums first.
-  constexpr int64_t kScanFrom = 2048;
+  // Up to kScanFrom blocks every packing workgroup adds up the totals before it by itself (4 loads per thread at
+  // the most); beyond, that would grow with the square of n and one workgroup forms the prefix sums first (whole call,
+  // tokens of 64 components: 524288 86.2 us without it, 79.4 with it).
+  constexpr int64_t kScanFrom = 1024;
   const int scanned = nblocks > kScanFrom ? 1 : 0;
   if (nblocks > 1)
     hipLaunchKernelGGL(kv_scan_totals_kernel, dim3((unsigned)nblocks), dim3(kKvScanBlock), 0, s, k, n, d, blocksum, hdr);

@@ -122,10 +122,13 @@ def test_kv_retain_rate_over_block_shares(n, d):
     np.testing.assert_allclose(gm.cpu().numpy(), soft / (n * d), rtol=1.5e-5)
 
 
-# packing groups of 16 tokens, scan blocks of 256, the step to a separate prefix sum (2048 blocks), counting blocks of 1024
+# packing groups of 16 tokens, scan blocks of 256, the step to a separate prefix sum (1024 blocks) and its second turn (4096),
+# counting blocks of 1024, segments of more than one turn of a wavefront
 @pytest.mark.parametrize("dtype,d,n", [("bf16", 64, 1), ("bf16", 128, 15), ("bf16", 64, 16), ("f32", 64, 17),
                                        ("bf16", 64, 255), ("bf16", 64, 256), ("bf16", 64, 257), ("f32", 128, 1025),
-                                       ("bf16", 64, 2049), ("bf16", 64, 524288), ("bf16", 64, 524300)])
+                                       ("bf16", 64, 2049), ("bf16", 64, 524288), ("bf16", 64, 524300),
+                                       ("f32", 576, 2050), ("bf16", 1088, 259), ("bf16", 64, 262144),
+                                       ("bf16", 64, 262145), ("bf16", 64, 1048600)])
 @pytest.mark.parametrize("off_base", [0, 1000 * 8])
 def test_kv_store_and_grouping_over_token_blocks(dtype, d, n, off_base):
     import torch
