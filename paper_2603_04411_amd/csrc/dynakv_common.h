@@ -71,6 +71,7 @@ struct KvBwdLayout {
 // Workgroups of the mask backward kernel: four 256-thread workgroups fit a compute unit (128 VGPRs),
 // so 1024 is one resident round on 256 compute units; each wavefront loops over its share of tokens.
 constexpr int kKvBwdMaxBlocks = 1024;
+constexpr int64_t kKvPairBytes = 32 << 20;
 
 static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   KvBwdLayout L{};
@@ -123,14 +124,25 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.gxt = take((size_t)L.ncap * L.d * L.esz);
   L.T1 = take((size_t)L.dp * L.ldK * L.esz);
   L.T2 = take((size_t)L.dp * L.ldK * L.esz);
-  // Up to 32 MB a copy the launches weigh more than the memory: one preparation, one product and one sum serve both
+  // Up to kKvPairBytes a copy the launches weigh more than the memory: one preparation, one product and one sum serve both
   // parameter gradients (4096 x 1024: 57 us of kernels before, 42 now; 300 x 128 fp32: 24 and 16).
-  L.pair = (size_t)L.dp * L.ldK * L.esz <= ((size_t)32 << 20);
+  L.pair = L.dp * L.ldK * L.esz <= kKvPairBytes;
   L.T3 = take(L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
   L.T4 = take(L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
   L.part = take((size_t)(L.pair ? 2 : 1) * L.ksplit * L.d * L.d * 4);
   L.dbpart = take((size_t)L.nblk * L.d * 4);
   L.total = off;
+  if (!L.pair) {
+    // A workspace sized for a long stream serves every shorter one: also the longest that still pairs, which may need more
+    // (bf16, d = 2048: 7680 tokens 1.42 times as much as 7936).
+    const int64_t ncap = (kKvPairBytes / (L.dp * L.esz) - 128 / L.esz) / kTile * kTile;
+    if (ncap > 0 && ncap < L.ncap) {
+      dynakv_desc shorter = *d;
+      shorter.n = (int32_t)ncap;
+      const size_t most = make_kv_bwd_layout(&shorter).total;
+      if (L.total < most) L.total = most;
+    }
+  }
   return L;
 }
 

@@ -240,6 +240,22 @@ def test_workspace_grows_with_the_problem_and_default_chunk_is_bounded():
     assert narrow < big
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_kv_workspaces_of_long_streams_serve_shorter_ones(lib, dtype):
+    for d in (64, 128, 320, 512, 1024, 2048, 8192):
+        sizes = []
+        n = 1
+        while True:
+            desc = L.make_kv_desc(n, d, dtype)
+            if n > 200000 or L.dynakv_validate_desc(desc) != 0:
+                break
+            sizes.append((L.dynakv_workspace_bytes(desc), L.dynakv_bwd_workspace_bytes(desc)))
+            n += max(1, n // 150)
+        assert len(sizes) > 500
+        for col in zip(*sizes):
+            assert list(col) == sorted(col), d
+
+
 def test_binding_has_no_cpu_fallback():
     import torch
     desc = L.make_desc(1, 1, 8, 64, 100, "bf16")
