@@ -91,7 +91,8 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.Vc = vc;
   L.nchunks = (L.Vp + vc - 1) / vc;
   const bool f32 = d->dtype == LMHEAD_F32;
-  L.edge = (d->flags & LMHEAD_FLAG_FP8_LOGITS) ? kTile : logits_edge(f32, d->V, L.N);
+  const bool fp8 = (d->flags & LMHEAD_FLAG_FP8_LOGITS) != 0;
+  L.edge = fp8 ? kTile : logits_edge(f32, d->V, L.N);
   L.edge_w = dw_edge(f32, d->d, vc, L.N);
   L.ntiles = (d->V + L.edge - 1) / L.edge;
   size_t off = 0;
@@ -108,7 +109,7 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.g_c = take((size_t)L.Ncap * 4);
   L.lse_c = take((size_t)L.Ncap * 4);
   L.zy = take((size_t)npol * L.Ncap * 4);
-  L.part = take((size_t)npol * 3 * L.ntiles * L.Ncap * 4);
+  L.part = take((size_t)npol * 3 * (fp8 ? L.ntiles * L.Ncap : logits_part_slots(f32, d->V, L.N)) * 4);
   const int64_t pad = 128 / L.esz;
   L.ldHc = d->d + pad;
   L.ldHcT = L.Ncap + pad;
@@ -134,7 +135,6 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   if ((size_t)L.Vc * L.dp * 4 * 8 < L.dWpart_bytes) L.dWpart_bytes = (size_t)L.Vc * L.dp * 4 * 8;
   L.dWpart = take(L.dWpart_bytes);
   L.ld8 = d->d + 128;
-  const bool fp8 = (d->flags & LMHEAD_FLAG_FP8_LOGITS) != 0;
   L.Hc8 = take(fp8 ? (size_t)L.Ncap * L.ld8 : 0);
   L.W8 = take(fp8 ? (size_t)npol * L.Vp * L.ld8 : 0);
   L.total = off;

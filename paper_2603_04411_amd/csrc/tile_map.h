@@ -101,13 +101,32 @@ inline int64_t tiles_of(int64_t m, int64_t n, int edge) { return ((m + edge - 1)
 inline int one_round_edge(int64_t m, int64_t n) {
   return tiles_of(m, n, 64) <= 2 * kComputeUnits ? 64 : tiles_of(m, n, 128) <= 2 * kComputeUnits ? 128 : kTile;
 }
-// Logits (forward and dZ): m = vocabulary rows, n = token slots.  A pass over several weight matrices takes the edge of a
+// Logits (forward and dZ): V = vocabulary rows, n = token slots.  A pass over several weight matrices takes the edge of a
 // single one: the edge groups the terms of the softmax, and the two calls promise the same bits.
-inline int logits_edge(bool f32, int64_t m, int64_t n) {
-  if (f32 && tiles_of(m, n, kTile) <= 4 * kComputeUnits) return 64;
-  const int e = n <= 64 ? 64 : n <= 192 ? 128 : kTile;   // few tokens: one tile of them, with little padding
-  const int r = one_round_edge(m, n);
-  return r < e ? r : e;
+// The most slots that a call may have for its tiles to be `edge` wide or narrower: one tile of tokens, with little padding, or
+// one round of tiles, two to a compute unit (fp32, edge 64: up to four rounds of 256 wide tiles).
+inline int64_t logits_slots(bool f32, int64_t V, int edge) {
+  const int64_t few = edge == 64 ? 64 : 192;
+  int64_t n = 2 * kComputeUnits / ((V + edge - 1) / edge) * edge;
+  if (f32 && edge == 64) {
+    const int64_t four = 4 * kComputeUnits / ((V + kTile - 1) / kTile) * kTile;
+    n = n > four ? n : four;
+  }
+  return n > few ? n : few;
+}
+inline int logits_edge(bool f32, int64_t V, int64_t n) {
+  return n <= logits_slots(f32, V, 64) ? 64 : n <= logits_slots(f32, V, 128) ? 128 : kTile;
+}
+// Per-tile softmax statistics (planes x slots) that the logits of any number of slots up to n need: fewer slots take narrower
+// tiles, i.e. more planes, and a workspace sized for a large batch has to serve the smaller ones.
+inline int64_t logits_part_slots(bool f32, int64_t V, int64_t n) {
+  int64_t most = 0;
+  for (int edge : {64, 128, kTile}) {
+    const int64_t slots = edge == kTile ? n : logits_slots(f32, V, edge);
+    const int64_t need = (V + edge - 1) / edge * (((slots < n ? slots : n) + kTile - 1) / kTile * kTile);
+    most = need > most ? need : most;
+  }
+  return most;
 }
 // dW: m = d, rows = vocabulary rows of a chunk, n = token slots (the contraction).
 inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {

@@ -256,6 +256,20 @@ def test_kv_workspaces_of_long_streams_serve_shorter_ones(lib, dtype):
             assert list(col) == sorted(col), d
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kw", [{}, {"flags": 8}, {"vocab_chunk": 256}])
+def test_workspaces_of_large_batches_serve_smaller_ones(dtype, kw):
+    for d, V in ((64, 100), (64, 4096), (1024, 8000), (512, 32000), (2048, 151936)):
+        sizes, n = [], 1
+        # up to where the default vocabulary chunk starts to shrink with the batch
+        while n <= min(40000, (48 << 30) // (8 * V)):
+            desc = L.make_desc(1, 1, n, d, V, dtype, **kw)
+            sizes.append([L.workspace_bytes(desc)] + [L.multi_workspace_bytes(desc, p) for p in (2, 4)])
+            n += max(1, n // 250)
+        for col in zip(*sizes):
+            assert list(col) == sorted(col), (d, V)
+
+
 def test_binding_has_no_cpu_fallback():
     import torch
     desc = L.make_desc(1, 1, 8, 64, 100, "bf16")

@@ -19,3 +19,7 @@ def test_tile_walk_is_balanced_over_the_xcds(tmp_path):
 
 def test_split_of_dh_is_allowed_cheapest_and_within_its_scratch(tmp_path):
     _run_host_check(tmp_path, "dh_split_check")
+
+
+def test_logits_edge_widens_with_the_slots_and_its_scratch_serves_fewer(tmp_path):
+    _run_host_check(tmp_path, "logits_edge_check")
