@@ -123,7 +123,7 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.dZT = take((size_t)L.Vc * L.ldZT * L.esz);
   {
     L.dh.ksteps = (int)(L.Vc * L.esz / 128);
-    L.dh.edge = dh_edge(f32, d->d, L.N, L.dh.ksteps);
+    L.dh.edge = dh_edge(d->d, L.N, L.dh.ksteps);
     L.dh.m_tiles = (d->d + L.dh.edge - 1) / L.dh.edge;
     // slice tiles for any N_v; a bf16 dH is accumulated in these fp32 buffers too and rounded once at the end
     const int64_t tiles = dh_split_tiles(L.dh, (L.N + L.dh.edge - 1) / L.dh.edge, (d->flags & LMHEAD_FLAG_DH_BF16) != 0);

@@ -137,10 +137,12 @@ inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
 }
 // dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
 // slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not
-// exceed the tokens by much.  (n 1024 d 1024 V 20000: 68.9 / 48.8 / 59.9 us on edge 256 / 128 / 64; n 256 V 8000:
-// 40.5 / 25.6 / 23.1; n 256 d 256 V 4096 fp32: 133 / 28 / 17.7; n 4096 d 1024 V 16000 fp32: 736 / 702 / 623.)
-inline int dh_edge(bool f32, int64_t m, int64_t n, int64_t ksteps) {
-  if (f32) return tiles_of(m, n, kTile) <= 4 * kComputeUnits ? 64 : kTile;
+// exceed the tokens by much, for fp32 as for bf16.  Edge 256 / 128 / 64, us (fp32 once took edge 64 up to four rounds of 256
+// wide tiles):
+//   bf16: n 1024 d 1024 V 20000 61.0 / 58.1 / 130    n 512 d 4096 V 32000 136 / 217 / 340    n 256 d 256 V 4096 24.5 / 15.0 / 12.4
+//   fp32: n 4096 d 1024 V 32000 1839 / 1960 / 2150   n 1024 d 1024 V 16000 269 / 258 / 326   n 512 d 256 V 4096 56 / 29 / 20
+//         n 4096 d 512 V 20000 607 / 620 / 671       n 512 d 512 V 20000 143 / 93 / 105      n 256 d 512 V 4096 60 / 31 / 22
+inline int dh_edge(int64_t m, int64_t n, int64_t ksteps) {
   const int64_t slices = ksteps / 32 > 0 ? ksteps / 32 : 1;
   if (n > 128 && tiles_of(m, n, kTile) * slices >= kComputeUnits) return kTile;
   if (n > 64 && tiles_of(m, n, 128) * slices >= kComputeUnits) return 128;

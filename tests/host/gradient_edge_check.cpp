@@ -1,0 +1,30 @@
+// Host check of the rules that pick the tile edges of dH and dW, at sizes where another edge was measured to be 10 % slower or
+// more: contractions that are long enough for wide tiles' rate to count take them, short ones narrow tiles.
+#include <algorithm>
+#include <cstdio>
+using std::min;
+#define LMHEAD_TILE_MAP_HOST 1
+#include "../../paper_2603_04411_amd/csrc/tile_map.h"
+
+int main() {
+  using namespace lmhead;
+  long bad = 0, cases = 0;
+  auto dh = [&](bool f32, int d, int n, int V, int want) {
+    ++cases;
+    const int64_t ksteps = (int64_t)(V + 255) / 256 * 256 * (f32 ? 4 : 2) / 128;
+    if (dh_edge(d, n, ksteps) != want) { ++bad; std::printf("dH f32=%d d=%d n=%d V=%d: %d\n", f32, d, n, V, dh_edge(d, n, ksteps)); }
+  };
+  for (int n : {2048, 4096, 8192}) {
+    dh(true, 1024, n, 32000, 256);
+    dh(true, 1024, n, 16000, 256);
+    dh(true, 512, n, 20000, 256);
+  }
+  dh(true, 1024, 512, 32000, 128);
+  dh(true, 256, 1024, 30000, 128);
+  dh(true, 256, 256, 4096, 64);
+  dh(true, 1024, 64, 32000, 64);
+  dh(false, 4096, 4096, 32000, 256);
+  dh(false, 256, 256, 4096, 64);
+  std::printf("cases=%ld bad=%ld\n", cases, bad);
+  return bad != 0;
+}

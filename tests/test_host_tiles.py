@@ -23,3 +23,7 @@ def test_split_of_dh_is_allowed_cheapest_and_within_its_scratch(tmp_path):
 
 def test_logits_edge_widens_with_the_slots_and_its_scratch_serves_fewer(tmp_path):
     _run_host_check(tmp_path, "logits_edge_check")
+
+
+def test_gradient_edges_follow_the_length_of_the_contraction(tmp_path):
+    _run_host_check(tmp_path, "gradient_edge_check")
