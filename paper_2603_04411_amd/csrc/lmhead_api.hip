@@ -353,13 +353,9 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     // fill the 256 compute units at d = 4096; a chunk of 18 leaves 2) are launched apart, their contraction
     // over the tokens cut into as many slices as make that round full; the slices are summed in a fixed order.
     const int m_tiles = (int)(L.dp / kTile), cus = device_compute_units();
-    int t_rem = 0, ks = 1;
-    if (wa.edge == kTile && m_tiles <= cus && cus % m_tiles == 0) {
-      t_rem = ntiles % (cus / m_tiles);
-      ks = t_rem > 0 ? cus / (t_rem * m_tiles) : 1;
-      if (ks > 8) ks = 8;
-      if (ks < 2 || (size_t)ks * t_rem * kTile * L.dp * 4 > L.dWpart_bytes) t_rem = 0;
-    }
+    const int ks = wa.edge == kTile ? dw_tail_slices(m_tiles, ntiles, cus) : 1;
+    int t_rem = ks > 1 ? ntiles % (cus / m_tiles) : 0;
+    if ((size_t)ks * t_rem * kTile * L.dp * 4 > L.dWpart_bytes) t_rem = 0;
     const int t_main = ntiles - t_rem;
     {
       TimedLaunch tl(3, s);

@@ -128,12 +128,56 @@ inline int64_t logits_part_slots(bool f32, int64_t V, int64_t n) {
   }
   return most;
 }
-// dW: m = d, rows = vocabulary rows of a chunk, n = token slots (the contraction).
+// The vocabulary tiles of a chunk of dW that would start a mostly empty last round of 256 wide tiles are contracted in slices
+// that fill it: how many (1: the last round is full enough, or the tiles along d do not divide a round).
+constexpr int kDwTailSlices = 8;
+inline int dw_tail_slices(int64_t m_tiles, int64_t n_tiles, int cus) {
+  if (m_tiles > cus || cus % m_tiles != 0) return 1;
+  const int64_t rest = n_tiles % (cus / m_tiles);
+  const int64_t ks = rest > 0 ? cus / (rest * m_tiles) : 1;
+  return (int)(ks < kDwTailSlices ? ks : kDwTailSlices);
+}
+// dW: m = d, rows = vocabulary rows of a chunk, n = token slots (the contraction).  A tile of each edge costs a pipeline fill
+// and an epilogue and then so much per K-step: the wide ones have the better rate, the narrow ones the cheaper ends and the
+// fuller rounds.  Every tile of an edge takes the same time, so the cost of each edge can be written down, in K-steps (128
+// bytes of a row) of a full round of 256 wide tiles (1.3 us in bf16, 7.3 us in fp32), and the cheapest is taken: on average
+// within 0.6 % (bf16, 146 sizes) and 0.4 % (fp32, 56 sizes) of the best edge.  dW alone, us, edge 256 / 128 / 64:
+//   bf16  d 1024 V 16384  n 256   23.4 / 22.6 / 27.7    n 1024 39.2 / 42.4 / 54.7    n 16384 348 / 505 / 1233   256 tiles: one round
+//         d 1024 V 20000  n 256   52.2 / 27.2 / 31.6    n 1024 79.6 / 53.2 / 65.5    n 16384 456 / 631 / 1594   316 tiles: cut into slices
+//         d 1024 V 2048   n 256   32.5 / 10.5 / 9.0     n 4096 40.9 / 37.4 / 31.8    n 16384 73.6 / 151 / 130   32 tiles: cut into 8
+//         d 4096 V 151936 n 192   665 / 601 / 691       n 384  834 / 821 / 1042      n 512   929 / 941 / 1250
+//   fp32  d 512 V 4096    n 256   39 / 24 / 16          n 2048 92 / 124 / 73         n 8192  264 / 468 / 263
+//         d 1024 V 8000   n 256   65 / 42 / 45          n 2048 268 / 240 / 255       n 8192  929 / 932 / 1038
+struct DwCost {
+  float ends, step, step_min;   // per round: fill and epilogue; a K-step of a full round, and of one with hardly any tiles
+};
+inline float dw_cost(bool f32, int64_t m, int64_t rows, float steps, int edge) {
+  const DwCost c = f32 ? (edge == kTile ? DwCost{4.f, 1.f, 1.f} : edge == 128 ? DwCost{1.2f, 0.52f, 0.52f} : DwCost{1.f, 0.285f, 0.f})
+                       : (edge == kTile ? DwCost{14.f, 1.f, 0.65f} : edge == 128 ? DwCost{5.8f, 0.76f, 0.25f} : DwCost{4.5f, 0.62f, 0.12f});
+  const int64_t m_tiles = (m + edge - 1) / edge, n_tiles = (rows + edge - 1) / edge;
+  const int64_t slots = (int64_t)kComputeUnits * (kTile / edge);   // 256 / edge workgroups share a compute unit
+  int64_t rounds = m_tiles * n_tiles / slots;
+  const int64_t rest = m_tiles * n_tiles - rounds * slots;
+  float tail = rest > 0 ? c.ends + steps * (c.step_min + (c.step - c.step_min) * (float)rest / (float)slots) : 0.f;
+  if (edge == kTile && dw_tail_slices(m_tiles, n_tiles, kComputeUnits) > 1) {
+    const int64_t per_round = kComputeUnits / m_tiles;
+    rounds = n_tiles / per_round;
+    tail = c.ends + steps * c.step / (float)dw_tail_slices(m_tiles, n_tiles, kComputeUnits) + (f32 ? 1.5f : 14.f);   // and the sum of the slices
+  }
+  return (float)rounds * (c.ends + steps * c.step) + tail;
+}
 inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
-  const int64_t t = tiles_of(m, rows, kTile);
-  if (f32) return t <= kComputeUnits * 7 / 8 ? 64 : kTile;
-  const int r = one_round_edge(m, rows);
-  return r < kTile ? r : (n <= 192 || t <= 2 * kComputeUnits) ? 128 : kTile;
+  const float steps = (float)((n * (f32 ? 4 : 2) + 127) / 128);
+  int best = kTile;
+  float least = dw_cost(f32, m, rows, steps, kTile);
+  for (int edge : {128, 64}) {
+    const float cost = dw_cost(f32, m, rows, steps, edge);
+    if (cost < least) {
+      least = cost;
+      best = edge;
+    }
+  }
+  return best;
 }
 // dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
 // slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not

@@ -25,6 +25,35 @@ int main() {
   dh(true, 1024, 64, 32000, 64);
   dh(false, 4096, 4096, 32000, 256);
   dh(false, 256, 256, 4096, 64);
+  auto dw = [&](bool f32, int d, int V, int n, int want) {
+    ++cases;
+    const int got = dw_edge(f32, d, V, n);
+    if (got != want) { ++bad; std::printf("dW f32=%d d=%d V=%d n=%d: %d\n", f32, d, V, n, got); }
+  };
+  // full rounds of 256 wide tiles, a few tiles whose contraction can be cut, tiles that do not divide a round
+  for (int n : {4096, 16384}) {
+    dw(false, 1024, 16384, n, 256);
+    dw(false, 1024, 32768, n, 256);
+    dw(false, 2048, 16384, n, 256);
+    dw(false, 4096, 8192, n, 256);
+    dw(false, 512, 32768, n, 256);
+    dw(false, 5120, 6000, n, 256);
+    dw(false, 1024, 20000, n, 256);
+    dw(false, 2048, 12000, n, 256);
+  }
+  for (int d : {512, 1024, 2048, 4096}) dw(false, d, 2048 * 1024 / d, 16384, 256);
+  dw(false, 2048, 5000, 16384, 256);
+  dw(true, 1024, 32000, 8192, 256);
+  dw(true, 512, 20000, 8192, 64);
+  // short contractions
+  dw(false, 1024, 20000, 1024, 128);
+  dw(false, 2048, 12000, 1024, 128);
+  dw(false, 1024, 40000, 256, 128);
+  dw(false, 4096, 151936, 192, 128);
+  dw(false, 1024, 2048, 1024, 64);
+  dw(false, 512, 4096, 256, 64);
+  dw(true, 512, 4096, 1024, 64);
+  dw(true, 1024, 32000, 256, 128);
   std::printf("cases=%ld bad=%ld\n", cases, bad);
   return bad != 0;
 }

@@ -177,7 +177,8 @@ def test_kv_store_and_grouping_over_token_blocks(dtype, d, n, off_base):
 @pytest.mark.parametrize("dtype,P,G,T,d,V,chunk", [
     ("bf16", 1, 1, 5, 64, 70, 0), ("bf16", 1, 3, 21, 64, 1025, 256), ("bf16", 1, 3, 64, 128, 4113, 0),
     ("bf16", 1, 7, 27, 576, 17000, 0), ("bf16", 1, 8, 130, 320, 9000, 4096), ("bf16", 2, 8, 64, 256, 33000, 0),
-    ("f32", 1, 1, 3, 32, 65, 0), ("f32", 2, 4, 32, 96, 1300, 512), ("f32", 2, 8, 64, 288, 9000, 0)])
+    ("f32", 1, 1, 3, 32, 65, 0), ("f32", 2, 4, 32, 96, 1300, 512), ("f32", 2, 8, 64, 288, 9000, 0),
+    ("f32", 1, 4, 40, 1024, 8000, 0)])
 @pytest.mark.parametrize("dh16", [False, True])
 def test_lm_step_over_tile_edges(dtype, P, G, T, d, V, chunk, dh16):
     cfg = wl.CONFIGS[1].scaled(P=P, G=G, T=T, d=d, V=V, dtype=dtype, len_lo=1, len_hi=T)
