@@ -85,28 +85,23 @@ constexpr int kComputeUnits = 256;
 // unit).  256 needs the fewest operand bytes per flop, the only edge the vector L1 feeds at full bf16 rate.  The smaller
 // ones give more and shorter tiles when 256 x 256 would leave most of the chip idle, waste less on padding when
 // there are few tokens, and two or four workgroups on a compute unit overlap one's stores with another's loads.
-// Times in us (n = slots, about 60 % of them valid; forward / dW; dH below):
-//                                            edge 256        edge 128        edge 64
-//   n 256   d 1024 V 8000   bf16            32.1 / 37.0     15.7 / 14.4     13.1 / 15.9
-//   n 1024  d 1024 V 20000  bf16            36.9 / 66.6     40.1 / 49.3     62.1 / 49.7
-//   n 192   d 2048 V 151936 bf16             239 / 310       215 / 295       218 / 296
-//   n 64    d 2048 V 151936 bf16             243 / 271       213 / 256       188 / 287
-//   n 384   d 2048 V 151936 bf16, all valid  296 / 432       288 / 497
-//   n 256   d 256  V 4096   fp32            72.9 / 32.0     23.5 / 19.9     11.4 / 10.4
-//   n 1024  d 512  V 20000  fp32             135 / 162       130 / 125       114 / 112
-//   n 4096  d 1024 V 16000  fp32             721 / 558       609 / 567       591 / 595
-// fp32 products are matrix-core bound on any edge, so there the edge only has to keep the chip evenly filled.
 inline int64_t tiles_of(int64_t m, int64_t n, int edge) { return ((m + edge - 1) / edge) * ((n + edge - 1) / edge); }
-// the smallest edge whose tiles run in one round, two to a compute unit
-inline int one_round_edge(int64_t m, int64_t n) {
-  return tiles_of(m, n, 64) <= 2 * kComputeUnits ? 64 : tiles_of(m, n, 128) <= 2 * kComputeUnits ? 128 : kTile;
-}
 // Logits (forward and dZ): V = vocabulary rows, n = token slots.  A pass over several weight matrices takes the edge of a
 // single one: the edge groups the terms of the softmax, and the two calls promise the same bits.
-// The most slots that a call may have for its tiles to be `edge` wide or narrower: one tile of tokens, with little padding, or
-// one round of tiles, two to a compute unit (fp32, edge 64: up to four rounds of 256 wide tiles).
+// The most slots that a call may have for its tiles to be `edge` wide or narrower.  Either one round of tiles, two to a
+// compute unit (fp32, edge 64: up to four rounds of 256 wide tiles, matrix-core bound on any edge, so that narrow tiles only
+// even out the rounds).  Or so few tokens that one tile holds them all and narrower ones are padded less: 64 wide up to
+// 64 slots; 128 wide while 5/8 of the slots fit, the share that is valid where lengths are uniform in [T/4, T].  N_v is not
+// known here: over 128 valid tokens 256 wide tiles win where W is long and wide, below that 128 wide ones, by as much.
+// Forward + dZ, us, edge 256 / 128 / 64 (V 151936 unless said):
+//   slots (valid)   64 (64)          128 (128)        200 (120)        200 (200)        256 (256)        320 (192)
+//   d 2048          480/400/354      479/405/412      473/405/412      472/462/634      474/461/640      470/470/512
+//   d 4096          713/624/574      715/625/747      707/618/746      711/812/1203     716/813/1219     708/808/958
+//   d 4096 V 32000  235/171/176      239/175/218      234/175/218      239/214/312      240/214/313      239/210/250
+//   d 1024 V 32000  66/37/32         66/37/41         66/36/42         67/47/64         70/49/64         68/46/55
+//   fp32, all valid: n 256 d 256 V 4096 155/49/25   n 1024 d 512 V 20000 538/335/339   n 4096 d 1024 V 16000 1982/1949/2076
 inline int64_t logits_slots(bool f32, int64_t V, int edge) {
-  const int64_t few = edge == 64 ? 64 : 192;
+  const int64_t few = edge == 64 ? 64 : 128 * 8 / 5;
   int64_t n = 2 * kComputeUnits / ((V + edge - 1) / edge) * edge;
   if (f32 && edge == 64) {
     const int64_t four = 4 * kComputeUnits / ((V + kTile - 1) / kTile) * kTile;

@@ -24,6 +24,13 @@ int main() {
         scratch = part;
       }
     }
+  // over a large vocabulary the number of slots decides: one tile of 64, one of 128 at a share of 5/8 valid, 256 beyond
+  for (int64_t V : {50257, 151936}) {
+    const int64_t n[] = {1, 64, 65, 128, 200, 204, 205, 256, 4096};
+    const int want[] = {64, 64, 128, 128, 128, 128, 256, 256, 256};
+    for (int i = 0; i < 9; ++i, ++cases)
+      if (logits_edge(false, V, n[i]) != want[i]) ++bad;
+  }
   std::printf("cases=%ld bad=%ld\n", cases, bad);
   return bad != 0;
 }
