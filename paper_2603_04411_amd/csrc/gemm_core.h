@@ -369,11 +369,12 @@ struct GemmTile {
     constexpr int FR = TM + TN;
     constexpr int LD_REGION = A_LD / NPART;     // loads per region (A_LD == B_LD is not required
     constexpr int LD_REGION_B = B_LD / NPART;   // but both are spread the same way)
-    static_assert(MMAS - (FR + 1) / 2 >= LD_REGION && MMAS - (FR + 1) / 2 >= LD_REGION_B, "region too short");
+    constexpr int RD_SLOTS = (FR + 1) / 2;
+    static_assert(MMAS >= RD_SLOTS, "region too short");
     // (program order is reads, loads, MFMAs; the loads must stay behind the reads because both
-    // touch LDS, so the reads go two per MFMA up front and the loads are spread over the rest)
+    // touch LDS, so the reads go two per MFMA up front and the loads are spread over the rest, where there is one: the 64
+    // wide tile of 32x32x16 blocks has a single MFMA per region)
     auto sched_region = [&](int nloads) {
-      constexpr int RD_SLOTS = (FR + 1) / 2;
 #pragma unroll
       for (int i = 0; i < MMAS; ++i) {
         __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
@@ -383,7 +384,7 @@ struct GemmTile {
           else
             __builtin_amdgcn_sched_group_barrier(kDsRead, 2, 0);
         }
-        if (nloads > 0 && i >= RD_SLOTS) {
+        if (nloads > 0 && MMAS - RD_SLOTS >= nloads && i >= RD_SLOTS) {
           const int gap = (MMAS - RD_SLOTS) / nloads;
           const int j = i - RD_SLOTS + 1;
           if (j % gap == 0 && j / gap <= nloads) __builtin_amdgcn_sched_group_barrier(kVmem, 1, 0);

@@ -1,6 +1,8 @@
-"""CPU-only checks of the rules that share work out over the chip."""
+"""CPU-only checks of the rules that share work out over the chip, and of the build variants of the tile kernels."""
 import os
 import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -27,3 +29,11 @@ def test_logits_edge_widens_with_the_slots_and_its_scratch_serves_fewer(tmp_path
 
 def test_gradient_edges_follow_the_length_of_the_contraction(tmp_path):
     _run_host_check(tmp_path, "gradient_edge_check")
+
+
+@pytest.mark.parametrize("source", ["lmhead_gemm.hip", "dynakv_gemm.hip", "dynakv_gate.hip"])
+def test_the_32x32x16_form_of_the_bf16_main_loop_still_compiles(source):
+    from paper_2603_04411_amd import build
+    r = subprocess.run([build._hipcc(), *build.FLAGS, "-DLMHEAD_BF16_BLOCK=32", "-fsyntax-only", "--cuda-device-only",
+                        os.path.join(build.CSRC, source)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
