@@ -26,6 +26,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_F32_MFMA_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
+# (over few tokens the products of kinds 4, 5, 9 and 10 are kv_few_kernel's)
 KINDS = {4: "kv_gemm_kernel<spectral projection>", 5: "kv_gemm_kernel<gate logits>",
          6: "kv_mask_kernel (softmax + cumulative mask + threshold)", 7: "kv_gemm_kernel<reconstruction>"}
 FUSED_GATE = "kv_gate_kernel (x U, gate logits, softmax, cumulative mask, threshold)"   # recorded as kind 4
@@ -33,7 +34,38 @@ FUSED_GATE = "kv_gate_kernel (x U, gate logits, softmax, cumulative mask, thresh
 BWD_KINDS = {4: "kv_gemm_kernel<spectral projection>", 5: "kv_gemm_kernel<gate logits> (forward + recompute)",
              6: "kv_mask_kernel", 8: "kv_mask_bwd_kernel", 9: "kv_gemm_kernel<g_x~ = g_l W^T + g_xhat m>",
              10: "kv_gemm_kernel<dx = g_x~ U^T>", 11: "gemm_t_kernel<dW>", 12: "gemm_t_kernel<dU>",
-             13: "transpose_kernel (two operand copies per parameter gradient)"}
+             13: "kv_prepare_kernel (two operand copies per parameter gradient)"}
+PAIRED_GRADIENTS = "gemm_t_kernel<dW and dU>"   # one launch for both, recorded as kind 11; their four copies as one kind 13
+
+
+def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
+    """One entry per kernel kind of the training pair, with its rate.  kern: kind -> (milliseconds, launches)."""
+    dense = 2.0 * n * d * d
+    # algorithmic bytes per launch: mask backward reads logits (4), x~ and g_xhat (esz each) and writes
+    # g_l and g_xhat*m (esz each); a transpose pair reads and writes two [n x d] operands
+    byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz), 13: 4.0 * n * d * esz}
+    products = dict.fromkeys(BWD_KINDS, 1)
+    names = dict(BWD_KINDS)
+    if kern[6][1] == 0:              # large streams: the forward's gate is one kernel, gate logits only the recompute
+        del names[6]
+        names[4], products[4] = FUSED_GATE, 2
+    if kern[12][1] == 0:             # both parameter gradients in one launch
+        del names[12]
+        names[11], products[11] = PAIRED_GRADIENTS, 2
+        byts[13] *= 2
+    kinds = []
+    for kind, name in names.items():
+        ms, cnt = kern[kind]
+        avg = ms / cnt if cnt else 0.0
+        if kind in byts:
+            rate = byts[kind] / (avg * 1e-3) / 1e9 if avg else 0.0
+            kinds.append({"kernel": name, "kind": kind, "launches": int(cnt), "avg_ms": avg, "bound": "hbm",
+                          "gbs": rate, "frac": rate / PEAK_HBM_GBS})
+        else:
+            rate = products[kind] * dense / (avg * 1e-3) / 1e12 if avg else 0.0
+            kinds.append({"kernel": name, "kind": kind, "launches": int(cnt), "avg_ms": avg, "bound": "mfma",
+                          "tflops": rate, "frac": rate / peak})
+    return kinds
 
 
 TRAFFIC_KEYS = {4: "spectral_projection", 5: "gate_logits", 6: "kv_mask_kernel", 7: "reconstruction"}
@@ -132,27 +164,7 @@ def backward_main(args, cfg, inp, L, desc, params, ws, xt, k) -> int:
     log(f"{ms_per_step:.3f} ms/step (gate forward + backward)")
     esz = 2 if cfg.dtype == "bf16" else 4
     peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_F32_MFMA_TFLOPS
-    dense = 2.0 * n * d * d
-    # algorithmic bytes per launch: mask backward reads logits (4), x~ and g_xhat (esz each) and writes
-    # g_l and g_xhat*m (esz each); a transpose pair reads and writes two [n x d] operands
-    byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz), 13: 4.0 * n * d * esz}
-    fused = kern[6][1] == 0          # large streams: the forward's gate is one kernel, gate logits only the recompute
-    kinds = []
-    for kind, name in BWD_KINDS.items():
-        if fused and kind == 6:
-            continue
-        if fused and kind == 4:
-            name = FUSED_GATE
-        ms, cnt = kern[kind]
-        avg = ms / cnt if cnt else 0.0
-        if kind in byts:
-            rate = byts[kind] / (avg * 1e-3) / 1e9 if avg else 0.0
-            kinds.append({"kernel": name, "kind": kind, "launches": int(cnt), "avg_ms": avg, "bound": "hbm",
-                          "gbs": rate, "frac": rate / PEAK_HBM_GBS})
-        else:
-            rate = dense * (2 if fused and kind == 4 else 1) / (avg * 1e-3) / 1e12 if avg else 0.0
-            kinds.append({"kernel": name, "kind": kind, "launches": int(cnt), "avg_ms": avg, "bound": "mfma",
-                          "tflops": rate, "frac": rate / peak})
+    kinds = backward_kinds(kern, n, d, esz, peak)
     per_step = {e["kernel"]: e["avg_ms"] * e["launches"] / args.steps for e in kinds}
     dom = max(kinds, key=lambda e: e["avg_ms"] * e["launches"])
     if dom["bound"] == "mfma":
@@ -184,7 +196,7 @@ def backward_main(args, cfg, inp, L, desc, params, ws, xt, k) -> int:
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": cfg.dtype, "data": "synthetic",
         "config": {"workload": f"kv_configs[{args.config}] {cfg.name} (gate forward + backward)", "n": n, "d_kv": d},
-        "step_tflops": 7 * dense / (ms_per_step * 1e-3) / 1e12,
+        "step_tflops": 14.0 * n * d * d / (ms_per_step * 1e-3) / 1e12,
         "roofline": roofline, "kernels": kinds, "ms_per_step_by_kernel": per_step, "cpu_baseline": cpu,
     }
     print(json.dumps(out), flush=True)
