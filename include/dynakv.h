@@ -18,7 +18,10 @@
  *    and return without synchronising.
  *  - Return value: LMHEAD_OK or a negative LMHEAD_E_* code (lmhead.h).  Argument errors are
  *    found on the host before anything is launched and leave all outputs untouched.
- *  - Results are bit-reproducible from run to run: no floating-point atomics are used.
+ *  - Results are bit-reproducible from run to run: no floating-point atomics are used.  Sums are grouped by the size of
+ *    the call: x~ and the gradients of a few tokens (their contraction is shared by sixteen wavefronts) and of many
+ *    may round differently, and so may the mask where it decides k.
+ *  - A workspace sized for a long stream serves every shorter one.
  *
  * Readings of the paper taken by this library (also listed in the design notes):
  *  - Eq. 6 is evaluated as the reverse cumulative sum m_i = sum_{j >= i} p_j, which is the mask
@@ -78,7 +81,9 @@ LMHEAD_API int dynakv_validate_desc(const dynakv_desc* desc);
  *     k    = #{ j : m_j > tau }          retained leading components            (Eq. 8)
  *   x     [n x d] row stride ldx  (in)     U, W  [d x d]  (in)     b  float[d]  (in)
  *   xt    [n x d] storage type    (out)    x~
- *   k     int32[n]                (out)    the hard mask of token i is 1 on [0, k[i]) and 0 after
+ *   k     int32[n]                (out)    the hard mask of token i is 1 on [0, k[i]) and 0 after.  From 10240 bf16
+ *                                          tokens on (d = 512 or 1024) a call without m and xhat adds the mask up in
+ *                                          another order than one with them: k may differ where m_j is within rounding of tau
  *   m     float[n x d] or NULL    (out)    soft mask (training)
  *   xhat  [n x d] storage type or NULL (out)  softly gated state (training)
  */

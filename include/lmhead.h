@@ -36,7 +36,11 @@
  *  - Outputs on padded slots are exactly 0 (logp, lse, entropy, g_logp, rows of
  *    dH); token ids on padded slots are ignored.
  *  - Results are bit-reproducible from run to run for a fixed descriptor: no
- *    floating-point atomics are used.
+ *    floating-point atomics are used.  The descriptor's sizes choose how the sums are grouped (tiles of 64,
+ *    128 or 256 vocabulary rows, merged in one of two widths; slices of dH's and dW's contractions), so a token's
+ *    results may differ in their last bits between calls of different sizes.
+ *  - A workspace sized for a descriptor serves every descriptor that differs from it in fewer slots only, while one
+ *    vocabulary chunk covers V (or vocab_chunk is set).
  */
 #ifndef LMHEAD_H_
 #define LMHEAD_H_
