@@ -173,13 +173,12 @@ static_assert(kTile % kIndexRows == 0, "a wavefront's rows stay inside the padde
 
 // out[c][r] = in[r][c] through a 64x64 LDS tile; rows >= `rows` and columns >= `cols` of the
 // source read as zero, so the padded extent of `out` is zero-filled.
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, int64_t ld_in,
+__global__ __launch_bounds__(256) void transpose_kernel(const uint32_t* __restrict__ in, int64_t ld_in,
                                                         int64_t rows_fixed, int cols, int rows_from_nv,
                                                         const WsHeader* __restrict__ hdr,
-                                                        T* __restrict__ out, int64_t ld_out,
+                                                        uint32_t* __restrict__ out, int64_t ld_out,
                                                         int64_t rows_p, int64_t cols_p) {
-  __shared__ T tile[64][65];
+  __shared__ uint32_t tile[64][65];
   const int64_t rows = rows_from_nv ? (int64_t)hdr->nv : rows_fixed;
   const int64_t r0 = (int64_t)blockIdx.x * 64;
   const int64_t c0 = (int64_t)blockIdx.y * 64;
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   for (int rr = ty; rr < 64; rr += 4) {
     const int64_t r = r0 + rr, c = c0 + tx;
-    tile[rr][tx] = (r < rows && c < cols) ? in[r * ld_in + c] : T(0);
+    tile[rr][tx] = (r < rows && c < cols) ? in[r * ld_in + c] : 0u;
   }
   __syncthreads();
   for (int cc = ty; cc < 64; cc += 4) {
@@ -217,7 +216,7 @@ __device__ inline void to_e4m3(const float (&x)[N], float scale, uint32_t (&out)
 }
 
 // The backward's operands in one launch, 64 x 64 tiles with 16-byte global accesses on both sides (the element-wise kernel
-// above moves 2 or 4 bytes per lane and runs at about half the rate): HcT, WT and, with 8-bit logits, the
+// above moves 4 bytes per lane and runs at about half the rate): HcT, WT and, with 8-bit logits, the
 // e4m3 copy of W, which the same read of W serves (151936 x 4096: 765 us for everything, 846 us in launches of their own); the rows of dH that
 // belong to padding are zeroed and the token ids of valid slots checked.  Rows of the source go to LDS as they
 // are (padded pitch); each thread then gathers the 16 bytes of one output chunk (consecutive r of one column).
@@ -529,17 +528,11 @@ hipError_t launch_index(const IndexArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// rows that are no multiple of 64 elements (fp32 only), or not 16-byte aligned
-static hipError_t launch_transpose(int dtype, const Transpose& t, const WsHeader* hdr, hipStream_t s) {
+// rows that are no multiple of 64 elements: fp32 only, d is a multiple of 64 in bf16
+static hipError_t launch_transpose(const Transpose& t, const WsHeader* hdr, hipStream_t s) {
   const dim3 grid((unsigned)((t.rows_p + 63) / 64), (unsigned)((t.cols_p + 63) / 64));
-  if (dtype == LMHEAD_BF16)
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, s, static_cast<const uint16_t*>(t.in), t.ld_in,
-                       t.rows, t.cols, t.rows_from_nv ? 1 : 0, hdr, static_cast<uint16_t*>(t.out), t.ld_out, t.rows_p,
-                       t.cols_p);
-  else
-    hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, dim3(256), 0, s, static_cast<const uint32_t*>(t.in), t.ld_in,
-                       t.rows, t.cols, t.rows_from_nv ? 1 : 0, hdr, static_cast<uint32_t*>(t.out), t.ld_out, t.rows_p,
-                       t.cols_p);
+  hipLaunchKernelGGL(transpose_kernel, grid, dim3(256), 0, s, static_cast<const uint32_t*>(t.in), t.ld_in, t.rows, t.cols,
+                     t.rows_from_nv ? 1 : 0, hdr, static_cast<uint32_t*>(t.out), t.ld_out, t.rows_p, t.cols_p);
   return hipGetLastError();
 }
 
@@ -552,10 +545,11 @@ hipError_t launch_operands(int dtype, const OperandArgs& a, hipStream_t s) {
     const bool wide = t.cols % 64 == 0 && t.cols_p % 64 == 0 && t.rows_p % 64 == 0 && (t.ld_in * esz) % 16 == 0 &&
                       (t.ld_out * esz) % 16 == 0 && (reinterpret_cast<uintptr_t>(t.in) & 15u) == 0 &&
                       (reinterpret_cast<uintptr_t>(t.out) & 15u) == 0;
+    if (!wide && dtype != LMHEAD_F32) return hipErrorInvalidValue;
     t.tiles = wide ? (int)(t.rows_p / 64 * (t.cols_p / 64)) : 0;
     if (!wide) {
       // (d is a multiple of 128 wherever an e4m3 copy is wanted: the wide kernel makes it)
-      const hipError_t e = launch_transpose(dtype, t, b.hdr, s);
+      const hipError_t e = launch_transpose(t, b.hdr, s);
       if (e != hipSuccess) return e;
     }
     blocks += t.tiles;
