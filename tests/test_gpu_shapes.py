@@ -276,6 +276,46 @@ def test_kv_gate_in_one_kernel(d, n, ldx, literal):
         assert torch.equal(kt, torch.full_like(kt, want))
 
 
+# the one-kernel gate against 64 bits, up to the benchmark's stream
+@pytest.mark.parametrize("n,d", [(10241, 1024), (10367, 512), (262144, 1024), (262143, 512)])
+@pytest.mark.parametrize("literal", [False, True])
+def test_kv_gate_in_one_kernel_against_64_bits(n, d, literal):
+    import torch
+    import paper_2603_04411_amd as L
+    tau = 0.1
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    sigma = torch.arange(1, d + 1, device="cuda").float().pow(-0.5)
+    Q = torch.linalg.qr(torch.randn(d, d, generator=torch.Generator().manual_seed(d)))[0].contiguous().cuda()
+    x = torch.empty(n, d, dtype=torch.bfloat16, device="cuda")
+    for r in range(0, n, 65536):
+        x[r:r + 65536] = (randn(min(65536, n - r), d) * sigma) @ Q.t()
+    U, W = (Q + 0.02 / d ** 0.5 * randn(d, d)).bfloat16(), (1.5 * randn(d, d)).bfloat16()
+    j = torch.arange(d, device="cuda").float()
+    b = 6.0 * torch.exp(-((j - 0.35 * d) ** 2) / (2 * (0.12 * d) ** 2))
+    desc = L.make_kv_desc(n, d, "bf16", flags=L.FLAG_LITERAL_FLIP if literal else 0)
+    xt, k = torch.full_like(x, 3.0), torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    ws = torch.full((L.dynakv_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    L.dynakv_gate(desc, x, U, W, b, tau, xt, k, None, None, ws)
+    assert L.dynakv_check(ws) == 0
+    for r in range(0, n, 16384):
+        e = min(n, r + 16384)
+        want = x[r:e].double() @ U.double()
+        # one rounding to bf16, which fp32 sums of d products (d * 2^-24 of the terms' magnitude) may tip the other way
+        scale = x[r:e].double().abs() @ U.double().abs()
+        assert bool(((xt[r:e].double() - want).abs() <= 2.0 ** -8 * want.abs() + d * 2.0 ** -24 * scale).all())
+        z = xt[r:e].double() @ W.double()
+        p = torch.softmax(z + b.double(), 1)
+        if literal:
+            p = p.flip(1)
+        m = p.flip(1).cumsum(1).flip(1)
+        # fp32 logits: d roundings at the partial sums' magnitude, below 2^6 here, less with their random signs: sqrt(d) 2^-18;
+        # the mask moves by at most that, its own sums by d 2^-24
+        eps = d ** 0.5 * 2.0 ** -18 + d * 2.0 ** -24
+        kk = k[r:e].long()
+        assert bool((kk >= (m > tau + eps).sum(1)).all()) and bool((kk <= (m > tau - eps).sum(1)).all())
+
+
 # the few-token products: one token to a group of 16 and its neighbours, the contraction shared by two to sixteen wavefronts and
 # taken in several turns, strided rows
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
