@@ -43,7 +43,6 @@ struct WsLayout {
   int64_t Vc;       // vocabulary chunk of the backward (multiple of the tile)
   int64_t nchunks;  // number of vocabulary chunks
   int edge;         // tile edge of the logits kernels
-  int edge_w;       // tile edge of dW
   int64_t ntiles;   // vocabulary tiles of `edge` = planes of per-tile softmax statistics per row
   // Row pitches (elements) of the workspace matrices.  Each is its logical width plus one
   // 128-byte line: a power-of-two pitch would put every row of a tile on the same L2
@@ -93,7 +92,6 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   const bool f32 = d->dtype == LMHEAD_F32;
   const bool fp8 = (d->flags & LMHEAD_FLAG_FP8_LOGITS) != 0;
   L.edge = fp8 ? kTile : logits_edge(f32, d->V, L.N);
-  L.edge_w = dw_edge(f32, d->d, vc, L.N);
   L.ntiles = (d->V + L.edge - 1) / L.edge;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -123,7 +121,7 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.dZT = take((size_t)L.Vc * L.ldZT * L.esz);
   {
     L.dh.ksteps = (int)(L.Vc * L.esz / 128);
-    L.dh.edge = dh_edge(d->d, L.N, L.dh.ksteps);
+    L.dh.edge = dh_edge(f32, d->d, L.N, L.dh.ksteps);
     L.dh.m_tiles = (d->d + L.dh.edge - 1) / L.dh.edge;
     // slice tiles for any N_v; a bf16 dH is accumulated in these fp32 buffers too and rounded once at the end
     const int64_t tiles = dh_split_tiles(L.dh, (L.N + L.dh.edge - 1) / L.dh.edge, (d->flags & LMHEAD_FLAG_DH_BF16) != 0);

@@ -270,6 +270,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     LM_TRY(launch_quantize_e4m3(dt, w.at<void>(L.Hc), L.ldHc, 0, true, hdr, desc->d, desc->fp8_exp_h,
                                 w.at<void>(L.Hc8), L.ld8, L.Ncap, s));
 
+  const int edge_w = dw_edge(dt == LMHEAD_F32, desc->d, L.Vc < desc->V ? L.Vc : desc->V, L.N);
   const int total_tiles = (int)(L.Vp / kTile);
   const int tiles_per_chunk = (int)(L.Vc / kTile);
   for (int c = 0; c < (int)L.nchunks; ++c) {
@@ -347,7 +348,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     wa.ldo = desc->d;
     wa.accumulate = (desc->flags & LMHEAD_FLAG_ACCUM_DW) != 0;
     wa.hdr = hdr;
-    wa.edge = L.edge_w;
+    wa.edge = edge_w;
     // Every output tile is one workgroup and the compute units take them a round at a time.  The vocabulary
     // tiles of this chunk that would start a mostly empty last round (with d / 256 tiles along d, 16 of them
     // fill the 256 compute units at d = 4096; a chunk of 18 leaves 2) are launched apart, their contraction

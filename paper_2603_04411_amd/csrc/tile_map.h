@@ -136,37 +136,54 @@ inline int dw_tail_slices(int64_t m_tiles, int64_t n_tiles, int cus) {
 // and an epilogue and then so much per K-step: the wide ones have the better rate, the narrow ones the cheaper ends and the
 // fuller rounds.  Every tile of an edge takes the same time, so the cost of each edge can be written down, in K-steps (128
 // bytes of a row) of a full round of 256 wide tiles (1.3 us in bf16, 7.3 us in fp32), and the cheapest is taken: on average
-// within 0.6 % (bf16, 146 sizes) and 0.4 % (fp32, 56 sizes) of the best edge.  dW alone, us, edge 256 / 128 / 64:
+// within 0.5 % (bf16, 217 sizes) and 0.3 % (fp32, 68 sizes) of the best edge.  dW alone, us, edge 256 / 128 / 64:
 //   bf16  d 1024 V 16384  n 256   23.4 / 22.6 / 27.7    n 1024 39.2 / 42.4 / 54.7    n 16384 348 / 505 / 1233   256 tiles: one round
 //         d 1024 V 20000  n 256   52.2 / 27.2 / 31.6    n 1024 79.6 / 53.2 / 65.5    n 16384 456 / 631 / 1594   316 tiles: cut into slices
 //         d 1024 V 2048   n 256   32.5 / 10.5 / 9.0     n 4096 40.9 / 37.4 / 31.8    n 16384 73.6 / 151 / 130   32 tiles: cut into 8
+//         d 512 V 300     n 500   20.9 / 11.5 / 9.0    n 6000 31 / 48 / 40    n 16000 49 / 116 / 93    4 tiles: cut into 8
+//         d 1024 V 151936 n 128   174 / 156 / 191    n 300 209 / 242 / 250      n 512   248 / 289 / 356
 //         d 4096 V 151936 n 192   665 / 601 / 691       n 384  834 / 821 / 1042      n 512   929 / 941 / 1250
 //   fp32  d 512 V 4096    n 256   39 / 24 / 16          n 2048 92 / 124 / 73         n 8192  264 / 468 / 263
 //         d 1024 V 8000   n 256   65 / 42 / 45          n 2048 268 / 240 / 255       n 8192  929 / 932 / 1038
-struct DwCost {
-  float ends, step, step_min;   // per round: fill and epilogue; a K-step of a full round, and of one with hardly any tiles
+struct TileCost {
+  // K-steps of a full round of 256 wide tiles: fill and epilogue per round; a K-step of a full round; a K-step of a tile that
+  // has its compute unit for itself, its operands in L2 or beyond
+  float ends, step, near, far;
 };
-inline float dw_cost(bool f32, int64_t m, int64_t rows, float steps, int edge) {
-  const DwCost c = f32 ? (edge == kTile ? DwCost{4.f, 1.f, 1.f} : edge == 128 ? DwCost{1.2f, 0.52f, 0.52f} : DwCost{1.f, 0.285f, 0.f})
-                       : (edge == kTile ? DwCost{14.f, 1.f, 0.65f} : edge == 128 ? DwCost{5.8f, 0.76f, 0.25f} : DwCost{4.5f, 0.62f, 0.12f});
+inline float tiles_cost(bool f32, int64_t m, int64_t rows, float steps, int edge) {
+  TileCost c = f32 ? (edge == kTile ? TileCost{4.f, 1.f, 1.f, 1.f}
+                                    : edge == 128 ? TileCost{1.2f, 0.52f, 0.52f, 0.52f} : TileCost{1.f, 0.285f, 0.f, 0.f})
+                   : (edge == kTile ? TileCost{11.6f, 1.f, 0.4f, 0.4f}
+                                    : edge == 128 ? TileCost{3.9f, 0.81f, 0.31f, 0.57f} : TileCost{2.2f, 0.6f, 0.27f, 0.43f});
+  // More output than the last-level cache holds: with rows of 4 KB or less the narrow tiles' ends cost more (d = 512 and
+  // 1024, V = 80000 and 151936; most from four K-steps on), with longer ones the wide tiles' less (d = 2048 to 4096).
+  if (!f32 && m * rows * 4 > ((int64_t)256 << 20)) {
+    if (m <= 1024) c.ends += edge == kTile ? 0.4f : edge == 128 ? (steps >= 4.f ? 2.2f : 1.f) : 0.7f;
+    else if (edge == kTile) c.ends -= 0.8f;
+  }
   const int64_t m_tiles = (m + edge - 1) / edge, n_tiles = (rows + edge - 1) / edge;
   const int64_t slots = (int64_t)kComputeUnits * (kTile / edge);   // 256 / edge workgroups share a compute unit
-  int64_t rounds = m_tiles * n_tiles / slots;
-  const int64_t rest = m_tiles * n_tiles - rounds * slots;
-  float tail = rest > 0 ? c.ends + steps * (c.step_min + (c.step - c.step_min) * (float)rest / (float)slots) : 0.f;
-  if (edge == kTile && dw_tail_slices(m_tiles, n_tiles, kComputeUnits) > 1) {
+  const int64_t rounds = m_tiles * n_tiles / slots;
+  const float fill = (float)(m_tiles * n_tiles - rounds * slots) / (float)slots;   // of the last round
+  const float round = c.ends + steps * c.step;
+  if (rounds >= 4) return ((float)rounds + fill) * round;   // a partial round behind many overlaps them
+  // the eight L2s hold 32 MB of operands; with 100 MB more next to nothing of a tile's is there
+  const float beyond = ((float)(m + rows) * steps * 128.f / 1048576.f - 32.f) / 100.f;
+  const float alone = c.near + (c.far - c.near) * (beyond < 0.f ? 0.f : beyond < 1.f ? beyond : 1.f);
+  auto partial = [&](float n, float f) { return c.ends + n * (c.step * f > alone ? c.step * f : alone); };
+  if (const int ks = edge == kTile ? dw_tail_slices(m_tiles, n_tiles, kComputeUnits) : 1; ks > 1) {
     const int64_t per_round = kComputeUnits / m_tiles;
-    rounds = n_tiles / per_round;
-    tail = c.ends + steps * c.step / (float)dw_tail_slices(m_tiles, n_tiles, kComputeUnits) + (f32 ? 1.5f : 14.f);   // and the sum of the slices
+    const float f = (float)(m_tiles * (n_tiles % per_round) * ks) / (float)kComputeUnits;
+    // and the sum of the slices, with what their 64 MB push out of the caches for the kernels around it
+    return (float)(n_tiles / per_round) * round + partial(steps / (float)ks, f) + (f32 ? 1.5f : 32.f) * f;
   }
-  return (float)rounds * (c.ends + steps * c.step) + tail;
+  return (float)rounds * round + (fill > 0.f ? partial(steps, fill) : 0.f);
 }
-inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
-  const float steps = (float)((n * (f32 ? 4 : 2) + 127) / 128);
+inline int cheapest_edge(bool f32, int64_t m, int64_t rows, float steps) {
   int best = kTile;
-  float least = dw_cost(f32, m, rows, steps, kTile);
+  float least = tiles_cost(f32, m, rows, steps, kTile);
   for (int edge : {128, 64}) {
-    const float cost = dw_cost(f32, m, rows, steps, edge);
+    const float cost = tiles_cost(f32, m, rows, steps, edge);
     if (cost < least) {
       least = cost;
       best = edge;
@@ -174,15 +191,20 @@ inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
   }
   return best;
 }
+inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
+  return cheapest_edge(f32, m, rows, (float)((n * (f32 ? 4 : 2) + 127) / 128));
+}
 // dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
 // slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not
-// exceed the tokens by much, for fp32 as for bf16.  Edge 256 / 128 / 64, us (fp32 once took edge 64 up to four rounds of 256
+// exceed the tokens by much, for fp32 as for bf16.  (An fp32 contraction that is too short to cut fills the rounds best
+// with 64 wide tiles: n 6000 d 1024 V 500 58 us against 72 on edge 128.)  Edge 256 / 128 / 64, us (fp32 once took edge 64 up to four rounds of 256
 // wide tiles):
 //   bf16: n 1024 d 1024 V 20000 61.0 / 58.1 / 130    n 512 d 4096 V 32000 136 / 217 / 340    n 256 d 256 V 4096 24.5 / 15.0 / 12.4
 //   fp32: n 4096 d 1024 V 32000 1839 / 1960 / 2150   n 1024 d 1024 V 16000 269 / 258 / 326   n 512 d 256 V 4096 56 / 29 / 20
 //         n 4096 d 512 V 20000 607 / 620 / 671       n 512 d 512 V 20000 143 / 93 / 105      n 256 d 512 V 4096 60 / 31 / 22
-inline int dh_edge(int64_t m, int64_t n, int64_t ksteps) {
+inline int dh_edge(bool f32, int64_t m, int64_t n, int64_t ksteps) {
   const int64_t slices = ksteps / 32 > 0 ? ksteps / 32 : 1;
+  if (f32 && slices == 1) return tiles_of(m, n, kTile) <= 4 * kComputeUnits ? 64 : kTile;
   if (n > 128 && tiles_of(m, n, kTile) * slices >= kComputeUnits) return kTile;
   if (n > 64 && tiles_of(m, n, 128) * slices >= kComputeUnits) return 128;
   return 64;

@@ -12,7 +12,7 @@ int main() {
   auto dh = [&](bool f32, int d, int n, int V, int want) {
     ++cases;
     const int64_t ksteps = (int64_t)(V + 255) / 256 * 256 * (f32 ? 4 : 2) / 128;
-    if (dh_edge(d, n, ksteps) != want) { ++bad; std::printf("dH f32=%d d=%d n=%d V=%d: %d\n", f32, d, n, V, dh_edge(d, n, ksteps)); }
+    if (dh_edge(f32, d, n, ksteps) != want) { ++bad; std::printf("dH f32=%d d=%d n=%d V=%d: %d\n", f32, d, n, V, dh_edge(f32, d, n, ksteps)); }
   };
   for (int n : {2048, 4096, 8192}) {
     dh(true, 1024, n, 32000, 256);
@@ -23,6 +23,7 @@ int main() {
   dh(true, 256, 1024, 30000, 128);
   dh(true, 256, 256, 4096, 64);
   dh(true, 1024, 64, 32000, 64);
+  dh(true, 1024, 6000, 500, 64);
   dh(false, 4096, 4096, 32000, 256);
   dh(false, 256, 256, 4096, 64);
   auto dw = [&](bool f32, int d, int V, int n, int want) {
@@ -45,10 +46,19 @@ int main() {
   dw(false, 2048, 5000, 16384, 256);
   dw(true, 1024, 32000, 8192, 256);
   dw(true, 512, 20000, 8192, 64);
+  // a handful of tiles: their contraction cut into slices beats a few narrow tiles on a few compute units
+  for (int d : {64, 256, 512, 1024}) dw(false, d, 300, 16000, 256);
+  dw(false, 512, 300, 6000, 256);
+  dw(false, 4096, 300, 6000, 64);
+  dw(false, 1024, 2048, 8000, 64);
   // short contractions
+  dw(false, 512, 300, 500, 64);
+  dw(false, 1024, 151936, 300, 256);
+  dw(false, 2048, 151936, 384, 256);
   dw(false, 1024, 20000, 1024, 128);
   dw(false, 2048, 12000, 1024, 128);
   dw(false, 1024, 40000, 256, 128);
+  dw(false, 1024, 151936, 150, 128);
   dw(false, 4096, 151936, 192, 128);
   dw(false, 1024, 2048, 1024, 64);
   dw(false, 512, 4096, 256, 64);
