@@ -207,7 +207,7 @@ struct KvGateArgs {
 };
 // From this many tokens on.  Its workgroups take 64 tokens (128 at d = 512) through everything, 60 us a round, so below
 // a round the separate kernels with their smaller tiles win.  Whole call, us, separate kernels / this one:
-//   d 1024: n 8192 60.9 / 65.5   12000 90.6 / 70.0   16384 99.9 / 83.6   65536 392 / 287   262144 1334 / 1049
+//   d 1024: n 8192 60.9 / 65.5   12000 90.6 / 70.0   16384 99.9 / 83.6   65536 392 / 287   262144 1334 / 1027
 //   d 512:  n 8192 34.5 / 38.3   16384 50.0 / 42.1   32768 77.7 / 49.0   65536 154 / 90    262144 560 / 342
 // bf16 at 512 and 1024 only: the tile is laid out for a whole token row in LDS next to 256 accumulators a lane, 64 tokens of
 // 1024 or 128 of 512 components.  A row of 2048 leaves room for 32 tokens, i.e. twice the parameter stream per token, which

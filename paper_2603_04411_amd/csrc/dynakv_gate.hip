@@ -13,9 +13,9 @@
 // What bounds it: the parameter stream.  Every 64 tokens read 2 d^2 x 2 bytes (4 MB at d = 1024) through a compute unit's
 // 64 bytes per clock, which just matches the matrix cores' pace; 256 x 256 tiles need half of that but pay a pipeline
 // fill and an epilogue per 16 K-steps, one write and one read of the fp32 logits and one read of x~ (3.2 GB at
-// 262144 x 1024).  Measured there: 1334 us with the separate kernels, 1049 with this one.  Of a round's 66 us about 10 are
-// the stream's (with every fragment load an L1 hit it takes 56) and 10 the softmax, which a wavefront alone on its SIMD
-// cannot overlap with anything.
+// 262144 x 1024).  Measured there: 1334 us with the separate kernels, 1027 with this one.  Of a round's 64 us (sixteen
+// rounds) the matrix pipe is busy for 34; about 13 are the stream's (with every fragment load an L1 hit a round takes 52) and
+// 8 the softmax (56 without it), which a wavefront alone on its SIMD cannot overlap with anything.
 //
 // Column order: accumulator element v of block i in lane group q of wavefront w is POSITION (d/4) w + (d/16) q + 4 i + v of
 // the mask, i.e. a lane holds d / 16 consecutive positions of one token per token block, and the cumulative sum is a

@@ -1,4 +1,4 @@
-// MFMA macro-tile main loop shared by every contraction of the library (gfx950).
+// MFMA macro-tile main loop shared by the macro-tile contractions of the library (gfx950).
 //
 // All contractions (logits, logits recompute for dZ, dH, dW; the KV path's spectral projection,
 // gate logits and ragged reconstruction) are brought to the same form
