@@ -49,6 +49,7 @@ def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
     if kern[6][1] == 0:              # large streams: the forward's gate is one kernel, gate logits only the recompute
         del names[6]
         names[4], products[4] = FUSED_GATE, 2
+        names[5] = "kv_gemm_kernel<gate logits> (recompute)"
     if kern[12][1] == 0:             # both parameter gradients in one launch
         del names[12]
         names[11], products[11] = PAIRED_GRADIENTS, 2
@@ -68,7 +69,7 @@ def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
     return kinds
 
 
-TRAFFIC_KEYS = {4: "spectral_projection", 5: "gate_logits", 6: "kv_mask_kernel", 7: "reconstruction"}
+TRAFFIC_KEYS = {4: "kv_gate_kernel", 5: "gate_logits", 6: "kv_mask_kernel", 7: "reconstruction"}
 
 
 def recorded_traffic(kind: int, config: int):
