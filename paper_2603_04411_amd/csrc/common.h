@@ -56,14 +56,14 @@ struct WsLayout {
   size_t hdr, cu_len, row_slot, tok_c, gid, g_c, lse_c, zy, part, Hc, HcT, WT, dZ, dZT, Hc8, W8, total;
 };
 
-// Default backward chunk: as wide as keeps the two dZ copies (worst case: every slot valid)
+// Default backward chunk: as wide as keeps dZ (fp32: and its transposed copy; worst case: every slot valid)
 // within about 48 GB, at most 262144 columns (small problems take the whole vocabulary in one
 // chunk).  Wider chunks mean fewer read-modify-write passes over dH and longer contractions per
 // launch.
 static inline int64_t default_vocab_chunk(const lmhead_desc* d) {
   const int64_t esz = d->dtype == LMHEAD_BF16 ? 2 : 4;
   const int64_t N = (int64_t)d->P * d->G * d->T;
-  int64_t vc = (48ll << 30) / (2 * esz * (N > 0 ? N : 1));
+  int64_t vc = (48ll << 30) / ((k_major(d->dtype == LMHEAD_F32) ? 1 : 2) * esz * (N > 0 ? N : 1));
   vc = vc / kTile * kTile;
   if (vc > 262144) vc = 262144;
   if (vc < 4 * kTile) vc = 4 * kTile;
@@ -115,10 +115,12 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.ldZ = L.Vc + pad;
   L.ldZT = L.Ncap + pad;
   L.Hc = take((size_t)L.Ncap * L.ldHc * L.esz);
-  L.HcT = take((size_t)L.dp * L.ldHcT * L.esz);
-  L.WT = take((size_t)L.dp * L.ldWT * L.esz);
+  // K-contiguous copies: fp32 only, bf16 contracts the operands as they lie
+  const bool copies = !k_major(f32);
+  L.HcT = take(copies ? (size_t)L.dp * L.ldHcT * L.esz : 0);
+  L.WT = take(copies ? (size_t)L.dp * L.ldWT * L.esz : 0);
   L.dZ = take((size_t)L.Ncap * L.ldZ * L.esz);
-  L.dZT = take((size_t)L.Vc * L.ldZT * L.esz);
+  L.dZT = take(copies ? (size_t)L.Vc * L.ldZT * L.esz : 0);
   {
     L.dh.ksteps = (int)(L.Vc * L.esz / 128);
     L.dh.edge = dh_edge(f32, d->d, L.N, L.dh.ksteps);
@@ -249,7 +251,7 @@ struct DzArgs {
   const float* lse_c;
   const WsHeader* hdr;
   void* dZ;       // [Ncap x chunk], pitch ldZ
-  void* dZT;      // [chunk x Ncap], pitch ldZT
+  void* dZT;      // [chunk x Ncap], pitch ldZT; fp32 output only
   float zscale;   // as in FwdArgs
 };
 // op_dtype: type of Hc / W as given in the arguments (LMHEAD_F32, LMHEAD_BF16 or kDtypeFp8);
@@ -288,8 +290,13 @@ struct GemmTArgs {
   bool part_accumulate;   // unless part_single.  part_slice = floats per slice (header.ksplit: n tiles x edge x part_ld).
   bool part_single;
   int edge;            // workgroup tile edge: 64, 128 or 256 (n_tiles_cap stays in units of kTile)
-  const void* A2;      // non-null: a second product of the same shape in the same launch, with its own operands and
-  const void* B2;      // out, its slices behind the first one's
+  // bf16 K-major operands (A always, B except for dH): A is [K x M], B is [K x N].  Nothing past these bytes from A / B is
+  // read (rows of the contraction beyond them count as zeros); dW's operands are readable to the end of the last K-step
+  // instead, with a row of 256 values from every column tile on.
+  int64_t a_bytes, b_bytes, a2_bytes, b2_bytes;
+  const void* A2;      // non-null: a second product of the same shape in the same launch, with its own operands (A2's pitch
+  const void* B2;      // is ldA) and out, its slices behind the first one's
+  int64_t ldB2;
   float* out2;
 };
 

@@ -309,9 +309,9 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
 
-  // Parameter gradients: contractions over the tokens, out[row][col] = sum_t B[row][t] A[col][t] with
-  // token-contiguous copies of both operands, cut into ksplit slices of the token range (one: stored directly).
+  // Parameter gradients: contractions over the tokens, cut into ksplit slices of the token range (one: stored directly).
   //   dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
+  // bf16: the operands as they lie, both gradients in one launch.  fp32: token-contiguous copies of them.
   auto token_copy = [&](const void* src, int64_t ld, size_t to) {
     return KvCopy{src, ld, L.n, L.ncap, d, (int)L.dp, at(to), L.ldK, KvCopy::kTransposed, 0};
   };
@@ -332,6 +332,27 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ta.part_slice = (int64_t)d * d;
   ta.ldo = d;
   ta.accumulate = accum;
+  if (k_major(dt == LMHEAD_F32)) {
+    ta.A = at(L.gl);
+    ta.A2 = at(L.gxt);
+    ta.B = xt;
+    ta.B2 = x;
+    ta.ldA = d;
+    ta.ldB = d;
+    ta.ldB2 = desc->ldx;
+    ta.K = L.n;
+    ta.a_bytes = ta.a2_bytes = ta.b_bytes = L.n * d * 2;
+    ta.b2_bytes = ((L.n - 1) * desc->ldx + d) * 2;
+    ta.out = dW;
+    ta.out2 = dU;
+    {
+      TimedLaunch tl(11, s);
+      LM_TRY(launch_gemm_t(dt, ta, s, 2));
+    }
+    if (L.ksplit > 1) LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, dW, accum, s, dU));
+    return LMHEAD_OK;
+  }
+  ta.ldB2 = L.ldK;
   // one gradient, or both: the second one's operands are in T3, T4
   auto param_grad = [&](const KvPrepareArgs& copies, int kind, float* out, float* out2) -> int {
     {

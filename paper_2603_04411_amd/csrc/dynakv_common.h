@@ -122,13 +122,15 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.logits = take((size_t)L.ncap * L.d * 4);
   L.gl = take((size_t)L.ncap * L.d * L.esz);
   L.gxt = take((size_t)L.ncap * L.d * L.esz);
-  L.T1 = take((size_t)L.dp * L.ldK * L.esz);
-  L.T2 = take((size_t)L.dp * L.ldK * L.esz);
+  const bool copies = !k_major(L.esz == 4);
+  L.T1 = take(copies ? (size_t)L.dp * L.ldK * L.esz : 0);
+  L.T2 = take(copies ? (size_t)L.dp * L.ldK * L.esz : 0);
   // Up to kKvPairBytes a copy the launches weigh more than the memory: one preparation, one product and one sum serve both
   // parameter gradients (4096 x 1024: 57 us of kernels before, 42 now; 300 x 128 fp32: 24 and 16).
-  L.pair = L.dp * L.ldK * L.esz <= kKvPairBytes;
-  L.T3 = take(L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
-  L.T4 = take(L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
+  // bf16 has no copies, and always pairs.
+  L.pair = !copies || L.dp * L.ldK * L.esz <= kKvPairBytes;
+  L.T3 = take(copies && L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
+  L.T4 = take(copies && L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
   L.part = take((size_t)(L.pair ? 2 : 1) * L.ksplit * L.d * L.d * 4);
   L.dbpart = take((size_t)L.nblk * L.d * 4);
   L.total = off;

@@ -2,7 +2,7 @@
 //
 // All contractions (logits, logits recompute for dZ, dH, dW; the KV path's spectral projection,
 // gate logits and ragged reconstruction) are brought to the same form
-// C[m][n] = sum_k A[m][k] * B[n][k]  with both operands K-contiguous.
+// C[m][n] = sum_k A[m][k] * B[n][k]  with both operands K-contiguous, or in bf16 K-major (below).
 // A workgroup owns a BM x BN tile of C; each wavefront owns a (BM/WGM) x (BN/WGN)
 // sub-tile built from 16x16 (bf16, e4m3) or 32x32 (fp32) MFMA blocks.
 //
@@ -42,6 +42,16 @@
 // Fragments are double-buffered in registers (e4m3: one set, refilled behind its last reader) and the hand-over
 // barrier is skewed so that the MFMAs after it overlap the first fragment reads of the next K-step and the
 // issue of the next loads.
+//
+// K-major operands (kTransA / kTransB, bf16 only): the operand's rows in memory run along M (or N) and K counts rows, as W
+// does for dH and the hidden states for dW.  A K-step is then 64 rows of BM values, and the fragments are read out of LDS
+// with ds_read_b64_tr_b16, which hands a 4 x 16 block (K x M) to sixteen lanes transposed: a lane supplies the address of 4
+// consecutive values of one row and receives 4 values of K of one column; two of them make a fragment.  No transposed copy of the
+// operand is needed, and the reads run at the rate of the plain ones (156 B/clk and compute unit against 123 for
+// 128-bit reads; without the swizzle 32).
+//   LDS slot: the 64 rows as they lie, cut into 32-byte units; unit u of row k sits at unit u ^ swzT(k) of its row.  The
+//   rows are put into the slot's 1 KB groups in an order (krow_of) that keeps whatever depends on the sub-step and on the
+//   half of a fragment in the last bits of the group index, so that it fits the DS instructions' immediate offset.
 //
 // Accumulator layout of a block (NB * NB / 64 floats per lane); a lane owns one column n = l % NB:
 //   NB = 32: element v of lane l  <->  m = 8*(v/4) + 4*(l/32) + v%4   (16 values)
@@ -88,6 +98,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 typedef __attribute__((ext_vector_type(8))) int i32x8_t;
+typedef __attribute__((ext_vector_type(4))) short i16x4_t;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
 struct bf16_tag {};
 struct f32_tag {};
@@ -95,9 +107,6 @@ struct fp8_tag {};   // OCP e4m3 operands (logits only), fp32 accumulation
 
 template <typename E>
 struct Elem;
-#ifndef LMHEAD_BF16_BLOCK
-#define LMHEAD_BF16_BLOCK 16
-#endif
 template <>
 struct Elem<bf16_tag> {
   static constexpr int size = 2;
@@ -180,7 +189,10 @@ __device__ inline void lds_barrier() {
 
 // kLeadB selects which operand goes first round the LDS ring (see run()).
 // kMaskB: every B row has its own K extent (ragged rows); loads past it fetch zeros (see run()).
-template <typename E, int BM_, int BN_, int WGM_, int WGN_, bool kLeadB = false, bool kMaskB = false>
+// kTransA / kTransB: the operand is K-major (see above).  kWalk: K-major operands are not limited to a window but followed by
+// a pointer that advances with the K-steps, for operands that are readable to the end of the last K-step.
+template <typename E, int BM_, int BN_, int WGM_, int WGN_, bool kLeadB = false, bool kMaskB = false, bool kTransA = false,
+          bool kTransB = false, bool kWalk = false>
 struct GemmTile {
   static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
   static constexpr int NWAVES = WGM * WGN;
@@ -208,6 +220,8 @@ struct GemmTile {
   static_assert(BM % (WGM * NB) == 0 && BN % (WGN * NB) == 0, "wave tiles are made of MFMA blocks");
   static_assert(NB == 32 || NB == 16, "block edge");
   static_assert(BM % (8 * NWAVES) == 0 && BN % (8 * NWAVES) == 0, "tile loads divide evenly");
+  static_assert(!(kTransA || kTransB) || (NB == 16 && Elem<E>::size == 2 && BM == BN && WGM == 2 && WGN == 2 && !kMaskB),
+                "K-major operands: bf16 on 16x16 blocks, four wavefronts");
   static_assert(NSUB == 1 || NSUB % 2 == 0, "fragment double-buffering assumes an even number of sub-steps");
 
   using Block = typename Elem<E>::acc_t;
@@ -234,6 +248,27 @@ struct GemmTile {
   __device__ static inline int ldA_row(int q) { return (wave() * A_LD + q) * 8 + (lane() >> 3); }
   __device__ static inline int ldB_row(int q) { return (wave() * B_LD + q) * 8 + (lane() >> 3); }
   __device__ static inline int ld_byte(int row) { return ((lane() & 7) ^ swz(row)) << 4; }
+
+  // K-major operand: values of K per K-step, bytes of a K row of the tile, K rows per 1 KB group.
+  static constexpr int KROWS = 64;
+  static constexpr int TROW = BM * 2;
+  static constexpr int TRPG = 1024 / TROW;
+  __device__ static inline int swzT(int k) {
+    return BM == 64 ? ((k >> 1) & 1) | ((k >> 2) & 2) : (k & 3) | ((k >> 1) & 4);
+  }
+  // K row (of the K-step) that this lane fetches in the wave's q-th load, and the byte inside the tile's part of that row.
+  // With k = 32 sub + 8 g + 4 h + r, group index = (lane-dependent: g, and r / 2 at edge 256) then (sub, h); edge 64 has
+  // h in the row of the group.
+  __device__ static inline int ldT_row(int q) {
+    const int gi = wave() * A_LD + q, in = lane() / (TROW / 16);
+    if constexpr (BM == 256) return 32 * ((gi >> 1) & 1) + 8 * (gi >> 3) + 4 * (gi & 1) + 2 * ((gi >> 2) & 1) + in;
+    if constexpr (BM == 128) return 32 * ((gi >> 1) & 1) + 8 * (gi >> 2) + 4 * (gi & 1) + in;
+    return 32 * (gi & 1) + 8 * (gi >> 1) + in;
+  }
+  __device__ static inline int ldT_byte(int krow) {
+    const int p = lane() % (TROW / 16);
+    return (((p >> 1) ^ swzT(krow)) << 5) | ((p & 1) << 4);
+  }
 
   __device__ static inline void zero(Acc& acc) {
 #pragma unroll
@@ -271,9 +306,18 @@ struct GemmTile {
   __device__ static inline void run(Acc& acc, const char* __restrict__ A, const uint32_t (&offA)[A_LD],
                                     const char* __restrict__ B, const uint32_t (&offB)[B_LD],
                                     int ksteps, char* lds, int trace_kind = 0) {
-    static_assert(!kMaskB, "ragged rows need their limits");
+    static_assert(!kMaskB && !kTransA && !kTransB, "these need limits or pitches");
     const int none[B_LD] = {};
     run_rows(acc, A, offA, B, offB, none, 0x7fffffffu, ksteps, lds, trace_kind);
+  }
+  // Same with K-major operands.  A K-major operand's offsets are ldT_row(q) * pitch + ldT_byte(that row), its step is
+  // KROWS * pitch (K-contiguous: KB), and loads beyond its `bytes` (at most 2^31 - 1, counted from the uniform pointer)
+  // fetch zeros; nothing may be requested beyond 2^32.  With kWalk there is no limit, and `bytes` is ignored.
+  __device__ static inline void run_steps(Acc& acc, const char* __restrict__ A, const uint32_t (&offA)[A_LD], uint32_t bytesA,
+                                          uint32_t stepA, const char* __restrict__ B, const uint32_t (&offB)[B_LD],
+                                          uint32_t bytesB, uint32_t stepB, int ksteps, char* lds, int trace_kind = 0) {
+    const int none[B_LD] = {};
+    run_rows(acc, A, offA, B, offB, none, bytesB, ksteps, lds, trace_kind, bytesA, stepA, stepB);
   }
 
   // Same, with B given as one buffer of `bytesB` bytes (at most 2^31) that holds rows of differing
@@ -285,7 +329,8 @@ struct GemmTile {
   __device__ static inline void run_rows(Acc& acc, const char* __restrict__ A, const uint32_t (&offA)[A_LD],
                                          const char* __restrict__ B, const uint32_t (&offB)[B_LD],
                                          const int (&limB)[B_LD], uint32_t bytesB, int ksteps, char* lds,
-                                         int trace_kind = 0) {
+                                         int trace_kind = 0, uint32_t bytesA = 0x7fffffffu, uint32_t stepA = KB,
+                                         uint32_t stepB = KB) {
     typedef __attribute__((address_space(3))) void* lptr_t;
     const int w = wave();
     const int l = lane();
@@ -307,14 +352,39 @@ struct GemmTile {
       const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
       return reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
     };
-    const __amdgpu_buffer_rsrc_t rsrcA = __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(A), 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcA = __builtin_amdgcn_make_buffer_rsrc(
+        uniform_ptr(A), 0, kTransA ? (int)__builtin_amdgcn_readfirstlane(bytesA) : 0x7fffffff, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcB = __builtin_amdgcn_make_buffer_rsrc(
         uniform_ptr(B), 0, (int)__builtin_amdgcn_readfirstlane(bytesB), 0x00020000);
+    // byte offset of K-step ks from the tile's first one
+    const uint32_t sA_ = kTransA ? __builtin_amdgcn_readfirstlane(stepA) : (uint32_t)KB;
+    const uint32_t sB_ = kTransB ? __builtin_amdgcn_readfirstlane(stepB) : (uint32_t)KB;
+    constexpr bool kWalkA = kTransA && kWalk, kWalkB = kTransB && kWalk;
+    auto kofs_a = [&](int ks) { return kWalkA ? 0 : (int)(ks * sA_); };
+    auto kofs_b = [&](int ks) { return kWalkB ? 0 : (int)(ks * sB_); };
+    // kWalk: the K-step that is requested next (each operand's K-steps are requested in order)
+    [[maybe_unused]] const char* nextA = static_cast<const char*>(uniform_ptr(A));
+    [[maybe_unused]] const char* nextB = static_cast<const char*>(uniform_ptr(B));
+    auto desc_a = [&]() -> __amdgpu_buffer_rsrc_t {
+      if constexpr (kWalkA)
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(nextA), 0, 0x7fffffff, 0x00020000);
+      else
+        return rsrcA;
+    };
+    auto desc_b = [&]() -> __amdgpu_buffer_rsrc_t {
+      if constexpr (kWalkB)
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(nextB), 0, 0x7fffffff, 0x00020000);
+      else
+        return rsrcB;
+    };
+    auto done_a = [&](int q) { if (kWalkA && q == A_LD - 1) nextA += sA_; };
+    auto done_b = [&](int q) { if (kWalkB && q == B_LD - 1) nextB += sB_; };
     auto issue_a = [&](int ks, int slot, int part) {
       char* st = lds + slot * SSTR;
 #pragma unroll
       for (int q = part * (A_LD / NPART); q < (part + 1) * (A_LD / NPART); ++q)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lptr_t)(st + (w * A_LD + q) * GSTR), 16, offA[q], ks * KB, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_a(), (lptr_t)(st + (w * A_LD + q) * GSTR), 16, offA[q], kofs_a(ks), 0, 0);
+      done_a((part + 1) * (A_LD / NPART) - 1);
     };
     auto issue_b = [&](int ks, int slot, int part) {
       char* st = lds + slot * SSTR;
@@ -322,12 +392,33 @@ struct GemmTile {
       for (int q = part * (B_LD / NPART); q < (part + 1) * (B_LD / NPART); ++q) {
         uint32_t vo = offB[q];
         if constexpr (kMaskB) vo = (ks * KB < limB[q]) ? vo : 0x80000000u;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB, (lptr_t)(st + (w * B_LD + q) * GSTR), 16, vo, ks * KB, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_b(), (lptr_t)(st + (w * B_LD + q) * GSTR), 16, vo, kofs_b(ks), 0, 0);
       }
+      done_b((part + 1) * (B_LD / NPART) - 1);
     };
 
     u32x4_t fa[2][TM][FC], fb[2][TN][FC];
+    // half h of a fragment of a K-major operand: sub-step s, unit (block column of 16 values) u of the tile
+    [[maybe_unused]] const int tr = (l & 15) >> 2;
+    [[maybe_unused]] const int tbase = BM == 256   ? (grp * 2 + (tr >> 1)) * 4 * GSTR + (tr & 1) * TROW
+                                       : BM == 128 ? grp * 4 * GSTR + tr * TROW
+                                                   : grp * 2 * GSTR + tr * TROW;
+    [[maybe_unused]] const int tf = swzT(8 * grp + tr);
+    auto read_t = [&](const char* st, int s, int u, int h) {
+      typedef __attribute__((address_space(3))) i16x4_t* tptr_t;
+      const int at = tbase + ((u ^ tf) << 5) + (l & 3) * 8 + (BM == 64 ? s * GSTR + h * 4 * TROW : (2 * s + h) * GSTR);
+      return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr_t)(st + at)));
+    };
+    auto half = [](u32x4_t& f, int h, u32x2_t v) {
+      if (h == 0) { f.x = v.x; f.y = v.y; } else { f.z = v.x; f.w = v.y; }
+    };
+    const int uA0 = wave_m() * TM, uB0 = wave_n() * TN;
     auto read_a = [&](const char* sa, int s, int buf) {
+      if constexpr (kTransA) {
+#pragma unroll
+        for (int i = 0; i < 2 * TM; ++i) half(fa[buf][i / 2][0], i % 2, read_t(sa, s, uA0 + i / 2, i % 2));
+        return;
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int r = rA0 + i * NB;
@@ -339,6 +430,11 @@ struct GemmTile {
       }
     };
     auto read_b = [&](const char* sb, int s, int buf) {
+      if constexpr (kTransB) {
+#pragma unroll
+        for (int j = 0; j < 2 * TN; ++j) half(fb[buf][j / 2][0], j % 2, read_t(sb, s, uB0 + j / 2, j % 2));
+        return;
+      }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int r = rB0 + j * NB;
@@ -498,43 +594,63 @@ struct GemmTile {
       // of this form issues every 16 cycles, which leaves room for about three other instructions).
       static_assert(NSUB == 2 && FC == 1 && TM == TN && TM % 2 == 0, "two regions per sub-step");
       constexpr int RMMAS = TM * TN / 2;     // MFMAs per region
-      constexpr int RREADS = TM;             // fragment reads per region
-      // loads start behind the reads where a region is long enough, else they share its last MFMAs
-      constexpr int LOAD0 = RREADS + LD_REGION <= RMMAS ? RREADS : RMMAS - LD_REGION;
-      static_assert(LOAD0 >= 0 && RREADS <= RMMAS, "region pattern");
+      // Fragment reads per region, one behind each of the first MFMAs: TM, or twice that of a K-major operand (two each where
+      // there are not that many MFMAs, edge 64).  Loads start behind the reads where a region is long enough, else they
+      // share its last MFMAs.
+      auto region_reads = [](bool trans) { return trans ? 2 * TM : TM; };
       auto read_a1 = [&](const char* sa, int sub, int buf, int i) {
+        if constexpr (kTransA) {
+          half(fa[buf][i / 2][0], i % 2, read_t(sa, sub, uA0 + i / 2, i % 2));
+          return;
+        }
         const int r = rA0 + i * NB;
         fa[buf][i][0] = *reinterpret_cast<const u32x4_t*>(sa + row_off(r) + (((LG * sub + grp) ^ swz(r)) << 4));
       };
       auto read_b1 = [&](const char* sb, int sub, int buf, int j) {
+        if constexpr (kTransB) {
+          half(fb[buf][j / 2][0], j % 2, read_t(sb, sub, uB0 + j / 2, j % 2));
+          return;
+        }
         const int r = rB0 + j * NB;
         fb[buf][j][0] = *reinterpret_cast<const u32x4_t*>(sb + row_off(r) + (((LG * sub + grp) ^ swz(r)) << 4));
       };
       auto issue_a1 = [&](int ks, int slot, int q) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lptr_t)(lds + slot * SSTR + (w * A_LD + q) * GSTR), 16, offA[q],
-                                                 ks * KB, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_a(), (lptr_t)(lds + slot * SSTR + (w * A_LD + q) * GSTR), 16, offA[q],
+                                                 kofs_a(ks), 0, 0);
+        done_a(q);
       };
       auto issue_b1 = [&](int ks, int slot, int q) {
         uint32_t vo = offB[q];
         if constexpr (kMaskB) vo = (ks * KB < limB[q]) ? vo : 0x80000000u;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB, (lptr_t)(lds + slot * SSTR + (w * B_LD + q) * GSTR), 16, vo,
-                                                 ks * KB, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(desc_b(), (lptr_t)(lds + slot * SSTR + (w * B_LD + q) * GSTR), 16, vo,
+                                                 kofs_b(ks), 0, 0);
+        done_b(q);
       };
       // One region: the MFMAs of row blocks [i0, i0 + TM/2) on fragment set `buf`, with the reads of
       // operand `rx` (true: X) for (slot base `src`, sub-step `sub`) into set `rbuf`, and, when `ld`,
       // the loads [q0, q0 + LD_REGION) of operand `lx` for K-step `lks` into ring slot `lslot`.
       auto region = [&](int buf, int i0, bool rd, bool rx, const char* src, int sub, int rbuf, bool ld, bool lx, int lks,
                         int lslot, int q0) {
-        constexpr int kGap = (RMMAS - LOAD0) / LD_REGION;
+        const bool ra = rx == !kLeadB;         // A is read
+        const int reads = region_reads(ra ? kTransA : kTransB);
+        const int per = (reads + RMMAS - 1) / RMMAS;
+        const int load0 = reads + LD_REGION <= RMMAS ? reads : RMMAS - LD_REGION;
+        const int gap = (RMMAS - load0) / LD_REGION;
 #pragma unroll
         for (int idx = 0; idx < RMMAS; ++idx) {
           const int i = i0 + idx / TN, j = idx % TN;
           Elem<E>::mma(acc[i][j], fa[buf][i], fb[buf][j]);
-          if (rd && idx < RREADS) {
-            if (rx == !kLeadB) read_a1(src, sub, rbuf, idx); else read_b1(src, sub, rbuf, idx);
+          if (rd) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int rr = idx * per + e;
+              if (e < per && rr < reads) {
+                if (ra) read_a1(src, sub, rbuf, rr); else read_b1(src, sub, rbuf, rr);
+              }
+            }
           }
-          if (ld && idx >= LOAD0 && (idx - LOAD0) % kGap == 0 && (idx - LOAD0) / kGap < LD_REGION) {
-            const int q = q0 + (idx - LOAD0) / kGap;
+          if (ld && idx >= load0 && (idx - load0) % gap == 0 && (idx - load0) / gap < LD_REGION) {
+            const int q = q0 + (idx - load0) / gap;
             if (lx == !kLeadB) issue_a1(lks, lslot, q); else issue_b1(lks, lslot, q);
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -648,13 +764,13 @@ struct GemmTile {
       auto b_of = [&](int sx, int sy) { return lds + (kLeadB ? sx : sy) * SSTR; };
       auto issue_a1 = [&](int ks, int slot, int q) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lptr_t)(lds + slot * SSTR + (w * A_LD + q) * GSTR), 16, offA[q],
-                                                 ks * KB, 0, 0);
+                                                 kofs_a(ks), 0, 0);
       };
       auto issue_b1 = [&](int ks, int slot, int q) {
         uint32_t vo = offB[q];
         if constexpr (kMaskB) vo = (ks * KB < limB[q]) ? vo : 0x80000000u;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB, (lptr_t)(lds + slot * SSTR + (w * B_LD + q) * GSTR), 16, vo,
-                                                 ks * KB, 0, 0);
+                                                 kofs_b(ks), 0, 0);
       };
       auto issue_x1 = [&](int ks, int slot, int q) {
         if constexpr (kLeadB) issue_b1(ks, slot, q); else issue_a1(ks, slot, q);

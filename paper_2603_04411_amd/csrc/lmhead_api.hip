@@ -258,14 +258,20 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
   oa.V = desc->V;
   oa.dH = static_cast<char*>(dH);
   oa.dh_bytes = (int64_t)desc->d * (dh16 ? 2 : 4);
-  oa.job[0] = {w.at<void>(L.Hc), L.ldHc, L.Ncap, L.Ncap, desc->d, (int)L.dp, true, w.at<void>(L.HcT), L.ldHcT};
-  oa.job[1] = {W, desc->ldW, desc->V, L.Vp, desc->d, (int)L.dp, false, w.at<void>(L.WT), L.ldWT};
-  if (fp8) {
-    oa.job[1].e4m3 = w.at<uint8_t>(L.W8);
-    oa.job[1].ld_e4m3 = L.ld8;
-    oa.job[1].scale = ldexpf(1.0f, desc->fp8_exp_w);
+  const bool kmajor = k_major(dt == LMHEAD_F32);   // operands as they lie
+  if (!kmajor) {
+    oa.job[0] = {w.at<void>(L.Hc), L.ldHc, L.Ncap, L.Ncap, desc->d, (int)L.dp, true, w.at<void>(L.HcT), L.ldHcT};
+    oa.job[1] = {W, desc->ldW, desc->V, L.Vp, desc->d, (int)L.dp, false, w.at<void>(L.WT), L.ldWT};
+    if (fp8) {
+      oa.job[1].e4m3 = w.at<uint8_t>(L.W8);
+      oa.job[1].ld_e4m3 = L.ld8;
+      oa.job[1].scale = ldexpf(1.0f, desc->fp8_exp_w);
+    }
   }
   LM_TRY(launch_operands(dt, oa, s));
+  if (fp8 && kmajor)
+    LM_TRY(launch_quantize_e4m3(dt, W, desc->ldW, desc->V, false, hdr, desc->d, desc->fp8_exp_w, w.at<void>(L.W8), L.ld8,
+                                L.Vp, s));
   if (fp8)
     LM_TRY(launch_quantize_e4m3(dt, w.at<void>(L.Hc), L.ldHc, 0, true, hdr, desc->d, desc->fp8_exp_h,
                                 w.at<void>(L.Hc8), L.ld8, L.Ncap, s));
@@ -304,8 +310,14 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
 
     // dH[slot(n)][m] (+)= sum_v W^T[m][c0 + v] dZ[n][v]
     GemmTArgs ha{};
-    ha.A = w.at<char>(L.WT) + (size_t)c0 * L.esz;
-    ha.ldA = L.ldWT;
+    if (kmajor) {
+      ha.A = static_cast<const char*>(W) + (int64_t)c0 * desc->ldW * 2;
+      ha.ldA = desc->ldW;
+      ha.a_bytes = ((int64_t)(desc->V - c0 - 1) * desc->ldW + desc->d) * 2;
+    } else {
+      ha.A = w.at<char>(L.WT) + (size_t)c0 * L.esz;
+      ha.ldA = L.ldWT;
+    }
     ha.B = w.at<void>(L.dZ);
     ha.ldB = L.ldZ;
     ha.M = desc->d;
@@ -334,10 +346,17 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
 
     // dW[c0 + n][m] = sum_i Hc^T[m][i] dZ^T[n][i]
     GemmTArgs wa{};
-    wa.A = w.at<void>(L.HcT);
-    wa.ldA = L.ldHcT;
-    wa.B = w.at<void>(L.dZT);
-    wa.ldB = L.ldZT;
+    if (kmajor) {
+      wa.A = w.at<void>(L.Hc);
+      wa.ldA = L.ldHc;
+      wa.B = w.at<void>(L.dZ);
+      wa.ldB = L.ldZ;
+    } else {
+      wa.A = w.at<void>(L.HcT);
+      wa.ldA = L.ldHcT;
+      wa.B = w.at<void>(L.dZT);
+      wa.ldB = L.ldZT;
+    }
     wa.M = desc->d;
     wa.n_limit = (desc->V - c0 < ntiles * kTile) ? desc->V - c0 : ntiles * kTile;
     wa.n_from_nv = false;
@@ -370,7 +389,8 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
       }
       if (t_rem > 0) {
         GemmTArgs r = wa;
-        r.B = w.at<char>(L.dZT) + (size_t)t_main * kTile * L.ldZT * L.esz;
+        const int64_t skip = (int64_t)t_main * kTile * (kmajor ? 1 : L.ldZT) * L.esz;
+        r.B = static_cast<const char*>(wa.B) + skip;
         r.n_limit = wa.n_limit - (int64_t)t_main * kTile;
         r.n_tiles_cap = t_rem;
         r.ksplit = ks;

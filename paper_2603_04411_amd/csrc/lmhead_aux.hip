@@ -542,6 +542,7 @@ hipError_t launch_operands(int dtype, const OperandArgs& a, hipStream_t s) {
   b.zero_blocks = (int)((b.N + kZeroSlots - 1) / kZeroSlots);
   int64_t blocks = b.zero_blocks;
   for (Transpose& t : b.job) {
+    if (!t.in) continue;   // bf16: no copies
     const bool wide = t.cols % 64 == 0 && t.cols_p % 64 == 0 && t.rows_p % 64 == 0 && (t.ld_in * esz) % 16 == 0 &&
                       (t.ld_out * esz) % 16 == 0 && (reinterpret_cast<uintptr_t>(t.in) & 15u) == 0 &&
                       (reinterpret_cast<uintptr_t>(t.out) & 15u) == 0;

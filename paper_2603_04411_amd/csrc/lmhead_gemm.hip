@@ -1,7 +1,7 @@
 // The three MFMA kernels of the LM-head path, all built on GemmTile (gemm_core.h):
 //   fwd_kernel    logits tile (vocabulary x tokens) -> max / sum-exp / sum-exp*z per token and tile,
 //                 target-logit capture; nothing of the tile is stored           (log-softmax of L_CE, Eq. 9)
-//   dz_kernel     logits tile recomputed -> dZ = g (onehot - softmax), stored in both orientations
+//   dz_kernel     logits tile recomputed -> dZ = g (onehot - softmax) (fp32: stored in both orientations)
 //   gemm_t_kernel plain contraction with a transposed, row-mapped fp32 store    (dH and dW)
 // fwd_kernel and dz_kernel also exist for 8-bit (e4m3) copies of their operands.
 //
@@ -33,8 +33,8 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 constexpr bool kLeadFwd = true, kLeadDz = true, kLeadDh = true, kLeadDw = true;
 
 // Workgroup tile, four wavefronts (2 x 2).
-template <typename E, bool kLeadB = false, int Edge = 256>
-using Tile = GemmTile<E, Edge, Edge, 2, 2, kLeadB>;
+template <typename E, bool kLeadB = false, int Edge = 256, bool kTransA = false, bool kTransB = false, bool kWalk = false>
+using Tile = GemmTile<E, Edge, Edge, 2, 2, kLeadB, false, kTransA, kTransB, kWalk>;
 
 // Block shape of the XCD-local tile walk (see xcd_tile_coords): 4 x 4 work items.
 constexpr int kMapBx = 4, kMapBy = 4;
@@ -281,24 +281,14 @@ struct DzRows {
 };
 
 // Epilogue of the dZ kernel on 16x16 blocks with bf16 output (bf16 or e4m3 operands; permuted W rows):
-// dZ = g (onehot - p) in bf16;
-//  - dZ [token][vocabulary] leaves straight from registers, 16 bytes per lane and block pair (a token's
-//    64 contiguous bytes come from the four lane groups of one store);
-//  - dZT [vocabulary][token] needs consecutive tokens, which sit in different lanes: the whole tile is
-//    staged once in LDS as [vocabulary row][token] and streamed out with 16 bytes per lane on
-//    line-contiguous rows.  One barrier per tile.
-// (Also tried: returning the packed block pairs transposed from the matrix cores, by multiplying them with a
-// 0/1 selection matrix, so that dZT leaves from registers too and LDS is not used at all.  It is exact, but
-// its stores, like those of dZ here, put consecutive lanes on different rows, and with both orientations
-// stored that way the kernel was 5 % slower than with this staging.)
+// dZ = g (onehot - p) in bf16, token-major, straight from registers: 16 bytes per lane and block pair (a token's
+// 64 contiguous bytes come from the four lane groups of one store).  dH and dW both read this one copy.
 template <typename G>
-__device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc, int m0, int mrel0, int64_t n0,
-                                          char* smem) {
+__device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc, int m0, int mrel0, int64_t n0) {
   typedef __attribute__((ext_vector_type(2))) float f32x2_t;
   typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-  constexpr int P2 = G::BN * 2 + 16;             // pitch of a staged [vocabulary row] of BN tokens
-  static_assert(G::BM * P2 <= G::LDS_BYTES && G::NB == 16 && G::VB == 4 && G::TM % 2 == 0, "staging fits in LDS");
-  const int q = G::lane() / 16, nl = G::lane() % 16;
+  static_assert(G::NB == 16 && G::VB == 4 && G::TM % 2 == 0, "pairs of blocks");
+  const int q = G::lane() / 16;
   const int mb = G::wave_m() * G::WM + 8 * q;    // lane part of the tile-relative vocabulary row
   const int vlim = a.V - m0 - mb;                // vocabulary rows with offset >= vlim are padding
   const float kz = kLog2e * a.zscale;            // logit = accumulator * zscale
@@ -328,7 +318,6 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
   //         such a wave at V = 152 k).   mode 2: the vocabulary's last tile (padding rows give 0).
   const int mode = (m0 + G::BM <= a.V) ? (__any(hit) ? 1 : 0) : 2;
   char* const dZ = static_cast<char*>(a.dZ);
-  char* const dZT = static_cast<char*>(a.dZT);
 
 #pragma unroll
   for (int j = 0; j < G::TN; ++j) {
@@ -336,9 +325,6 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
     const float bias = -lsej[j] * kLog2e;
     const int rel = relj[j];
     const int tl = G::n_of(j);                   // token within the tile
-    // rows 8 apart (the four lane groups) would share LDS banks: the 32-byte token groups of a staged
-    // row are permuted by (row / 8) % 4, which for this lane's rows is its lane group
-    char* const srow = smem + mb * P2 + (((tl >> 4) ^ q) << 5) + nl * 2;
     char* const grow = dZ + ((size_t)(n0 + tl) * a.ldZ + mrel0 + mb) * 2;
     auto emit = [&](auto mode_tag) {
       constexpr int kMode = decltype(mode_tag)::value;
@@ -370,9 +356,6 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
           uint32_t word = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
           if constexpr (kMode == 0) word ^= smask;
           pk[w] = word;
-          const int mo = DzRows::offset(2 * ap + (w >> 1), 2 * (w & 1));
-          *reinterpret_cast<uint16_t*>(srow + mo * P2) = (uint16_t)word;
-          *reinterpret_cast<uint16_t*>(srow + (mo + 1) * P2) = (uint16_t)(word >> 16);
         }
         *reinterpret_cast<u32x4_t*>(grow + 64 * ap) = pk;
         __builtin_amdgcn_sched_barrier(0);        // one block pair's values live at a time
@@ -386,20 +369,6 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
       emit(std::integral_constant<int, 2>{});
   }
   trace_stamp(12, 2);
-  lds_barrier();
-  trace_stamp(13, 2);
-  // [vocabulary row][token] rows -> dZT
-  constexpr int CPR = G::BN * 2 / 16;            // 16-byte chunks per staged row
-  constexpr int RPP = G::NT / CPR;               // rows per pass
-  const int c = threadIdx.x % CPR;
-  const int rin = threadIdx.x / CPR;
-#pragma unroll 8
-  for (int r0 = 0; r0 < G::BM; r0 += RPP) {
-    const int m = r0 + rin;
-    const int f = (m >> 3) & 3;
-    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(smem + m * P2 + ((((c >> 1) ^ f) << 5) | ((c & 1) << 4)));
-    *reinterpret_cast<u32x4_t*>(dZT + ((size_t)(mrel0 + m) * a.ldZT + n0 + c * 8) * 2) = v;
-  }
 }
 
 // E: type of the operands Hc and W (possibly e4m3 copies); EO: type of dZ / dZT.
@@ -423,7 +392,7 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
   // With 16x16 blocks and bf16 output the rows of the W tile enter LDS in a permuted order (DzRows), chosen so that a
   // lane's accumulators of two neighbouring blocks are EIGHT consecutive vocabulary entries of its token:
   // 16 bytes of a dZ row, stored straight from registers.
-  constexpr bool kDirect = G::NB == 16 && std::is_same<EO, bf16_tag>::value;
+  constexpr bool kDirect = G::NB == 16 && std::is_same<EO, bf16_tag>::value && k_major(false);
   uint32_t offA[G::A_LD], offB[G::B_LD];
 #pragma unroll
   for (int q = 0; q < G::A_LD; ++q) {
@@ -444,7 +413,7 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
          static_cast<const char*>(a.Hc) + n0 * pitchH, offB, ksteps, smem, 2);
   trace_stamp(2, 2); trace_cycles(2, 2);
   if constexpr (kDirect) {
-    dz_epilogue_direct<G>(a, acc, m0, mrel0, n0, smem);
+    dz_epilogue_direct<G>(a, acc, m0, mrel0, n0);
     trace_stamp(3, 2); trace_cycles(3, 2);
     return;
   }
@@ -572,12 +541,24 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
   }
 }
 
+// In bf16 the operands that have the contraction along their rows are taken as they lie (GemmTile's K-major operands): W for
+// dH, the hidden states and dZ for dW, both operands of a parameter gradient.  fp32, whose values are too wide for the transposing
+// LDS reads, goes by K-contiguous copies.  Against copies of all of them in bf16 too (8x8x256 step, d 2048): copies 294 -> 17 us
+// (what is left zeroes padding), dZ kernel, which had to write dZ in both orientations, 5.57 -> 5.01 ms, dH 4.46 -> 4.50, dW 4.48 ->
+// 4.46, the step 19.7 -> 18.8 ms; 4x8x2048, d 4096: dZ 39.7 -> 38.0 ms, the step 149.7 -> 147.0.  Which operand leads the ring
+// makes no difference here; two transposing reads behind an MFMA instead of one cost dW 2 %.
+template <typename E>
+constexpr bool k_major_a() { return k_major(Elem<E>::size == 4); }
+template <typename E>
+constexpr bool k_major_b(int role) { return k_major(Elem<E>::size == 4) && role != 0; }
+
 // Role: 0 = dH (contracts over a vocabulary chunk), 1 = dW (contracts over the valid tokens), 2 = a
 // parameter gradient of the KV gate (contracts over the tokens of a stream).  The code is the same; the
 // parameter only gives the uses distinct kernel names in profiles (and picks the lead operand).
 template <typename E, int Role, int Edge>
 __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTArgs a) {
-  using G = Tile<E, (Role == 0 ? kLeadDh : kLeadDw), Edge>;
+  constexpr bool kTA = k_major_a<E>(), kTB = k_major_b<E>(Role);
+  using G = Tile<E, (Role == 0 ? kLeadDh : kLeadDw), Edge, kTA, kTB, kTA && Role == 1>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nv = a.hdr->nv;
   const int64_t n_lim = a.n_from_nv ? (int64_t)nv : a.n_limit;
@@ -597,19 +578,20 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   const int per_slice = (ksteps_all + ksplit - 1) / ksplit;
   const int k_first = slice * per_slice;
   const int ksteps = max(0, min(per_slice, ksteps_all - k_first));
+  const bool second = blockIdx.y != 0;
   const int64_t pitchA = a.ldA * Elem<E>::size;
-  const int64_t pitchB = a.ldB * Elem<E>::size;
+  const int64_t pitchB = (second ? a.ldB2 : a.ldB) * Elem<E>::size;
 
   uint32_t offA[G::A_LD], offB[G::B_LD];
 #pragma unroll
   for (int q = 0; q < G::A_LD; ++q) {
-    const int row = G::ldA_row(q);
-    offA[q] = (uint32_t)(row * pitchA) + G::ld_byte(row);
+    const int row = kTA ? G::ldT_row(q) : G::ldA_row(q);
+    offA[q] = (uint32_t)(row * pitchA) + (kTA ? G::ldT_byte(row) : G::ld_byte(row));
   }
 #pragma unroll
   for (int q = 0; q < G::B_LD; ++q) {
-    const int row = G::ldB_row(q);
-    offB[q] = (uint32_t)(row * pitchB) + G::ld_byte(row);
+    const int row = kTB ? G::ldT_row(q) : G::ldB_row(q);
+    offB[q] = (uint32_t)(row * pitchB) + (kTB ? G::ldT_byte(row) : G::ld_byte(row));
   }
 
   // The fp32 tile leaves through LDS as [n][m] rows, as many tile columns per phase as fit: CH lanes of 16 bytes per
@@ -632,15 +614,40 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
     if (p < NPH && n < n_lim) my_row = (int)(to_part ? n : (a.rowmap ? (int64_t)a.rowmap[n] : a.row_base + n));
   }
   const int64_t part_slice = a.ksplit > 0 ? a.part_slice : (int64_t)ntiles * G::BN * a.part_ld;
-  const bool second = blockIdx.y != 0;
   float* const outp = to_part ? a.part + (size_t)(slice + (second ? ksplit : 0)) * part_slice : second ? a.out2 : a.out;
   const int64_t ldo = to_part ? a.part_ld : a.ldo;
   const bool accumulate = to_part ? a.part_accumulate : a.accumulate;
 
   typename G::Acc acc;
   G::zero(acc);
-  G::run(acc, static_cast<const char*>(second ? a.A2 : a.A) + (int64_t)m0 * pitchA + (int64_t)k_first * G::KB, offA,
-         static_cast<const char*>(second ? a.B2 : a.B) + n0 * pitchB + (int64_t)k_first * G::KB, offB, ksteps, smem, Role == 0 ? 3 : (Role == 1 ? 4 : 0));
+  constexpr int kKind = Role == 0 ? 3 : (Role == 1 ? 4 : 0);
+  const char* const pa = static_cast<const char*>(second ? a.A2 : a.A);
+  const char* const pb = static_cast<const char*>(second ? a.B2 : a.B);
+  if constexpr (!kTA) {
+    G::run(acc, pa + (int64_t)m0 * pitchA + (int64_t)k_first * G::KB, offA, pb + n0 * pitchB + (int64_t)k_first * G::KB, offB,
+           ksteps, smem, kKind);
+  } else if constexpr (Role == 1) {
+    // both operands lie in the workspace and are readable to the end of their last K-step
+    const int64_t stepA = G::KROWS * pitchA, stepB = G::KROWS * pitchB;
+    G::run_steps(acc, pa + k_first * stepA + (int64_t)m0 * 2, offA, 0, (uint32_t)stepA, pb + k_first * stepB + n0 * 2, offB, 0,
+                 (uint32_t)stepB, ksteps, smem, kKind);
+  } else {
+    // A K-major operand advances by 64 of its rows per K-step.  What lies past its end (the rows that fill the last
+    // K-step up) has to read as zeros: a buffer window does that, of at most 2 GiB; operands beyond that are taken in
+    // pieces, each of which fills the pipeline anew (3 us).
+    const int64_t stepA = G::KROWS * pitchA, stepB = kTB ? G::KROWS * pitchB : (int64_t)G::KB;
+    const int piece = (int)(0x7fffffff / (kTB && stepB > stepA ? stepB : stepA));
+    const int64_t bytesA = second ? a.a2_bytes : a.a_bytes, bytesB = second ? a.b2_bytes : a.b_bytes;
+    auto window = [](int64_t left) { return (uint32_t)(left < 0 ? 0 : left < 0x7fffffff ? left : 0x7fffffff); };
+    int k = 0;
+    do {
+      const int64_t atA = (k_first + k) * stepA + (int64_t)m0 * 2;
+      const int64_t atB = (k_first + k) * stepB + (kTB ? n0 * 2 : n0 * pitchB);
+      G::run_steps(acc, pa + atA, offA, window(bytesA - atA), (uint32_t)stepA, pb + atB, offB,
+                   kTB ? window(bytesB - atB) : 0x7fffffffu, (uint32_t)stepB, min(piece, ksteps - k), smem, kKind);
+      k += piece;
+    } while (k < ksteps);
+  }
 
   // Rows go in batches: the LDS reads and the loads of the old values of a whole batch are issued before its
   // first store, so a wave that is alone on its SIMD does not sit out one memory round trip per row.

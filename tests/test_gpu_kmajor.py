@@ -1,0 +1,72 @@
+"""Contractions whose operands run along the contraction in memory (W for dH, the hidden states and dZ for dW, both
+operands of the gate's parameter gradients): sizes at the edges of their tiles, of their K-steps of 64 rows and of their
+2 GiB windows, with NaN wherever a row or column is padding and in all of the workspace before the call."""
+import numpy as np
+import pytest
+
+import workloads.dynakv as kv
+from tests.harness import KvProblem, np64, rel_fro, to_device
+from tests.test_gpu_dynakv_bwd import _oracle_bwd
+
+pytestmark = pytest.mark.gpu
+
+
+# dZ is rounded to bf16 once (2^-9 relative per element, as uniform noise 1.1e-3 of the result) and everything else summed in fp32
+TOL_LM = 2.0 ** -8
+
+
+# N, d, V, ldW, vocab_chunk: one K-step and less; tiles 64, 128 and 256 wide; a chunk whose last K-step is past the vocabulary;
+# columns past d in the last tile; a W of 2.3 GB (two windows); a dZ of 2.5 GB
+@pytest.mark.parametrize("N,d,V,ldW,chunk", [(3, 64, 5, 64, 0), (63, 64, 65, 128, 0), (130, 320, 1000, 320, 256),
+                                             (700, 576, 4099, 640, 1024), (2100, 64, 20001, 64, 0), (300, 1088, 600, 1096, 0),
+                                             (200, 64, 70000, 16384, 0), (8192, 64, 152001, 64, 0)])
+def test_dh_and_dw(N, d, V, ldW, chunk):
+    import torch
+    import paper_2603_04411_amd as L
+    g = torch.Generator(device="cuda").manual_seed(N + V)
+    lens = torch.tensor([N, N - N // 3], dtype=torch.int32, device="cuda")
+    H = torch.randn(2 * N, d, generator=g, device="cuda").bfloat16()
+    H[2 * N - N // 3:] = float("nan")                                   # padding
+    wide = torch.full((V, ldW), float("nan"), dtype=torch.bfloat16, device="cuda")
+    W = wide[:, :d]
+    W.copy_(torch.randn(V, d, generator=g, device="cuda") * 0.05)
+    tok = torch.randint(0, V, (2 * N,), generator=g, device="cuda", dtype=torch.int32)
+    gl = torch.randn(2 * N, generator=g, device="cuda")
+    desc = L.make_desc(1, 2, N, d, V, "bf16", vocab_chunk=chunk, ldW=ldW)
+    ws = torch.full((L.workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    logp, lse = (torch.empty(2 * N, device="cuda") for _ in range(2))
+    L.lmhead_logprob_fwd(desc, H, wide, tok, lens, logp, lse, None, None, None, ws)
+    ws.fill_(0xFF)
+    dH, dW = torch.full((2 * N, d), 7.0, device="cuda"), torch.full((V, d), 7.0, device="cuda")
+    L.lmhead_logprob_bwd(desc, H, wide, tok, lens, lse, gl, dH, dW, ws)
+    assert L.lmhead_check(ws) == 0
+    valid = torch.arange(2 * N, device="cuda") < 2 * N - N // 3
+    Hf, Wf, gv, tv = H[valid].float(), W.float(), gl[valid], tok[valid].long()
+    wantH, wantW = torch.zeros(Hf.shape, device="cuda"), torch.zeros(V, d, device="cuda")
+    for r in range(0, Hf.shape[0], 2048):
+        z = Hf[r:r + 2048] @ Wf.t()
+        dz = torch.softmax(z, 1).mul_(-gv[r:r + 2048, None])
+        dz[torch.arange(dz.shape[0], device="cuda"), tv[r:r + 2048]] += gv[r:r + 2048]
+        wantH[r:r + 2048] = dz @ Wf
+        wantW += dz.t() @ Hf[r:r + 2048]
+    assert bool((dH[~valid] == 0).all())
+    assert float((dH[valid] - wantH).norm() / wantH.norm()) <= TOL_LM
+    assert float((dW - wantW).norm() / wantW.norm()) <= TOL_LM
+
+
+@pytest.mark.parametrize("n,d", [(1, 64), (63, 64), (65, 192), (257, 320), (1000, 576), (4100, 128), (5000, 1088)])
+def test_gate_parameter_gradients(n, d):
+    import torch
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d)
+    inp = kv.kv_inputs(cfg)
+    kp = KvProblem(cfg, inp, ldx=d + 8)
+    kp.x[:, d:] = float("nan")
+    xt, _, _, _ = kp.gate(cfg.tau, soft=False)
+    g_xhat, _ = kv.upstream(cfg, with_g_m=False)
+    o = _oracle_bwd(cfg, inp, g_xhat, None, 0.0, "suffix")
+    kp.ws_bwd = torch.full((kp.L.dynakv_bwd_workspace_bytes(kp.desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    got = kp.gate_bwd(xt, to_device(g_xhat))
+    assert kp.check() == 0
+    # the bound of test_gpu_dynakv_bwd.py: g_l and g_x~ are rounded to bf16 before they are contracted
+    errs = {name: rel_fro(np64(t), o[name]) for name, t in zip(("dx", "dU", "dW", "db"), got)}
+    assert all(np.isfinite(e) and e <= 1e-2 for e in errs.values()), errs
