@@ -102,16 +102,21 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
                           k, m, xhat, s));
     return LMHEAD_OK;
   }
-  // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
-  pa.job[0] = param_copy(U, d, w.at<void>(L.UT), L.ldT, L.dp, true);
-  pa.job[1] = param_copy(W, d, w.at<void>(L.WT), L.ldT, L.dp, true);
-  pa.njobs = 2;
-  LM_TRY(launch_kv_prepare(dt, pa, s));
+  const bool kmajor = k_major(dt == LMHEAD_F32);   // parameters as the caller has them
+  if (!kmajor) {
+    // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
+    pa.job[0] = param_copy(U, d, w.at<void>(L.UT), L.ldT, L.dp, true);
+    pa.job[1] = param_copy(W, d, w.at<void>(L.WT), L.ldT, L.dp, true);
+    pa.njobs = 2;
+    LM_TRY(launch_kv_prepare(dt, pa, s));
+  }
 
   KvGemmArgs ga{};
   ga.mode = 0;
-  ga.A = w.at<void>(L.UT);
-  ga.ldA = L.ldT;
+  ga.A = kmajor ? U : w.at<void>(L.UT);
+  ga.ldA = kmajor ? d : L.ldT;
+  ga.bytesA = (kmajor ? (int64_t)d : L.dp) * ga.ldA * L.esz;
+  ga.clear = kmajor;
   ga.B = x;
   ga.ldB = desc->ldx;
   ga.M = d;
@@ -125,7 +130,8 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   ga.mode = 1;
-  ga.A = w.at<void>(L.WT);
+  ga.A = kmajor ? W : w.at<void>(L.WT);
+  ga.clear = false;
   ga.B = xt;
   ga.ldB = d;
   ga.out_e = nullptr;
@@ -176,8 +182,11 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
   // A[j][kk] = U_inv[kk][j]: row j of the copy is output column j, contiguous over the retained index
   KvPrepareArgs pa{};
   pa.hdr = hdr;
-  pa.job[0] = param_copy(U_inv, d, w.at<void>(L.UiT), L.ldT, L.dp, true);
-  pa.njobs = 1;
+  const bool kmajor = k_major(dt == LMHEAD_F32);   // U_inv as the caller has it
+  if (!kmajor) {
+    pa.job[0] = param_copy(U_inv, d, w.at<void>(L.UiT), L.ldT, L.dp, true);
+    pa.njobs = 1;
+  }
   pa.count = make_kv_count(k, L.n, d, L.nbuckets, w.at<int32_t>(L.hist));
   LM_TRY(launch_kv_prepare(dt, pa, s));
   LM_TRY(launch_kv_order(dt, pa.count, off, packed_elems * L.esz, L.ncap, w.at<int32_t>(L.order),
@@ -185,8 +194,9 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
 
   KvGemmArgs ga{};
   ga.mode = 2;
-  ga.A = w.at<void>(L.UiT);
-  ga.ldA = L.ldT;
+  ga.A = kmajor ? U_inv : w.at<void>(L.UiT);
+  ga.ldA = kmajor ? d : L.ldT;
+  ga.bytesA = (kmajor ? (int64_t)d : L.dp) * ga.ldA * L.esz;
   ga.B = packed;
   ga.bytesB = packed_elems * L.esz;
   ga.M = d;
@@ -244,21 +254,23 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0;
   const bool accum = (desc->flags & DYNAKV_FLAG_ACCUM_GRAD) != 0;
 
-  const bool few = kv_few_fits(L.n, d);   // the parameters as the caller has them, no copies
-  // parameter operands of the three token-major products: W^T (K-contiguous copy) for the logits, and
-  // row-padded copies of W and U, which are K-contiguous as they are for g_l W^T and g_x~ U^T
+  // Parameter operands of the three token-major products.  Few tokens and bf16: as the caller has them, W is K-major in the
+  // logits and K-contiguous, like U, in g_l W^T and g_x~ U^T.  fp32: W^T as a K-contiguous copy, W and U as row-padded ones.
+  const bool few = kv_few_fits(L.n, d), kmajor = k_major(dt == LMHEAD_F32);
   KvPrepareArgs pa{};
   pa.hdr = hdr;
   pa.job[0] = param_copy(W, d, at(L.WT), L.ldT, L.dp, true);
   pa.job[1] = param_copy(W, d, at(L.Wp), L.ldT, L.dp, false);
   pa.job[2] = param_copy(U, d, at(L.Up), L.ldT, L.dp, false);
   pa.njobs = 3;
-  if (!few) LM_TRY(launch_kv_prepare(dt, pa, s));
+  if (!few && !kmajor) LM_TRY(launch_kv_prepare(dt, pa, s));
 
   KvGemmArgs ga{};
   ga.mode = 1;
-  ga.A = at(L.WT);
-  ga.ldA = L.ldT;
+  ga.A = kmajor ? W : at(L.WT);
+  ga.ldA = kmajor ? d : L.ldT;
+  ga.bytesA = (kmajor ? (int64_t)d : L.dp) * ga.ldA * L.esz;
+  ga.clear = kmajor;
   ga.B = xt;
   ga.ldB = d;
   ga.M = d;
@@ -283,8 +295,9 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   LM_TRY(launch_kv_sum_rows(static_cast<const float*>(at(L.dbpart)), L.nblk, d, d, db, accum, s));
 
   // g_x~ += g_l W^T
-  ga.mode = 0;
-  ga.A = at(L.Wp);
+  ga.mode = 3;
+  ga.A = kmajor ? W : at(L.Wp);
+  ga.clear = false;
   ga.B = at(L.gl);
   ga.out_f = nullptr;
   ga.out_e = at(L.gxt);
@@ -297,7 +310,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   // dx = g_x~ U^T
-  ga.A = at(L.Up);
+  ga.A = kmajor ? U : at(L.Up);
   ga.B = at(L.gxt);
   ga.out_e = dx;
   ga.accumulate = false;

@@ -41,9 +41,9 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
     return o;
   };
   L.hdr = take(sizeof(WsHeader));
-  L.UT = take((size_t)L.dp * L.ldT * L.esz);
+  L.UT = take((size_t)L.dp * L.ldT * L.esz);   // K-contiguous copies; bf16: the one-kernel gate's fragments
   L.WT = take((size_t)L.dp * L.ldT * L.esz);
-  L.UiT = take((size_t)L.dp * L.ldT * L.esz);
+  L.UiT = take(k_major(L.esz == 4) ? 0 : (size_t)L.dp * L.ldT * L.esz);
   L.logits = take((size_t)L.ncap * L.d * 4);
   L.order = take((size_t)L.ncap * 4);
   L.pos_off = take((size_t)L.ncap * 4);
@@ -56,8 +56,8 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
 }
 
 // Workspace of the gate's backward pass (dynakv_gate_bwd).  The two token-major gradients g_l and
-// g_xt are kept in the storage type; T1 / T2 hold the token-contiguous (transposed) operand copies of
-// one parameter-gradient contraction at a time.
+// g_xt are kept in the storage type.  fp32 only: Wp, Up, WT the parameter copies, T1 / T2 the token-contiguous (transposed) operand
+// copies of one parameter-gradient contraction at a time.
 struct KvBwdLayout {
   int esz;
   int64_t n, d, ncap, dp, ldT;
@@ -116,13 +116,13 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
     return o;
   };
   L.hdr = take(sizeof(WsHeader));
-  L.Wp = take((size_t)L.dp * L.ldT * L.esz);
-  L.Up = take((size_t)L.dp * L.ldT * L.esz);
-  L.WT = take((size_t)L.dp * L.ldT * L.esz);
+  const bool copies = !k_major(L.esz == 4);
+  L.Wp = take(copies ? (size_t)L.dp * L.ldT * L.esz : 0);
+  L.Up = take(copies ? (size_t)L.dp * L.ldT * L.esz : 0);
+  L.WT = take(copies ? (size_t)L.dp * L.ldT * L.esz : 0);
   L.logits = take((size_t)L.ncap * L.d * 4);
   L.gl = take((size_t)L.ncap * L.d * L.esz);
   L.gxt = take((size_t)L.ncap * L.d * L.esz);
-  const bool copies = !k_major(L.esz == 4);
   L.T1 = take(copies ? (size_t)L.dp * L.ldK * L.esz : 0);
   L.T2 = take(copies ? (size_t)L.dp * L.ldK * L.esz : 0);
   // Up to kKvPairBytes a copy the launches weigh more than the memory: one preparation, one product and one sum serve both
@@ -152,12 +152,14 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
 //   out[row(n)][m] = sum_k A[m][k] * Bop[n][k],  m < M, n < Nn.
 // mode 0/1: Bop rows are dense rows of B (pitch ldB), row(n) = n.  The output is the storage type
 //           (out_e) or fp32 (out_f), whichever is non-null.
+// mode 3:   as mode 0, with A always [M x K].  (bf16: A of modes 0 to 2 is the parameter matrix as the caller has it, [K x M].)
 // mode 2:   ragged rows: Bop[n] = the pos_len[n] bytes of the packed store at byte offset pos_off[n],
 //           zero beyond; row(n) = order[n] (< 0: no token); the tile's step count follows its
 //           first row, the longest (the three arrays are written by launch_kv_order).
 struct KvGemmArgs {
   int mode;
-  const void* A;        // [dp x K] transposed parameter copy, pitch ldA
+  const void* A;        // parameter matrix, pitch ldA: [M x K], or [K x M] for bf16 in modes 0 to 2
+  int64_t bytesA;       // readable at A; what lies beyond counts as zeros
   int64_t ldA;
   const void* B;        // dense rows (mode 0/1) or the packed store (mode 2)
   int64_t ldB;
@@ -171,7 +173,8 @@ struct KvGemmArgs {
   void* out_e;
   float* out_f;
   int64_t ldo;
-  bool accumulate;      // mode 0/1: the tile is added to what the output holds (rounded once more for bf16)
+  bool clear;           // the header is cleared
+  bool accumulate;      // dense modes: the tile is added to what the output holds (rounded once more for bf16)
   WsHeader* hdr;
   int walk_len;         // set by the launcher: length of the tile walk (tile_map.h)
 };

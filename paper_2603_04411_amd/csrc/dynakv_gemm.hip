@@ -1,10 +1,12 @@
 // Matrix-core kernels of the KV-compression path, built on GemmTile (gemm_core.h):
-//   mode 0  spectral projection     x~ = x U                      (Eq. 1); also the two token-major
-//           products of the gate's backward pass, optionally added to what the output holds
+//   mode 0  spectral projection     x~ = x U                      (Eq. 1)
 //   mode 1  gate logits             x~ W          (fp32, bias added by the mask kernel; Eq. 5)
 //   mode 2  dynamic low-rank reconstruction  x_bar = x^[0:k] U^-1[0:k, :]   (Eq. 3)
-// All three are  out[row(n)][m] = sum_k A[m][k] Bop[n][k]  with the parameter matrix (transposed
-// copy, K-contiguous) on the MFMA M axis and tokens on N, as in the LM-head kernels.  The
+//   mode 3  the two token-major products of the gate's backward pass (M^T in place of M), optionally added to what
+//           the output holds
+// All are  out[row(n)][m] = sum_k A[m][k] Bop[n][k]  with the parameter matrix on the MFMA M axis and tokens on N, as in the
+// LM-head kernels.  bf16 takes the matrix as the caller has it (K-major in modes 0 to 2), fp32 a K-contiguous copy: the launch that
+// made the copies was 4.5 us (gate of 4096 x 1024 42.2 -> 37.6 us, with the gradients' copies the training pair 166 -> 148).  The
 // parameter matrix (2 MB at d = 1024) stays in every XCD's L2; the token rows stream through once
 // per XCD because an XCD runs all M tiles of a token tile together (tile_map.h).
 //
@@ -53,13 +55,15 @@ constexpr int wg_per_cu(int edge) { return 256 / edge; }
 
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
-template <typename E, int Edge, bool kMask>
-using KvTile = GemmTile<E, Edge, Edge, 2, 2, /*kLeadB=*/true, kMask>;
+template <typename E, int Edge, int Mode>
+using KvTile = GemmTile<E, Edge, Edge, 2, 2, /*kLeadB=*/true, /*kMaskB=*/Mode == 2,
+                        /*kTransA=*/k_major(Elem<E>::size == 4) && Mode != 3>;
 
 // One output tile; `wg` is the tile's position in the XCD-aware walk.
 template <typename E, int Edge, int Mode>
 __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
-  using G = KvTile<E, Edge, Mode == 2>;
+  using G = KvTile<E, Edge, Mode>;
+  constexpr bool kTA = k_major(Elem<E>::size == 4) && Mode != 3;
   constexpr int ESZ = Elem<E>::size;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
   const int ntiles = (int)((a.Nn + G::BN - 1) / G::BN);
@@ -79,8 +83,8 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
   int limB[G::B_LD];
 #pragma unroll
   for (int q = 0; q < G::A_LD; ++q) {
-    const int row = G::ldA_row(q);
-    offA[q] = (uint32_t)(row * pitchA) + G::ld_byte(row);
+    const int row = kTA ? G::ldT_row(q) : G::ldA_row(q);
+    offA[q] = (uint32_t)(row * pitchA) + (kTA ? G::ldT_byte(row) : G::ld_byte(row));
   }
   const char* Bbase;
   uint32_t bytesB;
@@ -120,8 +124,9 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
 
   typename G::Acc acc;
   G::zero(acc);
-  G::run_rows(acc, static_cast<const char*>(a.A) + (int64_t)m0 * pitchA, offA, Bbase, offB, limB, bytesB, ksteps,
-              smem);
+  const int64_t atA = (int64_t)m0 * (kTA ? ESZ : pitchA);
+  G::run_ragged(acc, static_cast<const char*>(a.A) + atA, offA, (uint32_t)(a.bytesA - atA),
+                kTA ? (uint32_t)(G::KROWS * pitchA) : (uint32_t)G::KB, Bbase, offB, limB, bytesB, ksteps, smem);
 
   // The tile leaves through LDS as [n][m] rows of fp32 (as many tile columns per phase as fit) so that
   // each output row segment is written with 16 bytes per lane for fp32 and 8 for bf16, a whole
@@ -237,12 +242,16 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
 template <typename E, int Edge, int Mode>
 __global__ __launch_bounds__(256, wg_per_cu(Edge)) void kv_gemm_kernel(KvGemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (a.clear && blockIdx.x == 0 && threadIdx.x == 0) {
+    a.hdr->err = 0;
+    a.hdr->nv = 0;
+  }
   for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Edge, Mode>(a, wg, smem);
 }
 
 template <typename E, int Edge, int Mode>
 hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
-  using G = KvTile<E, Edge, Mode == 2>;
+  using G = KvTile<E, Edge, Mode>;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
   const int64_t ntiles = (a.Nn + G::BN - 1) / G::BN;
   if (a.accumulate && (Mode == 2 || a.out_f || !a.out_e)) return hipErrorInvalidValue;
@@ -366,7 +375,8 @@ hipError_t launch_e(const KvGemmArgs& a, hipStream_t s) {
   switch (a.mode) {
     case 0: return launch_mode<E, 0>(a, s);
     case 1: return launch_mode<E, 1>(a, s);
-    default: return launch_mode<E, 2>(a, s);
+    case 2: return launch_mode<E, 2>(a, s);
+    default: return launch_mode<E, k_major(Elem<E>::size == 4) ? 3 : 0>(a, s);   // fp32: A is [M x K] in mode 0 too
   }
 }
 

@@ -70,3 +70,42 @@ def test_gate_parameter_gradients(n, d):
     # the bound of test_gpu_dynakv_bwd.py: g_l and g_x~ are rounded to bf16 before they are contracted
     errs = {name: rel_fro(np64(t), o[name]) for name, t in zip(("dx", "dU", "dW", "db"), got)}
     assert all(np.isfinite(e) and e <= 1e-2 for e in errs.values()), errs
+
+
+# the tiled products, 64, 128 and 256 columns wide, with a last tile past d columns and a last token tile past n: parameters as the
+# caller has them, each with NaN right behind it
+@pytest.mark.parametrize("n,d,edge", [(8300, 64, 64), (1100, 576, 64), (2200, 1088, 128), (9000, 320, 128), (33000, 576, 256)])
+def test_gate_and_reconstruction(n, d, edge):
+    import torch
+    import paper_2603_04411_amd as L
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+
+    def param(t):
+        buf = torch.full((d * d + 65536,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        buf[:d * d] = t.flatten()
+        return buf[:d * d].view(d, d)
+    Q = torch.linalg.qr(torch.randn(d, d, generator=g, device="cuda"))[0]
+    U, Ui, W = param(Q), param(Q.t()), param(1.5 * torch.randn(d, d, generator=g, device="cuda"))
+    b = torch.randn(d, generator=g, device="cuda")
+    x = torch.randn(n, d, generator=g, device="cuda").bfloat16()
+    desc = L.make_kv_desc(n, d, "bf16")
+    ws = torch.full((L.dynakv_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    xt, xhat, xbar = (torch.full((n, d), 3.0, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    k = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    m = torch.full((n, d), 3.0, device="cuda")
+    L.dynakv_gate(desc, x, U, W, b, 0.1, xt, k, m, xhat, ws)
+    want = x.double() @ U.double()
+    # one rounding to bf16 of an fp32 sum
+    assert bool(((xt.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all())
+    p = torch.softmax(xt.double() @ W.double() + b.double(), 1)
+    # logits are fp32 sums of d terms of up to about 6: errors of 1e-5, so the mask's are a few of these
+    assert float((m.double() - p.flip(1).cumsum(1).flip(1)).abs().max()) <= 1e-4
+    assert torch.equal(k, (m > 0.1).sum(1, dtype=torch.int32))
+    off = torch.empty(n + 1, dtype=torch.int64, device="cuda")
+    packed = torch.full((n * d,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    L.dynakv_store(desc, xt, k, 0, off, packed, n * d, ws)
+    L.dynakv_reconstruct(desc, packed, n * d, off, k, Ui, xbar, ws)
+    assert L.dynakv_check(ws) == 0
+    keep = torch.arange(d, device="cuda")[None, :] < k[:, None]
+    want = torch.where(keep, xt.double(), 0.0) @ Ui.double()
+    assert bool(((xbar.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all())
