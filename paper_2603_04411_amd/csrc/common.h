@@ -47,23 +47,22 @@ struct WsLayout {
   // Row pitches (elements) of the workspace matrices.  Each is its logical width plus one
   // 128-byte line: a power-of-two pitch would put every row of a tile on the same L2
   // channel and set (the token-major operands have a pitch of Ncap elements, often 2^k).
-  int64_t ldHc, ldHcT, ldWT, ldZ, ldZT;
+  int64_t ldHc, ldZ;
   int64_t ld8;      // pitch (bytes) of the e4m3 operand copies: d + one 128-byte line
   DhSplit dh;           // dH: tiles and how their contraction may be cut; partial tiles go to dHpart
   size_t dHpart;
   size_t dWpart;        // partial tiles of the dW launches that split a remainder of vocabulary tiles
   size_t dWpart_bytes;
-  size_t hdr, cu_len, row_slot, tok_c, gid, g_c, lse_c, zy, part, Hc, HcT, WT, dZ, dZT, Hc8, W8, total;
+  size_t hdr, cu_len, row_slot, tok_c, gid, g_c, lse_c, zy, part, Hc, dZ, Hc8, W8, total;
 };
 
-// Default backward chunk: as wide as keeps dZ (fp32: and its transposed copy; worst case: every slot valid)
-// within about 48 GB, at most 262144 columns (small problems take the whole vocabulary in one
+// Default backward chunk: as wide as keeps dZ (worst case: every slot valid) within about 48 GB, at most 262144 columns (small problems take the whole vocabulary in one
 // chunk).  Wider chunks mean fewer read-modify-write passes over dH and longer contractions per
 // launch.
 static inline int64_t default_vocab_chunk(const lmhead_desc* d) {
   const int64_t esz = d->dtype == LMHEAD_BF16 ? 2 : 4;
   const int64_t N = (int64_t)d->P * d->G * d->T;
-  int64_t vc = (48ll << 30) / ((k_major(d->dtype == LMHEAD_F32) ? 1 : 2) * esz * (N > 0 ? N : 1));
+  int64_t vc = (48ll << 30) / (esz * (N > 0 ? N : 1));
   vc = vc / kTile * kTile;
   if (vc > 262144) vc = 262144;
   if (vc < 4 * kTile) vc = 4 * kTile;
@@ -110,17 +109,9 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.part = take((size_t)npol * 3 * (fp8 ? L.ntiles * L.Ncap : logits_part_slots(f32, d->V, L.N)) * 4);
   const int64_t pad = 128 / L.esz;
   L.ldHc = d->d + pad;
-  L.ldHcT = L.Ncap + pad;
-  L.ldWT = L.Vp + pad;
   L.ldZ = L.Vc + pad;
-  L.ldZT = L.Ncap + pad;
   L.Hc = take((size_t)L.Ncap * L.ldHc * L.esz);
-  // K-contiguous copies: fp32 only, bf16 contracts the operands as they lie
-  const bool copies = !k_major(f32);
-  L.HcT = take(copies ? (size_t)L.dp * L.ldHcT * L.esz : 0);
-  L.WT = take(copies ? (size_t)L.dp * L.ldWT * L.esz : 0);
   L.dZ = take((size_t)L.Ncap * L.ldZ * L.esz);
-  L.dZT = take(copies ? (size_t)L.Vc * L.ldZT * L.esz : 0);
   {
     L.dh.ksteps = (int)(L.Vc * L.esz / 128);
     L.dh.edge = dh_edge(f32, d->d, L.N, L.dh.ksteps);
@@ -149,7 +140,7 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
 //   number of slices for N_v;
 //   valid rows of H -> the dense, zero-padded Hc[Ncap x d]; tok -> tok_c (-1 for an id outside [0, V) and on the
 //   padding), g -> g_c and lse -> lse_c (unless null); the npol vectors zy[p * Ncap + .] are cleared and the npol vectors
-//   gid[p * Ncap + .] set to -1.
+//   gid[p * Ncap + .] set to -1; with dH the rows of dH of padded slots are set to 0.
 struct IndexArgs {
   const int32_t* len;
   int R, T;
@@ -176,37 +167,10 @@ struct IndexArgs {
   int64_t Ncap;
   int want_split;
   DhSplit split;
+  char* dH;
+  int64_t dh_bytes;    // bytes per row of dH
 };
 hipError_t launch_index(const IndexArgs& a, hipStream_t s);
-
-// out[c][r] = in[r][c] for r < rows (header.nv when rows_from_nv), c < cols, zero padding up to out's extent
-// [cols_p x rows_p] (pitch ld_out >= rows_p).  e4m3 (unless null): also e4m3(in[r][c] * scale) as it lies, zero up to rows_p.
-struct Transpose {
-  const void* in;
-  int64_t ld_in, rows, rows_p;
-  int cols, cols_p;
-  bool rows_from_nv;
-  void* out;
-  int64_t ld_out;
-  uint8_t* e4m3;
-  int64_t ld_e4m3;
-  float scale;
-  int tiles;           // set by the launcher
-};
-// The backward's K-contiguous operand copies; rows of dH of padded slots are set to 0; a token id outside [0, V) on a
-// valid slot sets header.err.
-struct OperandArgs {
-  WsHeader* hdr;
-  const int32_t* len;
-  const int32_t* tok;
-  int64_t N;
-  int T, V;
-  char* dH;
-  int64_t dh_bytes;    // bytes per row
-  Transpose job[2];
-  int zero_blocks;     // set by the launcher
-};
-hipError_t launch_operands(int dtype, const OperandArgs& a, hipStream_t s);
 
 struct FwdArgs {
   const void* Hc;      // [Ncap x d], pitch ldHc
@@ -242,20 +206,18 @@ struct DzArgs {
   int d, V;
   int64_t Ncap;
   int64_t ldZ;    // pitch of dZ (elements)
-  int64_t ldZT;   // pitch of dZT (elements)
   int c0;         // first vocabulary id of the chunk
   int edge;       // tile edge: 64, 128 or 256 (256 for e4m3)
   int ntiles;     // vocabulary tiles of kTile columns in this chunk
   const int32_t* tok_c;
   const float* g_c;
   const float* lse_c;
-  const WsHeader* hdr;
+  WsHeader* hdr;  // a valid slot whose tok_c is -1 sets header.err
   void* dZ;       // [Ncap x chunk], pitch ldZ
-  void* dZT;      // [chunk x Ncap], pitch ldZT; fp32 output only
   float zscale;   // as in FwdArgs
 };
 // op_dtype: type of Hc / W as given in the arguments (LMHEAD_F32, LMHEAD_BF16 or kDtypeFp8);
-// out_dtype: type of dZ / dZT (LMHEAD_F32 or LMHEAD_BF16; equal to op_dtype unless that is e4m3).
+// out_dtype: type of dZ (LMHEAD_F32 or LMHEAD_BF16; equal to op_dtype unless that is e4m3).
 hipError_t launch_dz(int op_dtype, int out_dtype, const DzArgs& a, hipStream_t s);
 
 // out[r][c] = e4m3(in[r][c] * 2^exp2) (clamped to +-448, round to nearest even) for r < rows, 0 for the
@@ -267,9 +229,9 @@ hipError_t launch_quantize_e4m3(int dtype, const void* in, int64_t ld_in, int64_
 
 // Generic C^T-store contraction: for m < M, n < Nn: out[rowmap(n)][m] (+)= sum_k A[m][k] B[n][k].
 struct GemmTArgs {
-  const void* A;       // [Mp x K], pitch ldA elements
+  const void* A;       // [K x M], pitch ldA elements
   int64_t ldA;
-  const void* B;       // [Np x K], pitch ldB elements
+  const void* B;       // [K x N], for dH [N x K], pitch ldB elements
   int64_t ldB;
   int M;               // valid output columns (d)
   int64_t n_limit;     // valid n (ignored when n_from_nv)
@@ -290,7 +252,7 @@ struct GemmTArgs {
   bool part_accumulate;   // unless part_single.  part_slice = floats per slice (header.ksplit: n tiles x edge x part_ld).
   bool part_single;
   int edge;            // workgroup tile edge: 64, 128 or 256 (n_tiles_cap stays in units of kTile)
-  // bf16 K-major operands (A always, B except for dH): A is [K x M], B is [K x N].  Nothing past these bytes from A / B is
+  // K-major operands (A always, B except for dH): A is [K x M], B is [K x N].  Nothing past these bytes from A / B is
   // read (rows of the contraction beyond them count as zeros); dW's operands are readable to the end of the last K-step
   // instead, with a row of 256 values from every column tile on.
   int64_t a_bytes, b_bytes, a2_bytes, b2_bytes;

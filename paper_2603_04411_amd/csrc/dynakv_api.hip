@@ -29,12 +29,6 @@ struct Ws {
   T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
 };
 
-// K-contiguous (transposed) or row-padded copy of a dense d x d parameter matrix, zero up to dp rows of the copy
-KvCopy param_copy(const void* in, int d, void* out, int64_t ld_out, int64_t dp, bool transposed) {
-  return {in, d, d, transposed ? d : dp, d, (int)(transposed ? dp : d), out, ld_out,
-          transposed ? KvCopy::kTransposed : KvCopy::kPlain, 0};
-}
-
 // common prologue of the compute entry points
 int open_ws(const dynakv_desc* desc, void* ws, size_t ws_bytes, Ws& w) {
   const int rc = validate(desc);
@@ -73,17 +67,17 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
   const int dt = desc->dtype;
   const int d = desc->d;
 
-  KvPrepareArgs pa{};
-  pa.hdr = hdr;
   if (!m && !xhat && kv_gate_fits(dt, L.n, d, desc->ldx)) {
     // nothing but x~ and k is wanted: one kernel, with the parameter matrices in its fragment order
     const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0;
-    pa.job[0] = {U, d, d, d, d, d, w.at<void>(L.UT), 0, KvCopy::kFragments, 0};
-    pa.job[1] = {W, d, d, d, d, d, w.at<void>(L.WT), 0, literal ? KvCopy::kFragmentsFlipped : KvCopy::kFragments, 0};
+    KvPrepareArgs pa{};
+    pa.hdr = hdr;
+    pa.job[0] = {U, d, w.at<void>(L.Ufrag), false};
+    pa.job[1] = {W, d, w.at<void>(L.Wfrag), literal};
     pa.njobs = 2;
-    LM_TRY(launch_kv_prepare(dt, pa, s));
+    LM_TRY(launch_kv_prepare(L.esz, pa, s));
     TimedLaunch tl(4, s);
-    LM_TRY(launch_kv_gate({x, desc->ldx, w.at<void>(L.UT), w.at<void>(L.WT), b, L.n, tau, literal ? 1 : 0, xt, k}, d, s));
+    LM_TRY(launch_kv_gate({x, desc->ldx, w.at<void>(L.Ufrag), w.at<void>(L.Wfrag), b, L.n, tau, literal ? 1 : 0, xt, k}, d, s));
     return LMHEAD_OK;
   }
   if (kv_few_fits(L.n, d)) {
@@ -102,21 +96,12 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
                           k, m, xhat, s));
     return LMHEAD_OK;
   }
-  const bool kmajor = k_major(dt == LMHEAD_F32);   // parameters as the caller has them
-  if (!kmajor) {
-    // K-contiguous copies of the two parameter matrices: UT[j][k] = U[k][j], WT likewise
-    pa.job[0] = param_copy(U, d, w.at<void>(L.UT), L.ldT, L.dp, true);
-    pa.job[1] = param_copy(W, d, w.at<void>(L.WT), L.ldT, L.dp, true);
-    pa.njobs = 2;
-    LM_TRY(launch_kv_prepare(dt, pa, s));
-  }
-
   KvGemmArgs ga{};
   ga.mode = 0;
-  ga.A = kmajor ? U : w.at<void>(L.UT);
-  ga.ldA = kmajor ? d : L.ldT;
-  ga.bytesA = (kmajor ? (int64_t)d : L.dp) * ga.ldA * L.esz;
-  ga.clear = kmajor;
+  ga.A = U;
+  ga.ldA = d;
+  ga.bytesA = (int64_t)d * d * L.esz;
+  ga.clear = true;
   ga.B = x;
   ga.ldB = desc->ldx;
   ga.M = d;
@@ -130,7 +115,7 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   ga.mode = 1;
-  ga.A = kmajor ? W : w.at<void>(L.WT);
+  ga.A = W;
   ga.clear = false;
   ga.B = xt;
   ga.ldB = d;
@@ -179,24 +164,18 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
   const int dt = desc->dtype;
   const int d = desc->d;
 
-  // A[j][kk] = U_inv[kk][j]: row j of the copy is output column j, contiguous over the retained index
   KvPrepareArgs pa{};
   pa.hdr = hdr;
-  const bool kmajor = k_major(dt == LMHEAD_F32);   // U_inv as the caller has it
-  if (!kmajor) {
-    pa.job[0] = param_copy(U_inv, d, w.at<void>(L.UiT), L.ldT, L.dp, true);
-    pa.njobs = 1;
-  }
   pa.count = make_kv_count(k, L.n, d, L.nbuckets, w.at<int32_t>(L.hist));
-  LM_TRY(launch_kv_prepare(dt, pa, s));
+  LM_TRY(launch_kv_prepare(L.esz, pa, s));
   LM_TRY(launch_kv_order(dt, pa.count, off, packed_elems * L.esz, L.ncap, w.at<int32_t>(L.order),
                          w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), hdr, s));
 
   KvGemmArgs ga{};
   ga.mode = 2;
-  ga.A = kmajor ? U_inv : w.at<void>(L.UiT);
-  ga.ldA = kmajor ? d : L.ldT;
-  ga.bytesA = (kmajor ? (int64_t)d : L.dp) * ga.ldA * L.esz;
+  ga.A = U_inv;
+  ga.ldA = d;
+  ga.bytesA = (int64_t)d * d * L.esz;
   ga.B = packed;
   ga.bytesB = packed_elems * L.esz;
   ga.M = d;
@@ -254,23 +233,14 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0;
   const bool accum = (desc->flags & DYNAKV_FLAG_ACCUM_GRAD) != 0;
 
-  // Parameter operands of the three token-major products.  Few tokens and bf16: as the caller has them, W is K-major in the
-  // logits and K-contiguous, like U, in g_l W^T and g_x~ U^T.  fp32: W^T as a K-contiguous copy, W and U as row-padded ones.
-  const bool few = kv_few_fits(L.n, d), kmajor = k_major(dt == LMHEAD_F32);
-  KvPrepareArgs pa{};
-  pa.hdr = hdr;
-  pa.job[0] = param_copy(W, d, at(L.WT), L.ldT, L.dp, true);
-  pa.job[1] = param_copy(W, d, at(L.Wp), L.ldT, L.dp, false);
-  pa.job[2] = param_copy(U, d, at(L.Up), L.ldT, L.dp, false);
-  pa.njobs = 3;
-  if (!few && !kmajor) LM_TRY(launch_kv_prepare(dt, pa, s));
-
+  // the parameters as the caller has them: W is K-major in the logits and K-contiguous, like U, in g_l W^T and g_x~ U^T
+  const bool few = kv_few_fits(L.n, d);
   KvGemmArgs ga{};
   ga.mode = 1;
-  ga.A = kmajor ? W : at(L.WT);
-  ga.ldA = kmajor ? d : L.ldT;
-  ga.bytesA = (kmajor ? (int64_t)d : L.dp) * ga.ldA * L.esz;
-  ga.clear = kmajor;
+  ga.A = W;
+  ga.ldA = d;
+  ga.bytesA = (int64_t)d * d * L.esz;
+  ga.clear = true;
   ga.B = xt;
   ga.ldB = d;
   ga.M = d;
@@ -296,7 +266,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
 
   // g_x~ += g_l W^T
   ga.mode = 3;
-  ga.A = kmajor ? W : at(L.Wp);
+  ga.A = W;
   ga.clear = false;
   ga.B = at(L.gl);
   ga.out_f = nullptr;
@@ -310,7 +280,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   // dx = g_x~ U^T
-  ga.A = kmajor ? U : at(L.Up);
+  ga.A = U;
   ga.B = at(L.gxt);
   ga.out_e = dx;
   ga.accumulate = false;
@@ -322,20 +292,21 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
 
-  // Parameter gradients: contractions over the tokens, cut into ksplit slices of the token range (one: stored directly).
-  //   dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
-  // bf16: the operands as they lie, both gradients in one launch.  fp32: token-contiguous copies of them.
-  auto token_copy = [&](const void* src, int64_t ld, size_t to) {
-    return KvCopy{src, ld, L.n, L.ncap, d, (int)L.dp, at(to), L.ldK, KvCopy::kTransposed, 0};
-  };
+  // Parameter gradients: contractions over the tokens, both in one launch, cut into ksplit slices of the token range (one:
+  // stored directly).  dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
   GemmTArgs ta{};
-  ta.A = at(L.T2);
-  ta.ldA = L.ldK;
-  ta.B = at(L.T1);
-  ta.ldB = L.ldK;
+  ta.A = at(L.gl);
+  ta.A2 = at(L.gxt);
+  ta.ldA = d;
+  ta.B = xt;
+  ta.B2 = x;
+  ta.ldB = d;
+  ta.ldB2 = desc->ldx;
+  ta.a_bytes = ta.a2_bytes = ta.b_bytes = L.n * d * L.esz;
+  ta.b2_bytes = ((L.n - 1) * desc->ldx + d) * L.esz;
   ta.M = d;
   ta.n_limit = d;
-  ta.K = L.ncap;
+  ta.K = L.n;
   ta.n_tiles_cap = L.dp / kTile;
   ta.hdr = hdr;
   ta.ksplit = L.ksplit;
@@ -343,61 +314,16 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ta.part = L.ksplit > 1 ? static_cast<float*>(at(L.part)) : nullptr;
   ta.part_ld = d;
   ta.part_slice = (int64_t)d * d;
+  ta.out = dW;
+  ta.out2 = dU;
   ta.ldo = d;
   ta.accumulate = accum;
-  if (k_major(dt == LMHEAD_F32)) {
-    ta.A = at(L.gl);
-    ta.A2 = at(L.gxt);
-    ta.B = xt;
-    ta.B2 = x;
-    ta.ldA = d;
-    ta.ldB = d;
-    ta.ldB2 = desc->ldx;
-    ta.K = L.n;
-    ta.a_bytes = ta.a2_bytes = ta.b_bytes = L.n * d * 2;
-    ta.b2_bytes = ((L.n - 1) * desc->ldx + d) * 2;
-    ta.out = dW;
-    ta.out2 = dU;
-    {
-      TimedLaunch tl(11, s);
-      LM_TRY(launch_gemm_t(dt, ta, s, 2));
-    }
-    if (L.ksplit > 1) LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, dW, accum, s, dU));
-    return LMHEAD_OK;
+  {
+    TimedLaunch tl(11, s);
+    LM_TRY(launch_gemm_t(dt, ta, s, 2));
   }
-  ta.ldB2 = L.ldK;
-  // one gradient, or both: the second one's operands are in T3, T4
-  auto param_grad = [&](const KvPrepareArgs& copies, int kind, float* out, float* out2) -> int {
-    {
-      TimedLaunch tl(13, s);
-      LM_TRY(launch_kv_prepare(dt, copies, s));
-    }
-    ta.out = out;
-    ta.out2 = out2;
-    ta.A2 = out2 ? at(L.T4) : nullptr;
-    ta.B2 = out2 ? at(L.T3) : nullptr;
-    {
-      TimedLaunch tl(kind, s);
-      LM_TRY(launch_gemm_t(dt, ta, s, 2));
-    }
-    if (L.ksplit > 1) LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, out, accum, s, out2));
-    return LMHEAD_OK;
-  };
-  KvPrepareArgs copies{};
-  copies.job[0] = token_copy(xt, d, L.T1);
-  copies.job[1] = token_copy(at(L.gl), d, L.T2);
-  copies.njobs = 2;
-  if (L.pair) {
-    copies.job[2] = token_copy(x, desc->ldx, L.T3);
-    copies.job[3] = token_copy(at(L.gxt), d, L.T4);
-    copies.njobs = 4;
-    return param_grad(copies, 11, dW, dU);
-  }
-  const int prc = param_grad(copies, 11, dW, nullptr);
-  if (prc != LMHEAD_OK) return prc;
-  copies.job[0] = token_copy(x, desc->ldx, L.T1);
-  copies.job[1] = token_copy(at(L.gxt), d, L.T2);
-  return param_grad(copies, 12, dU, nullptr);
+  if (L.ksplit > 1) LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, dW, accum, s, dU));
+  return LMHEAD_OK;
 }
 
 int dynakv_check(void* ws, void* stream) { return lmhead_check(ws, stream); }

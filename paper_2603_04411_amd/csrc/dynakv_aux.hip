@@ -510,16 +510,14 @@ __device__ inline int bucket_of(int k, int d, int esz) {
   return (k * esz + 127) / 128;
 }
 
-// One launch prepares a call: it clears the header, makes up to kKvMaxCopies operand copies (64 x 64 tiles, 16-byte
-// accesses on both sides, the transposed ones through LDS) and counts the tokens of each
-// length for the reconstruction's grouping.  Every one of these was a launch of its own, 3-5 us each and mostly dispatch
-// (the copies of d = 1024 are 2 MB).
-template <typename T>
-__global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a) {
-  constexpr int VEC = 16 / sizeof(T);         // elements per 16-byte chunk
-  constexpr int CPR = 64 / VEC;               // chunks per tile row
-  constexpr int PITCH = 64 + 4 / sizeof(T);   // elements; keeps rows 4-byte aligned and the gather conflict-free
-  __shared__ __attribute__((aligned(16))) T tile[64 * PITCH];
+// One launch prepares a call: it clears the header, puts the parameter matrices of the one-kernel gate into fragment order
+// (64 x 64 tiles through LDS, 16-byte accesses on both sides) and counts the tokens of each length for the reconstruction's
+// grouping.  Every one of these was a launch of its own, 3-5 us each and mostly dispatch.
+__global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a, int esz) {
+  constexpr int VEC = 8;         // elements per 16-byte chunk
+  constexpr int CPR = 64 / VEC;  // chunks per tile row
+  constexpr int PITCH = 66;      // elements; keeps rows 4-byte aligned and the gather conflict-free
+  __shared__ __attribute__((aligned(16))) uint16_t tile[64 * PITCH];
   if (a.hdr && blockIdx.x == 0 && threadIdx.x == 0) clear_header(a.hdr);
   int b = blockIdx.x;
   if (b < a.count.blocks) {
@@ -529,54 +527,43 @@ __global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a) {
     __syncthreads();
     const int64_t t1 = min(a.count.n, (int64_t)(b + 1) * a.count.per_block);
     for (int64_t i = (int64_t)b * a.count.per_block + threadIdx.x; i < t1; i += 256)
-      atomicAdd(&h[bucket_of(a.count.k[i], a.count.d, sizeof(T))], 1);
+      atomicAdd(&h[bucket_of(a.count.k[i], a.count.d, esz)], 1);
     __syncthreads();
     for (int i = threadIdx.x; i < a.count.nbuckets; i += 256) a.count.hist[(int64_t)b * a.count.nbuckets + i] = h[i];
     return;
   }
+  if (a.njobs == 0) return;
   b -= a.count.blocks;
-  int jb = 0;
-  while (jb + 1 < a.njobs && b >= a.job[jb].tiles) b -= a.job[jb++].tiles;
-  if (jb >= a.njobs || b >= a.job[jb].tiles) return;
-  const KvCopy& c = a.job[jb];
-  const T* const in = static_cast<const T*>(c.in);
-  T* const out = static_cast<T*>(c.out);
-  const int row_tiles = (int)(c.rows_p / 64);
-  const int64_t r0 = (int64_t)(b % row_tiles) * 64;
-  const int c0 = b / row_tiles * 64;
+  const int row_tiles = a.job[0].d / 64, tiles = row_tiles * row_tiles;   // the jobs' matrices are of one size
+  const KvCopy& c = a.job[b < tiles ? 0 : 1];
+  if (b >= tiles) b -= tiles;
+  const int d = c.d;
+  const uint16_t* const in = static_cast<const uint16_t*>(c.in);
+  uint16_t* const out = static_cast<uint16_t*>(c.out);
+  const int r0 = b % row_tiles * 64, c0 = b / row_tiles * 64;
 #pragma unroll
   for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
     const int id = pass * 256 + threadIdx.x;
     const int rr = id / CPR, cc = id % CPR;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r0 + rr < c.rows && c0 < c.cols) v = *reinterpret_cast<const uint4*>(in + (r0 + rr) * c.ld_in + c0 + cc * VEC);
-    if (c.form == KvCopy::kPlain) {
-      *reinterpret_cast<uint4*>(out + (r0 + rr) * c.ld_out + c0 + cc * VEC) = v;
-    } else {
-      uint32_t* const dst = reinterpret_cast<uint32_t*>(tile + rr * PITCH + cc * VEC);
-      dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-    }
+    const uint4 v = *reinterpret_cast<const uint4*>(in + (int64_t)(r0 + rr) * d + c0 + cc * VEC);
+    uint32_t* const dst = reinterpret_cast<uint32_t*>(tile + rr * PITCH + cc * VEC);
+    dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
   }
-  if (c.form == KvCopy::kPlain) return;
   __syncthreads();
 #pragma unroll
   for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
     const int id = pass * 256 + threadIdx.x;
     const int col = id / CPR, rc = id % CPR;
-    T e[VEC];
+    uint16_t e[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) e[i] = tile[(rc * VEC + i) * PITCH + col];
     uint4 v;
     __builtin_memcpy(&v, e, 16);
-    if (c.form == KvCopy::kTransposed) {
-      *reinterpret_cast<uint4*>(out + (int64_t)(c0 + col) * c.ld_out + r0 + rc * VEC) = v;
-    } else {
-      const int d = c.cols, k = (int)r0 + rc * VEC;
-      const int pos = c.form == KvCopy::kFragmentsFlipped ? d - 1 - (c0 + col) : c0 + col;
-      const int w = pos / (d / 4), q = pos % (d / 4) / (d / 16), i = pos % (d / 16) / 4;
-      const int lane = k / 8 % 4 * 16 + 4 * q + pos % 4;
-      *reinterpret_cast<uint4*>(out + (((int64_t)w * (d / 32) + k / 32) * (d / 64) + i) * 512 + lane * 8) = v;
-    }
+    const int k = r0 + rc * VEC;
+    const int pos = c.flipped ? d - 1 - (c0 + col) : c0 + col;
+    const int w = pos / (d / 4), q = pos % (d / 4) / (d / 16), i = pos % (d / 16) / 4;
+    const int lane = k / 8 % 4 * 16 + 4 * q + pos % 4;
+    *reinterpret_cast<uint4*>(out + (((int64_t)w * (d / 32) + k / 32) * (d / 64) + i) * 512 + lane * 8) = v;
   }
 }
 
@@ -996,18 +983,9 @@ hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, in
   return hipGetLastError();
 }
 
-hipError_t launch_kv_prepare(int dtype, const KvPrepareArgs& a, hipStream_t s) {
-  KvPrepareArgs b = a;
-  int64_t blocks = b.count.blocks;
-  for (int j = 0; j < b.njobs; ++j) {
-    b.job[j].tiles = (int)(b.job[j].rows_p / 64 * (b.job[j].cols_p / 64));
-    blocks += b.job[j].tiles;
-  }
-  const dim3 grid((unsigned)(blocks > 0 ? blocks : 1));
-  if (dtype == LMHEAD_BF16)
-    hipLaunchKernelGGL(kv_prepare_kernel<uint16_t>, grid, dim3(256), 0, s, b);
-  else
-    hipLaunchKernelGGL(kv_prepare_kernel<uint32_t>, grid, dim3(256), 0, s, b);
+hipError_t launch_kv_prepare(int esz, const KvPrepareArgs& a, hipStream_t s) {
+  const int64_t blocks = a.count.blocks + (a.njobs > 0 ? (int64_t)a.njobs * (a.job[0].d / 64) * (a.job[0].d / 64) : 0);
+  hipLaunchKernelGGL(kv_prepare_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, esz);
   return hipGetLastError();
 }
 

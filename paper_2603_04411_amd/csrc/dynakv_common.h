@@ -20,9 +20,8 @@ struct KvLayout {
   int64_t n, d;
   int64_t ncap;      // n rounded up to the tile
   int64_t dp;        // d rounded up to the tile
-  int64_t ldT;       // pitch (elements) of the transposed parameter copies: d + one 128-byte line
   int nbuckets;      // K-steps a token can need, plus one: d * esz / 128 + 1
-  size_t hdr, UT, WT, UiT, logits, order, pos_off, pos_len, hist, blocksum, red, total;
+  size_t hdr, Ufrag, Wfrag, logits, order, pos_off, pos_len, hist, blocksum, red, total;
 };
 
 static inline KvLayout make_kv_layout(const dynakv_desc* d) {
@@ -32,7 +31,6 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
   L.d = d->d;
   L.ncap = (int64_t)round_up((size_t)L.n, kTile);
   L.dp = (int64_t)round_up((size_t)L.d, kTile);
-  L.ldT = L.d + 128 / L.esz;
   L.nbuckets = (int)(L.d * L.esz / 128) + 1;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -41,9 +39,8 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
     return o;
   };
   L.hdr = take(sizeof(WsHeader));
-  L.UT = take((size_t)L.dp * L.ldT * L.esz);   // K-contiguous copies; bf16: the one-kernel gate's fragments
-  L.WT = take((size_t)L.dp * L.ldT * L.esz);
-  L.UiT = take(k_major(L.esz == 4) ? 0 : (size_t)L.dp * L.ldT * L.esz);
+  L.Ufrag = take((size_t)L.d * L.d * L.esz);   // for the one-kernel gate
+  L.Wfrag = take((size_t)L.d * L.d * L.esz);
   L.logits = take((size_t)L.ncap * L.d * 4);
   L.order = take((size_t)L.ncap * 4);
   L.pos_off = take((size_t)L.ncap * 4);
@@ -56,22 +53,18 @@ static inline KvLayout make_kv_layout(const dynakv_desc* d) {
 }
 
 // Workspace of the gate's backward pass (dynakv_gate_bwd).  The two token-major gradients g_l and
-// g_xt are kept in the storage type.  fp32 only: Wp, Up, WT the parameter copies, T1 / T2 the token-contiguous (transposed) operand
-// copies of one parameter-gradient contraction at a time.
+// g_xt are kept in the storage type.
 struct KvBwdLayout {
   int esz;
-  int64_t n, d, ncap, dp, ldT;
-  int64_t ldK;       // pitch (elements) of the token-contiguous copies: ncap + one 128-byte line
+  int64_t n, d, ncap, dp;
   int edge, ksplit;  // tile edge of dW / dU and slices of their contraction over the tokens
   int nblk;          // workgroups of the mask backward kernel = rows of the db partial sums
-  bool pair;         // dW and dU in one launch: four operand copies at a time
-  size_t hdr, Wp, Up, WT, logits, gl, gxt, T1, T2, T3, T4, part, dbpart, total;
+  size_t hdr, logits, gl, gxt, part, dbpart, total;
 };
 
 // Workgroups of the mask backward kernel: four 256-thread workgroups fit a compute unit (128 VGPRs),
 // so 1024 is one resident round on 256 compute units; each wavefront loops over its share of tokens.
 constexpr int kKvBwdMaxBlocks = 1024;
-constexpr int64_t kKvPairBytes = 32 << 20;
 
 static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   KvBwdLayout L{};
@@ -80,8 +73,6 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.d = d->d;
   L.ncap = (int64_t)round_up((size_t)L.n, kTile);
   L.dp = (int64_t)round_up((size_t)L.d, kTile);
-  L.ldT = L.d + 128 / L.esz;
-  L.ldK = L.ncap + 128 / L.esz;
   // Tile edge and slices of the contraction over the tokens: as many slices as give one workgroup per compute unit,
   // on the largest edge whose slices then keep 16 K-steps (of 128 bytes), else edge 64 with at least 2 each.
   // dW alone / whole backward call, us, bf16 unless said, with the choice in brackets:
@@ -116,35 +107,12 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
     return o;
   };
   L.hdr = take(sizeof(WsHeader));
-  const bool copies = !k_major(L.esz == 4);
-  L.Wp = take(copies ? (size_t)L.dp * L.ldT * L.esz : 0);
-  L.Up = take(copies ? (size_t)L.dp * L.ldT * L.esz : 0);
-  L.WT = take(copies ? (size_t)L.dp * L.ldT * L.esz : 0);
   L.logits = take((size_t)L.ncap * L.d * 4);
   L.gl = take((size_t)L.ncap * L.d * L.esz);
   L.gxt = take((size_t)L.ncap * L.d * L.esz);
-  L.T1 = take(copies ? (size_t)L.dp * L.ldK * L.esz : 0);
-  L.T2 = take(copies ? (size_t)L.dp * L.ldK * L.esz : 0);
-  // Up to kKvPairBytes a copy the launches weigh more than the memory: one preparation, one product and one sum serve both
-  // parameter gradients (4096 x 1024: 57 us of kernels before, 42 now; 300 x 128 fp32: 24 and 16).
-  // bf16 has no copies, and always pairs.
-  L.pair = !copies || L.dp * L.ldK * L.esz <= kKvPairBytes;
-  L.T3 = take(copies && L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
-  L.T4 = take(copies && L.pair ? (size_t)L.dp * L.ldK * L.esz : 0);
-  L.part = take((size_t)(L.pair ? 2 : 1) * L.ksplit * L.d * L.d * 4);
+  L.part = take((size_t)2 * L.ksplit * L.d * L.d * 4);   // the slices of both gradients
   L.dbpart = take((size_t)L.nblk * L.d * 4);
   L.total = off;
-  if (!L.pair) {
-    // A workspace sized for a long stream serves every shorter one: also the longest that still pairs, which may need more
-    // (bf16, d = 2048: 7680 tokens 1.42 times as much as 7936).
-    const int64_t ncap = (kKvPairBytes / (L.dp * L.esz) - 128 / L.esz) / kTile * kTile;
-    if (ncap > 0 && ncap < L.ncap) {
-      dynakv_desc shorter = *d;
-      shorter.n = (int32_t)ncap;
-      const size_t most = make_kv_bwd_layout(&shorter).total;
-      if (L.total < most) L.total = most;
-    }
-  }
   return L;
 }
 
@@ -152,13 +120,14 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
 //   out[row(n)][m] = sum_k A[m][k] * Bop[n][k],  m < M, n < Nn.
 // mode 0/1: Bop rows are dense rows of B (pitch ldB), row(n) = n.  The output is the storage type
 //           (out_e) or fp32 (out_f), whichever is non-null.
-// mode 3:   as mode 0, with A always [M x K].  (bf16: A of modes 0 to 2 is the parameter matrix as the caller has it, [K x M].)
+// mode 3:   as mode 0 for the transposed parameter matrix.
+// A is the parameter matrix as the caller has it: [K x M], mode 3: [M x K].
 // mode 2:   ragged rows: Bop[n] = the pos_len[n] bytes of the packed store at byte offset pos_off[n],
 //           zero beyond; row(n) = order[n] (< 0: no token); the tile's step count follows its
 //           first row, the longest (the three arrays are written by launch_kv_order).
 struct KvGemmArgs {
   int mode;
-  const void* A;        // parameter matrix, pitch ldA: [M x K], or [K x M] for bf16 in modes 0 to 2
+  const void* A;        // pitch ldA
   int64_t bytesA;       // readable at A; what lies beyond counts as zeros
   int64_t ldA;
   const void* B;        // dense rows (mode 0/1) or the packed store (mode 2)
@@ -197,7 +166,7 @@ bool kv_few_fits(int64_t n, int d);
 hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s);
 
 // The whole gate of many tokens in one kernel (dynakv_gate.hip), for callers that want x~ and k only.  Ufrag, Wfrag: the
-// parameter matrices in fragment order (KvCopy::kFragments, W's with the same `literal`).
+// parameter matrices in fragment order (KvCopy, W's flipped when `literal`).
 struct KvGateArgs {
   const void* x;
   int64_t ldx;
@@ -245,30 +214,23 @@ static inline KvCount make_kv_count(const int32_t* k, int64_t n, int d, int nbuc
   return {k, n, d, nbuckets, (int)((n + per - 1) / per), (int)per, hist};
 }
 
-// One operand copy.  kPlain: out[r][c] = in[r][c]; kTransposed: out[c][r] = in[r][c], for r < rows, c < cols; zero up to
-// rows_p x cols_p (of the source's orientation).  Rows of both sides 16-byte aligned; cols, cols_p, rows_p multiples
-// of 64.  kFragments (bf16, d x d, d a multiple of 64): the MFMA fragments in the order in which kv_gate_kernel's
+// A parameter matrix (bf16, d x d, d a multiple of 64) as the MFMA fragments in the order in which kv_gate_kernel's
 // wavefronts consume them, ((w * d/32 + s) * d/64 + i) KB + 16 lane bytes holding in[k][c] for the 8 values
 // k = 32 s + 8 (lane / 16) + [0, 8) and column c = position d/4 w + d/16 ((lane % 16) / 4) + 4 i + lane % 4
-// (kFragmentsFlipped: c = d - 1 - position).
+// (flipped: c = d - 1 - position).
 struct KvCopy {
-  enum Form { kPlain, kTransposed, kFragments, kFragmentsFlipped };
   const void* in;
-  int64_t ld_in, rows, rows_p;
-  int cols, cols_p;
+  int d;
   void* out;
-  int64_t ld_out;
-  Form form;
-  int tiles;           // set by the launcher
+  bool flipped;
 };
-constexpr int kKvMaxCopies = 4;
 struct KvPrepareArgs {
   WsHeader* hdr;       // cleared unless null
-  KvCopy job[kKvMaxCopies];
+  KvCopy job[2];
   int njobs;
   KvCount count;       // blocks = 0: nothing to count
 };
-hipError_t launch_kv_prepare(int dtype, const KvPrepareArgs& a, hipStream_t s);
+hipError_t launch_kv_prepare(int esz, const KvPrepareArgs& a, hipStream_t s);
 
 // order = tokens sorted by descending number of K-steps, padded with -1 up to ncap; pos_off / pos_len = byte offset and
 // byte length (k rounded up to the granule) of each sorted position's segment in a store of `bytes` readable bytes

@@ -5,8 +5,8 @@
 //   mode 3  the two token-major products of the gate's backward pass (M^T in place of M), optionally added to what
 //           the output holds
 // All are  out[row(n)][m] = sum_k A[m][k] Bop[n][k]  with the parameter matrix on the MFMA M axis and tokens on N, as in the
-// LM-head kernels.  bf16 takes the matrix as the caller has it (K-major in modes 0 to 2), fp32 a K-contiguous copy: the launch that
-// made the copies was 4.5 us (gate of 4096 x 1024 42.2 -> 37.6 us, with the gradients' copies the training pair 166 -> 148).  The
+// LM-head kernels.  It is taken as the caller has it, K-major in modes 0 to 2: the launch that made transposed copies was
+// 4.5 us (bf16 gate of 4096 x 1024 42.2 -> 37.6 us, with the gradients' copies the training pair 166 -> 148).  The
 // parameter matrix (2 MB at d = 1024) stays in every XCD's L2; the token rows stream through once
 // per XCD because an XCD runs all M tiles of a token tile together (tile_map.h).
 //
@@ -57,13 +57,13 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
 template <typename E, int Edge, int Mode>
 using KvTile = GemmTile<E, Edge, Edge, 2, 2, /*kLeadB=*/true, /*kMaskB=*/Mode == 2,
-                        /*kTransA=*/k_major(Elem<E>::size == 4) && Mode != 3>;
+                        /*kTransA=*/Mode != 3>;
 
 // One output tile; `wg` is the tile's position in the XCD-aware walk.
 template <typename E, int Edge, int Mode>
 __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
   using G = KvTile<E, Edge, Mode>;
-  constexpr bool kTA = k_major(Elem<E>::size == 4) && Mode != 3;
+  constexpr bool kTA = Mode != 3;
   constexpr int ESZ = Elem<E>::size;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
   const int ntiles = (int)((a.Nn + G::BN - 1) / G::BN);
@@ -376,7 +376,7 @@ hipError_t launch_e(const KvGemmArgs& a, hipStream_t s) {
     case 0: return launch_mode<E, 0>(a, s);
     case 1: return launch_mode<E, 1>(a, s);
     case 2: return launch_mode<E, 2>(a, s);
-    default: return launch_mode<E, k_major(Elem<E>::size == 4) ? 3 : 0>(a, s);   // fp32: A is [M x K] in mode 0 too
+    default: return launch_mode<E, 3>(a, s);
   }
 }
 

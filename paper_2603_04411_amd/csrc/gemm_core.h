@@ -43,15 +43,17 @@
 // barrier is skewed so that the MFMAs after it overlap the first fragment reads of the next K-step and the
 // issue of the next loads.
 //
-// K-major operands (kTransA / kTransB, bf16 only): the operand's rows in memory run along M (or N) and K counts rows, as W
-// does for dH and the hidden states for dW.  A K-step is then 64 rows of BM values, and the fragments are read out of LDS
-// with ds_read_b64_tr_b16, which hands a 4 x 16 block (K x M) to sixteen lanes transposed: a lane supplies the address of 4
-// consecutive values of one row and receives 4 values of K of one column; two of them make a fragment.  No transposed copy of the
-// operand is needed, and the reads run at the rate of the plain ones (156 B/clk and compute unit against 123 for
-// 128-bit reads; without the swizzle 32).
+// K-major operands (kTransA / kTransB; bf16 and fp32): the operand's rows in memory run along M (or N) and K counts rows, as
+// W does for dH and the hidden states for dW.  A K-step is then 64 (fp32: 32) rows of BM values, and the fragments are read out
+// of LDS transposed, so that no transposed copy of the operand is needed.
+//   bf16: ds_read_b64_tr_b16 hands a 4 x 16 block (K x M) to sixteen lanes transposed: a lane supplies the address of 4
+//   consecutive values of one row and receives 4 values of K of one column; two of them make a fragment.  They run at the rate of
+//   the plain reads (156 B/clk and compute unit against 123 for 128-bit ones; without the swizzle 32).
 //   LDS slot: the 64 rows as they lie, cut into 32-byte units; unit u of row k sits at unit u ^ swzT(k) of its row.  The
-//   rows are put into the slot's 1 KB groups in an order (krow_of) that keeps whatever depends on the sub-step and on the
+//   rows are put into the slot's 1 KB groups in an order (krow_at) that keeps whatever depends on the sub-step and on the
 //   half of a fragment in the last bits of the group index, so that it fits the DS instructions' immediate offset.
+//   fp32: an MFMA takes one value of K per lane, so four 32-bit reads, each of 32 consecutive values of a row, make a fragment;
+//   rows lie one behind the other.  The matrix rate is a sixteenth of bf16's: the reads do not show.
 //
 // Accumulator layout of a block (NB * NB / 64 floats per lane); a lane owns one column n = l % NB:
 //   NB = 32: element v of lane l  <->  m = 8*(v/4) + 4*(l/32) + v%4   (16 values)
@@ -107,6 +109,9 @@ struct fp8_tag {};   // OCP e4m3 operands (logits only), fp32 accumulation
 
 template <typename E>
 struct Elem;
+#ifndef LMHEAD_BF16_BLOCK
+#define LMHEAD_BF16_BLOCK 16
+#endif
 template <>
 struct Elem<bf16_tag> {
   static constexpr int size = 2;
@@ -220,8 +225,8 @@ struct GemmTile {
   static_assert(BM % (WGM * NB) == 0 && BN % (WGN * NB) == 0, "wave tiles are made of MFMA blocks");
   static_assert(NB == 32 || NB == 16, "block edge");
   static_assert(BM % (8 * NWAVES) == 0 && BN % (8 * NWAVES) == 0, "tile loads divide evenly");
-  static_assert(!(kTransA || kTransB) || (NB == 16 && Elem<E>::size == 2 && BM == BN && WGM == 2 && WGN == 2),
-                "K-major operands: bf16 on 16x16 blocks, four wavefronts");
+  static_assert(!(kTransA || kTransB) || (Elem<E>::size >= 2 && BM == BN && WGM == 2 && WGN == 2),
+                "K-major operands: bf16 or fp32, four wavefronts");
   static_assert(!(kTransB && kMaskB), "ragged rows are K-contiguous");
   static_assert(NSUB == 1 || NSUB % 2 == 0, "fragment double-buffering assumes an even number of sub-steps");
 
@@ -251,24 +256,35 @@ struct GemmTile {
   __device__ static inline int ld_byte(int row) { return ((lane() & 7) ^ swz(row)) << 4; }
 
   // K-major operand: values of K per K-step, bytes of a K row of the tile, K rows per 1 KB group.
-  static constexpr int KROWS = 64;
-  static constexpr int TROW = BM * 2;
+  static constexpr int KROWS = KB / Elem<E>::size;
+  static constexpr int TROW = BM * Elem<E>::size;
   static constexpr int TRPG = 1024 / TROW;
+  static constexpr uint32_t kWindow = 0x7fffffffu;   // most bytes that a buffer descriptor covers
   __device__ static inline int swzT(int k) {
     return BM == 64 ? ((k >> 1) & 1) | ((k >> 2) & 2) : (k & 3) | ((k >> 1) & 4);
   }
   // K row (of the K-step) that this lane fetches in the wave's q-th load, and the byte inside the tile's part of that row.
-  // With k = 32 sub + 8 g + 4 h + r, group index = (lane-dependent: g, and r / 2 at edge 256) then (sub, h); edge 64 has
+  // bf16: with k = 32 sub + 8 g + 4 h + r, group index = (lane-dependent: g, and r / 2 at edge 256) then (sub, h); edge 64 has
   // h in the row of the group.
   __device__ static inline int ldT_row(int q) {
     const int gi = wave() * A_LD + q, in = lane() / (TROW / 16);
+    if constexpr (Elem<E>::size == 4) return gi * TRPG + in;
     if constexpr (BM == 256) return 32 * ((gi >> 1) & 1) + 8 * (gi >> 3) + 4 * (gi & 1) + 2 * ((gi >> 2) & 1) + in;
     if constexpr (BM == 128) return 32 * ((gi >> 1) & 1) + 8 * (gi >> 2) + 4 * (gi & 1) + in;
     return 32 * (gi & 1) + 8 * (gi >> 1) + in;
   }
   __device__ static inline int ldT_byte(int krow) {
     const int p = lane() % (TROW / 16);
+    if constexpr (Elem<E>::size == 4) return p << 4;
     return (((p >> 1) ^ swzT(krow)) << 5) | ((p & 1) << 4);
+  }
+
+  // LDS byte (in its slot) of K row k.  Additive over the bit fields of k that ldT_row tells apart (fp32: over multiples of 4).
+  __device__ static constexpr int krow_at(int k) {
+    return Elem<E>::size == 4 ? k / TRPG * GSTR + k % TRPG * TROW
+           : BM == 256 ? ((((k >> 3) & 3) * 2 + ((k >> 1) & 1)) * 4 + 2 * (k >> 5) + ((k >> 2) & 1)) * GSTR + (k & 1) * TROW
+           : BM == 128 ? (((k >> 3) & 3) * 4 + 2 * (k >> 5) + ((k >> 2) & 1)) * GSTR + (k & 3) * TROW
+                       : (((k >> 3) & 3) * 2 + (k >> 5)) * GSTR + (k & 7) * TROW;
   }
 
   __device__ static inline void zero(Acc& acc) {
@@ -408,25 +424,29 @@ struct GemmTile {
     };
 
     u32x4_t fa[2][TM][FC], fb[2][TN][FC];
-    // half h of a fragment of a K-major operand: sub-step s, unit (block column of 16 values) u of the tile
+    // Part p (of TPARTS) of a fragment of a K-major operand: sub-step s, block b (of NB values along M or N) of the tile.
+    // bf16: four values of K (half a fragment) by a transposing read; fp32: one value.
+    constexpr int TPARTS = Elem<E>::size == 4 ? 4 : 2;
     [[maybe_unused]] const int tr = (l & 15) >> 2;
-    [[maybe_unused]] const int tbase = BM == 256   ? (grp * 2 + (tr >> 1)) * 4 * GSTR + (tr & 1) * TROW
-                                       : BM == 128 ? grp * 4 * GSTR + tr * TROW
-                                                   : grp * 2 * GSTR + tr * TROW;
-    [[maybe_unused]] const int tf = swzT(8 * grp + tr);
-    auto read_t = [&](const char* st, int s, int u, int h) {
-      typedef __attribute__((address_space(3))) i16x4_t* tptr_t;
-      const int at = tbase + ((u ^ tf) << 5) + (l & 3) * 8 + (BM == 64 ? s * GSTR + h * 4 * TROW : (2 * s + h) * GSTR);
-      return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr_t)(st + at)));
-    };
-    auto half = [](u32x4_t& f, int h, u32x2_t v) {
-      if (h == 0) { f.x = v.x; f.y = v.y; } else { f.z = v.x; f.w = v.y; }
+    [[maybe_unused]] const int tk = Elem<E>::size == 4 ? 4 * grp : 8 * grp + tr;   // lane's part of k
+    [[maybe_unused]] const int tbase = krow_at(tk) + (Elem<E>::size == 4 ? (l % NB) * 4 : (l & 3) * 8);
+    [[maybe_unused]] const int tu = NB == 32 ? (l >> 4) & 1 : 0;                      // 16-value half of a 32-value block
+    [[maybe_unused]] const int tf = swzT(tk);
+    auto read_t = [&](u32x4_t& f, const char* st, int s, int b, int p) {
+      if constexpr (Elem<E>::size == 4) {
+        f[p] = *reinterpret_cast<const uint32_t*>(st + tbase + krow_at(8 * s) + krow_at(p) + b * NB * 4);
+      } else {
+        typedef __attribute__((address_space(3))) i16x4_t* tptr_t;
+        const int at = tbase + krow_at((NB == 32 ? 16 : 32) * s) + krow_at(4 * p) + (((b * (NB / 16) + tu) ^ tf) << 5);
+        const u32x2_t v = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr_t)(st + at)));
+        if (p == 0) { f.x = v.x; f.y = v.y; } else { f.z = v.x; f.w = v.y; }
+      }
     };
     const int uA0 = wave_m() * TM, uB0 = wave_n() * TN;
     auto read_a = [&](const char* sa, int s, int buf) {
       if constexpr (kTransA) {
 #pragma unroll
-        for (int i = 0; i < 2 * TM; ++i) half(fa[buf][i / 2][0], i % 2, read_t(sa, s, uA0 + i / 2, i % 2));
+        for (int i = 0; i < TPARTS * TM; ++i) read_t(fa[buf][i / TPARTS][0], sa, s, uA0 + i / TPARTS, i % TPARTS);
         return;
       }
 #pragma unroll
@@ -442,7 +462,7 @@ struct GemmTile {
     auto read_b = [&](const char* sb, int s, int buf) {
       if constexpr (kTransB) {
 #pragma unroll
-        for (int j = 0; j < 2 * TN; ++j) half(fb[buf][j / 2][0], j % 2, read_t(sb, s, uB0 + j / 2, j % 2));
+        for (int j = 0; j < TPARTS * TN; ++j) read_t(fb[buf][j / TPARTS][0], sb, s, uB0 + j / TPARTS, j % TPARTS);
         return;
       }
 #pragma unroll
@@ -472,7 +492,9 @@ struct GemmTile {
     // (MMAS / loads)-th MFMA one global->LDS load, so that nothing leaves the matrix pipe idle.
     constexpr int kDsRead = 0x100, kVmem = 0x010, kMfma = 0x008;
     constexpr int MMAS = TM * TN * Elem<E>::mfma_per_block;
-    constexpr int FR = TM + TN;
+    // fragment reads of a region (a K-major operand's are several, as many as there are MFMAs to put them behind)
+    constexpr int FR_ALL = TM * (kTransA ? TPARTS : 1) + TN * (kTransB ? TPARTS : 1);
+    constexpr int FR = FR_ALL < 2 * MMAS ? FR_ALL : 2 * MMAS;
     constexpr int LD_REGION = A_LD / NPART;     // loads per region (A_LD == B_LD is not required
     constexpr int LD_REGION_B = B_LD / NPART;   // but both are spread the same way)
     constexpr int RD_SLOTS = (FR + 1) / 2;
@@ -610,7 +632,7 @@ struct GemmTile {
       auto region_reads = [](bool trans) { return trans ? 2 * TM : TM; };
       auto read_a1 = [&](const char* sa, int sub, int buf, int i) {
         if constexpr (kTransA) {
-          half(fa[buf][i / 2][0], i % 2, read_t(sa, sub, uA0 + i / 2, i % 2));
+          read_t(fa[buf][i / 2][0], sa, sub, uA0 + i / 2, i % 2);
           return;
         }
         const int r = rA0 + i * NB;
@@ -618,7 +640,7 @@ struct GemmTile {
       };
       auto read_b1 = [&](const char* sb, int sub, int buf, int j) {
         if constexpr (kTransB) {
-          half(fb[buf][j / 2][0], j % 2, read_t(sb, sub, uB0 + j / 2, j % 2));
+          read_t(fb[buf][j / 2][0], sb, sub, uB0 + j / 2, j % 2);
           return;
         }
         const int r = rB0 + j * NB;

@@ -34,11 +34,11 @@ int validate(const lmhead_desc* d) {
   if ((d->ldH * esz) % 16 != 0 || (d->ldW * esz) % 16 != 0) return LMHEAD_E_ALIGN;
   // The matrix-core kernels address an operand tile through one buffer descriptor with 32-bit byte
   // offsets inside a 2 GiB window: the last row of a 256-row tile plus the contraction's extent must
-  // stay below 2^31.  The widest rows are the token-major operand copies of the backward (N slots wide).
+  // stay below 2^31.  (N and V are held to that too, although no operand has rows of N values any more: the documented limits.)
   {
     const WsLayout L = make_layout(d, kMaxPolicies);
     int64_t pitch = d->ldW;
-    for (int64_t p : {L.ldHc, L.ldHcT, L.ldWT, L.ldZ, L.ldZT}) pitch = p > pitch ? p : pitch;
+    for (int64_t p : {L.ldHc, L.Ncap + 128 / esz, L.Vp + 128 / esz, L.ldZ}) pitch = p > pitch ? p : pitch;
     if ((int64_t)kTile * pitch * esz >= (1ll << 31)) return LMHEAD_E_SHAPE;
     // 1-D launch grids (tiles of the largest kernel, rounded up by the tile walk) must fit HIP's limit
     const int64_t tok_tiles = L.Ncap / kTile + 8 * 16, voc_tiles = L.Vp / kTile, d_tiles = L.dp / kTile;
@@ -246,35 +246,16 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
   ia.lse = lse;
   ia.want_split = 1;
   ia.split = L.dh;
+  ia.dH = static_cast<char*>(dH);
+  ia.dh_bytes = (int64_t)desc->d * (dh16 ? 2 : 4);
   LM_TRY(launch_index(ia, s));
-  // K-contiguous copies of the two operands that the backward contracts along their rows.  With 8-bit logits the
-  // recompute must see the logits the forward saw: the same 8-bit copies, W's from the same pass over it.
-  OperandArgs oa{};
-  oa.hdr = hdr;
-  oa.len = len;
-  oa.tok = tok;
-  oa.N = L.N;
-  oa.T = desc->T;
-  oa.V = desc->V;
-  oa.dH = static_cast<char*>(dH);
-  oa.dh_bytes = (int64_t)desc->d * (dh16 ? 2 : 4);
-  const bool kmajor = k_major(dt == LMHEAD_F32);   // operands as they lie
-  if (!kmajor) {
-    oa.job[0] = {w.at<void>(L.Hc), L.ldHc, L.Ncap, L.Ncap, desc->d, (int)L.dp, true, w.at<void>(L.HcT), L.ldHcT};
-    oa.job[1] = {W, desc->ldW, desc->V, L.Vp, desc->d, (int)L.dp, false, w.at<void>(L.WT), L.ldWT};
-    if (fp8) {
-      oa.job[1].e4m3 = w.at<uint8_t>(L.W8);
-      oa.job[1].ld_e4m3 = L.ld8;
-      oa.job[1].scale = ldexpf(1.0f, desc->fp8_exp_w);
-    }
-  }
-  LM_TRY(launch_operands(dt, oa, s));
-  if (fp8 && kmajor)
+  // With 8-bit logits the recompute must see the logits the forward saw: the same 8-bit copies.
+  if (fp8) {
     LM_TRY(launch_quantize_e4m3(dt, W, desc->ldW, desc->V, false, hdr, desc->d, desc->fp8_exp_w, w.at<void>(L.W8), L.ld8,
                                 L.Vp, s));
-  if (fp8)
     LM_TRY(launch_quantize_e4m3(dt, w.at<void>(L.Hc), L.ldHc, 0, true, hdr, desc->d, desc->fp8_exp_h,
                                 w.at<void>(L.Hc8), L.ld8, L.Ncap, s));
+  }
 
   const int edge_w = dw_edge(dt == LMHEAD_F32, desc->d, L.Vc < desc->V ? L.Vc : desc->V, L.N);
   const int total_tiles = (int)(L.Vp / kTile);
@@ -293,7 +274,6 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     za.V = desc->V;
     za.Ncap = L.Ncap;
     za.ldZ = L.ldZ;
-    za.ldZT = L.ldZT;
     za.c0 = c0;
     za.edge = L.edge;
     za.ntiles = ntiles;
@@ -302,22 +282,16 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     za.lse_c = w.at<float>(L.lse_c);
     za.hdr = hdr;
     za.dZ = w.at<void>(L.dZ);
-    za.dZT = w.at<void>(L.dZT);
     {
       TimedLaunch tl(1, s);
       LM_TRY(launch_dz(fp8 ? kDtypeFp8 : dt, dt, za, s));
     }
 
-    // dH[slot(n)][m] (+)= sum_v W^T[m][c0 + v] dZ[n][v]
+    // dH[slot(n)][m] (+)= sum_v W[c0 + v][m] dZ[n][v]
     GemmTArgs ha{};
-    if (kmajor) {
-      ha.A = static_cast<const char*>(W) + (int64_t)c0 * desc->ldW * 2;
-      ha.ldA = desc->ldW;
-      ha.a_bytes = ((int64_t)(desc->V - c0 - 1) * desc->ldW + desc->d) * 2;
-    } else {
-      ha.A = w.at<char>(L.WT) + (size_t)c0 * L.esz;
-      ha.ldA = L.ldWT;
-    }
+    ha.A = static_cast<const char*>(W) + (int64_t)c0 * desc->ldW * L.esz;
+    ha.ldA = desc->ldW;
+    ha.a_bytes = ((int64_t)(desc->V - c0 - 1) * desc->ldW + desc->d) * L.esz;
     ha.B = w.at<void>(L.dZ);
     ha.ldB = L.ldZ;
     ha.M = desc->d;
@@ -344,19 +318,12 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
                                     !dh16 && c > 0, dh16, s, 0, L.dh.edge, dh16));
     }
 
-    // dW[c0 + n][m] = sum_i Hc^T[m][i] dZ^T[n][i]
+    // dW[c0 + n][m] = sum_i Hc[i][m] dZ[i][n]
     GemmTArgs wa{};
-    if (kmajor) {
-      wa.A = w.at<void>(L.Hc);
-      wa.ldA = L.ldHc;
-      wa.B = w.at<void>(L.dZ);
-      wa.ldB = L.ldZ;
-    } else {
-      wa.A = w.at<void>(L.HcT);
-      wa.ldA = L.ldHcT;
-      wa.B = w.at<void>(L.dZT);
-      wa.ldB = L.ldZT;
-    }
+    wa.A = w.at<void>(L.Hc);
+    wa.ldA = L.ldHc;
+    wa.B = w.at<void>(L.dZ);
+    wa.ldB = L.ldZ;
     wa.M = desc->d;
     wa.n_limit = (desc->V - c0 < ntiles * kTile) ? desc->V - c0 : ntiles * kTile;
     wa.n_from_nv = false;
@@ -389,8 +356,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
       }
       if (t_rem > 0) {
         GemmTArgs r = wa;
-        const int64_t skip = (int64_t)t_main * kTile * (kmajor ? 1 : L.ldZT) * L.esz;
-        r.B = static_cast<const char*>(wa.B) + skip;
+        r.B = static_cast<const char*>(wa.B) + (int64_t)t_main * kTile * L.esz;
         r.n_limit = wa.n_limit - (int64_t)t_main * kTile;
         r.n_tiles_cap = t_rem;
         r.ksplit = ks;

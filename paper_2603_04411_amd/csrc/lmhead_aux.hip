@@ -1,6 +1,6 @@
 // Bandwidth-bound helper kernels around the MFMA kernels: batch indexing (mask, prefix
-// sums, compaction map), row gather of H, operand transposes, 8-bit operand copies, the merge of
-// the per-tile softmax statistics, the sum of split dH contractions, and zero-filling of padded dH rows.  All accesses are coalesced
+// sums, compaction map), row gather of H and zero-filling of padded dH rows, 8-bit operand copies, the merge of
+// the per-tile softmax statistics, the sum of split dH contractions.  All accesses are coalesced
 // (16-byte vectors where rows allow); none of these kernels is more than a few passes
 // over O(N d + V d) bytes.
 #include <math.h>
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restric
 
 // Everything that the valid slots' positions decide, in one launch: mask, compaction map, and the gather of the
 // valid rows of H (16 bytes per lane and step; zeros from N_v to the next tile multiple) with their token ids,
-// gradients and statistics.  Bound by the copy of H.  kScan: each workgroup scans the lengths itself (up to
+// gradients and statistics; for the backward the rows of dH of padded slots are zeroed.  Bound by the copy of H and the zeros.  kScan: each workgroup scans the lengths itself (up to
 // kIndexMaxR of them, a microsecond), which saves the launch that would have to come first: three
 // launches of 5 us each became one.  The range of the token ids is reported by the kernels that follow
 // (an id outside [0, V) is -1 here): the header is only cleared in this launch.
@@ -121,9 +121,24 @@ __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
       a.mask[i] = (int)(i - (int64_t)r * a.T) < cu[r + 1] - cu[r] ? 1 : 0;
     }
   }
+  typedef __attribute__((ext_vector_type(4))) uint32_t u4;
+  if (a.dH) {
+    constexpr int PER = 16;   // slots per wavefront and turn
+    for (int64_t i0 = ((int64_t)blockIdx.x * 4 + wave) * PER; i0 < N; i0 += (int64_t)gridDim.x * 4 * PER) {
+      const int64_t i = i0 + lane;
+      bool pad = false;
+      if (lane < PER && i < N) {
+        const int r = (int)(i / a.T);
+        pad = (int)(i - (int64_t)r * a.T) >= cu[r + 1] - cu[r];
+      }
+      for (uint64_t left = __ballot(pad); left; left &= left - 1) {
+        u4* const row = reinterpret_cast<u4*>(a.dH + (i0 + __ffsll((unsigned long long)left) - 1) * a.dh_bytes);
+        for (int64_t c = lane; c < a.dh_bytes / 16; c += 64) row[c] = u4{0, 0, 0, 0};
+      }
+    }
+  }
   const int nv = cu[a.R];
   const int64_t nvp = ((int64_t)nv + kTile - 1) / kTile * kTile;
-  typedef __attribute__((ext_vector_type(4))) uint32_t u4;
   const int nvec = a.row_bytes / 16;
   for (int64_t k0 = ((int64_t)blockIdx.x * 4 + wave) * kIndexRows; k0 < nvp; k0 += (int64_t)gridDim.x * 4 * kIndexRows) {
     // slot of row k0 + lane: the last response that starts at or before it (empty ones share their start with the next)
@@ -169,36 +184,6 @@ __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
 }
 static_assert(kTile % kIndexRows == 0, "a wavefront's rows stay inside the padded extent");
 
-// ---- transpose -------------------------------------------------------------------------
-
-// out[c][r] = in[r][c] through a 64x64 LDS tile; rows >= `rows` and columns >= `cols` of the
-// source read as zero, so the padded extent of `out` is zero-filled.
-__global__ __launch_bounds__(256) void transpose_kernel(const uint32_t* __restrict__ in, int64_t ld_in,
-                                                        int64_t rows_fixed, int cols, int rows_from_nv,
-                                                        const WsHeader* __restrict__ hdr,
-                                                        uint32_t* __restrict__ out, int64_t ld_out,
-                                                        int64_t rows_p, int64_t cols_p) {
-  __shared__ uint32_t tile[64][65];
-  const int64_t rows = rows_from_nv ? (int64_t)hdr->nv : rows_fixed;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  const int64_t c0 = (int64_t)blockIdx.y * 64;
-  if (rows_from_nv) {
-    // nothing beyond the tile-padded valid extent is ever read by the contractions
-    const int64_t rp = (rows + kTile - 1) / kTile * kTile;
-    if (r0 >= rp) return;
-  }
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int rr = ty; rr < 64; rr += 4) {
-    const int64_t r = r0 + rr, c = c0 + tx;
-    tile[rr][tx] = (r < rows && c < cols) ? in[r * ld_in + c] : 0u;
-  }
-  __syncthreads();
-  for (int cc = ty; cc < 64; cc += 4) {
-    const int64_t c = c0 + cc, r = r0 + tx;
-    if (c < cols_p && r < rows_p) out[c * ld_out + r] = tile[tx][cc];
-  }
-}
-
 // Eight (bf16) or four (fp32) values as e4m3: x * scale, rounded to nearest even.  The hardware conversion turns
 // magnitudes beyond the format's range into NaN, so values are clamped to +-448 (the largest e4m3 number) first.
 template <int N>
@@ -212,95 +197,6 @@ __device__ inline void to_e4m3(const float (&x)[N], float scale, uint32_t (&out)
     p = __builtin_amdgcn_cvt_pk_fp8_f32(v[4 * w], v[4 * w + 1], p, false);
     p = __builtin_amdgcn_cvt_pk_fp8_f32(v[4 * w + 2], v[4 * w + 3], p, true);
     out[w] = (uint32_t)p;
-  }
-}
-
-// The backward's operands in one launch, 64 x 64 tiles with 16-byte global accesses on both sides (the element-wise kernel
-// above moves 4 bytes per lane and runs at about half the rate): HcT, WT and, with 8-bit logits, the
-// e4m3 copy of W, which the same read of W serves (151936 x 4096: 765 us for everything, 846 us in launches of their own); the rows of dH that
-// belong to padding are zeroed and the token ids of valid slots checked.  Rows of the source go to LDS as they
-// are (padded pitch); each thread then gathers the 16 bytes of one output chunk (consecutive r of one column).
-// At memory speed: 4.7 to 5.2 TB/s of reads and writes (tiles of 128 rows: no faster).
-constexpr int kZeroSlots = 64;   // slots per workgroup of the zeroing
-template <typename T, bool kE4m3>
-__global__ __launch_bounds__(256) void operands_kernel(OperandArgs a) {
-  constexpr int VEC = 16 / sizeof(T);         // elements per 16-byte chunk
-  constexpr int CPR = 64 / VEC;               // chunks per tile row
-  constexpr int PITCH = 64 + 4 / sizeof(T);   // elements; keeps rows 4-byte aligned and the gather conflict-free
-  __shared__ __attribute__((aligned(16))) T tile[64 * PITCH];
-  int b = blockIdx.x;
-  if (b < a.zero_blocks) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int PER = kZeroSlots / 4;       // slots per wavefront
-    const int64_t i0 = (int64_t)b * kZeroSlots + wave * PER;
-    const int64_t i = i0 + lane;
-    bool pad = false;
-    if (lane < PER && i < a.N) {
-      const int r = (int)(i / a.T);
-      pad = (int)(i - (int64_t)r * a.T) >= min(max(a.len[r], 0), a.T);
-      if (!pad) {
-        const int tk = a.tok[i];
-        if (tk < 0 || tk >= a.V) atomicOr(&a.hdr->err, kErrTok);
-      }
-    }
-    typedef __attribute__((ext_vector_type(4))) float f4;    // 16 bytes of zeros, whatever the element type
-    const f4 z = {0.f, 0.f, 0.f, 0.f};
-    for (uint64_t left = __ballot(pad); left; left &= left - 1) {
-      f4* const row = reinterpret_cast<f4*>(a.dH + (i0 + __ffsll((unsigned long long)left) - 1) * a.dh_bytes);
-      for (int64_t c = lane; c < a.dh_bytes / 16; c += 64) row[c] = z;
-    }
-    return;
-  }
-  b -= a.zero_blocks;
-  const bool second = b >= a.job[0].tiles;
-  if (second) b -= a.job[0].tiles;
-  const Transpose& t = a.job[second ? 1 : 0];
-  const int64_t rows = t.rows_from_nv ? (int64_t)a.hdr->nv : t.rows;
-  const int row_tiles = (int)(t.rows_p / 64);
-  const int64_t r0 = (int64_t)(b % row_tiles) * 64;
-  const int c0 = b / row_tiles * 64;
-  // nothing beyond the tile-padded valid extent is ever read by the contractions
-  if (t.rows_from_nv && r0 >= (rows + kTile - 1) / kTile * kTile) return;
-  const T* const in = static_cast<const T*>(t.in);
-  T* const out = static_cast<T*>(t.out);
-#pragma unroll
-  for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
-    const int id = pass * 256 + threadIdx.x;
-    const int rr = id / CPR, cc = id % CPR;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r0 + rr < rows && c0 < t.cols) v = *reinterpret_cast<const uint4*>(in + (r0 + rr) * t.ld_in + c0 + cc * VEC);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(tile + rr * PITCH + cc * VEC);
-    dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-    if (kE4m3 && second && c0 < t.cols) {
-      float x[VEC];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        if constexpr (sizeof(T) == 2)
-          x[e] = __builtin_bit_cast(float, (e & 1) ? w[e / 2] & 0xffff0000u : w[e / 2] << 16);
-        else
-          x[e] = __builtin_bit_cast(float, w[e]);
-      }
-      uint32_t q[VEC / 4];
-      to_e4m3(x, t.scale, q);
-      uint32_t* const o8 = reinterpret_cast<uint32_t*>(t.e4m3 + (r0 + rr) * t.ld_e4m3 + c0 + cc * VEC);
-      if constexpr (VEC == 8)
-        *reinterpret_cast<uint2*>(o8) = make_uint2(q[0], q[1]);
-      else
-        *o8 = q[0];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int pass = 0; pass < 64 * CPR / 256; ++pass) {
-    const int id = pass * 256 + threadIdx.x;
-    const int c = id / CPR, rc = id % CPR;
-    T e[VEC];
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) e[i] = tile[(rc * VEC + i) * PITCH + c];
-    uint4 v;
-    __builtin_memcpy(&v, e, 16);
-    *reinterpret_cast<uint4*>(out + (int64_t)(c0 + c) * t.ld_out + r0 + rc * VEC) = v;
   }
 }
 
@@ -524,49 +420,6 @@ hipError_t launch_index(const IndexArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, a.len, a.R, a.T, a.hdr, a.cu_ws, a.cu_out,
                        a.want_split, a.split);
     hipLaunchKernelGGL(index_kernel<false>, grid, dim3(256), 0, s, a);
-  }
-  return hipGetLastError();
-}
-
-// rows that are no multiple of 64 elements: fp32 only, d is a multiple of 64 in bf16
-static hipError_t launch_transpose(const Transpose& t, const WsHeader* hdr, hipStream_t s) {
-  const dim3 grid((unsigned)((t.rows_p + 63) / 64), (unsigned)((t.cols_p + 63) / 64));
-  hipLaunchKernelGGL(transpose_kernel, grid, dim3(256), 0, s, static_cast<const uint32_t*>(t.in), t.ld_in, t.rows, t.cols,
-                     t.rows_from_nv ? 1 : 0, hdr, static_cast<uint32_t*>(t.out), t.ld_out, t.rows_p, t.cols_p);
-  return hipGetLastError();
-}
-
-hipError_t launch_operands(int dtype, const OperandArgs& a, hipStream_t s) {
-  OperandArgs b = a;
-  const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
-  b.zero_blocks = (int)((b.N + kZeroSlots - 1) / kZeroSlots);
-  int64_t blocks = b.zero_blocks;
-  for (Transpose& t : b.job) {
-    if (!t.in) continue;   // bf16: no copies
-    const bool wide = t.cols % 64 == 0 && t.cols_p % 64 == 0 && t.rows_p % 64 == 0 && (t.ld_in * esz) % 16 == 0 &&
-                      (t.ld_out * esz) % 16 == 0 && (reinterpret_cast<uintptr_t>(t.in) & 15u) == 0 &&
-                      (reinterpret_cast<uintptr_t>(t.out) & 15u) == 0;
-    if (!wide && dtype != LMHEAD_F32) return hipErrorInvalidValue;
-    t.tiles = wide ? (int)(t.rows_p / 64 * (t.cols_p / 64)) : 0;
-    if (!wide) {
-      // (d is a multiple of 128 wherever an e4m3 copy is wanted: the wide kernel makes it)
-      const hipError_t e = launch_transpose(t, b.hdr, s);
-      if (e != hipSuccess) return e;
-    }
-    blocks += t.tiles;
-  }
-  const dim3 grid((unsigned)blocks);
-  const bool e4m3 = b.job[1].e4m3 != nullptr;
-  if (dtype == LMHEAD_BF16) {
-    if (e4m3)
-      hipLaunchKernelGGL((operands_kernel<uint16_t, true>), grid, dim3(256), 0, s, b);
-    else
-      hipLaunchKernelGGL((operands_kernel<uint16_t, false>), grid, dim3(256), 0, s, b);
-  } else {
-    if (e4m3)
-      hipLaunchKernelGGL((operands_kernel<uint32_t, true>), grid, dim3(256), 0, s, b);
-    else
-      hipLaunchKernelGGL((operands_kernel<uint32_t, false>), grid, dim3(256), 0, s, b);
   }
   return hipGetLastError();
 }

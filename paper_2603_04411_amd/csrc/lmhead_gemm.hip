@@ -1,7 +1,7 @@
 // The three MFMA kernels of the LM-head path, all built on GemmTile (gemm_core.h):
 //   fwd_kernel    logits tile (vocabulary x tokens) -> max / sum-exp / sum-exp*z per token and tile,
 //                 target-logit capture; nothing of the tile is stored           (log-softmax of L_CE, Eq. 9)
-//   dz_kernel     logits tile recomputed -> dZ = g (onehot - softmax) (fp32: stored in both orientations)
+//   dz_kernel     logits tile recomputed -> dZ = g (onehot - softmax)
 //   gemm_t_kernel plain contraction with a transposed, row-mapped fp32 store    (dH and dW)
 // fwd_kernel and dz_kernel also exist for 8-bit (e4m3) copies of their operands.
 //
@@ -256,7 +256,6 @@ struct Store4<bf16_tag> {
     bf16x4_t v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
     *reinterpret_cast<bf16x4_t*>(p) = v;
   }
-  __device__ static inline void one(void* p, float a) { *reinterpret_cast<__bf16*>(p) = (__bf16)a; }
 };
 template <>
 struct Store4<f32_tag> {
@@ -264,7 +263,6 @@ struct Store4<f32_tag> {
     f32x4_t v = {a, b, c, d};
     *reinterpret_cast<f32x4_t*>(p) = v;
   }
-  __device__ static inline void one(void* p, float a) { *reinterpret_cast<float*>(p) = a; }
 };
 
 // Row order of the W tile in LDS for the 16x16-block dZ kernel.  LDS row R = WM w + 16 i + r feeds
@@ -371,7 +369,7 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
   trace_stamp(12, 2);
 }
 
-// E: type of the operands Hc and W (possibly e4m3 copies); EO: type of dZ / dZT.
+// E: type of the operands Hc and W (possibly e4m3 copies); EO: type of dZ.
 template <typename E, typename EO, int Edge>
 __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
   using G = Tile<E, kLeadDz, Edge>;
@@ -384,6 +382,10 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
   const int64_t n0 = (int64_t)nb * G::BN;
   const int mrel0 = mt * G::BM;  // within the chunk
   const int m0 = a.c0 + mrel0;
+  if (m0 == 0) {
+    const int64_t n = n0 + threadIdx.x;
+    if (threadIdx.x < G::BN && n < nv && a.tok_c[n] < 0) atomicOr(&a.hdr->err, kErrTok);
+  }
   const int mw = min(m0, a.V - 1);   // chunks end on multiples of 256: a narrower tile can lie beyond V (its dZ is 0)
   const int ksteps = a.d * Elem<E>::size / G::KB;
   const int64_t pitchH = a.ldHc * Elem<E>::size;
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
   // With 16x16 blocks and bf16 output the rows of the W tile enter LDS in a permuted order (DzRows), chosen so that a
   // lane's accumulators of two neighbouring blocks are EIGHT consecutive vocabulary entries of its token:
   // 16 bytes of a dZ row, stored straight from registers.
-  constexpr bool kDirect = G::NB == 16 && std::is_same<EO, bf16_tag>::value && k_major(false);
+  constexpr bool kDirect = G::NB == 16 && std::is_same<EO, bf16_tag>::value;
   uint32_t offA[G::A_LD], offB[G::B_LD];
 #pragma unroll
   for (int q = 0; q < G::A_LD; ++q) {
@@ -442,22 +444,16 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
   }
 
   char* dZ = static_cast<char*>(a.dZ);
-  char* dZT = static_cast<char*>(a.dZT);
-  // The tile leaves through LDS so that both copies are written with full 16-byte-per-lane,
-  // line-contiguous stores: registers hold 4 consecutive vocabulary entries of one token, which
-  // is neither orientation's row.  JG of the wave's TN token blocks are staged per phase (as many
-  // as fit next to each other in LDS in both orientations).
+  // The tile leaves through LDS so that it is written with full 16-byte-per-lane, line-contiguous stores: registers
+  // hold 4 consecutive vocabulary entries of one token.  JG of the wave's TN token blocks are staged per phase.
   constexpr int ESZ = Elem<EO>::size;
-  constexpr int JG0 = (ESZ == 2 ? 64 : 32) / G::NB;
+  constexpr int JG0 = 64 / G::NB;
   constexpr int JG = JG0 < G::TN ? JG0 : G::TN;      // token blocks per wave per phase
   constexpr int NTOK = G::WGN * JG * G::NB;       // tokens staged per phase
   constexpr int P1 = G::BM * ESZ + 16;            // pitch of the [token][vocab] staging rows
-  constexpr int P2 = NTOK * ESZ + 16;             // pitch of the [vocab][token] staging rows
-  constexpr int L2_OFF = NTOK * P1;
-  static_assert(L2_OFF + G::BM * P2 <= G::LDS_BYTES, "both staging layouts fit in LDS");
+  static_assert(NTOK * P1 <= G::LDS_BYTES, "staging fits in LDS");
   static_assert(G::TN % JG == 0, "phases cover the wave tile evenly");
   char* st1 = smem;
-  char* st2 = smem + L2_OFF;
   const int vlim = a.V - m0 - G::m_base();
   const float kz = kLog2e * a.zscale;              // logit = accumulator * zscale
   // Which form of the element-wise work this wave needs (wave-uniform, see emit below).
@@ -497,8 +493,6 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
             }
             const int mt = G::m_of(i, 4 * q);   // tile-relative vocabulary row, multiple of 4
             Store4<EO>::row(st1 + tl * P1 + mt * ESZ, dz[0], dz[1], dz[2], dz[3]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) Store4<EO>::one(st2 + (mt + e) * P2 + tl * ESZ, dz[e]);
           }
       };
       if (mode == 0)
@@ -522,43 +516,23 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
         *reinterpret_cast<u32x4_t*>(dZ + ((size_t)(n0 + nl) * a.ldZ + mrel0) * ESZ + c * 16) = v;
       }
     }
-    // [vocab][token] rows -> dZT: a staged row holds WGN runs of JG*32 consecutive tokens
-    {
-      constexpr int CPR = NTOK * ESZ / 16;
-      constexpr int RPP = G::NT / CPR;
-      constexpr int TPC = 16 / ESZ;           // tokens per 16-byte chunk
-      const int c = threadIdx.x % CPR;
-      const int tl = c * TPC;
-      const int nl = (tl / (JG * G::NB)) * G::WN + jg * (JG * G::NB) + tl % (JG * G::NB);
-#pragma unroll
-      for (int r0 = 0; r0 < G::BM; r0 += RPP) {
-        const int m = r0 + threadIdx.x / CPR;
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(st2 + m * P2 + c * 16);
-        *reinterpret_cast<u32x4_t*>(dZT + ((size_t)(mrel0 + m) * a.ldZT + n0 + nl) * ESZ) = v;
-      }
-    }
     if (jg + 1 < G::TN / JG) lds_barrier();
   }
 }
 
-// In bf16 the operands that have the contraction along their rows are taken as they lie (GemmTile's K-major operands): W for
-// dH, the hidden states and dZ for dW, both operands of a parameter gradient.  fp32, whose values are too wide for the transposing
-// LDS reads, goes by K-contiguous copies.  Against copies of all of them in bf16 too (8x8x256 step, d 2048): copies 294 -> 17 us
-// (what is left zeroes padding), dZ kernel, which had to write dZ in both orientations, 5.57 -> 5.01 ms, dH 4.46 -> 4.50, dW 4.48 ->
-// 4.46, the step 19.7 -> 18.8 ms; 4x8x2048, d 4096: dZ 39.7 -> 38.0 ms, the step 149.7 -> 147.0.  Which operand leads the ring
-// makes no difference here; two transposing reads behind an MFMA instead of one cost dW 2 %.
-template <typename E>
-constexpr bool k_major_a() { return k_major(Elem<E>::size == 4); }
-template <typename E>
-constexpr bool k_major_b(int role) { return k_major(Elem<E>::size == 4) && role != 0; }
-
+// The operands that have the contraction along their rows are taken as they lie (GemmTile's K-major operands): W for
+// dH, the hidden states and dZ for dW, both operands of a parameter gradient.  Against K-contiguous copies of all of them
+// (8x8x256 step, d 2048, bf16): copies 294 -> 17 us (the zeroing of padding), dZ kernel, which had to write dZ in both orientations,
+// 5.57 -> 5.01 ms, dH 4.46 -> 4.50, dW 4.48 -> 4.46, the step 19.7 -> 18.8 ms; 4x8x2048, d 4096: dZ 39.7 -> 38.0 ms, the step
+// 149.7 -> 147.0.  Which operand leads the ring makes no difference here; two transposing reads behind an MFMA instead of one cost
+// dW 2 %.
 // Role: 0 = dH (contracts over a vocabulary chunk), 1 = dW (contracts over the valid tokens), 2 = a
 // parameter gradient of the KV gate (contracts over the tokens of a stream).  The code is the same; the
 // parameter only gives the uses distinct kernel names in profiles (and picks the lead operand).
 template <typename E, int Role, int Edge>
 __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTArgs a) {
-  constexpr bool kTA = k_major_a<E>(), kTB = k_major_b<E>(Role);
-  using G = Tile<E, (Role == 0 ? kLeadDh : kLeadDw), Edge, kTA, kTB, kTA && Role == 1>;
+  constexpr bool kTB = Role != 0;
+  using G = Tile<E, (Role == 0 ? kLeadDh : kLeadDw), Edge, /*kTransA=*/true, kTB, /*kWalk=*/Role == 1>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nv = a.hdr->nv;
   const int64_t n_lim = a.n_from_nv ? (int64_t)nv : a.n_limit;
@@ -585,8 +559,8 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   uint32_t offA[G::A_LD], offB[G::B_LD];
 #pragma unroll
   for (int q = 0; q < G::A_LD; ++q) {
-    const int row = kTA ? G::ldT_row(q) : G::ldA_row(q);
-    offA[q] = (uint32_t)(row * pitchA) + (kTA ? G::ldT_byte(row) : G::ld_byte(row));
+    const int row = G::ldT_row(q);
+    offA[q] = (uint32_t)(row * pitchA) + G::ldT_byte(row);
   }
 #pragma unroll
   for (int q = 0; q < G::B_LD; ++q) {
@@ -623,28 +597,26 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   constexpr int kKind = Role == 0 ? 3 : (Role == 1 ? 4 : 0);
   const char* const pa = static_cast<const char*>(second ? a.A2 : a.A);
   const char* const pb = static_cast<const char*>(second ? a.B2 : a.B);
-  if constexpr (!kTA) {
-    G::run(acc, pa + (int64_t)m0 * pitchA + (int64_t)k_first * G::KB, offA, pb + n0 * pitchB + (int64_t)k_first * G::KB, offB,
-           ksteps, smem, kKind);
-  } else if constexpr (Role == 1) {
+  constexpr int ESZ = Elem<E>::size;
+  if constexpr (Role == 1) {
     // both operands lie in the workspace and are readable to the end of their last K-step
     const int64_t stepA = G::KROWS * pitchA, stepB = G::KROWS * pitchB;
-    G::run_steps(acc, pa + k_first * stepA + (int64_t)m0 * 2, offA, 0, (uint32_t)stepA, pb + k_first * stepB + n0 * 2, offB, 0,
-                 (uint32_t)stepB, ksteps, smem, kKind);
+    G::run_steps(acc, pa + k_first * stepA + (int64_t)m0 * ESZ, offA, G::kWindow, (uint32_t)stepA,
+                 pb + k_first * stepB + n0 * ESZ, offB, G::kWindow, (uint32_t)stepB, ksteps, smem, kKind);
   } else {
-    // A K-major operand advances by 64 of its rows per K-step.  What lies past its end (the rows that fill the last
+    // A K-major operand advances by KROWS of its rows per K-step.  What lies past its end (the rows that fill the last
     // K-step up) has to read as zeros: a buffer window does that, of at most 2 GiB; operands beyond that are taken in
     // pieces, each of which fills the pipeline anew (3 us).
     const int64_t stepA = G::KROWS * pitchA, stepB = kTB ? G::KROWS * pitchB : (int64_t)G::KB;
-    const int piece = (int)(0x7fffffff / (kTB && stepB > stepA ? stepB : stepA));
+    const int piece = (int)(G::kWindow / (kTB && stepB > stepA ? stepB : stepA));
     const int64_t bytesA = second ? a.a2_bytes : a.a_bytes, bytesB = second ? a.b2_bytes : a.b_bytes;
-    auto window = [](int64_t left) { return (uint32_t)(left < 0 ? 0 : left < 0x7fffffff ? left : 0x7fffffff); };
+    auto window = [](int64_t left) { return (uint32_t)(left < 0 ? 0 : left < G::kWindow ? left : G::kWindow); };
     int k = 0;
     do {
-      const int64_t atA = (k_first + k) * stepA + (int64_t)m0 * 2;
-      const int64_t atB = (k_first + k) * stepB + (kTB ? n0 * 2 : n0 * pitchB);
+      const int64_t atA = (k_first + k) * stepA + (int64_t)m0 * ESZ;
+      const int64_t atB = (k_first + k) * stepB + (kTB ? n0 * ESZ : n0 * pitchB);
       G::run_steps(acc, pa + atA, offA, window(bytesA - atA), (uint32_t)stepA, pb + atB, offB,
-                   kTB ? window(bytesB - atB) : 0x7fffffffu, (uint32_t)stepB, min(piece, ksteps - k), smem, kKind);
+                   kTB ? window(bytesB - atB) : G::kWindow, (uint32_t)stepB, min(piece, ksteps - k), smem, kKind);
       k += piece;
     } while (k < ksteps);
   }

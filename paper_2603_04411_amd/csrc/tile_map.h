@@ -13,13 +13,6 @@
 
 namespace lmhead {
 
-// Edge of the bf16 main loop's MFMA blocks (gemm_core.h): 16, or 32 in a build for comparison.  Only the former takes K-major
-// operands; the latter contracts K-contiguous copies in bf16 too, as fp32 does.
-#ifndef LMHEAD_BF16_BLOCK
-#define LMHEAD_BF16_BLOCK 16
-#endif
-constexpr bool k_major(bool f32) { return !f32 && LMHEAD_BF16_BLOCK == 16; }
-
 // Macro-tile of the contractions: the widest tile edge, and the unit that operands are padded to.
 constexpr int kTile = 256;
 
