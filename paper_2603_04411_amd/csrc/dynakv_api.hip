@@ -262,7 +262,6 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
     LM_TRY(launch_kv_mask_bwd(dt, static_cast<const float*>(at(L.logits)), b, xt, g_xhat, g_m, g_m_const, L.n, d,
                               literal, at(L.gl), at(L.gxt), static_cast<float*>(at(L.dbpart)), L.nblk, s));
   }
-  LM_TRY(launch_kv_sum_rows(static_cast<const float*>(at(L.dbpart)), L.nblk, d, d, db, accum, s));
 
   // g_x~ += g_l W^T
   ga.mode = 3;
@@ -322,7 +321,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
     TimedLaunch tl(11, s);
     LM_TRY(launch_gemm_t(dt, ta, s, 2));
   }
-  if (L.ksplit > 1) LM_TRY(launch_kv_sum_rows(ta.part, L.ksplit, ta.part_slice, ta.part_slice, dW, accum, s, dU));
+  LM_TRY(launch_kv_sums({static_cast<const float*>(at(L.dbpart)), L.nblk, ta.part, L.ksplit, d, db, dW, dU, accum}, s));
   return LMHEAD_OK;
 }
 

@@ -434,21 +434,18 @@ void kv_mask_bwd_kernel(const float* __restrict__ logits, const float* __restric
   }
 }
 
-// out[j] (+)= sum over the rows of part, in a fixed order.  Bound by reading part once; what differs is where the
-// parallelism is.
-//  - Few rows (slices of a parameter gradient): one thread per four columns walks the rows.
-//  - Many rows, few columns (the column sums of the mask backward): a workgroup owns 64 columns, its sixteen
-//    wavefronts each sum every sixteenth row, eight loads at a time.  (With four wavefronts and a chain of four loads each,
-//    1024 rows of 1024 columns took 22 us, now 5.4.)
-__global__ __launch_bounds__(256) void kv_sum_slices_kernel(const float* __restrict__ part, int rows, int64_t row_pitch,
-                                                            int64_t len4, float* __restrict__ out,
-                                                            float* __restrict__ out2, int accumulate) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j >= len4) return;
-  if (blockIdx.y) {
-    part += (int64_t)rows * row_pitch;
-    out = out2;
-  }
+// The sums that end a backward call, in one launch: the slices of the two parameter gradients (if they were cut) and the
+// column sums of the mask backward.  Bound by reading the parts once; what differs is where the parallelism is.
+//  - Slices (few rows, d x d columns): one thread per four columns walks the rows.
+//  - Column sums (many rows, d columns): a workgroup owns 64 columns, its sixteen wavefronts each sum every sixteenth
+//    row, eight loads at a time.  (With four wavefronts and a chain of four loads each, 1024 rows of 1024 columns took 22 us, now 5.4.)
+// The column sums are ready long before the gradients, but a launch of their own costs its 4 us of dispatch wherever it is put
+// (4096 x 1024 training pair 149.5 -> 145.7 us; 300 x 128 in fp32 48.5 -> 47.4 with the one-launch retain rate below, which
+// no longer waits for the GPU but for the host).
+constexpr int kSumWaves = 16, kSumBatch = 8;
+
+__device__ inline void sum_slices(const float* __restrict__ part, int rows, int64_t row_pitch, float* __restrict__ out,
+                                  int64_t j, bool accumulate) {
   float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
   for (int r = 0; r < rows; ++r) {
@@ -463,43 +460,42 @@ __global__ __launch_bounds__(256) void kv_sum_slices_kernel(const float* __restr
   *dst = t;
 }
 
-constexpr int kSumWaves = 16, kSumBatch = 8;
-
-__global__ __launch_bounds__(64 * kSumWaves) void kv_sum_rows_kernel(const float* __restrict__ part, int rows,
-                                                                     int64_t row_pitch, int64_t len,
-                                                                     float* __restrict__ out, float* __restrict__ out2,
-                                                                     int accumulate) {
+__global__ __launch_bounds__(64 * kSumWaves) void kv_sum_kernel(KvSums a) {
   __shared__ float sm[kSumWaves][64];
-  if (blockIdx.y) {
-    part += (int64_t)rows * row_pitch;
-    out = out2;
+  const int col_blocks = a.d / 64;
+  if ((int)blockIdx.x >= col_blocks) {
+    const int64_t len4 = (int64_t)a.d * a.d / 4;
+    int64_t j = (int64_t)(blockIdx.x - col_blocks) * (64 * kSumWaves) + threadIdx.x;
+    const bool second = j >= len4;
+    if (second) j -= len4;
+    if (j < len4)
+      sum_slices(a.part + (second ? a.slices * len4 * 4 : 0), a.slices, len4 * 4, second ? a.dU : a.dW, j, a.accumulate);
+    return;
   }
   const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
-  const int64_t j = (int64_t)blockIdx.x * 64 + cl;
+  const int j = blockIdx.x * 64 + cl;
   float t[kSumBatch] = {};
-  if (j < len) {
-    const float* const p = part + j;
-    int r = rl;
-    for (; r + (kSumBatch - 1) * kSumWaves < rows; r += kSumWaves * kSumBatch) {
-      float v[kSumBatch];
+  const float* const p = a.dbpart + j;
+  int r = rl;
+  for (; r + (kSumBatch - 1) * kSumWaves < a.db_rows; r += kSumWaves * kSumBatch) {
+    float v[kSumBatch];
 #pragma unroll
-      for (int u = 0; u < kSumBatch; ++u) v[u] = p[(int64_t)(r + u * kSumWaves) * row_pitch];
+    for (int u = 0; u < kSumBatch; ++u) v[u] = p[(int64_t)(r + u * kSumWaves) * a.d];
 #pragma unroll
-      for (int u = 0; u < kSumBatch; ++u) t[u] += v[u];
-    }
-    for (; r < rows; r += kSumWaves) t[0] += p[(int64_t)r * row_pitch];
+    for (int u = 0; u < kSumBatch; ++u) t[u] += v[u];
   }
+  for (; r < a.db_rows; r += kSumWaves) t[0] += p[(int64_t)r * a.d];
 #pragma unroll
   for (int o = kSumBatch / 2; o > 0; o >>= 1)
 #pragma unroll
     for (int u = 0; u < o; ++u) t[u] += t[u + o];
   sm[rl][cl] = t[0];
   __syncthreads();
-  if (rl == 0 && j < len) {
+  if (rl == 0) {
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < kSumWaves; ++w) v += sm[w][cl];
-    out[j] = accumulate ? out[j] + v : v;
+    a.db[j] = a.accumulate ? a.db[j] + v : v;
   }
 }
 
@@ -813,27 +809,22 @@ __global__ __launch_bounds__(256) void kv_scatter_kernel(const int32_t* __restri
 
 // ---- retain rate ----------------------------------------------------------------------------
 
-// red[2*b] = sum of k over the block's tokens, red[2*b+1] = sum of m over their rows.  The tokens are cut evenly over
-// the blocks.  Bound by the one read of m: as many blocks as the chip holds at once (kKvRetainBlocks), each thread with
-// four loads in flight.  (One block per 256 tokens gave 16 blocks for 4096 tokens and 66 us, now 5.5.)
-__global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* __restrict__ k,
-                                                                const float* __restrict__ m, int64_t n, int d,
-                                                                double* __restrict__ red, WsHeader* hdr) {
-  __shared__ double sk[4], sm[4];
-  if (blockIdx.x == 0 && threadIdx.x == 0) clear_header(hdr);
-  const int64_t t0 = n * blockIdx.x / gridDim.x;
-  const int64_t tn = n * (blockIdx.x + 1) / gridDim.x - t0;
-  double ks = 0.0;
+// Sums of k and of m over tokens [t0, t0 + tn), valid in thread 0; a workgroup of NT threads.
+template <int NT>
+__device__ inline void retain_sums(const int32_t* __restrict__ k, const float* __restrict__ m, int64_t t0, int64_t tn, int d,
+                                   double& ks, double& ms) {
+  __shared__ double sk[NT / 64], sm[NT / 64];
+  ks = 0.0;
   if (k)
-    for (int64_t i = threadIdx.x; i < tn; i += 256) ks += min(max(k[t0 + i], 0), d);
-  double ms = 0.0;
+    for (int64_t i = threadIdx.x; i < tn; i += NT) ks += min(max(k[t0 + i], 0), d);
+  ms = 0.0;
   if (m) {
     const int64_t cnt4 = tn * d / 4;
     const float4* p = reinterpret_cast<const float4*>(m + t0 * d);
-    for (int64_t i = threadIdx.x; i < cnt4; i += 1024) {
+    for (int64_t i = threadIdx.x; i < cnt4; i += 4 * NT) {
       float4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = i + 256 * u < cnt4 ? p[i + 256 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int u = 0; u < 4; ++u) v[u] = i + NT * u < cnt4 ? p[i + NT * u] : make_float4(0.f, 0.f, 0.f, 0.f);
       float t[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) t[u] = (v[u].x + v[u].y) + (v[u].z + v[u].w);
@@ -850,9 +841,46 @@ __global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* _
     sm[threadIdx.x >> 6] = ms;
   }
   __syncthreads();
+  ks = ms = 0.0;
+  if (threadIdx.x == 0)
+    for (int w = 0; w < NT / 64; ++w) {
+      ks += sk[w];
+      ms += sm[w];
+    }
+}
+__device__ inline void retain_out(double ks, double ms, bool have_k, bool have_m, double nd, float alpha,
+                                  float* __restrict__ out) {
+  const double rh = have_k ? ks / nd : 0.0, rs = have_m ? ms / nd : 0.0;
+  out[0] = (float)rh;
+  out[1] = (float)rs;
+  out[2] = (float)(alpha * rs * rs);
+}
+
+// red[2*b] = sum of k over the block's tokens, red[2*b+1] = sum of m over their rows.  The tokens are cut evenly over
+// the blocks.  Bound by the one read of m: as many blocks as the chip holds at once (kKvRetainBlocks), each thread with
+// four loads in flight.  (One block per 256 tokens gave 16 blocks for 4096 tokens and 66 us, now 5.5.)
+__global__ __launch_bounds__(256) void kv_retain_partial_kernel(const int32_t* __restrict__ k,
+                                                                const float* __restrict__ m, int64_t n, int d,
+                                                                double* __restrict__ red, WsHeader* hdr) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) clear_header(hdr);
+  const int64_t t0 = n * blockIdx.x / gridDim.x;
+  double ks, ms;
+  retain_sums<256>(k, m, t0, n * (blockIdx.x + 1) / gridDim.x - t0, d, ks, ms);
   if (threadIdx.x == 0) {
-    red[2 * blockIdx.x] = (sk[0] + sk[1]) + (sk[2] + sk[3]);
-    red[2 * blockIdx.x + 1] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
+    red[2 * blockIdx.x] = ks;
+    red[2 * blockIdx.x + 1] = ms;
+  }
+}
+
+// Few values (kRetainFew): one workgroup and one launch.
+__global__ __launch_bounds__(1024) void kv_retain_few_kernel(const int32_t* __restrict__ k, const float* __restrict__ m,
+                                                             int64_t n, int d, float alpha, float* __restrict__ out,
+                                                             WsHeader* hdr) {
+  double ks, ms;
+  retain_sums<1024>(k, m, 0, n, d, ks, ms);
+  if (threadIdx.x == 0) {
+    clear_header(hdr);
+    retain_out(ks, ms, k != nullptr, m != nullptr, (double)n * d, alpha, out);
   }
 }
 
@@ -880,14 +908,9 @@ __global__ __launch_bounds__(256) void kv_retain_final_kernel(const double* __re
     sm[threadIdx.x >> 6] = b;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const double nd = (double)n * d;
-    const double rh = have_k ? ((sk[0] + sk[1]) + (sk[2] + sk[3])) / nd : 0.0;
-    const double rs = have_m ? ((sm[0] + sm[1]) + (sm[2] + sm[3])) / nd : 0.0;
-    out[0] = (float)rh;
-    out[1] = (float)rs;
-    out[2] = (float)(alpha * rs * rs);
-  }
+  if (threadIdx.x == 0)
+    retain_out((sk[0] + sk[1]) + (sk[2] + sk[3]), (sm[0] + sm[1]) + (sm[2] + sm[3]), have_k, have_m, (double)n * d, alpha,
+               out);
 }
 
 __global__ __launch_bounds__(256) void kv_retain_grad_kernel(const float* __restrict__ out, float alpha,
@@ -970,16 +993,10 @@ hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, co
   return launch_mask_bwd_t<float>(logits, b, xt, g_xhat, g_m, g_m_const, n, d, literal, gl, a_out, dbpart, nblk, s);
 }
 
-hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, int64_t len, float* out,
-                              bool accumulate, hipStream_t s, float* out2) {
-  const unsigned outs = out2 ? 2 : 1;
-  // 256 rows: above the most slices of a parameter gradient, which has d x d columns
-  if (rows <= 256 && len % 4 == 0 && row_pitch % 4 == 0 && len >= 16384)
-    hipLaunchKernelGGL(kv_sum_slices_kernel, dim3((unsigned)((len / 4 + 255) / 256), outs), dim3(256), 0, s, part, rows,
-                       row_pitch, len / 4, out, out2, accumulate ? 1 : 0);
-  else
-    hipLaunchKernelGGL(kv_sum_rows_kernel, dim3((unsigned)((len + 63) / 64), outs), dim3(64 * kSumWaves), 0, s, part,
-                       rows, row_pitch, len, out, out2, accumulate ? 1 : 0);
+hipError_t launch_kv_sums(const KvSums& a, hipStream_t s) {
+  constexpr int64_t NT = 64 * kSumWaves;
+  const int64_t slices = a.slices > 1 ? ((int64_t)a.d * a.d / 2 + NT - 1) / NT : 0;   // both gradients, four columns a thread
+  hipLaunchKernelGGL(kv_sum_kernel, dim3((unsigned)(a.d / 64 + slices)), dim3((unsigned)NT), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1023,10 +1040,17 @@ hipError_t launch_kv_order(int dtype, const KvCount& c, const int64_t* off, int6
 
 hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, float alpha, float* out,
                             float* g_m, double* red, WsHeader* hdr, hipStream_t s) {
-  const int nblocks = (int)(n < kKvRetainBlocks ? n : kKvRetainBlocks);
-  hipLaunchKernelGGL(kv_retain_partial_kernel, dim3(nblocks), dim3(256), 0, s, k, m, n, d, red, hdr);
-  hipLaunchKernelGGL(kv_retain_final_kernel, dim3(1), dim3(256), 0, s, red, nblocks, n, d, alpha, k ? 1 : 0,
-                     m ? 1 : 0, out);
+  // Up to here one workgroup reads everything sooner than a second launch starts.  Whole call, us, two launches / one: 38400 values
+  // 11.3 / 8.0, 131072 11.1 / 7.3, 262144 11.0 / 9.7, 524288 11.2 / 17.5.
+  constexpr int64_t kRetainFew = 262144;
+  if (n * d <= kRetainFew) {
+    hipLaunchKernelGGL(kv_retain_few_kernel, dim3(1), dim3(1024), 0, s, k, m, n, d, alpha, out, hdr);
+  } else {
+    const int nblocks = (int)(n < kKvRetainBlocks ? n : kKvRetainBlocks);
+    hipLaunchKernelGGL(kv_retain_partial_kernel, dim3(nblocks), dim3(256), 0, s, k, m, n, d, red, hdr);
+    hipLaunchKernelGGL(kv_retain_final_kernel, dim3(1), dim3(256), 0, s, red, nblocks, n, d, alpha, k ? 1 : 0,
+                       m ? 1 : 0, out);
+  }
   if (g_m) {
     const int64_t count4 = n * d / 4;
     hipLaunchKernelGGL(kv_retain_grad_kernel, dim3((unsigned)((count4 + 255) / 256)), dim3(256), 0, s, out, alpha,

@@ -252,9 +252,16 @@ hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, co
                               const float* g_m, float g_m_const, int64_t n, int d, bool literal, void* gl,
                               void* a_out, float* dbpart, int nblk, hipStream_t s);
 
-// out[j] (+)= sum_r part[r][j] for j < len (rows of pitch row_pitch floats), in a fixed order; with out2 also
-// out2[j] (+)= sum_r part[rows + r][j].
-hipError_t launch_kv_sum_rows(const float* part, int rows, int64_t row_pitch, int64_t len, float* out,
-                              bool accumulate, hipStream_t s, float* out2 = nullptr);
+// db (+)= the column sums of dbpart [db_rows x d]; with slices > 1 also dW (+)= the sum of the first `slices` d x d matrices of
+// part and dU (+)= that of the next ones.  Fixed order.
+struct KvSums {
+  const float* dbpart;
+  int db_rows;
+  const float* part;
+  int slices, d;
+  float *db, *dW, *dU;
+  bool accumulate;
+};
+hipError_t launch_kv_sums(const KvSums& a, hipStream_t s);
 
 }  // namespace lmhead
