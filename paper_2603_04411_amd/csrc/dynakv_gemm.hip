@@ -50,19 +50,34 @@ int tile_edge(bool f32, int mode, int M, int64_t Nn) {
     if (cost(edge) < cost(best)) best = edge;
   return best;
 }
-// Workgroups of one tile edge that share a compute unit (bound by LDS: five slots of edge x 128 bytes each).
-constexpr int wg_per_cu(int edge) { return 256 / edge; }
+// Workgroups of one tile edge that share a compute unit (bound by LDS: five slots of edge x 128 bytes each, or both operands' stages).
+constexpr int wg_per_cu(int edge, int stages) { return stages ? 640 / (edge * stages) : 256 / edge; }
+
+// Tiles that hold five K-steps in LDS instead of two and a half (bf16): where every tile has a compute unit for itself, so that
+// nothing else covers an access to L2, which takes longer than the MFMAs of a K-step do, and the contraction has 16 K-steps or
+// more.  Shorter ones end before the lead pays for the five requests in front of the first MFMA, and two or more tiles on a
+// compute unit cover each other.  The ring / five stages, us:
+//   gate   1024 x 1024 25.0 / 20.6   550 x 1024 24.5 / 19.9   1100 x 2048 51.0 / 45.4   4096 x 1024 36.2 / 34.5
+//          (more tiles: 2048 x 1024 27.3 / 27.8, 4096 x 512 19.8 / 21.5; shorter: 2000 x 512 16.2 / 17.0)
+//   store + reconstruction   1000 x 1024 26.1 / 23.4; on edge 128 no faster (3000 x 1024 28.3 / 28.2)
+//   training pair   1024 x 1024 83.1 / 72.5   4096 x 1024 136.4 / 134.9
+// Eight stages are no faster (gate 1024 x 1024 22.0).
+constexpr int kStages = 5;
+bool deep_tiles(int mode, int edge, int M, int64_t Nn, int K) {
+  const int64_t tiles = (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge);
+  return tiles <= device_compute_units() && K / 64 >= 16 && (edge == 64 || (edge == 128 && mode != 2));
+}
 
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
-template <typename E, int Edge, int Mode>
+template <typename E, int Edge, int Mode, int Stages>
 using KvTile = GemmTile<E, Edge, Edge, 2, 2, /*kLeadB=*/true, /*kMaskB=*/Mode == 2,
-                        /*kTransA=*/Mode != 3>;
+                        /*kTransA=*/Mode != 3, /*kTransB=*/false, /*kWalk=*/false, Stages>;
 
 // One output tile; `wg` is the tile's position in the XCD-aware walk.
-template <typename E, int Edge, int Mode>
+template <typename E, int Edge, int Mode, int Stages>
 __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
-  using G = KvTile<E, Edge, Mode>;
+  using G = KvTile<E, Edge, Mode, Stages>;
   constexpr bool kTA = Mode != 3;
   constexpr int ESZ = Elem<E>::size;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
@@ -239,29 +254,29 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
 // Tiles here are short (d_kv / 64 K-steps or fewer), so the workgroups are persistent: as many as
 // are resident at a time (wg_per_cu of them on each compute unit), each taking every gridDim.x-th tile of the walk, which saves a workgroup
 // launch per tile.  gridDim.x is a multiple of 8, so a tile stays on the XCD that the walk meant it for.
-template <typename E, int Edge, int Mode>
-__global__ __launch_bounds__(256, wg_per_cu(Edge)) void kv_gemm_kernel(KvGemmArgs a) {
+template <typename E, int Edge, int Mode, int Stages>
+__global__ __launch_bounds__(256, wg_per_cu(Edge, Stages)) void kv_gemm_kernel(KvGemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   if (a.clear && blockIdx.x == 0 && threadIdx.x == 0) {
     a.hdr->err = 0;
     a.hdr->nv = 0;
   }
-  for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Edge, Mode>(a, wg, smem);
+  for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Edge, Mode, Stages>(a, wg, smem);
 }
 
-template <typename E, int Edge, int Mode>
+template <typename E, int Edge, int Mode, int Stages = 0>
 hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
-  using G = KvTile<E, Edge, Mode>;
+  using G = KvTile<E, Edge, Mode, Stages>;
   const int mtiles = (a.M + G::BM - 1) / G::BM;
   const int64_t ntiles = (a.Nn + G::BN - 1) / G::BN;
   if (a.accumulate && (Mode == 2 || a.out_f || !a.out_e)) return hipErrorInvalidValue;
   KvGemmArgs b = a;
   b.walk_len = (int)xcd_grid_size(mtiles, ntiles, kKvMapBy);
-  const unsigned resident = (unsigned)device_compute_units() / kNumXcd * kNumXcd * wg_per_cu(Edge);   // LDS-bound
+  const unsigned resident = (unsigned)device_compute_units() / kNumXcd * kNumXcd * wg_per_cu(Edge, Stages);   // LDS-bound
   const dim3 grid(b.walk_len < (int)resident ? (unsigned)b.walk_len : resident);
-  hipError_t e = allow_lds<kv_gemm_kernel<E, Edge, Mode>>(G::LDS_BYTES);
+  hipError_t e = allow_lds<kv_gemm_kernel<E, Edge, Mode, Stages>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((kv_gemm_kernel<E, Edge, Mode>), grid, dim3(G::NT), G::LDS_BYTES, s, b);
+  hipLaunchKernelGGL((kv_gemm_kernel<E, Edge, Mode, Stages>), grid, dim3(G::NT), G::LDS_BYTES, s, b);
   return hipGetLastError();
 }
 
@@ -363,7 +378,14 @@ static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
 
 template <typename E, int Mode>
 hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
-  switch (tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn)) {
+  const int edge = tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn);
+  if constexpr (Elem<E>::size == 2) {
+    if (deep_tiles(Mode, edge, a.M, a.Nn, a.K)) {
+      if (edge == 64) return launch_tiles<E, 64, Mode, kStages>(a, s);
+      if constexpr (Mode != 2) return launch_tiles<E, 128, Mode, kStages>(a, s);
+    }
+  }
+  switch (edge) {
     case 64: return launch_tiles<E, 64, Mode>(a, s);
     case 128: return launch_tiles<E, 128, Mode>(a, s);
     default: return launch_tiles<E, 256, Mode>(a, s);

@@ -196,8 +196,10 @@ __device__ inline void lds_barrier() {
 // kMaskB: every B row has its own K extent (ragged rows); loads past it fetch zeros (see run()).
 // kTransA / kTransB: the operand is K-major (see above).  kWalk: K-major operands are not limited to a window but followed by
 // a pointer that advances with the K-steps, for operands that are readable to the end of the last K-step.
+// kStages: 0 for the ring of five slots; else that many K-steps (both operands) are held in LDS, for tiles that have a compute
+// unit, or half of one, for themselves (see the deep loop in run_rows; bf16 on 16x16x32 blocks).
 template <typename E, int BM_, int BN_, int WGM_, int WGN_, bool kLeadB = false, bool kMaskB = false, bool kTransA = false,
-          bool kTransB = false, bool kWalk = false>
+          bool kTransB = false, bool kWalk = false, int kStages = 0>
 struct GemmTile {
   static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
   static constexpr int NWAVES = WGM * WGN;
@@ -210,7 +212,7 @@ struct GemmTile {
   static constexpr int KB = 128;                      // bytes of K per row per step (a cache line)
   static constexpr int FC = Elem<E>::frag_chunks;     // 16-byte chunks per lane and fragment
   static constexpr int NSUB = KB / 16 / (LG * FC);    // K sub-steps (one fragment pair each)
-  static constexpr int NSLOT = 5;                     // ring of operand-tile slots
+  static constexpr int NSLOT = kStages ? 2 * kStages : 5;   // ring of operand-tile slots
   static constexpr int SLOT = (BM > BN ? BM : BN) * KB;
   static constexpr int LDS_BYTES = NSLOT * SLOT;
   // The slots are interleaved in LDS by groups of 8 rows (1 KB, what one load instruction writes):
@@ -228,6 +230,7 @@ struct GemmTile {
   static_assert(!(kTransA || kTransB) || (Elem<E>::size >= 2 && BM == BN && WGM == 2 && WGN == 2),
                 "K-major operands: bf16 or fp32, four wavefronts");
   static_assert(!(kTransB && kMaskB), "ragged rows are K-contiguous");
+  static_assert(!kStages || (NB == 16 && FC == 1 && kStages > 2 && 2 * (kStages - 1) * A_LD < 64), "one vmcnt covers the ring");
   static_assert(NSUB == 1 || NSUB % 2 == 0, "fragment double-buffering assumes an even number of sub-steps");
 
   using Block = typename Elem<E>::acc_t;
@@ -308,6 +311,17 @@ struct GemmTile {
 #pragma unroll
         for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
       asm volatile("s_nop 7");
+    }
+  }
+
+  // The deep loop's wait: all but this wave's youngest n stages of loads (of one of them only X, when `half`) have landed.
+  template <int U = 0>
+  __device__ static inline void wait_young(int n, bool half) {
+    if (n == U) {
+      if (half) __builtin_amdgcn_s_waitcnt(wait_vm(U ? (2 * U - 1) * A_LD : 0));
+      else __builtin_amdgcn_s_waitcnt(wait_vm(2 * U * A_LD));
+    } else if constexpr (U + 1 < kStages) {
+      wait_young<U + 1>(n, half);
     }
   }
 
@@ -688,6 +702,63 @@ struct GemmTile {
           __builtin_amdgcn_sched_barrier(0);
         }
       };
+      if constexpr (kStages > 0) {
+        // The deep loop.  X(ks), Y(ks) sit in slots 2 st, 2 st + 1 of stage st = ks % kStages.  K-step ks requests
+        // Y(ks + D - 1) in its first half and, behind the hand-over barrier in its middle, X(ks + D) into its own stage, so
+        // that a load has D - 1 K-steps to land.  The five-slot ring gives it one: at edge 128 that is 512 cycles of
+        // MFMAs, less than an access to L2 takes, and a tile that is alone on its compute unit waited for every K-step.
+        constexpr int D = kStages;
+        const int first = ksteps < D ? ksteps : D;
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+          if (t < ksteps) {
+            issue_x(t, 2 * t, 0); issue_x(t, 2 * t, 1);
+            if (t < D - 1) { issue_y(t, 2 * t + 1, 0); issue_y(t, 2 * t + 1, 1); }
+          }
+        }
+        wait_young(first - 1, first == D);
+        __builtin_amdgcn_s_barrier();
+        frags_xy(lds, lds + SSTR, 0, 0);
+        settle(acc);
+        __builtin_amdgcn_sched_barrier(0);
+        auto step = [&](int c, int st, bool ldy, bool ldx, bool next, int young) {
+          const int st1 = st + 1 == D ? 0 : st + 1, stL = st == 0 ? D - 1 : st - 1;
+          const char* cx = lds + 2 * st * SSTR;
+          const char* cy = cx + SSTR;
+          region(0, 0, true, true, cx, 1, 1, ldy, false, c + D - 1, 2 * stL + 1, 0);
+          region(0, TM / 2, true, false, cy, 1, 1, ldy, false, c + D - 1, 2 * stL + 1, LD_REGION);
+          if (next) {
+            wait_young(young, false);
+            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          region(1, 0, next, true, lds + 2 * st1 * SSTR, 0, 0, ldx, true, c + D, 2 * st, 0);
+          region(1, TM / 2, next, false, lds + (2 * st1 + 1) * SSTR, 0, 0, ldx, true, c + D, 2 * st, LD_REGION);
+        };
+        int ks = 0, st = 0;
+        // unrolled by the ring's period: stage numbers and waits are constants
+        for (; ks + D + (D - 1) < ksteps; ks += D) {
+#pragma unroll
+          for (int u = 0; u < D; ++u) step(ks + u, u, true, true, true, D - 2);
+        }
+        for (; ks + D < ksteps; ++ks) {
+          step(ks, st, true, true, true, D - 2);
+          st = st + 1 == D ? 0 : st + 1;
+        }
+        // the last D K-steps: one Y tile is still to be requested where there are as many
+        if (ks + D == ksteps) {
+          step(ks, st, true, false, true, D - 2);
+          st = st + 1 == D ? 0 : st + 1;
+          ++ks;
+        }
+        for (; ks + 1 < ksteps; ++ks) {
+          step(ks, st, false, false, true, ksteps - 2 - ks);
+          st = st + 1 == D ? 0 : st + 1;
+        }
+        step(ks, st, false, false, false, 0);
+        asm volatile("s_nop 15\n\ts_nop 15");
+      } else {
       int sX = 0, sY = 1;
       issue_x(0, 0, 0); issue_x(0, 0, 1);
       issue_y(0, 1, 0); issue_y(0, 1, 1);
@@ -767,6 +838,7 @@ struct GemmTile {
       // the asm MFMAs' results are read by ordinary instructions next: let the last ones retire
       asm volatile("s_nop 15\n\ts_nop 15");
       trace_stamp(10, trace_kind);
+      }
     } else if constexpr (NB == 16 && FC == 2) {
       // e4m3 on 16x16x128 blocks: ONE MFMA per block pair consumes the whole K-step (32 cycles each, 64 per
       // K-step).  A second set of fragments does not fit the register file (2 x 128 registers), so there is
