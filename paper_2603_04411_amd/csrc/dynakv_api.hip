@@ -80,7 +80,7 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     LM_TRY(launch_kv_gate({x, desc->ldx, w.at<void>(L.Ufrag), w.at<void>(L.Wfrag), b, L.n, tau, literal ? 1 : 0, xt, k}, d, s));
     return LMHEAD_OK;
   }
-  if (kv_few_fits(L.n, d)) {
+  if (kv_few_fits(dt, L.n, d)) {
     KvFewArgs fa{x, desc->ldx, U, (int)L.n, d, xt, nullptr, hdr, false, false};
     {
       TimedLaunch tl(4, s);
@@ -234,7 +234,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   const bool accum = (desc->flags & DYNAKV_FLAG_ACCUM_GRAD) != 0;
 
   // the parameters as the caller has them: W is K-major in the logits and K-contiguous, like U, in g_l W^T and g_x~ U^T
-  const bool few = kv_few_fits(L.n, d);
+  const bool few = kv_few_fits(dt, L.n, d);
   KvGemmArgs ga{};
   ga.mode = 1;
   ga.A = W;

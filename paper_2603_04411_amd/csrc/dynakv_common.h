@@ -162,7 +162,7 @@ struct KvFewArgs {
   WsHeader* hdr;
   bool rows, accumulate;
 };
-bool kv_few_fits(int64_t n, int d);
+bool kv_few_fits(int dtype, int64_t n, int d);
 hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s);
 
 // The whole gate of many tokens in one kernel (dynakv_gate.hip), for callers that want x~ and k only.  Ufrag, Wfrag: the

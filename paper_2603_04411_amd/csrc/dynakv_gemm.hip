@@ -62,10 +62,10 @@ constexpr int wg_per_cu(int edge, int stages) { return stages ? 640 / (edge * st
 //   store + reconstruction   1000 x 1024 26.1 / 23.4; on edge 128 no faster (3000 x 1024 28.3 / 28.2)
 //   training pair   1024 x 1024 83.1 / 72.5   4096 x 1024 136.4 / 134.9
 // Eight stages are no faster (gate 1024 x 1024 22.0).
-constexpr int kStages = 5;
+constexpr int kStages = 5, kDeepSteps = 16;
 bool deep_tiles(int mode, int edge, int M, int64_t Nn, int K) {
   const int64_t tiles = (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge);
-  return tiles <= device_compute_units() && K / 64 >= 16 && (edge == 64 || (edge == 128 && mode != 2));
+  return tiles <= device_compute_units() && K / 64 >= kDeepSteps && (edge == 64 || (edge == 128 && mode != 2));
 }
 
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
@@ -406,10 +406,13 @@ hipError_t launch_e(const KvGemmArgs& a, hipStream_t s) {
 
 // Up to two workgroups per compute unit: every 16 tokens read all of the parameters again.  Gate of n tokens, copies and
 // tiled products / these (us):
-//   d 1024 bf16: n 16 27.4 / 15.7   n 256 28.3 / 17.1   n 512 32.0 / 24.1   n 1024 32.5 / 36.0
-//   d 2048 bf16: n 16 48.0 / 20.8   n 256 47.6 / 37.6;   d 1024 fp32: n 16 54.3 / 23.6   n 512 58.3 / 39.4
-bool kv_few_fits(int64_t n, int d) {
-  return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= 2 * (int64_t)kComputeUnits;
+//   d 1024 bf16: n 16 27.4 / 15.7   n 256 28.3 / 17.1;   d 1024 fp32: n 16 54.3 / 23.6   n 512 58.3 / 39.4
+// One per compute unit where the tiled products hold five K-steps (deep_tiles), tiled / these:
+//   d 1024: n 64 17.8 / 15.3   256 18.9 / 16.1   300 19.1 / 21.2   512 20.2 / 22.3;   d 2048: n 128 25.3 / 24.0   190 26.2 / 34.6
+//   training pair: d 1024 n 256 70.1 / 65.9   400 65.4 / 77.7;   d 2048 n 256 93.3 / 124.5
+bool kv_few_fits(int dtype, int64_t n, int d) {
+  const int per_unit = dtype == LMHEAD_BF16 && d / 64 >= kDeepSteps ? 1 : 2;
+  return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= per_unit * (int64_t)kComputeUnits;
 }
 
 hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {

@@ -5,9 +5,11 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# 16 to 21 K-steps, sizes above those that the few-token kernel takes, with a last token tile past n; 15 K-steps; two tiles to a unit
+# 16 to 21 K-steps, sizes above those that the few-token kernel takes, with a last token tile past n; 15 K-steps; two tiles to a unit;
+# the most tokens that the few-token kernel takes and one more
 @pytest.mark.parametrize("n,d", [(1001, 1024), (540, 1088), (500, 1152), (481, 1216), (451, 1280), (421, 1344),
-                                 (4001, 1024), (2201, 1088), (1501, 1152), (1901, 1280), (1301, 1344), (900, 960), (1101, 1024)])
+                                 (4001, 1024), (2201, 1088), (1501, 1152), (1901, 1280), (1301, 1344), (900, 960), (1101, 1024),
+                                 (256, 1024), (257, 1024), (128, 2048), (129, 2048)])
 def test_gate_reconstruction_and_dx(n, d):
     import torch
     import paper_2603_04411_amd as L
