@@ -164,14 +164,22 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
   const int dt = desc->dtype;
   const int d = desc->d;
 
-  KvPrepareArgs pa{};
-  pa.hdr = hdr;
-  pa.count = make_kv_count(k, L.n, d, L.nbuckets, w.at<int32_t>(L.hist));
-  LM_TRY(launch_kv_prepare(L.esz, pa, s));
-  LM_TRY(launch_kv_order(dt, pa.count, off, packed_elems * L.esz, L.ncap, w.at<int32_t>(L.order),
-                         w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), hdr, s));
-
   KvGemmArgs ga{};
+  if (L.n <= kKvGroupTo) {
+    int32_t* const outside = w.at<int32_t>(L.hist);
+    LM_TRY(launch_kv_group(dt, k, off, L.n, d, packed_elems * L.esz, L.nbuckets, kv_tile_edge(dt, 2, d, L.n),
+                           w.at<int32_t>(L.order), w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), outside, s));
+    ga.outside = outside;
+    ga.groups = (int)((L.n + kKvGroup - 1) / kKvGroup);
+  } else {
+    KvPrepareArgs pa{};
+    pa.hdr = hdr;
+    pa.count = make_kv_count(k, L.n, d, L.nbuckets, w.at<int32_t>(L.hist));
+    LM_TRY(launch_kv_prepare(L.esz, pa, s));
+    LM_TRY(launch_kv_order(dt, pa.count, off, packed_elems * L.esz, L.ncap, w.at<int32_t>(L.order),
+                           w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), hdr, s));
+  }
+
   ga.mode = 2;
   ga.A = U_inv;
   ga.ldA = d;

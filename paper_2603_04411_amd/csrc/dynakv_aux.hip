@@ -627,102 +627,109 @@ __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restric
   }
 }
 
-// Offsets and copy of the segments, kKvPackTokens tokens per workgroup, a wavefront per token.  A workgroup adds up
-// what lies before its tokens itself: the totals of the blocks before (or their prefix sum, when there are so many that
-// `scanned` says that has been formed) and the tokens before it in its own block.  That replaces a scan launch and an offset
-// launch: five launches (25 us at 16 tokens, 32 us at 16411) became two, one up to kKvScanBlock tokens.
+// Offsets and copy of the segments, four tokens per wavefront.  A workgroup adds up what lies before its tokens itself.
+// kAll (n up to kPackAll, sixteen wavefronts; four up to 256 tokens): all the counts before them, L2 reads of at most 128 KB, in one launch; the last workgroup
+// sees every count, so it sets the error word and clears the header with one store.  Otherwise (four wavefronts) the totals of
+// the blocks before, which a launch of its own has formed (or their prefix sum, when there are so many that `scanned` says so),
+// and the tokens before it in its own block.
 // A wavefront's four tokens are under way together: one 16-byte chunk per lane of each is requested before the first is
 // stored (one token after the other 262144 x 64 took 61.7 us, now 43.6).
-// Then (no totals launch: blocksum is null) the first workgroup sees every token: it clears the header and sets
-// the error word for all of them with one store.
-constexpr int kKvPackTokens = 16;
-template <typename T>
-__global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, const int32_t* __restrict__ k,
-                                                      const int64_t* __restrict__ blocksum, int scanned, int64_t n,
-                                                      int d, int64_t off_base, int64_t* __restrict__ off,
-                                                      T* __restrict__ packed, int64_t capacity, WsHeader* hdr) {
+constexpr int kPackPer = 4;
+template <typename T, int kWaves, bool kAll>
+__global__ __launch_bounds__(64 * kWaves) void kv_pack_kernel(const T* __restrict__ xt, const int32_t* __restrict__ k,
+                                                              const int64_t* __restrict__ blocksum, int scanned, int64_t n,
+                                                              int d, int64_t off_base, int64_t* __restrict__ off,
+                                                              T* __restrict__ packed, int64_t capacity, WsHeader* hdr) {
   constexpr int EPC = 16 / (int)sizeof(T);   // elements per 16-byte chunk
-  __shared__ int64_t part[4];
-  __shared__ int seg_s[kKvPackTokens], k_s[kKvPackTokens];
+  constexpr int TOK = kPackPer * kWaves, NT = 64 * kWaves;
+  __shared__ int64_t part[kWaves];
+  __shared__ int seg_s[TOK], k_s[TOK], bad_s[kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t0 = (int64_t)blockIdx.x * kKvPackTokens;
-  const int64_t blk = t0 / kKvScanBlock;
+  const int64_t t0 = (int64_t)blockIdx.x * TOK;
   int bad = 0;
-  int64_t before = 0;
-  if (scanned) {
-    if (threadIdx.x == 0) before = blocksum[blk];
+  int64_t before = 0, own;
+  if constexpr (kAll) {
+    constexpr int U = 8;
+    int sum = 0;
+    for (int i = threadIdx.x; i < (int)t0; i += NT * U) {
+      int kk[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) kk[u] = i + u * NT < (int)t0 ? k[i + u * NT] : 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum += seg_len(kk[u], d, bad);
+    }
+    before = sum;
+    own = t0 + threadIdx.x;
   } else {
-    for (int64_t i = threadIdx.x; i < blk; i += 256) before += blocksum[i];
+    const int64_t blk = t0 / kKvScanBlock;
+    if (scanned) {
+      if (threadIdx.x == 0) before = blocksum[blk];
+    } else {
+      for (int64_t i = threadIdx.x; i < blk; i += NT) before += blocksum[i];
+    }
+    own = blk * kKvScanBlock + threadIdx.x;   // one token of the own block per thread
   }
-  const int64_t own = blk * kKvScanBlock + threadIdx.x;   // one token of the own block per thread
-  const int own_k = own < n ? k[own] : 0;
-  const int own_seg = seg_len(own_k, d, bad);
-  if (own < t0) before += own_seg;
-  if (own >= t0 && own < t0 + kKvPackTokens) {
-    seg_s[own - t0] = own_seg;
-    k_s[own - t0] = min(max(own_k, 0), d);
+  if (!kAll || threadIdx.x < TOK) {
+    const int own_k = own < n ? k[own] : 0;
+    const int own_seg = seg_len(own_k, d, bad);
+    if (own < t0) before += own_seg;
+    if (own >= t0 && own < t0 + TOK) {
+      seg_s[own - t0] = own_seg;
+      k_s[own - t0] = min(max(own_k, 0), d);
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
-  if (lane == 0) part[wave] = before;
+  const bool wave_bad = __any(bad);
+  if (lane == 0) {
+    part[wave] = before;
+    bad_s[wave] = wave_bad;
+  }
   __syncthreads();
-  const int64_t base = off_base + ((part[0] + part[1]) + (part[2] + part[3]));
-  if (!blocksum && blockIdx.x == 0) {
-    // one block of tokens: this workgroup holds all the segments; a token is out of room if the running total is
-    __shared__ int wtot[4], werr[4];
-    int incl = own_seg;
+  int64_t base = off_base;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(incl, o);
-      if (lane >= o) incl += y;
-    }
-    if (lane == 63) wtot[wave] = incl;
-    __syncthreads();
-    int64_t end = off_base + incl;
-    for (int w = 0; w < wave; ++w) end += wtot[w];
-    int err = (bad ? kErrKvCount : 0) | (own < n && end > capacity ? kErrKvCapacity : 0);
+  for (int w = 0; w < kWaves; ++w) base += part[w];
+  if (!kAll && bad && own >= t0 && own < t0 + TOK) atomicOr(&hdr->err, kErrKvCount);
+  // every wavefront: the segments' lengths and their exclusive prefix sums, one per lane
+  const int lt = lane & (TOK - 1);
+  const int seg_l = seg_s[lt], k_l = k_s[lt];
+  int excl = seg_l;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o);
-    if (lane == 0) werr[wave] = err;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      hdr->err = (werr[0] | werr[1]) | (werr[2] | werr[3]);
-      hdr->nv = 0;
-    }
+  for (int o = 1; o < TOK; o <<= 1) {
+    const int y = __shfl_up(excl, o, TOK);
+    if (lt >= o) excl += y;
   }
-  if (blocksum && bad && own >= t0 && own < t0 + kKvPackTokens) atomicOr(&hdr->err, kErrKvCount);
-  // every wavefront: the sixteen segments' lengths and their exclusive prefix sums, one per lane
-  const int l16 = lane & (kKvPackTokens - 1);
-  const int seg16 = seg_s[l16], k16 = k_s[l16];
-  int excl16 = seg16;
-#pragma unroll
-  for (int o = 1; o < kKvPackTokens; o <<= 1) {
-    const int y = __shfl_up(excl16, o, kKvPackTokens);
-    if (l16 >= o) excl16 += y;
-  }
-  excl16 -= seg16;
-  if (wave == 0 && lane < kKvPackTokens && t0 + lane < n) {
-    const int64_t o = base + excl16;
+  excl -= seg_l;
+  if (wave == 0 && lane < TOK && t0 + lane < n) {
+    const int64_t o = base + excl;
     off[t0 + lane] = o;
-    if (t0 + lane == n - 1) off[n] = o + seg16;
-    if (blocksum && o + seg16 > capacity) atomicOr(&hdr->err, kErrKvCapacity);
+    if (t0 + lane == n - 1) {
+      off[n] = o + seg_l;
+      if (kAll) {   // the offsets never fall: some segment is out of room if the last one's end is
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) any |= bad_s[w];
+        hdr->err = (any ? kErrKvCount : 0) | (o + seg_l > capacity ? kErrKvCapacity : 0);
+        hdr->nv = 0;
+      }
+    }
+    if (!kAll && o + seg_l > capacity) atomicOr(&hdr->err, kErrKvCapacity);
   }
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-  constexpr int PER = kKvPackTokens / 4;   // tokens of a wavefront
-  u32x4 first[PER];
+  u32x4 first[kPackPer];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int ti = u * 4 + wave;
-    const int seg = __builtin_amdgcn_readlane(seg16, ti);
+  for (int u = 0; u < kPackPer; ++u) {
+    const int ti = u * kWaves + wave;
+    const int seg = __builtin_amdgcn_readlane(seg_l, ti);
     // lanes past the segment, and tokens past the last, read what is there and drop it
     first[u] = *reinterpret_cast<const u32x4*>(xt + min(t0 + ti, n - 1) * d + max(min(lane * EPC, seg - EPC), 0));
   }
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int ti = u * 4 + wave;
+  for (int u = 0; u < kPackPer; ++u) {
+    const int ti = u * kWaves + wave;
     const int64_t tok = t0 + ti;
-    const int seg = __builtin_amdgcn_readlane(seg16, ti), kk = __builtin_amdgcn_readlane(k16, ti);
-    const int64_t o = base + __builtin_amdgcn_readlane(excl16, ti);
+    const int seg = __builtin_amdgcn_readlane(seg_l, ti), kk = __builtin_amdgcn_readlane(k_l, ti);
+    const int64_t o = base + __builtin_amdgcn_readlane(excl, ti);
     if (tok >= n || o + seg > capacity) continue;
     for (int c = lane; c * EPC < seg; c += 64) {
       u32x4 v = c == lane ? first[u] : *reinterpret_cast<const u32x4*>(xt + tok * d + c * EPC);
@@ -738,7 +745,14 @@ __global__ __launch_bounds__(256) void kv_pack_kernel(const T* __restrict__ xt, 
     }
   }
 }
-static_assert(kKvScanBlock == 256 && kKvScanBlock % kKvPackTokens == 0 && kKvPackTokens == 16, "one thread per token of a block");
+// Most tokens of the one-launch form: 8192 components each still add up in 32 bits.  With the one-launch sort below, store and
+// reconstruction, five launches / three, us: 300 x 1024 23.5 / 19.1   1000 x 1024 26.1 / 19.0   4099 x 1024 33.7 / 27.2   8000 x 512
+// 27.2 / 21.7   16411 x 1024 50.3 / 45.6   32768 x 1024 68.9 / 65.0   32768 x 128 26.3 / 25.7: the gain falls as the counts grow.
+constexpr int64_t kPackAll = 32768;
+static_assert(kPackAll * kKvMaxD <= INT32_MAX, "32-bit sums");
+constexpr int kPackWaves = 4, kPackAllWaves = 16;
+static_assert(kKvScanBlock == 64 * kPackWaves && kKvScanBlock % (kPackPer * kPackWaves) == 0 && kPackPer * kPackAllWaves <= 64,
+              "one thread per token of a block, one lane per token of a workgroup");
 
 // ---- grouping by contraction length --------------------------------------------------------
 
@@ -805,6 +819,71 @@ __global__ __launch_bounds__(256) void kv_scatter_kernel(const int32_t* __restri
       pos_off[p] = 0x80000000u;
     }
   }
+}
+
+// Up to kKvGroupTo tokens one launch instead of two: a workgroup sorts kKvGroup tokens by itself, in LDS.  The tiles of a group
+// are then a little less even than those of all the tokens (16 tiles of 128 tokens each, about half a K-step of 7.5 more), which costs
+// less than the counts' launch did.  Rank r tiles of all groups come before the rank r + 1 tiles, so that the long ones still start
+// first; only the last group can have fewer tiles than the others.
+__global__ __launch_bounds__(1024) void kv_group_kernel(const int32_t* __restrict__ k, const int64_t* __restrict__ off,
+                                                        int64_t n, int d, int esz, int64_t bytes, int nbuckets, int edge,
+                                                        int32_t* __restrict__ order, uint32_t* __restrict__ pos_off,
+                                                        int32_t* __restrict__ pos_len, int32_t* __restrict__ outside_out) {
+  constexpr int PER = kKvGroup / 1024;
+  extern __shared__ int32_t h[];   // [nbuckets] tokens, [nbuckets] first rank
+  int32_t* const start = h + nbuckets;
+  const int groups = gridDim.x, g = blockIdx.x;
+  const int g0 = g * kKvGroup, gn = min((int)n - g0, kKvGroup);
+  const int last_tiles = ((int)n - (groups - 1) * kKvGroup + edge - 1) / edge;
+  for (int i = threadIdx.x; i < nbuckets; i += 1024) h[i] = 0;
+  int kk[PER];
+  int64_t o[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = u * 1024 + threadIdx.x;
+    kk[u] = i < gn ? k[g0 + i] : 0;
+    o[u] = i < gn ? off[g0 + i] : 0;
+  }
+  __syncthreads();
+  int rank[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    rank[u] = u * 1024 + (int)threadIdx.x < gn ? atomicAdd(&h[bucket_of(kk[u], d, esz)], 1) : 0;
+  __syncthreads();
+  for (int b = threadIdx.x; b < nbuckets; b += 1024) {
+    int longer = 0;
+    for (int q = b + 1; q < nbuckets; ++q) longer += h[q];
+    start[b] = longer;
+  }
+  __syncthreads();
+  auto position = [&](int p) {
+    const int r = p / edge;
+    const int tile = r < last_tiles ? r * groups + g : last_tiles * groups + (r - last_tiles) * (groups - 1) + g;
+    return tile * edge + p % edge;
+  };
+  int bad = 0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = u * 1024 + threadIdx.x;
+    if (i >= gn) continue;
+    int clamped = 0;
+    const int seg = seg_len(kk[u], d, clamped);
+    const bool outside = o[u] < 0 || (o[u] & (DYNAKV_GRANULE - 1)) || (o[u] + seg) * esz > bytes;
+    if (outside) bad = 1;
+    const int pos = position(start[bucket_of(kk[u], d, esz)] + rank[u]);
+    order[pos] = g0 + i;
+    pos_len[pos] = seg * esz;
+    pos_off[pos] = outside ? 0x80000000u : (uint32_t)(o[u] * esz);   // out of range: every load of the row gives zeros
+  }
+  // the rest of the last group's last tile
+  for (int p = gn + threadIdx.x; p < (gn + edge - 1) / edge * edge; p += 1024) {
+    const int pos = position(p);
+    order[pos] = -1;
+    pos_len[pos] = 0;
+    pos_off[pos] = 0x80000000u;
+  }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) outside_out[g] = bad;
 }
 
 // ---- retain rate ----------------------------------------------------------------------------
@@ -1015,17 +1094,28 @@ hipError_t launch_kv_store(int dtype, const void* xt, const int32_t* k, int64_t 
   // tokens of 64 components: 524288 86.2 us without it, 79.4 with it).
   constexpr int64_t kScanFrom = 1024;
   const int scanned = nblocks > kScanFrom ? 1 : 0;
-  if (nblocks > 1)
+  const bool all = n <= kPackAll;
+  if (!all)
     hipLaunchKernelGGL(kv_scan_totals_kernel, dim3((unsigned)nblocks), dim3(kKvScanBlock), 0, s, k, n, d, blocksum, hdr);
   if (scanned) hipLaunchKernelGGL(kv_scan_blocks_kernel, dim3(1), dim3(1024), 0, s, blocksum, (int)nblocks);
-  const int64_t* const totals = nblocks > 1 ? blocksum : nullptr;
-  const dim3 grid((unsigned)((n + kKvPackTokens - 1) / kKvPackTokens));
+  const int waves = n > kKvScanBlock && all ? kPackAllWaves : kPackWaves;
+  const dim3 grid((unsigned)((n + kPackPer * waves - 1) / (kPackPer * waves))), block(64 * waves);
+  auto launch = [&](auto kernel, auto* x, auto* out) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, x, k, blocksum, scanned, n, d, off_base, off, out, capacity, hdr);
+  };
+  auto typed = [&](auto* x, auto* out) {
+    using T = std::remove_reference_t<decltype(*out)>;
+    if (n <= kKvScanBlock)   // few counts to add up: 16 tokens a workgroup
+      launch(kv_pack_kernel<T, kPackWaves, true>, x, out);
+    else if (all)
+      launch(kv_pack_kernel<T, kPackAllWaves, true>, x, out);
+    else
+      launch(kv_pack_kernel<T, kPackWaves, false>, x, out);
+  };
   if (dtype == LMHEAD_BF16)
-    hipLaunchKernelGGL(kv_pack_kernel<__bf16>, grid, dim3(256), 0, s, static_cast<const __bf16*>(xt), k, totals, scanned,
-                       n, d, off_base, off, static_cast<__bf16*>(packed), capacity, hdr);
+    typed(static_cast<const __bf16*>(xt), static_cast<__bf16*>(packed));
   else
-    hipLaunchKernelGGL(kv_pack_kernel<float>, grid, dim3(256), 0, s, static_cast<const float*>(xt), k, totals, scanned, n,
-                       d, off_base, off, static_cast<float*>(packed), capacity, hdr);
+    typed(static_cast<const float*>(xt), static_cast<float*>(packed));
   return hipGetLastError();
 }
 
@@ -1035,6 +1125,14 @@ hipError_t launch_kv_order(int dtype, const KvCount& c, const int64_t* off, int6
   hipLaunchKernelGGL(kv_scatter_kernel, dim3((unsigned)c.blocks), dim3(256), 2 * c.nbuckets * sizeof(int32_t), s, c.k,
                      off, c.n, ncap, c.d, esz, bytes, c.nbuckets, c.hist, c.blocks, c.per_block, order, pos_off, pos_len,
                      hdr);
+  return hipGetLastError();
+}
+
+hipError_t launch_kv_group(int dtype, const int32_t* k, const int64_t* off, int64_t n, int d, int64_t bytes, int nbuckets, int edge,
+                           int32_t* order, uint32_t* pos_off, int32_t* pos_len, int32_t* outside, hipStream_t s) {
+  const int esz = dtype == LMHEAD_BF16 ? 2 : 4;
+  hipLaunchKernelGGL(kv_group_kernel, dim3((unsigned)((n + kKvGroup - 1) / kKvGroup)), dim3(1024),
+                     2 * nbuckets * sizeof(int32_t), s, k, off, n, d, esz, bytes, nbuckets, edge, order, pos_off, pos_len, outside);
   return hipGetLastError();
 }
 

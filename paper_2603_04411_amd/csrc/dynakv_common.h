@@ -139,6 +139,8 @@ struct KvGemmArgs {
   const int32_t* order;     // mode 2
   const uint32_t* pos_off;  // mode 2
   const int32_t* pos_len;   // mode 2
+  const int32_t* outside;   // mode 2, unless null: launch_kv_group's flags, from which the header is set
+  int groups;
   void* out_e;
   float* out_f;
   int64_t ldo;
@@ -148,6 +150,7 @@ struct KvGemmArgs {
   int walk_len;         // set by the launcher: length of the tile walk (tile_map.h)
 };
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
+int kv_tile_edge(int dtype, int mode, int M, int64_t Nn);   // of the tiles that launch_kv_gemm takes
 
 // out[n][j] = sum_k x[n][k] M[k][j], or with `rows` sum_k x[n][k] M[j][k], for few tokens: M [d x d] as the caller has
 // it (no copy), 16 tokens x 64 columns per workgroup.  out_e (storage type) or out_f (fp32), dense rows of d, whichever is
@@ -238,6 +241,14 @@ hipError_t launch_kv_prepare(int esz, const KvPrepareArgs& a, hipStream_t s);
 // The counts have been made by launch_kv_prepare.
 hipError_t launch_kv_order(int dtype, const KvCount& c, const int64_t* off, int64_t bytes, int64_t ncap, int32_t* order,
                            uint32_t* pos_off, int32_t* pos_len, WsHeader* hdr, hipStream_t s);
+
+// The same in one launch: the tokens are sorted within groups of kKvGroup, whose tiles of `edge` tokens are dealt out in turn.
+// outside[group]: whether a segment of the group does not lie inside the store.
+constexpr int kKvGroup = 2048;
+constexpr int64_t kKvGroupTo = 32768;
+static_assert(kKvGroup % kTile == 0 && kKvGroupTo / kKvGroup <= kKvCountBlocks, "whole tiles; the flags take the counts' place");
+hipError_t launch_kv_group(int dtype, const int32_t* k, const int64_t* off, int64_t n, int d, int64_t bytes, int nbuckets, int edge,
+                           int32_t* order, uint32_t* pos_off, int32_t* pos_len, int32_t* outside, hipStream_t s);
 
 // Retain rates; clears the header.
 hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, float alpha, float* out,

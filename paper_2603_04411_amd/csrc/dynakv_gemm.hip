@@ -257,9 +257,14 @@ __device__ inline void kv_tile(const KvGemmArgs& a, int wg, char* smem) {
 template <typename E, int Edge, int Mode, int Stages>
 __global__ __launch_bounds__(256, wg_per_cu(Edge, Stages)) void kv_gemm_kernel(KvGemmArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  if (a.clear && blockIdx.x == 0 && threadIdx.x == 0) {
-    a.hdr->err = 0;
-    a.hdr->nv = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (a.clear || (Mode == 2 && a.outside)) {
+      int out = 0;
+      if constexpr (Mode == 2)
+        for (int g = 0; g < a.groups; ++g) out |= a.outside[g];
+      a.hdr->err = out ? kErrKvCapacity : 0;
+      a.hdr->nv = 0;
+    }
   }
   for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Edge, Mode, Stages>(a, wg, smem);
 }
@@ -431,6 +436,8 @@ hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
   }
   return hipGetLastError();
 }
+
+int kv_tile_edge(int dtype, int mode, int M, int64_t Nn) { return tile_edge(dtype != LMHEAD_BF16, mode, M, Nn); }
 
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s) {
   return dtype == LMHEAD_BF16 ? launch_e<bf16_tag>(a, s) : launch_e<f32_tag>(a, s);
