@@ -384,7 +384,7 @@ static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
 template <typename E, int Mode>
 hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
   const int edge = tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn);
-  if constexpr (Elem<E>::size == 2) {
+  if constexpr (Elem<E>::size == 2 && Elem<E>::block == 16) {
     if (deep_tiles(Mode, edge, a.M, a.Nn, a.K)) {
       if (edge == 64) return launch_tiles<E, 64, Mode, kStages>(a, s);
       if constexpr (Mode != 2) return launch_tiles<E, 128, Mode, kStages>(a, s);
