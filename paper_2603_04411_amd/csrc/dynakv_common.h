@@ -74,7 +74,7 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.ncap = (int64_t)round_up((size_t)L.n, kTile);
   L.dp = (int64_t)round_up((size_t)L.d, kTile);
   // Tile edge and slices of the contraction over the tokens: as many slices as give one workgroup per compute unit,
-  // on the largest edge whose slices then keep 16 K-steps (of 128 bytes), else edge 64 with at least 2 each.
+  // on the largest edge whose slices then keep 16 K-steps (of 128 bytes; edge 256: 32), else edge 64 with at least 2 each.
   // dW alone / whole backward call, us, bf16 unless said, with the choice in brackets:
   //     n x d           edge 256         edge 128          edge 64          (slices giving 256 workgroups, or the best)
   //     32768 x 1024    [72.6 / 611]     99.6 / 638        208 / 867
@@ -83,6 +83,9 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   //     512 x 1024      17.4 / 117       11.3 / 100        [9.8 / 93]
   //     8192 x 256      18.0 / 115       11.5 / 102        [9.6 / 92]
   //     300 x 128 fp32  20.6 / 83        9.9 / 63          [7.6 / 59]
+  // Training pair, edge 256 / 128, where slices of 256 wide tiles have 16 K-steps: 4096 x 2048 346.5 / 309.7, 16384 x 1024
+  // 398.5 / 383.0, fp32 8192 x 1024 978 / 943; 23: 6000 x 2048 474 / 449, 24000 x 1024 596 / 583; 32: 8192 x 2048 568 / 570,
+  // 32768 x 1024 708 / 707, fp32 16384 x 1024 1874 / 1853; 64: 65536 x 1024 1317 / 1364.
   {
     const int64_t ksteps = L.ncap * L.esz / 128;
     for (int edge : {256, 128, 64}) {
@@ -93,7 +96,7 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
       if (ks < 1) ks = 1;
       L.edge = edge;
       L.ksplit = (int)ks;
-      if (last || ksteps / ks >= 16) break;
+      if (last || ksteps / ks >= (edge == 256 ? 32 : 16)) break;
     }
   }
   {
