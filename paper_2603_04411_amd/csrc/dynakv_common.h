@@ -153,7 +153,7 @@ struct KvGemmArgs {
   int walk_len;         // set by the launcher: length of the tile walk (tile_map.h)
 };
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
-int kv_tile_edge(int dtype, int mode, int M, int64_t Nn);   // of the tiles that launch_kv_gemm takes
+int kv_tile_edge(int dtype, int mode, int d, int64_t n);   // of the tiles that launch_kv_gemm takes
 
 // out[n][j] = sum_k x[n][k] M[k][j], or with `rows` sum_k x[n][k] M[j][k], for few tokens: M [d x d] as the caller has
 // it (no copy), 16 tokens x 64 columns per workgroup.  out_e (storage type) or out_f (fp32), dense rows of d, whichever is

@@ -34,21 +34,42 @@ constexpr int kKvMapBx = 4, kKvMapBy = 4;
 //     edge 128    14.3   15.3   15.7   17.2   25.3   35.9   44.5    179
 //     edge 256    29.4   30.5   30.8   31.9   34.5   37.0   42.2    143
 // (fp32, n = 1024: 26.8 / 66.8 / 239; n = 4096: 80 / 78 / 241.)  So: the smallest edge whose tiles run in one round, two to
-// a compute unit.  The reconstruction's tiles differ in length, which leaves its rounds more ragged, and more
-// and smaller tiles even them out: edge 128 up to four rounds (n = 16411, 32768, 65536: 32.8 / 51.6 / 95.5 against
-// 39.0 / 54.6 / 91.8 with edge 256).
-// Beyond that the padding of the d columns counts too: 320 columns are 512 in 256 wide tiles and 384 in 128 wide ones,
+// a compute unit.
+// Beyond that the padding of the d columns counts: 320 columns are 512 in 256 wide tiles and 384 in 128 wide ones,
 // 128 columns 256 and 128 (gate of 37065 x 320 94 -> 63 us, fp32 40000 x 320 354 -> 195, 262144 x 128 201 -> 147).
-int tile_edge(bool f32, int mode, int M, int64_t Nn) {
-  const int64_t room = 2 * (int64_t)device_compute_units();
+// In bf16 so do the rounds: 256 wide tiles have a compute unit each, and a round that is not full takes most of a full one's time;
+// 128 wide ones take longer per round, the more so the longer the contraction, but half as long as that.  wide_cost and
+// narrow_cost are fits, in full rounds of 256 wide tiles, to (training pair, us, edge 128 / 256):
+//   d 1024: n 9000 262 / 288   12000 309 / 331   17000 414 / 501   20000 469 / 541   24000 555 / 587   28000 653 / 645   32768 774 / 726
+//           36000 820 / 865   40000 912 / 911   49152 1099 / 1015   65536 1364 / 1317
+//   d 2048: n 4500 394 / 387   8192 619 / 569   9000 708 / 774   10000 766 / 816   12000 891 / 872   16384 1168 / 1042   20000 1403 / 1349
+//   d 512:  n 20000 206 / 236   32768 293 / 309   40000 349 / 421   65536 569 / 570   80000 695 / 721   120000 1015 / 1017
+//   others: 12000 x 1536 603 / 685   30000 x 768 497 / 542   70000 x 256 281 / 359   200000 x 256 729 / 822
+// and, the reconstruction counting half the K-steps as its tokens do (store and reconstruction): d 1024: n 32768 67 / 71   65536
+// 123 / 126   100000 184 / 200   131072 274 / 253;   d 512: 100000 82 / 96   200000 158 / 177;   d 2048: 12000 80 / 86   24000 138 / 122.
+// The choice is within 3 % of the better edge at all of these.
+int tile_edge(bool f32, int mode, int M, int64_t Nn, int K) {
+  const int64_t cus = device_compute_units();
   auto tiles = [&](int edge) { return (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge); };
-  if (tiles(64) <= room) return 64;
-  if (tiles(128) <= (mode == 2 ? 4 : 1) * room) return 128;
+  if (tiles(64) <= 2 * cus) return 64;
+  if (tiles(128) <= (f32 && mode == 2 ? 8 : 2) * cus) return 128;
   int best = 256;
-  auto cost = [&](int edge) { return (float)((M + edge - 1) / edge * edge) / tile_rate(edge, f32); };
-  for (int edge : {128, 64})
-    if (cost(edge) < cost(best)) best = edge;
-  return best;
+  auto padded = [&](int edge) { return (float)((M + edge - 1) / edge * edge) / tile_rate(edge, f32); };
+  if (!f32) {
+    auto rounds = [&](int edge, int64_t slots, float least) {   // a last round that is not full counts at least `least`
+      const int64_t full = tiles(edge) / slots;
+      const float rest = (float)(tiles(edge) % slots) / (float)slots;
+      return (float)full + (rest > 0.f ? (rest > least ? rest : least) : 0.f);
+    };
+    const float steps = (float)(K / 64) * (mode == 2 ? 0.5f : 1.f);
+    const float slope = 1.03f + 0.015f * steps, first = 0.45f - 0.0125f * steps;
+    const float wide_cost = rounds(256, cus, 0.8f);
+    const float narrow_cost = (slope < 1.3f ? slope : 1.3f) * rounds(128, 2 * cus, 0.5f) / 2 - (first > 0.f ? first : 0.f);
+    best = narrow_cost < wide_cost ? 128 : 256;
+  } else if (padded(128) < padded(256)) {
+    best = 128;
+  }
+  return padded(64) < padded(best) ? 64 : best;
 }
 // Workgroups of one tile edge that share a compute unit (bound by LDS: five slots of edge x 128 bytes each, or both operands' stages).
 constexpr int wg_per_cu(int edge, int stages) { return stages ? 640 / (edge * stages) : 256 / edge; }
@@ -383,7 +404,7 @@ static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
 
 template <typename E, int Mode>
 hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
-  const int edge = tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn);
+  const int edge = tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn, a.K);
   if constexpr (Elem<E>::size == 2 && Elem<E>::block == 16) {
     if (deep_tiles(Mode, edge, a.M, a.Nn, a.K)) {
       if (edge == 64) return launch_tiles<E, 64, Mode, kStages>(a, s);
@@ -437,7 +458,7 @@ hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int kv_tile_edge(int dtype, int mode, int M, int64_t Nn) { return tile_edge(dtype != LMHEAD_BF16, mode, M, Nn); }
+int kv_tile_edge(int dtype, int mode, int d, int64_t n) { return tile_edge(dtype != LMHEAD_BF16, mode, d, n, d); }
 
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s) {
   return dtype == LMHEAD_BF16 ? launch_e<bf16_tag>(a, s) : launch_e<f32_tag>(a, s);
