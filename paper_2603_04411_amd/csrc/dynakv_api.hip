@@ -299,6 +299,12 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
 
+  // x where it lies, unless its rows are too far apart: then a dense copy in the place of the logits, which are done with
+  const bool dense = kv_gradient_needs_dense(desc->ldx);
+  if (dense) {
+    TimedLaunch tl(11, s);
+    LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, at(L.logits), s));
+  }
   // Parameter gradients: contractions over the tokens, both in one launch, cut into ksplit slices of the token range (one:
   // stored directly).  dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
   GemmTArgs ta{};
@@ -306,11 +312,11 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ta.A2 = at(L.gxt);
   ta.ldA = d;
   ta.B = xt;
-  ta.B2 = x;
+  ta.B2 = dense ? at(L.logits) : x;
   ta.ldB = d;
-  ta.ldB2 = desc->ldx;
+  ta.ldB2 = dense ? d : desc->ldx;
   ta.a_bytes = ta.a2_bytes = ta.b_bytes = L.n * d * L.esz;
-  ta.b2_bytes = ((L.n - 1) * desc->ldx + d) * L.esz;
+  ta.b2_bytes = ((L.n - 1) * ta.ldB2 + d) * L.esz;
   ta.M = d;
   ta.n_limit = d;
   ta.K = L.n;

@@ -754,6 +754,17 @@ constexpr int kPackWaves = 4, kPackAllWaves = 16;
 static_assert(kKvScanBlock == 64 * kPackWaves && kKvScanBlock % (kPackPer * kPackWaves) == 0 && kPackPer * kPackAllWaves <= 64,
               "one thread per token of a block, one lane per token of a workgroup");
 
+// ---- dense copy of x ------------------------------------------------------------------------
+
+// A wavefront per row, 16 bytes per lane.  Only for rows megabytes apart, of which memory holds few: a launch and little more.
+__global__ __launch_bounds__(256) void kv_dense_kernel(const char* __restrict__ x, int64_t pitch, int64_t n, int row_bytes,
+                                                       char* __restrict__ out) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= n) return;
+  for (int c = (threadIdx.x & 63) * 16; c < row_bytes; c += 64 * 16)
+    *reinterpret_cast<uint4*>(out + r * row_bytes + c) = *reinterpret_cast<const uint4*>(x + r * pitch + c);
+}
+
 // ---- grouping by contraction length --------------------------------------------------------
 
 // Position of every token in descending order of K-step count.  Block b owns the tokens that block b of
@@ -1116,6 +1127,12 @@ hipError_t launch_kv_store(int dtype, const void* xt, const int32_t* k, int64_t 
     typed(static_cast<const __bf16*>(xt), static_cast<__bf16*>(packed));
   else
     typed(static_cast<const float*>(xt), static_cast<float*>(packed));
+  return hipGetLastError();
+}
+
+hipError_t launch_kv_dense(const void* x, int64_t pitch, int64_t n, int row_bytes, void* out, hipStream_t s) {
+  hipLaunchKernelGGL(kv_dense_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, static_cast<const char*>(x), pitch, n,
+                     row_bytes, static_cast<char*>(out));
   return hipGetLastError();
 }
 

@@ -155,6 +155,9 @@ struct KvGemmArgs {
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
 int kv_tile_edge(int dtype, int mode, int d, int64_t n);   // of the tiles that launch_kv_gemm takes
 
+// out = the n rows of row_bytes (a multiple of 16), `pitch` bytes apart, one behind the other.
+hipError_t launch_kv_dense(const void* x, int64_t pitch, int64_t n, int row_bytes, void* out, hipStream_t s);
+
 // out[n][j] = sum_k x[n][k] M[k][j], or with `rows` sum_k x[n][k] M[j][k], for few tokens: M [d x d] as the caller has
 // it (no copy), 16 tokens x 64 columns per workgroup.  out_e (storage type) or out_f (fp32), dense rows of d, whichever is
 // non-null; accumulate: out_e is added to.  Clears the header unless null.

@@ -262,7 +262,7 @@ struct GemmTile {
   static constexpr int KROWS = KB / Elem<E>::size;
   static constexpr int TROW = BM * Elem<E>::size;
   static constexpr int TRPG = 1024 / TROW;
-  static constexpr uint32_t kWindow = 0x7fffffffu;   // most bytes that a buffer descriptor covers
+  static constexpr uint32_t kWindow = (uint32_t)kWindowBytes;
   __device__ static inline int swzT(int k) {
     return BM == 64 ? ((k >> 1) & 1) | ((k >> 2) & 2) : (k & 3) | ((k >> 1) & 4);
   }

@@ -606,9 +606,9 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void gemm_t_kernel(GemmTAr
   } else {
     // A K-major operand advances by KROWS of its rows per K-step.  What lies past its end (the rows that fill the last
     // K-step up) has to read as zeros: a buffer window does that, of at most 2 GiB; operands beyond that are taken in
-    // pieces, each of which fills the pipeline anew (3 us).
+    // pieces, each of which fills the pipeline anew (about a microsecond).
     const int64_t stepA = G::KROWS * pitchA, stepB = kTB ? G::KROWS * pitchB : (int64_t)G::KB;
-    const int piece = (int)(G::kWindow / (kTB && stepB > stepA ? stepB : stepA));
+    const int piece = window_ksteps(kTB && stepB > stepA ? stepB : stepA);   // at least one: launch_gemm_t
     const int64_t bytesA = second ? a.a2_bytes : a.a_bytes, bytesB = second ? a.b2_bytes : a.b_bytes;
     auto window = [](int64_t left) { return (uint32_t)(left < 0 ? 0 : left < G::kWindow ? left : G::kWindow); };
     int k = 0;
@@ -761,6 +761,10 @@ static hipError_t launch_gemm_t_impl(const GemmTArgs& a, hipStream_t s) {
 
 hipError_t launch_gemm_t(int dtype, const GemmTArgs& a, hipStream_t s, int role) {
   if (role < 0) role = a.k_from_nv ? 1 : 0;
+  int64_t pitch = a.ldA;   // of the K-major operands, whose K-step of 128 bytes of K has to fit a window
+  if (role != 0)
+    for (int64_t p : {a.ldB, a.A2 ? a.ldB2 : a.ldB}) pitch = p > pitch ? p : pitch;
+  if (pitch > longest_pitch(1)) return hipErrorInvalidValue;
   if (dtype == LMHEAD_BF16)
     return role == 0   ? launch_gemm_t_impl<bf16_tag, 0>(a, s)
            : role == 1 ? launch_gemm_t_impl<bf16_tag, 1>(a, s)

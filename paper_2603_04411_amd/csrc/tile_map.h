@@ -78,6 +78,19 @@ inline float tile_rate(int edge, bool f32) {
   return edge == 256 ? 1.f : edge == 128 ? (f32 ? 1.f : 0.8f) : (f32 ? 0.95f : 0.57f);
 }
 
+// Most bytes that a buffer descriptor covers, and the K-steps of a K-major operand, `step` bytes apart, inside them: a longer
+// contraction is taken in pieces of that many.
+constexpr int64_t kWindowBytes = 0x7fffffff;
+LMHEAD_HD inline int window_ksteps(int64_t step) { return (int)(kWindowBytes / step); }
+// A K-step of a K-major operand is 128 times its row pitch in elements (64 rows in bf16, 32 in fp32): the longest pitch that leaves
+// room for `ksteps` of them.
+constexpr int64_t longest_pitch(int ksteps) { return kWindowBytes / (128 * ksteps); }
+// dU reads x where it lies while a window holds this many K-steps, and a dense copy of it beyond.  Backward call, bf16, us, where it
+// lies / copied, at 7, 3 and 1 K-steps a window: 1024 x 1024 48.8 / 48.6   50.2 / 48.6   56.0 / 48.8;   4096 x 1024 92.6 / 96.2
+// 94.9 / 95.6   102.1 / 95.6;   16384 x 1024 at 15 and 3: 255 / 254   261 / 257.
+constexpr int kLeastPiece = 2;
+inline bool kv_gradient_needs_dense(int64_t ldx) { return ldx > longest_pitch(kLeastPiece); }
+
 // Compute units that the launch rules count on (a GPU need not be present where workspaces are sized).
 constexpr int kComputeUnits = 256;
 

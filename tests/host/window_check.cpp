@@ -1,0 +1,32 @@
+// Host check of the pieces in which a K-major operand beyond one buffer window is contracted: whatever the row pitch of x, the
+// operand that dU is given has pieces of at least one K-step that lie inside a window, so that the loop over them ends.
+#include <algorithm>
+#include <cstdio>
+using std::min;
+#define LMHEAD_TILE_MAP_HOST 1
+#include "../../paper_2603_04411_amd/csrc/tile_map.h"
+
+int main() {
+  using namespace lmhead;
+  long bad = 0, cases = 0;
+  for (int esz : {2, 4})
+    for (int d : {64, 1024, 8192})
+      for (int64_t ldx = d; ldx > 0 && ldx < (int64_t)1 << 60; ldx += ldx / 97 / 8 * 8 + 8) {
+        ++cases;
+        const int64_t pitch = kv_gradient_needs_dense(ldx) ? d : ldx;
+        const int64_t step = 128 / esz * (pitch * esz);
+        const int piece = window_ksteps(step);
+        if (piece < 1 || piece * step > kWindowBytes || pitch > longest_pitch(1)) { ++bad; continue; }
+        int turns = 0;
+        for (int k = 0; k < 64; k += piece) ++turns;
+        if (turns > 64) ++bad;
+      }
+  // the strides around the line, and the first that one K-step does not fit
+  for (int64_t ldx : {(int64_t)64, (int64_t)1 << 20, (int64_t)1 << 22, ((int64_t)1 << 23) - 8})
+    if (++cases, kv_gradient_needs_dense(ldx)) ++bad;
+  for (int64_t ldx : {(int64_t)1 << 23, ((int64_t)1 << 24) - 8, (int64_t)1 << 24, (int64_t)1 << 26, (int64_t)1 << 40})
+    if (++cases, !kv_gradient_needs_dense(ldx)) ++bad;
+  if (window_ksteps(128 * ((int64_t)1 << 24)) != 0) ++bad;
+  std::printf("cases=%ld bad=%ld\n", cases, bad);
+  return bad != 0;
+}

@@ -31,6 +31,10 @@ def test_gradient_edges_follow_the_length_of_the_contraction(tmp_path):
     _run_host_check(tmp_path, "gradient_edge_check")
 
 
+def test_k_major_operands_are_taken_in_pieces_of_a_window(tmp_path):
+    _run_host_check(tmp_path, "window_check")
+
+
 @pytest.mark.parametrize("source", ["lmhead_gemm.hip", "dynakv_gemm.hip", "dynakv_gate.hip"])
 def test_the_32x32x16_form_of_the_bf16_main_loop_still_compiles(source):
     from paper_2603_04411_amd import build
