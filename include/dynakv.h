@@ -61,7 +61,8 @@ typedef struct dynakv_desc {
   int32_t dtype;    /* LMHEAD_F32 or LMHEAD_BF16: storage type of x, U, W, U_inv, x~, the      */
                     /* store and x_bar.  n * d * sizeof(type) must not exceed 2^31 - 2^20.     */
   uint32_t flags;   /* DYNAKV_FLAG_*                                                           */
-  int64_t ldx;      /* row stride of x in elements (>= d, ldx * sizeof(type) % 16 == 0)        */
+  int64_t ldx;      /* row stride of x in elements (>= d, ldx * sizeof(type) % 16 == 0; rows   */
+                    /* of which 64 to 256 do not lie within 2 GiB are copied together first)   */
   int64_t reserved; /* must be 0                                                               */
 } dynakv_desc;
 

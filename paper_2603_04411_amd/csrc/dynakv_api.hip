@@ -96,14 +96,20 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
                           k, m, xhat, s));
     return LMHEAD_OK;
   }
+  // rows too far apart for a tile's window: a dense copy, where the logits will be
+  const bool dense = kv_tiles_need_dense(L.n, kv_tile_edge(dt, 0, d, L.n), desc->ldx, d, L.esz);
+  if (dense) {
+    TimedLaunch tl(4, s);
+    LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, w.at<void>(L.logits), s));
+  }
   KvGemmArgs ga{};
   ga.mode = 0;
   ga.A = U;
   ga.ldA = d;
   ga.bytesA = (int64_t)d * d * L.esz;
   ga.clear = true;
-  ga.B = x;
-  ga.ldB = desc->ldx;
+  ga.B = dense ? w.at<void>(L.logits) : x;
+  ga.ldB = dense ? d : desc->ldx;
   ga.M = d;
   ga.Nn = L.n;
   ga.K = d;

@@ -90,6 +90,11 @@ constexpr int64_t longest_pitch(int ksteps) { return kWindowBytes / (128 * kstep
 // 94.9 / 95.6   102.1 / 95.6;   16384 x 1024 at 15 and 3: 255 / 254   261 / 257.
 constexpr int kLeastPiece = 2;
 inline bool kv_gradient_needs_dense(int64_t ldx) { return ldx > longest_pitch(kLeastPiece); }
+// The tiled projection addresses the rows of a token tile through one window: x is copied where they do not fit.
+inline bool kv_tiles_need_dense(int64_t n, int edge, int64_t ldx, int d, int esz) {
+  const int64_t rows = n < edge ? n : edge;
+  return rows > 1 && ldx > (kWindowBytes / esz - d) / (rows - 1);
+}
 
 // Compute units that the launch rules count on (a GPU need not be present where workspaces are sized).
 constexpr int kComputeUnits = 256;

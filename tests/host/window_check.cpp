@@ -1,5 +1,5 @@
-// Host check of the pieces in which a K-major operand beyond one buffer window is contracted: whatever the row pitch of x, the
-// operand that dU is given has pieces of at least one K-step that lie inside a window, so that the loop over them ends.
+// Host check of the buffer windows through which the gate reads x, whatever its row pitch: dU, which takes x in pieces beyond one
+// window, gets pieces of at least one K-step, so that the loop over them ends; the rows of a token tile of x U lie inside one.
 #include <algorithm>
 #include <cstdio>
 using std::min;
@@ -21,6 +21,17 @@ int main() {
         for (int k = 0; k < 64; k += piece) ++turns;
         if (turns > 64) ++bad;
       }
+  // the rows of a token tile of x~ = x U, as its offsets address them, end inside a window; a copy is made only where they do not
+  for (int esz : {2, 4})
+    for (int d : {64, 1024, 8192})
+      for (int edge : {64, 128, 256})
+        for (int64_t n : {1, 2, 63, 64, 65, 300, 100000})
+          for (int64_t ldx = d; ldx < (int64_t)1 << 32; ldx += ldx / 97 / 8 * 8 + 8) {
+            ++cases;
+            const int64_t pitch = kv_tiles_need_dense(n, edge, ldx, d, esz) ? d : ldx;
+            if ((min(n, (int64_t)edge) - 1) * pitch * esz + d * esz > kWindowBytes) ++bad;
+            if (pitch == d && ldx > d && (min(n, (int64_t)edge) - 1) * ldx * esz + d * esz <= kWindowBytes) ++bad;
+          }
   // the strides around the line, and the first that one K-step does not fit
   for (int64_t ldx : {(int64_t)64, (int64_t)1 << 20, (int64_t)1 << 22, ((int64_t)1 << 23) - 8})
     if (++cases, kv_gradient_needs_dense(ldx)) ++bad;

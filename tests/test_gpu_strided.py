@@ -13,7 +13,7 @@ def _problem(n, d, ldx, dtype):
     x = torch.full(((n - 1) * ldx + d,), float("nan"), dtype=tdt, **cuda).as_strided((n, d), (ldx, 1))
     x.copy_(torch.randn(n, d, generator=g, **cuda))
     U = torch.linalg.qr(torch.randn(d, d, generator=g, **cuda))[0].contiguous().to(tdt)
-    W = (1.5 * torch.randn(d, d, generator=g, **cuda)).to(tdt)
+    W = (12 / d ** 0.5 * torch.randn(d, d, generator=g, **cuda)).to(tdt)    # logits of standard deviation 12
     b = torch.randn(d, generator=g, **cuda)
     desc = L.make_kv_desc(n, d, dtype, ldx=ldx)
     assert L.dynakv_validate_desc(desc) == 0
@@ -43,3 +43,27 @@ def test_backward(n, d, ldx, dtype):
     # the bounds of test_gpu_dynakv_bwd.py: g_l and g_x~ are rounded to the storage type before they are contracted
     for got, ref in ((dx, gxt @ U.double().t()), (dU, x.double().t() @ gxt), (dW, xt.double().t() @ gl), (db, gl.sum(0))):
         assert float((got.double() - ref).norm() / ref.norm()) <= (1e-2 if dtype == "bf16" else 1e-4)
+
+
+# few tokens (any stride as it is); 64 and 128 wide tiles on both sides of their longest stride
+@pytest.mark.parametrize("n,d,ldx,dtype", [
+    (16, 1024, 1 << 26, "bf16"), (260, 1024, 17043504, "bf16"), (260, 1024, 17043512, "bf16"), (300, 1024, 1 << 25, "bf16"),
+    (400, 1344, 8521736, "f32"), (400, 1344, 8521740, "f32"), (2050, 1024, 8454648, "bf16"), (2050, 1024, 8454656, "bf16")])
+def test_gate(n, d, ldx, dtype):
+    import torch
+    L, desc, g, x, U, W, b = _problem(n, d, ldx, dtype)
+    ws = torch.full((L.dynakv_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    xt = torch.full((n, d), 3.0, dtype=x.dtype, device="cuda")
+    k = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    m = torch.full((n, d), 3.0, device="cuda")
+    L.dynakv_gate(desc, x, U, W, b, 0.1, xt, k, m, None, ws)
+    assert L.dynakv_check(ws) == 0
+    want = x.double() @ U.double()
+    # one rounding to bf16 of an fp32 sum
+    assert bool(((xt.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all())
+    p = torch.softmax(xt.double() @ W.double() + b.double(), 1)
+    # Logits are fp32 sums of d terms whose partial sums are of size 12, each rounded by up to 2^-24 of that: a random walk of standard
+    # deviation 12 * 2^-24 * (d / 3)^0.5, at most 1.6e-5.  The mask's error is at most half the span of a token's logit errors, i.e. six of
+    # these.
+    assert float((m.double() - p.flip(1).cumsum(1).flip(1)).abs().max()) <= 1e-4
+    assert torch.equal(k, (m > 0.1).sum(1, dtype=torch.int32))
