@@ -343,7 +343,7 @@ struct GemmTile {
   }
   // Same with K-major operands.  A K-major operand's offsets are ldT_row(q) * pitch + ldT_byte(that row), its step is
   // KROWS * pitch (K-contiguous: KB), and loads beyond its `bytes` (at most 2^31 - 1, counted from the uniform pointer)
-  // fetch zeros; nothing may be requested beyond 2^32.  With kWalk there is no limit, and `bytes` is ignored.
+  // fetch zeros; every K-step has to start inside them.  With kWalk there is no limit, and `bytes` is ignored.
   __device__ static inline void run_steps(Acc& acc, const char* __restrict__ A, const uint32_t (&offA)[A_LD], uint32_t bytesA,
                                           uint32_t stepA, const char* __restrict__ B, const uint32_t (&offB)[B_LD],
                                           uint32_t bytesB, uint32_t stepB, int ksteps, char* lds, int trace_kind = 0) {

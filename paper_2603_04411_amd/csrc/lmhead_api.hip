@@ -297,7 +297,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     ha.M = desc->d;
     ha.n_from_nv = true;
     ha.k_from_nv = false;
-    ha.K = (int64_t)ntiles * kTile;
+    ha.K = chunk_rows(desc->V, c0, ntiles);
     ha.rowmap = w.at<int32_t>(L.row_slot);
     ha.out = static_cast<float*>(dH);   // unused when the tiles go to the fp32 scratch slices
     ha.ldo = desc->d;
@@ -325,7 +325,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     wa.B = w.at<void>(L.dZ);
     wa.ldB = L.ldZ;
     wa.M = desc->d;
-    wa.n_limit = (desc->V - c0 < ntiles * kTile) ? desc->V - c0 : ntiles * kTile;
+    wa.n_limit = chunk_rows(desc->V, c0, ntiles);
     wa.n_from_nv = false;
     wa.k_from_nv = true;
     wa.rowmap = nullptr;

@@ -16,6 +16,10 @@ namespace lmhead {
 // Macro-tile of the contractions: the widest tile edge, and the unit that operands are padded to.
 constexpr int kTile = 256;
 
+// Vocabulary rows of a chunk of n_tiles tiles from row c0 on.  Both gradients end there: dH's contraction has no K-step that starts
+// behind W, where a buffer window (whose range check subtracts the K-step's offset from its size) promises nothing.
+inline int64_t chunk_rows(int64_t V, int64_t c0, int64_t n_tiles) { return V - c0 < n_tiles * kTile ? V - c0 : n_tiles * kTile; }
+
 // Workgroup -> tile mapping that keeps L2 traffic local to an XCD.
 //
 // The chip dispatches workgroup i of a 1-D grid to XCD i % 8, and each XCD has a private L2.

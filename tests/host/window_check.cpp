@@ -1,5 +1,6 @@
 // Host check of the buffer windows through which the gate reads x, whatever its row pitch: dU, which takes x in pieces beyond one
-// window, gets pieces of at least one K-step, so that the loop over them ends; the rows of a token tile of x U lie inside one.
+// window, gets pieces of at least one K-step, so that the loop over them ends; the rows of a token tile of x U lie inside one.  And
+// of W, which dH reads through them: no K-step starts behind it.
 #include <algorithm>
 #include <cstdio>
 using std::min;
@@ -32,6 +33,16 @@ int main() {
             if ((min(n, (int64_t)edge) - 1) * pitch * esz + d * esz > kWindowBytes) ++bad;
             if (pitch == d && ldx > d && (min(n, (int64_t)edge) - 1) * ldx * esz + d * esz <= kWindowBytes) ++bad;
           }
+  // dH: every K-step of a vocabulary chunk, 64 or 32 rows of W, starts inside W
+  for (int rows : {32, 64})
+    for (int64_t V = 1; V < 20000; V += 1 + V / 50)
+      for (int64_t tiles : {1, 4, 1024})
+        for (int64_t c0 = 0; c0 < V; c0 += tiles * kTile) {
+          ++cases;
+          const int64_t left = (V - c0 + kTile - 1) / kTile, K = chunk_rows(V, c0, left < tiles ? left : tiles);
+          const int64_t ksteps = (K + rows - 1) / rows;
+          if (K < 1 || c0 + (ksteps - 1) * rows >= V || c0 + ksteps * rows < min(V, c0 + tiles * kTile)) ++bad;
+        }
   // the strides around the line, and the first that one K-step does not fit
   for (int64_t ldx : {(int64_t)64, (int64_t)1 << 20, (int64_t)1 << 22, ((int64_t)1 << 23) - 8})
     if (++cases, kv_gradient_needs_dense(ldx)) ++bad;

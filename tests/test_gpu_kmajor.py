@@ -1,6 +1,7 @@
 """Contractions whose operands run along the contraction in memory (W for dH, the hidden states and dZ for dW, both
 operands of the gate's parameter gradients): sizes at the edges of their tiles, of their K-steps of 64 rows and of their
-2 GiB windows, with NaN wherever a row or column is padding and in all of the workspace before the call."""
+2 GiB windows, with NaN wherever a row or column is padding, behind W and the parameters, and in all of the workspace before the
+call."""
 import numpy as np
 import pytest
 
@@ -33,7 +34,7 @@ def test_dh_and_dw(dtype, N, d, V, ldW, chunk):
     tdt, wide_t = (torch.bfloat16, torch.float32) if dtype == "bf16" else (torch.float32, torch.float64)
     H = torch.randn(2 * N, d, generator=g, device="cuda").to(tdt)
     H[2 * N - N // 3:] = float("nan")                                   # padding
-    wide = torch.full((V, ldW), float("nan"), dtype=tdt, device="cuda")
+    wide = torch.full(((V + 256) * ldW,), float("nan"), dtype=tdt, device="cuda")[:V * ldW].view(V, ldW)
     W = wide[:, :d]
     W.copy_(torch.randn(V, d, generator=g, device="cuda") * 0.05)
     tok = torch.randint(0, V, (2 * N,), generator=g, device="cuda", dtype=torch.int32)
