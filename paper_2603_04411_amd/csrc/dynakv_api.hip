@@ -80,7 +80,7 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     LM_TRY(launch_kv_gate({x, desc->ldx, w.at<void>(L.Ufrag), w.at<void>(L.Wfrag), b, L.n, tau, literal ? 1 : 0, xt, k}, d, s));
     return LMHEAD_OK;
   }
-  if (kv_few_fits(dt, L.n, d)) {
+  if (kv_few_fits(dt == LMHEAD_F32, L.n, d)) {
     KvFewArgs fa{x, desc->ldx, U, (int)L.n, d, xt, nullptr, hdr, false, false};
     {
       TimedLaunch tl(4, s);
@@ -97,7 +97,8 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     return LMHEAD_OK;
   }
   // rows too far apart for a tile's window: a dense copy, where the logits will be
-  const bool dense = kv_tiles_need_dense(L.n, kv_tile_edge(dt, 0, d, L.n), desc->ldx, d, L.esz);
+  const int edge = kv_tile_edge(dt == LMHEAD_F32, 0, d, L.n, d, device_compute_units());
+  const bool dense = kv_tiles_need_dense(L.n, edge, desc->ldx, d, L.esz);
   if (dense) {
     TimedLaunch tl(4, s);
     LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, w.at<void>(L.logits), s));
@@ -173,8 +174,9 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
   KvGemmArgs ga{};
   if (L.n <= kKvGroupTo) {
     int32_t* const outside = w.at<int32_t>(L.hist);
-    LM_TRY(launch_kv_group(dt, k, off, L.n, d, packed_elems * L.esz, L.nbuckets, kv_tile_edge(dt, 2, d, L.n),
-                           w.at<int32_t>(L.order), w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), outside, s));
+    const int edge = kv_tile_edge(dt == LMHEAD_F32, 2, d, L.n, d, device_compute_units());   // of the tiles that follow
+    LM_TRY(launch_kv_group(dt, k, off, L.n, d, packed_elems * L.esz, L.nbuckets, edge, w.at<int32_t>(L.order),
+                           w.at<uint32_t>(L.pos_off), w.at<int32_t>(L.pos_len), outside, s));
     ga.outside = outside;
     ga.groups = (int)((L.n + kKvGroup - 1) / kKvGroup);
   } else {
@@ -248,7 +250,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   const bool accum = (desc->flags & DYNAKV_FLAG_ACCUM_GRAD) != 0;
 
   // the parameters as the caller has them: W is K-major in the logits and K-contiguous, like U, in g_l W^T and g_x~ U^T
-  const bool few = kv_few_fits(dt, L.n, d);
+  const bool few = kv_few_fits(dt == LMHEAD_F32, L.n, d);
   KvGemmArgs ga{};
   ga.mode = 1;
   ga.A = W;

@@ -153,7 +153,6 @@ struct KvGemmArgs {
   int walk_len;         // set by the launcher: length of the tile walk (tile_map.h)
 };
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
-int kv_tile_edge(int dtype, int mode, int d, int64_t n);   // of the tiles that launch_kv_gemm takes
 
 // out = the n rows of row_bytes (a multiple of 16), `pitch` bytes apart, one behind the other.
 hipError_t launch_kv_dense(const void* x, int64_t pitch, int64_t n, int row_bytes, void* out, hipStream_t s);
@@ -171,7 +170,6 @@ struct KvFewArgs {
   WsHeader* hdr;
   bool rows, accumulate;
 };
-bool kv_few_fits(int dtype, int64_t n, int d);
 hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s);
 
 // The whole gate of many tokens in one kernel (dynakv_gate.hip), for callers that want x~ and k only.  Ufrag, Wfrag: the

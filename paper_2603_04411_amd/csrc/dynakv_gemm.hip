@@ -26,68 +26,8 @@ namespace {
 
 constexpr int kKvMapBx = 4, kKvMapBy = 4;
 
-// Tile edge of the KV kernels: 64, 128 or 256, four wavefronts each.  The smaller the edge, the more operand bytes per
-// flop (edge 256 is the only one that the vector L1 can feed at full matrix rate), but the more workgroups there are
-// to fill the chip with, and the shorter a tile's serial K loop and epilogue are.  Spectral projection, d = 1024, us:
-//     n            256   1024   2048   4096   8192  12000  16384  65536
-//     edge 64     11.5   12.7   14.0   20.2   36.8   50.6   59.9    252
-//     edge 128    14.3   15.3   15.7   17.2   25.3   35.9   44.5    179
-//     edge 256    29.4   30.5   30.8   31.9   34.5   37.0   42.2    143
-// (fp32, n = 1024: 26.8 / 66.8 / 239; n = 4096: 80 / 78 / 241.)  So: the smallest edge whose tiles run in one round, two to
-// a compute unit.
-// Beyond that the padding of the d columns counts: 320 columns are 512 in 256 wide tiles and 384 in 128 wide ones,
-// 128 columns 256 and 128 (gate of 37065 x 320 94 -> 63 us, fp32 40000 x 320 354 -> 195, 262144 x 128 201 -> 147).
-// In bf16 so do the rounds: 256 wide tiles have a compute unit each, and a round that is not full takes most of a full one's time;
-// 128 wide ones take longer per round, the more so the longer the contraction, but half as long as that.  wide_cost and
-// narrow_cost are fits, in full rounds of 256 wide tiles, to (training pair, us, edge 128 / 256):
-//   d 1024: n 9000 262 / 288   12000 309 / 331   17000 414 / 501   20000 469 / 541   24000 555 / 587   28000 653 / 645   32768 774 / 726
-//           36000 820 / 865   40000 912 / 911   49152 1099 / 1015   65536 1364 / 1317
-//   d 2048: n 4500 394 / 387   8192 619 / 569   9000 708 / 774   10000 766 / 816   12000 891 / 872   16384 1168 / 1042   20000 1403 / 1349
-//   d 512:  n 20000 206 / 236   32768 293 / 309   40000 349 / 421   65536 569 / 570   80000 695 / 721   120000 1015 / 1017
-//   others: 12000 x 1536 603 / 685   30000 x 768 497 / 542   70000 x 256 281 / 359   200000 x 256 729 / 822
-// and, the reconstruction counting half the K-steps as its tokens do (store and reconstruction): d 1024: n 32768 67 / 71   65536
-// 123 / 126   100000 184 / 200   131072 274 / 253;   d 512: 100000 82 / 96   200000 158 / 177;   d 2048: 12000 80 / 86   24000 138 / 122.
-// The choice is within 3 % of the better edge at all of these.
-int tile_edge(bool f32, int mode, int M, int64_t Nn, int K) {
-  const int64_t cus = device_compute_units();
-  auto tiles = [&](int edge) { return (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge); };
-  if (tiles(64) <= 2 * cus) return 64;
-  if (tiles(128) <= (f32 && mode == 2 ? 8 : 2) * cus) return 128;
-  int best = 256;
-  auto padded = [&](int edge) { return (float)((M + edge - 1) / edge * edge) / tile_rate(edge, f32); };
-  if (!f32) {
-    auto rounds = [&](int edge, int64_t slots, float least) {   // a last round that is not full counts at least `least`
-      const int64_t full = tiles(edge) / slots;
-      const float rest = (float)(tiles(edge) % slots) / (float)slots;
-      return (float)full + (rest > 0.f ? (rest > least ? rest : least) : 0.f);
-    };
-    const float steps = (float)(K / 64) * (mode == 2 ? 0.5f : 1.f);
-    const float slope = 1.03f + 0.015f * steps, first = 0.45f - 0.0125f * steps;
-    const float wide_cost = rounds(256, cus, 0.8f);
-    const float narrow_cost = (slope < 1.3f ? slope : 1.3f) * rounds(128, 2 * cus, 0.5f) / 2 - (first > 0.f ? first : 0.f);
-    best = narrow_cost < wide_cost ? 128 : 256;
-  } else if (padded(128) < padded(256)) {
-    best = 128;
-  }
-  return padded(64) < padded(best) ? 64 : best;
-}
 // Workgroups of one tile edge that share a compute unit (bound by LDS: five slots of edge x 128 bytes each, or both operands' stages).
 constexpr int wg_per_cu(int edge, int stages) { return stages ? 640 / (edge * stages) : 256 / edge; }
-
-// Tiles that hold five K-steps in LDS instead of two and a half (bf16): where every tile has a compute unit for itself, so that
-// nothing else covers an access to L2, which takes longer than the MFMAs of a K-step do, and the contraction has 16 K-steps or
-// more.  Shorter ones end before the lead pays for the five requests in front of the first MFMA, and two or more tiles on a
-// compute unit cover each other.  The ring / five stages, us:
-//   gate   1024 x 1024 25.0 / 20.6   550 x 1024 24.5 / 19.9   1100 x 2048 51.0 / 45.4   4096 x 1024 36.2 / 34.5
-//          (more tiles: 2048 x 1024 27.3 / 27.8, 4096 x 512 19.8 / 21.5; shorter: 2000 x 512 16.2 / 17.0)
-//   store + reconstruction   1000 x 1024 26.1 / 23.4; on edge 128 no faster (3000 x 1024 28.3 / 28.2)
-//   training pair   1024 x 1024 83.1 / 72.5   4096 x 1024 136.4 / 134.9
-// Eight stages are no faster (gate 1024 x 1024 22.0).
-constexpr int kStages = 5, kDeepSteps = 16;
-bool deep_tiles(int mode, int edge, int M, int64_t Nn, int K) {
-  const int64_t tiles = (int64_t)((M + edge - 1) / edge) * ((Nn + edge - 1) / edge);
-  return tiles <= device_compute_units() && K / 64 >= kDeepSteps && (edge == 64 || (edge == 128 && mode != 2));
-}
 
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 
@@ -316,7 +256,7 @@ hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
 // bf16 fragments (8 values of k per lane and column) are put together with byte permutes.  kRows: out = x M^T, whose
 // fragments lie in memory as they are; MFMA t covers the columns 16 t + r.  No transposed or padded copies, so the launch
 // that made them goes too.
-constexpr int kFewWaves = 16, kFewCols = 64, kFewTok = 16;
+constexpr int kFewWaves = 16;
 
 template <typename E, bool kRows>
 __global__ __launch_bounds__(64 * kFewWaves) void kv_few_kernel(KvFewArgs a) {
@@ -404,9 +344,9 @@ static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
 
 template <typename E, int Mode>
 hipError_t launch_mode(const KvGemmArgs& a, hipStream_t s) {
-  const int edge = tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn, a.K);
+  const int cus = device_compute_units(), edge = kv_tile_edge(Elem<E>::size == 4, Mode, a.M, a.Nn, a.K, cus);
   if constexpr (Elem<E>::size == 2 && Elem<E>::block == 16) {
-    if (deep_tiles(Mode, edge, a.M, a.Nn, a.K)) {
+    if (kv_deep_tiles(Mode, edge, a.M, a.Nn, a.K, cus)) {
       if (edge == 64) return launch_tiles<E, 64, Mode, kStages>(a, s);
       if constexpr (Mode != 2) return launch_tiles<E, 128, Mode, kStages>(a, s);
     }
@@ -430,17 +370,6 @@ hipError_t launch_e(const KvGemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Up to two workgroups per compute unit: every 16 tokens read all of the parameters again.  Gate of n tokens, copies and
-// tiled products / these (us):
-//   d 1024 bf16: n 16 27.4 / 15.7   n 256 28.3 / 17.1;   d 1024 fp32: n 16 54.3 / 23.6   n 512 58.3 / 39.4
-// One per compute unit where the tiled products hold five K-steps (deep_tiles), tiled / these:
-//   d 1024: n 64 17.8 / 15.3   256 18.9 / 16.1   300 19.1 / 21.2   512 20.2 / 22.3;   d 2048: n 128 25.3 / 24.0   190 26.2 / 34.6
-//   training pair: d 1024 n 256 70.1 / 65.9   400 65.4 / 77.7;   d 2048 n 256 93.3 / 124.5
-bool kv_few_fits(int dtype, int64_t n, int d) {
-  const int per_unit = dtype == LMHEAD_BF16 && d / 64 >= kDeepSteps ? 1 : 2;
-  return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= per_unit * (int64_t)kComputeUnits;
-}
-
 hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
   const dim3 grid((unsigned)(a.d / kFewCols), (unsigned)((a.n + kFewTok - 1) / kFewTok));
   const dim3 block(64 * kFewWaves);
@@ -457,8 +386,6 @@ hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
   }
   return hipGetLastError();
 }
-
-int kv_tile_edge(int dtype, int mode, int d, int64_t n) { return tile_edge(dtype != LMHEAD_BF16, mode, d, n, d); }
 
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s) {
   return dtype == LMHEAD_BF16 ? launch_e<bf16_tag>(a, s) : launch_e<f32_tag>(a, s);

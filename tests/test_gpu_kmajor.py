@@ -80,11 +80,16 @@ def test_gate_parameter_gradients(n, d, dtype):
     assert all(np.isfinite(e) and e <= (1e-2 if dtype == "bf16" else 1e-4) for e in errs.values()), errs
 
 
-# the tiled products, 64, 128 and 256 columns wide, with a last tile past d columns and a last token tile past n: parameters as the
-# caller has them, each with NaN right behind it
+# the tiled products, with a last tile past d columns and a last token tile past n: parameters as the caller has them, each with NaN
+# right behind it; edges of the gate's and of the reconstruction's tiles in bf16, then in fp32 (held by test_host_tiles.py; 256 wide
+# ones are in test_gpu_deep_tiles.py)
+EDGES = {(8300, 64): (64, 64, 64, 64), (1100, 576): (64, 64, 64, 64), (2200, 1088): (128, 128, 128, 128),
+         (9000, 320): (128, 128, 128, 128), (33000, 576): (128, 128, 64, 128)}
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("n,d,edge", [(8300, 64, 64), (1100, 576, 64), (2200, 1088, 128), (9000, 320, 128), (33000, 576, 256)])
-def test_gate_and_reconstruction(n, d, edge, dtype):
+@pytest.mark.parametrize("n,d", list(EDGES))
+def test_gate_and_reconstruction(n, d, dtype):
     import torch
     import paper_2603_04411_amd as L
     g = torch.Generator(device="cuda").manual_seed(n + d)

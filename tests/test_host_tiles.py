@@ -35,6 +35,25 @@ def test_k_major_operands_are_taken_in_pieces_of_a_window(tmp_path):
     _run_host_check(tmp_path, "window_check")
 
 
+def test_kv_edge_is_the_faster_one_where_both_were_measured(tmp_path):
+    _run_host_check(tmp_path, "kv_edge_check")
+
+
+def test_the_gpu_tests_of_the_kv_products_take_the_tiles_that_they_name(tmp_path):
+    """The tables in the GPU tests say which tiles their sizes run on; the rule says which they really run on."""
+    from tests import test_gpu_deep_tiles as deep, test_gpu_kmajor as kmajor
+    want = [("bf16", 0, n, d, kind) for (n, d), kind in deep.SIZES.items()]
+    want += [(dt, mode, n, d, kind) for (dt, n, d), kind in deep.MORE.items() for mode in (0, 2) if mode == 0 or kind == "256 ring"]
+    for (n, d), edges in kmajor.EDGES.items():
+        want += [(dt, mode, n, d, edge) for (dt, mode), edge in zip([("bf16", 0), ("bf16", 2), ("f32", 0), ("f32", 2)], edges)]
+    _run_host_check(tmp_path, "kv_edge_check")
+    r = subprocess.run([str(tmp_path / "kv_edge_check"), *(str(v) for w in want for v in w[:4])], capture_output=True, text=True)
+    got = r.stdout.splitlines()
+    assert len(got) == len(want)
+    for w, line in zip(want, got):
+        assert line == w[4] if isinstance(w[4], str) else line.startswith(f"{w[4]} "), (w, line)
+
+
 @pytest.mark.parametrize("source", ["lmhead_gemm.hip", "dynakv_gemm.hip", "dynakv_gate.hip"])
 def test_the_32x32x16_form_of_the_bf16_main_loop_still_compiles(source):
     from paper_2603_04411_amd import build
