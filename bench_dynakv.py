@@ -33,27 +33,21 @@ FUSED_GATE = "kv_gate_kernel (x U, gate logits, softmax, cumulative mask, thresh
 # --backward: one step = dynakv_gate (training outputs off) + dynakv_gate_bwd
 BWD_KINDS = {4: "kv_gemm_kernel<spectral projection>", 5: "kv_gemm_kernel<gate logits> (forward + recompute)",
              6: "kv_mask_kernel", 8: "kv_mask_bwd_kernel", 9: "kv_gemm_kernel<g_x~ = g_l W^T + g_xhat m>",
-             10: "kv_gemm_kernel<dx = g_x~ U^T>", 11: "gemm_t_kernel<dW>", 12: "gemm_t_kernel<dU>",
-             13: "kv_prepare_kernel (two operand copies per parameter gradient)"}
-PAIRED_GRADIENTS = "gemm_t_kernel<dW and dU>"   # one launch for both, recorded as kind 11; their four copies as one kind 13
+             10: "kv_gemm_kernel<dx = g_x~ U^T>", 11: "gemm_t_kernel<dW and dU>"}
 
 
 def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
     """One entry per kernel kind of the training pair, with its rate.  kern: kind -> (milliseconds, launches)."""
     dense = 2.0 * n * d * d
     # algorithmic bytes per launch: mask backward reads logits (4), x~ and g_xhat (esz each) and writes
-    # g_l and g_xhat*m (esz each); a transpose pair reads and writes two [n x d] operands
-    byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz), 13: 4.0 * n * d * esz}
-    products = dict.fromkeys(BWD_KINDS, 1)
+    # g_l and g_xhat*m (esz each)
+    byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz)}
+    products = {**dict.fromkeys(BWD_KINDS, 1), 11: 2}
     names = dict(BWD_KINDS)
     if kern[6][1] == 0:              # large streams: the forward's gate is one kernel, gate logits only the recompute
         del names[6]
         names[4], products[4] = FUSED_GATE, 2
         names[5] = "kv_gemm_kernel<gate logits> (recompute)"
-    if kern[12][1] == 0:             # both parameter gradients in one launch
-        del names[12]
-        names[11], products[11] = PAIRED_GRADIENTS, 2
-        byts[13] *= 2
     kinds = []
     for kind, name in names.items():
         ms, cnt = kern[kind]

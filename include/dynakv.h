@@ -155,7 +155,7 @@ LMHEAD_API int dynakv_retain(const dynakv_desc* desc, const int32_t* k, const fl
  *   dx     [n x d] storage type, dense (out)
  *   dU, dW float[d x d]; db float[d]  (out; added to with DYNAKV_FLAG_ACCUM_GRAD)
  *   ws     dynakv_bwd_workspace_bytes(desc) bytes (larger than the forward's: it holds the logits, the
- *          two token-major gradients and token-contiguous copies of the operands of dW and dU)
+ *          two token-major gradients and the slices of the contractions of dW and dU)
  * The contractions over the tokens accumulate in fp32, in slices summed in a fixed order.
  */
 LMHEAD_API size_t dynakv_bwd_workspace_bytes(const dynakv_desc* desc);

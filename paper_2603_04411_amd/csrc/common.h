@@ -56,9 +56,9 @@ struct WsLayout {
   size_t hdr, cu_len, row_slot, tok_c, gid, g_c, lse_c, zy, part, Hc, dZ, Hc8, W8, total;
 };
 
-// Default backward chunk: as wide as keeps dZ (worst case: every slot valid) within about 48 GB, at most 262144 columns (small problems take the whole vocabulary in one
-// chunk).  Wider chunks mean fewer read-modify-write passes over dH and longer contractions per
-// launch.
+// Default backward chunk: as wide as keeps dZ (worst case: every slot valid) within about 48 GB, at most 262144 columns
+// (small problems take the whole vocabulary in one chunk).  Wider chunks mean fewer read-modify-write passes over dH and
+// longer contractions per launch.
 static inline int64_t default_vocab_chunk(const lmhead_desc* d) {
   const int64_t esz = d->dtype == LMHEAD_BF16 ? 2 : 4;
   const int64_t N = (int64_t)d->P * d->G * d->T;
@@ -68,7 +68,6 @@ static inline int64_t default_vocab_chunk(const lmhead_desc* d) {
   if (vc < 4 * kTile) vc = 4 * kTile;
   return vc;
 }
-
 
 // Weight matrices one forward launch can evaluate over the same hidden states.
 constexpr int kMaxPolicies = 4;
@@ -304,7 +303,7 @@ hipError_t static_scratch(float** out);
 // stream.  The pool is fixed-size; launches beyond it are simply not timed.
 // Kinds: 0 logits fwd, 1 dZ recompute, 2 dH, 3 dW, 4 spectral projection, 5 gate logits,
 // 6 truncation mask, 7 low-rank reconstruction; gate backward: 8 mask backward, 9 g_x~ product, 10 dx
-// product, 11 dW, 12 dU, 13 operand transposes.  The gate in one kernel is recorded as 4.
+// product, 11 dW and dU (12 and 13 were further launches for them, no longer made).  The gate in one kernel is recorded as 4.
 constexpr int kTimingKinds = 14;
 constexpr int kTimingPool = 8192;
 struct TimingState {

@@ -99,10 +99,6 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
   // rows too far apart for a tile's window: a dense copy, where the logits will be
   const int edge = kv_tile_edge(dt == LMHEAD_F32, 0, d, L.n, d, device_compute_units());
   const bool dense = kv_tiles_need_dense(L.n, edge, desc->ldx, d, L.esz);
-  if (dense) {
-    TimedLaunch tl(4, s);
-    LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, w.at<void>(L.logits), s));
-  }
   KvGemmArgs ga{};
   ga.mode = 0;
   ga.A = U;
@@ -119,6 +115,7 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
   ga.hdr = hdr;
   {
     TimedLaunch tl(4, s);
+    if (dense) LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, w.at<void>(L.logits), s));
     LM_TRY(launch_kv_gemm(dt, ga, s));
   }
   ga.mode = 1;
@@ -309,10 +306,6 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
 
   // x where it lies, unless its rows are too far apart: then a dense copy in the place of the logits, which are done with
   const bool dense = kv_gradient_needs_dense(desc->ldx);
-  if (dense) {
-    TimedLaunch tl(11, s);
-    LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, at(L.logits), s));
-  }
   // Parameter gradients: contractions over the tokens, both in one launch, cut into ksplit slices of the token range (one:
   // stored directly).  dW[k][j] = sum_t x~[t][k] g_l[t][j];  dU[i][k] = sum_t x[t][i] g_x~[t][k]
   GemmTArgs ta{};
@@ -341,6 +334,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ta.accumulate = accum;
   {
     TimedLaunch tl(11, s);
+    if (dense) LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, at(L.logits), s));
     LM_TRY(launch_gemm_t(dt, ta, s, 2));
   }
   LM_TRY(launch_kv_sums({static_cast<const float*>(at(L.dbpart)), L.nblk, ta.part, L.ksplit, d, db, dW, dU, accum}, s));

@@ -628,8 +628,9 @@ __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restric
 }
 
 // Offsets and copy of the segments, four tokens per wavefront.  A workgroup adds up what lies before its tokens itself.
-// kAll (n up to kPackAll, sixteen wavefronts; four up to 256 tokens): all the counts before them, L2 reads of at most 128 KB, in one launch; the last workgroup
-// sees every count, so it sets the error word and clears the header with one store.  Otherwise (four wavefronts) the totals of
+// kAll (n up to kPackAll, sixteen wavefronts; four up to 256 tokens): all the counts before them, L2 reads of at most
+// 128 KB, in one launch; the last workgroup sees every count, so it sets the error word and clears the header with one
+// store.  Otherwise (four wavefronts) the totals of
 // the blocks before, which a launch of its own has formed (or their prefix sum, when there are so many that `scanned` says so),
 // and the tokens before it in its own block.
 // A wavefront's four tokens are under way together: one 16-byte chunk per lane of each is requested before the first is

@@ -127,7 +127,7 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
 // A is the parameter matrix as the caller has it: [K x M], mode 3: [M x K].
 // mode 2:   ragged rows: Bop[n] = the pos_len[n] bytes of the packed store at byte offset pos_off[n],
 //           zero beyond; row(n) = order[n] (< 0: no token); the tile's step count follows its
-//           first row, the longest (the three arrays are written by launch_kv_order).
+//           first row, the longest (the three arrays are written by launch_kv_order or launch_kv_group).
 struct KvGemmArgs {
   int mode;
   const void* A;        // pitch ldA

@@ -2,7 +2,7 @@
 //
 // All contractions (logits, logits recompute for dZ, dH, dW; the KV path's spectral projection,
 // gate logits and ragged reconstruction) are brought to the same form
-// C[m][n] = sum_k A[m][k] * B[n][k]  with both operands K-contiguous, or in bf16 K-major (below).
+// C[m][n] = sum_k A[m][k] * B[n][k]  with both operands K-contiguous, or K-major (below; not in e4m3).
 // A workgroup owns a BM x BN tile of C; each wavefront owns a (BM/WGM) x (BN/WGN)
 // sub-tile built from 16x16 (bf16, e4m3) or 32x32 (fp32) MFMA blocks.
 //
@@ -47,8 +47,9 @@
 // W does for dH and the hidden states for dW.  A K-step is then 64 (fp32: 32) rows of BM values, and the fragments are read out
 // of LDS transposed, so that no transposed copy of the operand is needed.
 //   bf16: ds_read_b64_tr_b16 hands a 4 x 16 block (K x M) to sixteen lanes transposed: a lane supplies the address of 4
-//   consecutive values of one row and receives 4 values of K of one column; two of them make a fragment.  They run at the rate of
-//   the plain reads (156 B/clk and compute unit against 123 for 128-bit ones; without the swizzle 32).
+//   consecutive values of one row and receives 4 values of K of one column; two of them make a fragment.  In a bare
+//   loop a compute unit reads 176 bytes a clock with them, 128 with the 128-bit reads of a K-contiguous operand, and 32 with them if
+//   the swizzle is left out.
 //   LDS slot: the 64 rows as they lie, cut into 32-byte units; unit u of row k sits at unit u ^ swzT(k) of its row.  The
 //   rows are put into the slot's 1 KB groups in an order (krow_at) that keeps whatever depends on the sub-step and on the
 //   half of a fragment in the last bits of the group index, so that it fits the DS instructions' immediate offset.

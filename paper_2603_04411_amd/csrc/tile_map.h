@@ -325,8 +325,8 @@ inline bool kv_deep_tiles(int mode, int edge, int M, int64_t Nn, int K, int64_t 
   return tiles_of(M, Nn, edge) <= cus && K / 64 >= kDeepSteps && (edge == 64 || (edge == 128 && mode != 2));
 }
 
-// The few-token kernel (16 tokens x 64 columns a workgroup): up to two workgroups per compute unit: every 16 tokens read all of the parameters again.  Gate of n tokens, copies and
-// tiled products / these (us):
+// The few-token kernel (16 tokens x 64 columns a workgroup) takes up to two workgroups per compute unit: every 16 tokens read all
+// of the parameters again.  Gate of n tokens, copies and tiled products / these (us):
 //   d 1024 bf16: n 16 27.4 / 15.7   n 256 28.3 / 17.1;   d 1024 fp32: n 16 54.3 / 23.6   n 512 58.3 / 39.4
 // One per compute unit where the tiled products hold five K-steps (kv_deep_tiles), tiled / these:
 //   d 1024: n 64 17.8 / 15.3   256 18.9 / 16.1   300 19.1 / 21.2   512 20.2 / 22.3;   d 2048: n 128 25.3 / 24.0   190 26.2 / 34.6

@@ -67,17 +67,17 @@ def test_row_subset():
 def test_bench_counts_what_a_launch_does():
     import bench_dynakv as B
     n, d, esz = 4096, 1024, 2
-    flop, byts = 2.0 * n * d * d, 4.0 * n * d * esz
+    flop, byts = 2.0 * n * d * d, n * d * (4.0 + 4 * esz)
     split = {kind: (0.5, 10) for kind in B.BWD_KINDS}                     # 50 us a launch
     rows = {e["kind"]: e for e in B.backward_kinds(split, n, d, esz, 2500.0)}
     assert set(rows) == set(B.BWD_KINDS)
-    assert all(abs(rows[k]["tflops"] - flop / 50e-6 / 1e12) < 1e-6 for k in (4, 5, 9, 10, 11, 12))
-    assert abs(rows[13]["gbs"] - byts / 50e-6 / 1e9) < 1e-6
-    # one launch for both parameter gradients, and one kernel for the whole gate
+    assert all(abs(rows[k]["tflops"] - flop / 50e-6 / 1e12) < 1e-6 for k in (4, 5, 9, 10))
+    assert abs(rows[11]["tflops"] - 2 * flop / 50e-6 / 1e12) < 1e-6       # both parameter gradients in one launch
+    assert abs(rows[8]["gbs"] - byts / 50e-6 / 1e9) < 1e-6
+    # and one kernel for the whole gate
     joint = dict(split)
-    joint[12] = joint[6] = (0.0, 0)
+    joint[6] = (0.0, 0)
     rows = {e["kind"]: e for e in B.backward_kinds(joint, n, d, esz, 2500.0)}
-    assert set(rows) == set(B.BWD_KINDS) - {6, 12}
+    assert set(rows) == set(B.BWD_KINDS) - {6}
     assert all(abs(rows[k]["tflops"] - 2 * flop / 50e-6 / 1e12) < 1e-6 for k in (4, 11))
-    assert abs(rows[13]["gbs"] - 2 * byts / 50e-6 / 1e9) < 1e-6
-    assert rows[11]["kernel"] == B.PAIRED_GRADIENTS and rows[4]["kernel"] == B.FUSED_GATE
+    assert rows[4]["kernel"] == B.FUSED_GATE
