@@ -366,7 +366,6 @@ __device__ inline void dz_epilogue_direct(const DzArgs& a, typename G::Acc& acc,
     else
       emit(std::integral_constant<int, 2>{});
   }
-  trace_stamp(12, 2);
 }
 
 // E: type of the operands Hc and W (possibly e4m3 copies); EO: type of dZ.

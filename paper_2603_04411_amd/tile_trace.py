@@ -5,7 +5,7 @@
 
 The trace build writes, for each of the first 2^19 workgroups, the 100 MHz real-time counter at fourteen points of
 the tile (kernel entry, main-loop entry, first data landed, after 5 / 10 / 15 K-steps, end of the unrolled loop,
-end of the drain, epilogue start, three points inside it, and its end) and the shader clock counter at six of them, which gives the clock
+end of the drain, epilogue start, up to three points inside it, and its end) and the shader clock counter at six of them, which gives the clock
 frequency inside the loop and inside the epilogue separately.  Inputs are seeded and synthetic (N(0,1) hidden
 states, N(0, 0.02^2) weights, uniform lengths in [T/4, T]).  A diagnostic: it loads the trace library directly
 and is not used by the binding, the tests or the benchmark.
@@ -30,8 +30,7 @@ EPILOGUE = {
     "fwd": [("epilogue: target-logit capture", 2, 11), ("epilogue: softmax statistics of 256 values per lane", 11, 12),
             ("epilogue: lane-group merges, partials to LDS", 12, 13), ("epilogue: barrier, cross-wave merge, stores", 13, 3)],
     "dz": [("epilogue: per-token scalars fetched (one round trip)", 2, 11),
-           ("epilogue: dZ formed, stored from registers, staged in LDS", 11, 12), ("epilogue: barrier", 12, 13),
-           ("epilogue: vocabulary-major copy streamed out of LDS", 13, 3)],
+           ("epilogue: dZ formed, stored from registers", 11, 3)],
 }
 
 

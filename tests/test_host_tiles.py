@@ -60,3 +60,13 @@ def test_the_32x32x16_form_of_the_bf16_main_loop_still_compiles(source):
     r = subprocess.run([build._hipcc(), *build.FLAGS, "-DLMHEAD_BF16_BLOCK=32", "-fsyntax-only", "--cuda-device-only",
                         os.path.join(build.CSRC, source)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_the_tile_trace_reads_points_that_the_kernels_stamp():
+    import re
+    from paper_2603_04411_amd import build, tile_trace
+    with open(os.path.join(build.CSRC, "lmhead_gemm.hip")) as src:
+        stamped = {(int(p), int(k)) for p, k in re.findall(r"trace_stamp\((\d+), (\d)\)", src.read())}
+    for kernel, kind in (("fwd", 1), ("dz", 2)):
+        for _, a, b in tile_trace.EPILOGUE[kernel]:
+            assert {(a, kind), (b, kind)} <= stamped, (kernel, a, b)
