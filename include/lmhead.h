@@ -91,7 +91,7 @@ typedef struct lmhead_desc {
   int32_t d, V;        /* hidden size (multiple of 64; 32 for fp32) and vocabulary size   */
   int32_t dtype;       /* LMHEAD_F32 or LMHEAD_BF16: storage type of H and W              */
   int32_t vocab_chunk; /* vocabulary chunk of the backward (columns of dZ held at once);  */
-                       /* 0 = library default (as wide as ~48 GB of scratch allows, at    */
+                       /* 0 = library default (as wide as ~24 GB for dZ allow, at         */
                        /* most 262144, so small problems take the vocabulary in one       */
                        /* chunk).  Rounded up to a multiple of the 256-wide tile.         */
   int32_t fp8_exp_h;   /* with LMHEAD_FLAG_FP8_LOGITS: H is scaled by 2^fp8_exp_h before rounding  */

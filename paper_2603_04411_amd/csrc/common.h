@@ -56,13 +56,16 @@ struct WsLayout {
   size_t hdr, cu_len, row_slot, tok_c, gid, g_c, lse_c, zy, part, Hc, dZ, Hc8, W8, total;
 };
 
-// Default backward chunk: as wide as keeps dZ (worst case: every slot valid) within about 48 GB, at most 262144 columns
+// Default backward chunk: as wide as keeps dZ (worst case: every slot valid) within about 24 GB, at most 262144 columns
 // (small problems take the whole vocabulary in one chunk).  Wider chunks mean fewer read-modify-write passes over dH and
-// longer contractions per launch.
+// longer contractions per launch, but dZ's rows lie further apart, for the dZ kernel, which stores them, and for dW, which reads
+// them 64 at a time.  Backward, bf16, V = 151936, ms, within 48 GB / within 24 GB: 131072 slots x 4096 214.0 / 211.1   262144 x 4096
+// 404.0 / 399.9   262144 x 2048 215.8 / 216.1   524288 x 2048 429.8 / 431.3;   the step of 524288 x 4096 1142 / 1133 (dZ 294 / 289,
+// dW 284 / 281);   fp32, 65536 x 1024 270 / 270.
 static inline int64_t default_vocab_chunk(const lmhead_desc* d) {
   const int64_t esz = d->dtype == LMHEAD_BF16 ? 2 : 4;
   const int64_t N = (int64_t)d->P * d->G * d->T;
-  int64_t vc = (48ll << 30) / (esz * (N > 0 ? N : 1));
+  int64_t vc = (24ll << 30) / (esz * (N > 0 ? N : 1));
   vc = vc / kTile * kTile;
   if (vc > 262144) vc = 262144;
   if (vc < 4 * kTile) vc = 4 * kTile;

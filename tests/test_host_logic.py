@@ -238,6 +238,10 @@ def test_workspace_grows_with_the_problem_and_default_chunk_is_bounded():
     assert small < big < huge < 100 * 2 ** 30          # sized for a 288 GB part, well below it
     narrow = L.workspace_bytes(L.make_desc(32, 8, 2048, 4096, 151936, "bf16", vocab_chunk=2048))
     assert narrow < big
+    # dZ of the default chunk stays within 24 GB: 524288 slots take 24576 columns at a time
+    def bytes_of(chunk):
+        return L.workspace_bytes(L.make_desc(32, 8, 2048, 4096, 151936, "bf16", vocab_chunk=chunk))
+    assert bytes_of(0) == bytes_of(24576) < bytes_of(24576 + 256)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
