@@ -439,10 +439,13 @@ void kv_mask_bwd_kernel(const float* __restrict__ logits, const float* __restric
 //  - Slices (few rows, d x d columns): one thread per four columns walks the rows.
 //  - Column sums (many rows, d columns): a workgroup owns 64 columns, its sixteen wavefronts each sum every sixteenth
 //    row, eight loads at a time.  (With four wavefronts and a chain of four loads each, 1024 rows of 1024 columns took 22 us, now 5.4.)
+//    The slices of small parameters (d up to kSumByColumns) are as many as 256 and a thread per four columns would be two to eight
+//    workgroups: they are summed like this too.  Whole backward call, us, by threads / by columns: bf16 40000 x 64 95.0 / 58.6
+//    12000 x 128 46.9 / 40.1   fp32 12000 x 64 66.7 / 40.1;   not at d 256: 12000 x 256 49.0 / 51.3.
 // The column sums are ready long before the gradients, but a launch of their own costs its 4 us of dispatch wherever it is put
 // (4096 x 1024 training pair 149.5 -> 145.7 us; 300 x 128 in fp32 48.5 -> 47.4 with the one-launch retain rate below, which
 // no longer waits for the GPU but for the host).
-constexpr int kSumWaves = 16, kSumBatch = 8;
+constexpr int kSumWaves = 16, kSumBatch = 8, kSumByColumns = 128;
 
 __device__ inline void sum_slices(const float* __restrict__ part, int rows, int64_t row_pitch, float* __restrict__ out,
                                   int64_t j, bool accumulate) {
@@ -460,31 +463,42 @@ __device__ inline void sum_slices(const float* __restrict__ part, int rows, int6
   *dst = t;
 }
 
-__global__ __launch_bounds__(64 * kSumWaves) void kv_sum_kernel(KvSums a) {
+__global__ __launch_bounds__(64 * kSumWaves) void kv_sum_kernel(KvSums a, int by_columns) {
   __shared__ float sm[kSumWaves][64];
   const int col_blocks = a.d / 64;
+  const int64_t len = (int64_t)a.d * a.d;
+  const float* part = a.dbpart;
+  float* out = a.db;
+  int64_t rows = a.db_rows, pitch = a.d, j0 = (int64_t)blockIdx.x * 64;
   if ((int)blockIdx.x >= col_blocks) {
-    const int64_t len4 = (int64_t)a.d * a.d / 4;
-    int64_t j = (int64_t)(blockIdx.x - col_blocks) * (64 * kSumWaves) + threadIdx.x;
-    const bool second = j >= len4;
-    if (second) j -= len4;
-    if (j < len4)
-      sum_slices(a.part + (second ? a.slices * len4 * 4 : 0), a.slices, len4 * 4, second ? a.dU : a.dW, j, a.accumulate);
-    return;
+    const int64_t at = (int64_t)(blockIdx.x - col_blocks) * (by_columns ? 64 : 4 * 64 * kSumWaves);
+    if (!by_columns) {
+      int64_t j = at / 4 + threadIdx.x;
+      const bool second = j >= len / 4;
+      if (second) j -= len / 4;
+      if (j < len / 4) sum_slices(a.part + (second ? a.slices * len : 0), a.slices, len, second ? a.dU : a.dW, j, a.accumulate);
+      return;
+    }
+    const bool second = at >= len;
+    part = a.part + (second ? a.slices * len : 0);
+    out = second ? a.dU : a.dW;
+    rows = a.slices;
+    pitch = len;
+    j0 = second ? at - len : at;
   }
   const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + cl;
+  const int64_t j = j0 + cl;
   float t[kSumBatch] = {};
-  const float* const p = a.dbpart + j;
-  int r = rl;
-  for (; r + (kSumBatch - 1) * kSumWaves < a.db_rows; r += kSumWaves * kSumBatch) {
+  const float* const p = part + j;
+  int64_t r = rl;
+  for (; r + (kSumBatch - 1) * kSumWaves < rows; r += kSumWaves * kSumBatch) {
     float v[kSumBatch];
 #pragma unroll
-    for (int u = 0; u < kSumBatch; ++u) v[u] = p[(int64_t)(r + u * kSumWaves) * a.d];
+    for (int u = 0; u < kSumBatch; ++u) v[u] = p[(r + u * kSumWaves) * pitch];
 #pragma unroll
     for (int u = 0; u < kSumBatch; ++u) t[u] += v[u];
   }
-  for (; r < a.db_rows; r += kSumWaves) t[0] += p[(int64_t)r * a.d];
+  for (; r < rows; r += kSumWaves) t[0] += p[r * pitch];
 #pragma unroll
   for (int o = kSumBatch / 2; o > 0; o >>= 1)
 #pragma unroll
@@ -495,7 +509,7 @@ __global__ __launch_bounds__(64 * kSumWaves) void kv_sum_kernel(KvSums a) {
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < kSumWaves; ++w) v += sm[w][cl];
-    a.db[j] = a.accumulate ? a.db[j] + v : v;
+    out[j] = a.accumulate ? out[j] + v : v;
   }
 }
 
@@ -1086,8 +1100,10 @@ hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, co
 
 hipError_t launch_kv_sums(const KvSums& a, hipStream_t s) {
   constexpr int64_t NT = 64 * kSumWaves;
-  const int64_t slices = a.slices > 1 ? ((int64_t)a.d * a.d / 2 + NT - 1) / NT : 0;   // both gradients, four columns a thread
-  hipLaunchKernelGGL(kv_sum_kernel, dim3((unsigned)(a.d / 64 + slices)), dim3((unsigned)NT), 0, s, a);
+  const bool by_columns = a.d <= kSumByColumns;
+  const int64_t columns = a.slices > 1 ? 2 * (int64_t)a.d * a.d : 0, per_block = by_columns ? 64 : 4 * NT;   // of both gradients
+  hipLaunchKernelGGL(kv_sum_kernel, dim3((unsigned)(a.d / 64 + (columns + per_block - 1) / per_block)), dim3((unsigned)NT), 0, s, a,
+                     by_columns ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -31,8 +31,9 @@ def test_retain_rate(n, d, have):
     assert float((gm - 2 * 0.5 * out[1] / (n * d)).abs().max()) <= 4 * 2.0 ** -24 / (n * d)
 
 
-# slices of the token range: none (d 1088, few tokens), a few, one per workgroup; accumulated and not
-@pytest.mark.parametrize("n,d", [(40, 1088), (700, 576), (2000, 64)])
+# slices of the token range: none (d 1088, few tokens), a few, one per workgroup; the most that d = 64 and 128 have, summed by columns,
+# and next to them; accumulated and not
+@pytest.mark.parametrize("n,d", [(40, 1088), (700, 576), (2000, 64), (16700, 64), (8300, 128), (4200, 192)])
 def test_gradient_sums(n, d):
     import torch
     cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d)
