@@ -642,10 +642,9 @@ __global__ __launch_bounds__(1024) void kv_scan_blocks_kernel(int64_t* __restric
 }
 
 // Offsets and copy of the segments, four tokens per wavefront.  A workgroup adds up what lies before its tokens itself.
-// kAll (n up to kPackAll, sixteen wavefronts; four up to 256 tokens): all the counts before them, L2 reads of at most
-// 128 KB, in one launch; the last workgroup sees every count, so it sets the error word and clears the header with one
-// store.  Otherwise (four wavefronts) the totals of
-// the blocks before, which a launch of its own has formed (or their prefix sum, when there are so many that `scanned` says so),
+// kAll (pack_waves below): all the counts before them, L2 reads of at most 128 KB, in one launch; the last workgroup sees
+// every count, so it sets the error word and clears the header with one store.  Otherwise (four wavefronts) the totals of the
+// blocks before, which a launch of its own has formed (or their prefix sum, when there are so many that `scanned` says so),
 // and the tokens before it in its own block.
 // A wavefront's four tokens are under way together: one 16-byte chunk per lane of each is requested before the first is
 // stored (one token after the other 262144 x 64 took 61.7 us, now 43.6).
@@ -760,12 +759,21 @@ __global__ __launch_bounds__(64 * kWaves) void kv_pack_kernel(const T* __restric
     }
   }
 }
-// Most tokens of the one-launch form: 8192 components each still add up in 32 bits.  With the one-launch sort below, store and
-// reconstruction, five launches / three, us: 300 x 1024 23.5 / 19.1   1000 x 1024 26.1 / 19.0   4099 x 1024 33.7 / 27.2   8000 x 512
-// 27.2 / 21.7   16411 x 1024 50.3 / 45.6   32768 x 1024 68.9 / 65.0   32768 x 128 26.3 / 25.7: the gain falls as the counts grow.
-constexpr int64_t kPackAll = 32768;
+// Wavefronts of the one-launch form, 0: the counts get a launch of their own.  A workgroup of four, 16 tokens, spreads the copy best but
+// adds up 2048 counts a round of loads; one of sixteen, 64 tokens, 8192.  Past two rounds of those the launch is cheaper, but for
+// long rows, whose copy covers it.  (8192 components of each of 32768 tokens still add up in 32 bits.)  Store, us, GPU time,
+// two launches / sixteen / four:
+//   bf16 d 64    n 1500 6.0 / 5.6 / 4.0   4500 6.4 / 5.7 / 5.4   6000 6.5 / 5.7 / 5.4   9000 7.0 / 6.1 / 7.0   16000 7.7 / 6.8 / 9.9
+//                20000 8.2 / 10.3 / 12.3   32768 10.0 / 12.0 / 21.5
+//   bf16 d 1024  n 1000 6.6 / 6.6 / 4.6   6000 7.7 / 7.6 / 6.7   9000 8.5 / 8.1 / 8.5   16000 10.5 / 9.8 / 12.8   24000 12.6 / 14.3 / 18.5
+//   bf16 d 2048  n 24000 21.8 / 19.8 / 22.7   32768 27.1 / 24.6 / 29.4;   fp32 d 8192  n 700 21.7 / 31.9 / 19.4   6000 49.4 / 47.4 / 46.6
+constexpr int64_t kPackFew = 6144, kPackMost = 16384, kPackAll = 32768;
+constexpr int64_t kPackLongRow = 4096;   // bytes
 static_assert(kPackAll * kKvMaxD <= INT32_MAX, "32-bit sums");
 constexpr int kPackWaves = 4, kPackAllWaves = 16;
+inline int pack_waves(int64_t n, int64_t row_bytes) {
+  return n <= kPackFew ? kPackWaves : n <= (row_bytes >= kPackLongRow ? kPackAll : kPackMost) ? kPackAllWaves : 0;
+}
 static_assert(kKvScanBlock == 64 * kPackWaves && kKvScanBlock % (kPackPer * kPackWaves) == 0 && kPackPer * kPackAllWaves <= 64,
               "one thread per token of a block, one lane per token of a workgroup");
 
@@ -1122,18 +1130,18 @@ hipError_t launch_kv_store(int dtype, const void* xt, const int32_t* k, int64_t 
   // tokens of 64 components: 524288 86.2 us without it, 79.4 with it).
   constexpr int64_t kScanFrom = 1024;
   const int scanned = nblocks > kScanFrom ? 1 : 0;
-  const bool all = n <= kPackAll;
+  const int all = pack_waves(n, (int64_t)d * (dtype == LMHEAD_BF16 ? 2 : 4));
   if (!all)
     hipLaunchKernelGGL(kv_scan_totals_kernel, dim3((unsigned)nblocks), dim3(kKvScanBlock), 0, s, k, n, d, blocksum, hdr);
   if (scanned) hipLaunchKernelGGL(kv_scan_blocks_kernel, dim3(1), dim3(1024), 0, s, blocksum, (int)nblocks);
-  const int waves = n > kKvScanBlock && all ? kPackAllWaves : kPackWaves;
+  const int waves = all ? all : kPackWaves;
   const dim3 grid((unsigned)((n + kPackPer * waves - 1) / (kPackPer * waves))), block(64 * waves);
   auto launch = [&](auto kernel, auto* x, auto* out) {
     hipLaunchKernelGGL(kernel, grid, block, 0, s, x, k, blocksum, scanned, n, d, off_base, off, out, capacity, hdr);
   };
   auto typed = [&](auto* x, auto* out) {
     using T = std::remove_reference_t<decltype(*out)>;
-    if (n <= kKvScanBlock)   // few counts to add up: 16 tokens a workgroup
+    if (all == kPackWaves)
       launch(kv_pack_kernel<T, kPackWaves, true>, x, out);
     else if (all)
       launch(kv_pack_kernel<T, kPackAllWaves, true>, x, out);

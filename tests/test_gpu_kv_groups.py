@@ -1,5 +1,6 @@
 """Store and reconstruction around the sizes where their launches change: one workgroup's tokens, one group of the sort, tiles of the last
-group, the most tokens that one launch takes; every length from none to all, and errors in the first, a middle and the last token."""
+group, the most tokens that each form of the store and the one-launch sort take; every length from none to all, and errors in the
+first, a middle and the last token."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -20,7 +21,8 @@ def _problem(n, d, dtype):
 
 
 @pytest.mark.parametrize("n,d,dtype", [(1, 64, "bf16"), (63, 64, "f32"), (65, 128, "bf16"), (2047, 192, "bf16"), (2049, 1024, "bf16"),
-                                       (4097, 320, "f32"), (4500, 1024, "bf16"), (18433, 1024, "bf16"), (20000, 64, "bf16"),
+                                       (4097, 320, "f32"), (4500, 1024, "bf16"), (18433, 1024, "bf16"), (20000, 64, "bf16"), (257, 64, "bf16"), (6144, 64, "f32"), (6145, 64, "bf16"), (16384, 64, "bf16"),
+                                       (16385, 64, "f32"), (16385, 2048, "bf16"), (16385, 1984, "bf16"),
                                        (32767, 128, "bf16"), (32768, 576, "bf16"), (32769, 128, "f32"), (300, 8192, "f32"),
                                        (24001, 1984, "bf16")])
 def test_store_and_reconstruct(n, d, dtype):
@@ -50,7 +52,7 @@ def test_store_and_reconstruct(n, d, dtype):
     assert bool(((xbar.double() - want).abs() <= bound).all())
 
 
-@pytest.mark.parametrize("n", [40, 2100, 32768, 33000])
+@pytest.mark.parametrize("n", [40, 2100, 7000, 32768, 33000])
 @pytest.mark.parametrize("where", [0.0, 0.5, 1.0])
 def test_errors(n, where):
     import torch
