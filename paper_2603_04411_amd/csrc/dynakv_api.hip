@@ -169,7 +169,7 @@ int dynakv_reconstruct(const dynakv_desc* desc, const void* packed, int64_t pack
   const int d = desc->d;
 
   KvGemmArgs ga{};
-  if (L.n <= kKvGroupTo) {
+  if (kv_group_fits(L.esz, L.n, d)) {
     int32_t* const outside = w.at<int32_t>(L.hist);
     const int edge = kv_tile_edge(dt == LMHEAD_F32, 2, d, L.n, d, device_compute_units());   // of the tiles that follow
     LM_TRY(launch_kv_group(dt, k, off, L.n, d, packed_elems * L.esz, L.nbuckets, edge, w.at<int32_t>(L.order),

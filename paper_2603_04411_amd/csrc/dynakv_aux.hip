@@ -855,7 +855,7 @@ __global__ __launch_bounds__(256) void kv_scatter_kernel(const int32_t* __restri
   }
 }
 
-// Up to kKvGroupTo tokens one launch instead of two: a workgroup sorts kKvGroup tokens by itself, in LDS.  The tiles of a group
+// Where kv_group_fits, one launch instead of two: a workgroup sorts kKvGroup tokens by itself, in LDS.  The tiles of a group
 // are then a little less even than those of all the tokens (16 tiles of 128 tokens each, about half a K-step of 7.5 more), which costs
 // less than the counts' launch did.  Rank r tiles of all groups come before the rank r + 1 tiles, so that the long ones still start
 // first; only the last group can have fewer tiles than the others.

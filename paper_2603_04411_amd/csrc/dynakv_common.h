@@ -250,6 +250,11 @@ hipError_t launch_kv_order(int dtype, const KvCount& c, const int64_t* off, int6
 // outside[group]: whether a segment of the group does not lie inside the store.
 constexpr int kKvGroup = 2048;
 constexpr int64_t kKvGroupTo = 32768;
+// fp32 products of 200 us and more stay with the sort of all the tokens: there the evener tiles are worth more than the launch.
+// Reconstruction, lengths uniform in [0, d], us, all / groups:  fp32 3000 x 4096 503 / 552   24000 x 2048 957 / 1025   9000 x 2048
+// 397 / 418   24000 x 1024 229 / 236   16384 x 1024 173 / 169   4500 x 512 45 / 41;   bf16 24000 x 2048 118 / 120   32768 x 4096
+// 555 / 524   16384 x 1024 38 / 34   3000 x 512 13.6 / 10.7.
+inline bool kv_group_fits(int esz, int64_t n, int64_t d) { return n <= kKvGroupTo && (esz == 2 || n * d * d <= (int64_t)1 << 34); }
 static_assert(kKvGroup % kTile == 0 && kKvGroupTo / kKvGroup <= kKvCountBlocks, "whole tiles; the flags take the counts' place");
 hipError_t launch_kv_group(int dtype, const int32_t* k, const int64_t* off, int64_t n, int d, int64_t bytes, int nbuckets, int edge,
                            int32_t* order, uint32_t* pos_off, int32_t* pos_len, int32_t* outside, hipStream_t s);
