@@ -1180,9 +1180,10 @@ hipError_t launch_kv_group(int dtype, const int32_t* k, const int64_t* off, int6
 
 hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, float alpha, float* out,
                             float* g_m, double* red, WsHeader* hdr, hipStream_t s) {
-  // Up to here one workgroup reads everything sooner than a second launch starts.  Whole call, us, two launches / one: 38400 values
-  // 11.3 / 8.0, 131072 11.1 / 7.3, 262144 11.0 / 9.7, 524288 11.2 / 17.5.
-  constexpr int64_t kRetainFew = 262144;
+  // Up to here one workgroup reads everything sooner than two launches do.  GPU time, us, two launches / one: 1024 values 4.2 / 2.8,
+  // 32768 4.8 / 3.4, 65536 4.9 / 4.0, 96000 7.0 / 5.0 (1500 x 64), 102400 4.7 / 5.2 (100 x 1024), 131584 4.8 / 5.8, 204800 4.8 / 8.0.
+  // (A caller that enqueues nothing else waits for the host instead, 11 us for two launches, 8 for one.)
+  constexpr int64_t kRetainFew = 98304;
   if (n * d <= kRetainFew) {
     hipLaunchKernelGGL(kv_retain_few_kernel, dim3(1), dim3(1024), 0, s, k, m, n, d, alpha, out, hdr);
   } else {

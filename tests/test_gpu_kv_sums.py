@@ -10,7 +10,8 @@ from tests.harness import KvProblem, np64, rel_fro, to_device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,d", [(1, 64), (63, 64), (4095, 64), (4096, 64), (4097, 64), (31, 8192), (32, 8192), (33, 8192)])
+@pytest.mark.parametrize("n,d", [(1, 64), (63, 64), (4095, 64), (4096, 64), (4097, 64), (31, 8192), (32, 8192), (33, 8192),
+                                 (1535, 64), (1536, 64), (1537, 64), (12, 8192), (13, 8192)])
 @pytest.mark.parametrize("have", ["k", "m", "both"])
 def test_retain_rate(n, d, have):
     import torch
