@@ -287,7 +287,8 @@ inline int64_t dh_split_tiles(const DhSplit& p, int64_t n_tiles, bool single) {
 // and, the reconstruction counting half the K-steps as its tokens do (store and reconstruction): d 1024: n 32768 67 / 71   65536
 // 123 / 126   100000 184 / 200   131072 274 / 253;   d 512: 100000 82 / 96   200000 158 / 177;   d 2048: 12000 80 / 86   24000 138 / 122.
 // The choice is within 3 % of the better edge at all of these but one: the reconstruction of 100000 x 1024, a tie by the fits, is
-// 9 % slower than it would be on edge 128.
+// 9 % slower than it would be on edge 128.  (Lengths as a gate with a retain rate of 0.44 leaves them.  Longer ones favour edge 256:
+// the reconstruction of 200000 x 512 alone, lengths in [0.8 d, d], 196 us on edge 128, 180 on 256.)
 inline int kv_tile_edge(bool f32, int mode, int M, int64_t Nn, int K, int64_t cus) {
   auto tiles = [&](int edge) { return tiles_of(M, Nn, edge); };
   if (tiles(64) <= 2 * cus) return 64;
