@@ -92,8 +92,8 @@ __global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restric
 // valid rows of H (16 bytes per lane and step; zeros from N_v to the next tile multiple) with their token ids,
 // gradients and statistics; for the backward the rows of dH of padded slots are zeroed.  Bound by the copy of H and the
 // zeros.  kScan: each workgroup scans the lengths itself (up to kIndexMaxR of them, a microsecond), which saves the launch
-// that would have to come first: three launches of 5 us each became one.  The range of the token ids is reported by the kernels that follow
-// (an id outside [0, V) is -1 here): the header is only cleared in this launch.
+// that would have to come first: three launches of 5 us each became one.  The range of the token ids is reported by the
+// kernels that follow (an id outside [0, V) is -1 here): the header is only cleared in this launch.
 // A wavefront takes kIndexRows consecutive rows at a time; its lanes look up their slots together.
 constexpr int kIndexMaxR = 4096, kIndexRows = 4;
 template <bool kScan>

@@ -523,8 +523,8 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void dz_kernel(DzArgs a) {
 // dH, the hidden states and dZ for dW, both operands of a parameter gradient.  Against K-contiguous copies of all of them
 // (8x8x256 step, d 2048, bf16): copies 294 -> 17 us (the zeroing of padding), dZ kernel, which had to write dZ in both orientations,
 // 5.57 -> 5.01 ms, dH 4.46 -> 4.50, dW 4.48 -> 4.46, the step 19.7 -> 18.8 ms; 4x8x2048, d 4096: dZ 39.7 -> 38.0 ms (the
-// step, 150 ms, by no more than its runs differ).  Which operand leads the ring makes no difference here; two transposing reads behind an MFMA instead of one cost
-// dW 2 %.
+// step, 150 ms, by no more than its runs differ).  Which operand leads the ring makes no difference here; two transposing
+// reads behind an MFMA instead of one cost dW 2 %.
 // Role: 0 = dH (contracts over a vocabulary chunk), 1 = dW (contracts over the valid tokens), 2 = a
 // parameter gradient of the KV gate (contracts over the tokens of a stream).  The code is the same; the
 // parameter only gives the uses distinct kernel names in profiles (and picks the lead operand).

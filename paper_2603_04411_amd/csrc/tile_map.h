@@ -219,8 +219,8 @@ inline int dw_edge(bool f32, int64_t m, int64_t rows, int64_t n) {
 // dH: m = d, n = token slots, contraction of `ksteps` 128-byte steps over the vocabulary that can be cut into
 // slices (see DhSplit): the largest edge that fills the chip with slices of 32 K-steps and does not
 // exceed the tokens by much, for fp32 as for bf16.  (An fp32 contraction that is too short to cut fills the rounds best
-// with 64 wide tiles: n 6000 d 1024 V 500 58 us against 72 on edge 128.)  Edge 256 / 128 / 64, us (fp32 once took edge 64 up to four rounds of 256
-// wide tiles):
+// with 64 wide tiles: n 6000 d 1024 V 500 58 us against 72 on edge 128.)  Edge 256 / 128 / 64, us (fp32 once took edge 64
+// up to four rounds of 256 wide tiles):
 //   bf16: n 1024 d 1024 V 20000 61.0 / 58.1 / 130    n 512 d 4096 V 32000 136 / 217 / 340    n 256 d 256 V 4096 24.5 / 15.0 / 12.4
 //   fp32: n 4096 d 1024 V 32000 1839 / 1960 / 2150   n 1024 d 1024 V 16000 269 / 258 / 326   n 512 d 256 V 4096 56 / 29 / 20
 //         n 4096 d 512 V 20000 607 / 620 / 671       n 512 d 512 V 20000 143 / 93 / 105      n 256 d 512 V 4096 60 / 31 / 22
