@@ -764,10 +764,12 @@ __global__ __launch_bounds__(64 * kWaves) void kv_pack_kernel(const T* __restric
 // long rows, whose copy covers it.  (8192 components of each of 32768 tokens still add up in 32 bits.)  Store, us, GPU time,
 // two launches / sixteen / four:
 //   bf16 d 64    n 1500 6.0 / 5.6 / 4.0   4500 6.4 / 5.7 / 5.4   6000 6.5 / 5.7 / 5.4   9000 7.0 / 6.1 / 7.0   16000 7.7 / 6.8 / 9.9
-//                20000 8.2 / 10.3 / 12.3   32768 10.0 / 12.0 / 21.5
-//   bf16 d 1024  n 1000 6.6 / 6.6 / 4.6   6000 7.7 / 7.6 / 6.7   9000 8.5 / 8.1 / 8.5   16000 10.5 / 9.8 / 12.8   24000 12.6 / 14.3 / 18.5
+//                16400 7.9 / 7.8   17000 8.2 / 9.4   20000 8.2 / 10.3 / 12.3   32768 10.0 / 12.0 / 21.5
+//   bf16 d 1024  n 1000 6.6 / 6.6 / 4.6   6000 7.7 / 7.6 / 6.7   9000 8.5 / 8.1 / 8.5   16000 10.5 / 9.8 / 12.8   16400 10.6 / 10.1
+//                17000 10.9 / 12.5   24000 12.6 / 14.3 / 18.5;   d 1536  n 16400 12.4 / 11.4   17000 12.8 / 14.0
 //   bf16 d 2048  n 24000 21.8 / 19.8 / 22.7   32768 27.1 / 24.6 / 29.4;   fp32 d 8192  n 700 21.7 / 31.9 / 19.4   6000 49.4 / 47.4 / 46.6
-constexpr int64_t kPackFew = 6144, kPackMost = 16384, kPackAll = 32768;
+constexpr int64_t kPackFew = 6144, kPackAll = 32768;
+constexpr int64_t kPackMost = 2 * 8192 + 64;   // the counts before the last workgroup's tokens are two rounds
 constexpr int64_t kPackLongRow = 4096;   // bytes
 static_assert(kPackAll * kKvMaxD <= INT32_MAX, "32-bit sums");
 constexpr int kPackWaves = 4, kPackAllWaves = 16;

@@ -21,8 +21,9 @@ def _problem(n, d, dtype):
 
 
 @pytest.mark.parametrize("n,d,dtype", [(1, 64, "bf16"), (63, 64, "f32"), (65, 128, "bf16"), (2047, 192, "bf16"), (2049, 1024, "bf16"),
-                                       (4097, 320, "f32"), (4500, 1024, "bf16"), (18433, 1024, "bf16"), (20000, 64, "bf16"), (257, 64, "bf16"), (6144, 64, "f32"), (6145, 64, "bf16"), (16384, 64, "bf16"),
-                                       (16385, 64, "f32"), (16385, 2048, "bf16"), (16385, 1984, "bf16"),
+                                       (4097, 320, "f32"), (4500, 1024, "bf16"), (18433, 1024, "bf16"), (20000, 64, "bf16"), (257, 64, "bf16"),
+                                       (6144, 64, "f32"), (6145, 64, "bf16"), (16384, 64, "bf16"), (16385, 64, "f32"),
+                                       (16385, 2048, "bf16"), (16385, 1984, "bf16"), (16448, 64, "bf16"), (16449, 64, "bf16"),
                                        (32767, 128, "bf16"), (32768, 576, "bf16"), (32769, 128, "f32"), (300, 8192, "f32"),
                                        (24001, 1984, "bf16"), (4200, 2048, "f32")])
 def test_store_and_reconstruct(n, d, dtype):
