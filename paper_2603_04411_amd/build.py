@@ -18,7 +18,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblmhead.so")
 TRACE_LIB = os.path.join(HERE, "liblmhead_trace.so")
-SOURCES = ["lmhead_api.hip", "lmhead_aux.hip", "lmhead_loss.hip", "lmhead_gemm.hip", "lmhead_probe.hip",
+SOURCES = ["lmhead_api.hip", "lmhead_aux.hip", "lmhead_loss.hip", "lmhead_gemm.hip", "lmhead_stream.hip", "lmhead_probe.hip",
            "dynakv_api.hip", "dynakv_aux.hip", "dynakv_gemm.hip", "dynakv_gate.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

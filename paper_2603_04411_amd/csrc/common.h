@@ -42,8 +42,8 @@ struct WsLayout {
   int64_t dp;       // d rounded up to the tile
   int64_t Vc;       // vocabulary chunk of the backward (multiple of the tile)
   int64_t nchunks;  // number of vocabulary chunks
-  int edge;         // tile edge of the logits kernels
-  int64_t ntiles;   // vocabulary tiles of `edge` = planes of per-tile softmax statistics per row
+  int edge;         // tile edge of the forward's logits, 0: it takes W in ranges (lmhead_stream.hip)
+  int64_t ntiles;   // vocabulary tiles of `edge`, or ranges = planes of softmax statistics per row
   // Row pitches (elements) of the workspace matrices.  Each is its logical width plus one
   // 128-byte line: a power-of-two pitch would put every row of a tile on the same L2
   // channel and set (the token-major operands have a pitch of Ncap elements, often 2^k).
@@ -92,8 +92,13 @@ static inline WsLayout make_layout(const lmhead_desc* d, int npol = 1) {
   L.nchunks = (L.Vp + vc - 1) / vc;
   const bool f32 = d->dtype == LMHEAD_F32;
   const bool fp8 = (d->flags & LMHEAD_FLAG_FP8_LOGITS) != 0;
-  L.edge = fp8 ? kTile : logits_edge(f32, d->V, L.N);
-  L.ntiles = (d->V + L.edge - 1) / L.edge;
+#if defined(LMHEAD_BF16_BLOCK) && LMHEAD_BF16_BLOCK != 16
+  const bool streams = false;   // written for 16x16x32 blocks
+#else
+  const bool streams = !f32 && !fp8 && logits_stream(d->V, d->d, L.N);
+#endif
+  L.edge = fp8 ? kTile : streams ? 0 : logits_edge(f32, d->V, L.N);
+  L.ntiles = streams ? kComputeUnits : (d->V + L.edge - 1) / L.edge;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
@@ -182,8 +187,8 @@ struct FwdArgs {
   int64_t ldW;
   int d, V;
   int64_t Ncap;
-  int edge;            // tile edge: 64, 128 or 256 (256 for e4m3)
-  int ntiles;          // vocabulary tiles of that edge (one per workgroup and policy)
+  int edge;            // tile edge: 64, 128 or 256 (256 for e4m3); 0: ranges
+  int ntiles;          // vocabulary tiles of that edge, or ranges (one per workgroup and policy)
   const int32_t* tok_c;
   const WsHeader* hdr;
   float* part;         // [npol][3][ntiles][Ncap]: per-tile (max, sum exp, sum exp*z) of each row
@@ -193,6 +198,7 @@ struct FwdArgs {
   float zscale;        // logits = accumulator * zscale (1, or 2^-(e_H + e_W) for e4m3 operands)
 };
 hipError_t launch_fwd(int dtype, const FwdArgs& a, hipStream_t s);
+hipError_t launch_fwd_stream(const FwdArgs& a, hipStream_t s);   // edge 0
 
 // Merges the per-tile partials and scatters logp / lse / entropy to slot order (0 on padding).
 // A valid slot whose tok_c is -1 sets header.err.

@@ -275,7 +275,7 @@ int lmhead_logprob_bwd(const lmhead_desc* desc, const void* H, const void* W, co
     za.Ncap = L.Ncap;
     za.ldZ = L.ldZ;
     za.c0 = c0;
-    za.edge = L.edge;
+    za.edge = L.edge ? L.edge : logits_edge(dt == LMHEAD_F32, desc->V, L.N);   // dZ takes tiles also where the forward does not
     za.ntiles = ntiles;
     za.tok_c = w.at<int32_t>(L.tok_c);
     za.g_c = w.at<float>(L.g_c);

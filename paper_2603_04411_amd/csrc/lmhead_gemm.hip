@@ -16,15 +16,11 @@
 
 #include "common.h"
 #include "gemm_core.h"
+#include "logits_tile.h"
 
 namespace lmhead {
 
 namespace {
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kNegInf = -__builtin_huge_valf();
-
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Which operand leads the LDS ring in each kernel (see GemmTile::run); true = the B side.
 // Measured on the 32x8x2048 workload with the 16x16x32 main loop: the logits kernels do best with the
@@ -40,17 +36,6 @@ using Tile = GemmTile<E, Edge, Edge, 2, 2, kLeadB, false, kTransA, kTransB, kWal
 constexpr int kMapBx = 4, kMapBy = 4;
 // The forward does best with narrower, taller blocks (measured on the 32x8x2048 workload).
 constexpr int kFwdMapBx = 2, kFwdMapBy = 8;
-
-// Merge (m2, s2, t2) into (m, s, t): statistics of a union of disjoint logit sets.
-__device__ inline void merge_stats(float& m, float& s, float& t, float m2, float s2, float t2) {
-  const float mn = fmaxf(m, m2);
-  const float ms = (mn == kNegInf) ? 0.f : mn;
-  const float a = fast_exp2((m - ms) * kLog2e);
-  const float b = fast_exp2((m2 - ms) * kLog2e);
-  s = s * a + s2 * b;
-  t = t * a + t2 * b;
-  m = mn;
-}
 
 template <typename E, int Edge>
 __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void fwd_kernel(FwdArgs a) {
@@ -101,138 +86,18 @@ __global__ __launch_bounds__(Tile<E>::NT, 256 / Edge) void fwd_kernel(FwdArgs a)
   G::run(acc, Wp + (int64_t)m0 * pitchW, offA, static_cast<const char*>(a.Hc) + n0 * pitchH, offB, ksteps, smem, 1);
   trace_stamp(2, 1); trace_cycles(2, 1);
 
-  float mr[G::TN], sr[G::TN], tr[G::TN];
-#pragma unroll
-  for (int j = 0; j < G::TN; ++j) {
-    mr[j] = kNegInf;
-    sr[j] = 0.f;
-    tr[j] = 0.f;
-  }
-
-  // target-logit capture: only where some lane's target falls inside this tile
-  {
-    int relj[G::TN];
-    bool hit = false;
-#pragma unroll
-    for (int j = 0; j < G::TN; ++j) {
-      const int tk = tkj[j];
-      hit |= (tk >= m0) & (tk < m0 + G::BM);
-      relj[j] = tk - m0 - G::m_base();   // compared with compile-time constants
-    }
-    if (__any(hit)) {
-#pragma unroll
-      for (int j = 0; j < G::TN; ++j) {
-        float zsel = 0.f;
-        bool found = false;
-#pragma unroll
-        for (int i = 0; i < G::TM; ++i)
-#pragma unroll
-          for (int v = 0; v < G::VB; ++v) {
-            const bool eq = relj[j] == G::m_const(i, v);
-            zsel = eq ? acc[i][j][v] : zsel;
-            found |= eq;
-          }
-        if (found) {
-          zy[n0 + G::n_of(j)] = zsel * a.zscale;
-          // vocabulary column of the accumulator element just selected (the compare above held for it)
-          gid[n0 + G::n_of(j)] = m0 + G::m_base() + relj[j];
-        }
-      }
-    }
-  }
-
+  capture_target<G>(a, acc, tkj, m0, m0 + G::BM, n0, zy, gid);
   trace_stamp(11, 1);
-  // softmax statistics of this tile, inside the lane, 16 values of one token column at a time (one
-  // 32x32 block or four 16x16 blocks); the scheduling barrier after each group keeps the
-  // accumulator reads of later groups from being hoisted, so only 16 values are live in VGPRs at a time
-  {
-    const int vlim = a.V - m0 - G::m_base();   // vocabulary rows with m_const >= vlim are padding
-    // logit = accumulator * zscale (zscale = 1 unless the operands are scaled 8-bit copies); the factor
-    // is folded into the constants of the group instead of being applied per element
-    const float zscale = a.zscale;
-    const float kz = kLog2e * zscale;
-    constexpr int BPC = 16 / G::VB < G::TM ? 16 / G::VB : G::TM;   // blocks per group
-    constexpr int GV = BPC * G::VB;            // values per group: 16 (8 in the 64 wide bf16 tile)
-    static_assert(G::TM % BPC == 0 && GV % 2 == 0, "whole groups");
-    auto group_stats = [&](auto full_tag, auto ent_tag, int ic, int j, float& m_run, float& s_run, float& t_run) {
-      constexpr bool kFull = decltype(full_tag)::value;
-      constexpr bool kEnt = decltype(ent_tag)::value;   // the third accumulator (sum exp * z) feeds the entropy only
-      float z[GV];
-      bool ok[GV];
-#pragma unroll
-      for (int b = 0; b < BPC; ++b)
-#pragma unroll
-        for (int v = 0; v < G::VB; ++v) {
-          ok[b * G::VB + v] = kFull || G::m_const(ic * BPC + b, v) < vlim;
-          z[b * G::VB + v] = ok[b * G::VB + v] ? acc[ic * BPC + b][j][v] : kNegInf;
-        }
-      float tmax = fmaxf(z[0], z[1]);
-#pragma unroll
-      for (int v = 2; v < GV; v += 2) tmax = fmaxf(tmax, fmaxf(z[v], z[v + 1]));
-      const float mn = fmaxf(m_run, tmax * zscale);
-      const float ms = (mn == kNegInf) ? 0.f : mn;
-      const float sc = fast_exp2((m_run - ms) * kLog2e);
-      const float bias = -ms * kLog2e;
-      float ss = 0.f, ts = 0.f;
-#pragma unroll
-      for (int v = 0; v < GV; ++v) {
-        const float e = fast_exp2(fmaf(z[v], kz, bias));   // exp2(-inf) = 0 on padding rows
-        ss += e;
-        if constexpr (kEnt) ts = fmaf(e, ok[v] ? z[v] : 0.f, ts);
-      }
-      s_run = fmaf(s_run, sc, ss);
-      if constexpr (kEnt) t_run = fmaf(t_run, sc, ts * zscale);
-      m_run = mn;
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto all_groups = [&](auto full_tag, auto ent_tag) {
-#pragma unroll
-      for (int j = 0; j < G::TN; ++j)
-#pragma unroll
-        for (int ic = 0; ic < G::TM / BPC; ++ic) group_stats(full_tag, ent_tag, ic, j, mr[j], sr[j], tr[j]);
-    };
-    const bool want_t = a.want_entropy && pol == 0;   // entropy is reported for the first weight matrix only
-    if (m0 + G::BM <= a.V) {
-      if (want_t) all_groups(std::true_type{}, std::true_type{}); else all_groups(std::true_type{}, std::false_type{});
-    } else {
-      if (want_t) all_groups(std::false_type{}, std::true_type{}); else all_groups(std::false_type{}, std::false_type{});
-    }
-  }
-
+  TileStats<G> stats;
+  stats.clear();
+  const bool want_t = a.want_entropy && pol == 0;   // entropy is reported for the first weight matrix only
+  // vocabulary rows with m_const >= V - m0 - m_base are padding
+  stats.add(acc, a.zscale, a.V - m0 - G::m_base(), m0 + G::BM <= a.V, want_t);
   trace_stamp(12, 1);
-  // combine the lane groups of a block (same token, other vocabulary rows), then the WGM waves via LDS
   float* red = reinterpret_cast<float*>(smem);  // [WGM][BN][3]
-#pragma unroll
-  for (int j = 0; j < G::TN; ++j) {
-#pragma unroll
-    for (int o = 32; o >= G::NB; o >>= 1) {
-      const float m2 = __shfl_xor(mr[j], o);
-      const float s2 = __shfl_xor(sr[j], o);
-      const float t2 = __shfl_xor(tr[j], o);
-      merge_stats(mr[j], sr[j], tr[j], m2, s2, t2);
-    }
-    if (G::lane() < G::NB) {
-      float* q = red + ((size_t)G::wave_m() * G::BN + G::n_of(j)) * 3;
-      q[0] = mr[j];
-      q[1] = sr[j];
-      q[2] = tr[j];
-    }
-  }
+  stats.to_lds(red);
   trace_stamp(13, 1);
-  lds_barrier();
-  for (int n = threadIdx.x; n < G::BN; n += G::NT) {
-    float m = red[n * 3], s = red[n * 3 + 1], t = red[n * 3 + 2];
-#pragma unroll
-    for (int w = 1; w < G::WGM; ++w) {
-      const float* q = red + ((size_t)w * G::BN + n) * 3;
-      merge_stats(m, s, t, q[0], q[1], q[2]);
-    }
-    const size_t base = (size_t)tile * a.Ncap + n0 + n;
-    const size_t plane = (size_t)a.ntiles * a.Ncap;
-    part[base] = m;
-    part[plane + base] = s;
-    if (a.want_entropy && pol == 0) part[2 * plane + base] = t;
-  }
+  stats.store(a, red, part, tile, n0, want_t);
 #ifdef LMHEAD_TRACE
   trace_stamp(3, 1);
   trace_cycles(3, 1);
@@ -707,6 +572,7 @@ static hipError_t launch_fwd_edge(const FwdArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_fwd(int dtype, const FwdArgs& a, hipStream_t s) {
+  if (a.edge == 0) return launch_fwd_stream(a, s);
   if (dtype == kDtypeFp8) return launch_fwd_e<fp8_tag, 256>(a, s);   // its main loop is written for edge 256
   return dtype == LMHEAD_BF16 ? launch_fwd_edge<bf16_tag>(a, s) : launch_fwd_edge<f32_tag>(a, s);
 }

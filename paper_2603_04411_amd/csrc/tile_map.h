@@ -134,6 +134,17 @@ inline int64_t logits_slots(bool f32, int64_t V, int edge) {
 inline int logits_edge(bool f32, int64_t V, int64_t n) {
   return n <= logits_slots(f32, V, 64) ? 64 : n <= logits_slots(f32, V, 128) ? 128 : kTile;
 }
+// The forward of as many bf16 slots as 128 wide tiles are for, over a W of 96 MB or more: one range of rows per compute unit instead of
+// tiles (lmhead_stream.hip).  A W that the caches hold, or most of it, is read sooner by more workgroups than that.  Call, us, tiles /
+// ranges, 64 (64), 192 (120) and 200 (200) slots (valid); beyond them the 256 wide tiles are as fast where their rounds are full:
+//   d 2048 V 151936 144/116   169/119   214/169      d 4096 V 151936 254/212   283/223   398/313     d 1024 V 151936 80/67 83/68 118/98
+//   d 2048 V 32000  44/42     47/43     59/49        d 4096 V 32000  69/65     75/68     100/77      d 2560 V 64000  87/68 82/69 120/98
+//   d 768 V 64000   35/32     34/32     48/43        d 4096 V 16000  60/62     69/63     69/69       d 1024 V 32000  27/30 30/30 36/34
+//   d 512 V 32000   20/24     22/24     25/28        256 slots, 256 valid: d 2048 V 151936 190/174   d 2560 V 64000 90/98
+constexpr int64_t kStreamSlots = 128 * 8 / 5, kStreamBytes = (int64_t)96 << 20, kStreamRows = 64;
+inline bool logits_stream(int64_t V, int64_t d, int64_t n) {
+  return n <= kStreamSlots && V * d * 2 >= kStreamBytes && V >= kStreamRows * kComputeUnits;
+}
 // Per-tile softmax statistics (planes x slots) that the logits of any number of slots up to n need: fewer slots take narrower
 // tiles, i.e. more planes, and a workspace sized for a large batch has to serve the smaller ones.
 inline int64_t logits_part_slots(bool f32, int64_t V, int64_t n) {
@@ -141,6 +152,10 @@ inline int64_t logits_part_slots(bool f32, int64_t V, int64_t n) {
   for (int edge : {64, 128, kTile}) {
     const int64_t slots = edge == kTile ? n : logits_slots(f32, V, edge);
     const int64_t need = (V + edge - 1) / edge * (((slots < n ? slots : n) + kTile - 1) / kTile * kTile);
+    most = need > most ? need : most;
+  }
+  if (!f32 && V >= kStreamRows * kComputeUnits) {   // the planes of logits_stream, one per range
+    const int64_t need = (int64_t)kComputeUnits * (((kStreamSlots < n ? kStreamSlots : n) + kTile - 1) / kTile * kTile);
     most = need > most ? need : most;
   }
   return most;
