@@ -571,9 +571,10 @@ __global__ __launch_bounds__(256) void kv_prepare_kernel(KvPrepareArgs a, int es
     __builtin_memcpy(&v, e, 16);
     const int k = r0 + rc * VEC;
     const int pos = c.flipped ? d - 1 - (c0 + col) : c0 + col;
-    const int w = pos / (d / 4), q = pos % (d / 4) / (d / 16), i = pos % (d / 16) / 4;
+    constexpr int NW = kKvGateWaves;
+    const int w = pos / (d / NW), q = pos % (d / NW) / (d / (4 * NW)), i = pos % (d / (4 * NW)) / 4;
     const int lane = k / 8 % 4 * 16 + 4 * q + pos % 4;
-    *reinterpret_cast<uint4*>(out + (((int64_t)w * (d / 32) + k / 32) * (d / 64) + i) * 512 + lane * 8) = v;
+    *reinterpret_cast<uint4*>(out + (((int64_t)w * (d / 32) + k / 32) * (d / (16 * NW)) + i) * 512 + lane * 8) = v;
   }
 }
 

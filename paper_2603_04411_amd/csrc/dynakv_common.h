@@ -188,13 +188,14 @@ struct KvGateArgs {
 };
 // From this many tokens on.  Its workgroups take 64 tokens (128 at d = 512) through everything, 60 us a round, so below
 // a round the separate kernels with their smaller tiles win.  Whole call, us, separate kernels / this one:
-//   d 1024: n 8192 60.9 / 65.5   12000 90.6 / 70.0   16384 99.9 / 83.6   65536 392 / 287   262144 1334 / 1027
-//   d 512:  n 8192 34.5 / 38.3   16384 50.0 / 42.1   32768 77.7 / 49.0   65536 154 / 90    262144 560 / 342
+//   d 1024: n 8192 55.6 / 61.2   12000 90.6 / 64.0   16384 99.9 / 73   65536 392 / 248   262144 1334 / 976
+//   d 512:  n 8192 30.4 / 34.6   10000 34.6 / 35.2   16384 50.0 / 38   65536 154 / 82    262144 560 / 303
 // bf16 at 512 and 1024 only: the tile is laid out for a whole token row in LDS next to 256 accumulators a lane, 64 tokens of
 // 1024 or 128 of 512 components.  A row of 2048 leaves room for 32 tokens, i.e. twice the parameter stream per token, which
 // is the bound; 256 and 768 would take other piece and lane maps, unwritten since no workload has such a d at
 // these lengths, and fp32 is bound by the matrix rate, which the separate kernels come close to (135 of 157 TFLOP/s).
 constexpr int kKvGateFrom = 10240;
+constexpr int kKvGateWaves = 8;
 bool kv_gate_fits(int dtype, int64_t n, int d, int64_t ldx);
 hipError_t launch_kv_gate(const KvGateArgs& a, int d, hipStream_t s);
 
@@ -221,9 +222,9 @@ static inline KvCount make_kv_count(const int32_t* k, int64_t n, int d, int nbuc
   return {k, n, d, nbuckets, (int)((n + per - 1) / per), (int)per, hist};
 }
 
-// A parameter matrix (bf16, d x d, d a multiple of 64) as the MFMA fragments in the order in which kv_gate_kernel's
-// wavefronts consume them, ((w * d/32 + s) * d/64 + i) KB + 16 lane bytes holding in[k][c] for the 8 values
-// k = 32 s + 8 (lane / 16) + [0, 8) and column c = position d/4 w + d/16 ((lane % 16) / 4) + 4 i + lane % 4
+// A parameter matrix (bf16, d x d, d a multiple of 128) as the MFMA fragments in the order in which kv_gate_kernel's
+// wavefronts consume them, ((w * d/32 + s) * d/128 + i) KB + 16 lane bytes holding in[k][c] for the 8 values
+// k = 32 s + 8 (lane / 16) + [0, 8) and column c = position d/8 w + d/32 ((lane % 16) / 4) + 4 i + lane % 4
 // (flipped: c = d - 1 - position).
 struct KvCopy {
   const void* in;

@@ -3,8 +3,9 @@
 // ask for the soft mask or x^ (prefill, decoding); training takes the separate kernels.
 //
 // A workgroup owns TOK = 16 TJ tokens and ALL d output columns of both products, so that a token's softmax
-// never crosses workgroups: four wavefronts, each d / 4 columns x TOK tokens of 16x16 MFMA blocks (256 accumulator
-// registers).  The token rows (TOK x d bf16, 128 KB) sit in LDS for the whole product and are read by all four
+// never crosses workgroups: eight wavefronts, each d / 8 columns x TOK tokens of 16x16 MFMA blocks (128 accumulator
+// registers; two on a SIMD, which cover each other's waits: four of twice the columns are up to 7 % slower at d = 512, as
+// fast at 262144 x 1024).  The token rows (TOK x d bf16, 128 KB) sit in LDS for the whole product and are read by all
 // wavefronts; the parameter matrices stream from L2 straight into registers, each value into the one wavefront that
 // needs it, in fragments of 1 KB that kv_prepare_kernel has laid out in the order they are consumed (a full-line
 // load per instruction, no LDS, no barrier in the main loop).  A fragment register is reloaded right behind
@@ -13,13 +14,13 @@
 // What bounds it: the parameter stream.  Every 64 tokens read 2 d^2 x 2 bytes (4 MB at d = 1024) through a compute unit's
 // 64 bytes per clock, which just matches the matrix cores' pace; 256 x 256 tiles need half of that but pay a pipeline
 // fill and an epilogue per 16 K-steps, one write and one read of the fp32 logits and one read of x~ (3.2 GB at
-// 262144 x 1024).  Measured there: 1334 us with the separate kernels, 1027 with this one.  Of a round's 64 us (sixteen
-// rounds) the matrix pipe is busy for 34; about 13 are the stream's (with every fragment load an L1 hit a round takes 52) and
-// 8 the softmax (56 without it), which a wavefront alone on its SIMD cannot overlap with anything.
+// 262144 x 1024).  Measured there: 1334 us with the separate kernels, 1036 with four wavefronts that all read the same parameters at
+// a time, now 976 (d = 512: 313, now 303; 12000 x 1024: 69, now 64; with both contractions turned 940, 294 and 63).  Of a round's
+// 60 us (sixteen rounds) the matrix pipe is busy for 34, the softmax takes 8.
 //
-// Column order: accumulator element v of block i in lane group q of wavefront w is POSITION (d/4) w + (d/16) q + 4 i + v of
-// the mask, i.e. a lane holds d / 16 consecutive positions of one token per token block, and the cumulative sum is a
-// loop inside the lane plus an exchange of 16 partial sums per token.  (Position p is gate column p, or d - 1 - p for
+// Column order: accumulator element v of block i in lane group q of wavefront w is POSITION (d/8) w + (d/32) q + 4 i + v of
+// the mask, i.e. a lane holds d / 32 consecutive positions of one token per token block, and the cumulative sum is a
+// loop inside the lane plus an exchange of 32 partial sums per token.  (Position p is gate column p, or d - 1 - p for
 // Eq. 6 as printed; the fragment layout of W and the bias follow that order.)
 #include "dynakv_common.h"
 #include "gemm_core.h"
@@ -34,27 +35,27 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 template <int NI_, int TJ_>
 struct Gate {
-  static constexpr int NI = NI_, TJ = TJ_;      // 16-row blocks of columns per wavefront, 16-token blocks
-  static constexpr int D = 64 * NI;
+  static constexpr int NI = NI_, TJ = TJ_, NW = kKvGateWaves;   // 16-row blocks of columns per wavefront, 16-token blocks, wavefronts
+  static constexpr int D = 16 * NW * NI;
   static constexpr int TOK = 16 * TJ;
   static constexpr int S = D / 32;              // K sub-steps of one MFMA each
   static constexpr int ROW = D * 2;             // bytes of a token row
   static constexpr int PITCH = ROW + 16;        // in LDS: 16 rows' chunks fall on different banks
   static constexpr int X_BYTES = TOK * PITCH;
   static constexpr int BIAS_OFF = X_BYTES, RED_OFF = BIAS_OFF + D * 4;
-  static constexpr int LDS_BYTES = RED_OFF + 3 * 4 * TOK * 4;
+  static constexpr int LDS_BYTES = RED_OFF + 3 * NW * TOK * 4;
   static constexpr int STEP = NI * 1024;        // bytes of one wavefront's fragments per sub-step
-  static constexpr int PIECES = TOK / 4 * (ROW / 1024);   // 1 KB pieces of token rows per wavefront
-  static_assert((ROW == 1024 || ROW == 2048) && PIECES % S == 0 && S % 2 == 0 && S >= 6 && LDS_BYTES <= 160 * 1024, "tile shape");
+  static constexpr int PIECES = TOK / NW * (ROW / 1024);   // 1 KB pieces of token rows per wavefront
+  static_assert((ROW == 1024 || ROW == 2048) && (PIECES % S == 0 || S % PIECES == 0) && S % 2 == 0 && S >= 6 && LDS_BYTES <= 160 * 1024, "tile shape");
 };
 
 template <typename G>
-__global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
+__global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a) {
   typedef __attribute__((address_space(3))) void* lptr_t;
-  constexpr int NI = G::NI, TJ = G::TJ, S = G::S;
+  constexpr int NI = G::NI, TJ = G::TJ, NW = G::NW, S = G::S;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float* const bias_s = reinterpret_cast<float*>(smem + G::BIAS_OFF);
-  float* const red = reinterpret_cast<float*>(smem + G::RED_OFF);   // [3][4 wavefronts][TOK]
+  float* const red = reinterpret_cast<float*>(smem + G::RED_OFF);   // [3][NW][TOK]
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // The lane number, opaque to the optimiser: every phase derives its addresses from it anew.  (Hoisted out of the
   // tile loop they were 25 registers too many, and each reload from scratch memory in the loop a wait for
@@ -77,10 +78,10 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
   const __amdgpu_buffer_rsrc_t rX = rsrc(a.x, ((a.n - 1) * a.ldx + G::D) * 2), rXt = rsrc(a.xt, a.n * G::D * 2);
   const int woff = w * S * G::STEP;   // this wavefront's part of a stream
 
-  for (int c = threadIdx.x; c < G::D; c += 256) bias_s[c] = a.bias[a.literal ? G::D - 1 - c : c];
+  for (int c = threadIdx.x; c < G::D; c += 64 * NW) bias_s[c] = a.bias[a.literal ? G::D - 1 - c : c];
 
   // 1 KB piece p of this wavefront's token rows: tile row and byte within it
-  auto piece_row = [&](int p) { return w * (G::TOK / 4) + p / (G::ROW / 1024); };
+  auto piece_row = [&](int p) { return w * (G::TOK / NW) + p / (G::ROW / 1024); };
   auto piece_col = [&](int p) { return p % (G::ROW / 1024) * 1024; };
   auto load_x = [&](int64_t t0) {
     const uint32_t pitch = (uint32_t)(a.ldx * 2);
@@ -96,6 +97,10 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
 
   typedef u32x4_t Frags[NI];
   const int frag_vo = (threadIdx.x & 63) * 16;
+  // Each workgroup of an XCD begins the second contraction at another sub-step: one that all of them read at a time is 16 KB of the
+  // parameters, which meet on a few of the L2's channels.  (The first one keeps the order of the separate kernels, so that
+  // x~ is the same to the bit.)
+  const int turn = blockIdx.x / kNumXcd * 5;
   auto load_frag = [&](const __amdgpu_buffer_rsrc_t& r, int s, int i) {
     return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, frag_vo, woff + s * G::STEP + i * 1024, 0));
   };
@@ -103,10 +108,10 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
   Frags wb[2];
   u32x4_t fb[2][TJ];
   // One sub-step: NI x TJ MFMAs (the first of a product starts from 0: no pass that clears the accumulators, and
-  // none of the wait states that a just-written addend needs, see GemmTile::settle); the token fragments of the next sub-step are read behind the first of them, and
+  // none of the wait states that a just-written addend needs, see GemmTile::settle); the token fragments of the next sub-step, `s`, are read behind the first of them, and
   // each parameter fragment is replaced, one MFMA after its last use, by that of sub-step `ns` of stream `nr`.
   auto substep = [&](auto first_tag, const char* xrow, int s, int buf, bool more, bool refill, const __amdgpu_buffer_rsrc_t& nr, int ns) {
-    const char* const xn = xrow + (s + 1) * 64;
+    const char* const xn = xrow + s * 64;   // of the next sub-step
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
 #pragma unroll
@@ -127,26 +132,30 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     if (refill) wb[buf][NI - 1] = load_frag(nr, ns, NI - 1);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // acc = X W for one stream; with `chain`, the first two sub-steps of the next stream are on their way at the end
-  auto product = [&](const __amdgpu_buffer_rsrc_t& r, bool chain, const __amdgpu_buffer_rsrc_t& next, auto&& per_substep) {
+  // acc = X W for one stream, from sub-step `first` round to it; with `chain`, the first two sub-steps of the next stream are on their
+  // way at the end
+  auto product = [&](const __amdgpu_buffer_rsrc_t& r, int first, bool chain, const __amdgpu_buffer_rsrc_t& next, int first_next,
+                     auto&& per_substep) {
     const int l = lane_id();
     const char* const xrow = smem + (l & 15) * G::PITCH + (l >> 4) * 16;
+    auto at = [&](int s) { return (s + first) & (S - 1); };
+    auto at_next = [&](int s) { return (s + first_next) & (S - 1); };
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) fb[0][j] = *reinterpret_cast<const u32x4_t*>(xrow + j * 16 * G::PITCH);
+    for (int j = 0; j < TJ; ++j) fb[0][j] = *reinterpret_cast<const u32x4_t*>(xrow + at(0) * 64 + j * 16 * G::PITCH);
     __builtin_amdgcn_sched_barrier(0);
-    substep(std::true_type{}, xrow, 0, 0, true, true, r, 2);
+    substep(std::true_type{}, xrow, at(1), 0, true, true, r, at(2));
     per_substep(0);
-    substep(std::false_type{}, xrow, 1, 1, true, true, r, 3);
+    substep(std::false_type{}, xrow, at(2), 1, true, true, r, at(3));
     per_substep(1);
     for (int s = 2; s < S - 2; s += 2) {
-      substep(std::false_type{}, xrow, s, 0, true, true, r, s + 2);
+      substep(std::false_type{}, xrow, at(s + 1), 0, true, true, r, at(s + 2));
       per_substep(s);
-      substep(std::false_type{}, xrow, s + 1, 1, true, true, r, s + 3);
+      substep(std::false_type{}, xrow, at(s + 2), 1, true, true, r, at(s + 3));
       per_substep(s + 1);
     }
-    substep(std::false_type{}, xrow, S - 2, 0, true, chain, next, 0);
+    substep(std::false_type{}, xrow, at(S - 1), 0, true, chain, next, at_next(0));
     per_substep(S - 2);
-    substep(std::false_type{}, xrow, S - 1, 1, false, chain, next, 1);
+    substep(std::false_type{}, xrow, 0, 1, false, chain, next, at_next(1));
     per_substep(S - 1);
     asm volatile("s_nop 15\n\ts_nop 15");   // results are read by ordinary instructions next
   };
@@ -167,12 +176,12 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     __syncthreads();
 
     // ---- x~ = x U
-    product(rU, true, rW, [](int) {});
+    product(rU, 0, true, rW, turn, [](int) {});
     lds_barrier();   // every wavefront has read its last token fragments
     // rounded to bf16 into the place of x; blocks i, i + 1 are 8 consecutive columns
     {
       const int l = lane_id();
-      char* const dst = smem + (l & 15) * G::PITCH + (w * (G::D / 4) + (l >> 4) * (G::D / 16)) * 2;
+      char* const dst = smem + (l & 15) * G::PITCH + (w * (G::D / NW) + (l >> 4) * (G::D / (4 * NW))) * 2;
 #pragma unroll
       for (int j = 0; j < TJ; ++j)
 #pragma unroll
@@ -189,10 +198,12 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
     // ---- x~ W, with x~ streamed out to memory meanwhile
     const int l2 = lane_id();
     const uint32_t xt0 = (uint32_t)t0 * G::ROW + l2 * 16;
-    product(rW, false, rU, [&](int s) {
+    product(rW, turn, false, rU, 0, [&](int s) {
+      constexpr int kEvery = S > G::PIECES ? S / G::PIECES : 1;   // sub-steps a piece
+      if (s % kEvery != 0) return;
 #pragma unroll
-      for (int u = 0; u < G::PIECES / S; ++u) {
-        const int p = s * (G::PIECES / S) + u;
+      for (int u = 0; u < (G::PIECES > S ? G::PIECES / S : 1); ++u) {
+        const int p = s * G::PIECES / S + u;
         const u32x4_t v = *reinterpret_cast<const u32x4_t*>(smem + piece_row(p) * G::PITCH + piece_col(p) + l2 * 16);
         __builtin_amdgcn_raw_buffer_store_b128(v, rXt, xt0 + piece_row(p) * G::ROW + piece_col(p), 0, 0);
       }
@@ -215,7 +226,7 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
       // every step of the contraction at the bias's magnitude.  (262144 tokens: 1019 -> 1026 us at d = 1024, 317 -> 313
       // at d = 512, the passes that cleared the accumulators having gone; as fp32 MFMAs of bias * 1 under the maxima of
       // the neighbouring block 1084 and 336.)  Four running maxima per token: a single chain would wait for itself.
-      const float* const bp = bias_s + w * (G::D / 4) + q * (G::D / 16);
+      const float* const bp = bias_s + w * (G::D / NW) + q * (G::D / (4 * NW));
       f32x4_t m4[TJ];
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
@@ -243,7 +254,9 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
       const float* const r = rt + 16 * j;
-      mx[j] = fmaxf(fmaxf(r[0], r[G::TOK]), fmaxf(r[2 * G::TOK], r[3 * G::TOK]));
+      mx[j] = r[0];
+#pragma unroll
+      for (int u = 1; u < NW; ++u) mx[j] = fmaxf(mx[j], r[u * G::TOK]);
       float sum = 0.f;
 #pragma unroll
       for (int i = NI - 1; i >= 0; --i) {
@@ -256,17 +269,17 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
       own[j] = sum;
       const float s1 = of_lane(l3 + 16, sum), s2 = of_lane(l3 + 32, sum), s3 = of_lane(l3 + 48, sum);   // modulo 64
       above[j] = (q < 1 ? s3 : 0.f) + (q < 2 ? s2 : 0.f) + (q < 3 ? s1 : 0.f);
-      if (q == 0) rt[(4 + w) * G::TOK + 16 * j] = above[j] + sum;
+      if (q == 0) rt[(NW + w) * G::TOK + 16 * j] = above[j] + sum;
       __builtin_amdgcn_sched_barrier(0);
     }
     lds_barrier();
     int cnt[TJ];
 #pragma unroll
     for (int j = 0; j < TJ; ++j) {
-      const float* const r = rt + 4 * G::TOK + 16 * j;
+      const float* const r = rt + NW * G::TOK + 16 * j;
       float tot = 0.f, behind = 0.f;
 #pragma unroll
-      for (int u = 3; u >= 0; --u) {
+      for (int u = NW - 1; u >= 0; --u) {
         if (u == w) behind = tot;
         tot += r[u * G::TOK];
       }
@@ -291,12 +304,15 @@ __global__ __launch_bounds__(256) void kv_gate_kernel(KvGateArgs a) {
       }
       cnt[j] += of_lane(x16, cnt[j]);
       cnt[j] += of_lane(x32, cnt[j]);
-      if (q == 0) reinterpret_cast<int*>(rt)[(8 + w) * G::TOK + 16 * j] = cnt[j];
+      if (q == 0) reinterpret_cast<int*>(rt)[(2 * NW + w) * G::TOK + 16 * j] = cnt[j];
     }
     lds_barrier();
     if (threadIdx.x < G::TOK && t0 + threadIdx.x < a.n) {
-      const int* const r = reinterpret_cast<const int*>(red) + 8 * G::TOK + threadIdx.x;
-      a.k[t0 + threadIdx.x] = (r[0] + r[G::TOK]) + (r[2 * G::TOK] + r[3 * G::TOK]);
+      const int* const r = reinterpret_cast<const int*>(red) + 2 * NW * G::TOK + threadIdx.x;
+      int sum = 0;
+#pragma unroll
+      for (int u = 0; u < NW; ++u) sum += r[u * G::TOK];
+      a.k[t0 + threadIdx.x] = sum;
     }
   }
 }
@@ -307,7 +323,7 @@ hipError_t launch(const KvGateArgs& a, hipStream_t s) {
   const int64_t cus = device_compute_units();
   hipError_t e = allow_lds<kv_gate_kernel<G>>(G::LDS_BYTES);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kv_gate_kernel<G>, dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(256), G::LDS_BYTES, s, a);
+  hipLaunchKernelGGL(kv_gate_kernel<G>, dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(64 * G::NW), G::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
@@ -320,7 +336,7 @@ bool kv_gate_fits(int dtype, int64_t n, int d, int64_t ldx) {
 }
 
 hipError_t launch_kv_gate(const KvGateArgs& a, int d, hipStream_t s) {
-  return d == 1024 ? launch<Gate<16, 4>>(a, s) : launch<Gate<8, 8>>(a, s);
+  return d == 1024 ? launch<Gate<1024 / (16 * kKvGateWaves), 4>>(a, s) : launch<Gate<512 / (16 * kKvGateWaves), 8>>(a, s);
 }
 
 }  // namespace lmhead
