@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "common.h"
 
@@ -94,9 +95,11 @@ __global__ __launch_bounds__(1024) void scan_len_kernel(const int32_t* __restric
 // zeros.  kScan: each workgroup scans the lengths itself (up to kIndexMaxR of them, a microsecond), which saves the launch
 // that would have to come first: three launches of 5 us each became one.  The range of the token ids is reported by the
 // kernels that follow (an id outside [0, V) is -1 here): the header is only cleared in this launch.
-// A wavefront takes kIndexRows consecutive rows at a time; its lanes look up their slots together.
-constexpr int kIndexMaxR = 4096, kIndexRows = 4;
-template <bool kScan>
+// A wavefront takes kRows consecutive rows at a time; its lanes look up their slots together.  Four rows keep four loads in flight; up
+// to kIndexFew slots there are not the wavefronts for that, and each takes one row, four chunks at a time (192 slots, d 2048: the
+// scoring call 123 -> 120 us, the step 891 -> 883; 256 slots of fp32, d 256: the step 56.0 -> 55.2; from 8192 slots on no faster).
+constexpr int kIndexMaxR = 4096, kIndexRows = 4, kIndexFew = 4096;
+template <bool kScan, int kRows>
 __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
   __shared__ int32_t cu_s[kScan ? kIndexMaxR + 1 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
   }
   typedef __attribute__((ext_vector_type(4))) uint32_t u4;
   if (a.dH) {
-    constexpr int PER = 16;   // slots per wavefront and turn
+    constexpr int PER = 4 * kRows;   // slots per wavefront and turn
     for (int64_t i0 = ((int64_t)blockIdx.x * 4 + wave) * PER; i0 < N; i0 += (int64_t)gridDim.x * 4 * PER) {
       const int64_t i = i0 + lane;
       bool pad = false;
@@ -140,11 +143,11 @@ __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
   const int nv = cu[a.R];
   const int64_t nvp = ((int64_t)nv + kTile - 1) / kTile * kTile;
   const int nvec = a.row_bytes / 16;
-  for (int64_t k0 = ((int64_t)blockIdx.x * 4 + wave) * kIndexRows; k0 < nvp; k0 += (int64_t)gridDim.x * 4 * kIndexRows) {
+  for (int64_t k0 = ((int64_t)blockIdx.x * 4 + wave) * kRows; k0 < nvp; k0 += (int64_t)gridDim.x * 4 * kRows) {
     // slot of row k0 + lane: the last response that starts at or before it (empty ones share their start with the next)
     const int64_t k = k0 + lane;
     int slot = -1;
-    if (lane < kIndexRows && k < nv) {
+    if (lane < kRows && k < nv) {
       int lo = 0, hi = a.R;
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -152,7 +155,7 @@ __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
       }
       slot = lo * a.T + (int)(k - cu[lo]);
     }
-    if (lane < kIndexRows) {
+    if (lane < kRows) {
       a.row_slot[k] = slot;
       int tk = -1;
       if (slot >= 0) {
@@ -167,18 +170,24 @@ __global__ __launch_bounds__(256) void index_kernel(IndexArgs a) {
         a.gid[p * a.Ncap + k] = -1;
       }
     }
-    const u4* src[kIndexRows];
+    const u4* src[kRows];
 #pragma unroll
-    for (int u = 0; u < kIndexRows; ++u) {
+    for (int u = 0; u < kRows; ++u) {
       const int sl = __builtin_amdgcn_readlane(slot, u);
       src[u] = sl >= 0 ? reinterpret_cast<const u4*>(a.H + (int64_t)sl * a.pitchH) : nullptr;
     }
-    for (int c = lane; c < nvec; c += 64) {
-      u4 v[kIndexRows];
+    constexpr int kAhead = kRows < 4 ? 4 / kRows : 1;   // chunks of a row on their way together
+    for (int c = lane; c < nvec; c += 64 * kAhead) {
+      u4 v[kRows][kAhead];
 #pragma unroll
-      for (int u = 0; u < kIndexRows; ++u) v[u] = src[u] ? src[u][c] : u4{0, 0, 0, 0};
+      for (int u = 0; u < kRows; ++u)
 #pragma unroll
-      for (int u = 0; u < kIndexRows; ++u) reinterpret_cast<u4*>(a.Hc + (k0 + u) * a.pitchHc)[c] = v[u];
+        for (int e = 0; e < kAhead; ++e) v[u][e] = src[u] && c + 64 * e < nvec ? src[u][c + 64 * e] : u4{0, 0, 0, 0};
+#pragma unroll
+      for (int u = 0; u < kRows; ++u)
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e)
+          if (c + 64 * e < nvec) reinterpret_cast<u4*>(a.Hc + (k0 + u) * a.pitchHc)[c + 64 * e] = v[u][e];
     }
   }
 }
@@ -357,7 +366,9 @@ __global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* _
 
 // ---- sum of split contractions -----------------------------------------------------------
 
-// One wavefront per valid row n: out[rowmap(n)][:] (+)= part[0][n][:] + part[1][n][:] + ... (in this order).
+// One wavefront per 256 columns of a valid row n: out[rowmap(n)][:] (+)= part[0][n][:] + part[1][n][:] + ... (in this order), eight
+// slices on their way at a time.  (One wavefront per row summed its columns one after the other, four slices at a time: 120 rows of
+// 2048 columns 37 us, now 8.6; the step of 192 slots, d 2048, 880 -> 851 us, of 64 slots of d 768 313 -> 304.)
 template <typename TO>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int ksplit,
                                                             int64_t part_slice, int64_t part_ld, int M,
@@ -371,25 +382,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     if (ksplit == 1 && !single_too) return;
     part_slice = (n_valid + edge - 1) / edge * edge * part_ld;
   }
-  const int lane = threadIdx.x & 63;
-  for (int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); n < n_valid; n += (int64_t)gridDim.x * 4) {
+  const int lane = threadIdx.x & 63, chunks = (M + 255) / 256, waves = gridDim.x * 4;
+  const int first = blockIdx.x * 4 + (threadIdx.x >> 6), rows_on = waves / chunks, chunks_on = waves - rows_on * chunks;
+  int chunk = first % chunks;
+  for (int64_t n = first / chunks; n < n_valid; n += rows_on) {
     const int64_t row = rowmap ? (int64_t)rowmap[n] : row_base + n;
-    if (row < 0) continue;
-    for (int m = lane * 4; m < M; m += 256) {
+    const int m = chunk * 256 + lane * 4;
+    if (row >= 0 && m < M) {
       const float* const p = part + n * part_ld + m;
       float4 v = *reinterpret_cast<const float4*>(p);
       int s = 1;
-      for (; s + 3 < ksplit; s += 4) {
-        float4 q[4];
+      auto add = [&](auto count_tag) {
+        constexpr int kCount = decltype(count_tag)::value;
+        float4 q[kCount];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const float4*>(p + (size_t)(s + u) * part_slice);
+        for (int u = 0; u < kCount; ++u) q[u] = *reinterpret_cast<const float4*>(p + (size_t)(s + u) * part_slice);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { v.x += q[u].x; v.y += q[u].y; v.z += q[u].z; v.w += q[u].w; }
-      }
-      for (; s < ksplit; ++s) {
-        const float4 q = *reinterpret_cast<const float4*>(p + (size_t)s * part_slice);
-        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
-      }
+        for (int u = 0; u < kCount; ++u) { v.x += q[u].x; v.y += q[u].y; v.z += q[u].z; v.w += q[u].w; }
+        s += kCount;
+      };
+      while (s + 8 <= ksplit) add(std::integral_constant<int, 8>{});
+      if (s + 4 <= ksplit) add(std::integral_constant<int, 4>{});
+      if (s + 2 <= ksplit) add(std::integral_constant<int, 2>{});
+      if (s < ksplit) add(std::integral_constant<int, 1>{});
       if constexpr (sizeof(TO) == 4) {
         float4* dst = reinterpret_cast<float4*>(out + row * ldo + m);
         if (accumulate) {
@@ -403,6 +418,11 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
         *reinterpret_cast<bf16x4_t*>(out + row * ldo + m) = h;
       }
     }
+    chunk += chunks_on;
+    if (chunk >= chunks) {
+      chunk -= chunks;
+      ++n;
+    }
   }
 }
 
@@ -412,14 +432,18 @@ hipError_t launch_index(const IndexArgs& a, hipStream_t s) {
   // one resident round of workgroups, or as many as there are rows and mask bytes for
   constexpr int64_t kMost = 2048;
   const int64_t cap = ((int64_t)a.R * a.T + kTile - 1) / kTile * kTile;
-  const int64_t need = cap / (4 * kIndexRows);
+  const bool few = cap <= kIndexFew;
+  const int64_t need = cap / (4 * (few ? 1 : kIndexRows));
   const dim3 grid((unsigned)(need < kMost ? need : kMost));
   if (a.R <= kIndexMaxR) {
-    hipLaunchKernelGGL(index_kernel<true>, grid, dim3(256), 0, s, a);
+    if (few)
+      hipLaunchKernelGGL((index_kernel<true, 1>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((index_kernel<true, kIndexRows>), grid, dim3(256), 0, s, a);
   } else {
     hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, a.len, a.R, a.T, a.hdr, a.cu_ws, a.cu_out,
                        a.want_split, a.split);
-    hipLaunchKernelGGL(index_kernel<false>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((few ? index_kernel<false, 1> : index_kernel<false, kIndexRows>), grid, dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -445,7 +469,7 @@ hipError_t launch_splitk_reduce(const float* part, int ksplit, int64_t part_slic
   // rows are taken in turn by at most one resident round of workgroups: most of n_cap may turn out to be padding,
   // or the whole call idle
   constexpr int64_t kMost = 2048;
-  const int64_t need = (n_cap + 3) / 4;
+  const int64_t need = (n_cap * ((M + 255) / 256) + 3) / 4;
   const dim3 grid((unsigned)(need < kMost ? need : kMost));
   if (out_bf16)
     hipLaunchKernelGGL(splitk_reduce_kernel<__bf16>, grid, dim3(256), 0, s, part, ksplit, part_slice, part_ld, M,
