@@ -81,19 +81,45 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
     return LMHEAD_OK;
   }
   if (kv_few_fits(dt == LMHEAD_F32, L.n, d)) {
-    KvFewArgs fa{x, desc->ldx, U, (int)L.n, d, xt, nullptr, hdr, false, false};
+    const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0, one = kv_mask_with_logits(L.esz, L.n, d, m || xhat);
+    KvFewArgs fa{};
+    fa.x = x;
+    fa.ldx = desc->ldx;
+    fa.M = U;
+    fa.n = (int)L.n;
+    fa.d = d;
+    fa.out_e = xt;
+    fa.hdr = hdr;
+    fa.clear = one ? w.at<int32_t>(L.order) : nullptr;
     {
       TimedLaunch tl(4, s);
       LM_TRY(launch_kv_few(dt, fa, s));
     }
-    fa = {xt, d, W, (int)L.n, d, nullptr, w.at<float>(L.logits), nullptr, false, false};
+    KvFewArgs la{};
+    la.x = xt;
+    la.ldx = d;
+    la.M = W;
+    la.n = (int)L.n;
+    la.d = d;
+    la.out_f = w.at<float>(L.logits);
+    if (one) {
+      la.k = k;
+      la.done = w.at<int32_t>(L.order);
+      la.bias = b;
+      la.xt = xt;
+      la.tau = tau;
+      la.literal = literal;
+      la.m = m;
+      la.xhat = xhat;
+    }
     {
       TimedLaunch tl(5, s);
-      LM_TRY(launch_kv_few(dt, fa, s));
+      LM_TRY(launch_kv_few(dt, la, s));
     }
-    TimedLaunch tl(6, s);
-    LM_TRY(launch_kv_mask(dt, w.at<float>(L.logits), b, xt, L.n, d, tau, (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0,
-                          k, m, xhat, s));
+    if (!one) {
+      TimedLaunch tl(6, s);
+      LM_TRY(launch_kv_mask(dt, w.at<float>(L.logits), b, xt, L.n, d, tau, literal, k, m, xhat, s));
+    }
     return LMHEAD_OK;
   }
   // rows too far apart for a tile's window: a dense copy, where the logits will be

@@ -169,6 +169,16 @@ struct KvFewArgs {
   float* out_f;
   WsHeader* hdr;
   bool rows, accumulate;
+  int32_t* clear;      // unless null: one counter per 16 tokens, set to 0
+  // With k: out_f holds gate logits, and the last workgroup of 16 tokens makes their mask (launch_kv_mask, d up to kKvFewMask).
+  int32_t* k;
+  int32_t* done;       // the counters, cleared by a launch before
+  const float* bias;
+  const void* xt;
+  float tau;
+  bool literal;
+  float* m;
+  void* xhat;
 };
 hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s);
 

@@ -353,4 +353,16 @@ inline bool kv_few_fits(bool f32, int64_t n, int d) {
   return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= per_unit * (int64_t)kComputeUnits;
 }
 
+// Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  The workgroup that is
+// last has 16 tokens to itself, behind stores that have gone through to memory: 5.5 us at d = 1024 where the launch and its gap are 5 to
+// 7, more with soft outputs to write.  Call, us, launch / same launch:
+//   decode  16 x 1024 23.0/20.7  128 x 1024 22.3/21.3  200 x 1024 21.5/22.2  160 x 768 26.1/22.6  256 x 512 25.5/18.8  32 x 320 20.5/17.8
+//   gate  2000 x 128 12.8/10.2  1000 x 256 15.7/13.1  300 x 1024 fp32 37.5/40.3
+//   training pair  300 x 128 fp32 47.3/45.0  4096 x 64 43.1/40.3  1000 x 256 51.0/48.4  600 x 256 fp32 49.2/49.8  256 x 512 49.5/49.9
+//                  128 x 1024 55.6/57.7  700 x 512 58.4/61.0
+constexpr int kKvFewMask = 1024;
+inline bool kv_mask_with_logits(int esz, int64_t n, int d, bool soft) {
+  return soft ? d * esz <= 512 : d < kKvFewMask || (d == kKvFewMask && n <= 128);
+}
+
 }  // namespace lmhead
