@@ -268,6 +268,7 @@ struct GemmTArgs {
   const void* B2;      // is ldA) and out, its slices behind the first one's
   int64_t ldB2;
   float* out2;
+  int32_t* done;       // gemm_t_tile's kSum: one counter per output tile, both products', cleared before
 };
 
 // out[row(n)][m] (+)= sum_s part[s][n][m] for n < n_valid, m < M, slices summed in order.  With a row map:

@@ -299,7 +299,8 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
     // g_l, and the direct part g_xhat * m of dL/dx~ (into the buffer that the next product adds to)
     TimedLaunch tl(8, s);
     LM_TRY(launch_kv_mask_bwd(dt, static_cast<const float*>(at(L.logits)), b, xt, g_xhat, g_m, g_m_const, L.n, d,
-                              literal, at(L.gl), at(L.gxt), static_cast<float*>(at(L.dbpart)), L.nblk, s));
+                              literal, at(L.gl), at(L.gxt), static_cast<float*>(at(L.dbpart)), L.nblk,
+                              static_cast<int32_t*>(at(L.done)), L.tail ? (int)kv_tail_counters(d) : 0, s));
   }
 
   // g_x~ += g_l W^T
@@ -322,7 +323,8 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ga.B = at(L.gxt);
   ga.out_e = dx;
   ga.accumulate = false;
-  {
+  const bool dx_apart = !L.tail || kv_tail_dx_apart(dt == LMHEAD_F32, d, few);
+  if (dx_apart) {
     TimedLaunch tl(10, s);
     if (few)
       LM_TRY(launch_kv_few(dt, {at(L.gxt), d, U, (int)L.n, d, dx, nullptr, nullptr, true, false}, s));
@@ -361,9 +363,16 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   {
     TimedLaunch tl(11, s);
     if (dense) LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, at(L.logits), s));
+    const KvSums sums{static_cast<const float*>(at(L.dbpart)), L.nblk, ta.part, L.ksplit, d, db, dW, dU, accum};
+    if (L.tail) {
+      if (dx_apart) ga.Nn = 0;
+      ta.done = static_cast<int32_t*>(at(L.done));
+      LM_TRY(launch_kv_tail(dt, ga, ta, sums, s));
+      return LMHEAD_OK;
+    }
     LM_TRY(launch_gemm_t(dt, ta, s, 2));
+    LM_TRY(launch_kv_sums(sums, s));
   }
-  LM_TRY(launch_kv_sums({static_cast<const float*>(at(L.dbpart)), L.nblk, ta.part, L.ksplit, d, db, dW, dU, accum}, s));
   return LMHEAD_OK;
 }
 

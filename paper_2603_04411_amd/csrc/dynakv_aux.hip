@@ -49,8 +49,11 @@ template <typename T, int NG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NG > 0 && NG <= 4 ? 4 : 2)))
 void kv_mask_bwd_kernel(const float* __restrict__ logits, const float* __restrict__ bias, const T* __restrict__ xt,
                         const T* __restrict__ gxh, const float* __restrict__ gm, float gmc, int64_t n, int d,
-                        int literal, T* __restrict__ gl, T* __restrict__ a_out, float* __restrict__ dbpart) {
+                        int literal, T* __restrict__ gl, T* __restrict__ a_out, float* __restrict__ dbpart, int32_t* __restrict__ clear,
+                        int nclear) {
   extern __shared__ float colsum[];   // [4][d], position order
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < nclear; i += 256) clear[i] = 0;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   float* const acc = colsum + wave * d;
@@ -284,7 +287,7 @@ void kv_mask_bwd_kernel(const float* __restrict__ logits, const float* __restric
 // The column sums are ready long before the gradients, but a launch of their own costs its 4 us of dispatch wherever it is put
 // (4096 x 1024 training pair 149.5 -> 145.7 us; 300 x 128 in fp32 48.5 -> 47.4 with the one-launch retain rate below, which
 // no longer waits for the GPU but for the host).
-constexpr int kSumWaves = 16, kSumBatch = 8, kSumByColumns = 128;
+constexpr int kSumByColumns = 128;
 
 __device__ inline void sum_slices(const float* __restrict__ part, int rows, int64_t row_pitch, float* __restrict__ out,
                                   int64_t j, bool accumulate) {
@@ -327,22 +330,7 @@ __global__ __launch_bounds__(64 * kSumWaves) void kv_sum_kernel(KvSums a, int by
   }
   const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
   const int64_t j = j0 + cl;
-  float t[kSumBatch] = {};
-  const float* const p = part + j;
-  int64_t r = rl;
-  for (; r + (kSumBatch - 1) * kSumWaves < rows; r += kSumWaves * kSumBatch) {
-    float v[kSumBatch];
-#pragma unroll
-    for (int u = 0; u < kSumBatch; ++u) v[u] = p[(r + u * kSumWaves) * pitch];
-#pragma unroll
-    for (int u = 0; u < kSumBatch; ++u) t[u] += v[u];
-  }
-  for (; r < rows; r += kSumWaves) t[0] += p[r * pitch];
-#pragma unroll
-  for (int o = kSumBatch / 2; o > 0; o >>= 1)
-#pragma unroll
-    for (int u = 0; u < o; ++u) t[u] += t[u + o];
-  sm[rl][cl] = t[0];
+  column_sums<1>(part + j, pitch, rows, rl, &sm[rl][cl], 0);
   __syncthreads();
   if (rl == 0) {
     float v = 0.f;
@@ -911,7 +899,7 @@ hipError_t launch_kv_mask(int dtype, const float* logits, const float* b, const 
 template <typename T>
 static hipError_t launch_mask_bwd_t(const float* logits, const float* b, const void* xt, const void* g_xhat,
                                     const float* g_m, float g_m_const, int64_t n, int d, bool literal, void* gl,
-                                    void* a_out, float* dbpart, int nblk, hipStream_t s) {
+                                    void* a_out, float* dbpart, int nblk, int32_t* clear, int nclear, hipStream_t s) {
   const dim3 grid((unsigned)nblk);
   const size_t lds = (size_t)4 * d * sizeof(float);
   const T* x = static_cast<const T*>(xt);
@@ -925,7 +913,7 @@ static hipError_t launch_mask_bwd_t(const float* logits, const float* b, const v
     hipError_t e = allow_lds<kv_mask_bwd_kernel<T, NG>>((int)lds);                                               \
     if (e != hipSuccess) return e;                                                                               \
     hipLaunchKernelGGL((kv_mask_bwd_kernel<T, NG>), grid, dim3(256), lds, s, logits, b, x, gx, g_m, g_m_const, n, \
-                       d, lit, g1, a1, dbpart);                                                                  \
+                       d, lit, g1, a1, dbpart, clear, nclear);                                                   \
   } while (0)
   switch (ng) {
     case 1: KV_MASK_BWD(1); break;
@@ -942,10 +930,10 @@ static hipError_t launch_mask_bwd_t(const float* logits, const float* b, const v
 
 hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, const void* xt, const void* g_xhat,
                               const float* g_m, float g_m_const, int64_t n, int d, bool literal, void* gl,
-                              void* a_out, float* dbpart, int nblk, hipStream_t s) {
+                              void* a_out, float* dbpart, int nblk, int32_t* clear, int nclear, hipStream_t s) {
   if (dtype == LMHEAD_BF16)
-    return launch_mask_bwd_t<__bf16>(logits, b, xt, g_xhat, g_m, g_m_const, n, d, literal, gl, a_out, dbpart, nblk, s);
-  return launch_mask_bwd_t<float>(logits, b, xt, g_xhat, g_m, g_m_const, n, d, literal, gl, a_out, dbpart, nblk, s);
+    return launch_mask_bwd_t<__bf16>(logits, b, xt, g_xhat, g_m, g_m_const, n, d, literal, gl, a_out, dbpart, nblk, clear, nclear, s);
+  return launch_mask_bwd_t<float>(logits, b, xt, g_xhat, g_m, g_m_const, n, d, literal, gl, a_out, dbpart, nblk, clear, nclear, s);
 }
 
 hipError_t launch_kv_sums(const KvSums& a, hipStream_t s) {

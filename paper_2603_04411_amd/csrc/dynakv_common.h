@@ -58,8 +58,9 @@ struct KvBwdLayout {
   int esz;
   int64_t n, d, ncap, dp;
   int edge, ksplit;  // tile edge of dW / dU and slices of their contraction over the tokens
+  bool tail;         // they, dx and db in one launch
   int nblk;          // workgroups of the mask backward kernel = rows of the db partial sums
-  size_t hdr, logits, gl, gxt, part, dbpart, total;
+  size_t hdr, logits, gl, gxt, part, dbpart, done, total;
 };
 
 // Workgroups of the mask backward kernel: four 256-thread workgroups fit a compute unit (128 VGPRs),
@@ -99,6 +100,12 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
       if (last || ksteps / ks >= (edge == 256 ? 32 : 16)) break;
     }
   }
+  const int part_slices = L.ksplit;
+  if (const KvTail t = kv_tail(L.esz == 4, L.n, L.d, L.edge, L.ksplit); t.edge) {
+    L.tail = true;
+    L.edge = t.edge;
+    L.ksplit = t.slices;
+  }
   {
     const int64_t blocks = (L.n + 3) / 4;
     L.nblk = (int)(blocks < kKvBwdMaxBlocks ? blocks : kKvBwdMaxBlocks);
@@ -113,8 +120,9 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.logits = take((size_t)L.ncap * L.d * 4);
   L.gl = take((size_t)L.ncap * L.d * L.esz);
   L.gxt = take((size_t)L.ncap * L.d * L.esz);
-  L.part = take((size_t)2 * L.ksplit * L.d * L.d * 4);   // the slices of both gradients
+  L.part = take((size_t)2 * part_slices * L.d * L.d * 4);   // the slices of both gradients
   L.dbpart = take((size_t)L.nblk * L.d * 4);
+  L.done = take((size_t)kv_tail_counters(L.d) * 4);
   L.total = off;
   return L;
 }
@@ -278,10 +286,10 @@ hipError_t launch_kv_retain(const int32_t* k, const float* m, int64_t n, int d, 
 //   q = g_xhat * xt + g_m + g_m_const;  r = inclusive prefix sums of q;  g_l = p * (r - sum p r);
 //   a = g_xhat * m.
 // g_l goes to gl (gate column order) and a to a_out, both [n x d] in the storage type; dbpart
-// receives one row of column sums of g_l per workgroup (nblk rows, launch grid = nblk).
+// receives one row of column sums of g_l per workgroup (nblk rows, launch grid = nblk).  clear[0 .. nclear) is set to 0.
 hipError_t launch_kv_mask_bwd(int dtype, const float* logits, const float* b, const void* xt, const void* g_xhat,
                               const float* g_m, float g_m_const, int64_t n, int d, bool literal, void* gl,
-                              void* a_out, float* dbpart, int nblk, hipStream_t s);
+                              void* a_out, float* dbpart, int nblk, int32_t* clear, int nclear, hipStream_t s);
 
 // db (+)= the column sums of dbpart [db_rows x d]; with slices > 1 also dW (+)= the sum of the first `slices` d x d matrices of
 // part and dU (+)= that of the next ones.  Fixed order.
@@ -293,6 +301,49 @@ struct KvSums {
   float *db, *dW, *dU;
   bool accumulate;
 };
+// The sum of a column's rows, by kSumWaves chains of every kSumWaves-th row, kSumBatch loads at a time.  The caller makes Q of the
+// chains, first and every kSumWaves / Q after it, and stores them `to_step` floats apart.
+constexpr int kSumWaves = 16, kSumBatch = 8;
+template <int Q>
+__device__ inline void column_sums(const float* __restrict__ p, int64_t pitch, int64_t rows, int first, float* to, int to_step) {
+  constexpr int kStep = kSumWaves / Q;
+  float t[Q][kSumBatch] = {};
+  int64_t r0 = first;
+  if constexpr (Q > 1)
+    for (; r0 + (Q - 1) * kStep + (kSumBatch - 1) * kSumWaves < rows; r0 += kSumWaves * kSumBatch) {
+      float v[Q][kSumBatch];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int u = 0; u < kSumBatch; ++u) v[q][u] = p[(r0 + q * kStep + u * kSumWaves) * pitch];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int u = 0; u < kSumBatch; ++u) t[q][u] += v[q][u];
+    }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    int64_t r = r0 + q * kStep;
+    for (; r + (kSumBatch - 1) * kSumWaves < rows; r += kSumWaves * kSumBatch) {
+      float v[kSumBatch];
+#pragma unroll
+      for (int u = 0; u < kSumBatch; ++u) v[u] = p[(r + u * kSumWaves) * pitch];
+#pragma unroll
+      for (int u = 0; u < kSumBatch; ++u) t[q][u] += v[u];
+    }
+    for (; r < rows; r += kSumWaves) t[q][0] += p[r * pitch];
+#pragma unroll
+    for (int o = kSumBatch / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int u = 0; u < o; ++u) t[q][u] += t[q][u + o];
+    to[q * to_step] = t[q][0];
+  }
+}
+
 hipError_t launch_kv_sums(const KvSums& a, hipStream_t s);
+
+// What follows g_x~ in a backward call, in one launch (kv_tail): the dense product `dx` (mode 3; Nn 0: without it), both gradients with
+// the sum of their slices (role 2; g.done: their counters, cleared), and the column sums of q (its slices are not looked at).
+hipError_t launch_kv_tail(int dtype, const KvGemmArgs& dx, const GemmTArgs& g, const KvSums& q, hipStream_t s);
 
 }  // namespace lmhead

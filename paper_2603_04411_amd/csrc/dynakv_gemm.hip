@@ -16,7 +16,7 @@
 // K-steps as its first token needs: `order` lists tokens by descending step count, so that is
 // the tile's maximum and tiles of short tokens are short.
 #include "dynakv_mask.h"
-#include "gemm_core.h"
+#include "gemm_t.h"
 
 #include <type_traits>
 
@@ -230,6 +230,59 @@ __global__ __launch_bounds__(256, wg_per_cu(Edge, Stages)) void kv_gemm_kernel(K
   for (int wg = blockIdx.x; wg < a.walk_len; wg += gridDim.x) kv_tile<E, Edge, Mode, Stages>(a, wg, smem);
 }
 
+// The end of a backward call: the workgroup's number says whether it takes 64 columns of db (a long chain of little work, so first; as
+// many as keep the tiles on their XCDs), a tile of dW or of dU (the longer ones) or one of dx.  Bound by the tiles' K-steps where they
+// fill the chip, by latency below.  4096 x 1024 in bf16: dx 13.7 us, both gradients 23.6, sums 9.9 in launches of their own; the whole
+// call and its gate 145 us, with this 134.
+template <typename E, int Edge>
+__global__ __launch_bounds__(256, wg_per_cu(Edge, 0)) void kv_tail_kernel(KvGemmArgs dx, GemmTArgs g, KvSums q, int db_wgs, int grad_wgs) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  int wg = blockIdx.x;
+  if (wg < db_wgs) {
+    if (wg >= q.d / 64) return;
+    // four chains to a wavefront, added up in the order of kv_sum_kernel
+    constexpr int kWaves = 4;
+    float* const sm = reinterpret_cast<float*>(smem);
+    const int cl = threadIdx.x & 63, rl = threadIdx.x >> 6, j = wg * 64 + cl;
+    column_sums<kSumWaves / kWaves>(q.dbpart + j, q.d, q.db_rows, rl, sm + rl * 64 + cl, kWaves * 64);
+    __syncthreads();
+    if (rl == 0) {
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < kSumWaves; ++w) v += sm[w * 64 + cl];
+      q.db[j] = q.accumulate ? q.db[j] + v : v;
+    }
+    return;
+  }
+  wg -= db_wgs;
+  if (wg < 2 * grad_wgs) {
+    gemm_t_tile<E, 2, Edge, /*kSum=*/true>(g, wg < grad_wgs ? wg : wg - grad_wgs, wg >= grad_wgs, smem);
+    return;
+  }
+  kv_tile<E, Edge, 3, 0>(dx, wg - 2 * grad_wgs, smem);
+}
+
+template <typename E, int Edge>
+hipError_t launch_tail(const KvGemmArgs& dx, const GemmTArgs& g, const KvSums& q, hipStream_t s) {
+  using G = KvTile<E, Edge, 3, 0>;
+  static_assert(G::LDS_BYTES == Tile<E, false, Edge>::LDS_BYTES, "the two kinds of tiles share a workgroup's LDS");
+  const int64_t mtiles = (dx.M + Edge - 1) / Edge, ntiles = (dx.Nn + Edge - 1) / Edge, side = (g.M + Edge - 1) / Edge;
+  if (dx.out_f || !dx.out_e || dx.accumulate || dx.mode != 3 || !g.A2 || !g.done || g.ksplit < 1 || (g.ksplit > 1 && !g.part) ||
+      (g.ksplit == 1 && g.part) || g.n_limit != g.M)
+    return hipErrorInvalidValue;
+  for (int64_t p : {g.ldA, g.ldB, g.ldB2})   // a K-step has to fit a window
+    if (p > longest_pitch(1)) return hipErrorInvalidValue;
+  KvGemmArgs b = dx;
+  b.walk_len = (int)xcd_grid_size((int)mtiles, ntiles, kKvMapBy);
+  const unsigned grad = xcd_grid_size((int)side, side * g.ksplit, kMapBy);
+  hipError_t e = allow_lds<kv_tail_kernel<E, Edge>>(G::LDS_BYTES);
+  if (e != hipSuccess) return e;
+  const unsigned db = (unsigned)(q.d / 64 + kNumXcd - 1) / kNumXcd * kNumXcd;
+  hipLaunchKernelGGL((kv_tail_kernel<E, Edge>), dim3(db + 2 * grad + (unsigned)b.walk_len), dim3(G::NT), G::LDS_BYTES, s, b, g, q, (int)db,
+                     (int)grad);
+  return hipGetLastError();
+}
+
 template <typename E, int Edge, int Mode, int Stages = 0>
 hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
   using G = KvTile<E, Edge, Mode, Stages>;
@@ -421,6 +474,11 @@ hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
   else
     typed(f32_tag{});
   return hipGetLastError();
+}
+
+hipError_t launch_kv_tail(int dtype, const KvGemmArgs& dx, const GemmTArgs& g, const KvSums& q, hipStream_t s) {
+  if (dtype == LMHEAD_BF16) return g.edge == 64 ? launch_tail<bf16_tag, 64>(dx, g, q, s) : launch_tail<bf16_tag, 128>(dx, g, q, s);
+  return g.edge == 64 ? launch_tail<f32_tag, 64>(dx, g, q, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s) {

@@ -353,6 +353,46 @@ inline bool kv_few_fits(bool f32, int64_t n, int d) {
   return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= per_unit * (int64_t)kComputeUnits;
 }
 
+// What follows g_x~ in a backward call (dx, both parameter gradients, the sums of their slices, db) as one launch: none of them waits
+// for another, each leaves compute units idle by itself, and a launch costs its 4 us wherever it is put.  All on tiles of one edge.  The
+// last workgroup of a gradient tile reads all its slices alone, so there are to be few of them, and of equal length with the rest.
+// Training pair, us, launches of their own / one (bf16; edge, slices: of launches of their own / of one):
+//     n x d        us             edge, slices           n x d        us             edge, slices
+//     64 x 64      45.6 / 39.3    64, 2 / 64, 1          1024 x 1024  76.1 / 68.4    64, 1 / 64, 1
+//     700 x 256    49.3 / 42.5    64, 6 / 64, 1          4096 x 1024  145 / 134      128, 4 / 128, 2
+//     2000 x 512   65.8 / 59.6    64, 4 / 64, 2          1500 x 1536  153 / 130      64, 1 / 128, 1
+//     5000 x 256   62.6 / 58.3    64, 16 / 64, 5         8192 x 1024  218 / 203      128, 4 / 128, 2
+//     32768 x 256  141 / 136      64, 16 / 64, 16        2048 x 2048  201 / 199      128, 1 / 128, 1
+// Other choices: 4096 x 1024 with 1, 3, 4, 8 slices 140, 137, 145, 180; 1024 x 1024 on edge 128 79, 2048 x 1024 107 instead of 100;
+// 1500 x 1536 on edge 64 140.  Beyond the work and the slices that it stops at: 3000 x 2048 (71) 256 / 259, 16384 x 1024 397 / 391,
+// 65536 x 64 (64 slices) 122 / 124, 16700 x 64 63 / 64.
+// fp32 keeps the slices that its sums had (longer ones raise the error of dU from 2.28e-6 to 2.49e-6 at 4096 x 1024), and so edge
+// 64 (2048 x 1024 with 4 slices on edge 128: 305 / 370); 2000 x 256, 16 slices, 66.5 / 72.9.
+struct KvTail {
+  int edge = 0, slices = 0;   // edge 0: launches of their own
+};
+inline KvTail kv_tail(bool f32, int64_t n, int d, int own_edge, int own_slices) {
+  const int kMostSlices = f32 ? 8 : 16, kMostWork = 48;
+  if (own_edge > (f32 ? 64 : 128)) return {};
+  const int esz = f32 ? 4 : 2;
+  const int64_t ksteps = (n * esz + 127) / 128, dx_steps = ((int64_t)d * esz + 127) / 128;
+  // K-steps of a place for a workgroup (256 / edge of them on a compute unit), were all equally loaded
+  auto work = [&](int edge) {
+    return (2 * tiles_of(d, d, edge) * ksteps + tiles_of(d, n, edge) * dx_steps) / (kComputeUnits * (256 / edge));
+  };
+  KvTail t;
+  t.edge = !f32 && work(128) >= 16 ? 128 : 64;
+  const int64_t w = work(t.edge), steps = w > 12 ? w * 4 / 3 : 16;   // of a slice
+  t.slices = own_slices;   // never more: the scratch memory is sized for these, and grows with n
+  if (!f32 && (ksteps + steps - 1) / steps < own_slices) t.slices = (int)((ksteps + steps - 1) / steps);
+  return w <= kMostWork && t.slices <= kMostSlices ? t : KvTail{};
+}
+// Whether dx of few tokens stays the product of few tokens before it: sixteen wavefronts share its contraction, one has it here.
+// 16 tokens, d 1024 / 2048 / 4096, the pair with dx apart / within, us: 52.6 / 49.2, 85.2 / 84.3, 188 / 190; 1 x 8192: 442 / 491.
+// In fp32 they also keep its sums short (300 x 128: error 3.98e-7, within 4.58e-7).
+inline bool kv_tail_dx_apart(bool f32, int d, bool few) { return few && (f32 || d > 2048); }
+inline int64_t kv_tail_counters(int64_t d) { return 2 * ((d + 63) / 64) * ((d + 63) / 64); }
+
 // Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  The workgroup that is
 // last has 16 tokens to itself, behind stores that have gone through to memory: 5.5 us at d = 1024 where the launch and its gap are 5 to
 // 7, more with soft outputs to write.  Call, us, launch / same launch:
