@@ -44,7 +44,13 @@ def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
     byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz)}
     products = {**dict.fromkeys(BWD_KINDS, 1), 11: 2}
     names = dict(BWD_KINDS)
-    if kern[6][1] == 0:              # large streams: the forward's gate is one kernel, gate logits only the recompute
+    if kern[10][1] == 0:             # shorter streams: dx and the gradients in one launch
+        del names[10]
+        names[11], products[11] = "kv_tail_kernel (dx, dW and dU, the sums of their slices, db)", 3
+    if kern[6][1] == 0 and kern[5][1] > kern[4][1]:   # few tokens: the mask in the launch of the logits
+        del names[6]
+        names[5] = "kv_few_kernel<gate logits> (forward, with the mask, + recompute)"
+    elif kern[6][1] == 0:            # large streams: the forward's gate is one kernel, gate logits only the recompute
         del names[6]
         names[4], products[4] = FUSED_GATE, 2
         names[5] = "kv_gemm_kernel<gate logits> (recompute)"
@@ -279,12 +285,12 @@ def main(argv=None) -> int:
     work = {4: 2.0 * n * d * d, 5: 2.0 * n * d * d, 7: 2.0 * d * float(k_host.sum())}
     step_flops = work[4] + work[5] + work[7]
     mask_bytes = n * d * 4.0 + n * 4.0 + d * 4.0
-    fused = kern[6][1] == 0          # large streams: one kernel for the whole gate
+    fused = kern[6][1] == 0 and kern[5][1] == 0   # large streams: one kernel for the whole gate
     if fused:
         work[4] += work[5]
     kinds = []
     for kind, name in KINDS.items():
-        if fused and kind in (5, 6):
+        if fused and kind in (5, 6) or kern[6][1] == 0 and kind == 6:   # few tokens: the mask in the launch of the logits
             continue
         if fused and kind == 4:
             name = FUSED_GATE
