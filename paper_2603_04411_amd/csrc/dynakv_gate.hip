@@ -4,9 +4,8 @@
 //
 // A workgroup owns TOK = 16 TJ tokens and ALL d output columns of both products, so that a token's softmax
 // never crosses workgroups: eight wavefronts, each d / 8 columns x TOK tokens of 16x16 MFMA blocks (128 accumulator
-// registers; two on a SIMD, which cover each other's waits: four of twice the columns are up to 7 % slower at d = 512, as
-// fast at 262144 x 1024).  The token rows (TOK x d bf16, 128 KB) sit in LDS for the whole product and are read by all
-// wavefronts; the parameter matrices stream from L2 straight into registers, each value into the one wavefront that
+// registers; two on a SIMD, which cover each other's waits).  The token rows (TOK x d bf16, 128 KB) sit in LDS for the whole
+// product and are read by all wavefronts; the parameter matrices stream from L2 straight into registers, each value into the one wavefront that
 // needs it, in fragments of 1 KB that kv_prepare_kernel has laid out in the order they are consumed (a full-line
 // load per instruction, no LDS, no barrier in the main loop).  A fragment register is reloaded right behind
 // its last use, two K sub-steps ahead (about 2000 cycles).
@@ -14,9 +13,10 @@
 // What bounds it: the parameter stream.  Every 64 tokens read 2 d^2 x 2 bytes (4 MB at d = 1024) through a compute unit's
 // 64 bytes per clock, which just matches the matrix cores' pace; 256 x 256 tiles need half of that but pay a pipeline
 // fill and an epilogue per 16 K-steps, one write and one read of the fp32 logits and one read of x~ (3.2 GB at
-// 262144 x 1024).  Measured there: 1334 us with the separate kernels, 1036 with four wavefronts that all read the same parameters at
-// a time, now 976 (d = 512: 313, now 303; 12000 x 1024: 69, now 64; with both contractions turned 940, 294 and 63).  Of a round's
-// 60 us (sixteen rounds) the matrix pipe is busy for 34, the softmax takes 8.
+// 262144 x 1024).  Measured there: 1334 us with the separate kernels, 1038 with four wavefronts, 981 now (d = 512: 309, now 296;
+// 16384 x 1024: 78, now 75).  Of a round's 60 us (sixteen rounds) the matrix pipe is busy for 34, the softmax takes 8.  Beginning the
+// contractions at another sub-step in each workgroup, so that they do not read the same parameters at a time: the second
+// alone nothing (979; d = 512: 300), both up to 4 %, but a token's sums would depend on its place in the call.
 //
 // Column order: accumulator element v of block i in lane group q of wavefront w is POSITION (d/8) w + (d/32) q + 4 i + v of
 // the mask, i.e. a lane holds d / 32 consecutive positions of one token per token block, and the cumulative sum is a
@@ -97,10 +97,6 @@ __global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a
 
   typedef u32x4_t Frags[NI];
   const int frag_vo = (threadIdx.x & 63) * 16;
-  // Each workgroup of an XCD begins the second contraction at another sub-step: one that all of them read at a time is 16 KB of the
-  // parameters, which meet on a few of the L2's channels.  (The first one keeps the order of the separate kernels, so that
-  // x~ is the same to the bit.)
-  const int turn = blockIdx.x / kNumXcd * 5;
   auto load_frag = [&](const __amdgpu_buffer_rsrc_t& r, int s, int i) {
     return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, frag_vo, woff + s * G::STEP + i * 1024, 0));
   };
@@ -108,10 +104,10 @@ __global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a
   Frags wb[2];
   u32x4_t fb[2][TJ];
   // One sub-step: NI x TJ MFMAs (the first of a product starts from 0: no pass that clears the accumulators, and
-  // none of the wait states that a just-written addend needs, see GemmTile::settle); the token fragments of the next sub-step, `s`, are read behind the first of them, and
+  // none of the wait states that a just-written addend needs, see GemmTile::settle); the token fragments of the next sub-step are read behind the first of them, and
   // each parameter fragment is replaced, one MFMA after its last use, by that of sub-step `ns` of stream `nr`.
   auto substep = [&](auto first_tag, const char* xrow, int s, int buf, bool more, bool refill, const __amdgpu_buffer_rsrc_t& nr, int ns) {
-    const char* const xn = xrow + s * 64;   // of the next sub-step
+    const char* const xn = xrow + (s + 1) * 64;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
 #pragma unroll
@@ -132,30 +128,26 @@ __global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a
     if (refill) wb[buf][NI - 1] = load_frag(nr, ns, NI - 1);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // acc = X W for one stream, from sub-step `first` round to it; with `chain`, the first two sub-steps of the next stream are on their
-  // way at the end
-  auto product = [&](const __amdgpu_buffer_rsrc_t& r, int first, bool chain, const __amdgpu_buffer_rsrc_t& next, int first_next,
-                     auto&& per_substep) {
+  // acc = X W for one stream; with `chain`, the first two sub-steps of the next stream are on their way at the end
+  auto product = [&](const __amdgpu_buffer_rsrc_t& r, bool chain, const __amdgpu_buffer_rsrc_t& next, auto&& per_substep) {
     const int l = lane_id();
     const char* const xrow = smem + (l & 15) * G::PITCH + (l >> 4) * 16;
-    auto at = [&](int s) { return (s + first) & (S - 1); };
-    auto at_next = [&](int s) { return (s + first_next) & (S - 1); };
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) fb[0][j] = *reinterpret_cast<const u32x4_t*>(xrow + at(0) * 64 + j * 16 * G::PITCH);
+    for (int j = 0; j < TJ; ++j) fb[0][j] = *reinterpret_cast<const u32x4_t*>(xrow + j * 16 * G::PITCH);
     __builtin_amdgcn_sched_barrier(0);
-    substep(std::true_type{}, xrow, at(1), 0, true, true, r, at(2));
+    substep(std::true_type{}, xrow, 0, 0, true, true, r, 2);
     per_substep(0);
-    substep(std::false_type{}, xrow, at(2), 1, true, true, r, at(3));
+    substep(std::false_type{}, xrow, 1, 1, true, true, r, 3);
     per_substep(1);
     for (int s = 2; s < S - 2; s += 2) {
-      substep(std::false_type{}, xrow, at(s + 1), 0, true, true, r, at(s + 2));
+      substep(std::false_type{}, xrow, s, 0, true, true, r, s + 2);
       per_substep(s);
-      substep(std::false_type{}, xrow, at(s + 2), 1, true, true, r, at(s + 3));
+      substep(std::false_type{}, xrow, s + 1, 1, true, true, r, s + 3);
       per_substep(s + 1);
     }
-    substep(std::false_type{}, xrow, at(S - 1), 0, true, chain, next, at_next(0));
+    substep(std::false_type{}, xrow, S - 2, 0, true, chain, next, 0);
     per_substep(S - 2);
-    substep(std::false_type{}, xrow, 0, 1, false, chain, next, at_next(1));
+    substep(std::false_type{}, xrow, S - 1, 1, false, chain, next, 1);
     per_substep(S - 1);
     asm volatile("s_nop 15\n\ts_nop 15");   // results are read by ordinary instructions next
   };
@@ -176,7 +168,7 @@ __global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a
     __syncthreads();
 
     // ---- x~ = x U
-    product(rU, 0, true, rW, turn, [](int) {});
+    product(rU, true, rW, [](int) {});
     lds_barrier();   // every wavefront has read its last token fragments
     // rounded to bf16 into the place of x; blocks i, i + 1 are 8 consecutive columns
     {
@@ -198,7 +190,7 @@ __global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a
     // ---- x~ W, with x~ streamed out to memory meanwhile
     const int l2 = lane_id();
     const uint32_t xt0 = (uint32_t)t0 * G::ROW + l2 * 16;
-    product(rW, turn, false, rU, 0, [&](int s) {
+    product(rW, false, rU, [&](int s) {
       constexpr int kEvery = S > G::PIECES ? S / G::PIECES : 1;   // sub-steps a piece
       if (s % kEvery != 0) return;
 #pragma unroll
