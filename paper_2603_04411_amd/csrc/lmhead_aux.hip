@@ -304,7 +304,7 @@ __global__ __launch_bounds__(64 * kFinWaves) void finalize_kernel(const float* _
         sc[u] = in ? p[plane + (size_t)c * Ncap] : 0.f;
         tc[u] = in && ent ? p[2 * plane + (size_t)c * Ncap] : 0.f;
       }
-      // a tile whose logits are all -inf holds nothing: its sum of exp * z is 0 * -inf
+      // a tile without a maximum holds nothing: its logits are all -inf, or NaN
 #pragma unroll
       for (int u = 0; u < kFinBatch; ++u) {
         const bool none = mc[u] == -__builtin_huge_valf();

@@ -11,7 +11,7 @@ namespace lmhead {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kNegInf = -__builtin_huge_valf();
+constexpr float kNegInf = -__builtin_huge_valf(), kLowest = -__FLT_MAX__;
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -76,6 +76,7 @@ struct TileStats {
   // Inside the lane, 16 values of one token column at a time (one 32x32 block or four 16x16 blocks); the scheduling
   // barrier after each group keeps the accumulator reads of later groups from being hoisted, so only 16 values are live
   // in VGPRs at a time.  vlim: rows with m_const >= vlim do not count (whole: there are none).  want_t: the third sum is needed.
+  // A logit of -inf (a masked row of W) does not count either, in any of the three: its exponential is 0.
   __device__ inline void add(typename G::Acc& acc, float zscale, int vlim, bool whole, bool want_t) {
     // logit = accumulator * zscale (zscale = 1 unless the operands are scaled 8-bit copies); the factor
     // is folded into the constants of the group instead of being applied per element
@@ -87,14 +88,11 @@ struct TileStats {
       constexpr bool kFull = decltype(full_tag)::value;
       constexpr bool kEnt = decltype(ent_tag)::value;   // the third accumulator (sum exp * z) feeds the entropy only
       float z[GV];
-      bool ok[GV];
 #pragma unroll
       for (int b = 0; b < BPC; ++b)
 #pragma unroll
-        for (int v = 0; v < G::VB; ++v) {
-          ok[b * G::VB + v] = kFull || G::m_const(ic * BPC + b, v) < vlim;
-          z[b * G::VB + v] = ok[b * G::VB + v] ? acc[ic * BPC + b][j][v] : kNegInf;
-        }
+        for (int v = 0; v < G::VB; ++v)
+          z[b * G::VB + v] = kFull || G::m_const(ic * BPC + b, v) < vlim ? acc[ic * BPC + b][j][v] : kNegInf;
       float tmax = fmaxf(z[0], z[1]);
 #pragma unroll
       for (int v = 2; v < GV; v += 2) tmax = fmaxf(tmax, fmaxf(z[v], z[v + 1]));
@@ -107,7 +105,7 @@ struct TileStats {
       for (int v = 0; v < GV; ++v) {
         const float e = fast_exp2(fmaf(z[v], kz, bias));   // exp2(-inf) = 0 on padding rows
         ss += e;
-        if constexpr (kEnt) ts = fmaf(e, ok[v] ? z[v] : 0.f, ts);
+        if constexpr (kEnt) ts = fmaf(e, fmaxf(z[v], kLowest), ts);   // 0 * -inf would be NaN
       }
       s_run = fmaf(s_run, sc, ss);
       if constexpr (kEnt) t_run = fmaf(t_run, sc, ts * zscale);

@@ -391,6 +391,42 @@ def test_vocabulary_tiles_of_minus_infinity(dtype, T):
         assert np.abs(np64(got) - want).max() <= 1e-4
 
 
+# the same at every tile edge and in the ranges of a long W, and runs that begin and end inside a tile: a masked row counts for nothing
+@pytest.mark.parametrize("runs", ["one tile", "any"])
+@pytest.mark.parametrize("dtype,n,d,V", [("bf16", 40, 64, 1024), ("bf16", 200, 64, 16384), ("bf16", 2200, 64, 5000), ("bf16", 40, 320, 157301),
+                                         ("bf16", 204, 320, 157301), ("f32", 40, 64, 1024), ("f32", 2200, 64, 16384)])
+def test_runs_of_minus_infinity(dtype, n, d, V, runs):
+    import torch
+    import paper_2603_04411_amd as L
+    g = torch.Generator(device="cuda").manual_seed(n + V)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    H = torch.randn(n, d, generator=g, device="cuda").to(tdt)
+    W = (0.1 * torch.randn(V, d, generator=g, device="cuda")).to(tdt)
+    H[:, 0] = 1.0
+    keep = torch.ones(V, dtype=torch.bool, device="cuda")
+    for at, length in [(256, 256)] if runs == "one tile" else [(3, 1), (70, 50), (131, 301), (V // 2 - 9, V // 64), (V - 33, 33)]:
+        keep[at:at + length] = False
+    W[~keep, 0] = -float("inf")
+    ids = keep.nonzero().flatten()
+    tok = ids[torch.randint(0, len(ids), (n,), generator=g, device="cuda")].int()
+    lens = torch.tensor([n], dtype=torch.int32, device="cuda")
+    desc = L.make_desc(1, 1, n, d, V, dtype)
+    ws = torch.full((L.workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    logp, lse, ent = (torch.full((n,), 7.0, device="cuda") for _ in range(3))
+    L.lmhead_logprob_fwd(desc, H, W, tok, lens, logp, lse, ent, None, None, ws)
+    assert L.lmhead_check(ws) == 0
+    z = H.double() @ W[keep].double().t()
+    want = z.logsumexp(1)
+    zy = (H.double() * W[tok.long()].double()).sum(1)
+    entropy = want - (torch.softmax(z, 1) * z).sum(1)
+    # an fp32 sum of d terms, a random walk of roundings by 2^-24 of its partial sums, six standard deviations; the merge of the sums and
+    # their logarithm, some roundings of 2^-24 of a figure below 20 each
+    bound = 6 * d ** 0.5 * 2.0 ** -24 * float(z.abs().max()) + 32 * 2.0 ** -24 * 20
+    assert float((lse.double() - want).abs().max()) <= bound
+    assert float((logp.double() - (zy - want)).abs().max()) <= 2 * bound
+    assert float((ent.double() - entropy).abs().max()) <= 4 * bound
+
+
 # many tokens per block of the sum: its error is that of one rounding to fp32, not of a long fp32 chain
 @pytest.mark.parametrize("n,d", [(4096, 1024), (16000000, 64)])
 def test_kv_retain_rate_of_a_constant_mask(n, d):
