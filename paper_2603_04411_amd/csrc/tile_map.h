@@ -134,14 +134,20 @@ inline int64_t logits_slots(bool f32, int64_t V, int edge) {
 inline int logits_edge(bool f32, int64_t V, int64_t n) {
   return n <= logits_slots(f32, V, 64) ? 64 : n <= logits_slots(f32, V, 128) ? 128 : kTile;
 }
-// The forward of as many bf16 slots as 128 wide tiles are for, over a W of 96 MB or more: one range of rows per compute unit instead of
-// tiles (lmhead_stream.hip).  A W that the caches hold, or most of it, is read sooner by more workgroups than that.  Call, us, tiles /
-// ranges, 64 (64), 192 (120) and 200 (200) slots (valid); beyond them the 256 wide tiles are as fast where their rounds are full:
-//   d 2048 V 151936 144/116   169/119   214/169      d 4096 V 151936 254/212   283/223   398/313     d 1024 V 151936 80/67 83/68 118/98
-//   d 2048 V 32000  44/42     47/43     59/49        d 4096 V 32000  69/65     75/68     100/77      d 2560 V 64000  87/68 82/69 120/98
-//   d 768 V 64000   35/32     34/32     48/43        d 4096 V 16000  60/62     69/63     69/69       d 1024 V 32000  27/30 30/30 36/34
-//   d 512 V 32000   20/24     22/24     25/28        256 slots, 256 valid: d 2048 V 151936 190/174   d 2560 V 64000 90/98
-constexpr int64_t kStreamSlots = 128 * 8 / 5, kStreamBytes = (int64_t)96 << 20, kStreamRows = 64;
+// The forward of as many bf16 slots as 128 wide tiles are for, over a W that the last-level cache (256 MB) cannot hold or mostly hold:
+// one range of rows per compute unit instead of tiles (lmhead_stream.hip).  What is still there of a smaller W from the call before
+// the tiles read sooner, and the ranges, which go past the caches, leave none of it to the dZ of a step.  Calls one after the other on
+// the same W, us, tiles / ranges, 64 (64), 192 (120) and 200 (200) slots (valid); steps are forward, loss and backward:
+//   below: d 2048 V 32000   32/42 40/48 41/48   steps 158/166 190/201 192/204      d 4096 V 16384   41/62 49/66 49/66   187/210 229/242 227/247
+//          d 1024 V 64000   35/37 43/47 43/47         157/158 197/206 199/212      d 512 V 151936   43/44 60/63 59/63   181/188 259/267 268/282
+//          d 2048 V 66000   65/71 85/100 87/101       354/355 468/438 486/461      d 4096 V 33000   69/68 93/117 95/119 349/346 472/453 494/483
+//   above: d 2048 V 80000   97/74 130/106 128/106      465/426 541/489 560/514     d 1024 V 151936  81/68 116/97 115/97 414/388 544/501 543/511
+//          d 2048 V 151936  157/117 229/170 217/171    814/750 928/857 953/893     d 4096 V 50000   120/80 174/130 170/131 573/517 672/596 717/650
+//          d 8192 V 20000   120/117 169/125 164/125    489/474 628/544 635/564     d 64 V 2100000   280/132 402/255 371/257
+//          (fewer rows a range, most of whose tile is empty: d 8192 V 18500 112/116 167/125 167/124)
+// (With other work in between, which takes W out of the caches, ranges are the faster ones for the smaller W too: d 2048 V 32000 68/50
+// 85/55 79/55; but not for steps, 205/206 236/235 242/242, which read it twice.)
+constexpr int64_t kStreamSlots = 128 * 8 / 5, kStreamBytes = (int64_t)288 << 20, kStreamRows = 76;
 inline bool logits_stream(int64_t V, int64_t d, int64_t n) {
   return n <= kStreamSlots && V * d * 2 >= kStreamBytes && V >= kStreamRows * kComputeUnits;
 }

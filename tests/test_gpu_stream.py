@@ -5,7 +5,8 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(64, 786437), (320, 157301), (1024, 50257), (4096, 16384), (2048, 24577)]
+SIZES = [(64, 2359301), (320, 471901), (1024, 150001), (8192, 19457), (2048, 73729)]
+STEP_SIZES = [(8192, 19457), (2048, 73729)]
 
 
 @pytest.mark.parametrize("d,V", SIZES)
@@ -45,3 +46,34 @@ def test_few_tokens(d, V, n, valid):
         del z
     off, nbytes = L.binding.workspace_region(desc, 1, L.binding.WS_GATHERED_ID)
     assert torch.equal(ws[off:off + nbytes].view(torch.int32)[:valid], tok[:valid])
+
+
+@pytest.mark.parametrize("d,V", STEP_SIZES)
+@pytest.mark.parametrize("n,valid", [(1, 1), (128, 128), (204, 129), (204, 204)])
+def test_backward_after_it(d, V, n, valid):
+    """dZ takes tiles also where the forward takes ranges; the workspace is sized for both and starts full of ones each time."""
+    import torch
+    import paper_2603_04411_amd as L
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    H = torch.randn(n, d, generator=g, device="cuda").bfloat16()
+    H[valid:] = float("nan")
+    W = (0.02 * torch.randn(V, d, generator=g, device="cuda")).bfloat16()
+    tok = torch.randint(0, V, (n,), generator=g, device="cuda", dtype=torch.int32)
+    tok[0] = V - 1
+    gl = torch.randn(n, generator=g, device="cuda")
+    lens = torch.tensor([valid], dtype=torch.int32, device="cuda")
+    desc = L.make_desc(1, 1, n, d, V, "bf16")
+    ws = torch.full((L.workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    logp, lse = (torch.full((n,), 7.0, device="cuda") for _ in range(2))
+    L.lmhead_logprob_fwd(desc, H, W, tok, lens, logp, lse, None, None, None, ws)
+    ws.fill_(0xFF)
+    dH, dW = torch.full((n, d), 7.0, device="cuda"), torch.full((V, d), 7.0, device="cuda")
+    L.lmhead_logprob_bwd(desc, H, W, tok, lens, lse, gl, dH, dW, ws)
+    assert L.lmhead_check(ws) == 0
+    Hf, Wf, gv = H[:valid].double(), W.double(), gl[:valid].double()
+    dz = torch.softmax(Hf @ Wf.t(), 1).mul_(-gv[:, None])
+    dz[torch.arange(valid, device="cuda"), tok[:valid].long()] += gv
+    assert not dH[valid:].any()
+    # dZ is rounded to bf16: 2^-9 of each element
+    for got, want in ((dH[:valid], dz @ Wf), (dW, dz.t() @ Hf)):
+        assert float((got.double() - want).norm() / want.norm()) <= 2.0 ** -8

@@ -27,6 +27,16 @@ def test_logits_edge_widens_with_the_slots_and_its_scratch_serves_fewer(tmp_path
     _run_host_check(tmp_path, "logits_edge_check")
 
 
+def test_the_gpu_tests_of_the_streaming_forward_take_it(tmp_path):
+    from tests import test_gpu_shapes as shapes, test_gpu_stream as stream
+    want = [(V, d, n, n <= 204) for d, V in stream.SIZES for n in (1, 130, 204, 205)]
+    want += [(V, d, n, True) for d, V in stream.STEP_SIZES for n in (1, 204)]
+    want += [(V, d, n, V >= 150000) for dtype, n, d, V in shapes.MASKED if dtype == "bf16"]
+    _run_host_check(tmp_path, "logits_edge_check")
+    r = subprocess.run([str(tmp_path / "logits_edge_check"), *(str(v) for w in want for v in w[:3])], capture_output=True, text=True)
+    assert [bool(int(line)) for line in r.stdout.split()] == [w[3] for w in want]
+
+
 def test_gradient_edges_follow_the_length_of_the_contraction(tmp_path):
     _run_host_check(tmp_path, "gradient_edge_check")
 
