@@ -399,16 +399,21 @@ inline KvTail kv_tail(bool f32, int64_t n, int d, int own_edge, int own_slices) 
 inline bool kv_tail_dx_apart(bool f32, int d, bool few) { return few && (f32 || d > 2048); }
 inline int64_t kv_tail_counters(int64_t d) { return 2 * ((d + 63) / 64) * ((d + 63) / 64); }
 
-// Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  The workgroup that is
-// last has 16 tokens to itself, behind stores that have gone through to memory: 5.5 us at d = 1024 where the launch and its gap are 5 to
-// 7, more with soft outputs to write.  Call, us, launch / same launch:
-//   decode  16 x 1024 23.0/20.7  128 x 1024 22.3/21.3  200 x 1024 21.5/22.2  160 x 768 26.1/22.6  256 x 512 25.5/18.8  32 x 320 20.5/17.8
-//   gate  2000 x 128 12.8/10.2  1000 x 256 15.7/13.1  300 x 1024 fp32 37.5/40.3
-//   training pair  300 x 128 fp32 47.3/45.0  4096 x 64 43.1/40.3  1000 x 256 51.0/48.4  600 x 256 fp32 49.2/49.8  256 x 512 49.5/49.9
-//                  128 x 1024 55.6/57.7  700 x 512 58.4/61.0
+// Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  That launch costs its
+// 2.5 us where calls are short enough to wait for each other's launches (20 us of gate and store, less of a gate alone), and next to
+// nothing in a captured graph.  The workgroup that is last has 16 tokens to itself, behind stores that have gone through to memory: 0.2 us
+// for a few short rows, 3 us for many long ones, more with soft outputs to write.  So: where a gate alone is not slower, by tokens x
+// components for each group of 256 components.  Gate alone / with the store, us, launch : same launch, bf16:
+//   16 x 256   14.6 : 11.9  22.6 : 20.2     256 x 512  - : -        22.8 : 20.2     540 x 448  14.3 : 12.7             1000 x 448  14.8 : 16.1
+//   64 x 640   14.5 : 13.3  20.9 : 18.2     64 x 768   13.3 : 13.4  20.9 : 20.7     160 x 768  13.3 : 14.2  20.2 : 18.6  240 x 704  14.3 : 15.2
+//   16 x 1024  15.3 : 15.4  20.4 : 18.8     16 x 896   14.7 : 14.6  20.6 : 18.1     64 x 896   14.9 : 15.4  20.2 : 18.8  128 x 1024 15.5 : 16.7  20.5 : 20.9
+// fp32:  512 x 256 15 : 12.5    64 x 448 15.0 : 14.9  20.8 : 18.4    300 x 448 15.5 : 15.9    16 x 640 17.4 : 17.8  20.9 : 21.4    300 x 768 20.4 : 21.7
+// with soft outputs (training pair):  300 x 128 fp32 47.3 : 45.0  4096 x 64 43.1 : 40.3  1000 x 256 51.0 : 48.4  600 x 256 fp32 49.2 : 49.8
+//   256 x 512 49.5 : 49.9  128 x 1024 55.6 : 57.7  700 x 512 58.4 : 61.0
 constexpr int kKvFewMask = 1024;
 inline bool kv_mask_with_logits(int esz, int64_t n, int d, bool soft) {
-  return soft ? d * esz <= 512 : d < kKvFewMask || (d == kKvFewMask && n <= 128);
+  constexpr int64_t kMost[2][kKvFewMask / 256] = {{512 << 10, 256 << 10, 64 << 10, 32 << 10}, {512 << 10, 48 << 10, 0, 0}};
+  return soft ? d * esz <= 512 : d <= kKvFewMask && n * d <= kMost[esz == 4][(d - 1) / 256];
 }
 
 }  // namespace lmhead

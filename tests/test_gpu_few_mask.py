@@ -7,7 +7,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("n,d", [(1, 64), (17, 64), (15, 320), (100, 128), (8000, 64), (300, 256), (33, 768), (128, 1024), (129, 1024), (16, 1088)])
+@pytest.mark.parametrize("n,d", [(1, 64), (17, 64), (15, 320), (100, 128), (8000, 64), (300, 256), (512, 512), (513, 512), (96, 512), (97, 512),
+                                 (85, 768), (86, 768), (32, 1024), (33, 1024), (16, 1088)])
 @pytest.mark.parametrize("literal", [False, True])
 def test_mask_with_the_logits(dtype, n, d, literal):
     import torch

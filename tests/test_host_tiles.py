@@ -49,6 +49,10 @@ def test_kv_edge_is_the_faster_one_where_both_were_measured(tmp_path):
     _run_host_check(tmp_path, "kv_edge_check")
 
 
+def test_kv_launches_are_merged_where_that_was_measured_to_be_faster(tmp_path):
+    _run_host_check(tmp_path, "kv_launch_check")
+
+
 def test_the_gpu_tests_of_the_kv_products_take_the_tiles_that_they_name(tmp_path):
     """The tables in the GPU tests say which tiles their sizes run on; the rule says which they really run on."""
     from tests import test_gpu_deep_tiles as deep, test_gpu_kmajor as kmajor
