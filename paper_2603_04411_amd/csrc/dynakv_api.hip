@@ -82,43 +82,20 @@ int dynakv_gate(const dynakv_desc* desc, const void* x, const void* U, const voi
   }
   if (kv_few_fits(dt == LMHEAD_F32, L.n, d)) {
     const bool literal = (desc->flags & DYNAKV_FLAG_LITERAL_FLIP) != 0, one = kv_mask_with_logits(L.esz, L.n, d, m || xhat);
-    KvFewArgs fa{};
-    fa.x = x;
-    fa.ldx = desc->ldx;
-    fa.M = U;
-    fa.n = (int)L.n;
-    fa.d = d;
-    fa.out_e = xt;
-    fa.hdr = hdr;
-    fa.clear = one ? w.at<int32_t>(L.order) : nullptr;
+    int32_t* const done = one ? w.at<int32_t>(L.order) : nullptr;
+    float* const logits = w.at<float>(L.logits);
     {
       TimedLaunch tl(4, s);
-      LM_TRY(launch_kv_few(dt, fa, s));
+      LM_TRY(launch_kv_few(dt, {x, desc->ldx, U, (int)L.n, d, xt, hdr, done, 0}, s));
     }
-    KvFewArgs la{};
-    la.x = xt;
-    la.ldx = d;
-    la.M = W;
-    la.n = (int)L.n;
-    la.d = d;
-    la.out_f = w.at<float>(L.logits);
-    if (one) {
-      la.k = k;
-      la.done = w.at<int32_t>(L.order);
-      la.bias = b;
-      la.xt = xt;
-      la.tau = tau;
-      la.literal = literal;
-      la.m = m;
-      la.xhat = xhat;
-    }
+    const KvFewMask mask{k, done, b, xt, m, xhat, tau, literal};
     {
       TimedLaunch tl(5, s);
-      LM_TRY(launch_kv_few(dt, la, s));
+      LM_TRY(launch_kv_few(dt, {xt, d, W, (int)L.n, d, logits, nullptr, nullptr, kFewWide}, s, one ? &mask : nullptr));
     }
     if (!one) {
       TimedLaunch tl(6, s);
-      LM_TRY(launch_kv_mask(dt, w.at<float>(L.logits), b, xt, L.n, d, tau, literal, k, m, xhat, s));
+      LM_TRY(launch_kv_mask(dt, logits, b, xt, L.n, d, tau, literal, k, m, xhat, s));
     }
     return LMHEAD_OK;
   }
@@ -291,7 +268,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   {
     TimedLaunch tl(5, s);
     if (few)
-      LM_TRY(launch_kv_few(dt, {xt, d, W, (int)L.n, d, nullptr, ga.out_f, hdr, false, false}, s));
+      LM_TRY(launch_kv_few(dt, {xt, d, W, (int)L.n, d, ga.out_f, hdr, nullptr, kFewWide}, s));
     else
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
@@ -314,7 +291,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   {
     TimedLaunch tl(9, s);
     if (few)
-      LM_TRY(launch_kv_few(dt, {at(L.gl), d, W, (int)L.n, d, at(L.gxt), nullptr, nullptr, true, true}, s));
+      LM_TRY(launch_kv_few(dt, {at(L.gl), d, W, (int)L.n, d, at(L.gxt), nullptr, nullptr, kFewRows | kFewAdd}, s));
     else
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }
@@ -327,7 +304,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   if (dx_apart) {
     TimedLaunch tl(10, s);
     if (few)
-      LM_TRY(launch_kv_few(dt, {at(L.gxt), d, U, (int)L.n, d, dx, nullptr, nullptr, true, false}, s));
+      LM_TRY(launch_kv_few(dt, {at(L.gxt), d, U, (int)L.n, d, dx, nullptr, nullptr, kFewRows}, s));
     else
       LM_TRY(launch_kv_gemm(dt, ga, s));
   }

@@ -165,30 +165,35 @@ hipError_t launch_kv_gemm(int dtype, const KvGemmArgs& a, hipStream_t s);
 // out = the n rows of row_bytes (a multiple of 16), `pitch` bytes apart, one behind the other.
 hipError_t launch_kv_dense(const void* x, int64_t pitch, int64_t n, int row_bytes, void* out, hipStream_t s);
 
-// out[n][j] = sum_k x[n][k] M[k][j], or with `rows` sum_k x[n][k] M[j][k], for few tokens: M [d x d] as the caller has
-// it (no copy), 16 tokens x 64 columns per workgroup.  out_e (storage type) or out_f (fp32), dense rows of d, whichever is
-// non-null; accumulate: out_e is added to.  Clears the header unless null.
+// out[n][j] = sum_k x[n][k] M[k][j], or with kFewRows sum_k x[n][k] M[j][k], for few tokens: M [d x d] as the caller has
+// it (no copy), 16 tokens x 64 columns per workgroup.  out: dense rows of d, in the storage type or (kFewWide) fp32; kFewAdd: added to,
+// storage type only.  Clears the header unless null.
+constexpr int kFewRows = 1, kFewAdd = 2, kFewWide = 4;
 struct KvFewArgs {
   const void* x;
   int64_t ldx;
   const void* M;
   int n, d;
-  void* out_e;
-  float* out_f;
+  void* out;
   WsHeader* hdr;
-  bool rows, accumulate;
   int32_t* clear;      // unless null: one counter per 16 tokens, set to 0
-  // With k: out_f holds gate logits, and the last workgroup of 16 tokens makes their mask (launch_kv_mask, d up to kKvFewMask).
+  int flags;
+};
+// The arguments of a launch come from host memory, a line at a time, and each of these products waits for them: with the next line in it
+// a gate of 32 x 1024 in fp32 took 23.4 us instead of 22.9.
+static_assert(sizeof(KvFewArgs) <= 64, "one line");
+// The product is the gate's logits (kFewWide), and the last workgroup of 16 tokens makes their mask (launch_kv_mask, d up to kKvFewMask).
+struct KvFewMask {
   int32_t* k;
   int32_t* done;       // the counters, cleared by a launch before
   const float* bias;
   const void* xt;
-  float tau;
-  bool literal;
   float* m;
   void* xhat;
+  float tau;
+  bool literal;
 };
-hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s);
+hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s, const KvFewMask* mask = nullptr);
 
 // The whole gate of many tokens in one kernel (dynakv_gate.hip), for callers that want x~ and k only.  Ufrag, Wfrag: the
 // parameter matrices in fragment order (KvCopy, W's flipped when `literal`).

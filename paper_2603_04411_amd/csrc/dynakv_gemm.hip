@@ -310,23 +310,19 @@ hipError_t launch_tiles(const KvGemmArgs& a, hipStream_t s) {
 // fragments lie in memory as they are; MFMA t covers the columns 16 t + r.  No transposed or padded copies, so the launch
 // that made them goes too.
 //
-// kMask: the gate's logits, and their mask in the same launch.  The workgroups of 16 tokens count themselves, and the one that
-// finishes last has the tokens' whole rows to read and a wavefront for each.  They come from workgroups on other XCDs, whose L2s do
+// kv_few_mask_kernel: the gate's logits, and their mask in the same launch.  The workgroups of 16 tokens count themselves, and the one
+// that finishes last has the tokens' whole rows to read and a wavefront for each.  They come from workgroups on other XCDs, whose L2s do
 // not see each other's lines: logits are stored and loaded at device scope, and the count goes up when a workgroup's stores
-// have been acknowledged.  (Nobody waits for anybody.)  DECODE.
+// have been acknowledged.  (Nobody waits for anybody.)
 constexpr int kFewWaves = 16;
 
-template <typename E, bool kRows, int kMask = 0>
-__global__ __launch_bounds__(64 * kFewWaves) void kv_few_kernel(KvFewArgs a) {
+// The output of this thread: token threadIdx.x / kFewCols and column threadIdx.x % kFewCols of the workgroup's.
+template <typename E, bool kRows>
+__device__ inline float few_product(const KvFewArgs& a) {
   constexpr int PITCH = kFewCols + 4;   // floats
   __shared__ __attribute__((aligned(16))) float part[kFewWaves][kFewTok * PITCH];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int q = lane >> 4, tl = lane & 15;
-  if (a.hdr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-    a.hdr->err = 0;
-    a.hdr->nv = 0;
-  }
-  if (!kMask && a.clear && blockIdx.x == 0 && threadIdx.x == 0) a.clear[blockIdx.y] = 0;
   const int c0 = blockIdx.x * kFewCols, t0 = blockIdx.y * kFewTok;
   const int tok = min(t0 + tl, a.n - 1);   // tokens past the end re-read the last one
   f32x4_t acc[4] = {};
@@ -385,43 +381,62 @@ __global__ __launch_bounds__(64 * kFewWaves) void kv_few_kernel(KvFewArgs a) {
     *reinterpret_cast<f32x4_t*>(&part[w][tl * PITCH + (kRows ? 16 * u + 4 * q : 16 * q + 4 * u)]) = o;
   }
   __syncthreads();
-  using T = typename std::conditional<Elem<E>::size == 2, __bf16, float>::type;
-  const int ot = threadIdx.x / kFewCols, oc = threadIdx.x % kFewCols;
-  const bool in = t0 + ot < a.n;
   float sum = 0.f;
 #pragma unroll
-  for (int u = 0; u < kFewWaves; ++u) sum += part[u][ot * PITCH + oc];
-  const int64_t at = (int64_t)(t0 + ot) * a.d + c0 + oc;
-  if constexpr (kMask == 0) {
-    if (!in) return;
-    if (a.out_f) {
-      a.out_f[at] = sum;
-    } else {
-      T* const out = static_cast<T*>(a.out_e) + at;
-      *out = (T)(a.accumulate ? sum + (float)*out : sum);
-    }
-  } else {
-    if (in) __hip_atomic_store(a.out_f + at, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    __shared__ int last;
-    if (threadIdx.x == 0)
-      last = __hip_atomic_fetch_add(a.done + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
-    __syncthreads();
-    const int64_t mine = t0 + w;
-    if (!last || mine >= a.n) return;
-    const float* const z = a.out_f + mine * a.d;
-    auto row4 = [&](int j) {
-      const unsigned long long* const q = reinterpret_cast<const unsigned long long*>(z + j);
-      const unsigned long long lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return make_float4(__builtin_bit_cast(float, (uint32_t)lo), __builtin_bit_cast(float, (uint32_t)(lo >> 32)),
-                         __builtin_bit_cast(float, (uint32_t)hi), __builtin_bit_cast(float, (uint32_t)(hi >> 32)));
-    };
-    const int count = mask_token<T, kMask>(row4, a.bias, static_cast<const T*>(a.xt), mine, a.d, a.tau, a.literal ? 1 : 0, a.m,
-                                           static_cast<T*>(a.xhat));
-    if (lane == 0) a.k[mine] = count;
+  for (int u = 0; u < kFewWaves; ++u) sum += part[u][threadIdx.x / kFewCols * PITCH + threadIdx.x % kFewCols];
+  return sum;
+}
+
+template <typename E>
+using FewT = typename std::conditional<Elem<E>::size == 2, __bf16, float>::type;
+
+template <typename E, bool kRows>
+__global__ __launch_bounds__(64 * kFewWaves) void kv_few_kernel(KvFewArgs a) {
+  if (a.hdr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    a.hdr->err = 0;
+    a.hdr->nv = 0;
   }
+  const float sum = few_product<E, kRows>(a);
+  const int tok = blockIdx.y * kFewTok + threadIdx.x / kFewCols;
+  if (tok >= a.n) return;
+  if (a.clear && blockIdx.x == 0 && threadIdx.x == 0) a.clear[blockIdx.y] = 0;   // here: loads do not wait for the pointer
+  const int64_t at = (int64_t)tok * a.d + blockIdx.x * kFewCols + threadIdx.x % kFewCols;
+  if (a.flags & kFewWide) {
+    static_cast<float*>(a.out)[at] = sum;
+  } else {
+    FewT<E>* const out = static_cast<FewT<E>*>(a.out) + at;
+    *out = (FewT<E>)(a.flags & kFewAdd ? sum + (float)*out : sum);
+  }
+}
+
+// NG: groups of 256 columns.
+template <typename E, int NG>
+__global__ __launch_bounds__(64 * kFewWaves) void kv_few_mask_kernel(KvFewArgs a, KvFewMask b) {
+  using T = FewT<E>;
+  const float sum = few_product<E, false>(a);
+  const int t0 = blockIdx.y * kFewTok, tok = t0 + threadIdx.x / kFewCols;
+  float* const logits = static_cast<float*>(a.out);
+  if (tok < a.n)
+    __hip_atomic_store(logits + (int64_t)tok * a.d + blockIdx.x * kFewCols + threadIdx.x % kFewCols, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  __shared__ int last;
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(b.done + blockIdx.y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.d / kFewCols - 1;
+  __syncthreads();
+  const int64_t mine = t0 + (threadIdx.x >> 6);
+  if (!last || mine >= a.n) return;
+  const float* const z = logits + mine * a.d;
+  auto row4 = [&](int j) {
+    const unsigned long long* const q = reinterpret_cast<const unsigned long long*>(z + j);
+    const unsigned long long lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float4(__builtin_bit_cast(float, (uint32_t)lo), __builtin_bit_cast(float, (uint32_t)(lo >> 32)),
+                       __builtin_bit_cast(float, (uint32_t)hi), __builtin_bit_cast(float, (uint32_t)(hi >> 32)));
+  };
+  const int count = mask_token<T, NG>(row4, b.bias, static_cast<const T*>(b.xt), mine, a.d, b.tau, b.literal ? 1 : 0, b.m,
+                                      static_cast<T*>(b.xhat));
+  if ((threadIdx.x & 63) == 0) b.k[mine] = count;
 }
 static_assert(kFewTok * kFewCols == 64 * kFewWaves, "one output per thread");
 
@@ -453,20 +468,22 @@ hipError_t launch_e(const KvGemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s) {
+hipError_t launch_kv_few(int dtype, const KvFewArgs& a, hipStream_t s, const KvFewMask* mask) {
   const dim3 grid((unsigned)(a.d / kFewCols), (unsigned)((a.n + kFewTok - 1) / kFewTok));
   const dim3 block(64 * kFewWaves);
-  if (a.k && (a.d > kKvFewMask || a.rows || !a.out_f || !a.done)) return hipErrorInvalidValue;
+  if (mask && (a.d > kKvFewMask || (a.flags & kFewRows) || !(a.flags & kFewWide) || !mask->k || !mask->done)) return hipErrorInvalidValue;
   auto typed = [&](auto tag) {
     using E = decltype(tag);
-    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a); };
-    if (a.rows) return launch(kv_few_kernel<E, true>);
-    if (!a.k) return launch(kv_few_kernel<E, false>);
+    if (!mask) {
+      hipLaunchKernelGGL((a.flags & kFewRows ? kv_few_kernel<E, true> : kv_few_kernel<E, false>), grid, block, 0, s, a);
+      return;
+    }
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, a, *mask); };
     switch ((a.d + 255) / 256) {
-      case 1: return launch(kv_few_kernel<E, false, 1>);
-      case 2: return launch(kv_few_kernel<E, false, 2>);
-      case 3: return launch(kv_few_kernel<E, false, 3>);
-      default: return launch(kv_few_kernel<E, false, 4>);
+      case 1: return launch(kv_few_mask_kernel<E, 1>);
+      case 2: return launch(kv_few_mask_kernel<E, 2>);
+      case 3: return launch(kv_few_mask_kernel<E, 3>);
+      default: return launch(kv_few_mask_kernel<E, 4>);
     }
   };
   if (dtype == LMHEAD_BF16)
