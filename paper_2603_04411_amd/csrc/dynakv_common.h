@@ -74,34 +74,11 @@ static inline KvBwdLayout make_kv_bwd_layout(const dynakv_desc* d) {
   L.d = d->d;
   L.ncap = (int64_t)round_up((size_t)L.n, kTile);
   L.dp = (int64_t)round_up((size_t)L.d, kTile);
-  // Tile edge and slices of the contraction over the tokens: as many slices as give one workgroup per compute unit,
-  // on the largest edge whose slices then keep 16 K-steps (of 128 bytes; edge 256: 32), else edge 64 with at least 2 each.
-  // dW alone / whole backward call, us, bf16 unless said, with the choice in brackets:
-  //     n x d           edge 256         edge 128          edge 64          (slices giving 256 workgroups, or the best)
-  //     32768 x 1024    [72.6 / 611]     99.6 / 638        208 / 867
-  //     8192 x 2048     [63.4 / 528]     79.2 / 555        113 / 626
-  //     4096 x 1024     23.4 / 177       [18.3 / 156]      30.6 / 181
-  //     512 x 1024      17.4 / 117       11.3 / 100        [9.8 / 93]
-  //     8192 x 256      18.0 / 115       11.5 / 102        [9.6 / 92]
-  //     300 x 128 fp32  20.6 / 83        9.9 / 63          [7.6 / 59]
-  // Training pair, edge 256 / 128, where slices of 256 wide tiles have 16 K-steps: 4096 x 2048 346.5 / 309.7, 16384 x 1024
-  // 398.5 / 383.0, fp32 8192 x 1024 978 / 943; 23: 6000 x 2048 474 / 449, 24000 x 1024 596 / 583; 32: 8192 x 2048 568 / 570,
-  // 32768 x 1024 708 / 707, fp32 16384 x 1024 1874 / 1853; 64: 65536 x 1024 1317 / 1364.
-  {
-    const int64_t ksteps = L.ncap * L.esz / 128;
-    for (int edge : {256, 128, 64}) {
-      const int64_t side = (L.d + edge - 1) / edge;
-      int64_t ks = (256 + side * side - 1) / (side * side);
-      const bool last = edge == 64;
-      if (last && ks > ksteps / 2) ks = ksteps / 2;
-      if (ks < 1) ks = 1;
-      L.edge = edge;
-      L.ksplit = (int)ks;
-      if (last || ksteps / ks >= (edge == 256 ? 32 : 16)) break;
-    }
-  }
+  const KvTail own = kv_gradient_slices(L.esz == 4, L.n, L.d);
+  L.edge = own.edge;
+  L.ksplit = own.slices;
   const int part_slices = L.ksplit;
-  if (const KvTail t = kv_tail(L.esz == 4, L.n, L.d, L.edge, L.ksplit); t.edge) {
+  if (const KvTail t = kv_tail(L.esz == 4, L.n, L.d, own); t.edge) {
     L.tail = true;
     L.edge = t.edge;
     L.ksplit = t.slices;

@@ -359,6 +359,38 @@ inline bool kv_few_fits(bool f32, int64_t n, int d) {
   return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= per_unit * (int64_t)kComputeUnits;
 }
 
+// Tile edge and slices of the parameter gradients' contraction over the tokens, in a launch of their own: as many slices as give one workgroup per compute unit,
+// on the largest edge whose slices then keep 16 K-steps (of 128 bytes; edge 256: 32), else edge 64 with at least 2 each.
+// dW alone / whole backward call, us, bf16 unless said, with the choice in brackets:
+//     n x d           edge 256         edge 128          edge 64          (slices giving 256 workgroups, or the best)
+//     32768 x 1024    [72.6 / 611]     99.6 / 638        208 / 867
+//     8192 x 2048     [63.4 / 528]     79.2 / 555        113 / 626
+//     4096 x 1024     23.4 / 177       [18.3 / 156]      30.6 / 181
+//     512 x 1024      17.4 / 117       11.3 / 100        [9.8 / 93]
+//     8192 x 256      18.0 / 115       11.5 / 102        [9.6 / 92]
+//     300 x 128 fp32  20.6 / 83        9.9 / 63          [7.6 / 59]
+// Training pair, edge 256 / 128, where slices of 256 wide tiles have 16 K-steps: 4096 x 2048 346.5 / 309.7, 16384 x 1024
+// 398.5 / 383.0, fp32 8192 x 1024 978 / 943; 23: 6000 x 2048 474 / 449, 24000 x 1024 596 / 583; 32: 8192 x 2048 568 / 570,
+// 32768 x 1024 708 / 707, fp32 16384 x 1024 1874 / 1853; 64: 65536 x 1024 1317 / 1364.
+struct KvTail {
+  int edge = 0, slices = 0;
+};
+inline KvTail kv_gradient_slices(bool f32, int64_t n, int d) {
+  const int64_t ksteps = (n + kTile - 1) / kTile * kTile * (f32 ? 4 : 2) / 128;
+  KvTail t;
+  for (int edge : {256, 128, 64}) {
+    const int64_t side = (d + edge - 1) / edge;
+    int64_t ks = (256 + side * side - 1) / (side * side);
+    const bool last = edge == 64;
+    if (last && ks > ksteps / 2) ks = ksteps / 2;
+    if (ks < 1) ks = 1;
+    t.edge = edge;
+    t.slices = (int)ks;
+    if (last || ksteps / ks >= (edge == 256 ? 32 : 16)) break;
+  }
+  return t;
+}
+
 // What follows g_x~ in a backward call (dx, both parameter gradients, the sums of their slices, db) as one launch: none of them waits
 // for another, each leaves compute units idle by itself, and a launch costs its 4 us wherever it is put.  All on tiles of one edge.  The
 // last workgroup of a gradient tile reads all its slices alone, so there are to be few of them, and of equal length with the rest.
@@ -369,17 +401,22 @@ inline bool kv_few_fits(bool f32, int64_t n, int d) {
 //     2000 x 512   65.8 / 59.6    64, 4 / 64, 2          1500 x 1536  153 / 130      64, 1 / 128, 1
 //     5000 x 256   62.6 / 58.3    64, 16 / 64, 5         8192 x 1024  218 / 203      128, 4 / 128, 2
 //     32768 x 256  141 / 136      64, 16 / 64, 16        2048 x 2048  201 / 199      128, 1 / 128, 1
+//     16384 x 384  125 / 120      64, 8 / 64, 8          14000 x 640  213 / 195      128, 11 / 128, 6
 // Other choices: 4096 x 1024 with 1, 3, 4, 8 slices 140, 137, 145, 180; 1024 x 1024 on edge 128 79, 2048 x 1024 107 instead of 100;
 // 1500 x 1536 on edge 64 140.  Beyond the work and the slices that it stops at: 3000 x 2048 (71) 256 / 259, 16384 x 1024 397 / 391,
-// 65536 x 64 (64 slices) 122 / 124, 16700 x 64 63 / 64.
+// 65536 x 64 (64 slices) 122 / 124, 16700 x 64 63 / 64; on edge 128 with 9 to 16 slices 16384 x 448 141 / 144, 32768 x 448 261 / 283,
+// 32768 x 384 224 / 234, 40000 x 320 240 / 244.
 // fp32 keeps the slices that its sums had (longer ones raise the error of dU from 2.28e-6 to 2.49e-6 at 4096 x 1024), and so edge
-// 64 (2048 x 1024 with 4 slices on edge 128: 305 / 370); 2000 x 256, 16 slices, 66.5 / 72.9.
-struct KvTail {
-  int edge = 0, slices = 0;   // edge 0: launches of their own
-};
-inline KvTail kv_tail(bool f32, int64_t n, int d, int own_edge, int own_slices) {
-  const int kMostSlices = f32 ? 8 : 16, kMostWork = 48;
-  if (own_edge > (f32 ? 64 : 128)) return {};
+// 64 (2048 x 1024 with 4 slices on edge 128: 305 / 370; 2000 x 256, 16 slices, 66.5 / 72.9).  Launches of their own / one:
+//     100 x 64   41 / 36    40 x 192  40.7 / 38.6    300 x 128 40.7 / 38.2    2000 x 576  163 / 147    1000 x 768  139 / 122
+//     1500 x 448 97 / 85    300 x 1024 123 / 119     600 x 1280 202 / 185     1000 x 1152 272 / 248
+// Of few tokens, whose dx stays apart, only the gradients are left, and their slices go through memory instead of staying in L2:
+//     300 x 256 45.0 / 46.9    512 x 320 54.4 / 55.9    16 x 512 52.6 / 57.3    16 x 640 62.1 / 67.1    100 x 448 53.9 / 54.6
+// edge 0: launches of their own.
+inline KvTail kv_tail(bool f32, int64_t n, int d, const KvTail& own) {
+  const int kMostWork = 48;
+  if (own.edge > (f32 ? 64 : 128)) return {};
+  if (f32 && own.slices > 1 && own.slices * d > 1024 && kv_few_fits(f32, n, d)) return {};
   const int esz = f32 ? 4 : 2;
   const int64_t ksteps = (n * esz + 127) / 128, dx_steps = ((int64_t)d * esz + 127) / 128;
   // K-steps of a place for a workgroup (256 / edge of them on a compute unit), were all equally loaded
@@ -389,14 +426,14 @@ inline KvTail kv_tail(bool f32, int64_t n, int d, int own_edge, int own_slices) 
   KvTail t;
   t.edge = !f32 && work(128) >= 16 ? 128 : 64;
   const int64_t w = work(t.edge), steps = w > 12 ? w * 4 / 3 : 16;   // of a slice
-  t.slices = own_slices;   // never more: the scratch memory is sized for these, and grows with n
-  if (!f32 && (ksteps + steps - 1) / steps < own_slices) t.slices = (int)((ksteps + steps - 1) / steps);
-  return w <= kMostWork && t.slices <= kMostSlices ? t : KvTail{};
+  t.slices = own.slices;   // never more: the scratch memory is sized for these, and grows with n
+  if (!f32 && (ksteps + steps - 1) / steps < own.slices) t.slices = (int)((ksteps + steps - 1) / steps);
+  return w <= kMostWork && t.slices <= (f32 || t.edge == 128 ? 8 : 16) ? t : KvTail{};
 }
 // Whether dx of few tokens stays the product of few tokens before it: sixteen wavefronts share its contraction, one has it here.
 // 16 tokens, d 1024 / 2048 / 4096, the pair with dx apart / within, us: 52.6 / 49.2, 85.2 / 84.3, 188 / 190; 1 x 8192: 442 / 491.
 // In fp32 they also keep its sums short (300 x 128: error 3.98e-7, within 4.58e-7).
-inline bool kv_tail_dx_apart(bool f32, int d, bool few) { return few && (f32 || d > 2048); }
+inline bool kv_tail_dx_apart(bool f32, int64_t n, int d) { return kv_few_fits(f32, n, d) && (f32 || d > 2048); }
 inline int64_t kv_tail_counters(int64_t d) { return 2 * ((d + 63) / 64) * ((d + 63) / 64); }
 
 // Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  That launch costs its
