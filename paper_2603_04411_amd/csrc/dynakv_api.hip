@@ -300,7 +300,7 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ga.B = at(L.gxt);
   ga.out_e = dx;
   ga.accumulate = false;
-  const bool dx_apart = !L.tail || kv_tail_dx_apart(dt == LMHEAD_F32, L.n, d);
+  const bool dx_apart = !L.tail || kv_tail_dx_apart(dt == LMHEAD_F32, L.n, d, {L.edge, L.ksplit});
   if (dx_apart) {
     TimedLaunch tl(10, s);
     if (few)

@@ -430,10 +430,21 @@ inline KvTail kv_tail(bool f32, int64_t n, int d, const KvTail& own) {
   if (!f32 && (ksteps + steps - 1) / steps < own.slices) t.slices = (int)((ksteps + steps - 1) / steps);
   return w <= kMostWork && t.slices <= (f32 || t.edge == 128 ? 8 : 16) ? t : KvTail{};
 }
-// Whether dx of few tokens stays the product of few tokens before it: sixteen wavefronts share its contraction, one has it here.
-// 16 tokens, d 1024 / 2048 / 4096, the pair with dx apart / within, us: 52.6 / 49.2, 85.2 / 84.3, 188 / 190; 1 x 8192: 442 / 491.
-// In fp32 they also keep its sums short (300 x 128: error 3.98e-7, within 4.58e-7).
-inline bool kv_tail_dx_apart(bool f32, int64_t n, int d) { return kv_few_fits(f32, n, d) && (f32 || d > 2048); }
+// Whether dx stays a launch of its own before it (pair, us, launches of their own / dx within / apart):
+//  - few tokens, bf16 from 2048 components on: sixteen wavefronts share the contraction of the product of few tokens, one has it in
+//    a tile.  16 tokens, d 1024 / 2048 / 4096, apart / within: 52.6 / 49.2, 85.2 / 84.3, 188 / 190; 1 x 8192: 442 / 491.  In fp32 it also
+//    keeps the sums short (300 x 128: error 3.98e-7, within 4.58e-7).
+//  - bf16 tiles that hold five K-steps by themselves (kv_deep_tiles), whose contraction is longer than all the rest:
+//    100 x 3072 145 / 148 / 144   256 x 4096 208 / 212 / 200   100 x 5120 259 / 292 / 260   100 x 8192 499 / 544 / 490; 256 x 2560 140 / 137
+//  - fp32 tiles that would start in a last round of places that they have to themselves: they share compute units there, four to one,
+//    and others idle.  800 x 960 162 / 173 / 160   600 x 1408 216 / 229 / 214   400 x 1536 216 / 226 / 212   256 x 2560 356 / 377 / 354; with a
+//    fuller round 400 x 1792 256 / 240, with more tiles of dx than compute units 1200 x 896 223 / 205, 800 x 1280 291 / 271
+inline bool kv_tail_dx_apart(bool f32, int64_t n, int d, const KvTail& t) {
+  if (kv_few_fits(f32, n, d)) return f32 || d > 2048;
+  if (!f32) return d >= 3072 && kv_deep_tiles(3, kv_tile_edge(false, 3, d, n, d, kComputeUnits), d, n, d, kComputeUnits);
+  const int64_t places = kComputeUnits * (256 / t.edge), dx = tiles_of(d, n, t.edge), all = dx + 2 * t.slices * tiles_of(d, d, t.edge);
+  return dx <= kComputeUnits && all > places && all % places < places / 2;
+}
 inline int64_t kv_tail_counters(int64_t d) { return 2 * ((d + 63) / 64) * ((d + 63) / 64); }
 
 // Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  That launch costs its

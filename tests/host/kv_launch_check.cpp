@@ -33,19 +33,21 @@ int main() {
   auto tail = [&](bool f32, int64_t n, int d, bool one, bool apart) {
     ++cases;
     const KvTail t = kv_tail(f32, n, d, kv_gradient_slices(f32, n, d));
-    if ((t.edge != 0) != one || (one && kv_tail_dx_apart(f32, n, d) != apart)) { ++bad; std::printf("tail f32=%d n=%ld d=%d\n", f32, (long)n, d); }
+    if ((t.edge != 0) != one || (one && kv_tail_dx_apart(f32, n, d, t) != apart)) { ++bad; std::printf("tail f32=%d n=%ld d=%d\n", f32, (long)n, d); }
   };
   const struct { int64_t n; int d; bool one, apart; } bf16[] = {
       {64, 64, true, false}, {700, 256, true, false}, {2000, 512, true, false}, {32768, 256, true, false}, {16384, 384, true, false},
       {14000, 640, true, false}, {4096, 1024, true, false}, {1500, 1536, true, false}, {2048, 2048, true, false}, {3000, 2048, false, false},
       {65536, 64, false, false}, {16384, 448, false, false}, {32768, 448, false, false}, {32768, 384, false, false}, {40000, 320, false, false},
-      {16, 1024, true, false}, {16, 4096, true, true}, {256, 2560, true, false}};
+      {16, 1024, true, false}, {16, 4096, true, true}, {256, 2560, true, false}, {100, 3072, true, true}, {256, 4096, true, true},
+      {300, 4096, true, false}, {100, 5120, true, true}, {60, 6144, true, true}, {100, 8192, true, true}};
   for (const auto& c : bf16) tail(false, c.n, c.d, c.one, c.apart);
   const struct { int64_t n; int d; bool one, apart; } fp32[] = {
       {100, 64, true, true}, {300, 128, true, true}, {40, 192, true, true}, {100, 256, true, true}, {300, 192, false, false}, {300, 256, false, false},
       {512, 320, false, false}, {16, 512, false, false}, {100, 448, false, false}, {16, 640, false, false}, {16, 768, false, false},
       {1500, 448, true, false}, {2000, 576, true, false}, {1000, 768, true, false}, {300, 1024, true, true}, {600, 1280, true, false},
-      {1000, 1152, true, false}, {800, 1280, true, false}, {1200, 896, true, false}, {400, 1792, true, false}, {2000, 256, false, false}, {4096, 1024, false, false}};
+      {1000, 1152, true, false}, {800, 1280, true, false}, {1200, 896, true, false}, {400, 1792, true, false}, {800, 960, true, true},
+      {600, 1408, true, true}, {400, 1536, true, true}, {256, 2560, true, true}, {2000, 256, false, false}, {4096, 1024, false, false}};
   for (const auto& c : fp32) tail(true, c.n, c.d, c.one, c.apart);
   // the scratch is sized for the slices of launches of their own, and one counter per tile of both gradients on edge 64
   for (bool f32 : {false, true})

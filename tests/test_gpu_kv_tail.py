@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,d,dtype", [(1, 64, "bf16"), (1025, 64, "bf16"), (16383, 64, "bf16"), (16385, 64, "bf16"), (65, 320, "bf16"),
-                                       (2305, 1088, "bf16"), (1500, 1408, "bf16"), (3, 2112, "bf16"), (1, 64, "f32"),
-                                       (513, 64, "f32"), (129, 192, "f32"), (1025, 704, "f32")])
+                                       (2305, 1088, "bf16"), (1500, 1408, "bf16"), (3, 2112, "bf16"), (97, 3072, "bf16"), (1, 64, "f32"),
+                                       (513, 64, "f32"), (129, 192, "f32"), (1025, 704, "f32"), (577, 960, "f32")])
 def test_one_launch_after_g_xt(n, d, dtype):
     import torch
     cfg = dataclasses.replace(kv.KV_CONFIGS[1].scaled(n=n, d=d), dtype=dtype)
