@@ -279,7 +279,9 @@ LMHEAD_API int lmhead_check(void* ws, void* stream);
  * (0 = logits forward, 1 = dZ recompute, 2 = dH contraction, 3 = dW contraction, 4 = spectral
  * projection, or the whole gate where one kernel computes it, 5 = gate logits, 6 = truncation mask, 7 = low-rank
  * reconstruction; of dynakv_gate_bwd: 8 = mask backward, 9 = g_x~ product, 10 = dx product, 11 = dW and dU, which
- * one launch makes, of shorter streams with dx; a mask that the launch of the logits makes counts as 5; 12 and 13 are not recorded), the summed elapsed milliseconds and the number of launches since the
+ * one launch makes, without the sums behind it, 12 = dW and dU of shorter streams, where that launch makes the sums and db
+ * too, and dx unless 10 was recorded; a mask that the launch of the logits makes counts as 5; 13 is not
+ * recorded), the summed elapsed milliseconds and the number of launches since the
  * last enable call.
  */
 LMHEAD_API int lmhead_timing_enable(int on);

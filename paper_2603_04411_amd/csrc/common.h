@@ -313,8 +313,8 @@ hipError_t static_scratch(float** out);
 // stream.  The pool is fixed-size; launches beyond it are simply not timed.
 // Kinds: 0 logits fwd, 1 dZ recompute, 2 dH, 3 dW, 4 spectral projection, 5 gate logits,
 // 6 truncation mask, 7 low-rank reconstruction; gate backward: 8 mask backward, 9 g_x~ product, 10 dx
-// product, 11 dW and dU, with dx where one launch makes all (12 and 13 were further launches for them, no longer made).  The gate in one kernel is recorded as 4, the
-// mask of few tokens, where their logits make it, with 5.
+// product, 11 dW and dU, 12 the one launch for what follows g_x~ of shorter streams (with dx unless 10 was recorded), 13 none.
+// The gate in one kernel is recorded as 4, the mask of few tokens, where their logits make it, with 5.
 constexpr int kTimingKinds = 14;
 constexpr int kTimingPool = 8192;
 struct TimingState {

@@ -337,10 +337,10 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
   ta.out2 = dU;
   ta.ldo = d;
   ta.accumulate = accum;
+  const KvSums sums{static_cast<const float*>(at(L.dbpart)), L.nblk, ta.part, L.ksplit, d, db, dW, dU, accum};
   {
-    TimedLaunch tl(11, s);
+    TimedLaunch tl(L.tail ? 12 : 11, s);
     if (dense) LM_TRY(launch_kv_dense(x, desc->ldx * L.esz, L.n, d * L.esz, at(L.logits), s));
-    const KvSums sums{static_cast<const float*>(at(L.dbpart)), L.nblk, ta.part, L.ksplit, d, db, dW, dU, accum};
     if (L.tail) {
       if (dx_apart) ga.Nn = 0;
       ta.done = static_cast<int32_t*>(at(L.done));
@@ -348,8 +348,8 @@ int dynakv_gate_bwd(const dynakv_desc* desc, const void* x, const void* U, const
       return LMHEAD_OK;
     }
     LM_TRY(launch_gemm_t(dt, ta, s, 2));
-    LM_TRY(launch_kv_sums(sums, s));
   }
+  LM_TRY(launch_kv_sums(sums, s));
   return LMHEAD_OK;
 }
 

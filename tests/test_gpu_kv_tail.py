@@ -36,3 +36,19 @@ def test_one_launch_after_g_xt(n, d, dtype):
         assert torch.equal(again[0], got[0])
         for a, t in zip(again[1:], got[1:]):
             assert torch.equal(a, t + 0.5)
+
+
+@pytest.mark.parametrize("n,d,kinds", [(700, 704, {12}), (97, 3072, {10, 12}), (16384, 448, {10, 11}), (300, 192, {12})])
+def test_timing_kinds_of_the_launches(n, d, kinds):
+    import paper_2603_04411_amd as L
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d)
+    kp = KvProblem(cfg, kv.kv_inputs(cfg))
+    xt, _, _, _ = kp.gate(cfg.tau, soft=False)
+    g_xhat = to_device(kv.upstream(cfg, with_g_m=False)[0])
+    L.lmhead_timing_enable(True)
+    try:
+        kp.gate_bwd(xt, g_xhat)
+        counts = {kind: L.lmhead_timing_read(kind)[1] for kind in range(14)}
+    finally:
+        L.lmhead_timing_enable(False)
+    assert counts == {kind: int(kind in kinds | {5, 8, 9}) for kind in range(14)}
