@@ -443,7 +443,8 @@ hipError_t launch_index(const IndexArgs& a, hipStream_t s) {
   } else {
     hipLaunchKernelGGL(scan_len_kernel, dim3(1), dim3(1024), 0, s, a.len, a.R, a.T, a.hdr, a.cu_ws, a.cu_out,
                        a.want_split, a.split);
-    hipLaunchKernelGGL((few ? index_kernel<false, 1> : index_kernel<false, kIndexRows>), grid, dim3(256), 0, s, a);
+    static_assert(kIndexFew <= kIndexMaxR, "so many responses are not few slots");
+    hipLaunchKernelGGL((index_kernel<false, kIndexRows>), grid, dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
