@@ -32,12 +32,17 @@ def test_retain_rate(n, d, have):
     assert float((gm - 2 * 0.5 * out[1] / (n * d)).abs().max()) <= 4 * 2.0 ** -24 / (n * d)
 
 
-# slices of the token range: none (d 1088, few tokens), a few, one per workgroup; the most that d = 64 and 128 have, summed by columns,
-# and next to them; accumulated and not
-@pytest.mark.parametrize("n,d", [(40, 1088), (700, 576), (2000, 64), (16700, 64), (8300, 128), (4200, 192)])
-def test_gradient_sums(n, d):
+# slices of the token range, in launches of their own (bf16 from some 16000 tokens on, fp32) and in one with the gradients: none, a few,
+# one per workgroup; the most that d = 64 and 128 have, summed by columns, and next to them; accumulated and not
+GRADIENTS = [(40, 1088, "bf16"), (700, 576, "bf16"), (2000, 64, "bf16"), (16700, 64, "bf16"), (8300, 128, "bf16"), (4200, 192, "bf16"),
+             (16700, 128, "bf16"), (16700, 192, "bf16"), (700, 64, "f32"), (1100, 128, "f32"), (512, 192, "f32"), (300, 256, "f32"),
+             (40, 576, "f32"), (2000, 1088, "f32"), (2000, 1280, "f32")]
+
+
+@pytest.mark.parametrize("n,d,dtype", GRADIENTS)
+def test_gradient_sums(n, d, dtype):
     import torch
-    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d)
+    cfg = kv.KV_CONFIGS[1].scaled(n=n, d=d, dtype=dtype)
     inp = kv.kv_inputs(cfg)
     kp = KvProblem(cfg, inp)
     xt, _, _, _ = kp.gate(cfg.tau, soft=False)
@@ -46,7 +51,8 @@ def test_gradient_sums(n, d):
     o = O.gate_bwd(f(inp["x"]), f(inp["U"]), f(inp["W"]), inp["b"], f(g_xhat), None, order="suffix", store_dtype=cfg.dtype)
     got = kp.gate_bwd(xt, to_device(g_xhat))
     for name, t in zip(("dx", "dU", "dW", "db"), got):
-        assert rel_fro(np64(t), o[name]) <= 1e-2, name
+        # bf16: g_l and g_x~ are rounded to 2^-9; fp32: sums of max(n, d) terms, with the cancellation in the mask's gradient
+        assert rel_fro(np64(t), o[name]) <= (1e-2 if dtype == "bf16" else 1e-4), name
     base = [torch.full_like(t, 0.5) for t in got[1:]]
     again = kp.gate_bwd(xt, to_device(g_xhat), accumulate_into=base)
     assert kp.check() == 0
