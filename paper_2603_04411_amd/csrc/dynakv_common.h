@@ -186,11 +186,14 @@ struct KvGateArgs {
   void* xt;
   int32_t* k;
 };
-// From this many tokens on.  Its workgroups take 64 tokens (128 at d = 512) through everything, 60 us a round, so below
-// a round the separate kernels with their smaller tiles win.  Whole call, us, separate kernels / this one:
-//   d 1024: n 8192 55.6 / 61.2   12000 90.6 / 64.0   16384 99.9 / 73   65536 392 / 248   262144 1334 / 976
-//   d 512:  n 8192 30.4 / 34.6   10000 34.6 / 35.2   16384 50.0 / 38   65536 154 / 82    262144 560 / 303
-// bf16 at 512 and 1024 only: the tile is laid out for a whole token row in LDS next to 256 accumulators a lane, 64 tokens of
+// From this many tokens on.  Its workgroups take 64 tokens (128 at d = 512) through everything, 60 us a round, so with less than
+// half a round the separate kernels with their smaller tiles win.  Whole call, us, separate kernels / this one:
+//   d 1024: n 8192 53.8 / 60.2   9000 69.4 / 60.9   10240 72.1 / 61.9   12000 76.7 / 64.7   16384 89.3 / 71.9   20000 115 / 121
+//           32768 176 / 136   65536 342 / 258   262144 1309 / 1002
+//   d 512:  n 8192 29.4 / 32.7   10000 33.9 / 33.6   12000 35.5 / 35.4   16384 42.0 / 37.4   32768 68.8 / 45.2   65536 132 / 83
+//           262144 539 / 312
+// (20000 x 1024 begins a second round of 57 workgroups.)
+// bf16 at 512 and 1024 only: the tile is laid out for a whole token row in LDS next to 128 accumulators a lane, 64 tokens of
 // 1024 or 128 of 512 components.  A row of 2048 leaves room for 32 tokens, i.e. twice the parameter stream per token, which
 // is the bound; 256 and 768 would take other piece and lane maps, unwritten since no workload has such a d at
 // these lengths, and fp32 is bound by the matrix rate, which the separate kernels come close to (135 of 157 TFLOP/s).

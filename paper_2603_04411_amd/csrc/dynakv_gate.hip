@@ -157,8 +157,8 @@ __global__ __launch_bounds__(64 * kKvGateWaves) void kv_gate_kernel(KvGateArgs a
   load_x(tile * G::TOK);
   for (; tile < ntiles; tile += gridDim.x) {
     const int64_t t0 = tile * G::TOK;
-    // the first fragments are requested here and not under the previous tile's softmax, which needs the registers
-    // (128 of them kept across it made the compiler spill 25, each reload a wait for everything in flight)
+    // the first fragments are requested here and not under the previous tile's softmax, which needs the registers (kept across
+    // it, 64 a lane at d = 1024, some spill, and each reload waits for everything in flight: 1164 us for 262144 tokens instead of 982)
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       wb[0][i] = load_frag(rU, 0, i);

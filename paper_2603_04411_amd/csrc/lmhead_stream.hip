@@ -4,7 +4,7 @@
 // the last round of them is as good as empty.  Here the vocabulary is cut into one range of rows per compute unit, even to 16
 // rows, and a workgroup takes its range through all of d in passes of up to 256 rows (128 from 129 tokens on) as ONE sequence of
 // K-steps: the ring never runs dry, and the next rows are on their way under the epilogue of the last ones.  The softmax statistics
-// of a range stay in registers until its end, one plane per range, a quarter to a ninth of what there was to merge.
+// of a range stay in registers until its end, one plane per range: of 151936 rows 256 to merge instead of 1187 or 2374.
 //  - W goes past the caches (nt): it is read once, and is larger than they are.
 //  - Tall tiles: per byte of W as few bytes of hidden states as fit.  These come from L2 but through the same path
 //    (128 x 128 tiles: 141 us, without their requests 121; 256 x 128: 137).

@@ -138,13 +138,20 @@ inline int logits_edge(bool f32, int64_t V, int64_t n) {
 // one range of rows per compute unit instead of tiles (lmhead_stream.hip).  What is still there of a smaller W from the call before
 // the tiles read sooner, and the ranges, which go past the caches, leave none of it to the dZ of a step.  Calls one after the other on
 // the same W, us, tiles / ranges, 64 (64), 192 (120) and 200 (200) slots (valid); steps are forward, loss and backward:
-//   below: d 2048 V 32000   32/42 40/48 41/48   steps 158/166 190/201 192/204      d 4096 V 16384   41/62 49/66 49/66   187/210 229/242 227/247
-//          d 1024 V 64000   35/37 43/47 43/47         157/158 197/206 199/212      d 512 V 151936   43/44 60/63 59/63   181/188 259/267 268/282
-//          d 2048 V 66000   65/71 85/100 87/101       354/355 468/438 486/461      d 4096 V 33000   69/68 93/117 95/119 349/346 472/453 494/483
-//   above: d 2048 V 80000   97/74 130/106 128/106      465/426 541/489 560/514     d 1024 V 151936  81/68 116/97 115/97 414/388 544/501 543/511
-//          d 2048 V 151936  157/117 229/170 217/171    814/750 928/857 953/893     d 4096 V 50000   120/80 174/130 170/131 573/517 672/596 717/650
-//          d 8192 V 20000   120/117 169/125 164/125    489/474 628/544 635/564     d 64 V 2100000   280/132 402/255 371/257
-//          (fewer rows a range, most of whose tile is empty: d 8192 V 18500 112/116 167/125 167/124)
+//                           call                     step
+//   below:  d 2048 V 32000  32/42   40/48   41/48      158/166 190/201 192/204
+//           d 4096 V 16384  41/62   49/66   49/66      187/210 229/242 227/247
+//           d 1024 V 64000  35/37   43/47   43/47      157/158 197/206 199/212
+//           d 512 V 151936  43/44   60/63   59/63      181/188 259/267 268/282
+//           d 2048 V 66000  65/71   85/100  87/101     354/355 468/438 486/461
+//           d 4096 V 33000  69/68   93/117  95/119     349/346 472/453 494/483
+//   above:  d 2048 V 80000  97/74   130/106 128/106    465/426 541/489 560/514
+//           d 1024 V 151936 81/68   116/97  115/97     414/388 544/501 543/511
+//           d 2048 V 151936 157/117 229/170 217/171    814/750 928/857 953/893
+//           d 4096 V 50000  120/80  174/130 170/131    573/517 672/596 717/650
+//           d 8192 V 20000  120/117 169/125 164/125    489/474 628/544 635/564
+//           d 64 V 2100000  280/132 402/255 371/257
+//           (fewer rows a range, most of whose tile is empty: d 8192 V 18500 112/116 167/125 167/124)
 // (With other work in between, which takes W out of the caches, ranges are the faster ones for the smaller W too: d 2048 V 32000 68/50
 // 85/55 79/55; but not for steps, 205/206 236/235 242/242, which read it twice.)
 constexpr int64_t kStreamSlots = 128 * 8 / 5, kStreamBytes = (int64_t)288 << 20, kStreamRows = 76;
@@ -359,8 +366,9 @@ inline bool kv_few_fits(bool f32, int64_t n, int d) {
   return (n + kFewTok - 1) / kFewTok * (d / kFewCols) <= per_unit * (int64_t)kComputeUnits;
 }
 
-// Tile edge and slices of the parameter gradients' contraction over the tokens, in a launch of their own: as many slices as give one workgroup per compute unit,
-// on the largest edge whose slices then keep 16 K-steps (of 128 bytes; edge 256: 32), else edge 64 with at least 2 each.
+// Tile edge and slices of the parameter gradients' contraction over the tokens, in a launch of their own: as many slices as give one
+// workgroup per compute unit, on the largest edge whose slices then keep 16 K-steps (of 128 bytes; edge 256: 32), else edge 64 with
+// at least 2 each.
 // dW alone / whole backward call, us, bf16 unless said, with the choice in brackets:
 //     n x d           edge 256         edge 128          edge 64          (slices giving 256 workgroups, or the best)
 //     32768 x 1024    [72.6 / 611]     99.6 / 638        208 / 867
@@ -435,10 +443,11 @@ inline KvTail kv_tail(bool f32, int64_t n, int d, const KvTail& own) {
 //    a tile.  16 tokens, d 1024 / 2048 / 4096, apart / within: 52.6 / 49.2, 85.2 / 84.3, 188 / 190; 1 x 8192: 442 / 491.  In fp32 it also
 //    keeps the sums short (300 x 128: error 3.98e-7, within 4.58e-7).
 //  - bf16 tiles that hold five K-steps by themselves (kv_deep_tiles), whose contraction is longer than all the rest:
-//    100 x 3072 145 / 148 / 144   256 x 4096 208 / 212 / 200   100 x 5120 259 / 292 / 260   100 x 8192 499 / 544 / 490; 256 x 2560 140 / 137
+//    100 x 3072 145 / 148 / 144   256 x 4096 208 / 212 / 200   100 x 5120 259 / 292 / 260   100 x 8192 499 / 544 / 490;
+//    not 256 x 2560 140 / 137
 //  - fp32 tiles that would start in a last round of places that they have to themselves: they share compute units there, four to one,
-//    and others idle.  800 x 960 162 / 173 / 160   600 x 1408 216 / 229 / 214   400 x 1536 216 / 226 / 212   256 x 2560 356 / 377 / 354; with a
-//    fuller round 400 x 1792 256 / 240, with more tiles of dx than compute units 1200 x 896 223 / 205, 800 x 1280 291 / 271
+//    and others idle.  800 x 960 162 / 173 / 160   600 x 1408 216 / 229 / 214   400 x 1536 216 / 226 / 212   256 x 2560 356 / 377 / 354;
+//    with a fuller round 400 x 1792 256 / 240, with more tiles of dx than compute units 1200 x 896 223 / 205, 800 x 1280 291 / 271
 inline bool kv_tail_dx_apart(bool f32, int64_t n, int d, const KvTail& t) {
   if (kv_few_fits(f32, n, d)) return f32 || d > 2048;
   if (!f32) return d >= 3072 && kv_deep_tiles(3, kv_tile_edge(false, 3, d, n, d, kComputeUnits), d, n, d, kComputeUnits);
@@ -447,15 +456,17 @@ inline bool kv_tail_dx_apart(bool f32, int64_t n, int d, const KvTail& t) {
 }
 inline int64_t kv_tail_counters(int64_t d) { return 2 * ((d + 63) / 64) * ((d + 63) / 64); }
 
-// Whether the few-token product of the logits makes their mask too (kv_few_kernel), instead of a launch for it.  That launch costs its
+// Whether the few-token product of the logits makes their mask too (kv_few_mask_kernel), instead of a launch for it.  That launch costs its
 // 2.5 us where calls are short enough to wait for each other's launches (20 us of gate and store, less of a gate alone), and next to
 // nothing in a captured graph.  The workgroup that is last has 16 tokens to itself, behind stores that have gone through to memory: 0.2 us
 // for a few short rows, 3 us for many long ones, more with soft outputs to write.  So: where a gate alone is not slower, by tokens x
 // components for each group of 256 components.  Gate alone / with the store, us, launch : same launch, bf16:
-//   16 x 256   14.6 : 11.9  22.6 : 20.2     256 x 512  - : -        22.8 : 20.2     540 x 448  14.3 : 12.7             1000 x 448  14.8 : 16.1
-//   64 x 640   14.5 : 13.3  20.9 : 18.2     64 x 768   13.3 : 13.4  20.9 : 20.7     160 x 768  13.3 : 14.2  20.2 : 18.6  240 x 704  14.3 : 15.2
-//   16 x 1024  15.3 : 15.4  20.4 : 18.8     16 x 896   14.7 : 14.6  20.6 : 18.1     64 x 896   14.9 : 15.4  20.2 : 18.8  128 x 1024 15.5 : 16.7  20.5 : 20.9
-// fp32:  512 x 256 15 : 12.5    64 x 448 15.0 : 14.9  20.8 : 18.4    300 x 448 15.5 : 15.9    16 x 640 17.4 : 17.8  20.9 : 21.4    300 x 768 20.4 : 21.7
+//   16 x 256   14.6 : 11.9  22.6 : 20.2      256 x 512   - : -        22.8 : 20.2     540 x 448  14.3 : 12.7
+//   64 x 640   13.1 : 12.6  20.9 : 18.2      64 x 768    13.3 : 13.3  20.8 : 18.2     16 x 896   14.4 : 14.4  22.7 : 20.1
+//   32 x 1024  15.2 : 15.1  22.1 : 20.0      not  1000 x 448 14.8 : 16.1   240 x 704 14.3 : 15.2   160 x 768 13.3 : 14.2  20.2 : 18.6
+//   64 x 896 14.9 : 15.4  20.2 : 18.8   128 x 1024 15.5 : 16.7  20.5 : 20.9
+// fp32:  300 x 256 14.6 : 12.5  23.1 : 20.3   64 x 448 15.0 : 15.0  22.8 : 20.3   not 300 x 448 15.5 : 15.9   16 x 640 17.4 : 17.8  20.9 : 21.4
+//   300 x 768 20.4 : 21.7
 // with soft outputs (training pair):  300 x 128 fp32 47.3 : 45.0  4096 x 64 43.1 : 40.3  1000 x 256 51.0 : 48.4  600 x 256 fp32 49.2 : 49.8
 //   256 x 512 49.5 : 49.9  128 x 1024 55.6 : 57.7  700 x 512 58.4 : 61.0
 constexpr int kKvFewMask = 1024;
