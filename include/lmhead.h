@@ -131,7 +131,7 @@ LMHEAD_API int lmhead_workspace_region(const lmhead_desc* desc, int32_t npol, in
  *     z_v   = sum_k H[i,k] W[v,k]                 (fp32 accumulation, never stored)
  *     lse_i = log sum_v exp(z_v)                  (online max/sum over vocabulary tiles)
  *     logp_i = z[y_i] - lse_i,   y_i = tok[i]
- *     entropy_i = lse_i - sum_v softmax(z)_v z_v  (optional)
+ *     entropy_i = lse_i - sum_v softmax(z)_v z_v  (optional; a logit of -inf counts for nothing)
  * Also emits the integer indexing of the batch.
  *   H      [N x d], row stride ldH, dtype per desc      (in)
  *   W      [V x d], row stride ldW, row v = output embedding of token v   (in)
