@@ -33,8 +33,8 @@ FUSED_GATE = "kv_gate_kernel (x U, gate logits, softmax, cumulative mask, thresh
 # --backward: one step = dynakv_gate (training outputs off) + dynakv_gate_bwd
 BWD_KINDS = {4: "kv_gemm_kernel<spectral projection>", 5: "kv_gemm_kernel<gate logits> (forward + recompute)",
              6: "kv_mask_kernel", 8: "kv_mask_bwd_kernel", 9: "kv_gemm_kernel<g_x~ = g_l W^T + g_xhat m>",
-             10: "kv_gemm_kernel<dx = g_x~ U^T>", 11: "gemm_t_kernel<dW and dU>",
-             12: "kv_tail_kernel (dW and dU, the sums of their slices, db)"}
+             10: "kv_gemm_kernel<dx = g_x~ U^T>", 11: "gemm_t_kernel<dW and dU>"}
+ONE_LAUNCH = 12   # of shorter streams, in the place of 11, and of 10 where that is not recorded
 
 
 def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
@@ -43,12 +43,14 @@ def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
     # algorithmic bytes per launch: mask backward reads logits (4), x~ and g_xhat (esz each) and writes
     # g_l and g_xhat*m (esz each)
     byts = {6: n * d * 4.0, 8: n * d * (4.0 + 4 * esz)}
-    products = {**dict.fromkeys(BWD_KINDS, 1), 11: 2, 12: 2}
+    products = {**dict.fromkeys(BWD_KINDS, 1), 11: 2}
     names = dict(BWD_KINDS)
-    del names[11 if kern[12][1] else 12]   # shorter streams: what follows g_x~ in one launch
-    if kern[10][1] == 0:                   # dx too
-        del names[10]
-        names[12], products[12] = "kv_tail_kernel (dx, dW and dU, the sums of their slices, db)", 3
+    if kern.get(ONE_LAUNCH, (0.0, 0))[1]:
+        del names[11]
+        names[ONE_LAUNCH], products[ONE_LAUNCH] = "kv_tail_kernel (dW and dU, the sums of their slices, db)", 2
+        if kern[10][1] == 0:
+            del names[10]
+            names[ONE_LAUNCH], products[ONE_LAUNCH] = "kv_tail_kernel (dx, dW and dU, the sums of their slices, db)", 3
     if kern[6][1] == 0 and kern[5][1] > kern[4][1]:   # few tokens: the mask in the launch of the logits
         del names[6]
         names[5] = "kv_few_kernel<gate logits> (forward, with the mask, + recompute)"
@@ -161,7 +163,7 @@ def backward_main(args, cfg, inp, L, desc, params, ws, xt, k) -> int:
         step()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
-    kern = {kind: L.lmhead_timing_read(kind) for kind in BWD_KINDS}
+    kern = {kind: L.lmhead_timing_read(kind) for kind in (*BWD_KINDS, ONE_LAUNCH)}
     L.lmhead_timing_enable(False)
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     log(f"{ms_per_step:.3f} ms/step (gate forward + backward)")

@@ -81,3 +81,18 @@ def test_bench_counts_what_a_launch_does():
     assert set(rows) == set(B.BWD_KINDS) - {6}
     assert all(abs(rows[k]["tflops"] - 2 * flop / 50e-6 / 1e12) < 1e-6 for k in (4, 11))
     assert rows[4]["kernel"] == B.FUSED_GATE
+
+
+def test_bench_names_the_one_launch_of_shorter_streams():
+    import bench_dynakv as B
+    n, d, esz = 4096, 1024, 2
+    flop = 2.0 * n * d * d
+    kern = {kind: (0.5, 10) for kind in (*B.BWD_KINDS, B.ONE_LAUNCH)}
+    kern[11] = (0.0, 0)
+    for with_dx in (False, True):
+        if with_dx:
+            kern[10] = (0.0, 0)
+        rows = {e["kind"]: e for e in B.backward_kinds(kern, n, d, esz, 2500.0)}
+        assert set(rows) == (set(B.BWD_KINDS) | {B.ONE_LAUNCH}) - ({10, 11} if with_dx else {11})
+        assert abs(rows[B.ONE_LAUNCH]["tflops"] - (3 if with_dx else 2) * flop / 50e-6 / 1e12) < 1e-6
+        assert rows[B.ONE_LAUNCH]["kernel"].startswith("kv_tail_kernel (dx" if with_dx else "kv_tail_kernel (dW")
