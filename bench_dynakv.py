@@ -53,7 +53,7 @@ def backward_kinds(kern, n: int, d: int, esz: int, peak: float):
             names[ONE_LAUNCH], products[ONE_LAUNCH] = "kv_tail_kernel (dx, dW and dU, the sums of their slices, db)", 3
     if kern[6][1] == 0 and kern[5][1] > kern[4][1]:   # few tokens: the mask in the launch of the logits
         del names[6]
-        names[5] = "kv_few_kernel<gate logits> (forward, with the mask, + recompute)"
+        names[5] = "kv_few_mask_kernel, kv_few_kernel<gate logits> (forward with the mask, recompute)"
     elif kern[6][1] == 0:            # large streams: the forward's gate is one kernel, gate logits only the recompute
         del names[6]
         names[4], products[4] = FUSED_GATE, 2
